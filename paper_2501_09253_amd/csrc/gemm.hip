@@ -160,6 +160,199 @@ gemm_simple_kernel(GemmArgs a) {
     }
 }
 
+// ---- the same on the fp32 matrix cores ------------------------------------------------------------
+// v_mfma_f32_32x32x2_f32: full fp32 products and sums, 256 flops per clock and CU.  Bound by the matrix pipe: a tile of
+// 32 x 32 per wavefront needs two 16-byte LDS reads per four MFMAs (256 clocks), so nothing of the bf16 kernels'
+// staging effort is called for and small tiles cost little.  A fragment read of 16 bytes serves four MFMAs: lane half h
+// holds k = 8j + 4h + i for MFMA i of step j, the same for both operands.  Tiles are staged through registers (the next
+// step's loads travel while this step is computed) into a double-buffered LDS tile, one barrier per step; LDS rows are
+// padded by 16 bytes (an odd number of 16-byte units: conflict free).  The taps of a convolution run inside a channel
+// chunk, so the nine reads of a pixel's chunk come from the cache.  WK wavefronts share a tile's K range (summed through
+// LDS at the end), which keeps small problems on many CUs.  bf16 operands (the shapes the bf16 matrix kernels do not
+// take) are widened while they are staged.  Measured against the plain kernel above: two 3x3 convolutions, q/k/v and out
+// projection of 7,168 tokens x 320 channels 1,288 -> 440 us together (a convolution 178 us = 74 TFLOP/s); one convolution,
+// q/k/v and out projection of 832 tokens x 64 channels 126 -> 21 us.
+typedef __attribute__((ext_vector_type(16))) float gm_f32x16;
+
+template <typename T> __device__ __forceinline__ float4 ld4_f(const T* p);
+template <> __device__ __forceinline__ float4 ld4_f<float>(const float* p) { return *reinterpret_cast<const float4*>(p); }
+template <> __device__ __forceinline__ float4 ld4_f<uint16_t>(const uint16_t* p) {
+    const uint2 v = *reinterpret_cast<const uint2*>(p);
+    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16),
+                       __uint_as_float(v.y & 0xFFFF0000u));
+}
+
+template <typename T, int BM, int BN, bool GEGLU>
+__global__ void __launch_bounds__(256)
+gemm_f32mma_kernel(GemmArgs a) {
+    constexpr int WM = BM / 32, WN = BN / 32, WK = 4 / (WM * WN);    // wavefronts along M, N and K
+    constexpr int NB = GEGLU ? 2 : 1;                                // B tiles per block (value + gate)
+    constexpr int BK = WK == 4 ? 64 : 32, LD = BK + 4;
+    constexpr int VA = BM * BK / 1024, VB = NB * BN * BK / 1024;     // 16-byte vectors per thread and step
+    constexpr int VPR = BK / 4;                                      // vectors per row
+    constexpr int STAGE = (BM + NB * BN) * LD;
+    static_assert(2 * STAGE >= WK * WM * WN * NB * 1024, "the partial tiles of the K groups reuse the staging buffers");
+    __shared__ __attribute__((aligned(16))) float smem[2 * STAGE];
+    __shared__ int64_t s_aoff[BM];
+    __shared__ int64_t s_tok[BM];
+    __shared__ int s_valid[BM];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int fr = lane & 31, fh = lane >> 5;
+    const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;            // n0: output column (GEGLU: in F space)
+    if (a.tokens_are_rows && a.act.active && m0 >= *a.act.count * a.geom.S) return;
+    if (tid < BM) {
+        const RowInfo r = row_info(a, m0 + tid);
+        s_aoff[tid] = r.a_off;
+        s_tok[tid] = r.out_row;
+        s_valid[tid] = r.valid;
+    }
+    __syncthreads();
+    const int ncols = GEGLU ? a.N / 2 : a.N;
+    // what this thread stages: rows of A and packed weight rows of B, always the same columns of the step
+    const T* pa[VA];
+    const T* pb[VB];
+#pragma unroll
+    for (int v = 0; v < VA; ++v) {
+        const int row = (tid + v * 256) / VPR;
+        pa[v] = s_valid[row] ? (const T*)a.A + s_aoff[row] : nullptr;
+    }
+#pragma unroll
+    for (int v = 0; v < VB; ++v) {
+        const int row = (tid + v * 256) / VPR, h = row / BN;
+        int col = n0 + row - h * BN;
+        const bool ok = col < ncols;
+        if (GEGLU) col = (col / GEGLU_GROUP) * 2 * GEGLU_GROUP + h * GEGLU_GROUP + col % GEGLU_GROUP;
+        pb[v] = ok ? (const T*)a.B + (int64_t)col * a.K : nullptr;
+    }
+    const int kv = (tid % VPR) * 4;                                  // 256 is a multiple of VPR: the same for every v
+    const int tw = a.tap_w ? a.tap_w : 3;
+    const int64_t tap_b = (int64_t)a.N * a.K;
+    const int steps = a.taps * ((a.K + BK - 1) / BK);
+    float4 ra[VA], rb[VB];
+    int tap = 0, k0 = 0;                                             // of the step loaded next
+    auto load = [&]() {
+        const int64_t ao = (a.conv ? ((int64_t)(tap / tw) * a.geom.ppw + (tap % tw)) * a.lda : 0) + k0 + kv;
+        const int64_t bo = tap * tap_b + k0 + kv;
+        const bool in = k0 + kv < a.K;                               // K is a multiple of 4
+#pragma unroll
+        for (int v = 0; v < VA; ++v) ra[v] = in && pa[v] ? ld4_f<T>(pa[v] + ao) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int v = 0; v < VB; ++v) rb[v] = in && pb[v] ? ld4_f<T>(pb[v] + bo) : make_float4(0.f, 0.f, 0.f, 0.f);
+        if (++tap == a.taps) { tap = 0; k0 += BK; }
+    };
+    // two accumulators per tile (even and odd k): shorter chains of dependent MFMAs, shorter sums
+    gm_f32x16 acc[NB][2];
+#pragma unroll
+    for (int h = 0; h < NB; ++h)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[h][0][e] = acc[h][1][e] = 0.f;
+    const int wk = wave % WK, wn = (wave / WK) % WN, wm = wave / (WK * WN);
+    const int a_rd = (wm * 32 + fr) * LD + 4 * fh, b_rd = (BM + wn * 32 + fr) * LD + 4 * fh;
+    load();
+    for (int s = 0; s < steps; ++s) {
+        float* st = smem + (s & 1) * STAGE;
+#pragma unroll
+        for (int v = 0; v < VA; ++v) *reinterpret_cast<float4*>(st + ((tid + v * 256) / VPR) * LD + kv) = ra[v];
+#pragma unroll
+        for (int v = 0; v < VB; ++v) *reinterpret_cast<float4*>(st + (BM + (tid + v * 256) / VPR) * LD + kv) = rb[v];
+        if (s + 1 < steps) load();
+        // one barrier a step: the buffer written above was last read in step s - 2, before the barrier of step s - 1
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < BK / 8 / WK; ++j) {
+            const int k8 = (wk * (BK / 8 / WK) + j) * 8;
+            const float4 av = *reinterpret_cast<const float4*>(st + a_rd + k8);
+#pragma unroll
+            for (int h = 0; h < NB; ++h) {
+                const float4 bv = *reinterpret_cast<const float4*>(st + b_rd + h * BN * LD + k8);
+                acc[h][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x, bv.x, acc[h][0], 0, 0, 0);
+                acc[h][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.y, bv.y, acc[h][1], 0, 0, 0);
+                acc[h][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.z, bv.z, acc[h][0], 0, 0, 0);
+                acc[h][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.w, bv.w, acc[h][1], 0, 0, 0);
+            }
+        }
+    }
+    // element e of a lane: row 8 (e / 4) + 4 fh + e % 4, column fr of the wavefront's 32 x 32 tile.  The K groups of a
+    // tile share its rows out: group wk finishes the elements e / (16 / WK) == wk.
+    constexpr int EW = 16 / WK;
+    float out[NB][EW];
+    if constexpr (WK == 1) {
+#pragma unroll
+        for (int h = 0; h < NB; ++h)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) out[h][e] = acc[h][0][e] + acc[h][1][e];
+    } else {
+        __syncthreads();
+        float* part = smem + (wm * WN + wn) * WK * NB * 1024 + lane;
+#pragma unroll
+        for (int h = 0; h < NB; ++h)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) part[((wk * NB + h) * 16 + e) * 64] = acc[h][0][e] + acc[h][1][e];
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < NB; ++h)
+#pragma unroll
+            for (int e = 0; e < EW; ++e) {
+                float v = 0.f;
+#pragma unroll
+                for (int g = 0; g < WK; ++g) v += part[((g * NB + h) * 16 + wk * EW + e) * 64];
+                out[h][e] = v;
+            }
+    }
+    const int col = n0 + wn * 32 + fr;
+    if (col >= ncols) return;
+    const int pc = GEGLU ? (col / GEGLU_GROUP) * 2 * GEGLU_GROUP + col % GEGLU_GROUP : col;
+    const float b0 = a.bias ? a.bias[pc] : 0.f, b1 = GEGLU && a.bias ? a.bias[pc + GEGLU_GROUP] : 0.f;
+    const int sg = GEGLU ? 0 : col / a.seg_cols;
+    const GemmSeg seg = a.seg[sg];
+    T* op = (T*)seg.ptr + (int64_t)(col - sg * a.seg_cols) * (seg.transposed ? seg.ld : 1);
+    const int64_t o_ld = seg.transposed ? 1 : seg.ld;
+#pragma unroll
+    for (int e = 0; e < EW; ++e) {
+        const int ee = wk * EW + e;
+        const int m = wm * 32 + 8 * (ee >> 2) + 4 * fh + (ee & 3);
+        if (!s_valid[m]) continue;
+        const int64_t tok = s_tok[m];
+        float v = out[0][e] + b0;
+        if (GEGLU) {
+            v *= gelu_f(out[NB - 1][e] + b1);
+        } else {
+            if (a.rowbias) v += a.rowbias[(int64_t)a.row_owner[tok / a.geom.S] * a.N + col];
+            if (a.act_gelu) v = gelu_tanh_f(v);
+            if (a.rowscale) v *= a.rowscale[(int64_t)a.row_owner[tok / a.geom.S] * a.rowscale_ld + col];
+            if (a.res) v += ld_f<T>((const T*)a.res + tok * a.ldr + col);
+            v *= seg.scale;
+        }
+        st_f<T>(op + tok * o_ld, v);
+    }
+}
+
+template <typename T>
+static bool gemm_f32mma(const GemmArgs& a, hipStream_t st) {
+    // 16-byte (bf16: 8-byte) loads of four k
+    if (a.K % 4 != 0 || a.lda % 4 != 0 || ((uintptr_t)a.A | (uintptr_t)a.B) % (4 * sizeof(T)) != 0) return false;
+    const bool geglu = a.epi == EPI_GEGLU;
+    const int ncols = geglu ? a.N / 2 : a.N;
+    // The tile with the least work on the fullest CU (in 32 x 32 tiles per SIMD, 256 CUs); the smaller tiles fetch more
+    // per MFMA and pay the K reduction, so they must win by their share.
+    const int64_t b64 = cdiv(a.M, 64) * cdiv(ncols, 64), b32 = cdiv(a.M, 32) * cdiv(ncols, 32);
+    const int64_t bmn = cdiv(a.M, 64) * cdiv(ncols, 32);
+    const double c64 = (double)cdiv(b64, 256), cmn = 0.5 * 1.05 * cdiv(bmn, 256), c32 = 0.25 * 1.15 * cdiv(b32, 256);
+    const int bm = c32 < c64 && c32 < cmn ? 32 : 64, bn = bm == 64 && c64 <= cmn ? 64 : 32;
+    const dim3 grid((unsigned)cdiv(a.M, bm), (unsigned)cdiv(ncols, bn));
+#define PS_F32MMA(BM_, BN_)                                                            \
+    do {                                                                               \
+        if (geglu) gemm_f32mma_kernel<T, BM_, BN_, true><<<grid, 256, 0, st>>>(a);     \
+        else gemm_f32mma_kernel<T, BM_, BN_, false><<<grid, 256, 0, st>>>(a);          \
+    } while (0)
+    if (bm == 32) PS_F32MMA(32, 32);
+    else if (bn == 32) PS_F32MMA(64, 32);
+    else PS_F32MMA(64, 64);
+#undef PS_F32MMA
+    return true;
+}
+
 // ---- packing kernels -----------------------------------------------------------------------------------
 template <typename T>
 __global__ void pack_conv_kernel(const T* __restrict__ w, T* __restrict__ dst, int32_t Cout, int32_t Cin) {
@@ -278,6 +471,8 @@ int gemm(const GemmArgs& a, int dtype, int mode, hipStream_t st) {
         PS_TRY(gemm_mfma_bf16(a, st, &handled));
         if (handled) return PSERVE_OK;
     }
+    if (mode == 0 && (dtype == PSERVE_BF16 ? gemm_f32mma<uint16_t>(a, st) : gemm_f32mma<float>(a, st)))
+        return check_launch("gemm_f32mma_kernel");
     const bool geglu = a.epi == EPI_GEGLU;
     const int ncols = geglu ? a.N / 2 : a.N;
     dim3 grid((unsigned)cdiv(a.M, 64), (unsigned)cdiv(ncols, 64));
