@@ -86,6 +86,247 @@ attn_simple_kernel(AttnArgs a) {
     }
 }
 
+// ---- the same on the fp32 matrix cores --------------------------------------------------------------
+// For fp32, and for the bf16 shapes the bf16 matrix kernels do not take (widened while they are staged).  A block is 32
+// queries of one (request, head); its four wavefronts take every fourth tile of 32 keys each, with a softmax state of
+// their own, and meet once at the end: many blocks for few queries, no barrier in the loop, and the long and short
+// requests of a batch spread evenly over the CUs.  S^T = K Q^T and O^T = V^T P^T with v_mfma_f32_32x32x2_f32: a lane owns
+// one query column, and its 16 scores are exactly the B operands of the 16 steps of the second product (key 8 (e / 4) +
+// 4 h + e % 4 for lane half h), so the probabilities stay in their registers.  Bound by the matrix pipe (a tile is
+// 2 x D / 2 MFMAs of 64 clocks against ~150 vector instructions of softmax and staging): the next tile's rows travel in
+// registers while the current one, in LDS private to the wavefront, is computed.  Measured against the plain kernel
+// above (5 heads of 64, requests of 4,096 and 3,072 tokens): 62.0 -> 0.42 ms (79 TFLOP/s); 2 heads of 32, 256 and 576 tokens: 136 -> 15 us.
+typedef __attribute__((ext_vector_type(16))) float at_f32x16;
+
+template <typename T> __device__ __forceinline__ float4 at_ld4(const T* p);
+template <> __device__ __forceinline__ float4 at_ld4<float>(const float* p) { return *reinterpret_cast<const float4*>(p); }
+template <> __device__ __forceinline__ float4 at_ld4<uint16_t>(const uint16_t* p) {
+    const uint2 v = *reinterpret_cast<const uint2*>(p);
+    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16),
+                       __uint_as_float(v.y & 0xFFFF0000u));
+}
+
+// D: head dim rounded up to 32, 64 or 128 (channels past d are zero).  VT: V is [C][ldv] instead of [rows][ldv].
+template <typename T, int D, bool VT>
+__global__ void __launch_bounds__(256, D == 128 ? 1 : 2)
+attn_f32mma_kernel(AttnArgs a, int group) {
+    constexpr int KT = 32;                              // keys per tile
+    constexpr int LK = D + 4;                           // LDS row of a key (16-byte fragment reads: odd number of units)
+    constexpr int LV = VT ? KT + 4 : D + 8;             // VT: row of a channel; else row of a key (4 LV = 32 mod 64 banks)
+    constexpr int NV = VT ? D : KT;
+    constexpr int WAVE = KT * LK + NV * LV;             // floats of LDS per wavefront
+    constexpr int NQ = D / 8;                           // 16-byte fragments of a query / key row per lane half
+    constexpr int NL = KT * D / 256;                    // vectors of four per lane and operand of a tile
+    static_assert(WAVE >= 32 * LK + 64, "the partial results reuse the tiles");
+    extern __shared__ __attribute__((aligned(16))) float at_smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int fr = lane & 31, fh = lane >> 5;
+    float* sK = at_smem + wave * WAVE;
+    float* sV = sK + KT * LK;
+
+    // groups of `group` consecutive items (query tiles of one head) are dealt to the XCDs in turn
+    const int nsub = 4 * a.qt;                          // 32-query tiles per tile of the call's tables
+    const int64_t seq = blockIdx.x >> 3;
+    const int64_t it = ((seq / group) * 8 + (blockIdx.x & 7)) * group + seq % group;
+    int s, h, tile;
+    if (!attn_item_at(a, it / nsub, s, h, tile)) return;
+    const int S = a.geom.S;
+    const int rows_s = (a.act_off[s + 1] - a.act_off[s]) * S;
+    const int r0 = (tile * nsub + (int)(it % nsub)) * 32;
+    if (r0 >= rows_s) return;
+    int64_t k0;
+    int nk;
+    if (a.cross_len) { k0 = (int64_t)a.perm[s] * a.cross_ld; nk = a.cross_len; }
+    else { k0 = a.cu_seqlens[s]; nk = a.seq_len ? a.seq_len[s] : a.cu_seqlens[s + 1] - (int)k0; }
+    const int d = a.d, C = a.C;
+    auto token = [&](int r) -> int64_t {                // compact row of the request -> token
+        const int pi = a.act_off[s] + r / S;
+        const int p = a.act.active ? a.act.active[pi] : pi;
+        return (int64_t)p * S + (r - (r / S) * S);
+    };
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 q[NQ];
+    {
+        const T* qp = (const T*)a.Q + token(min(r0 + fr, rows_s - 1)) * C + h * d;
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) q[j] = 8 * j + 4 * fh < d ? at_ld4<T>(qp + 8 * j + 4 * fh) : zero;
+    }
+    const T* Kp = (const T*)a.K + k0 * C + h * d;
+    const T* Vp = VT ? (const T*)a.V + (int64_t)h * d * a.ldv + k0 : (const T*)a.V + k0 * a.ldv + h * d;
+    // staging: vector v of a lane is row (v * 64 + lane) / (D / 4) of the tile; rows past the last key are clamped to it
+    // (their scores are masked, their probabilities zero).  VT: channel row, four keys a vector.
+    constexpr int VR = D / 4, VK = KT / 4;
+    float4 rk[NL], rv[NL];
+    auto load = [&](int t) {
+#pragma unroll
+        for (int v = 0; v < NL; ++v) {
+            const int i = v * 64 + lane, row = i / VR, c = (i % VR) * 4;
+            const int key = min(t * KT + row, nk - 1);
+            rk[v] = c < d ? at_ld4<T>(Kp + (int64_t)key * C + c) : zero;
+            if constexpr (!VT) {
+                rv[v] = c < d ? at_ld4<T>(Vp + (int64_t)key * a.ldv + c) : zero;
+            } else {
+                const int ch = i / VK, kk = t * KT + (i % VK) * 4;
+                const T* vp = Vp + (int64_t)ch * a.ldv;
+                rv[v] = ch < d ? make_float4(ld_f<T>(vp + min(kk, nk - 1)), ld_f<T>(vp + min(kk + 1, nk - 1)),
+                                             ld_f<T>(vp + min(kk + 2, nk - 1)), ld_f<T>(vp + min(kk + 3, nk - 1)))
+                               : zero;
+            }
+        }
+    };
+    float m = -INFINITY, l = 0.f;                       // of the lane's query, over the keys of this wavefront
+    at_f32x16 o[D / 32];
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[dt][e] = 0.f;
+    const int tiles = (nk + KT - 1) / KT;
+    if (wave < tiles) load(wave);
+    for (int t = wave; t < tiles; t += 4) {
+        // LDS of the wavefront alone: its accesses execute in order, only the compiler has to keep that order
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int v = 0; v < NL; ++v) {
+            const int i = v * 64 + lane;
+            *reinterpret_cast<float4*>(sK + (i / VR) * LK + (i % VR) * 4) = rk[v];
+            if constexpr (VT) *reinterpret_cast<float4*>(sV + (i / VK) * LV + (i % VK) * 4) = rv[v];
+            else *reinterpret_cast<float4*>(sV + (i / VR) * LV + (i % VR) * 4) = rv[v];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (t + 4 < tiles) load(t + 4);
+        at_f32x16 sc[2];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sc[0][e] = sc[1][e] = 0.f;
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) {
+            const float4 kf = *reinterpret_cast<const float4*>(sK + fr * LK + 8 * j + 4 * fh);
+            sc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.x, q[j].x, sc[0], 0, 0, 0);
+            sc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.y, q[j].y, sc[1], 0, 0, 0);
+            sc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.z, q[j].z, sc[0], 0, 0, 0);
+            sc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.w, q[j].w, sc[1], 0, 0, 0);
+        }
+        float p[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) p[e] = sc[0][e] + sc[1][e];
+        if ((t + 1) * KT > nk) {                        // ragged last tile
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                if (t * KT + 8 * (e >> 2) + 4 * fh + (e & 3) >= nk) p[e] = -INFINITY;
+        }
+        float mn = m;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) mn = fmaxf(mn, p[e]);
+        mn = fmaxf(mn, __shfl_xor(mn, 32, 64));
+        const float corr = exp2f(m - mn);
+        float sum = 0.f;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            p[e] = exp2f(p[e] - mn);
+            sum += p[e];
+        }
+        l = l * corr + sum;
+        m = mn;
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) o[dt][e] *= corr;
+        }
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            if constexpr (VT) {
+                float4 vf[D / 32];
+#pragma unroll
+                for (int dt = 0; dt < D / 32; ++dt)
+                    vf[dt] = *reinterpret_cast<const float4*>(sV + (32 * dt + fr) * LV + 8 * g + 4 * fh);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int dt = 0; dt < D / 32; ++dt)
+                        o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(i == 0 ? vf[dt].x : i == 1 ? vf[dt].y : i == 2 ? vf[dt].z : vf[dt].w,
+                                                                     p[4 * g + i], o[dt], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int dt = 0; dt < D / 32; ++dt)
+                        o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(sV[(8 * g + 4 * fh + i) * LV + 32 * dt + fr], p[4 * g + i],
+                                                                     o[dt], 0, 0, 0);
+            }
+        }
+    }
+    l += __shfl_xor(l, 32, 64);
+    // ---- the four wavefronts' results: common maximum, then the sums in a fixed order
+    __syncthreads();                                    // all tiles of LDS are free
+    float* sO = sK;                                     // [32 queries][LK], then the row sums and maxima
+    float* sL = sK + 32 * LK;
+    if (fh == 0) { sL[fr] = m; sL[32 + fr] = l; }
+    __syncthreads();
+    float mall = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) mall = fmaxf(mall, at_smem[w * WAVE + 32 * LK + fr]);
+    const float f = m == -INFINITY ? 0.f : exp2f(m - mall);
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<float4*>(sO + fr * LK + 32 * dt + 8 * g + 4 * fh) =
+                make_float4(o[dt][4 * g] * f, o[dt][4 * g + 1] * f, o[dt][4 * g + 2] * f, o[dt][4 * g + 3] * f);
+    __syncthreads();
+    const int qr = tid >> 3;                            // eight threads per query
+    if (r0 + qr >= rows_s) return;
+    float mq = -INFINITY, lq = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) mq = fmaxf(mq, at_smem[w * WAVE + 32 * LK + qr]);
+    float fw[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const float mw = at_smem[w * WAVE + 32 * LK + qr];
+        fw[w] = mw == -INFINITY ? 0.f : exp2f(mw - mq);
+        lq += at_smem[w * WAVE + 32 * LK + 32 + qr] * fw[w];
+    }
+    const float inv = 1.f / lq;
+    T* op = (T*)a.O + token(r0 + qr) * C + h * d;
+#pragma unroll
+    for (int c = (tid & 7) * 4; c < D; c += 32) {
+        if (c >= d) break;
+        float4 v = zero;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float4 u = *reinterpret_cast<const float4*>(at_smem + w * WAVE + qr * LK + c);
+            v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+        }
+        if constexpr (sizeof(T) == 2)
+            *reinterpret_cast<uint2*>(op + c) = make_uint2(pack_bf16x2(v.x * inv, v.y * inv), pack_bf16x2(v.z * inv, v.w * inv));
+        else
+            *reinterpret_cast<float4*>(op + c) = make_float4(v.x * inv, v.y * inv, v.z * inv, v.w * inv);
+    }
+}
+
+template <typename T, int D, bool VT>
+static int attn_f32mma_launch(const AttnArgs& a, hipStream_t st) {
+    const int64_t items = (int64_t)a.max_tiles * 4 * a.qt * a.heads;
+    // enough groups that every XCD gets its share of the long items; long ones keep a head's keys in one L2
+    const int group = (int)std::max<int64_t>(1, std::min<int64_t>(64, items / 64));
+    const unsigned grid = (unsigned)(8 * group * cdiv(items, 8 * group));
+    constexpr int lds = 4 * (32 * (D + 4) + (VT ? D * 36 : 32 * (D + 8))) * 4;
+    PS_SET_LDS_ONCE((attn_f32mma_kernel<T, D, VT>), lds);
+    attn_f32mma_kernel<T, D, VT><<<grid, 256, lds, st>>>(a, group);
+    return check_launch("attn_f32mma_kernel");
+}
+
+template <typename T>
+static int attn_f32mma(const AttnArgs& a, hipStream_t st) {
+    const int D = a.d <= 32 ? 32 : a.d <= 64 ? 64 : 128;
+    if constexpr (sizeof(T) == 2)                       // the transposed layout goes with bf16 and 64 channels a head
+        if (a.v_transposed) return attn_f32mma_launch<T, 64, true>(a, st);
+    if (D == 32) return attn_f32mma_launch<T, 32, false>(a, st);
+    if (D == 64) return attn_f32mma_launch<T, 64, false>(a, st);
+    return attn_f32mma_launch<T, 128, false>(a, st);
+}
+
 int attention_mfma_bf16(const AttnArgs& a, hipStream_t st, bool* handled);     // attn_mfma.hip
 
 int attention(const AttnArgs& a, int dtype, int mode, hipStream_t st) {
@@ -95,6 +336,11 @@ int attention(const AttnArgs& a, int dtype, int mode, hipStream_t st) {
         PS_TRY(attention_mfma_bf16(a, st, &handled));
         if (handled) return PSERVE_OK;
     }
+    // four channels a load (the queries, keys and values are the library's own buffers: rows start 16-byte aligned when C
+    // and d are multiples of four)
+    if (mode == 0 && a.d % 4 == 0 && a.C % 4 == 0 && (a.v_transposed ? a.d == 64 && dtype == PSERVE_BF16 : a.ldv % 4 == 0) &&
+        a.tile_off && a.act_off)
+        return dtype == PSERVE_BF16 ? attn_f32mma<uint16_t>(a, st) : attn_f32mma<float>(a, st);
     const int64_t items = (int64_t)a.geom.P * a.geom.S * a.heads;
     const unsigned grid = (unsigned)cdiv(items, 4);
 #define PS_ATTN(TT, DM) attn_simple_kernel<TT, DM><<<grid, 256, 0, st>>>(a)

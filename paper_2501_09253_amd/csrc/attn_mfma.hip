@@ -63,31 +63,14 @@ __device__ __forceinline__ int kperm(int r) { return (r & ~12) | ((r & 4) << 1) 
 extern __shared__ __attribute__((aligned(16))) uint8_t att_smem[];
 
 // Work item of a block: (request slot, head, query tile of that request).  A block's run time goes with the number of
-// keys of its request, so the items are ordered longest first: request slots from the last (the plan sorts requests by
-// size, largest last) to the first, head-major inside a slot, so that consecutive items are consecutive query tiles of
-// one head.  Groups of ATT_GROUP consecutive items are dealt to the XCDs in turn (block b runs on XCD b mod 8 and an XCD
-// starts its blocks in order): the blocks resident on an XCD stream the K / V^T tiles of the same head through that
-// XCD's L2, every XCD gets the same share of the long items, and the short ones fill the last round.
+// keys of its request, so the items run longest first (attn_item_at).  Groups of ATT_GROUP consecutive items are dealt to
+// the XCDs in turn (block b runs on XCD b mod 8 and an XCD starts its blocks in order): the blocks resident on an XCD
+// stream the K / V^T tiles of the same head through that XCD's L2, every XCD gets the same share of the long items, and
+// the short ones fill the last round.
 constexpr int ATT_GROUP = 64;
 __device__ __forceinline__ bool attn_item(const AttnArgs& a, int& s, int& head, int& tile_in_s) {
-    const int total_tiles = a.tile_off[a.n];
-    const int64_t items = (int64_t)total_tiles * a.heads;
     const int64_t seq = blockIdx.x >> 3;
-    const int64_t k = ((seq / ATT_GROUP) * 8 + (blockIdx.x & 7)) * ATT_GROUP + seq % ATT_GROUP;
-    if (k >= items) return false;
-    const int64_t q = items - 1 - k;                 // position in ascending slot order
-    const int qt = (int)(q / a.heads);
-    int lo = 0, hi = a.n;                            // largest s with tile_off[s] <= qt
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (a.tile_off[mid] <= qt) lo = mid; else hi = mid;
-    }
-    s = lo;
-    const int tiles_s = a.tile_off[s + 1] - a.tile_off[s];
-    const int r = tiles_s * a.heads - 1 - (int)(q - (int64_t)a.tile_off[s] * a.heads);
-    head = r / tiles_s;
-    tile_in_s = r - head * tiles_s;
-    return true;
+    return attn_item_at(a, ((seq / ATT_GROUP) * 8 + (blockIdx.x & 7)) * ATT_GROUP + seq % ATT_GROUP, s, head, tile_in_s);
 }
 
 template <int ATT_QT>

@@ -158,6 +158,26 @@ struct AttnArgs {
     int32_t qt;                // 1 or 2: the tables were built for query tiles of 128 * qt rows
     int32_t max_rows;          // host upper bound of the query rows of one request (its tokens)
 };
+// Item k of the work list of a call, longest first: request slots from the last (the plan sorts requests by size,
+// largest last) to the first, head-major inside a slot, so that consecutive items are consecutive query tiles of one head.
+__device__ __forceinline__ bool attn_item_at(const AttnArgs& a, int64_t k, int& s, int& head, int& tile_in_s) {
+    const int total_tiles = a.tile_off[a.n];
+    const int64_t items = (int64_t)total_tiles * a.heads;
+    if (k >= items) return false;
+    const int64_t q = items - 1 - k;                 // position in ascending slot order
+    const int qt = (int)(q / a.heads);
+    int lo = 0, hi = a.n;                            // largest s with tile_off[s] <= qt
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (a.tile_off[mid] <= qt) lo = mid; else hi = mid;
+    }
+    s = lo;
+    const int tiles_s = a.tile_off[s + 1] - a.tile_off[s];
+    const int r = tiles_s * a.heads - 1 - (int)(q - (int64_t)a.tile_off[s] * a.heads);
+    head = r / tiles_s;
+    tile_in_s = r - head * tiles_s;
+    return true;
+}
 int attention_tiles(const int32_t* request_offset, const uint8_t* mask, int32_t n, int32_t S, int32_t qt, int32_t* act_off,
                     int32_t* tile_off, hipStream_t st);
 int attention_max_tiles(const pserve_plan_t* plan, int32_t qt);

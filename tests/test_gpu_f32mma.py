@@ -34,3 +34,31 @@ def _check(cfg):
 def test_gemm_and_convolution_tiles(res, patch, C, dtype):
     _check(wl.custom_config(res, patch, C=C, G=8, heads=1, stages=("RES2T", "LFFN"), dtype=dtype, seed=7, temb_dim=36,
                             ffn_mult=8 if C % 16 else 4))
+
+
+# head widths that fill, straddle and pad the 32 / 64 / 128 channel tiles; keys from one to several rounds of four tiles
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [4, 20, 32, 36, 64, 100, 128])
+@pytest.mark.parametrize("res,patch,L", [([(1, 3), (6, 6)], (1, 3), 1), ([(10, 10), (20, 10), (10, 30)], (10, 10), 33),
+                                         ([(12, 12)], (6, 6), 130)])
+def test_attention_tiles(res, patch, L, d, dtype):
+    _check(wl.custom_config(res, patch, C=2 * d, G=2, heads=2, stages=("LSATTN", "LXATTN"), dtype=dtype, ctx_len=L,
+                            ctx_dim=24, seed=9))
+
+
+# cached patches: compacted query rows, all keys (patches of 36 tokens: bf16 takes this kernel with transposed values)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_attention_with_reuse(dtype):
+    _check(wl.custom_config([(24, 18), (6, 12)], (6, 6), C=128, G=8, heads=2, stages=("RES2", "SATTN"), dtype=dtype,
+                            reuse_p=0.5, seed=13))
+
+
+def test_attention_logits_far_apart():
+    """fp32 logits over a range of a few hundred (queries scaled up): the running maximum moves in every tile."""
+    cfg = wl.custom_config([(16, 24), (8, 8)], (8, 8), C=64, G=8, heads=2, stages=("LSATTN",), seed=17)
+    w = wl.make_workload(cfg)
+    w.params[0]["wq"] *= 40.0
+    got = GpuRun(w).forward_images()
+    ref, _ = ob.forward_batch(w.images, cfg.stages, w.params, G=cfg.G, heads=cfg.heads, eps=cfg.eps)
+    # a logit of 300 is known to 300 * 2^-23 * sqrt(32 + 64) = 3.5e-4, and so is its exponential
+    assert rel_err(got, ref) < 1e-3
