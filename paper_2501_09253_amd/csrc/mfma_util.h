@@ -1,0 +1,44 @@
+// Types and small device helpers shared by the bf16 matrix-core kernels.
+#pragma once
+
+#include "kernels.h"
+
+namespace pserve {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+// GELU(v) = v/2 (1 + erf(v/sqrt 2)) with erf from the 5-term rational-exponential form (Abramowitz & Stegun
+// 7.1.26, |error| < 1.5e-7): far below the bf16 resolution of the output and several times cheaper than erff.
+// With u = |v|, t = 1/(1 + p u/sqrt 2) and y = (a1 t + .. + a5 t^5)/2 * exp(-u^2/2):  erf(u/sqrt 2) = 1 - 2y, so
+// GELU(v) = v (1 - y) for v >= 0 and v y for v < 0.  Hardware reciprocal and exp2 (1 ulp each); 15 instructions.
+__device__ __forceinline__ float gelu_erf(float v) {
+    const float u = fabsf(v);
+    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752f, u, 1.f));
+    float p = fmaf(0.5f * 1.061405429f, t, 0.5f * -1.453152027f);
+    p = fmaf(p, t, 0.5f * 1.421413741f);
+    p = fmaf(p, t, 0.5f * -0.284496736f);
+    p = fmaf(p, t, 0.5f * 0.254829592f);
+    const float y = p * t * __builtin_amdgcn_exp2f(u * u * (-0.5f * 1.4426950408889634f));
+    const float r = v * y;
+    return v >= 0.f ? v - r : r;
+}
+
+// GELU, tanh form: v/2 (1 + tanh(u)) = v / (1 + exp(-2u)), u = sqrt(2/pi) (v + 0.044715 v^3); hardware exp2 and reciprocal
+__device__ __forceinline__ float gelu_tanh(float v) {
+    const float u2 = v * fmaf(0.044715f * v, v, 1.f) * (-2.f * 0.7978845608028654f * 1.4426950408889634f);   // -2u log2(e)
+    return v * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(u2));
+}
+
+// value of lane l ^ 32 (v_permlane32_swap: upper half of the first operand <-> lower half of the second)
+__device__ __forceinline__ float other_half_f(float v) {
+    const uint32_t u = __float_as_uint(v);
+    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __uint_as_float((threadIdx.x & 32) ? r[0] : r[1]);
+}
+
+typedef __attribute__((address_space(3))) void lds_void;
+
+}  // namespace pserve

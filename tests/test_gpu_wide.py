@@ -1,0 +1,52 @@
+"""GPU: linear layers on 256- and 320-row tiles (sizes of at least 128 tiles), at ragged ends of rows and columns, with
+transposed segments, gates, masks and padded row groups, against the plain reference kernels of the library.
+
+Both sides round to bf16 at the same places, so they differ by single roundings (2^-8 of a value) and what the following
+layers make of them: 1e-2 of the largest value, half the bar against the oracle."""
+import numpy as np
+import pytest
+
+import paper_2501_09253_amd as ps
+import workloads as wl
+
+torch = pytest.importorskip("torch")
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(), reason="no GPU")]
+
+from harness import GpuRun, rel_err                                  # noqa: E402
+
+
+def _forward(w, mode):
+    ps.set_kernel_mode(mode)
+    try:
+        run = GpuRun(w)
+        if w.cache is not None:
+            run.load_cache()
+        return run.forward_images(reuse=w.reuse)
+    finally:
+        ps.set_kernel_mode(0)
+
+
+CASES = {
+    # q/k/v with transposed values, tokens of a run of eight across patches of 36, last row tile ragged
+    "qkv_640": dict(res=[(12, 18)] * 19 + [(6, 6)], patch=(6, 6), C=640, stages=("LSATTN",)),
+    # 704 = 11 x 64: only the 320-row tile's wavefronts (64 columns) stay inside a segment; last column tile padded
+    "qkv_704": dict(res=[(16, 16)] * 18 + [(8, 24)], patch=(8, 8), C=704, stages=("LSATTN",)),
+    "geglu": dict(res=[(20, 20)] * 4 + [(20, 15)], patch=(20, 5), C=640, stages=("LFFN",)),
+    # gate and residual, tanh GELU: rows of many requests in a tile
+    "gate": dict(res=[(16, 16)] * 42 + [(12, 20)], patch=(4, 4), C=768, stages=("AMLP",), temb_dim=64),
+    # out projection with residual, text keys / values in row groups of 77 padded to 80
+    "cross": dict(res=[(12, 12)] * 46, patch=(4, 4), C=1280, stages=("LXATTN",), ctx_len=77, ctx_dim=128),
+    # computed patches only
+    "masked": dict(res=[(32, 48)] * 5 + [(16, 16)], patch=(16, 16), C=640, stages=("SATTN",), reuse_p=0.3),
+    "masked_res2": dict(res=[(32, 32)] * 6, patch=(8, 8), C=640, stages=("RES2", "SATTN"), reuse_p=0.4),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_wide_tiles(name):
+    c = dict(CASES[name])
+    C = c.pop("C")
+    cfg = wl.custom_config(c.pop("res"), c.pop("patch"), C=C, G=32, heads=C // 64, stages=c.pop("stages"), dtype="bf16", seed=51, **c)
+    w = wl.make_workload(cfg)
+    err = rel_err(_forward(w, 0), _forward(w, 1))
+    assert np.isfinite(err) and err < 1e-2, err
