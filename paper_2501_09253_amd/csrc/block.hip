@@ -293,6 +293,8 @@ struct pserve_cache_s {
     void* apad = nullptr;                     // [P][ph+2][pw+2][C]
     float* partial = nullptr;
     float* scale_shift = nullptr;
+    float* split_ws = nullptr;                // partial sums of convolutions with few tiles (main stream only)
+    size_t split_ws_bytes = 0;
     // per-channel moments of the block input left behind by pserve_split_stats: [P][in_nch][C][2]; in_stats_x = the x
     // they were taken from (the next forward call on that x uses them once instead of a statistics pass)
     float* in_partial = nullptr;
@@ -612,6 +614,11 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
     const bool sattn = any_stage(d, is_sattn), xattn = any_stage(d, is_xattn);
     const bool ffn = any_stage(d, is_ffn) || has_stage(d, PSERVE_AMLP) || joint;
     const bool gn_sattn = has_stage(d, PSERVE_SATTN);
+    if (conv) {
+        PatchGeom g{plan->P, plan->S, plan->ph, plan->pw, plan->pw + 2, (plan->ph + 2) * (plan->pw + 2)};
+        c->split_ws_bytes = conv_split_bytes(g, (int32_t)plan->T, d.C, d.C, d.dtype, g_kernel_mode == 1 ? 1 : 0);
+        if (c->split_ws_bytes) PS_TRY(c->pool.alloc((void**)&c->split_ws, c->split_ws_bytes));
+    }
     if (conv) PS_TRY(c->pool.alloc(&c->apad, (size_t)plan->P * (plan->ph + 2) * (plan->pw + 2) * d.C * es));
     if (conv || gn_sattn) {
         PS_TRY(c->pool.alloc_t(&c->partial, (size_t)plan->P * std::max<int64_t>(c->nsplit, plan->S / 64) * d.G * 2));
@@ -926,6 +933,7 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         }
         GemmArgs g = base_gemm(cache->apad, C, C, C, w.w[ci], w.b[ci]);
         g.conv = 1; g.taps = 9; g.res = res; g.ldr = C;
+        g.split_ws = cache->split_ws; g.split_ws_bytes = cache->split_ws_bytes;
         g.rowbias = rowbias; g.row_owner = owner;
         g.seg[0].ptr = out; g.seg[0].ld = C;
         if (stats_next && !reuse_mask) {

@@ -571,6 +571,7 @@ struct ConvTile {
     // ceil(2^32 / d) for d = seg_pix, pw + 2, seg_tokens, pw: x / d == __umulhi(x, m) for the small x of the set-up
     // (x * d < 2^32; a true integer division is ~40 instructions, and 28 of them sat in front of the first halo load)
     uint32_t m_seg_pix, m_hw, m_seg_tokens, m_pw;
+    int32_t splits;                                 // blocks that share a tile's channel chunks (1: none)
 };
 __device__ __forceinline__ int div_small(int x, uint32_t m, int d) { return d == 1 ? x : (int)__umulhi((uint32_t)x, m); }
 
@@ -579,7 +580,9 @@ __device__ __forceinline__ int div_small(int x, uint32_t m, int d) { return d ==
 // KS = 2: eight wavefronts, two per SIMD.  Wavefronts w and w + 4 own the same output rows and split every 64-wide
 // K step (sub-steps 0, 1 / 2, 3); the first four fetch the weights, the last four the halo; the partial sums meet in
 // LDS before the epilogue, which the first four run.
-template <int BM, int BN, int WGM, int WGN, int APIX, int NSB, int KS>
+// SPLIT: the tile's channel chunks are shared by ct.splits blocks, which leave fp32 partial sums behind (compiled apart: the
+// few values it keeps across the loop cost the other form 5 %).
+template <int BM, int BN, int WGM, int WGN, int APIX, int NSB, int KS, bool SPLIT>
 __global__ void __launch_bounds__(256 * KS)
 conv_mfma_kernel(GemmArgs a, ConvTile ct) {
     constexpr int BK = 64, CH = 8;
@@ -603,9 +606,17 @@ conv_mfma_kernel(GemmArgs a, ConvTile ct) {
     // the same residue mod 8 and consecutive slots: they run on one XCD back to back and share the A tile in its L2
     const int n_tiles = a.N / BN, m_tiles = (a.M + BM - 1) / BM;
     const int slot = blockIdx.x >> 3;
-    const int m_tile = (slot / n_tiles) * 8 + (blockIdx.x & 7);
+    int m_tile = (slot / n_tiles) * 8 + (blockIdx.x & 7), n_tile = slot % n_tiles, part = 0;
+    if constexpr (SPLIT) {
+        // shared tiles: an XCD takes all M tiles of a (column tile, share of the chunks), whose weights it then fetches once
+        const int unit = (slot / m_tiles) * 8 + (blockIdx.x & 7);
+        if (unit >= n_tiles * ct.splits) return;
+        m_tile = slot % m_tiles;
+        n_tile = unit % n_tiles;
+        part = unit / n_tiles;
+    }
     if (m_tile >= m_tiles) return;
-    const int m0 = m_tile * BM, n0 = (slot % n_tiles) * BN;
+    const int m0 = m_tile * BM, n0 = n_tile * BN;
     if (a.act.active && m0 >= *a.act.count * a.geom.S) return;
     const int S = a.geom.S, pw = a.geom.pw, hw = pw + 2;
 
@@ -634,12 +645,14 @@ conv_mfma_kernel(GemmArgs a, ConvTile ct) {
     const int b_lane = (int)(((int64_t)(n0 + lr) * a.K + gc * 8) * 2);   // byte offset of this lane's first weight row
     const int64_t b_row32 = (int64_t)32 * a.K;
     const int64_t b_tap_stride = (int64_t)a.N * a.K;
-    const int kchunks = a.K / BK;
+    // first channel chunk of this block, and their number
+    const int kbase = SPLIT ? a.K / BK * part / ct.splits : 0;
+    const int kchunks = SPLIT ? a.K / BK * (part + 1) / ct.splits - kbase : a.K / BK;
     int itap = 0, ikc = 0;                          // (tap, chunk) of the next weight stage to issue; clamps at the last step
 #pragma unroll
     for (int t = 0; t < NSB; ++t) {
         u32x4* dB = sB + t * BSTAGE + wave * 64;
-        const int64_t off = itap * b_tap_stride + ikc * BK;
+        const int64_t off = itap * b_tap_stride + (kbase + ikc) * BK;
         if (pro_b) {
 #pragma unroll
             for (int i = 0; i < B_LD; ++i) PS_LOAD_B(dB, off, i);
@@ -682,7 +695,7 @@ conv_mfma_kernel(GemmArgs a, ConvTile ct) {
     if (pro_a) {                                    // halo of chunk 0: in flight during the rest of the set-up
         u32x4* dA = sA + wave * 64;
 #pragma unroll
-        for (int i = 0; i < A_LD; ++i) PS_LOAD_A(dA, 0, i);
+        for (int i = 0; i < A_LD; ++i) PS_LOAD_A(dA, kbase * BK, i);
     }
     f32x16 acc[TM][TN];
 #pragma unroll
@@ -766,7 +779,7 @@ conv_mfma_kernel(GemmArgs a, ConvTile ct) {
             const u32x4* curA = sA + (kc & 1) * ASTAGE;
             const int nkc_a = kc + 1 < kchunks ? kc + 1 : kc;   // halo chunk fetched during tap 0 (last: itself, never read)
             u32x4* dA = sA + ((kc & 1) ^ 1) * ASTAGE + wave * 64;
-            const int a_off = nkc_a * BK;
+            const int a_off = (kbase + nkc_a) * BK;
 #pragma unroll 1
             for (int tap = 0; tap < 9; ++tap) {
                 const u32x4* curB = sB + bst * BSTAGE;
@@ -778,7 +791,7 @@ conv_mfma_kernel(GemmArgs a, ConvTile ct) {
                 int nfa_cur[TM], nfa_sw[TM];
 #pragma unroll
                 for (int i = 0; i < TM; ++i) { nfa_cur[i] = fa_slot[i] + nty * hw + ntx; nfa_sw[i] = (nfa_cur[i] >> 1) & 7; }
-                const int64_t b_off = itap * b_tap_stride + ikc * BK;
+                const int64_t b_off = itap * b_tap_stride + (kbase + ikc) * BK;
                 if (!(itap == 8 && ikc == kchunks - 1)) { if (++itap == 9) { itap = 0; ++ikc; } }
                 u32x4* dB = sB + bst * BSTAGE + wave * 64;
 #pragma unroll
@@ -893,18 +906,169 @@ conv_mfma_kernel(GemmArgs a, ConvTile ct) {
         }
         if (kg == 1) return;
     }
+    if constexpr (SPLIT) {
+        // fp32 partial sums [share][row of the tile grid][N]: 128 contiguous bytes per row and store
+        float* dst = a.split_ws + ((int64_t)part * (m_tiles * BM) + m0 + wm * WM + 4 * fh) * a.N + n0 + wn * WN + fr;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                float* row = dst + (int64_t)(i * 32 + 8 * (e >> 2) + (e & 3)) * a.N;
+#pragma unroll
+                for (int j = 0; j < TN; ++j) row[j * 32] = acc[i][j][e];
+            }
+        return;
+    }
     // the launch conditions of these kernels rule the other paths out (conv_select)
     gemm_epilogue<BM, BN, false, WGM, WGN, true, 0>(a, acc, smem, s_tok, n0, bias_t);
 }
 
+// Second half of a convolution whose tiles were shared: sums the partial tiles in a fixed order, adds the bias (and the
+// request's), leaves the next norm's moments behind (column sums of 64 rows, exact two-pass form) and adds the residual.
+// A block is 64 rows x W columns (whole groups of the norm): 16 row lanes x W / 8 column vectors, four rows a thread.
+// Memory bound: (4 x splits + 2 (+ 2 with a residual)) bytes per output.
+constexpr int SPLIT_RL = 16;
+__global__ void __launch_bounds__(256)
+split_reduce_kernel(GemmArgs a, int splits, int m_pad, int W) {
+    const int cvs = W / 8, tid = threadIdx.x, cv = tid % cvs, rl = tid / cvs;
+    const int n0 = blockIdx.y * W, col = n0 + cv * 8, m0 = blockIdx.x * 64;
+    __shared__ float s_part[SPLIT_RL][128];
+    __shared__ float s_grp[64];
+    const int cnt = a.act.active ? *a.act.count * a.geom.S : a.M;
+    if (m0 >= cnt) return;
+    const bool in = col < a.N;                      // (the last slab may be narrower; the threads stay for the barriers)
+    const int colc = in ? col : 0;
+    float v[4][8];
+    int64_t tok[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int row = m0 + rl + SPLIT_RL * r;
+        tok[r] = -1;
+        if (row < cnt) {
+            tok[r] = row;
+            if (a.act.active) { const int pi = row / a.geom.S; tok[r] = (int64_t)a.act.active[pi] * a.geom.S + (row - pi * a.geom.S); }
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[r][q] = 0.f;
+    }
+    const float* src = a.split_ws + (int64_t)(m0 + rl) * a.N + colc;     // rows up to the next multiple of 64 exist in the scratch
+    for (int z = 0; z < splits; ++z) {
+        f32x4 lo[4], hi[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float* p = src + ((int64_t)z * m_pad + SPLIT_RL * r) * a.N;
+            lo[r] = *reinterpret_cast<const f32x4*>(p);
+            hi[r] = *reinterpret_cast<const f32x4*>(p + 4);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) { v[r][q] += lo[r][q]; v[r][4 + q] += hi[r][q]; }
+    }
+    float bias[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) bias[q] = a.bias ? a.bias[colc + q] : 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const float* rb = a.rowbias && tok[r] >= 0 ? a.rowbias + (int64_t)a.row_owner[tok[r] / a.geom.S] * a.N + colc : nullptr;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[r][q] += bias[q] + (rb ? rb[q] : 0.f);
+    }
+    if (a.stats) {                                  // all 64 rows exist and lie in one patch (gemm_emits_stats)
+        const int cg = a.N / a.stats_G, groups = W / cg;
+        float mean[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) mean[q] = 0.f;
+#pragma unroll 1
+        for (int pass = 0; pass < 2; ++pass) {      // sums, then squared deviations from the group's mean
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                float s = 0.f;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) { const float d = v[r][q] - mean[q]; s += pass ? d * d : d; }
+                s_part[rl][cv * 8 + q] = s;
+            }
+            __syncthreads();
+            if (tid < W) {                          // column sums over the row lanes
+                float s = 0.f;
+#pragma unroll
+                for (int r = 0; r < SPLIT_RL; ++r) s += s_part[r][tid];
+                s_part[0][tid] = s;
+            }
+            __syncthreads();
+            if (tid < groups) {
+                float s = 0.f;
+                for (int c = 0; c < cg; ++c) s += s_part[0][tid * cg + c];
+                if (!pass) s_grp[tid] = s / (64.f * cg);
+                else if (n0 + tid * cg < a.N) {
+                    const int p = m0 / a.geom.S, slot = (m0 - p * a.geom.S) / 64;
+                    float* dst = a.stats + (((int64_t)p * a.stats_slots + slot) * a.stats_G + n0 / cg + tid) * 2;
+                    dst[0] = s_grp[tid];
+                    dst[1] = s;
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < 8; ++q) mean[q] = s_grp[(cv * 8 + q) / cg];
+        }
+    }
+    if (!in) return;
+    const int sg = col / a.seg_cols;
+    const GemmSeg seg = sg == 0 ? a.seg[0] : (sg == 1 ? a.seg[1] : a.seg[2]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        if (tok[r] < 0) continue;
+        if (a.res) {
+            const u32x4 x = *reinterpret_cast<const u32x4*>((const uint16_t*)a.res + tok[r] * a.ldr + col);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                v[r][2 * q] += __uint_as_float(x[q] << 16);
+                v[r][2 * q + 1] += __uint_as_float(x[q] & 0xFFFF0000u);
+            }
+        }
+        u32x4 o;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = pack_bf16x2(v[r][2 * q], v[r][2 * q + 1]);
+        *reinterpret_cast<u32x4*>((uint16_t*)seg.ptr + tok[r] * seg.ld + col - sg * a.seg_cols) = o;
+    }
+}
+
+// Columns of a block of split_reduce_kernel: whole groups of cg channels and whole vectors of 8, about 64, at most 128.
+static int split_slab(int cg) {
+    int unit = 8;
+    while (unit % cg != 0 && unit <= 128) unit += 8;
+    return unit > 128 ? 0 : unit >= 64 ? unit : unit * ((63 + unit) / unit);
+}
+
+// Blocks that share a tile: as many as the chip has CUs for, in equal shares of the channel chunks; only where less than
+// half of the CUs would have a tile (each share writes and reads back 4 bytes per output: at half the chip the second
+// pass would cost what the split saves).
+static int conv_splits(int64_t tiles, int64_t kchunks) {
+    if (tiles * 2 > 256 || kchunks < 2) return 1;
+    const int64_t z = std::min<int64_t>(256 / tiles, kchunks), share = cdiv(kchunks, z);
+    // the second pass is a launch of ~5 us; a chunk is nine steps of ~0.6 us
+    return kchunks - share < 2 ? 1 : (int)cdiv(kchunks, share);
+}
+
 template <int BM, int BN, int WGM, int WGN, int APIX, int NSB, int KS = 1>
-static int launch_conv(const GemmArgs& a, const ConvTile& ct, hipStream_t st) {
+static int launch_conv(const GemmArgs& a, ConvTile& ct, hipStream_t st) {
     constexpr size_t lds = (size_t)(NSB * BN + 2 * APIX) * 128 + BM * sizeof(int32_t) + 64 * sizeof(int32_t);
     static_assert(lds <= 160 * 1024, "conv LDS budget");
-    PS_SET_LDS_ONCE((conv_mfma_kernel<BM, BN, WGM, WGN, APIX, NSB, KS>), lds);
-    const unsigned grid = (unsigned)(8 * cdiv(cdiv(a.M, BM), 8) * (a.N / BN));
-    conv_mfma_kernel<BM, BN, WGM, WGN, APIX, NSB, KS><<<grid, 256 * KS, lds, st>>>(a, ct);
-    return check_launch("conv_mfma_kernel");
+    const int64_t mt = cdiv(a.M, BM), nt = a.N / BN;
+    ct.splits = conv_splits(mt * nt, a.K / 64);
+    const int slab = split_slab(a.stats ? a.N / a.stats_G : 8);
+    if (!a.split_ws || a.split_ws_bytes < sizeof(float) * ct.splits * mt * BM * a.N || slab == 0) ct.splits = 1;
+    if (ct.splits == 1) {
+        PS_SET_LDS_ONCE((conv_mfma_kernel<BM, BN, WGM, WGN, APIX, NSB, KS, false>), lds);
+        conv_mfma_kernel<BM, BN, WGM, WGN, APIX, NSB, KS, false><<<(unsigned)(8 * cdiv(mt, 8) * nt), 256 * KS, lds, st>>>(a, ct);
+        return check_launch("conv_mfma_kernel");
+    }
+    PS_SET_LDS_ONCE((conv_mfma_kernel<BM, BN, WGM, WGN, APIX, NSB, KS, true>), lds);
+    conv_mfma_kernel<BM, BN, WGM, WGN, APIX, NSB, KS, true><<<(unsigned)(8 * cdiv(nt * ct.splits, 8) * mt), 256 * KS, lds, st>>>(a, ct);
+    PS_TRY(check_launch("conv_mfma_kernel"));
+    split_reduce_kernel<<<dim3((unsigned)cdiv(a.M, 64), (unsigned)cdiv(a.N, slab)), SPLIT_RL * slab / 8, 0, st>>>(
+        a, ct.splits, (int)(mt * BM), slab);
+    return check_launch("split_reduce_kernel");
 }
 
 // Tile geometry of the halo-in-LDS convolution; false if the patch shape does not fit it.
@@ -984,6 +1148,20 @@ bool gemm_emits_stats(const GemmArgs& a, int dtype, int mode) {
     // a wavefront's 64 rows must lie in one patch, and its columns must hold whole groups
     return a.geom.S % 64 == 0 && a.stats_slots == a.geom.S / 64 && !a.act.active && a.N % a.stats_G == 0 &&
            wc % (a.N / a.stats_G) == 0;
+}
+
+size_t conv_split_bytes(const PatchGeom& g, int32_t M, int32_t N, int32_t K, int dtype, int mode) {
+    if (dtype != PSERVE_BF16 || mode != 0 || K % 64 != 0) return 0;
+    GemmArgs a{};
+    a.conv = 1; a.tokens_are_rows = 1; a.taps = 9; a.geom = g; a.M = M; a.N = N; a.K = K; a.lda = K; a.seg_cols = N;
+    for (auto& s : a.seg) s.scale = 1.f;
+    ConvTile ct;
+    static const int bm[7] = {0, 256, 128, 128, 128, 128, 256}, bn[7] = {1, 160, 320, 256, 128, 64, 160};
+    const int sel = conv_select(a, &ct);
+    if (!sel) return 0;
+    const int64_t mt = cdiv(M, bm[sel]);
+    const int z = conv_splits(mt * (N / bn[sel]), K / 64);
+    return z > 1 ? sizeof(float) * z * mt * bm[sel] * (size_t)N : 0;
 }
 
 int gemm_wide_bf16(const GemmArgs& a, hipStream_t st, bool* handled);     // gemm_wide.hip

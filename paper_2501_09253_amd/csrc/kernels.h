@@ -115,7 +115,13 @@ struct GemmArgs {
     // (stats_slots = S / 64) and one group.  Only the kernels gemm_emits_stats() accepts fill it (plain stores).
     float* stats;
     int32_t stats_G, stats_slots;
+    // Optional scratch for partial sums (fp32): a convolution with too few tiles for the chip shares the K range of a tile
+    // between blocks (conv_split_bytes says how much it needs).  Not shared with a call that may run at the same time.
+    float* split_ws;
+    size_t split_ws_bytes;
 };
+// scratch a 3x3 convolution of M rows, N output and K input channels over this patch geometry can use (0: none)
+size_t conv_split_bytes(const PatchGeom& g, int32_t M, int32_t N, int32_t K, int dtype, int mode);
 // true if gemm(a, ...) will take a kernel that fills a.stats (the caller otherwise runs gn_stats on the output)
 bool gemm_emits_stats(const GemmArgs& a, int dtype, int mode);
 int gemm(const GemmArgs& a, int dtype, int mode, hipStream_t st);

@@ -1,5 +1,6 @@
 """GPU: linear layers on 256- and 320-row tiles (sizes of at least 128 tiles), at ragged ends of rows and columns, with
-transposed segments, gates, masks and padded row groups, against the plain reference kernels of the library.
+transposed segments, gates, masks and padded row groups; convolutions whose tiles are shared between blocks.  Against the
+plain reference kernels of the library.
 
 Both sides round to bf16 at the same places, so they differ by single roundings (2^-8 of a value) and what the following
 layers make of them: 1e-2 of the largest value, half the bar against the oracle."""
@@ -47,6 +48,29 @@ def test_wide_tiles(name):
     c = dict(CASES[name])
     C = c.pop("C")
     cfg = wl.custom_config(c.pop("res"), c.pop("patch"), C=C, G=32, heads=C // 64, stages=c.pop("stages"), dtype="bf16", seed=51, **c)
+    w = wl.make_workload(cfg)
+    err = rel_err(_forward(w, 0), _forward(w, 1))
+    assert np.isfinite(err) and err < 1e-2, err
+
+
+# convolutions whose tiles are shared between blocks (few rows, many channels): group widths that straddle vectors of
+# eight, whole and ragged row tiles, time embedding, masks, two residual convolutions in a row (moments of the first)
+SPLIT = {
+    "c1280": dict(res=[(32, 32)], patch=(8, 8), C=1280, stages=("RES2T",), temb_dim=40),
+    "c1280_ragged": dict(res=[(8, 16), (24, 8)], patch=(8, 8), C=1280, stages=("RES2", "RES1")),
+    "c320": dict(res=[(16, 32), (16, 16)], patch=(16, 16), C=320, stages=("RES2",)),
+    "c960": dict(res=[(16, 16)], patch=(16, 16), C=960, stages=("RES2",)),
+    "c512": dict(res=[(32, 32), (32, 64)], patch=(32, 32), C=512, stages=("RES2T", "RES2"), temb_dim=24),
+    "c384_whole": dict(res=[(8, 4)], patch=(8, 4), C=384, stages=("RES1", "RES2")),
+    "c640_masked": dict(res=[(32, 32), (16, 48)], patch=(16, 16), C=640, stages=("RES2",), reuse_p=0.4),
+}
+
+
+@pytest.mark.parametrize("name", list(SPLIT))
+def test_shared_convolution_tiles(name):
+    c = dict(SPLIT[name])
+    C = c.pop("C")
+    cfg = wl.custom_config(c.pop("res"), c.pop("patch"), C=C, G=32, heads=1, stages=c.pop("stages"), dtype="bf16", seed=53, **c)
     w = wl.make_workload(cfg)
     err = rel_err(_forward(w, 0), _forward(w, 1))
     assert np.isfinite(err) and err < 1e-2, err
