@@ -98,16 +98,28 @@ attn_simple_kernel(AttnArgs a) {
 // above (5 heads of 64, requests of 4,096 and 3,072 tokens): 62.0 -> 0.42 ms (79 TFLOP/s); 2 heads of 32, 256 and 576 tokens: 136 -> 15 us.
 typedef __attribute__((ext_vector_type(16))) float at_f32x16;
 
-template <typename T> __device__ __forceinline__ float4 at_ld4(const T* p);
-template <> __device__ __forceinline__ float4 at_ld4<float>(const float* p) { return *reinterpret_cast<const float4*>(p); }
-template <> __device__ __forceinline__ float4 at_ld4<uint16_t>(const uint16_t* p) {
-    const uint2 v = *reinterpret_cast<const uint2*>(p);
-    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16),
-                       __uint_as_float(v.y & 0xFFFF0000u));
-}
+typedef __attribute__((ext_vector_type(4))) float at_f32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t at_u32x2;
 
-// D: head dim rounded up to 32, 64 or 128 (channels past d are zero).  VT: V is [C][ldv] instead of [rows][ldv].
-template <typename T, int D, bool VT>
+// four elements as loaded (converted where they are used: a load that is converted at once is waited for at once)
+template <typename T> struct AtRaw;
+template <> struct AtRaw<float> {
+    at_f32x4 r;
+    __device__ __forceinline__ void load(const float* p) { r = *reinterpret_cast<const at_f32x4*>(p); }
+    __device__ __forceinline__ at_f32x4 get() const { return r; }
+};
+template <> struct AtRaw<uint16_t> {
+    at_u32x2 r;
+    __device__ __forceinline__ void load(const uint16_t* p) { r = *reinterpret_cast<const at_u32x2*>(p); }
+    __device__ __forceinline__ at_f32x4 get() const {
+        return at_f32x4{__uint_as_float(r[0] << 16), __uint_as_float(r[0] & 0xFFFF0000u), __uint_as_float(r[1] << 16),
+                        __uint_as_float(r[1] & 0xFFFF0000u)};
+    }
+};
+
+// D: head dim rounded up to 32, 64 or 128 (FULL: it is that; else channels past d are zero).  VT: V is [C][ldv] instead of
+// [rows][ldv].
+template <typename T, int D, bool VT, bool FULL>
 __global__ void __launch_bounds__(256, D == 128 ? 1 : 2)
 attn_f32mma_kernel(AttnArgs a, int group) {
     constexpr int KT = 32;                              // keys per tile
@@ -145,33 +157,41 @@ attn_f32mma_kernel(AttnArgs a, int group) {
         const int p = a.act.active ? a.act.active[pi] : pi;
         return (int64_t)p * S + (r - (r / S) * S);
     };
-    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-    float4 q[NQ];
+    const at_f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    at_f32x4 q[NQ];
     {
         const T* qp = (const T*)a.Q + token(min(r0 + fr, rows_s - 1)) * C + h * d;
+        AtRaw<T> raw[NQ];
 #pragma unroll
-        for (int j = 0; j < NQ; ++j) q[j] = 8 * j + 4 * fh < d ? at_ld4<T>(qp + 8 * j + 4 * fh) : zero;
+        for (int j = 0; j < NQ; ++j) raw[j].load(qp + (FULL ? 8 * j + 4 * fh : min(8 * j + 4 * fh, d - 4)));
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) q[j] = FULL || 8 * j + 4 * fh < d ? raw[j].get() : zero;
     }
     const T* Kp = (const T*)a.K + k0 * C + h * d;
     const T* Vp = VT ? (const T*)a.V + (int64_t)h * d * a.ldv + k0 : (const T*)a.V + k0 * a.ldv + h * d;
     // staging: vector v of a lane is row (v * 64 + lane) / (D / 4) of the tile; rows past the last key are clamped to it
     // (their scores are masked, their probabilities zero).  VT: channel row, four keys a vector.
     constexpr int VR = D / 4, VK = KT / 4;
-    float4 rk[NL], rv[NL];
+    const int ch = (lane % VR) * 4, chc = FULL ? ch : min(ch, d - 4);        // the lane's channels (64 is a multiple of VR)
+    AtRaw<T> rk[NL], rv[VT ? 1 : NL];
+    at_f32x4 rvt[VT ? NL : 1];
     auto load = [&](int t) {
+        const int last = nk - 1 - t * KT;               // last row of the tile that exists
+        const T* kt = Kp + (int64_t)t * KT * C;
+        const T* vt = VT ? Vp + t * KT : Vp + (int64_t)t * KT * a.ldv;
 #pragma unroll
         for (int v = 0; v < NL; ++v) {
-            const int i = v * 64 + lane, row = i / VR, c = (i % VR) * 4;
-            const int key = min(t * KT + row, nk - 1);
-            rk[v] = c < d ? at_ld4<T>(Kp + (int64_t)key * C + c) : zero;
-            if constexpr (!VT) {
-                rv[v] = c < d ? at_ld4<T>(Vp + (int64_t)key * a.ldv + c) : zero;
-            } else {
-                const int ch = i / VK, kk = t * KT + (i % VK) * 4;
-                const T* vp = Vp + (int64_t)ch * a.ldv;
-                rv[v] = ch < d ? make_float4(ld_f<T>(vp + min(kk, nk - 1)), ld_f<T>(vp + min(kk + 1, nk - 1)),
-                                             ld_f<T>(vp + min(kk + 2, nk - 1)), ld_f<T>(vp + min(kk + 3, nk - 1)))
-                               : zero;
+            const int row = min((v * 64 + lane) / VR, last);
+            rk[v].load(kt + row * C + chc);
+            if constexpr (!VT) rv[v].load(vt + row * (int)a.ldv + chc);
+        }
+        if constexpr (VT) {
+#pragma unroll
+            for (int v = 0; v < NL; ++v) {
+                const int i = v * 64 + lane, kk = (i % VK) * 4;
+                const T* vp = vt + (int64_t)(i / VK) * a.ldv;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) rvt[v][u] = ld_f<T>(vp + min(kk + u, last));
             }
         }
     };
@@ -190,9 +210,10 @@ attn_f32mma_kernel(AttnArgs a, int group) {
 #pragma unroll
         for (int v = 0; v < NL; ++v) {
             const int i = v * 64 + lane;
-            *reinterpret_cast<float4*>(sK + (i / VR) * LK + (i % VR) * 4) = rk[v];
-            if constexpr (VT) *reinterpret_cast<float4*>(sV + (i / VK) * LV + (i % VK) * 4) = rv[v];
-            else *reinterpret_cast<float4*>(sV + (i / VR) * LV + (i % VR) * 4) = rv[v];
+            const bool in = FULL || ch < d;
+            *reinterpret_cast<at_f32x4*>(sK + (i / VR) * LK + ch) = in ? rk[v].get() : zero;
+            if constexpr (VT) *reinterpret_cast<at_f32x4*>(sV + (i / VK) * LV + (i % VK) * 4) = rvt[v];
+            else *reinterpret_cast<at_f32x4*>(sV + (i / VR) * LV + ch) = in ? rv[v].get() : zero;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -202,7 +223,7 @@ attn_f32mma_kernel(AttnArgs a, int group) {
         for (int e = 0; e < 16; ++e) sc[0][e] = sc[1][e] = 0.f;
 #pragma unroll
         for (int j = 0; j < NQ; ++j) {
-            const float4 kf = *reinterpret_cast<const float4*>(sK + fr * LK + 8 * j + 4 * fh);
+            const at_f32x4 kf = *reinterpret_cast<const at_f32x4*>(sK + fr * LK + 8 * j + 4 * fh);
             sc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.x, q[j].x, sc[0], 0, 0, 0);
             sc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.y, q[j].y, sc[1], 0, 0, 0);
             sc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.z, q[j].z, sc[0], 0, 0, 0);
@@ -237,16 +258,15 @@ attn_f32mma_kernel(AttnArgs a, int group) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             if constexpr (VT) {
-                float4 vf[D / 32];
+                at_f32x4 vf[D / 32];
 #pragma unroll
                 for (int dt = 0; dt < D / 32; ++dt)
-                    vf[dt] = *reinterpret_cast<const float4*>(sV + (32 * dt + fr) * LV + 8 * g + 4 * fh);
+                    vf[dt] = *reinterpret_cast<const at_f32x4*>(sV + (32 * dt + fr) * LV + 8 * g + 4 * fh);
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
                     for (int dt = 0; dt < D / 32; ++dt)
-                        o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(i == 0 ? vf[dt].x : i == 1 ? vf[dt].y : i == 2 ? vf[dt].z : vf[dt].w,
-                                                                     p[4 * g + i], o[dt], 0, 0, 0);
+                        o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[dt][i], p[4 * g + i], o[dt], 0, 0, 0);
             } else {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
@@ -272,8 +292,8 @@ attn_f32mma_kernel(AttnArgs a, int group) {
     for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
         for (int g = 0; g < 4; ++g)
-            *reinterpret_cast<float4*>(sO + fr * LK + 32 * dt + 8 * g + 4 * fh) =
-                make_float4(o[dt][4 * g] * f, o[dt][4 * g + 1] * f, o[dt][4 * g + 2] * f, o[dt][4 * g + 3] * f);
+            *reinterpret_cast<at_f32x4*>(sO + fr * LK + 32 * dt + 8 * g + 4 * fh) =
+                at_f32x4{o[dt][4 * g] * f, o[dt][4 * g + 1] * f, o[dt][4 * g + 2] * f, o[dt][4 * g + 3] * f};
     __syncthreads();
     const int qr = tid >> 3;                            // eight threads per query
     if (r0 + qr >= rows_s) return;
@@ -292,39 +312,35 @@ attn_f32mma_kernel(AttnArgs a, int group) {
 #pragma unroll
     for (int c = (tid & 7) * 4; c < D; c += 32) {
         if (c >= d) break;
-        float4 v = zero;
+        at_f32x4 v = zero;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const float4 u = *reinterpret_cast<const float4*>(at_smem + w * WAVE + qr * LK + c);
-            v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
-        }
+        for (int w = 0; w < 4; ++w) v += *reinterpret_cast<const at_f32x4*>(at_smem + w * WAVE + qr * LK + c);
         if constexpr (sizeof(T) == 2)
             *reinterpret_cast<uint2*>(op + c) = make_uint2(pack_bf16x2(v.x * inv, v.y * inv), pack_bf16x2(v.z * inv, v.w * inv));
         else
-            *reinterpret_cast<float4*>(op + c) = make_float4(v.x * inv, v.y * inv, v.z * inv, v.w * inv);
+            *reinterpret_cast<at_f32x4*>(op + c) = v * inv;
     }
 }
 
-template <typename T, int D, bool VT>
+template <typename T, int D, bool VT, bool FULL>
 static int attn_f32mma_launch(const AttnArgs& a, hipStream_t st) {
     const int64_t items = (int64_t)a.max_tiles * 4 * a.qt * a.heads;
     // enough groups that every XCD gets its share of the long items; long ones keep a head's keys in one L2
     const int group = (int)std::max<int64_t>(1, std::min<int64_t>(64, items / 64));
     const unsigned grid = (unsigned)(8 * group * cdiv(items, 8 * group));
     constexpr int lds = 4 * (32 * (D + 4) + (VT ? D * 36 : 32 * (D + 8))) * 4;
-    PS_SET_LDS_ONCE((attn_f32mma_kernel<T, D, VT>), lds);
-    attn_f32mma_kernel<T, D, VT><<<grid, 256, lds, st>>>(a, group);
+    PS_SET_LDS_ONCE((attn_f32mma_kernel<T, D, VT, FULL>), lds);
+    attn_f32mma_kernel<T, D, VT, FULL><<<grid, 256, lds, st>>>(a, group);
     return check_launch("attn_f32mma_kernel");
 }
 
 template <typename T>
 static int attn_f32mma(const AttnArgs& a, hipStream_t st) {
-    const int D = a.d <= 32 ? 32 : a.d <= 64 ? 64 : 128;
     if constexpr (sizeof(T) == 2)                       // the transposed layout goes with bf16 and 64 channels a head
-        if (a.v_transposed) return attn_f32mma_launch<T, 64, true>(a, st);
-    if (D == 32) return attn_f32mma_launch<T, 32, false>(a, st);
-    if (D == 64) return attn_f32mma_launch<T, 64, false>(a, st);
-    return attn_f32mma_launch<T, 128, false>(a, st);
+        if (a.v_transposed) return attn_f32mma_launch<T, 64, true, true>(a, st);
+#define PS_AF(DD) (a.d == DD ? attn_f32mma_launch<T, DD, false, true>(a, st) : attn_f32mma_launch<T, DD, false, false>(a, st))
+    return a.d <= 32 ? PS_AF(32) : a.d <= 64 ? PS_AF(64) : PS_AF(128);
+#undef PS_AF
 }
 
 int attention_mfma_bf16(const AttnArgs& a, hipStream_t st, bool* handled);     // attn_mfma.hip

@@ -174,13 +174,23 @@ gemm_simple_kernel(GemmArgs a) {
 // q/k/v and out projection of 832 tokens x 64 channels 126 -> 21 us.
 typedef __attribute__((ext_vector_type(16))) float gm_f32x16;
 
-template <typename T> __device__ __forceinline__ float4 ld4_f(const T* p);
-template <> __device__ __forceinline__ float4 ld4_f<float>(const float* p) { return *reinterpret_cast<const float4*>(p); }
-template <> __device__ __forceinline__ float4 ld4_f<uint16_t>(const uint16_t* p) {
-    const uint2 v = *reinterpret_cast<const uint2*>(p);
-    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16),
-                       __uint_as_float(v.y & 0xFFFF0000u));
-}
+typedef __attribute__((ext_vector_type(4))) float gm_f32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t gm_u32x2;
+// four elements as loaded (converted when they go to LDS: a load that is converted at once is waited for at once)
+template <typename T> struct GmRaw;
+template <> struct GmRaw<float> {
+    gm_f32x4 r;
+    __device__ __forceinline__ void load(const float* p) { r = *reinterpret_cast<const gm_f32x4*>(p); }
+    __device__ __forceinline__ gm_f32x4 get() const { return r; }
+};
+template <> struct GmRaw<uint16_t> {
+    gm_u32x2 r;
+    __device__ __forceinline__ void load(const uint16_t* p) { r = *reinterpret_cast<const gm_u32x2*>(p); }
+    __device__ __forceinline__ gm_f32x4 get() const {
+        return gm_f32x4{__uint_as_float(r[0] << 16), __uint_as_float(r[0] & 0xFFFF0000u), __uint_as_float(r[1] << 16),
+                        __uint_as_float(r[1] & 0xFFFF0000u)};
+    }
+};
 
 template <typename T, int BM, int BN, bool GEGLU>
 __global__ void __launch_bounds__(256)
@@ -215,30 +225,31 @@ gemm_f32mma_kernel(GemmArgs a) {
 #pragma unroll
     for (int v = 0; v < VA; ++v) {
         const int row = (tid + v * 256) / VPR;
-        pa[v] = s_valid[row] ? (const T*)a.A + s_aoff[row] : nullptr;
+        pa[v] = (const T*)a.A + s_aoff[s_valid[row] ? row : 0];        // rows past the end: any that exists (not stored)
     }
 #pragma unroll
     for (int v = 0; v < VB; ++v) {
         const int row = (tid + v * 256) / VPR, h = row / BN;
-        int col = n0 + row - h * BN;
-        const bool ok = col < ncols;
+        int col = min(n0 + row - h * BN, ncols - 1);
         if (GEGLU) col = (col / GEGLU_GROUP) * 2 * GEGLU_GROUP + h * GEGLU_GROUP + col % GEGLU_GROUP;
-        pb[v] = ok ? (const T*)a.B + (int64_t)col * a.K : nullptr;
+        pb[v] = (const T*)a.B + (int64_t)col * a.K;
     }
     const int kv = (tid % VPR) * 4;                                  // 256 is a multiple of VPR: the same for every v
     const int tw = a.tap_w ? a.tap_w : 3;
     const int64_t tap_b = (int64_t)a.N * a.K;
     const int steps = a.taps * ((a.K + BK - 1) / BK);
-    float4 ra[VA], rb[VB];
+    GmRaw<T> ra[VA], rb[VB];
+    bool in = true;                                                  // the loaded k exist (K is a multiple of 4, not of BK)
     int tap = 0, k0 = 0;                                             // of the step loaded next
     auto load = [&]() {
-        const int64_t ao = (a.conv ? ((int64_t)(tap / tw) * a.geom.ppw + (tap % tw)) * a.lda : 0) + k0 + kv;
-        const int64_t bo = tap * tap_b + k0 + kv;
-        const bool in = k0 + kv < a.K;                               // K is a multiple of 4
+        const int k = min(k0 + kv, a.K - 4);
+        in = k0 + kv < a.K;
+        const int64_t ao = (a.conv ? ((int64_t)(tap / tw) * a.geom.ppw + (tap % tw)) * a.lda : 0) + k;
+        const int64_t bo = tap * tap_b + k;
 #pragma unroll
-        for (int v = 0; v < VA; ++v) ra[v] = in && pa[v] ? ld4_f<T>(pa[v] + ao) : make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int v = 0; v < VA; ++v) ra[v].load(pa[v] + ao);
 #pragma unroll
-        for (int v = 0; v < VB; ++v) rb[v] = in && pb[v] ? ld4_f<T>(pb[v] + bo) : make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int v = 0; v < VB; ++v) rb[v].load(pb[v] + bo);
         if (++tap == a.taps) { tap = 0; k0 += BK; }
     };
     // two accumulators per tile (even and odd k): shorter chains of dependent MFMAs, shorter sums
@@ -253,19 +264,21 @@ gemm_f32mma_kernel(GemmArgs a) {
     for (int s = 0; s < steps; ++s) {
         float* st = smem + (s & 1) * STAGE;
 #pragma unroll
-        for (int v = 0; v < VA; ++v) *reinterpret_cast<float4*>(st + ((tid + v * 256) / VPR) * LD + kv) = ra[v];
+        for (int v = 0; v < VA; ++v)
+            *reinterpret_cast<gm_f32x4*>(st + ((tid + v * 256) / VPR) * LD + kv) = in ? ra[v].get() : gm_f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int v = 0; v < VB; ++v) *reinterpret_cast<float4*>(st + (BM + (tid + v * 256) / VPR) * LD + kv) = rb[v];
+        for (int v = 0; v < VB; ++v)
+            *reinterpret_cast<gm_f32x4*>(st + (BM + (tid + v * 256) / VPR) * LD + kv) = in ? rb[v].get() : gm_f32x4{0.f, 0.f, 0.f, 0.f};
         if (s + 1 < steps) load();
         // one barrier a step: the buffer written above was last read in step s - 2, before the barrier of step s - 1
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < BK / 8 / WK; ++j) {
             const int k8 = (wk * (BK / 8 / WK) + j) * 8;
-            const float4 av = *reinterpret_cast<const float4*>(st + a_rd + k8);
+            const gm_f32x4 av = *reinterpret_cast<const gm_f32x4*>(st + a_rd + k8);
 #pragma unroll
             for (int h = 0; h < NB; ++h) {
-                const float4 bv = *reinterpret_cast<const float4*>(st + b_rd + h * BN * LD + k8);
+                const gm_f32x4 bv = *reinterpret_cast<const gm_f32x4*>(st + b_rd + h * BN * LD + k8);
                 acc[h][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x, bv.x, acc[h][0], 0, 0, 0);
                 acc[h][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.y, bv.y, acc[h][1], 0, 0, 0);
                 acc[h][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.z, bv.z, acc[h][0], 0, 0, 0);
