@@ -142,7 +142,7 @@ const char* pserve_last_error(void);
  * convolution).  resolutions_hw: HOST int32 [n][2] = (H, W) in latent pixels, caller
  * order.  ph = pw = 0 selects the greatest common divisor of all heights resp. widths
  * (the paper's patch-size rule).  Requests are sorted ascending by (H, W), stable.
- * The tables are built by device kernels on `stream`; the call returns after they are
+ * The per-patch tables are built by a device kernel on `stream`; the call returns after they are
  * complete (it synchronises the stream once to mirror them on the host).
  * Errors: EINVAL for n <= 0, non-positive sizes, H % ph != 0, W % pw != 0, or more
  * than 2^31-1 tokens; ENOMEM; EHIP.  *out is owned by the caller until pserve_plan_free. */

@@ -325,8 +325,8 @@ attn_f32mma_kernel(AttnArgs a, int group) {
 template <typename T, int D, bool VT, bool FULL>
 static int attn_f32mma_launch(const AttnArgs& a, hipStream_t st) {
     const int64_t items = (int64_t)a.max_tiles * 4 * a.qt * a.heads;
-    // enough groups that every XCD gets its share of the long items; long ones keep a head's keys in one L2
-    const int group = (int)std::max<int64_t>(1, std::min<int64_t>(64, items / 64));
+    // eight groups per XCD: its share of the long and short items, and consecutive query tiles of a head on one L2
+    const int group = (int)std::min<int64_t>(64, cdiv(items, 64));
     const unsigned grid = (unsigned)(8 * group * cdiv(items, 8 * group));
     constexpr int lds = 4 * (32 * (D + 4) + (VT ? D * 36 : 32 * (D + 8))) * 4;
     PS_SET_LDS_ONCE((attn_f32mma_kernel<T, D, VT, FULL>), lds);

