@@ -484,6 +484,17 @@ int gemm(const GemmArgs& a, int dtype, int mode, hipStream_t st) {
         PS_TRY(gemm_mfma_bf16(a, st, &handled));
         if (handled) return PSERVE_OK;
     }
+    if (a.classes) {                                    // the kernels below take one class at a time
+        for (int c = 0; c < a.classes; ++c) {
+            GemmArgs g = a;
+            g.classes = 0;
+            g.a_dy = g.o_dy = c >> 1;
+            g.a_dx = g.o_dx = c & 1;
+            g.B = (const char*)a.B + (size_t)c * a.taps * a.N * a.K * dtype_size(dtype);
+            PS_TRY(gemm(g, dtype, mode, st));
+        }
+        return PSERVE_OK;
+    }
     if (mode == 0 && (dtype == PSERVE_BF16 ? gemm_f32mma<uint16_t>(a, st) : gemm_f32mma<float>(a, st)))
         return check_launch("gemm_f32mma_kernel");
     const bool geglu = a.epi == EPI_GEGLU;

@@ -312,35 +312,28 @@ gemm_mfma_kernel(GemmArgs a) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // scalar: LDS destinations of the loads are SGPR math
     const int wm = wave / WGN, wn = wave % WGN;
-    // XCD-aware tile order.  Block ids are dealt round-robin to the 8 XCDs (each with its own L2), so the blocks of one
-    // residue mod 8 run on one XCD; they take that XCD's slots in order, gridDim / 8 at a time.  An XCD owns every 8th
-    // M tile; it takes them in groups of `gm` whose A panels together fit its L2, and walks a group M tile fastest,
-    // then N tile: the blocks in flight share `gm` A panels and a few B panels, A is fetched once and B once per group
-    // (N fastest, i.e. gm = 1, re-streams all of B for every M tile: 375 MB instead of 145 MB for a 5120 x 640 weight).
-    const int n_tiles = a.N / BN, m_tiles = (a.M + BM - 1) / BM;
-    const int mx = (m_tiles + 7) >> 3;              // M tiles per XCD
-    const int64_t a_panel = (int64_t)BM * a.K * a.taps * 2;
-    const int gm = (int)max((int64_t)1, min((int64_t)mx, (int64_t)(2560 * 1024) / a_panel));
-    const int slots = mx * n_tiles, slot_step = gridDim.x >> 3;
+    // Tile order.  Tiles are numbered in groups of gm M tiles, M fastest inside a group, and XCD x (block id mod 8; each has
+    // its own L2) takes the x-th eighth of the numbers: the blocks in flight on an XCD (64 at most) cover about gm x 64 / gm
+    // neighbouring tiles, so gm is chosen for the fewest bytes of A and B panels, and few rows with many columns end up
+    // shared out by columns.  (An eighth of the M tiles per XCD instead: with 8 M tiles every XCD read all weights, 115 MB
+    // for 13 MB of them at K = 5120.)
     const int act_count = (a.tokens_are_rows && a.act.active) ? *a.act.count : 0;              // computed patches
     const int m_limit = (a.tokens_are_rows && a.act.active) ? act_count * a.geom.S : a.M;      // rows that exist
-    // tile of a slot; false when it has no rows
-    auto decode = [&](int slot, int& m0, int& n0) -> bool {
+    const int n_tiles = a.N / BN * (a.classes ? a.classes : 1), m_tiles = (m_limit + BM - 1) / BM;
+    const int total = n_tiles * m_tiles, slot_step = gridDim.x >> 3;
+    const int slots = (int)((int64_t)total * ((blockIdx.x & 7) + 1) / 8);      // end of this XCD's tiles
+    const int gm = min(max((int)(sqrtf((float)min((total + 7) / 8, 64) * BN / BM) + 0.5f), 1), max(m_tiles, 1));
+    auto decode = [&](int slot, int& m0, int& n0) {
         const int grp = slot / (gm * n_tiles), r_in = slot - grp * (gm * n_tiles);
-        const int gm_here = min(gm, mx - grp * gm); // the last group may be short
+        const int gm_here = min(gm, m_tiles - grp * gm);    // the last group may be short
         const int n_tile = r_in / gm_here;
-        const int m_tile = (grp * gm + (r_in - n_tile * gm_here)) * 8 + (blockIdx.x & 7);
-        m0 = m_tile * BM;
+        m0 = (grp * gm + r_in - n_tile * gm_here) * BM;
         n0 = n_tile * BN;
-        return m_tile < m_tiles && m0 < m_limit;
-    };
-    auto next_tile = [&](int slot, int& m0, int& n0) -> int {       // first slot >= `slot` of this block with rows
-        while (slot < slots && !decode(slot, m0, n0)) slot += slot_step;
-        return slot;
     };
     int m0 = 0, n0 = 0;
-    int slot = next_tile(blockIdx.x >> 3, m0, n0);
+    int slot = (int)((int64_t)total * (blockIdx.x & 7) / 8) + (blockIdx.x >> 3);
     if (slot >= slots) return;
+    decode(slot, m0, n0);
 
     // Staging by direct global -> LDS loads.  One wavefront instruction fills 64 consecutive 16-byte slots
     // (8 rows x 8 chunk positions); the lane at (row, position pos) fetches global chunk pos ^ f(row),
@@ -359,6 +352,9 @@ gemm_mfma_kernel(GemmArgs a) {
     // operand pointers and the row -> token table `tok_tab` of tile (tm0, tn0)
 #define PS_SETUP(tm0, tn0, tok_tab)                                                                               \
     {                                                                                                             \
+        const int cls_ = a.classes ? (tn0) / a.N : 0, nl_ = (tn0) - cls_ * a.N;      /* class, column inside it */             \
+        const int ady_ = a.classes ? cls_ >> 1 : a.a_dy, adx_ = a.classes ? cls_ & 1 : a.a_dx;                    \
+        const int ody_ = a.classes ? cls_ >> 1 : a.o_dy, odx_ = a.classes ? cls_ & 1 : a.o_dx;                    \
         /* the patch ids of all rows first (one memory round trip for the tile, not one per row) */              \
         int act_p[A_LD];                                                                                          \
         if (a.tokens_are_rows && a.act.active) {                                                                  \
@@ -384,8 +380,8 @@ gemm_mfma_kernel(GemmArgs a) {
                 const int p = (int)(tok / a.geom.S), q = (int)(tok - (int64_t)p * a.geom.S);                      \
                 const int y = q / a.geom.pw, x = q - y * a.geom.pw;                                               \
                 const int am = a.a_mul ? a.a_mul : 1;                                                             \
-                off = ((int64_t)p * a.geom.pS + (am * y + a.a_dy) * a.geom.ppw + am * x + a.a_dx) * a.lda;        \
-                if (a.o_mul) orow = (int64_t)p * a.o_S + (a.o_mul * y + a.o_dy) * a.o_pw + a.o_mul * x + a.o_dx;  \
+                off = ((int64_t)p * a.geom.pS + (am * y + ady_) * a.geom.ppw + am * x + adx_) * a.lda;        \
+                if (a.o_mul) orow = (int64_t)p * a.o_S + (a.o_mul * y + ody_) * a.o_pw + a.o_mul * x + odx_;  \
             } else {                                                                                              \
                 off = tok * a.lda;                                                                                \
             }                                                                                                     \
@@ -396,7 +392,7 @@ gemm_mfma_kernel(GemmArgs a) {
                 (tok_tab)[row] = valid ? (int32_t)orow : -1;                                                      \
             }                                                                                                     \
         }                                                                                                         \
-        b_lane = (int)(((int64_t)((tn0) + lr) * a.K + gc * 8) * 2);                                               \
+        b_lane = (int)((((int64_t)cls_ * a.taps * a.N + nl_ + lr) * a.K + gc * 8) * 2);                                               \
     }
     // one direct global->LDS load (64 lanes x 16 bytes): l < A_LD an A row group, else a B row group
     // (buffer loads rather than global loads into LDS: behind a flat-class load the compiler turns every wait for one
@@ -521,11 +517,11 @@ gemm_mfma_kernel(GemmArgs a) {
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();                            // ring drained: free for the next tile (or the epilogue's staging)
-
         int nm0 = 0, nn0 = 0;
-        const int nslot = next_tile(slot + slot_step, nm0, nn0);
+        const int nslot = slot + slot_step;
+        if (nslot < slots) decode(nslot, nm0, nn0);
         const int32_t* tok_cur = s_tok2 + buf * BM;
-        const int n0_cur = n0;
+        const int n0_cur = a.classes ? n0 % a.N : n0;
         // the bias is read before the next tile's loads are issued: a wait for a load waits for all loads issued
         // before it, so a bias load behind them would stall the epilogue until the whole next tile start has landed
         float bias_t[TN];
@@ -1096,7 +1092,7 @@ static int launch(const GemmArgs& a, hipStream_t st) {
     PS_SET_LDS_ONCE((gemm_mfma_kernel<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP>), lds);
     // all tiles, or as many blocks as run at once (256 CUs x the blocks of this LDS size per CU): each block then
     // walks over several tiles
-    const int64_t all = 8 * cdiv(cdiv(a.M, BM), 8) * (a.N / BN);
+    const int64_t all = 8 * cdiv(cdiv(a.M, BM) * (a.N / BN) * std::max(1, a.classes), 8);
     const int64_t resident = 256 * (int64_t)std::max<size_t>(1, std::min<size_t>(2, (160 * 1024) / lds));
     const unsigned grid = (unsigned)std::min(all, resident);
     gemm_mfma_kernel<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP><<<grid, 256, lds, st>>>(a);
@@ -1107,7 +1103,7 @@ static int launch(const GemmArgs& a, hipStream_t st) {
 static bool mfma_eligible(const GemmArgs& a) {
     // the kernels stage both operands by buffer loads with 32-bit byte offsets from the tensors' bases
     const int64_t a_rows = a.conv ? (int64_t)a.geom.P * a.geom.pS : (int64_t)a.M;
-    const bool fits = a_rows * a.lda < ((int64_t)1 << 30) && (int64_t)a.taps * a.N * a.K < ((int64_t)1 << 30);
+    const bool fits = a_rows * a.lda < ((int64_t)1 << 30) && (int64_t)a.taps * a.N * a.K * std::max(1, a.classes) < ((int64_t)1 << 30);
     return a.K % 64 == 0 && a.lda % 8 == 0 && !((uintptr_t)a.A & 15) && !((uintptr_t)a.B & 15) && fits;
 }
 
@@ -1204,7 +1200,8 @@ int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
     // the rounds are the same: 34 -> 28 us (13,312 x 640 x 640), 68 -> 63 us (K = 2560), 80 -> 72 us
     // (13.4 k x 1280 x 1280), 165 -> 137 us (79 k x 640 x 640).  The fused q/k/v projections (N = 1920, 3840, with the
     // transposed V^T segment and its long epilogue of 8-byte stores) gain 6-11 % over 128 x 128 tiles as well.
-    if (a.N % 160 == 0 && m128 * (a.N / 160) >= 256) return launch<128, 160, false, 4, 1, 2, false>(a, st);
+    // From 208 tiles on (1,694 x 2560 x 2048, 224 tiles: 39 us against 44 with 128 x 64; 1,024 x 3840 x 1280, 192: 21.8 against 19.6).
+    if (a.N % 160 == 0 && m128 * (a.N / 160) * std::max(1, a.classes) >= 208) return launch<128, 160, false, 4, 1, 2, false>(a, st);
     const int64_t tiles128 = a.N % 128 == 0 ? m128 * (a.N / 128) : 0;
     // a transposed segment otherwise: 128 x 128, two blocks per CU (70 -> 62 us and 212 -> 184 us against 256-row tiles)
     if (has_t && tiles128 >= 512) return launch<128, 128, false, 2, 2, 2, false>(a, st);

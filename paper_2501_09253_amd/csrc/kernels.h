@@ -91,6 +91,9 @@ struct GemmArgs {
     // (one parity class of a nearest-up convolution, whose rows are INPUT tokens)
     int32_t tap_w, a_mul, a_dy, a_dx;
     int32_t o_mul, o_dy, o_dx, o_S, o_pw;
+    // 4: the four parity classes (2a + b) of a nearest-up convolution in one call: a_dy = o_dy = a, a_dx = o_dx = b, and
+    // the weights are [class][taps][N][K].  0: one problem as described by the fields above.
+    int32_t classes;
     PatchGeom geom;
     ActiveList act;            // row compaction by patch (rows are tokens)
     int32_t tokens_are_rows;   // 1: row ids are token ids (act applies); 0: plain row ids (M rows)

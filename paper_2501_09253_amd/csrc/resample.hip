@@ -114,16 +114,10 @@ int pserve_resample_forward(const pserve_resample_t* op, const pserve_plan_t* pl
         g.M = (int32_t)plan_out->T; g.taps = 9; g.tap_w = 3; g.a_mul = 2; g.B = op->w;
         return gemm(g, dt, 0, st);
     }
-    const size_t es = dtype_size(dt);
     g.M = (int32_t)plan_in->T; g.taps = 4; g.tap_w = 2; g.a_mul = 1;                     // rows: input tokens
     g.o_mul = 2; g.o_S = plan_out->S; g.o_pw = plan_out->pw;
-    for (int cls = 0; cls < 4; ++cls) {
-        g.a_dy = g.o_dy = cls >> 1;
-        g.a_dx = g.o_dx = cls & 1;
-        g.B = (const char*)op->w + (size_t)cls * 4 * op->C_out * op->C_in * es;
-        PS_TRY(gemm(g, dt, 0, st));
-    }
-    return PSERVE_OK;
+    g.classes = 4; g.B = op->w;                         // the four output parities
+    return gemm(g, dt, 0, st);
 }
 
 }  // extern "C"
