@@ -114,7 +114,9 @@ temb_proj_kernel(const T* __restrict__ temb, const T* __restrict__ wt, const flo
 template <typename T, int LPR>
 __global__ void __launch_bounds__(1024)
 temb_proj_wide_kernel(const T* __restrict__ temb, const T* __restrict__ wt, const float* __restrict__ bt,
-                      const int32_t* __restrict__ perm, int32_t n, int32_t D, int32_t C, float* __restrict__ e) {
+                      const int32_t* __restrict__ perm, int32_t n, int32_t D, int32_t C, float* __restrict__ e,
+                      const T* __restrict__ wt2, const float* __restrict__ bt2, float* __restrict__ e2) {
+    if (blockIdx.z) { wt = wt2; bt = bt2; e = e2; }          // the second stream of a joint block
     constexpr int TEMB_WKG = 1024 / LPR, CPB = 2 * LPR;     // k groups, channels per block
     extern __shared__ float s_t[];                  // [2][D] SiLU(temb) of the two slots, then [TEMB_WKG][2][CPB] partial sums
     float* s_part = s_t + 2 * D;
@@ -697,7 +699,8 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
         for (int k = 0; k < d.n_stages; ++k)
             if (needs_temb(d.stages[k]))
                 macs += (int64_t)plan->n * d.temb_dim * (d.stages[k] == PSERVE_RES2T ? d.C : d.stages[k] == PSERVE_MMDIT ? 12 * d.C : 3 * d.C);
-        c->side_temb = macs >= (int64_t)8 << 20;
+        // A joint block's two projections are one launch of about the length of one (17 us) and run inline.
+        c->side_temb = !joint && macs >= (int64_t)8 << 20;
         // A joint block runs the text stream's kernels (5 % of the rows, few tiles each: latency bound) on the side stream,
         // beside the image stream's (config 9: the text kernels alone were 19 % of the block).
         if (side_kv || c->side_temb || joint) {
@@ -959,18 +962,21 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         return gemm(gk, dt, mode, s2);
     };
     // SiLU -> linear on the per-request vector of stage si: cache->temb_e[si] [n][width] in slot order
-    auto temb_proj = [&](const StageWeights& w, int si, int width, hipStream_t s2, float* dst = nullptr) -> int {
+    // w2 / dst2: a second projection of the same vectors (joint block), in the same launch where it is a wide one
+    auto temb_proj = [&](const StageWeights& w, int si, int width, hipStream_t s2, float* dst = nullptr,
+                         const StageWeights* w2 = nullptr, float* dst2 = nullptr) -> int {
         if (!dst) dst = cache->temb_e[si];
         ProfScope ps("temb_proj", s2);
         const int32_t* perm = plan->d_tab[PSERVE_TAB_PERM];
         if (plan->n >= 2 && width >= 2048 && width % 2 == 0) {      // wide: pairs of slots
             const int64_t pairs = cdiv(plan->n, 2);
             const int cpb = pairs * cdiv(width, 64) <= 256 ? 64 : 128;    // channels per block: at most ~one block per CU
-            const dim3 wgrid((unsigned)pairs, (unsigned)cdiv(width, cpb));
+            const dim3 wgrid((unsigned)pairs, (unsigned)cdiv(width, cpb), w2 ? 2u : 1u);
             const size_t wlds = sizeof(float) * (2 * d.temb_dim + 2 * 1024 * 2);     // SiLU(temb) x 2, partial sums
             if (wlds <= 64 * 1024) {
 #define PS_TW(TT, LPR_) temb_proj_wide_kernel<TT, LPR_><<<wgrid, 1024, wlds, s2>>>((const TT*)temb, (const TT*)w.wt, w.bt, perm, \
-                                                                                 plan->n, d.temb_dim, width, dst)
+                                                                                 plan->n, d.temb_dim, width, dst, \
+                                                                                 w2 ? (const TT*)w2->wt : nullptr, w2 ? w2->bt : nullptr, dst2)
                 if (dt == PSERVE_BF16) { if (cpb == 64) PS_TW(uint16_t, 32); else PS_TW(uint16_t, 64); }
                 else { if (cpb == 64) PS_TW(float, 32); else PS_TW(float, 64); }
 #undef PS_TW
@@ -979,23 +985,25 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         }
         const dim3 grid(plan->n, (unsigned)cdiv(width, 64));
         const size_t lds = sizeof(float) * (d.temb_dim + TEMB_KG * 64);
-        if (dt == PSERVE_BF16)
-            temb_proj_kernel<uint16_t><<<grid, 1024, lds, s2>>>((const uint16_t*)temb, (const uint16_t*)w.wt, w.bt, perm,
-                                                               d.temb_dim, width, dst);
-        else
-            temb_proj_kernel<float><<<grid, 1024, lds, s2>>>((const float*)temb, (const float*)w.wt, w.bt, perm,
-                                                            d.temb_dim, width, dst);
+        for (int k = 0; k < (w2 ? 2 : 1); ++k) {
+            const StageWeights& v = k ? *w2 : w;
+            float* to = k ? dst2 : dst;
+            if (dt == PSERVE_BF16)
+                temb_proj_kernel<uint16_t><<<grid, 1024, lds, s2>>>((const uint16_t*)temb, (const uint16_t*)v.wt, v.bt, perm,
+                                                                   d.temb_dim, width, to);
+            else
+                temb_proj_kernel<float><<<grid, 1024, lds, s2>>>((const float*)temb, (const float*)v.wt, v.bt, perm,
+                                                                d.temb_dim, width, to);
+        }
         return check_launch("temb_proj_kernel");
     };
     // all projections of stage k (one for RES2T and the adaLN sub-layers, one per stream for a joint block)
     auto temb_stage = [&](int k, hipStream_t s2) -> int {
-        if (d.stages[k] == PSERVE_MMDIT) {
-            PS_TRY(temb_proj(block->sw[k], k, 6 * C, s2, cache->temb_e[k]));
-            return temb_proj(block->sw_txt[k], k, 6 * C, s2, cache->temb_e2[k]);
-        }
+        if (d.stages[k] == PSERVE_MMDIT)
+            return temb_proj(block->sw[k], k, 6 * C, s2, cache->temb_e[k], &block->sw_txt[k], cache->temb_e2[k]);
         return temb_proj(block->sw[k], k, d.stages[k] == PSERVE_RES2T ? C : 3 * C, s2);
     };
-    if (cache->side) {                              // fork: the side stream starts where this call starts
+    if (cache->side_temb || cache->side_stage >= 0) {   // fork: the side stream starts where this call starts
         PS_CHECK_HIP(hipEventRecord(cache->ev_fork, st));
         PS_CHECK_HIP(hipStreamWaitEvent(cache->side, cache->ev_fork, 0));
         for (int k = 0; k < d.n_stages; ++k)        // the short projections first: their consumers come early
@@ -1029,15 +1037,17 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         return attention(aa, dt, mode, st);
     };
     // fused q / k / v projection of `in` (rows of the patches in `rows`) into cache->q (scaled), k[si], v[si]
-    auto qkv_proj = [&](const void* in, const void* wqkv, int si, ActiveList rows, hipStream_t sq = nullptr) -> int {
-        if (!sq) sq = st;
+    auto qkv_args = [&](const void* in, const void* wqkv, int si, ActiveList rows) -> GemmArgs {
         GemmArgs g = base_gemm(in, C, C, 3 * C, wqkv, nullptr);
         g.act = rows; g.seg_cols = C;
         g.seg[0].ptr = cache->q; g.seg[0].ld = C; g.seg[0].scale = qscale;
         g.seg[1].ptr = cache->k[si]; g.seg[1].ld = C;
         g.seg[2].ptr = cache->v[si]; g.seg[2].ld = cache->v_transposed ? T : C; g.seg[2].transposed = cache->v_transposed;
-        ProfScope ps("linear_qkv", sq);
-        return gemm(g, dt, mode, sq);
+        return g;
+    };
+    auto qkv_proj = [&](const void* in, const void* wqkv, int si, ActiveList rows) -> int {
+        ProfScope ps("linear_qkv", st);
+        return gemm(qkv_args(in, wqkv, si, rows), dt, mode, st);
     };
     // the projection of stage si as seen from the main stream: wait for the side stream, or run it here
     auto temb_ready = [&](const StageWeights&, int si, int) -> int {
@@ -1110,10 +1120,67 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
             // Two streams (image patches, text patches) with their own weights, as two patch lists over the joint
             // token matrix; one attention per request over all its tokens.
             const int F = d.ffn_mult * C;
-            PS_TRY(temb_ready(w, si, 6 * C));
             void* mid = (cur == cache->ping[0] || out == cache->ping[0]) ? ((cur == cache->ping[1] || out == cache->ping[1]) ? cache->q : cache->ping[1]) : cache->ping[0];
-            // The text stream's kernels go to the side stream: they touch the rows of the text patches only (every
-            // buffer is shared row-wise), so the two streams meet at the attention and at the end of the stage.
+            // the four linear layers of stream xs
+            enum { QKV, OUT, IN, MLP_OUT };
+            auto layer = [&](int which, int xs) -> GemmArgs {
+                const StageWeights& v = xs == 0 ? block->sw[si] : block->sw_txt[si];
+                const float* mod = xs == 0 ? cache->temb_e[si] : cache->temb_e2[si];
+                GemmArgs g;
+                if (which == QKV) {
+                    g = qkv_args(cache->u, v.w[0], si, act);
+                } else if (which == OUT) {
+                    g = base_gemm(cache->o, C, C, C, v.w[1], v.b[1]);
+                    g.res = cur; g.ldr = C;
+                    g.rowscale = mod + 2 * C; g.rowscale_ld = 6 * C; g.row_owner = owner;
+                    g.seg[0].ptr = mid; g.seg[0].ld = C;
+                } else if (which == IN) {
+                    g = base_gemm(cache->u, C, C, F, v.w[3], v.b[3]);
+                    g.act_gelu = 1;
+                    g.seg[0].ptr = cache->hidden; g.seg[0].ld = F;
+                } else {
+                    g = base_gemm(cache->hidden, F, F, C, v.w[4], v.b[4]);
+                    g.res = mid; g.ldr = C;
+                    g.rowscale = mod + 5 * C; g.rowscale_ld = 6 * C; g.row_owner = owner;
+                    g.seg[0].ptr = out; g.seg[0].ld = C;
+                }
+                g.act = ActiveList{cache->stream_list[xs], cache->stream_count + xs};
+                return g;
+            };
+            // both streams' layer as one launch
+            const int txt_patches = plan->n * plan->text_patches;
+            auto both = [&](int which) -> GemmArgs {
+                GemmArgs g = layer(which, 0);
+                const GemmArgs t = layer(which, 1);
+                g.M = (int32_t)((plan->P - txt_patches) * (int64_t)plan->S);
+                g.B2 = t.B; g.bias2 = t.bias; g.rowscale2 = t.rowscale; g.act2 = t.act; g.M2 = (int32_t)(txt_patches * (int64_t)plan->S);
+                return g;
+            };
+            PS_TRY(temb_ready(w, si, 6 * C));
+            static const char* const label[4] = {"linear_qkv", "linear_out", "mlp_in", "mlp_out"};
+            bool one = true;
+            for (int k = 0; k < 4; ++k) one = one && gemm_takes_two(both(k), dt, mode);
+            if (one) {
+                // Large enough for the wide tiles: every layer once over both streams, everything on the caller's stream
+                // (as two kernels on two streams the text stream's few tiles took whole CUs from the image stream's
+                // rounds, and every fork and join cost ~10 us: 1.11 -> 1.04 ms for 11,520 + 616 tokens of 1536).
+                auto norm = [&](const void* in, int off) -> int {
+                    ProfScope ps("layer_norm", st);
+                    return layer_norm(in, nullptr, nullptr, cache->temb_e[si] + off, 6 * C, owner, C, d.eps, gm, dt, cache->u, all, st,
+                                      cache->temb_e2[si] + off, plan->d_tab[PSERVE_TAB_PATCH_RC]);
+                };
+                auto run = [&](int which) -> int { ProfScope ps(label[which], st); return gemm(both(which), dt, mode, st); };
+                PS_TRY(norm(cur, 0));
+                PS_TRY(run(QKV));
+                PS_TRY(run_attention(si, /*cross=*/false, /*joint=*/true));
+                PS_TRY(run(OUT));
+                PS_TRY(norm(mid, 3 * C));
+                PS_TRY(run(IN));
+                PS_TRY(run(MLP_OUT));
+                break;
+            }
+            // Small batches: the text stream's kernels go to the side stream.  They touch the rows of the text patches only
+            // (every buffer is shared row-wise), so the two streams meet at the attention and at the end of the stage.
             hipStream_t sx[2] = {st, cache->side ? cache->side : st};
             auto fork_txt = [&](int e) -> int {           // the side stream continues from this point of the main one
                 if (sx[1] == st) return PSERVE_OK;
@@ -1127,39 +1194,26 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
                 PS_CHECK_HIP(hipStreamWaitEvent(st, cache->ev_txt[e], 0));
                 return PSERVE_OK;
             };
+            auto norm = [&](const void* in, int off, int xs) -> int {
+                const float* mod = xs == 0 ? cache->temb_e[si] : cache->temb_e2[si];
+                ProfScope ps("layer_norm", sx[xs]);
+                return layer_norm(in, nullptr, nullptr, mod + off, 6 * C, owner, C, d.eps, gm, dt, cache->u,
+                                  ActiveList{cache->stream_list[xs], cache->stream_count + xs}, sx[xs]);
+            };
+            auto run = [&](int which, int xs) -> int { ProfScope ps(label[which], sx[xs]); return gemm(layer(which, xs), dt, mode, sx[xs]); };
             PS_TRY(fork_txt(0));
             for (int xs = 0; xs < 2; ++xs) {
-                const StageWeights& v = xs == 0 ? block->sw[si] : block->sw_txt[si];
-                const float* mod = xs == 0 ? cache->temb_e[si] : cache->temb_e2[si];
-                const ActiveList ax{cache->stream_list[xs], cache->stream_count + xs};
-                { ProfScope ps("layer_norm", sx[xs]);
-                  PS_TRY(layer_norm(cur, nullptr, nullptr, mod, 6 * C, owner, C, d.eps, gm, dt, cache->u, ax, sx[xs])); }
-                PS_TRY(qkv_proj(cache->u, v.w[0], si, ax, sx[xs]));
+                PS_TRY(norm(cur, 0, xs));
+                PS_TRY(run(QKV, xs));
             }
             PS_TRY(join_txt(1));
             PS_TRY(run_attention(si, /*cross=*/false, /*joint=*/true));
             PS_TRY(fork_txt(2));
             for (int xs = 0; xs < 2; ++xs) {
-                const StageWeights& v = xs == 0 ? block->sw[si] : block->sw_txt[si];
-                const float* mod = xs == 0 ? cache->temb_e[si] : cache->temb_e2[si];
-                const ActiveList ax{cache->stream_list[xs], cache->stream_count + xs};
-                hipStream_t s_ = sx[xs];
-                GemmArgs go = base_gemm(cache->o, C, C, C, v.w[1], v.b[1]);
-                go.act = ax; go.res = cur; go.ldr = C;
-                go.rowscale = mod + 2 * C; go.rowscale_ld = 6 * C; go.row_owner = owner;
-                go.seg[0].ptr = mid; go.seg[0].ld = C;
-                { ProfScope ps("linear_out", s_); PS_TRY(gemm(go, dt, mode, s_)); }
-                { ProfScope ps("layer_norm", s_);
-                  PS_TRY(layer_norm(mid, nullptr, nullptr, mod + 3 * C, 6 * C, owner, C, d.eps, gm, dt, cache->u, ax, s_)); }
-                GemmArgs g1 = base_gemm(cache->u, C, C, F, v.w[3], v.b[3]);
-                g1.act = ax; g1.act_gelu = 1;
-                g1.seg[0].ptr = cache->hidden; g1.seg[0].ld = F;
-                { ProfScope ps("mlp_in", s_); PS_TRY(gemm(g1, dt, mode, s_)); }
-                GemmArgs g2 = base_gemm(cache->hidden, F, F, C, v.w[4], v.b[4]);
-                g2.act = ax; g2.res = mid; g2.ldr = C;
-                g2.rowscale = mod + 5 * C; g2.rowscale_ld = 6 * C; g2.row_owner = owner;
-                g2.seg[0].ptr = out; g2.seg[0].ld = C;
-                { ProfScope ps("mlp_out", s_); PS_TRY(gemm(g2, dt, mode, s_)); }
+                PS_TRY(run(OUT, xs));
+                PS_TRY(norm(mid, 3 * C, xs));
+                PS_TRY(run(IN, xs));
+                PS_TRY(run(MLP_OUT, xs));
             }
             PS_TRY(join_txt(3));
             break;

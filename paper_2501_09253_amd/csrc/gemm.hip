@@ -484,6 +484,7 @@ int gemm(const GemmArgs& a, int dtype, int mode, hipStream_t st) {
         PS_TRY(gemm_mfma_bf16(a, st, &handled));
         if (handled) return PSERVE_OK;
     }
+    PS_REQUIRE(!a.B2, "gemm: no kernel takes the second problem of this shape");
     if (a.classes) {                                    // the kernels below take one class at a time
         for (int c = 0; c < a.classes; ++c) {
             GemmArgs g = a;

@@ -1167,7 +1167,7 @@ int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
     if (!mfma_eligible(a)) return PSERVE_OK;
     if (!a.conv) {
         PS_TRY(gemm_wide_bf16(a, st, handled));
-        if (*handled) return PSERVE_OK;
+        if (*handled || a.B2) return PSERVE_OK;
     }
     if (a.epi == EPI_GEGLU) {
         if (a.N % 128 != 0) return PSERVE_OK;

@@ -61,35 +61,43 @@ gemm_wide_kernel(GemmArgs a) {
     // Tile order.  Tiles are numbered in groups of GM M tiles, M fastest inside a group; XCD x (block id mod 8) takes the
     // x-th eighth of the numbers: the ~32 blocks of an XCD run on about GM x 32 / GM neighbouring tiles whose A and B
     // panels they stream at the same time, and every XCD has the same share whatever the number of M tiles is.
-    const int act_count = (a.tokens_are_rows && a.act.active) ? *a.act.count : 0;
-    const int m_limit = (a.tokens_are_rows && a.act.active) ? act_count * a.geom.S : a.M;
-    const int n_tiles = (a.N + BN - 1) / BN, m_tiles = (m_limit + BM - 1) / BM;
+    // A second problem (a.B2: another patch list, weights of its own) continues the M tiles of the first.
+    const bool masked = a.tokens_are_rows && a.act.active;
+    const int cnt1 = masked ? *a.act.count : 0, cnt2 = a.B2 ? *a.act2.count : 0;                // computed patches
+    const int mt1 = ((masked ? cnt1 * a.geom.S : a.M) + BM - 1) / BM;
+    const int n_tiles = (a.N + BN - 1) / BN, m_tiles = mt1 + (cnt2 * a.geom.S + BM - 1) / BM;
     const int total = n_tiles * m_tiles, xcd = blockIdx.x & 7;
     const int t_end = (int)((int64_t)total * (xcd + 1) / 8), t_step = gridDim.x >> 3;
     int t = (int)((int64_t)total * xcd / 8) + (blockIdx.x >> 3);
     if (t >= t_end) return;
-    auto decode = [&](int tt, int& m0, int& n0) {
+    auto decode = [&](int tt, int& m0, int& n0, bool& second) {
         const int grp = tt / (GM * n_tiles), r = tt - grp * (GM * n_tiles);
         const int gm = min(GM, m_tiles - grp * GM);
         const int nt = r / gm;
-        m0 = (grp * GM + r - nt * gm) * BM;
+        const int mt = grp * GM + r - nt * gm;
+        second = mt >= mt1;
+        m0 = (second ? mt - mt1 : mt) * BM;
         n0 = nt * BN;
     };
     int m0, n0;
-    decode(t, m0, n0);
+    bool second;
+    decode(t, m0, n0, second);
 
     // staging: a load of a wavefront fills 8 rows x 8 chunks; the lane at (row, position) fetches chunk
     // position ^ ((row >> 1) & 7), so the bank swizzle is free.  Rows lr + RP * l of both operands.
     const int lc = lane & 7, lr = 8 * wave + (lane >> 3);
     const int gc = lc ^ ((lr >> 1) & 7);
     int a_lane[A_LD], b_lane[B_LD];                     // byte offsets from the tensors' bases
+    const void* b_cur = second ? a.B2 : a.B;            // weights of the tile being loaded
     const int KT = a.K / 64;
-    auto setup = [&](int tm0, int tn0, int32_t* tok_tab) {
+    auto setup = [&](int tm0, int tn0, bool sec, int32_t* tok_tab) {
         int tok[A_LD], orow[A_LD];                      // input row (0 where there is none), output row
-        if (a.tokens_are_rows && a.act.active) {
+        if (masked) {
+            const int32_t* active = sec ? a.act2.active : a.act.active;
+            const int act_count = sec ? cnt2 : cnt1;
             int p[A_LD];
 #pragma unroll
-            for (int l = 0; l < A_LD; ++l) p[l] = a.act.active[min((tm0 + lr + l * RP) / a.geom.S, act_count - 1)];
+            for (int l = 0; l < A_LD; ++l) p[l] = active[min((tm0 + lr + l * RP) / a.geom.S, act_count - 1)];
 #pragma unroll
             for (int l = 0; l < A_LD; ++l) {
                 const int ri = tm0 + lr + l * RP, pi = ri / a.geom.S;
@@ -120,14 +128,14 @@ gemm_wide_kernel(GemmArgs a) {
     };
 #if defined(__HIP_DEVICE_COMPILE__)
     const __amdgpu_buffer_rsrc_t ga_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.A, 0, 0x7fffffff, 0x00020000);
-    const __amdgpu_buffer_rsrc_t gb_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.B, 0, 0x7fffffff, 0x00020000);
 #define PS_LOAD(dst_, koff_, l_)                                                                                       \
     {                                                                                                                  \
         if ((l_) < A_LD)                                                                                               \
             __builtin_amdgcn_raw_ptr_buffer_load_lds(ga_rsrc, (lds_void*)((dst_) + (l_) * (64 * NW)), 16,              \
                                                      a_lane[(l_) < A_LD ? (l_) : 0], (koff_), 0, 0);                   \
         else if ((l_) < LD)                                                                                            \
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(gb_rsrc, (lds_void*)((dst_) + BM * 8 + ((l_) - A_LD) * (64 * NW)), 16, \
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)b_cur, 0, 0x7fffffff, 0x00020000), \
+                                                     (lds_void*)((dst_) + BM * 8 + ((l_) - A_LD) * (64 * NW)), 16, \
                                                      b_lane[(l_) >= A_LD && (l_) < LD ? (l_) - A_LD : 0], (koff_), 0, 0); \
     }
 #else       // the host pass only needs the kernel's stub
@@ -142,12 +150,12 @@ gemm_wide_kernel(GemmArgs a) {
     f32x16 acc[TM][TN];
     bf16x8 fa[SA ? 1 : 2][TM], fb[2][TN];
     int buf = 0;
-    setup(m0, n0, s_tok2);
+    setup(m0, n0, second, s_tok2);
     load_stage(0, 0);
     if (KT > 1) load_stage(1, 1);
 
     // one tile of this wavefront: main loop and output.  TR: the wavefront's columns belong to a transposed segment.
-    auto tile = [&](auto tr_c, int nt, int nm0, int nn0) {
+    auto tile = [&](auto tr_c, int nt, int nm0, int nn0, bool nsec) {
         constexpr bool TR = decltype(tr_c)::value;
         const int rowA = wm * WM + (TR ? gw_kperm(fr) : fr), rowB = wn * WN + (TR ? fr : gw_kperm(fr));
         const int swA = (rowA >> 1) & 7, swB = (rowB >> 1) & 7;
@@ -174,10 +182,11 @@ gemm_wide_kernel(GemmArgs a) {
             }
         };
         // accumulators start at the bias (of columns that exist)
-        if (a.bias) {
+        const float* bias = second ? a.bias2 : a.bias;
+        if (bias) {
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                const float* bp = a.bias + min(wcol + 32 * j, a.N - 32);
+                const float* bp = bias + min(wcol + 32 * j, a.N - 32);
                 if constexpr (TR) {
                     const float b = bp[fr];
 #pragma unroll
@@ -270,7 +279,8 @@ gemm_wide_kernel(GemmArgs a) {
         // every wavefront has read its last fragments (a bare barrier: __syncthreads() would wait for the residual)
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         if (nt < t_end) {                               // first step of the next tile beside the end of this one
-            setup(nm0, nn0, s_tok2 + (buf ^ 1) * BM);
+            b_cur = nsec ? a.B2 : a.B;
+            setup(nm0, nn0, nsec, s_tok2 + (buf ^ 1) * BM);
             load_stage(0, 0);
         }
         if (wcol >= a.N) return;
@@ -329,7 +339,7 @@ gemm_wide_kernel(GemmArgs a) {
                 const GemmSeg seg = sg == 0 ? a.seg[0] : (sg == 1 ? a.seg[1] : a.seg[2]);
                 const float* gate = nullptr;
                 if constexpr (END == GW_GATE_RES)
-                    gate = a.rowscale + (int64_t)a.row_owner[max(w_tok[32 * i + fr], 0) / a.geom.S] * a.rowscale_ld + pcol + 8 * fh;
+                    gate = (second ? a.rowscale2 : a.rowscale) + (int64_t)a.row_owner[max(w_tok[32 * i + fr], 0) / a.geom.S] * a.rowscale_ld + pcol + 8 * fh;
 #pragma unroll
                 for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
@@ -382,19 +392,20 @@ gemm_wide_kernel(GemmArgs a) {
     for (;;) {
         const int nt = t + t_step;
         int nm0 = 0, nn0 = 0;
-        if (nt < t_end) decode(nt, nm0, nn0);
+        bool nsec = false;
+        if (nt < t_end) decode(nt, nm0, nn0, nsec);
         bool tr = false;
         if constexpr (END == GW_PLAIN) {
             const int sg = min(n0 + wn * WN, a.N - 1) / a.seg_cols;
             tr = (sg == 0 ? a.seg[0].transposed : (sg == 1 ? a.seg[1].transposed : a.seg[2].transposed)) != 0;
-            if (tr) tile(std::true_type{}, nt, nm0, nn0);
+            if (tr) tile(std::true_type{}, nt, nm0, nn0, nsec);
         }
-        if (!tr) tile(std::false_type{}, nt, nm0, nn0);
+        if (!tr) tile(std::false_type{}, nt, nm0, nn0, nsec);
         if (nt >= t_end) break;
         // the output staging is done with the second stage (a bare barrier: the stores are not waited for)
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         if (KT > 1) load_stage(1, 1);
-        t = nt; m0 = nm0; n0 = nn0; buf ^= 1;
+        t = nt; m0 = nm0; n0 = nn0; second = nsec; buf ^= 1;
     }
 #undef PS_LOAD
 }
@@ -403,7 +414,7 @@ template <int WGM, int WGN, int TM, int TN, int END>
 static int launch_wide_end(const GemmArgs& a, hipStream_t st) {
     using Cfg = WideCfg<WGM, WGN, TM, TN>;
     PS_SET_LDS_ONCE((gemm_wide_kernel<WGM, WGN, TM, TN, END>), Cfg::LDS);
-    const int64_t tiles = cdiv(a.M, Cfg::BM) * cdiv(a.N, Cfg::BN);
+    const int64_t tiles = (cdiv(a.M, Cfg::BM) + cdiv(a.B2 ? a.M2 : 0, Cfg::BM)) * cdiv(a.N, Cfg::BN);
     const unsigned grid = (unsigned)std::min<int64_t>(256, 8 * cdiv(tiles, 8));
     gemm_wide_kernel<WGM, WGN, TM, TN, END><<<grid, 64 * Cfg::NW, Cfg::LDS, st>>>(a);
     return check_launch("gemm_wide_kernel");
@@ -444,6 +455,8 @@ static bool wide_eligible(const GemmArgs& a, int wave_cols) {
         return wave_cols == 2 * GEGLU_GROUP && a.N % 128 == 0 && !((uintptr_t)a.seg[0].ptr & 15) && a.seg[0].ld % 8 == 0;
     if (a.N % 64 != 0 || a.seg_cols % 64 != 0 || (a.res && a.ldr % 8 != 0)) return false;
     if (a.rowscale && !a.tokens_are_rows) return false;
+    if (a.B2 && (!a.tokens_are_rows || !a.act.active || !a.act2.active || (((uintptr_t)a.B2 | (uintptr_t)a.bias2) & 15) ||
+                 !a.bias != !a.bias2 || !a.rowscale != !a.rowscale2)) return false;
     for (int s = 0; s * a.seg_cols < a.N; ++s) {
         if (((uintptr_t)a.seg[s].ptr & 15) || a.seg[s].ld % 8 != 0) return false;
         // a wavefront's columns take one operand order
@@ -465,24 +478,33 @@ static double wide_cost(int64_t tiles, int64_t steps, double s0, double s1, doub
 // out 61 -> 48; 13,312 x 640 q/k/v 47.6 -> 41.7, GEGLU 115 -> 108.  They lose where their rounds come out badly (13,312 x
 // 640 x 640: 156 tiles for 256 CUs, 25 against 22 us) and to smaller tiles on few rows, so the launch compares the
 // modelled times of both; the model is within 10 % of the measured shapes (K = 640 .. 6144).
-int gemm_wide_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
-    *handled = false;
+// Returns the rows of the tile to use, 0: the other kernel.
+static int wide_select(const GemmArgs& a) {
     const int64_t steps = a.K / 64;
-    int64_t t256 = cdiv(a.M, 256) * cdiv(a.N, 256), t320 = cdiv(a.M, 320) * cdiv(a.N, 256);
+    auto m_tiles = [&](int bm) { return cdiv(a.M, bm) + cdiv(a.B2 ? a.M2 : 0, bm); };
+    int64_t t256 = m_tiles(256) * cdiv(a.N, 256), t320 = m_tiles(320) * cdiv(a.N, 256);
     if (!wide_eligible(a, 128)) t256 = 0;
     if (!wide_eligible(a, 64)) t320 = 0;
-    if (std::max(t256, t320) < 128) return PSERVE_OK;           // half the chip idle: smaller tiles
+    if (std::max(t256, t320) < 128) return 0;                   // half the chip idle: smaller tiles
     const double c256 = t256 >= 128 ? wide_cost(t256, steps, 0.97, 1.62, 8.0) : 1e30;
     const double c320 = t320 >= 128 ? wide_cost(t320, steps, 1.20, 2.05, 9.0) : 1e30;
     // the other kernel's tiles: 512 blocks at a time, a last round at most half full leaves one block per CU
     const bool geglu = a.epi == EPI_GEGLU, n160 = !geglu && a.N % 160 == 0;
-    const int64_t t128 = cdiv(a.M, 128) * cdiv(a.N, n160 ? 160 : 128), full = t128 / 512, rest = t128 % 512;
+    const int64_t t128 = m_tiles(128) * cdiv(a.N, n160 ? 160 : 128), full = t128 / 512, rest = t128 % 512;
     const double per = n160 ? 0.95 * steps + 9.0 : geglu ? 0.80 * steps + 5.5 : 0.97 * steps + 6.0;
     const double last = n160 ? 1.05 * steps + 11.8 : 1.1 * per;
     const double c128 = full * per + (rest == 0 ? 0.0 : rest <= 256 ? 0.75 * last : last);
-    if (c128 <= std::min(c256, c320)) return PSERVE_OK;
-    *handled = true;
-    return c256 <= c320 ? launch_wide<4, 2, 2, 4>(a, st) : launch_wide<2, 4, 5, 2>(a, st);
+    return c128 <= std::min(c256, c320) ? 0 : c256 <= c320 ? 256 : 320;
+}
+
+bool gemm_takes_two(const GemmArgs& a, int dtype, int mode) { return dtype == PSERVE_BF16 && mode == 0 && a.B2 && wide_select(a) != 0; }
+
+int gemm_wide_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
+    const int rows = wide_select(a);
+    *handled = rows != 0;
+    if (rows == 256) return launch_wide<4, 2, 2, 4>(a, st);
+    if (rows == 320) return launch_wide<2, 4, 5, 2>(a, st);
+    return PSERVE_OK;
 }
 
 }  // namespace pserve

@@ -66,8 +66,10 @@ int gn_apply(const GroupNormArgs& a, const PatchGeom& g, int dtype, bool silu, b
 // Per-token LayerNorm over the C channels (biased variance) of the patches of `act`; out [T][C] at the same token
 // positions.  Affine part: gamma / beta [C] of the block dtype, or (gamma == nullptr) the adaptive form
 // xhat * (1 + scale) + shift with shift = mod[slot * mod_ld + c], scale = mod[slot * mod_ld + C + c], slot = owner[patch].
+// mod_txt (with patch_rc [P][2]): the table of the text patches (patch_rc[2p] < 0), mod being that of the image patches.
 int layer_norm(const void* x, const void* gamma, const void* beta, const float* mod, int64_t mod_ld, const int32_t* owner,
-               int32_t C, float eps, const PatchGeom& g, int dtype, void* out, ActiveList act, hipStream_t st);
+               int32_t C, float eps, const PatchGeom& g, int dtype, void* out, ActiveList act, hipStream_t st,
+               const float* mod_txt = nullptr, const int32_t* patch_rc = nullptr);
 // Fill the one-pixel ring of every active padded patch from the interiors of its neighbours (zeros outside the image).
 int halo_gather(void* apad, const int32_t* halo_src, const PatchGeom& g, int32_t C, int32_t ring, int dtype,
                 ActiveList act, hipStream_t st);
@@ -122,7 +124,16 @@ struct GemmArgs {
     // between blocks (conv_split_bytes says how much it needs).  Not shared with a call that may run at the same time.
     float* split_ws;
     size_t split_ws_bytes;
+    // Optional second problem in the same launch: the rows of another patch list (act2, at most M2 of them) with weights,
+    // bias and gate of their own, everything else alike.  Only where gemm_takes_two() says so.
+    const void* B2;
+    const float* bias2;
+    const float* rowscale2;
+    ActiveList act2;
+    int32_t M2;
 };
+// true if gemm(a, ...) with its second problem will take a kernel that runs both in one launch
+bool gemm_takes_two(const GemmArgs& a, int dtype, int mode);
 // scratch a 3x3 convolution of M rows, N output and K input channels over this patch geometry can use (0: none)
 size_t conv_split_bytes(const PatchGeom& g, int32_t M, int32_t N, int32_t K, int dtype, int mode);
 // true if gemm(a, ...) will take a kernel that fills a.stats (the caller otherwise runs gn_stats on the output)

@@ -347,7 +347,8 @@ __global__ void gn_apply_kernel(const T* __restrict__ x, const float* __restrict
 template <typename T, int VPL>
 __global__ void __launch_bounds__(256)
 layer_norm_kernel(const T* __restrict__ x, const T* __restrict__ gamma, const T* __restrict__ beta,
-                  const float* __restrict__ mod, int64_t mod_ld, const int32_t* __restrict__ owner, int32_t C, int32_t S,
+                  const float* __restrict__ mod, int64_t mod_ld, const int32_t* __restrict__ owner,
+                  const float* __restrict__ mod_txt, const int32_t* __restrict__ patch_rc, int32_t C, int32_t S,
                   int32_t LPT, float eps, ActiveList act, T* __restrict__ out) {
     constexpr int VN = Vec<T>::N;
     int p = blockIdx.x;
@@ -358,7 +359,8 @@ layer_norm_kernel(const T* __restrict__ x, const T* __restrict__ gamma, const T*
     const int CV = C / VN;
     const int sub = threadIdx.x % LPT, tl = threadIdx.x / LPT, tpb = blockDim.x / LPT;
     uint4 graw[VPL], braw[VPL];
-    const float* mrow = mod ? mod + (int64_t)owner[p] * mod_ld : nullptr;     // adaptive form: [shift | scale] of the request
+    // adaptive form: [shift | scale] of the request, of the patch's stream where there are two
+    const float* mrow = mod ? (mod_txt && patch_rc[2 * p] < 0 ? mod_txt : mod) + (int64_t)owner[p] * mod_ld : nullptr;
     if (!mod) {
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
@@ -520,20 +522,21 @@ int gn_apply(const GroupNormArgs& a, const PatchGeom& g, int dtype, bool silu, b
 
 template <typename T>
 static void launch_layer_norm(const void* x, const void* gamma, const void* beta, const float* mod, int64_t mod_ld,
-                              const int32_t* owner, int32_t C, float eps, const PatchGeom& g, void* out, ActiveList act,
-                              int LPT, int VPL, hipStream_t st) {
+                              const int32_t* owner, const float* mod_txt, const int32_t* patch_rc, int32_t C, float eps,
+                              const PatchGeom& g, void* out, ActiveList act, int LPT, int VPL, hipStream_t st) {
     const int tpb = 256 / LPT;
     // one token per lane group while that gives at most ~16 blocks per CU, else more tokens per group
     int64_t per = 1;
     while (per < 8 && g.P * cdiv(g.S, tpb * per) > 4096) per *= 2;
     dim3 grid(g.P, (unsigned)std::max<int64_t>(1, std::min<int64_t>(cdiv(g.S, tpb * per), 65535)));
-#define PS_LN(V) case V: layer_norm_kernel<T, V><<<grid, 256, 0, st>>>((const T*)x, (const T*)gamma, (const T*)beta, mod, mod_ld, owner, C, g.S, LPT, eps, act, (T*)out); break
+#define PS_LN(V) case V: layer_norm_kernel<T, V><<<grid, 256, 0, st>>>((const T*)x, (const T*)gamma, (const T*)beta, mod, mod_ld, owner, mod_txt, patch_rc, C, g.S, LPT, eps, act, (T*)out); break
     switch (VPL) { PS_LN(1); PS_LN(2); PS_LN(3); PS_LN(4); PS_LN(5); PS_LN(6); PS_LN(7); PS_LN(8); }
 #undef PS_LN
 }
 
 int layer_norm(const void* x, const void* gamma, const void* beta, const float* mod, int64_t mod_ld, const int32_t* owner,
-               int32_t C, float eps, const PatchGeom& g, int dtype, void* out, ActiveList act, hipStream_t st) {
+               int32_t C, float eps, const PatchGeom& g, int dtype, void* out, ActiveList act, hipStream_t st,
+               const float* mod_txt, const int32_t* patch_rc) {
     PS_REQUIRE((gamma && beta) || (mod && owner), "LayerNorm: neither gamma / beta nor a modulation table");
     if (gamma) mod = nullptr;
     const int vn = dtype == PSERVE_BF16 ? 8 : 4;
@@ -546,8 +549,8 @@ int layer_norm(const void* x, const void* gamma, const void* beta, const float* 
         const int v = (int)cdiv(CV, l);
         if (v <= 8 && v * l - CV < waste) { LPT = l; VPL = v; waste = v * l - CV; }
     }
-    if (dtype == PSERVE_BF16) launch_layer_norm<uint16_t>(x, gamma, beta, mod, mod_ld, owner, C, eps, g, out, act, LPT, VPL, st);
-    else launch_layer_norm<float>(x, gamma, beta, mod, mod_ld, owner, C, eps, g, out, act, LPT, VPL, st);
+    if (dtype == PSERVE_BF16) launch_layer_norm<uint16_t>(x, gamma, beta, mod, mod_ld, owner, mod_txt, patch_rc, C, eps, g, out, act, LPT, VPL, st);
+    else launch_layer_norm<float>(x, gamma, beta, mod, mod_ld, owner, mod_txt, patch_rc, C, eps, g, out, act, LPT, VPL, st);
     return check_launch("layer_norm_kernel");
 }
 

@@ -74,3 +74,22 @@ def test_shared_convolution_tiles(name):
     w = wl.make_workload(cfg)
     err = rel_err(_forward(w, 0), _forward(w, 1))
     assert np.isfinite(err) and err < 1e-2, err
+
+
+@pytest.mark.parametrize("res,L", [([(32, 32)] * 9 + [(24, 32), (16, 48)], 77), ([(48, 48)] * 5, 320)])
+def test_both_streams_of_a_joint_block_in_one_launch(res, L):
+    """Row tiles of the image and of the text patches in one launch (weights, bias and gate change between tiles)."""
+    cfg = wl.custom_config(res, (8, 8), C=768, G=32, heads=12, stages=("MMDIT",), dtype="bf16", ctx_len=L, ctx_dim=768, temb_dim=128,
+                           seed=57)
+    w = wl.make_workload(cfg)
+    out = []
+    for mode in (0, 1):
+        ps.set_kernel_mode(mode)
+        try:
+            run = GpuRun(w)
+            y = run.forward()
+            out.append([a.float().cpu().numpy() for a in run.plan.reassemble(y) + [run.plan.text_gather(y)]])
+        finally:
+            ps.set_kernel_mode(0)
+    err = rel_err(*out)
+    assert np.isfinite(err) and err < 1e-2, err
