@@ -897,6 +897,7 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
     auto gn_args = [&](const void* in, const void* gamma, const void* beta) {
         GroupNormArgs a;
         a.x = in; a.gamma = gamma; a.beta = beta; a.C = C; a.G = d.G; a.n = plan->n; a.eps = d.eps;
+        a.max_tokens = plan->max_tokens_per_image;
         a.nsplit = cache->nsplit; a.partial = cache->partial; a.scale_shift = cache->scale_shift;
         a.request_offset = request_offset; a.owner = owner; a.neighbour = plan->d_tab[PSERVE_TAB_NEIGHBOUR];
         return a;

@@ -43,6 +43,7 @@ struct GroupNormArgs {
     const void* beta;          // [C]
     int32_t C, G, n;
     float eps;
+    int32_t max_tokens;        // tokens of the largest request
     int32_t nsplit;            // token chunks per patch used for the partial sums
     float* partial;            // [P][nsplit][G][2] (sum, sum of squares)
     float* scale_shift;        // [n][C][2]: y = x*scale + shift for sorted slot s

@@ -194,6 +194,74 @@ gn_finalize_kernel(const float* __restrict__ partial, const int32_t* __restrict_
     }
 }
 
+// Statistics of small requests in one launch: a block is one (request slot, group) and reads the group's channels of all
+// the request's tokens (V channels a load).  Two launches of ~5 us each otherwise, of which the second waits for the first
+// (1,024 tokens x 1280 channels in bf16: 12.0 -> 4.8 us back to back, 24 requests of it 19.9 -> 13.6).  Sums run over x - K, K
+// being the group's first element, in fp32 per thread and fp64 across threads.
+constexpr int GN_DIRECT_THREADS = 512;
+template <typename T, int V>
+__global__ void __launch_bounds__(GN_DIRECT_THREADS)
+gn_direct_kernel(const T* __restrict__ x, const int32_t* __restrict__ request_offset, const T* __restrict__ gamma,
+                 const T* __restrict__ beta, int32_t C, int32_t G, int32_t S, float eps, float* __restrict__ scale_shift) {
+    struct __attribute__((aligned(V * sizeof(T)))) Chunk { T e[V]; };
+    const int s = blockIdx.x, g = blockIdx.y, cg = C / G, per = cg / V;
+    const int p0 = request_offset[s], tokens = (request_offset[s + 1] - p0) * S, items = tokens * per;
+    const T* base = x + (int64_t)p0 * S * C + g * cg;
+    const float k0 = ld_f<T>(base);
+    float s1 = 0.f, s2 = 0.f;
+    constexpr int U = 4;                                        // loads in flight
+    for (int i = threadIdx.x; i < items; i += U * GN_DIRECT_THREADS) {
+        Chunk v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = min(i + u * GN_DIRECT_THREADS, items - 1), t = j / per;
+            v[u] = *reinterpret_cast<const Chunk*>(base + (int64_t)t * C + (j - t * per) * V);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i + u * GN_DIRECT_THREADS < items) {
+#pragma unroll
+                for (int e = 0; e < V; ++e) { const float d = ld_f<T>(&v[u].e[e]) - k0; s1 += d; s2 = fmaf(d, d, s2); }
+            }
+    }
+    double a = (double)s1, b = (double)s2;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        a += __shfl_down(a, off, 64);
+        b += __shfl_down(b, off, 64);
+    }
+    __shared__ double red[GN_DIRECT_THREADS / 64][2];
+    if ((threadIdx.x & 63) == 0) { red[threadIdx.x >> 6][0] = a; red[threadIdx.x >> 6][1] = b; }
+    __syncthreads();
+    a = 0.0;
+    b = 0.0;
+#pragma unroll
+    for (int w = 0; w < GN_DIRECT_THREADS / 64; ++w) { a += red[w][0]; b += red[w][1]; }    // fixed order: deterministic
+    const double cnt = (double)tokens * cg, mean = (double)k0 + a / cnt;
+    double var = (b - a * a / cnt) / cnt;
+    var = var > 0.0 ? var : 0.0;
+    const double rstd = 1.0 / sqrt(var + (double)eps);
+    for (int c = g * cg + threadIdx.x; c < (g + 1) * cg; c += GN_DIRECT_THREADS) {
+        const double sc = rstd * (double)ld_f<T>(gamma + c);
+        float* dst = scale_shift + ((int64_t)s * C + c) * 2;
+        dst[0] = (float)sc;
+        dst[1] = (float)((double)ld_f<T>(beta + c) - mean * sc);
+    }
+}
+
+template <typename T>
+static int gn_direct(const GroupNormArgs& a, const PatchGeom& g, hipStream_t st) {
+    const int cg = a.C / a.G;
+#define PS_GND(V) gn_direct_kernel<T, V><<<dim3(a.n, a.G), GN_DIRECT_THREADS, 0, st>>>((const T*)a.x, a.request_offset, \
+        (const T*)a.gamma, (const T*)a.beta, a.C, a.G, g.S, a.eps, a.scale_shift)
+    if (sizeof(T) == 2 && cg % 8 == 0) PS_GND(16 / sizeof(T));
+    else if (cg % 4 == 0) PS_GND(4);
+    else if (cg % 2 == 0) PS_GND(2);
+    else PS_GND(1);
+#undef PS_GND
+    return check_launch("gn_direct_kernel");
+}
+
 // v * sigmoid(v) with the hardware reciprocal (1 ulp): a true division expands to ten instructions per element
 __device__ __forceinline__ float silu_f(float v) { return v * __builtin_amdgcn_rcpf(1.f + __expf(-v)); }
 
@@ -464,6 +532,13 @@ int gn_stats(const GroupNormArgs& a, const PatchGeom& g, int dtype, hipStream_t 
     PS_REQUIRE(a.C % a.G == 0, "GroupNorm: C %% G != 0");
     const size_t lds = sizeof(float) * 2 * TL * a.C;
     PS_REQUIRE(lds <= 64 * 1024, "GroupNorm: C=%d too wide for the reduction buffer", a.C);
+    // One launch for small requests: a block reads its request's tokens in pieces of C / G channels, so its time grows with
+    // the tokens and, past an L2's 4 MB, with the lines shared between groups.  us, two launches -> one, bf16 / fp32, C = 320,
+    // 6 requests: 1,024 tokens 8.1 -> 4.8 / 7.9 -> 4.8, 2,048 8.5 -> 6.3 / 8.3 -> 12.4, 4,096 9.1 -> 14.2 / 10.0 -> 21.5;
+    // C = 640 bf16, 2,048 tokens: 2 requests 9.9 -> 6.2, 6 (16 MB) 10.2 -> 12.6.
+    const int64_t bytes = (int64_t)g.P * g.S * a.C * dtype_size(dtype);
+    if (a.max_tokens <= 1024 || (a.max_tokens <= 2048 && bytes <= (8 << 20)))
+        return dtype == PSERVE_BF16 ? gn_direct<uint16_t>(a, g, st) : gn_direct<float>(a, g, st);
     dim3 grid(g.P, a.nsplit);
     if (dtype == PSERVE_BF16)
         gn_partial_kernel<uint16_t><<<grid, TL * CV, lds, st>>>((const uint16_t*)a.x, a.C, a.G, g.S, a.nsplit, TL, a.partial);

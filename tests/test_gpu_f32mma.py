@@ -62,3 +62,20 @@ def test_attention_logits_far_apart():
     ref, _ = ob.forward_batch(w.images, cfg.stages, w.params, G=cfg.G, heads=cfg.heads, eps=cfg.eps)
     # a logit of 300 is known to 300 * 2^-23 * sqrt(32 + 64) = 3.5e-4, and so is its exponential
     assert rel_err(got, ref) < 1e-3
+
+
+# GroupNorm statistics in one launch (at most 2,048 tokens a request) and in two: group widths with every load size, a mean
+# far from zero
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("C,G,big", [(64, 32, (16, 12)), (96, 32, (16, 12)), (40, 8, (16, 12)), (256, 8, (16, 12)), (320, 32, (16, 12)),
+                                     (1280, 32, (16, 12)), (64, 32, (46, 44)), (64, 32, (46, 46)), (40, 8, (46, 46))])
+def test_group_norm_of_small_requests(C, G, big, dtype):
+    cfg = wl.custom_config([(1, 2), big, (7, 10)], (1, 2), C=C, G=G, heads=1, stages=("RES1",), dtype=dtype, seed=19)
+    w = wl.make_workload(cfg)
+    w.images[1] = (w.images[1] + 30.0).astype(np.float32)
+    if dtype == "bf16":
+        w.images[1] = wl.bf16_round(w.images[1])
+    got = GpuRun(w).forward_images()
+    ref, _ = ob.forward_batch(w.images, cfg.stages, w.params, G=cfg.G, heads=cfg.heads, eps=cfg.eps)
+    for a, b in zip(got, ref):                                       # each request against its own scale
+        assert rel_err([a], [b]) < tolerance(dtype)
