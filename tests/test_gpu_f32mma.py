@@ -79,3 +79,12 @@ def test_group_norm_of_small_requests(C, G, big, dtype):
     ref, _ = ob.forward_batch(w.images, cfg.stages, w.params, G=cfg.G, heads=cfg.heads, eps=cfg.eps)
     for a, b in zip(got, ref):                                       # each request against its own scale
         assert rel_err([a], [b]) < tolerance(dtype)
+
+
+# LayerNorm with every number of lanes and vectors a token can have, last vectors partly or not there, gamma / beta and adaptive
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("stage", ["LFFN", "AMLP"])
+@pytest.mark.parametrize("C", [8, 24, 40, 72, 136, 264, 520, 640])
+def test_layer_norm_widths(C, stage, dtype):
+    _check(wl.custom_config([(6, 4), (7, 10)], (1, 2), C=C, G=1, heads=1, stages=(stage,), dtype=dtype, seed=23, ffn_mult=8,
+                            temb_dim=32 if stage == "AMLP" else 0))
