@@ -88,3 +88,11 @@ def test_group_norm_of_small_requests(C, G, big, dtype):
 def test_layer_norm_widths(C, stage, dtype):
     _check(wl.custom_config([(6, 4), (7, 10)], (1, 2), C=C, G=1, heads=1, stages=(stage,), dtype=dtype, seed=23, ffn_mult=8,
                             temb_dim=32 if stage == "AMLP" else 0))
+
+
+# wide modulation projections: two and four request slots a block, sets of slots and channel ranges that are not full, both streams
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [2, 3, 5])
+def test_modulation_of_many_slots(n, dtype):
+    _check(wl.custom_config([(2, 2), (2, 4), (4, 2), (2, 2), (6, 2)][:n], (2, 2), C=696, G=1, heads=1, stages=("AMLP",), dtype=dtype,
+                            seed=29, ffn_mult=8, temb_dim=83))
