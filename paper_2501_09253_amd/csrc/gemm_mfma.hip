@@ -1197,7 +1197,7 @@ int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
     *handled = true;
     const bool has_t = a.seg[0].transposed || a.seg[1].transposed || a.seg[2].transposed;
     // N a multiple of 160: 128 x 160 tiles, two blocks per CU (wavefront tile 32 x 160).  Against the 256 x 160 tile
-    // the rounds are the same: 34 -> 28 us (13,312 x 640 x 640), 68 -> 63 us (K = 2560), 80 -> 72 us
+    // the rounds were the same: 34 -> 28 us (13,312 x 640 x 640), 68 -> 63 us (K = 2560), 80 -> 72 us
     // (13.4 k x 1280 x 1280), 165 -> 137 us (79 k x 640 x 640).  The fused q/k/v projections (N = 1920, 3840, with the
     // transposed V^T segment and its long epilogue of 8-byte stores) gain 6-11 % over 128 x 128 tiles as well.
     // From 208 tiles on (1,694 x 2560 x 2048, 224 tiles: 39 us against 44 with 128 x 64; 1,024 x 3840 x 1280, 192: 21.8 against 19.6).
@@ -1209,23 +1209,18 @@ int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
     // whole round) and 128 x 128 with two blocks per CU (512 per round; a last round that is at most half full leaves
     // one block per CU, which runs faster alone: about 0.65 of a round).  A full round of either does the same work
     // in about the same time (measured at K = 1536 and 6144), so the cost is rounds x outputs per CU and round.
-    int bn_a = 0;
-    if (a.N % 160 == 0 && m256 * (a.N / 160) >= 160) bn_a = 160;
-    else if (a.N % 128 == 0 && m256 * (a.N / 128) >= 160) bn_a = 128;
-    if (bn_a) {
-        const int64_t tiles_a = m256 * (a.N / bn_a);
+    if (a.N % 128 == 0 && m256 * (a.N / 128) >= 160) {
+        const int64_t tiles_a = m256 * (a.N / 128);
         if (tiles128 >= 512) {
-            const double cost_a = (double)cdiv(tiles_a, 256) * 256 * bn_a;
+            const double cost_a = (double)cdiv(tiles_a, 256) * 256 * 128;
             const int64_t full = tiles128 / 512, rest = tiles128 % 512;
             const double cost_b = ((double)full + (rest == 0 ? 0.0 : (rest <= 256 ? 0.65 : 1.0))) * 2 * 128 * 128;
             if (cost_b < cost_a) return launch<128, 128, false, 2, 2, 2, false>(a, st);
         }
-        if (bn_a == 160) return launch<256, 160, false, 4, 1, 2, true>(a, st);
         return launch<256, 128, false, 4, 1, 2, true>(a, st);
     }
     const bool small = a.N % 64 == 0 && m128 * cdiv(a.N, 320) < 128;
-    if (!small) {
-        if (a.N % 320 == 0) return launch<128, 320, false, 2, 2, 2, true>(a, st);
+    if (!small) {                                               // (multiples of 320 are taken above)
         if (a.N % 256 == 0) return launch<128, 256, false, 2, 2, 2, true>(a, st);
         if (a.N % 128 == 0) return launch<128, 128, false, 2, 2, 3, true>(a, st);
     }

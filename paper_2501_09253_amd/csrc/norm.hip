@@ -7,12 +7,13 @@
 // border pixels of same-image neighbour patches, zeros where the neighbour is absent
 // ("Patch-Tailored Diffusion Operators").
 //
-// Three kernels for the norm:
+// Kernels of the norm:
 //   gn_partial_kernel   per (patch, token chunk): per-group mean and sum of squared deviations
 //                       (fp32, shifted sums), 16-byte loads, per-thread channel accumulators,
 //                       LDS tree to groups
 //   gn_finalize_kernel  per (request, group): the partial moments merged in fp64 (shuffles +
 //                       LDS) -> mean, rstd -> per (request, channel) scale and shift
+//   gn_direct_kernel    both of these in one launch, for small requests
 //   gn_apply_kernel     y = x*scale + shift (+SiLU), written plain or into the interior of
 //                       the padded patch buffer the convolution reads
 // Reductions are deterministic (no float atomics).

@@ -5,7 +5,7 @@
 //   1. the input is copied into the padded patch layout and its rims are pushed to the neighbours (the apply pass
 //      of the GroupNorm without a scale table: the "Patch Edge Stitcher" of the paper as a plain copy);
 //   2. DOWN2: one implicit GEMM whose rows are OUTPUT tokens (p, y, x) reading the padded pixels (2y + ty, 2x + tx);
-//      UP2:   four implicit GEMMs, one per output parity (a, b), whose rows are INPUT tokens (p, y, x): the nine taps
+//      UP2:   four implicit GEMMs in one launch, one per output parity (a, b), with rows = INPUT tokens (p, y, x): the nine taps
 //             of output pixel (2y + a, 2x + b) fall on 2 x 2 input pixels, so the weights are merged into four taps per
 //             class when the operator is created (4/9 of the multiply-adds of the plain form).
 #include "kernels.h"
