@@ -1101,10 +1101,7 @@ static int launch(const GemmArgs& a, hipStream_t st) {
 
 // shapes the MFMA kernels take at all
 static bool mfma_eligible(const GemmArgs& a) {
-    // the kernels stage both operands by buffer loads with 32-bit byte offsets from the tensors' bases
-    const int64_t a_rows = a.conv ? (int64_t)a.geom.P * a.geom.pS : (int64_t)a.M;
-    const bool fits = a_rows * a.lda < ((int64_t)1 << 30) && (int64_t)a.taps * a.N * a.K * std::max(1, a.classes) < ((int64_t)1 << 30);
-    return a.K % 64 == 0 && a.lda % 8 == 0 && !((uintptr_t)a.A & 15) && !((uintptr_t)a.B & 15) && fits;
+    return a.K % 64 == 0 && a.lda % 8 == 0 && !((uintptr_t)a.A & 15) && !((uintptr_t)a.B & 15) && gemm_fits32(a);
 }
 
 // Which halo-in-LDS convolution kernel a problem takes (0: none) and the columns one wavefront of it covers.
@@ -1114,13 +1111,10 @@ static bool mfma_eligible(const GemmArgs& a) {
 static int conv_select(const GemmArgs& a, ConvTile* ct, int* wave_cols = nullptr) {
     int wc = 0, sel = 0;
     const bool plain3x3 = a.taps == 9 && (a.tap_w == 0 || a.tap_w == 3) && a.a_mul <= 1 && !a.a_dy && !a.a_dx && !a.o_mul;
-    // the kernels address the padded patch buffer and the weights with 32-bit byte offsets below 2^31
-    const bool fits32 = (int64_t)a.geom.P * a.geom.pS * a.lda < ((int64_t)1 << 30) &&
-                        (int64_t)a.taps * a.N * a.K < ((int64_t)1 << 30);
     // no gate, no GELU, no transposed segment; a per-request bias only where a wavefront's 64 rows lie in one patch (the
     // kernels compile the epilogue without those paths)
     const bool lean = a.seg[0].scale == 1.f && !a.rowscale && !a.act_gelu && (!a.rowbias || (a.geom.S % 64 == 0 && a.geom.pw <= 64 && 64 % a.geom.pw == 0));
-    if (plain3x3 && fits32 && lean && a.epi == EPI_ROUTE && a.seg_cols % 32 == 0 && a.seg_cols == a.N && !a.seg[0].transposed) {
+    if (plain3x3 && gemm_fits32(a) && lean && a.epi == EPI_ROUTE && a.seg_cols % 32 == 0 && a.seg_cols == a.N && !a.seg[0].transposed) {
         if (a.N % 160 == 0 && conv_tile(a, 256, 384, ct)) { sel = 1; wc = 160; }
         // small patches (8 x 8: four segments of 10 x 10 pixels per 256 rows) need more halo slots than that tile's LDS
         // has beside three weight stages; with two weight stages 416 slots fit

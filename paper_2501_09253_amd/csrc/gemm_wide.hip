@@ -449,8 +449,7 @@ static int launch_wide(const GemmArgs& a, hipStream_t st) {
 static bool wide_eligible(const GemmArgs& a, int wave_cols) {
     if (a.conv || a.taps != 1 || a.rowbias || a.stats || a.K % 64 != 0 || a.lda % 8 != 0 || wide_end(a) < 0) return false;
     if (((uintptr_t)a.A | (uintptr_t)a.B | (uintptr_t)a.bias | (uintptr_t)a.res) & 15) return false;
-    // operands are addressed with 32-bit byte offsets below 2^31
-    if ((int64_t)a.M * a.lda >= ((int64_t)1 << 30) || (int64_t)a.N * a.K >= ((int64_t)1 << 30)) return false;
+    if (!gemm_fits32(a)) return false;
     if (a.epi == EPI_GEGLU)
         return wave_cols == 2 * GEGLU_GROUP && a.N % 128 == 0 && !((uintptr_t)a.seg[0].ptr & 15) && a.seg[0].ld % 8 == 0;
     if (a.N % 64 != 0 || a.seg_cols % 64 != 0 || (a.res && a.ldr % 8 != 0)) return false;
@@ -505,6 +504,26 @@ int gemm_wide_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
     if (rows == 256) return launch_wide<4, 2, 2, 4>(a, st);
     if (rows == 320) return launch_wide<2, 4, 5, 2>(a, st);
     return PSERVE_OK;
+}
+
+// For tests (host only, no part of the ABI): the rows of the tile such a layer takes here, 0: another kernel's.  P patches of
+// S tokens; rows: those of the layer's patch list, rows2: of a second problem's, 0: none.  flags: 1 last segment transposed,
+// 2 residual, 4 gate, 8 GELU, 16 value-gate pairs, 32 rows without a patch list.
+extern "C" int pserve_test_linear_tile(int32_t P, int32_t S, int32_t rows, int32_t rows2, int32_t N, int32_t K, int32_t seg_cols,
+                                       int32_t flags) {
+    GemmArgs a{};
+    void* some = reinterpret_cast<void*>(64);           // tested for alignment, never read
+    static const int32_t list = 0;
+    a.A = a.B = some; a.lda = a.K = K; a.N = N; a.M = rows; a.taps = 1; a.seg_cols = seg_cols; a.ldr = N;
+    a.geom.P = P; a.geom.S = S; a.tokens_are_rows = !(flags & 32);
+    for (int s = 0; s < 3; ++s) { a.seg[s].ptr = some; a.seg[s].ld = 8; a.seg[s].scale = 1.f; }
+    if (flags & 1) a.seg[N / seg_cols - 1].transposed = 1;
+    if (flags & 2) a.res = some;
+    if (flags & 4) a.rowscale = a.rowscale2 = static_cast<float*>(some);
+    a.act_gelu = (flags & 8) != 0;
+    a.epi = flags & 16 ? EPI_GEGLU : EPI_ROUTE;
+    if (rows2) { a.B2 = some; a.M2 = rows2; a.act.active = a.act.count = a.act2.active = a.act2.count = &list; }
+    return wide_select(a);
 }
 
 }  // namespace pserve

@@ -133,6 +133,16 @@ struct GemmArgs {
     ActiveList act2;
     int32_t M2;
 };
+// Rows of A a problem can address: where rows are tokens, any token of the batch, however few patches its list has (the two
+// lists of a joint batch lie interleaved in one token matrix).
+inline int64_t gemm_a_rows(const GemmArgs& a) {
+    return a.conv ? (int64_t)a.geom.P * a.geom.pS : a.tokens_are_rows ? (int64_t)a.geom.P * a.geom.S : (int64_t)a.M;
+}
+// The bf16 matrix kernels stage both operands by buffer loads with 32-bit byte offsets below 2^31 from the tensors' bases.
+inline bool gemm_fits32(const GemmArgs& a) {
+    return gemm_a_rows(a) * a.lda < ((int64_t)1 << 30) &&
+           (int64_t)a.taps * a.N * a.K * std::max(1, a.classes) < ((int64_t)1 << 30);
+}
 // true if gemm(a, ...) with its second problem will take a kernel that runs both in one launch
 bool gemm_takes_two(const GemmArgs& a, int dtype, int mode);
 // scratch a 3x3 convolution of M rows, N output and K input channels over this patch geometry can use (0: none)
