@@ -38,7 +38,7 @@ enum : int {
     EPF_ALL = 31
 };
 template <int BM, int BN, bool GEGLU, int WGM = 2, int WGN = 2, bool MAY_STAT = true, int FEAT = EPF_ALL>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[BM / WGM / 32][BN / WGN / 32], uint8_t* smem,
+__device__ __forceinline__ void gemm_epilogue(const GemmCore& a, f32x16 (&acc)[BM / WGM / 32][BN / WGN / 32], uint8_t* smem,
                                               const int32_t* s_tok, int n0, const float* bias_pre = nullptr) {
     constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;     // WGM x WGN wavefront grid
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -567,7 +567,10 @@ struct ConvTile {
     // ceil(2^32 / d) for d = seg_pix, pw + 2, seg_tokens, pw: x / d == __umulhi(x, m) for the small x of the set-up
     // (x * d < 2^32; a true integer division is ~40 instructions, and 28 of them sat in front of the first halo load)
     uint32_t m_seg_pix, m_hw, m_seg_tokens, m_pw;
-    int32_t splits;                                 // blocks that share a tile's channel chunks (1: none)
+};
+struct SharedConvTile : ConvTile {
+    float* ws;                                      // GemmArgs::split_ws
+    int32_t splits;                                 // blocks that share a tile's channel chunks
 };
 __device__ __forceinline__ int div_small(int x, uint32_t m, int d) { return d == 1 ? x : (int)__umulhi((uint32_t)x, m); }
 
@@ -580,7 +583,7 @@ __device__ __forceinline__ int div_small(int x, uint32_t m, int d) { return d ==
 // few values it keeps across the loop cost the other form 5 %).
 template <int BM, int BN, int WGM, int WGN, int APIX, int NSB, int KS, bool SPLIT>
 __global__ void __launch_bounds__(256 * KS)
-conv_mfma_kernel(GemmArgs a, ConvTile ct) {
+conv_mfma_kernel(GemmCore a, std::conditional_t<SPLIT, SharedConvTile, ConvTile> ct) {
     constexpr int BK = 64, CH = 8;
     constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
     constexpr int B_LD = BN * CH / 256, A_LD = APIX * CH / 256;
@@ -641,9 +644,11 @@ conv_mfma_kernel(GemmArgs a, ConvTile ct) {
     const int b_lane = (int)(((int64_t)(n0 + lr) * a.K + gc * 8) * 2);   // byte offset of this lane's first weight row
     const int64_t b_row32 = (int64_t)32 * a.K;
     const int64_t b_tap_stride = (int64_t)a.N * a.K;
-    // first channel chunk of this block, and their number
-    const int kbase = SPLIT ? a.K / BK * part / ct.splits : 0;
-    const int kchunks = SPLIT ? a.K / BK * (part + 1) / ct.splits - kbase : a.K / BK;
+    int kbase = 0, kchunks = a.K / BK;              // first channel chunk of this block, and their number
+    if constexpr (SPLIT) {
+        kbase = a.K / BK * part / ct.splits;
+        kchunks = a.K / BK * (part + 1) / ct.splits - kbase;
+    }
     int itap = 0, ikc = 0;                          // (tap, chunk) of the next weight stage to issue; clamps at the last step
 #pragma unroll
     for (int t = 0; t < NSB; ++t) {
@@ -904,7 +909,7 @@ conv_mfma_kernel(GemmArgs a, ConvTile ct) {
     }
     if constexpr (SPLIT) {
         // fp32 partial sums [share][row of the tile grid][N]: 128 contiguous bytes per row and store
-        float* dst = a.split_ws + ((int64_t)part * (m_tiles * BM) + m0 + wm * WM + 4 * fh) * a.N + n0 + wn * WN + fr;
+        float* dst = ct.ws + ((int64_t)part * (m_tiles * BM) + m0 + wm * WM + 4 * fh) * a.N + n0 + wn * WN + fr;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -1047,23 +1052,23 @@ static int conv_splits(int64_t tiles, int64_t kchunks) {
 }
 
 template <int BM, int BN, int WGM, int WGN, int APIX, int NSB, int KS = 1>
-static int launch_conv(const GemmArgs& a, ConvTile& ct, hipStream_t st) {
+static int launch_conv(const GemmArgs& a, const ConvTile& ct, hipStream_t st) {
     constexpr size_t lds = (size_t)(NSB * BN + 2 * APIX) * 128 + BM * sizeof(int32_t) + 64 * sizeof(int32_t);
     static_assert(lds <= 160 * 1024, "conv LDS budget");
     const int64_t mt = cdiv(a.M, BM), nt = a.N / BN;
-    ct.splits = conv_splits(mt * nt, a.K / 64);
+    const int splits = conv_splits(mt * nt, a.K / 64);
     const int slab = split_slab(a.stats ? a.N / a.stats_G : 8);
-    if (!a.split_ws || a.split_ws_bytes < sizeof(float) * ct.splits * mt * BM * a.N || slab == 0) ct.splits = 1;
-    if (ct.splits == 1) {
+    if (splits == 1 || !a.split_ws || a.split_ws_bytes < sizeof(float) * splits * mt * BM * a.N || slab == 0) {
         PS_SET_LDS_ONCE((conv_mfma_kernel<BM, BN, WGM, WGN, APIX, NSB, KS, false>), lds);
         conv_mfma_kernel<BM, BN, WGM, WGN, APIX, NSB, KS, false><<<(unsigned)(8 * cdiv(mt, 8) * nt), 256 * KS, lds, st>>>(a, ct);
         return check_launch("conv_mfma_kernel");
     }
     PS_SET_LDS_ONCE((conv_mfma_kernel<BM, BN, WGM, WGN, APIX, NSB, KS, true>), lds);
-    conv_mfma_kernel<BM, BN, WGM, WGN, APIX, NSB, KS, true><<<(unsigned)(8 * cdiv(nt * ct.splits, 8) * mt), 256 * KS, lds, st>>>(a, ct);
+    conv_mfma_kernel<BM, BN, WGM, WGN, APIX, NSB, KS, true><<<(unsigned)(8 * cdiv(nt * splits, 8) * mt), 256 * KS, lds, st>>>(
+        a, SharedConvTile{ct, a.split_ws, splits});
     PS_TRY(check_launch("conv_mfma_kernel"));
     split_reduce_kernel<<<dim3((unsigned)cdiv(a.M, 64), (unsigned)cdiv(a.N, slab)), SPLIT_RL * slab / 8, 0, st>>>(
-        a, ct.splits, (int)(mt * BM), slab);
+        a, splits, (int)(mt * BM), slab);
     return check_launch("split_reduce_kernel");
 }
 
