@@ -197,8 +197,10 @@ gn_finalize_kernel(const float* __restrict__ partial, const int32_t* __restrict_
 
 // Statistics of small requests in one launch: a block is one (request slot, group) and reads the group's channels of all
 // the request's tokens (V channels a load).  Two launches of ~5 us each otherwise, of which the second waits for the first
-// (1,024 tokens x 1280 channels in bf16: 12.0 -> 4.8 us back to back, 24 requests of it 19.9 -> 13.6).  Sums run over x - K, K
-// being the group's first element, in fp32 per thread and fp64 across threads.
+// (1,024 tokens x 1280 channels in bf16: 12.1 -> 5.4 us back to back, 24 requests of it 19.8 -> 13.4).  A thread keeps mean
+// and sum of squared deviations, the U * V elements of an iteration around their own mean and merged into it (Chan, Golub,
+// LeVeque: all terms positive), so one far-off value costs no digits of the others; threads are merged in fp64.  (Sums of
+// x - K with one K for the block were 0.6 us faster there and lost 3 digits of the variance when K was 1,000 deviations out.)
 constexpr int GN_DIRECT_THREADS = 512;
 template <typename T, int V>
 __global__ void __launch_bounds__(GN_DIRECT_THREADS)
@@ -208,8 +210,7 @@ gn_direct_kernel(const T* __restrict__ x, const int32_t* __restrict__ request_of
     const int s = blockIdx.x, g = blockIdx.y, cg = C / G, per = cg / V;
     const int p0 = request_offset[s], tokens = (request_offset[s + 1] - p0) * S, items = tokens * per;
     const T* base = x + (int64_t)p0 * S * C + g * cg;
-    const float k0 = ld_f<T>(base);
-    float s1 = 0.f, s2 = 0.f;
+    float k0 = 0.f, n = 0.f, mean = 0.f, m2 = 0.f;              // moments of x - k0 over the n elements read so far
     constexpr int U = 4;                                        // loads in flight
     for (int i = threadIdx.x; i < items; i += U * GN_DIRECT_THREADS) {
         Chunk v[U];
@@ -218,14 +219,32 @@ gn_direct_kernel(const T* __restrict__ x, const int32_t* __restrict__ request_of
             const int j = min(i + u * GN_DIRECT_THREADS, items - 1), t = j / per;
             v[u] = *reinterpret_cast<const Chunk*>(base + (int64_t)t * C + (j - t * per) * V);
         }
+        if (n == 0.f) k0 = ld_f<T>(&v[0].e[0]);
+        float d[U][V], sum[U], dev[U], cnt = 0.f;               // a chain of sums for every load
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (i + u * GN_DIRECT_THREADS < items) {
+        for (int u = 0; u < U; ++u) {
+            const bool in = i + u * GN_DIRECT_THREADS < items;
+            cnt += in ? (float)V : 0.f;
+            sum[u] = 0.f;
 #pragma unroll
-                for (int e = 0; e < V; ++e) { const float d = ld_f<T>(&v[u].e[e]) - k0; s1 += d; s2 = fmaf(d, d, s2); }
-            }
+            for (int e = 0; e < V; ++e) { d[u][e] = ld_f<T>(&v[u].e[e]) - k0; sum[u] += d[u][e]; }
+            sum[u] = in ? sum[u] : 0.f;
+        }
+        const float local = ((sum[0] + sum[1]) + (sum[2] + sum[3])) / cnt;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            dev[u] = 0.f;
+#pragma unroll
+            for (int e = 0; e < V; ++e) { const float r = d[u][e] - local; dev[u] = fmaf(r, r, dev[u]); }
+            dev[u] = i + u * GN_DIRECT_THREADS < items ? dev[u] : 0.f;
+        }
+        const float delta = local - mean, share = cnt / (n + cnt);
+        mean = fmaf(delta, share, mean);
+        m2 += ((dev[0] + dev[1]) + (dev[2] + dev[3])) + delta * delta * n * share;
+        n += cnt;
     }
-    double a = (double)s1, b = (double)s2;
+    const double at = (double)k0 + (double)mean;
+    double a = (double)n * at, b = (double)m2 + (double)n * at * at;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         a += __shfl_down(a, off, 64);
@@ -238,15 +257,15 @@ gn_direct_kernel(const T* __restrict__ x, const int32_t* __restrict__ request_of
     b = 0.0;
 #pragma unroll
     for (int w = 0; w < GN_DIRECT_THREADS / 64; ++w) { a += red[w][0]; b += red[w][1]; }    // fixed order: deterministic
-    const double cnt = (double)tokens * cg, mean = (double)k0 + a / cnt;
-    double var = (b - a * a / cnt) / cnt;
+    const double total = (double)tokens * cg, mu = a / total;
+    double var = b / total - mu * mu;
     var = var > 0.0 ? var : 0.0;
     const double rstd = 1.0 / sqrt(var + (double)eps);
     for (int c = g * cg + threadIdx.x; c < (g + 1) * cg; c += GN_DIRECT_THREADS) {
         const double sc = rstd * (double)ld_f<T>(gamma + c);
         float* dst = scale_shift + ((int64_t)s * C + c) * 2;
         dst[0] = (float)sc;
-        dst[1] = (float)((double)ld_f<T>(beta + c) - mean * sc);
+        dst[1] = (float)((double)ld_f<T>(beta + c) - mu * sc);
     }
 }
 

@@ -81,6 +81,23 @@ def test_group_norm_of_small_requests(C, G, big, dtype):
         assert rel_err([a], [b]) < tolerance(dtype)
 
 
+# the first value of every group 30 to 10,000 deviations out: the statistics of the others keep their digits.  Without the
+# residual, away from that pixel, against the largest value there; the bar of the other fp32 tests.
+@pytest.mark.parametrize("far", [30.0, 1e3, 1e4])
+@pytest.mark.parametrize("C,G", [(320, 32), (320, 8)])
+def test_group_norm_with_a_far_off_first_value(C, G, far):
+    cfg = wl.custom_config([(32, 32), (8, 16)], (8, 8), C=C, G=G, heads=1, stages=("RES1",), seed=31)
+    w = wl.make_workload(cfg)
+    for im in w.images:
+        im[::C // G, 0, 0] = far
+    got = GpuRun(w).forward_images()
+    ref, _ = ob.forward_batch(w.images, cfg.stages, w.params, G=cfg.G, heads=cfg.heads, eps=cfg.eps)
+    for a, b, x in zip(got, ref, w.images):
+        a, b = (np.asarray(v, np.float64) - x for v in (a, b))
+        err = rel_err([a[:, 2:]], [b[:, 2:]])
+        assert np.isfinite(err) and err < 1e-4, err
+
+
 # LayerNorm with every number of lanes and vectors a token can have, last vectors partly or not there, gamma / beta and adaptive
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("stage", ["LFFN", "AMLP"])
