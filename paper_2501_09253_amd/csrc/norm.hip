@@ -597,11 +597,14 @@ int gn_stats(const GroupNormArgs& a, const PatchGeom& g, int dtype, hipStream_t 
     const size_t lds = sizeof(float) * 2 * TL * a.C;
     PS_REQUIRE(lds <= 64 * 1024, "GroupNorm: C=%d too wide for the reduction buffer", a.C);
     // One launch for small requests: a block reads its request's tokens in pieces of C / G channels, so its time grows with
-    // the tokens and, past an L2's 4 MB, with the lines shared between groups.  us, two launches -> one, bf16 / fp32, C = 320,
-    // 6 requests: 1,024 tokens 8.1 -> 4.8 / 7.9 -> 4.8, 2,048 8.5 -> 6.3 / 8.3 -> 12.4, 4,096 9.1 -> 14.2 / 10.0 -> 21.5;
-    // C = 640 bf16, 2,048 tokens: 2 requests 9.9 -> 6.2, 6 (16 MB) 10.2 -> 12.6.
-    const int64_t bytes = (int64_t)g.P * g.S * a.C * dtype_size(dtype);
-    if (a.max_tokens <= 1024 || (a.max_tokens <= 2048 && bytes <= (8 << 20)))
+    // its elements and, past an L2's 4 MB, with the lines shared between groups.  us, two launches -> one:
+    // G = 32 at 1,024 tokens, 1 .. 24 requests of 64 .. 1280 channels: 6.2 .. 27 -> 3.4 .. 21, always faster; at 2,048, 6
+    // requests of C = 320: bf16 8.5 -> 6.3, fp32 (16 MB) 8.3 -> 12.4; bf16 C = 640: 2 requests 9.9 -> 6.2, 6 (16 MB) 10.3 -> 12.2.
+    // Few wide groups up to 1,024 tokens: always faster too (fp32, G = 1: C = 320 36.4 -> 9.4 at 256, 37.4 -> 29.6 at 1,024).  At 2,048 the block's
+    // elements decide (131,072: fp32 11.8 -> 13.2; 655,360: 37.5 -> 56.4, bf16 35.9 -> 40.0; 81,920, bf16: 12.3 -> 7.3), and more
+    // than 32 groups share too many lines (G = 64, 3 requests: fp32 C = 320 7.4 -> 11.4, bf16 C = 640 9.0 -> 11.4).
+    const int64_t bytes = (int64_t)g.P * g.S * a.C * dtype_size(dtype), block = (int64_t)a.max_tokens * (a.C / a.G);
+    if (a.max_tokens <= 1024 || (a.max_tokens <= 2048 && bytes <= (8 << 20) && block <= 100000 && a.G <= 32))
         return dtype == PSERVE_BF16 ? gn_direct<uint16_t>(a, g, st) : gn_direct<float>(a, g, st);
     dim3 grid(g.P, a.nsplit);
     if (dtype == PSERVE_BF16)
