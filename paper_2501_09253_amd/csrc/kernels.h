@@ -85,7 +85,9 @@ struct GemmSeg {
 enum { EPI_ROUTE = 0, EPI_GEGLU = 1 };
 // What every kernel takes.  A convolution whose tiles are not shared takes this alone: with the fields of GemmArgs among its
 // arguments it waited for more of them before its first loads (two convolutions of 29,696 tokens x 320 channels with their
-// norms, split and reassembly, mean over ten placements of the buffers: 164.2 against 163.7 us).
+// norms, split and reassembly, mean over ten placements of the buffers: 164.2 against 163.7 us).  Arguments are fetched in
+// pieces of up to 32 bytes by dependent reads, so their offsets count in short kernels: `geom` at a multiple of eight bytes,
+// 10.9 / 5.0 / 4.4 -> 10.6 / 4.8 / 4.2 us for three fp32 products of 832 rows.
 struct GemmCore {
     const void* A;             // linear: [rows][lda]; conv: padded patch buffer
     int64_t lda;
@@ -97,6 +99,9 @@ struct GemmCore {
     // (one parity class of a nearest-up convolution, whose rows are INPUT tokens)
     int32_t tap_w, a_mul, a_dy, a_dx;
     int32_t o_mul, o_dy, o_dx, o_S, o_pw;
+    // 4: the four parity classes (2a + b) of a nearest-up convolution in one call: a_dy = o_dy = a, a_dx = o_dx = b, and
+    // the weights are [class][taps][N][K].  0: one problem as described by the fields above.
+    int32_t classes;
     PatchGeom geom;
     ActiveList act;            // row compaction by patch (rows are tokens)
     int32_t tokens_are_rows;   // 1: row ids are token ids (act applies); 0: plain row ids (M rows)
@@ -123,9 +128,6 @@ struct GemmCore {
     int32_t stats_G, stats_slots;
 };
 struct GemmArgs : GemmCore {
-    // 4: the four parity classes (2a + b) of a nearest-up convolution in one call: a_dy = o_dy = a, a_dx = o_dx = b, and
-    // the weights are [class][taps][N][K].  0: one problem as described by the fields above.
-    int32_t classes;
     // Optional scratch for partial sums (fp32): a convolution with too few tiles for the chip shares the K range of a tile
     // between blocks (conv_split_bytes says how much it needs).  Not shared with a call that may run at the same time.
     float* split_ws;
