@@ -170,7 +170,8 @@ attn_f32mma_kernel(AttnArgs a, int group) {
     const T* Kp = (const T*)a.K + k0 * C + h * d;
     const T* Vp = VT ? (const T*)a.V + (int64_t)h * d * a.ldv + k0 : (const T*)a.V + k0 * a.ldv + h * d;
     // staging: vector v of a lane is row (v * 64 + lane) / (D / 4) of the tile; rows past the last key are clamped to it
-    // (their scores are masked, their probabilities zero).  VT: channel row, four keys a vector.
+    // (their scores are masked, their probabilities zero) and their values staged as zeros (zero times a last value that is
+    // not finite would be NaN).  VT: channel row, four keys a vector.
     constexpr int VR = D / 4, VK = KT / 4;
     const int ch = (lane % VR) * 4, chc = FULL ? ch : min(ch, d - 4);        // the lane's channels (64 is a multiple of VR)
     AtRaw<T> rk[NL], rv[VT ? 1 : NL];
@@ -214,6 +215,11 @@ attn_f32mma_kernel(AttnArgs a, int group) {
             *reinterpret_cast<at_f32x4*>(sK + (i / VR) * LK + ch) = in ? rk[v].get() : zero;
             if constexpr (VT) *reinterpret_cast<at_f32x4*>(sV + (i / VK) * LV + (i % VK) * 4) = rvt[v];
             else *reinterpret_cast<at_f32x4*>(sV + (i / VR) * LV + ch) = in ? rv[v].get() : zero;
+        }
+        if (const int left = nk - t * KT; left < KT) {  // ragged last tile
+#pragma unroll 1
+            for (int i = lane; i < KT * D; i += 64)
+                if ((VT ? i % KT : i / D) >= left) sV[VT ? (i / KT) * LV + i % KT : (i / D) * LV + i % D] = 0.f;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();

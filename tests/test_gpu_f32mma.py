@@ -53,6 +53,26 @@ def test_attention_with_reuse(dtype):
                             reuse_p=0.5, seed=13))
 
 
+# an infinite cached value in the last key of a request (72 and 108 keys: the last tile is ragged) gives infinities where its
+# probability times weight does, and no NaN.  36-token patches of 64-wide bf16 heads: the transposed layout.
+@pytest.mark.parametrize("dtype,heads", [("f32", 2), ("bf16", 2), ("bf16", 1)])
+def test_attention_infinite_last_value(dtype, heads):
+    cfg = wl.custom_config([(6, 12), (18, 6)], (6, 6), C=64, G=8, heads=heads, stages=("LSATTN",), dtype=dtype, reuse_p=0.5, seed=37)
+    w = wl.make_workload(cfg)
+    for r, v in zip(w.reuse, w.cache["0.V"]):
+        r[:] = False
+        r[-1, -1] = True
+        v[5, -1, -1] = np.inf
+    run = GpuRun(w)
+    run.load_cache()
+    got = run.forward_images(reuse=w.reuse)
+    with np.errstate(invalid="ignore"):
+        ref, _ = ob.forward_batch(w.images, cfg.stages, w.params, G=cfg.G, heads=cfg.heads, eps=cfg.eps, reuse=w.reuse, cache=w.cache)
+    for a, b in zip(got, ref):
+        assert np.isinf(b).any() and np.array_equal(np.isnan(a), np.isnan(b))
+        assert np.array_equal(np.where(np.isinf(a), np.sign(a), 0), np.where(np.isinf(b), np.sign(b), 0))
+
+
 def test_attention_logits_far_apart():
     """fp32 logits over a range of a few hundred (queries scaled up): the running maximum moves in every tile."""
     cfg = wl.custom_config([(16, 24), (8, 8)], (8, 8), C=64, G=8, heads=2, stages=("LSATTN",), seed=17)
