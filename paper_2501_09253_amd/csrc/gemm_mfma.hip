@@ -1160,6 +1160,12 @@ size_t conv_split_bytes(const PatchGeom& g, int32_t M, int32_t N, int32_t K, int
 }
 
 int gemm_wide_bf16(const GemmArgs& a, hipStream_t st, bool* handled);     // gemm_wide.hip
+// For tests (host only, no part of the ABI): 1 if the 3x3 convolutions of such a batch (bf16, C to C channels) share tiles.
+extern "C" int pserve_test_conv_shares(int32_t P, int32_t ph, int32_t pw, int32_t C) {
+    const PatchGeom g{P, ph * pw, ph, pw, pw + 2, (ph + 2) * (pw + 2)};
+    return conv_split_bytes(g, P * ph * pw, C, C, PSERVE_BF16, 0) > 0;
+}
+
 
 int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
     *handled = false;

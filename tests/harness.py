@@ -87,6 +87,15 @@ class GpuRun:
         return [to_host(a) for a in self.plan.reassemble(y)]
 
 
+def joint_layers_in_one_launch(cfg) -> bool:
+    """Whether all four layers of a bf16 joint block take the image and the text rows together (host side of the dispatch)."""
+    C, F, S, n = cfg.C, cfg.ffn_mult * cfg.C, cfg.patch[0] * cfg.patch[1], len(cfg.resolutions)
+    image, text = sum(h * w for h, w in cfg.resolutions), n * -(-cfg.ctx_len // S) * S
+    transposed, res, gate, gelu = 1, 2, 4, 8
+    return all(ps.lib().pserve_test_linear_tile((image + text) // S, S, image, text, N, K, seg, flags)
+               for N, K, seg, flags in ((3 * C, C, C, transposed), (C, C, C, res + gate), (F, C, F, gelu), (C, F, C, res + gate)))
+
+
 def rel_err(got, ref) -> float:
     """max |got - ref| / max |ref| over a list of arrays."""
     num = max(float(np.abs(np.asarray(g, dtype=np.float64) - r).max()) for g, r in zip(got, ref))

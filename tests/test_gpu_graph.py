@@ -9,7 +9,7 @@ import torch
 
 import paper_2501_09253_amd as ps
 import workloads as wl
-from harness import GpuRun, to_dev
+from harness import GpuRun, joint_layers_in_one_launch, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -64,11 +64,14 @@ def test_step_replayed_from_a_graph_equals_eager(stages, reuse, stats):
             assert torch.equal(o, r), f"eager after replay {k}"
 
 
-def test_joint_block_replayed_from_a_graph_equals_eager():
-    """A joint text-image block: its text stream's kernels run on the library's side stream, forked from and joined to
-    the captured stream twice per stage; the capture must hold both streams' work."""
-    cfg = wl.custom_config([(32, 32), (16, 48), (16, 16)], (16, 16), C=128, G=32, heads=2, stages=(wl.MMDIT, wl.MMDIT),
-                           dtype="bf16", ctx_len=40, ctx_dim=128, seed=72, temb_dim=96)
+@pytest.mark.parametrize("res,C,one", [([(32, 32), (16, 48), (16, 16)], 128, False), ([(48, 48)] * 5, 768, True)])
+def test_joint_block_replayed_from_a_graph_equals_eager(res, C, one):
+    """A joint text-image block.  Small batches: its text stream's kernels run on the library's side stream, forked from and
+    joined to the captured stream twice per stage, and the capture must hold both streams' work.  Larger ones: every layer is
+    one launch on the captured stream."""
+    cfg = wl.custom_config(res, (16, 16), C=C, G=32, heads=C // 64, stages=(wl.MMDIT, wl.MMDIT), dtype="bf16", ctx_len=40, ctx_dim=C,
+                           seed=72, temb_dim=96)
+    assert joint_layers_in_one_launch(cfg) == one
     w = wl.make_workload(cfg)
     run = GpuRun(w)
     ps.profile_enable(False)
