@@ -199,7 +199,9 @@ void pserve_block_free(pserve_block_t* block);
 
 /* ---- per (plan, block) activation store: the cached operand tensors of the patch-level
  * cache ("Patch-aware Caching Strategy": operands of context operators and the block
- * output of the previous step, per patch) plus all scratch the forward pass needs.
+ * output of the previous step, per patch) plus all scratch the forward pass needs (for bf16
+ * residual convolutions of few patches also up to 42 MB of partial sums: the forward pass then
+ * shares a tile's input channels between blocks).
  * with_slots = 0 allocates scratch only (then reuse_mask must be NULL). */
 int  pserve_cache_create(const pserve_plan_t* plan, const pserve_block_t* block, int with_slots,
                          pserve_cache_t** out);

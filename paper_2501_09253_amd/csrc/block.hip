@@ -702,7 +702,9 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
         for (int k = 0; k < d.n_stages; ++k)
             if (needs_temb(d.stages[k]))
                 macs += (int64_t)plan->n * d.temb_dim * (d.stages[k] == PSERVE_RES2T ? d.C : d.stages[k] == PSERVE_MMDIT ? 12 * d.C : 3 * d.C);
-        // A joint block's two projections are one launch (23 us for 4 slots, 57 MB of weights) and run inline.
+        // A joint block's two projections are one launch (23 us for 4 slots, 57 MB of weights) and run inline, at the start of
+        // their stage.  Those of later stages beside the stage before: 2,064 -> 2,060 us for two stages of 11,520 + 616 tokens
+        // x 1536, 4,080 -> 4,065 for four, but 705 -> 717 for three of 4,352 + 462 x 768, which fork and join already.
         c->side_temb = !joint && macs >= (int64_t)8 << 20;
         // A joint block whose layers do not take both streams in one launch (small batches, fp32) runs the text stream's
         // kernels (few tiles each: latency bound) on the side stream, beside the image stream's.

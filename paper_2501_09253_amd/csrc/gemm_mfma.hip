@@ -1,10 +1,11 @@
 // bf16 MFMA GEMM / implicit-GEMM 3x3 convolution for gfx950.
 //
 // Two kernels share one epilogue:
-//   gemm_mfma_kernel  block tile 256 x 160 / 256 x 128 / 128 x 160 (four wavefronts stacked along M) or 128 x BN
-//                     (2 x 2), K in steps of 64, A and B tiles staged by direct global -> LDS loads into a ring of
-//                     2-4 stages (one barrier per step); linear layers (one tap) and the fallback form of the
-//                     convolution (nine taps re-load A).  The 128-row tiles with two stages run two blocks per CU.
+//   gemm_mfma_kernel  block tile 256 x 128 / 128 x 160 / 128 x 128 (four wavefronts stacked along M) or 128 x 256 / 128 /
+//                     64 (2 x 2), K in steps of 64, A and B tiles staged by direct global -> LDS loads into a ring of
+//                     two or three stages (one barrier per step); the linear layers gemm_wide.hip (asked first) does not
+//                     take, and convolutions conv_mfma_kernel does not take (taps re-load A): level changes, odd patches.
+//                     The 128-row tiles with two stages run two blocks per CU.
 //   conv_mfma_kernel  3x3 convolution with the haloed activation tile kept in LDS across the nine taps;
 //                     preferred tile 256 x 160 with four wavefronts stacked along M, each doubled by a second
 //                     wavefront that takes the other half of every K step (two wavefronts per SIMD).
@@ -1159,13 +1160,13 @@ size_t conv_split_bytes(const PatchGeom& g, int32_t M, int32_t N, int32_t K, int
     return z > 1 ? sizeof(float) * z * mt * bm[sel] * (size_t)N : 0;
 }
 
-int gemm_wide_bf16(const GemmArgs& a, hipStream_t st, bool* handled);     // gemm_wide.hip
 // For tests (host only, no part of the ABI): 1 if the 3x3 convolutions of such a batch (bf16, C to C channels) share tiles.
 extern "C" int pserve_test_conv_shares(int32_t P, int32_t ph, int32_t pw, int32_t C) {
     const PatchGeom g{P, ph * pw, ph, pw, pw + 2, (ph + 2) * (pw + 2)};
     return conv_split_bytes(g, P * ph * pw, C, C, PSERVE_BF16, 0) > 0;
 }
 
+int gemm_wide_bf16(const GemmArgs& a, hipStream_t st, bool* handled);     // gemm_wide.hip
 
 int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
     *handled = false;
@@ -1205,7 +1206,9 @@ int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
     // the rounds were the same: 34 -> 28 us (13,312 x 640 x 640), 68 -> 63 us (K = 2560), 80 -> 72 us
     // (13.4 k x 1280 x 1280), 165 -> 137 us (79 k x 640 x 640).  The fused q/k/v projections (N = 1920, 3840, with the
     // transposed V^T segment and its long epilogue of 8-byte stores) gain 6-11 % over 128 x 128 tiles as well.
-    // From 208 tiles on (1,694 x 2560 x 2048, 224 tiles: 39 us against 44 with 128 x 64; 1,024 x 3840 x 1280, 192: 21.8 against 19.6).
+    // From 208 tiles on: the 128 x 64 tiles, 2.5 times as many, run 512 at a time, so up to 204 of these they take one round
+    // and then two.  us, 128 x 160 / 128 x 64: 200 tiles K = 320 16.8 / 13.1, 640 20.1 / 15.8, 1280 26.6 / 22.8, 2560 40.3 / 33.8,
+    // 5120 69.3 / 59.5; 204 tiles K = 640 18.9 / 16.8; 208 tiles 17.0 / 17.4, 20.2 / 21.0, 27.0 / 30.0, 42.7 / 46.3, 69.3 / 82.6.
     if (a.N % 160 == 0 && m128 * (a.N / 160) * std::max(1, a.classes) >= 208) return launch<128, 160, false, 4, 1, 2, false>(a, st);
     const int64_t tiles128 = a.N % 128 == 0 ? m128 * (a.N / 128) : 0;
     // a transposed segment otherwise: 128 x 128, two blocks per CU (70 -> 62 us and 212 -> 184 us against 256-row tiles)
