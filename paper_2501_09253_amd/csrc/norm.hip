@@ -197,10 +197,10 @@ gn_finalize_kernel(const float* __restrict__ partial, const int32_t* __restrict_
 
 // Statistics of small requests in one launch: a block is one (request slot, group) and reads the group's channels of all
 // the request's tokens (V channels a load).  Two launches of ~5 us each otherwise, of which the second waits for the first
-// (1,024 tokens x 1280 channels in bf16: 12.1 -> 5.4 us back to back, 24 requests of it 19.8 -> 13.4).  A thread keeps mean
+// (1,024 tokens x 1280 channels in bf16: 12.1 -> 5.0 us back to back, 24 requests of it 19.8 -> 13.1).  A thread keeps mean
 // and sum of squared deviations, the U * V elements of an iteration around their own mean and merged into it (Chan, Golub,
 // LeVeque: all terms positive), so one far-off value costs no digits of the others; threads are merged in fp64.  (Sums of
-// x - K with one K for the block were 0.6 us faster there and lost 3 digits of the variance when K was 1,000 deviations out.)
+// x - K with one K for the block took the same time and lost 3 digits of the variance when K was 1,000 deviations out.)
 constexpr int GN_DIRECT_THREADS = 512;
 template <typename T, int V>
 __global__ void __launch_bounds__(GN_DIRECT_THREADS)
@@ -210,7 +210,8 @@ gn_direct_kernel(const T* __restrict__ x, const int32_t* __restrict__ request_of
     const int s = blockIdx.x, g = blockIdx.y, cg = C / G, per = cg / V;
     const int p0 = request_offset[s], tokens = (request_offset[s + 1] - p0) * S, items = tokens * per;
     const T* base = x + (int64_t)p0 * S * C + g * cg;
-    float k0 = 0.f, n = 0.f, mean = 0.f, m2 = 0.f;              // moments of x - k0 over the n elements read so far
+    float n = 0.f, mean = 0.f, m2 = 0.f;                        // moments of x - k0 over the n elements read so far
+    float k0 = 0.f;                                             // fp32: the thread's first element (8 bits of bf16 need none)
     constexpr int U = 4;                                        // loads in flight
     for (int i = threadIdx.x; i < items; i += U * GN_DIRECT_THREADS) {
         Chunk v[U];
@@ -219,32 +220,34 @@ gn_direct_kernel(const T* __restrict__ x, const int32_t* __restrict__ request_of
             const int j = min(i + u * GN_DIRECT_THREADS, items - 1), t = j / per;
             v[u] = *reinterpret_cast<const Chunk*>(base + (int64_t)t * C + (j - t * per) * V);
         }
-        if (n == 0.f) k0 = ld_f<T>(&v[0].e[0]);
-        float d[U][V], sum[U], dev[U], cnt = 0.f;               // a chain of sums for every load
+        if (sizeof(T) == 4 && n == 0.f) k0 = ld_f<T>(&v[0].e[0]);
+        auto value = [&](int u, int e) { const float f = ld_f<T>(&v[u].e[e]); return sizeof(T) == 4 ? f - k0 : f; };
+        float sum[U], dev[U], cnt = 0.f;                        // a chain of sums for every load
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const bool in = i + u * GN_DIRECT_THREADS < items;
             cnt += in ? (float)V : 0.f;
             sum[u] = 0.f;
 #pragma unroll
-            for (int e = 0; e < V; ++e) { d[u][e] = ld_f<T>(&v[u].e[e]) - k0; sum[u] += d[u][e]; }
+            for (int e = 0; e < V; ++e) sum[u] += value(u, e);
             sum[u] = in ? sum[u] : 0.f;
         }
-        const float local = ((sum[0] + sum[1]) + (sum[2] + sum[3])) / cnt;
+        // (a mean that is an ulp off shifts nothing: the deviations are taken from the value used)
+        const float local = ((sum[0] + sum[1]) + (sum[2] + sum[3])) * __builtin_amdgcn_rcpf(cnt);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             dev[u] = 0.f;
 #pragma unroll
-            for (int e = 0; e < V; ++e) { const float r = d[u][e] - local; dev[u] = fmaf(r, r, dev[u]); }
+            for (int e = 0; e < V; ++e) { const float d = value(u, e) - local; dev[u] = fmaf(d, d, dev[u]); }
             dev[u] = i + u * GN_DIRECT_THREADS < items ? dev[u] : 0.f;
         }
-        const float delta = local - mean, share = cnt / (n + cnt);
+        const float delta = local - mean, share = cnt * __builtin_amdgcn_rcpf(n + cnt);
         mean = fmaf(delta, share, mean);
         m2 += ((dev[0] + dev[1]) + (dev[2] + dev[3])) + delta * delta * n * share;
         n += cnt;
     }
     const double at = (double)k0 + (double)mean;
-    double a = (double)n * at, b = (double)m2 + (double)n * at * at;
+    double a = (double)n * at, b = (double)m2 + a * at;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         a += __shfl_down(a, off, 64);
@@ -598,13 +601,14 @@ int gn_stats(const GroupNormArgs& a, const PatchGeom& g, int dtype, hipStream_t 
     PS_REQUIRE(lds <= 64 * 1024, "GroupNorm: C=%d too wide for the reduction buffer", a.C);
     // One launch for small requests: a block reads its request's tokens in pieces of C / G channels, so its time grows with
     // its elements and, past an L2's 4 MB, with the lines shared between groups.  us, two launches -> one:
-    // G = 32 at 1,024 tokens, 1 .. 24 requests of 64 .. 1280 channels: 6.2 .. 27 -> 3.4 .. 21, always faster; at 2,048, 6
-    // requests of C = 320: bf16 8.5 -> 6.3, fp32 (16 MB) 8.3 -> 12.4; bf16 C = 640: 2 requests 9.9 -> 6.2, 6 (16 MB) 10.3 -> 12.2.
-    // Few wide groups up to 1,024 tokens: always faster too (fp32, G = 1: C = 320 36.4 -> 9.4 at 256, 37.4 -> 29.6 at 1,024).  At 2,048 the block's
-    // elements decide (131,072: fp32 11.8 -> 13.2; 655,360: 37.5 -> 56.4, bf16 35.9 -> 40.0; 81,920, bf16: 12.3 -> 7.3), and more
-    // than 32 groups share too many lines (G = 64, 3 requests: fp32 C = 320 7.4 -> 11.4, bf16 C = 640 9.0 -> 11.4).
+    // G = 32 at 1,024 tokens, 1 .. 24 requests of 64 .. 1280 channels: 6.2 .. 27 -> 3.4 .. 20, always faster; at 2,048, 6
+    // requests of C = 320: bf16 9.6 -> 6.0, fp32 (16 MB) 9.5 -> 12.0; bf16 C = 640: 3 requests 10.0 -> 8.3, 6 (16 MB) 10.2 -> 12.1.
+    // Few wide groups up to 1,024 tokens: always faster too (fp32, G = 1: C = 320 35.9 -> 8.3 at 256, 37.0 -> 25.6 at 1,024).  At
+    // 2,048 the block's elements decide in fp32 (163,840: 14.5 -> 14.3; 655,360: 37.3 -> 48.7; bf16 35.8 -> 33.8), and more than
+    // 32 groups share too many lines (G = 64, 3 requests: fp32 C = 320 7.4 -> 11.3, bf16 C = 640 9.1 -> 11.4).
     const int64_t bytes = (int64_t)g.P * g.S * a.C * dtype_size(dtype), block = (int64_t)a.max_tokens * (a.C / a.G);
-    if (a.max_tokens <= 1024 || (a.max_tokens <= 2048 && bytes <= (8 << 20) && block <= 100000 && a.G <= 32))
+    if (a.max_tokens <= 1024 ||
+        (a.max_tokens <= 2048 && bytes <= (8 << 20) && a.G <= 32 && (dtype == PSERVE_BF16 || block <= 200000)))
         return dtype == PSERVE_BF16 ? gn_direct<uint16_t>(a, g, st) : gn_direct<float>(a, g, st);
     dim3 grid(g.P, a.nsplit);
     if (dtype == PSERVE_BF16)

@@ -89,7 +89,7 @@ def test_attention_logits_far_apart():
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("C,G,big", [(64, 32, (16, 12)), (96, 32, (16, 12)), (40, 8, (16, 12)), (256, 8, (16, 12)), (320, 32, (16, 12)),
                                      (1280, 32, (16, 12)), (64, 32, (46, 44)), (64, 32, (46, 46)), (40, 8, (46, 46)),
-                                     (64, 1, (16, 12)), (40, 1, (46, 44)), (64, 1, (46, 44)), (64, 64, (46, 44))])
+                                     (64, 1, (16, 12)), (96, 1, (46, 44)), (104, 1, (46, 44)), (64, 64, (46, 44))])
 def test_group_norm_of_small_requests(C, G, big, dtype):
     cfg = wl.custom_config([(1, 2), big, (7, 10)], (1, 2), C=C, G=G, heads=1, stages=("RES1",), dtype=dtype, seed=19)
     w = wl.make_workload(cfg)
