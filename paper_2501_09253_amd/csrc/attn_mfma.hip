@@ -5,7 +5,8 @@
 // patch-major token matrix (RequestOffset of the CSP format times the tokens per patch), so
 // no image is reassembled.  Cross-attention uses the request's own text tokens as keys.
 //
-// Work item = (query tile of 256 compact rows of ONE image, head).  4 wavefronts x 64 queries.
+// Work item = (query tile of 256 compact rows of ONE image, head).  4 wavefronts x 64 queries.  Calls with few items take
+// 128 or 64 rows and share the keys of a block between two or four groups of wavefronts (attn_body).
 // Scores are formed transposed, S^T = K Q^T, so that a lane owns one query column of each
 // 32x32 MFMA tile: the softmax row reductions are in-lane plus one exchange between the two
 // lane halves, and the probabilities leave the accumulators already in the layout of the
@@ -59,36 +60,48 @@ __device__ __forceinline__ int kperm(int r) { return (r & ~12) | ((r & 4) << 1) 
 //     lane's partial row sum shows that a shifted score got large (rare; the exact maximum is then taken, the
 //     accumulators are rescaled and the probabilities recomputed);
 //   * the row sum is taken over the bf16-rounded probabilities, i.e. of exactly what multiplies V.
-// K / V^T tiles of 64 keys are staged by direct global->LDS loads into a ring of three stages, two tiles ahead.
+// K / V^T tiles of 64 keys are staged by direct global->LDS loads into a ring of NS stages, NS - 1 tiles ahead.
+// KG > 1: the block has KG groups of QW wavefronts with a ring each; they take the tiles in turn and meet at the end.  A call
+// of few blocks is a chain of tiles (1 us each with one wavefront a SIMD): the groups shorten it and fill each other's waits.
 extern __shared__ __attribute__((aligned(16))) uint8_t att_smem[];
 
 // Work item of a block: (request slot, head, query tile of that request).  A block's run time goes with the number of
-// keys of its request, so the items run longest first (attn_item_at).  Groups of ATT_GROUP consecutive items are dealt to
-// the XCDs in turn (block b runs on XCD b mod 8 and an XCD starts its blocks in order): the blocks resident on an XCD
-// stream the K / V^T tiles of the same head through that XCD's L2, every XCD gets the same share of the long items, and
-// the short ones fill the last round.
-constexpr int ATT_GROUP = 64;
-__device__ __forceinline__ bool attn_item(const AttnArgs& a, int& s, int& head, int& tile_in_s) {
-    const int64_t seq = blockIdx.x >> 3;
-    return attn_item_at(a, ((seq / ATT_GROUP) * 8 + (blockIdx.x & 7)) * ATT_GROUP + seq % ATT_GROUP, s, head, tile_in_s);
+// keys of its request, so the items run longest first (attn_item_at).  Groups of up to eight consecutive items are dealt to
+// the XCDs in turn (block b runs on XCD b mod 8 and an XCD starts its blocks in order): neighbouring blocks of an XCD
+// stream the K / V^T tiles of the same head through its L2, every XCD gets the same share of the long items, and the short
+// ones fill the last round.  Groups of 64 left XCDs idle below 512 items (40 items of 1,024 keys: all on one XCD, the layer 41.3 -> 34.2 us)
+// and gave some a whole group more than others above; with 4, 8, 16, 32 the layers of 520 and 1,160 items take 140.5 / 137.8 /
+// 139.0 / 141.7 and 245.8 / 243.5 / 245.9 / 245.5 us (64: 142.4, 250.4), and the 16 MB of keys and values of a head of 65,536 tokens
+// cost nothing more (9.57 against 9.55 ms).
+constexpr int ATT_GROUP = 8;
+// BQ: query rows of a block; a tile of the call's tables (128 * a.qt rows) is 128 * a.qt / BQ of them.  r0: its first row.
+template <int BQ>
+__device__ __forceinline__ bool attn_item(const AttnArgs& a, int& s, int& head, int& r0) {
+    const int seq = blockIdx.x >> 3, grp = seq / a.group;
+    const int it = (grp * 8 + (blockIdx.x & 7)) * a.group + (seq - grp * a.group);
+    const int nsub = BQ == 256 ? 1 : 128 * a.qt / BQ;
+    int tile;
+    if (!attn_item_at(a, it / nsub, s, head, tile)) return false;
+    r0 = (tile * nsub + it % nsub) * BQ;
+    return true;
 }
 
-template <int ATT_QT>
+template <int ATT_QT, int QW, int KG, int NS>
 __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
-    constexpr int ATT_BQ = 4 * 32 * ATT_QT;
-    u32x4* sK = reinterpret_cast<u32x4*>(att_smem);            // [ATT_NS][64 keys][8 chunks], chunk ^ ((key>>1)&7)
-    u32x4* sV = sK + ATT_NS * 512;                             // [ATT_NS][64 d][8 chunks of 8 keys], chunk ^ ((d>>1)&7)
-
+    constexpr int ATT_BQ = QW * 32 * ATT_QT, LPO = 8 / QW;      // query rows of the block; loads per wavefront, tile and operand
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = KG == 1 ? wave_all : wave_all % QW, kg = KG == 1 ? 0 : wave_all / QW;     // query rows, key group
     const int fr = lane & 31, fh = lane >> 5;
+    u32x4* sK = reinterpret_cast<u32x4*>(att_smem) + kg * (NS * 1024);     // [NS][64 keys][8 chunks], chunk ^ ((key>>1)&7)
+    u32x4* sV = sK + NS * 512;                                 // [NS][64 d][8 chunks of 8 keys], chunk ^ ((d>>1)&7)
 
-    // ---- which (request slot, head, query tile) ---------------------------------------------------
-    int s, head, tile_in_s;
-    if (!attn_item(a, s, head, tile_in_s)) return;
+    // ---- which (request slot, head, query rows) ---------------------------------------------------
+    int s, head, r0;
+    if (!attn_item<ATT_BQ>(a, s, head, r0)) return;
     const int S = a.geom.S;
     const int rows_s = (a.act_off[s + 1] - a.act_off[s]) * S;            // computed query rows of this image
-    const int r0 = tile_in_s * ATT_BQ;
+    if (ATT_BQ < 256 && r0 >= rows_s) return;
     int64_t k0;
     int nk;
     if (a.cross_len) { k0 = (int64_t)a.perm[s] * a.cross_ld; nk = a.cross_len; }
@@ -106,8 +119,8 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
 #pragma unroll
     for (int qt = 0; qt < ATT_QT; ++qt) {
         int r = r0 + wave * (32 * ATT_QT) + qt * 32 + fr;
-        q_ok[qt] = r < rows_s;
-        if (!q_ok[qt]) r = rows_s - 1;
+        q_ok[qt] = r < rows_s && kg == 0;
+        r = min(r, rows_s - 1);
         const int pi = a.act_off[s] + r / S;
         const int p = a.act.active ? a.act.active[pi] : pi;
         q_tok[qt] = (int64_t)p * S + (r - (r / S) * S);
@@ -116,23 +129,23 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
         for (int ks = 0; ks < 4; ++ks) fq[qt][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + ks * 16));
     }
 
-    // ---- staging by direct loads: a wavefront instruction fills 8 rows x 8 chunk positions; rows lr and lr + 32
+    // ---- staging by direct loads: a wavefront instruction fills 8 rows x 8 chunk positions; rows lr + 8 * QW * i
     const int lc = lane & 7, lr = 8 * wave + (lane >> 3);
-    const int gc = lc ^ ((lr >> 1) & 7);                     // global chunk fetched into position lc (same for both rows)
+    const int gc = lc ^ ((lr >> 1) & 7);                     // global chunk fetched into position lc (same for all rows)
     const uint16_t* k_base = K + k0 * C + head * ATT_D + gc * 8;
     const uint16_t* v_base = V + (int64_t)(head * ATT_D + lr) * a.ldv + k0;
-    const int64_t v_row32 = (int64_t)32 * a.ldv;
+    const int64_t v_row = (int64_t)8 * QW * a.ldv;
     const int steps = (nk + ATT_BKV - 1) / ATT_BKV;
     // A tile that lies inside the sequence is addressed as (uniform base of the tile) + (32-bit byte offset of the lane,
     // the same for every tile), so that its four loads cost no vector arithmetic (a 64-bit multiply per load before:
     // ~30 vector instructions per tile, two of them quarter-rate).  The launch checks that the offsets fit 32 bits.
     const uint8_t* k_uni = reinterpret_cast<const uint8_t*>(K + k0 * C + head * ATT_D);
     const uint8_t* v_uni = reinterpret_cast<const uint8_t*>(V + (int64_t)(head * ATT_D) * a.ldv + k0);
-    uint32_t k_lane[2], v_lane[2];
+    uint32_t k_lane[LPO], v_lane[LPO];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        k_lane[i] = (uint32_t)(((lr + 32 * i) * C + gc * 8) * 2);
-        v_lane[i] = (uint32_t)(((int64_t)(lr + 32 * i) * a.ldv + gc * 8) * 2);
+    for (int i = 0; i < LPO; ++i) {
+        k_lane[i] = (uint32_t)(((lr + 8 * QW * i) * C + gc * 8) * 2);
+        v_lane[i] = (uint32_t)(((int64_t)(lr + 8 * QW * i) * a.ldv + gc * 8) * 2);
     }
     // keys / chunks past the image are clamped to valid ones: their scores are masked, their P is zero
 #define PS_ISSUE_TILE(t_, st_)                                                                                   \
@@ -142,19 +155,19 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
         if ((t_) < steps - 1) {                                                                                  \
             const uint8_t* kt_ = k_uni + (int64_t)(t_) * (ATT_BKV * 2) * C;                                      \
             const uint8_t* vt_ = v_uni + (int64_t)(t_) * (ATT_BKV * 2);                                          \
-            _Pragma("unroll") for (int i = 0; i < 2; ++i)                                                        \
-                __builtin_amdgcn_global_load_lds((const void*)(kt_ + k_lane[i]), (lds_void*)(dk_ + i * 256), 16, 0, 0); \
-            _Pragma("unroll") for (int i = 0; i < 2; ++i)                                                        \
-                __builtin_amdgcn_global_load_lds((const void*)(vt_ + v_lane[i]), (lds_void*)(dv_ + i * 256), 16, 0, 0); \
+            _Pragma("unroll") for (int i = 0; i < LPO; ++i)                                                      \
+                __builtin_amdgcn_global_load_lds((const void*)(kt_ + k_lane[i]), (lds_void*)(dk_ + i * (64 * QW)), 16, 0, 0); \
+            _Pragma("unroll") for (int i = 0; i < LPO; ++i)                                                      \
+                __builtin_amdgcn_global_load_lds((const void*)(vt_ + v_lane[i]), (lds_void*)(dv_ + i * (64 * QW)), 16, 0, 0); \
         } else {                                                                                                 \
             const int kv_ = (steps - 1) * ATT_BKV;                                                               \
-            _Pragma("unroll") for (int i = 0; i < 2; ++i) {                                                      \
-                const int key_ = min(kv_ + lr + 32 * i, nk - 1);                                                 \
-                __builtin_amdgcn_global_load_lds((const void*)(k_base + (int64_t)key_ * C), (lds_void*)(dk_ + i * 256), 16, 0, 0); \
+            _Pragma("unroll") for (int i = 0; i < LPO; ++i) {                                                    \
+                const int key_ = min(kv_ + lr + 8 * QW * i, nk - 1);                                             \
+                __builtin_amdgcn_global_load_lds((const void*)(k_base + (int64_t)key_ * C), (lds_void*)(dk_ + i * (64 * QW)), 16, 0, 0); \
             }                                                                                                    \
             const int vc_ = kv_ + gc * 8 < nk ? kv_ + gc * 8 : 0;                                                \
-            _Pragma("unroll") for (int i = 0; i < 2; ++i)                                                        \
-                __builtin_amdgcn_global_load_lds((const void*)(v_base + i * v_row32 + vc_), (lds_void*)(dv_ + i * 256), 16, 0, 0); \
+            _Pragma("unroll") for (int i = 0; i < LPO; ++i)                                                      \
+                __builtin_amdgcn_global_load_lds((const void*)(v_base + i * v_row + vc_), (lds_void*)(dv_ + i * (64 * QW)), 16, 0, 0); \
         }                                                                                                        \
     }
 
@@ -180,8 +193,9 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) { ksw[i] = (krow[i] >> 1) & 7; vsw[i] = ((fr + 32 * i) >> 1) & 7; }
 
-    PS_ISSUE_TILE(0, 0);
-    PS_ISSUE_TILE(1, 1);
+    // the key groups of the block take the tiles in turn; a group whose tiles are used up loads the last tile again
+    PS_ISSUE_TILE(kg, 0);
+    if (NS == 3) PS_ISSUE_TILE(kg + KG, 1);
 
     // probabilities of query sub-tile QT from its shifted scores minus SH_: exp2, bf16 pack, row sum of the packed values
 #define PS_PROBS(QT, SH_)                                                                                        \
@@ -258,23 +272,61 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
 
     bf16x8 fkn_[4];                                             // key fragments of the second half tile, read ahead
     int st = 0;
-    for (int t = 0; t < steps; ++t) {
-        // own loads of tile t have landed (tile t+1 may be in flight); then tile t is visible to all and the stage of
-        // tile t-1 is free.  A bare s_barrier: __syncthreads() carries a fence that waits for ALL loads in flight.
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");
-        const int st2 = st == 0 ? ATT_NS - 1 : st - 1;          // stage of tile t-1 == stage of tile t+2
-        PS_ISSUE_TILE(t + 2, st2);
+    for (int t0 = 0; t0 < steps; t0 += KG) {
+        // own loads of the group's tile have landed (its next tile may be in flight); then the tile is visible to all and
+        // the stage of the tile before is free.  A bare s_barrier: __syncthreads() carries a fence that waits for ALL loads.
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NS == 3 ? 2 * LPO : 0) : "memory");
+        const int t = t0 + kg;
+        const int st2 = st == 0 ? NS - 1 : st - 1;              // stage of the tile before == stage of the tile loaded now
+        PS_ISSUE_TILE(t + (NS - 1) * KG, st2);
         const int kv0 = t * ATT_BKV;
-        const bool first = t == 0;
-        PS_HALF(st, 0, kv0, first);
-        PS_HALF(st, 1, kv0, false);
-        st = st + 1 == ATT_NS ? 0 : st + 1;
+        const bool first = t0 == 0;
+        if (KG == 1 || t < steps) {
+            PS_HALF(st, 0, kv0, first);
+            PS_HALF(st, 1, kv0, false);
+        }
+        st = st + 1 == NS ? 0 : st + 1;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // no load may still target LDS when the block retires
 #undef PS_HALF
 #undef PS_PROBS
 #undef PS_ISSUE_TILE
 
+    if constexpr (KG > 1) {
+        // The groups' results meet in LDS (the same lane of the same place in every group): common reference, then the sums
+        // in a fixed order.  A group without tiles leaves nothing.
+        static_assert(ATT_QT == 1, "one query sub-tile per wavefront");
+        __syncthreads();
+        float* part = reinterpret_cast<float*>(att_smem) + lane;
+        auto at = [&](int g, int e) -> float& { return part[(((g - 1) * QW + wave) * 34 + e) * 64]; };
+        if (kg > 0) {
+#pragma unroll
+            for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) at(kg, 16 * dt + e) = acc_o[0][dt][e];
+            at(kg, 32) = m_ref[0];
+            at(kg, 33) = l_run[0];
+        }
+        __syncthreads();
+        if (kg > 0) return;
+        const int groups = min(KG, steps);
+        float m = m_ref[0];
+        for (int g = 1; g < groups; ++g) m = fmaxf(m, at(g, 32));
+        const float f0 = __builtin_amdgcn_exp2f(m_ref[0] - m);
+        l_run[0] *= f0;
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc_o[0][dt][e] *= f0;
+        for (int g = 1; g < groups; ++g) {
+            const float f = __builtin_amdgcn_exp2f(at(g, 32) - m);
+            l_run[0] = fmaf(at(g, 33), f, l_run[0]);
+#pragma unroll
+            for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc_o[0][dt][e] = fmaf(at(g, 16 * dt + e), f, acc_o[0][dt][e]);
+        }
+    }
     // ---- O[q][head*64 + d] = O^T / l ; lane holds d = 32*dt + 8*(e/4) + 4*fh + e%4 of query fr
     uint16_t* O = (uint16_t*)a.O;
 #pragma unroll
@@ -305,10 +357,10 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
     }
 }
 
-template <int ATT_QT>
-__global__ void __launch_bounds__(256, ATT_QT == 1 ? 3 : 2)
+template <int QW, int KG, int NS>
+__global__ void __launch_bounds__(64 * QW * KG, KG == 1 ? 3 : 2)
 attn_mfma_kernel(AttnArgs a) {
-    attn_body<ATT_QT>(a, threadIdx.x);
+    attn_body<1, QW, KG, NS>(a, threadIdx.x);
 }
 
 // ---- the software-pipelined form (256 queries per block) ------------------------------------------------------
@@ -346,11 +398,10 @@ attn_pipe_kernel(AttnArgs a) {
     const int fr = lane & 31, fh = lane >> 5;
 
     // ---- which (request slot, head, query tile) ---------------------------------------------------
-    int s, head, tile_in_s;
-    if (!attn_item(a, s, head, tile_in_s)) return;
+    int s, head, r0;
+    if (!attn_item<ATT_BQ>(a, s, head, r0)) return;
     const int S = a.geom.S;
     const int rows_s = (a.act_off[s + 1] - a.act_off[s]) * S;            // computed query rows of this image
-    const int r0 = tile_in_s * ATT_BQ;
     int64_t k0;
     int nk;
     if (a.cross_len) { k0 = (int64_t)a.perm[s] * a.cross_ld; nk = a.cross_len; }
@@ -688,7 +739,7 @@ attn_pipe_kernel(AttnArgs a) {
         // ahead of the loop above
         int tid2 = threadIdx.x;
         asm volatile("" : "+v"(tid2));
-        attn_body<2>(a, tid2);
+        attn_body<2, 4, 1, ATT_NS>(a, tid2);
         return;
     }
 
@@ -946,15 +997,39 @@ int attention_mfma_bf16(const AttnArgs& a, hipStream_t st, bool* handled) {
         attn_cross_kernel<<<(unsigned)(pairs * chunks), 256, 4 * 512 * 16, st>>>(a, chunks);
         return check_launch("attn_cross_kernel");
     }
-    const int64_t items = (int64_t)a.max_tiles * a.heads;
-    const unsigned grid = (unsigned)(8 * ATT_GROUP * cdiv(items, 8 * ATT_GROUP));
-    constexpr int lds = ATT_NS * 2 * 512 * 16;
-    constexpr int lds_pipe = ATT_PNS * 2 * 512 * 16;
-    PS_SET_LDS_ONCE(attn_mfma_kernel<1>, lds);
-    PS_SET_LDS_ONCE(attn_pipe_kernel, lds_pipe);
-    if (a.qt == 1) attn_mfma_kernel<1><<<grid, 256, lds, st>>>(a);
-    else attn_pipe_kernel<<<grid, 256, lds_pipe, st>>>(a);
-    return check_launch("attn_mfma_kernel");
+    auto go = [&](auto kernel, int bq, int threads, int lds, const char* name) -> int {
+        AttnArgs b = a;
+        const int64_t items = (int64_t)a.max_tiles * (128 * a.qt / bq) * a.heads;
+        b.group = (int)std::min<int64_t>(ATT_GROUP, cdiv(items, 8));
+        const unsigned grid = (unsigned)(8 * b.group * cdiv(items, 8 * b.group));
+        kernel<<<grid, threads, lds, st>>>(b);
+        return check_launch(name);
+    };
+#define PS_ATT(QW_, KG_, NS_)                                                                                          \
+    do {                                                                                                               \
+        constexpr int lds_ = KG_ * NS_ * 2 * 512 * 16;                                                                 \
+        PS_SET_LDS_ONCE((attn_mfma_kernel<QW_, KG_, NS_>), lds_);                                                      \
+        return go(attn_mfma_kernel<QW_, KG_, NS_>, 32 * QW_, 64 * QW_ * KG_, lds_, "attn_mfma_kernel");                \
+    } while (0)
+    if (a.qt == 2) {
+        constexpr int lds_pipe = ATT_PNS * 2 * 512 * 16;
+        PS_SET_LDS_ONCE(attn_pipe_kernel, lds_pipe);
+        return go(attn_pipe_kernel, 256, 256, lds_pipe, "attn_pipe_kernel");
+    }
+    // Few items: the keys of a block are shared between groups of wavefronts, and 64 queries instead of 128 where half the
+    // CUs would have no block.  us of an LSATTN layer, 128 queries x 1 group / 128 x 2 / 64 x 4 / 64 x 2: 40 items of 16 key
+    // tiles 34.2 / 32.3 / 29.6 / 30.0; 64 of 64: 65.8 / 53.4 / 41.3 / 45.7; 40 of 4: 35.4 / 36.1 / 35.4 / 34.4; 80 of 4: 30.6 /
+    // 31.4 / 30.7 / 29.9; 160 of 16: 51.3 / 49.2 / 55.0 / 50.0; 160 of 64: 74.2 / 61.8 / 73.4 / 65.9; 240 of 3 (text keys): 43.8 /
+    // 44.7 / 48.7 / 45.1; 320 of 16: 60.7 / 65.8 / 78.0 / 66.9.
+    const int64_t items = (int64_t)a.max_tiles * a.qt * a.heads;
+    const int keys = a.cross_len ? a.cross_len : a.max_rows;
+    if (items <= 128) {
+        if (keys >= 1024) PS_ATT(2, 4, 2);
+        PS_ATT(2, 2, 2);
+    }
+    if (items <= 256 && keys >= 512) PS_ATT(4, 2, 3);
+    PS_ATT(4, 1, 3);
+#undef PS_ATT
 }
 
 }  // namespace pserve

@@ -195,6 +195,7 @@ struct AttnArgs {
     int32_t max_tiles;         // host upper bound of tile_off[n]
     int32_t qt;                // 1 or 2: the tables were built for query tiles of 128 * qt rows
     int32_t max_rows;          // host upper bound of the query rows of one request (its tokens)
+    int32_t group;             // consecutive work items dealt to an XCD at a time (filled in by the launch)
 };
 // Item k of the work list of a call, longest first: request slots from the last (the plan sorts requests by size,
 // largest last) to the first, head-major inside a slot, so that consecutive items are consecutive query tiles of one head.
