@@ -342,7 +342,7 @@ static int attn_f32mma_launch(const AttnArgs& a, hipStream_t st) {
 
 template <typename T>
 static int attn_f32mma(const AttnArgs& a, hipStream_t st) {
-    if constexpr (sizeof(T) == 2)                       // the transposed layout goes with bf16 and 64 channels a head
+    if constexpr (sizeof(T) == 2)                       // the transposed layout: bf16, 64 channels a head, rows past 32-bit offsets
         if (a.v_transposed) return attn_f32mma_launch<T, 64, true, true>(a, st);
 #define PS_AF(DD) (a.d == DD ? attn_f32mma_launch<T, DD, false, true>(a, st) : attn_f32mma_launch<T, DD, false, false>(a, st))
     return a.d <= 32 ? PS_AF(32) : a.d <= 64 ? PS_AF(64) : PS_AF(128);

@@ -46,6 +46,7 @@ typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 constexpr int ATT_NS = 3;        // K / V^T ring depth in 64-key tiles
+constexpr float ATT_TINY = 1.17549435e-38f;
 constexpr float ATT_SUM_MAX = 4096.f;   // a lane's 16-key partial row sum above this moves the softmax reference
 
 // MFMA tile row r of a score tile holds key kperm(r) (bits 2 and 3 swapped): with this order the eight scores a lane
@@ -86,7 +87,7 @@ __device__ __forceinline__ bool attn_item(const AttnArgs& a, int& s, int& head, 
     return true;
 }
 
-template <int ATT_QT, int QW, int KG, int NS>
+template <int ATT_QT, int QW, int KG, int NS, bool RAG>
 __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
     constexpr int ATT_BQ = QW * 32 * ATT_QT, LPO = 8 / QW;      // query rows of the block; loads per wavefront, tile and operand
     const int lane = tid & 63;
@@ -106,6 +107,12 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
     int nk;
     if (a.cross_len) { k0 = (int64_t)a.perm[s] * a.cross_ld; nk = a.cross_len; }
     else { k0 = a.cu_seqlens[s]; nk = a.seq_len ? a.seq_len[s] : a.cu_seqlens[s + 1] - a.cu_seqlens[s]; }
+    // RAG: the request need not start on a 16-byte boundary of the V^T rows.  The keys then start at the boundary before
+    // it; the `lead` keys in front belong to the request before, as those behind the last one may to the next: their scores
+    // are masked and their values zeroed in the fragments (0 times a value that is not finite would be NaN).  The probabilities
+    // keep their 24 bits, in three pieces (three output MFMAs for one: such requests took the fp32 kernel, which keeps them).
+    const int lead = RAG ? (int)(k0 & 7) : 0;
+    if (RAG) { k0 -= lead; nk += lead; }
 
     const uint16_t* Q = (const uint16_t*)a.Q;
     const uint16_t* K = (const uint16_t*)a.K;
@@ -181,7 +188,8 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
     float m_ref[ATT_QT] = {}, l_run[ATT_QT] = {};   // reference maximum (log2 domain) and partial row sums
     f32x16 cinit[ATT_QT];                                       // -m_ref of the lane's query in every element
     f32x16 acc_s[ATT_QT];                                       // shifted scores of one 32-key half tile, per query sub-tile
-    bf16x8 fp[ATT_QT][2];                                       // [query sub-tile][16-key step]: probabilities (B operand)
+    constexpr int NP = RAG ? 3 : 1;                             // bf16 pieces of a probability
+    bf16x8 fp[ATT_QT][NP][2];                                   // [query sub-tile][piece][16-key step]: probabilities (B operand)
 #pragma unroll
     for (int qt = 0; qt < ATT_QT; ++qt)
 #pragma unroll
@@ -198,19 +206,31 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
     if (NS == 3) PS_ISSUE_TILE(kg + KG, 1);
 
     // probabilities of query sub-tile QT from its shifted scores minus SH_: exp2, bf16 pack, row sum of the packed values
+    // (RAG: row sum of the fp32 values, which go into the product as three pieces of eight bits, exactly; a piece that would
+    // be zero is the smallest normal number, since zero times an infinite value would be NaN)
 #define PS_PROBS(QT, SH_)                                                                                        \
     {                                                                                                            \
         sum_ = 0.f;                                                                                              \
         _Pragma("unroll") for (int k2 = 0; k2 < 2; ++k2) {                                                       \
-            uint32_t pk_[4];                                                                                     \
+            u32x4 pk_[NP];                                                                                       \
             _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                                      \
-                const f32x2 pf_ = {__builtin_amdgcn_exp2f(acc_s[QT][8 * k2 + 2 * i] - (SH_)),                    \
-                                   __builtin_amdgcn_exp2f(acc_s[QT][8 * k2 + 2 * i + 1] - (SH_))};               \
-                const bf16x2 pb_ = __builtin_convertvector(pf_, bf16x2);                                         \
-                sum_ = __builtin_amdgcn_fdot2_f32_bf16(pb_, bf16x2{(__bf16)1.f, (__bf16)1.f}, sum_, false);      \
-                pk_[i] = __builtin_bit_cast(uint32_t, pb_);                                                      \
+                f32x2 pf_ = {__builtin_amdgcn_exp2f(acc_s[QT][8 * k2 + 2 * i] - (SH_)),                          \
+                             __builtin_amdgcn_exp2f(acc_s[QT][8 * k2 + 2 * i + 1] - (SH_))};                     \
+                if constexpr (RAG) {                                                                             \
+                    sum_ += pf_[0] + pf_[1];                                                                     \
+                    _Pragma("unroll") for (int q_ = 0; q_ < NP; ++q_) {                                          \
+                        const uint32_t u0_ = __float_as_uint(pf_[0]), u1_ = __float_as_uint(pf_[1]);             \
+                        pk_[q_][i] = __builtin_amdgcn_perm(u1_, u0_, 0x07060302);                                \
+                        pf_[0] = fmaxf(pf_[0] - __uint_as_float(u0_ & 0xFFFF0000u), ATT_TINY);                   \
+                        pf_[1] = fmaxf(pf_[1] - __uint_as_float(u1_ & 0xFFFF0000u), ATT_TINY);                   \
+                    }                                                                                            \
+                } else {                                                                                         \
+                    const bf16x2 pb_ = __builtin_convertvector(pf_, bf16x2);                                     \
+                    sum_ = __builtin_amdgcn_fdot2_f32_bf16(pb_, bf16x2{(__bf16)1.f, (__bf16)1.f}, sum_, false);  \
+                    pk_[0][i] = __builtin_bit_cast(uint32_t, pb_);                                               \
+                }                                                                                                \
             }                                                                                                    \
-            fp[QT][k2] = __builtin_bit_cast(bf16x8, u32x4{pk_[0], pk_[1], pk_[2], pk_[3]});                      \
+            _Pragma("unroll") for (int q_ = 0; q_ < NP; ++q_) fp[QT][q_][k2] = __builtin_bit_cast(bf16x8, pk_[q_]); \
         }                                                                                                        \
     }
     // one 32-key half tile (KT = 0 / 1 of the tile in stage ST): S^T = K Q^T - m_ref, P = 2^S, O^T += V^T P
@@ -241,10 +261,21 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
                 fkn_[ks] = __builtin_bit_cast(bf16x8, sK[(ST) * 512 + krow[1] * 8 + ((2 * ks + fh) ^ ksw[1])]);  \
         }                                                                                                        \
         __builtin_amdgcn_sched_barrier(0);                                                                       \
-        if ((KV0) + ATT_BKV > nk) {                                                                              \
+        if ((KV0) + ATT_BKV > nk || (RAG && (KV0) < lead)) {                                                     \
             _Pragma("unroll") for (int e = 0; e < 16; ++e) {                                                     \
                 const int key_ = (KV0) + 32 * (KT) + 16 * (e >> 3) + 8 * fh + (e & 7);                           \
-                if (key_ >= nk) { _Pragma("unroll") for (int qt = 0; qt < ATT_QT; ++qt) acc_s[qt][e] = -INFINITY; }                            \
+                if (key_ >= nk || (RAG && key_ < lead)) { _Pragma("unroll") for (int qt = 0; qt < ATT_QT; ++qt) acc_s[qt][e] = -INFINITY; } \
+            }                                                                                                    \
+            if (RAG) {                                                                                           \
+                _Pragma("unroll") for (int k2 = 0; k2 < 2; ++k2)                                                 \
+                    _Pragma("unroll") for (int dt = 0; dt < 2; ++dt) {                                           \
+                        u32x4 w_ = __builtin_bit_cast(u32x4, fv_[k2][dt]);                                       \
+                        _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                          \
+                            const int key_ = (KV0) + 32 * (KT) + 16 * k2 + 8 * fh + 2 * i;                       \
+                            w_[i] &= (key_ >= lead && key_ < nk ? 0xFFFFu : 0u) | (key_ + 1 >= lead && key_ + 1 < nk ? 0xFFFF0000u : 0u); \
+                        }                                                                                        \
+                        fv_[k2][dt] = __builtin_bit_cast(bf16x8, w_);                                            \
+                    }                                                                                            \
             }                                                                                                    \
         }                                                                                                        \
         _Pragma("unroll") for (int qt = 0; qt < ATT_QT; ++qt) {                                                       \
@@ -265,8 +296,9 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
             }                                                                                                    \
             l_run[qt] += sum_;                                                                                   \
             _Pragma("unroll") for (int k2 = 0; k2 < 2; ++k2)                                                     \
-                _Pragma("unroll") for (int dt = 0; dt < 2; ++dt)                                                 \
-                    acc_o[qt][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fv_[k2][dt], fp[qt][k2], acc_o[qt][dt], 0, 0, 0); \
+                _Pragma("unroll") for (int q_ = 0; q_ < NP; ++q_)                                                \
+                    _Pragma("unroll") for (int dt = 0; dt < 2; ++dt)                                             \
+                        acc_o[qt][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fv_[k2][dt], fp[qt][q_][k2], acc_o[qt][dt], 0, 0, 0); \
         }                                                                                                        \
     }
 
@@ -357,10 +389,10 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
     }
 }
 
-template <int QW, int KG, int NS>
-__global__ void __launch_bounds__(64 * QW * KG, KG == 1 ? 3 : 2)
+template <int QW, int KG, int NS, bool RAG>
+__global__ void __launch_bounds__(64 * QW * KG, KG == 1 && !RAG ? 3 : 2)
 attn_mfma_kernel(AttnArgs a) {
-    attn_body<1, QW, KG, NS>(a, threadIdx.x);
+    attn_body<1, QW, KG, NS, RAG>(a, threadIdx.x);
 }
 
 // ---- the software-pipelined form (256 queries per block) ------------------------------------------------------
@@ -739,7 +771,7 @@ attn_pipe_kernel(AttnArgs a) {
         // ahead of the loop above
         int tid2 = threadIdx.x;
         asm volatile("" : "+v"(tid2));
-        attn_body<2, 4, 1, ATT_NS>(a, tid2);
+        attn_body<2, 4, 1, ATT_NS, false>(a, tid2);
         return;
     }
 
@@ -983,11 +1015,7 @@ int attention_mfma_bf16(const AttnArgs& a, hipStream_t st, bool* handled) {
     if (a.d != ATT_D || !a.v_transposed || !a.tile_off || !a.act_off || (a.qt != 1 && a.qt != 2)) return PSERVE_OK;
     if (a.C % 8 != 0 || a.ldv % 8 != 0) return PSERVE_OK;
     if ((int64_t)64 * a.ldv * 2 + 128 >= ((int64_t)1 << 32) || (int64_t)64 * a.C * 2 + 128 >= ((int64_t)1 << 32)) return PSERVE_OK;
-    if (a.cross_len) {
-        if (a.cross_ld % 8 != 0) return PSERVE_OK;
-    } else if (a.geom.S % 8 != 0) {
-        return PSERVE_OK;              // image token ranges must start on 16-byte boundaries of the V^T rows
-    }
+    if (a.cross_len && a.cross_ld % 8 != 0) return PSERVE_OK;
     *handled = true;
     if (a.cross_len && a.cross_len <= ATT_XK) {
         // one block per (request, head, chunk of its query tiles): about six blocks per CU in all (three run at once)
@@ -997,6 +1025,10 @@ int attention_mfma_bf16(const AttnArgs& a, hipStream_t st, bool* handled) {
         attn_cross_kernel<<<(unsigned)(pairs * chunks), 256, 4 * 512 * 16, st>>>(a, chunks);
         return check_launch("attn_cross_kernel");
     }
+    // Requests may start inside a 16-byte piece of the V^T rows: the compiled-apart form of attn_body.  us of an LSATTN layer
+    // against the fp32 kernel: 20,736 tokens x 192 in 6 x 6 patches 3,809 -> 727, 3,780 in four requests 96.5 -> 41.4, 900 x 1280
+    // 121 -> 58; errors against 64 bits equal to four digits.
+    const bool rag = !a.cross_len && a.geom.S % 8 != 0;
     auto go = [&](auto kernel, int bq, int threads, int lds, const char* name) -> int {
         AttnArgs b = a;
         const int64_t items = (int64_t)a.max_tiles * (128 * a.qt / bq) * a.heads;
@@ -1008,10 +1040,12 @@ int attention_mfma_bf16(const AttnArgs& a, hipStream_t st, bool* handled) {
 #define PS_ATT(QW_, KG_, NS_)                                                                                          \
     do {                                                                                                               \
         constexpr int lds_ = KG_ * NS_ * 2 * 512 * 16;                                                                 \
-        PS_SET_LDS_ONCE((attn_mfma_kernel<QW_, KG_, NS_>), lds_);                                                      \
-        return go(attn_mfma_kernel<QW_, KG_, NS_>, 32 * QW_, 64 * QW_ * KG_, lds_, "attn_mfma_kernel");                \
+        PS_SET_LDS_ONCE((attn_mfma_kernel<QW_, KG_, NS_, false>), lds_);                                               \
+        PS_SET_LDS_ONCE((attn_mfma_kernel<QW_, KG_, NS_, true>), lds_);                                                \
+        return go(rag ? attn_mfma_kernel<QW_, KG_, NS_, true> : attn_mfma_kernel<QW_, KG_, NS_, false>, 32 * QW_,      \
+                  64 * QW_ * KG_, lds_, "attn_mfma_kernel");                                                           \
     } while (0)
-    if (a.qt == 2) {
+    if (a.qt == 2 && !rag) {
         constexpr int lds_pipe = ATT_PNS * 2 * 512 * 16;
         PS_SET_LDS_ONCE(attn_pipe_kernel, lds_pipe);
         return go(attn_pipe_kernel, 256, 256, lds_pipe, "attn_pipe_kernel");

@@ -243,15 +243,15 @@ __global__ void gather_patches_kernel(const uint4* __restrict__ src, uint4* __re
     uint4* d = dst + (int64_t)p * vec_per_patch;
     for (int64_t i = blockIdx.y * blockDim.x + threadIdx.x; i < vec_per_patch; i += (int64_t)gridDim.y * blockDim.x) d[i] = s[i];
 }
-// The same for a channel-major slot (V^T [C][T]): per channel row, the S tokens of the patch are contiguous.
+// The same for a channel-major slot (V^T [C][ld]): per channel row, the S tokens of the patch are contiguous.
 template <typename T>
-__global__ void gather_patch_cols_kernel(const T* __restrict__ src, T* __restrict__ dst, int64_t T_old, int64_t T_new,
+__global__ void gather_patch_cols_kernel(const T* __restrict__ src, T* __restrict__ dst, int64_t ld_old, int64_t ld_new,
                                          int32_t S, int32_t C, const int32_t* __restrict__ src_of) {
     const int p = blockIdx.x, q = src_of[p];
     if (q < 0) return;
     for (int64_t i = blockIdx.y * blockDim.x + threadIdx.x; i < (int64_t)S * C; i += (int64_t)gridDim.y * blockDim.x) {
         const int64_t c = i / S, t = i - c * S;
-        dst[c * T_new + (int64_t)p * S + t] = src[c * T_old + (int64_t)q * S + t];
+        dst[c * ld_new + (int64_t)p * S + t] = src[c * ld_old + (int64_t)q * S + t];
     }
 }
 __global__ void patch_valid_kernel(const int32_t* __restrict__ src_of, int32_t P, uint8_t* __restrict__ valid) {
@@ -259,9 +259,10 @@ __global__ void patch_valid_kernel(const int32_t* __restrict__ src_of, int32_t P
     if (p < P) valid[p] = src_of[p] >= 0 ? 1 : 0;
 }
 
-// dst[c][t] = src[t][c] (or the reverse), used by the cache load/read hooks for the transposed V slot
+// dst[c][t] = src[t][c] (or the reverse) with rows of ld tokens on the channel-major side, used by the cache load/read hooks
+// for the transposed V slot
 template <typename T>
-__global__ void transpose_tc_kernel(const T* __restrict__ src, T* __restrict__ dst, int64_t Tn, int32_t C, int to_ct) {
+__global__ void transpose_tc_kernel(const T* __restrict__ src, T* __restrict__ dst, int64_t Tn, int64_t ld, int32_t C, int to_ct) {
     __shared__ T tile[32][33];
     const int64_t t0 = (int64_t)blockIdx.x * 32;
     const int c0 = blockIdx.y * 32;
@@ -271,10 +272,10 @@ __global__ void transpose_tc_kernel(const T* __restrict__ src, T* __restrict__ d
             if (t0 + r < Tn && c0 + tx < C) tile[r][tx] = src[(t0 + r) * C + c0 + tx];
         __syncthreads();
         for (int r = ty; r < 32; r += 8)
-            if (c0 + r < C && t0 + tx < Tn) dst[(int64_t)(c0 + r) * Tn + t0 + tx] = tile[tx][r];
+            if (c0 + r < C && t0 + tx < Tn) dst[(int64_t)(c0 + r) * ld + t0 + tx] = tile[tx][r];
     } else {
         for (int r = ty; r < 32; r += 8)
-            if (c0 + r < C && t0 + tx < Tn) tile[r][tx] = src[(int64_t)(c0 + r) * Tn + t0 + tx];
+            if (c0 + r < C && t0 + tx < Tn) tile[r][tx] = src[(int64_t)(c0 + r) * ld + t0 + tx];
         __syncthreads();
         for (int r = ty; r < 32; r += 8)
             if (t0 + r < Tn && c0 + tx < C) dst[(t0 + r) * C + c0 + tx] = tile[tx][r];
@@ -294,6 +295,7 @@ struct pserve_cache_s {
     const pserve_block_t* block = nullptr;
     bool with_slots = false, filled = false, v_transposed = false;
     int32_t nsplit = 1, cross_ld = 0;
+    int64_t v_ld = 0;                         // row stride of the transposed values: T up to whole 16-byte pieces
     void* ping[2] = {};                       // [T][C] stage outputs
     void* apad = nullptr;                     // [P][ph+2][pw+2][C]
     float* partial = nullptr;
@@ -308,7 +310,7 @@ struct pserve_cache_s {
     void* h1[PSERVE_MAX_STAGES] = {};         // RES2: first convolution output (slot H1)
     void* r[PSERVE_MAX_STAGES] = {};          // SATTN: stage input (slot R), only with slots
     void* k[PSERVE_MAX_STAGES] = {};          // SATTN: keys (slot K)
-    void* v[PSERVE_MAX_STAGES] = {};          // SATTN: values (slot V; [C][T] when v_transposed)
+    void* v[PSERVE_MAX_STAGES] = {};          // SATTN: values (slot V; [C][v_ld] when v_transposed)
     void* q = nullptr;                        // [T][C] scaled queries
     void* o = nullptr;                        // [T][C] attention output
     void* u = nullptr;                        // [T][C] normalised tokens
@@ -612,6 +614,7 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
     const size_t TC = (size_t)plan->T * d.C * es;
     const int head_dim = d.heads > 0 ? d.C / d.heads : 0;
     c->v_transposed = d.dtype == PSERVE_BF16 && head_dim == 64 && g_kernel_mode != 1;
+    c->v_ld = (plan->T + 7) / 8 * 8;
     c->nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(cdiv(768, plan->P), std::max(1, plan->S / 32)));
     PS_TRY(c->pool.alloc(&c->ping[0], TC));
     PS_TRY(c->pool.alloc(&c->ping[1], TC));
@@ -648,7 +651,7 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
         if (is_sattn(d.stages[s])) {
             if (with_slots && d.stages[s] == PSERVE_SATTN) PS_TRY(c->pool.alloc(&c->r[s], TC));
             PS_TRY(c->pool.alloc(&c->k[s], TC));
-            PS_TRY(c->pool.alloc(&c->v[s], TC));
+            PS_TRY(c->pool.alloc(&c->v[s], c->v_transposed ? (size_t)c->v_ld * d.C * es : TC));
         }
     }
     if (sattn || xattn) {
@@ -762,9 +765,9 @@ static int slot_copy(const pserve_cache_t* c, void* slot, bool transposed, void*
     }
     dim3 grid((unsigned)cdiv(T, 32), (unsigned)cdiv(d.C, 32));
     if (d.dtype == PSERVE_BF16)
-        transpose_tc_kernel<uint16_t><<<grid, 256, 0, st>>>((const uint16_t*)(load ? user : slot), (uint16_t*)(load ? slot : user), T, d.C, load ? 1 : 0);
+        transpose_tc_kernel<uint16_t><<<grid, 256, 0, st>>>((const uint16_t*)(load ? user : slot), (uint16_t*)(load ? slot : user), T, c->v_ld, d.C, load ? 1 : 0);
     else
-        transpose_tc_kernel<float><<<grid, 256, 0, st>>>((const float*)(load ? user : slot), (float*)(load ? slot : user), T, d.C, load ? 1 : 0);
+        transpose_tc_kernel<float><<<grid, 256, 0, st>>>((const float*)(load ? user : slot), (float*)(load ? slot : user), T, c->v_ld, d.C, load ? 1 : 0);
     return check_launch("transpose_tc_kernel");
 }
 
@@ -815,10 +818,10 @@ int pserve_cache_migrate(const pserve_cache_t* old_cache, pserve_cache_t* new_ca
             else {
                 if (d.dtype == PSERVE_BF16)
                     gather_patch_cols_kernel<uint16_t><<<grid, 256, 0, st>>>((const uint16_t*)old_cache->v[s], (uint16_t*)new_cache->v[s],
-                                                                             old_cache->plan->T, pn->T, pn->S, d.C, patch_src);
+                                                                             old_cache->v_ld, new_cache->v_ld, pn->S, d.C, patch_src);
                 else
                     gather_patch_cols_kernel<float><<<grid, 256, 0, st>>>((const float*)old_cache->v[s], (float*)new_cache->v[s],
-                                                                          old_cache->plan->T, pn->T, pn->S, d.C, patch_src);
+                                                                          old_cache->v_ld, new_cache->v_ld, pn->S, d.C, patch_src);
                 PS_TRY(check_launch("gather_patch_cols_kernel"));
             }
         }
@@ -1034,7 +1037,7 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         aa.K = cross ? cache->kc : cache->k[si];
         aa.V = cross ? cache->vc : cache->v[si];
         aa.v_transposed = cache->v_transposed;
-        aa.ldv = !cache->v_transposed ? C : cross ? (int64_t)plan->n * cache->cross_ld : T;
+        aa.ldv = !cache->v_transposed ? C : cross ? (int64_t)plan->n * cache->cross_ld : cache->v_ld;
         aa.act = joint ? all : act;
         aa.owner = owner; aa.perm = plan->d_tab[PSERVE_TAB_PERM];
         aa.cu_seqlens = plan->d_tab[PSERVE_TAB_CU_SEQLENS];
@@ -1051,7 +1054,7 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         g.act = rows; g.seg_cols = C;
         g.seg[0].ptr = cache->q; g.seg[0].ld = C; g.seg[0].scale = qscale;
         g.seg[1].ptr = cache->k[si]; g.seg[1].ld = C;
-        g.seg[2].ptr = cache->v[si]; g.seg[2].ld = cache->v_transposed ? T : C; g.seg[2].transposed = cache->v_transposed;
+        g.seg[2].ptr = cache->v[si]; g.seg[2].ld = cache->v_transposed ? cache->v_ld : C; g.seg[2].transposed = cache->v_transposed;
         return g;
     };
     auto qkv_proj = [&](const void* in, const void* wqkv, int si, ActiveList rows) -> int {

@@ -1,5 +1,6 @@
-"""GPU: bf16 self-attention of few work items (the keys of a block shared between groups of wavefronts), against the oracle; bar:
-the bf16 bar of the other parity tests."""
+"""GPU: bf16 self-attention of few work items (the keys of a block shared between groups of wavefronts) and of requests that
+start and end anywhere in the transposed values' 16-byte pieces (patches of a token count that is no multiple of eight), against
+the oracle; bar: the bf16 bar of the other parity tests."""
 import numpy as np
 import pytest
 
@@ -14,7 +15,10 @@ from harness import GpuRun, rel_err, tolerance                      # noqa: E402
 
 # fewer key tiles than groups, one more, many; (64 queries x 4 groups), (64 x 2), (128 x 2), (128 x 1)
 SHAPES = [([(8, 8), (8, 16), (32, 40), (8, 24)], (8, 8), 64), ([(8, 8), (24, 24), (16, 8)], (8, 8), 128),
-          ([(8, 8), (32, 32), (32, 32)], (8, 8), 640), ([(40, 40), (40, 48)], (8, 8), 640)]
+          ([(8, 8), (32, 32), (32, 32)], (8, 8), 640), ([(40, 40), (40, 48)], (8, 8), 640),
+          ([(3, 3), (3, 6), (9, 9), (33, 36)], (3, 3), 64), ([(6, 6), (12, 18), (18, 6)], (6, 6), 128),
+          ([(6, 6), (30, 36), (30, 30)], (6, 6), 640), ([(6, 6), (54, 66)], (6, 6), 640),
+          ([(5, 5), (5, 10), (25, 45)], (5, 5), 64)]
 
 
 def _check(cfg):
@@ -31,16 +35,27 @@ def _check(cfg):
 
 
 @pytest.mark.parametrize("res,patch,C", SHAPES)
-def test_groups(res, patch, C):
+def test_groups_and_ragged_requests(res, patch, C):
     _check(wl.custom_config(res, patch, C=C, G=8, heads=C // 64, stages=("LSATTN",), dtype="bf16", seed=41))
 
 
-@pytest.mark.parametrize("res,patch,C", SHAPES[:2])
+@pytest.mark.parametrize("res,patch,C", [SHAPES[0], SHAPES[4], SHAPES[5]])
 def test_with_reuse(res, patch, C):
     _check(wl.custom_config(res, patch, C=C, G=8, heads=C // 64, stages=("LSATTN",), dtype="bf16", reuse_p=0.5, seed=43))
 
 
-@pytest.mark.parametrize("res,patch,C", SHAPES[:3])
+@pytest.mark.parametrize("res,patch,L", [([(6, 6), (18, 24)], (6, 6), 77), ([(10, 10), (30, 20)], (10, 10), 5)])
+def test_ragged_joint_requests(res, patch, L):
+    cfg = wl.custom_config(res, patch, C=128, G=8, heads=2, stages=("MMDIT",), dtype="bf16", ctx_len=L, ctx_dim=128, temb_dim=32, seed=47)
+    w = wl.make_workload(cfg)
+    got = GpuRun(w).forward_images()
+    ref = [ob.mmdit(im, w.ctx[i], w.temb[i], w.params[0], cfg.heads, cfg.eps)[0] for i, im in enumerate(w.images)]
+    for a, b in zip(got, ref):
+        err = rel_err([a], [b])
+        assert np.isfinite(err) and err < tolerance("bf16"), err
+
+
+@pytest.mark.parametrize("res,patch,C", [SHAPES[0], SHAPES[1], SHAPES[2], SHAPES[4]])
 def test_references_of_groups_far_apart(res, patch, C):
     """Logits over a range of some tens: the groups' softmax references differ.  Against the plain kernel on the same bf16
     queries and keys (a logit of 60 off by its bf16 queries' rounding would move the oracle's result itself)."""
@@ -55,3 +70,21 @@ def test_references_of_groups_far_apart(res, patch, C):
         ps.set_kernel_mode(0)
     for a, b in zip(got, ref):
         assert rel_err([a], [b]) < tolerance("bf16")
+
+
+@pytest.mark.parametrize("patch", [(5, 5), (3, 3), (4, 4)])
+def test_value_slot_round_trip(patch):
+    """The value slot's rows are padded to whole 16-byte pieces: what is loaded comes back, also through a migration."""
+    ph, pw = patch
+    cfg = wl.custom_config([(ph, pw), (3 * ph, pw)], patch, C=64, G=8, heads=1, stages=("LSATTN",), dtype="bf16", reuse_p=0.5, seed=59)
+    run = GpuRun(wl.make_workload(cfg))
+    t = torch.randn((run.plan.T, 64), device="cuda").to(torch.bfloat16)
+    run.load_cache()
+    run.cache.load(0, ps.SLOT_V, t)
+    assert torch.equal(run.cache.read(0, ps.SLOT_V), t)
+    plan = ps.Plan([(ph, pw), (2 * ph, pw)], ph, pw)
+    other = ps.Cache(plan, run.block, True)
+    src = torch.tensor([2, 0, 3], dtype=torch.int32, device="cuda")
+    other.migrate_from(run.cache, src)
+    S = ph * pw
+    assert torch.equal(other.read(0, ps.SLOT_V), torch.cat([t[p * S:(p + 1) * S] for p in src.tolist()]))
