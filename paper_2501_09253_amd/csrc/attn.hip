@@ -323,7 +323,18 @@ attn_f32mma_kernel(AttnArgs a, int group) {
         for (int w = 0; w < 4; ++w) v += *reinterpret_cast<const at_f32x4*>(at_smem + w * WAVE + qr * LK + c);
         if constexpr (sizeof(T) == 2)
             *reinterpret_cast<uint2*>(op + c) = make_uint2(pack_bf16x2(v.x * inv, v.y * inv), pack_bf16x2(v.z * inv, v.w * inv));
-        else
+        else if (a.out_pieces) {
+            uint16_t* o16 = (uint16_t*)a.O + token(r0 + qr) * 3 * C + piece_index(h * d + c);
+            v *= inv;
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) {
+                uint32_t u[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { u[e] = __float_as_uint(v[e]); v[e] -= __uint_as_float(u[e] & 0xFFFF0000u); }
+                *reinterpret_cast<uint2*>(o16 + 32 * pl) =
+                    make_uint2(__builtin_amdgcn_perm(u[1], u[0], 0x07060302), __builtin_amdgcn_perm(u[3], u[2], 0x07060302));
+            }
+        } else
             *reinterpret_cast<at_f32x4*>(op + c) = v * inv;
     }
 }

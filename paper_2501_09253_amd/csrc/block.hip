@@ -464,6 +464,13 @@ static int block_create_impl(const pserve_block_desc* desc, const pserve_block_p
     hipStream_t st = (hipStream_t)stream;
     const size_t es = dtype_size(d.dtype);
     const int C = d.C;
+    struct Packed { void* p; int64_t rows; int32_t K; };
+    std::vector<Packed> packed;                      // all packed weights: fp32 ones get their bf16 pieces at the end
+    auto weights = [&](void** dst, int64_t rows, int32_t K) -> int {
+        PS_TRY(b->pool.alloc(dst, packed_weight_bytes(rows, K, d.dtype)));
+        packed.push_back({*dst, rows, K});
+        return PSERVE_OK;
+    };
     for (int s = 0; s < d.n_stages; ++s) {
         StageWeights& w = b->sw[s];
         const void* const* p = params->p[s];
@@ -491,7 +498,7 @@ static int block_create_impl(const pserve_block_desc* desc, const pserve_block_p
             for (int c = 0; c < convs; ++c) {
                 PS_TRY(dup_param(b->pool, p[4 * c + 0], es * C, &w.gn_g[c], st));
                 PS_TRY(dup_param(b->pool, p[4 * c + 1], es * C, &w.gn_b[c], st));
-                PS_TRY(b->pool.alloc(&w.w[c], es * 9 * C * C));
+                PS_TRY(weights(&w.w[c], 9 * C, C));
                 PS_TRY(pack_conv(p[4 * c + 2], w.w[c], C, C, d.dtype, st));
                 PS_TRY(b->pool.alloc_t(&w.b[c], C));
                 PS_TRY(pack_bias(p[4 * c + 3], w.b[c], C, d.dtype, st));
@@ -506,9 +513,9 @@ static int block_create_impl(const pserve_block_desc* desc, const pserve_block_p
                 PS_TRY(dup_param(b->pool, p[0], es * C, &w.gn_g[0], st));
                 PS_TRY(dup_param(b->pool, p[1], es * C, &w.gn_b[0], st));
             }
-            PS_TRY(b->pool.alloc(&w.w[0], es * 3 * C * C));                       // fused [Wq | Wk | Wv]
+            PS_TRY(weights(&w.w[0], 3 * C, C));                       // fused [Wq | Wk | Wv]
             for (int k = 0; k < 3; ++k) PS_TRY(pack_linear(p[o + k], w.w[0], C, C, k * C, d.dtype, st));
-            PS_TRY(b->pool.alloc(&w.w[1], es * C * C));
+            PS_TRY(weights(&w.w[1], C, C));
             PS_TRY(pack_linear(p[o + 3], w.w[1], C, C, 0, d.dtype, st));
             PS_TRY(b->pool.alloc_t(&w.b[1], C));
             PS_TRY(pack_bias(p[o + 4], w.b[1], C, d.dtype, st));
@@ -522,17 +529,17 @@ static int block_create_impl(const pserve_block_desc* desc, const pserve_block_p
                 PS_TRY(dup_param(b->pool, q[0], es * d.temb_dim * 6 * C, &v.wt, st));
                 PS_TRY(b->pool.alloc_t(&v.bt, 6 * C));
                 PS_TRY(pack_bias(q[1], v.bt, 6 * C, d.dtype, st));
-                PS_TRY(b->pool.alloc(&v.w[0], es * 3 * C * C));
+                PS_TRY(weights(&v.w[0], 3 * C, C));
                 for (int k = 0; k < 3; ++k) PS_TRY(pack_linear(q[2 + k], v.w[0], C, C, k * C, d.dtype, st));
-                PS_TRY(b->pool.alloc(&v.w[1], es * C * C));
+                PS_TRY(weights(&v.w[1], C, C));
                 PS_TRY(pack_linear(q[5], v.w[1], C, C, 0, d.dtype, st));
                 PS_TRY(b->pool.alloc_t(&v.b[1], C));
                 PS_TRY(pack_bias(q[6], v.b[1], C, d.dtype, st));
-                PS_TRY(b->pool.alloc(&v.w[3], es * F * C));
+                PS_TRY(weights(&v.w[3], F, C));
                 PS_TRY(pack_linear(q[7], v.w[3], C, F, 0, d.dtype, st));
                 PS_TRY(b->pool.alloc_t(&v.b[3], F));
                 PS_TRY(pack_bias(q[8], v.b[3], F, d.dtype, st));
-                PS_TRY(b->pool.alloc(&v.w[4], es * C * F));
+                PS_TRY(weights(&v.w[4], C, F));
                 PS_TRY(pack_linear(q[9], v.w[4], F, C, 0, d.dtype, st));
                 PS_TRY(b->pool.alloc_t(&v.b[4], C));
                 PS_TRY(pack_bias(q[10], v.b[4], C, d.dtype, st));
@@ -541,11 +548,11 @@ static int block_create_impl(const pserve_block_desc* desc, const pserve_block_p
         }
         case PSERVE_AMLP: {
             const int F = d.ffn_mult * C;
-            PS_TRY(b->pool.alloc(&w.w[0], es * F * C));
+            PS_TRY(weights(&w.w[0], F, C));
             PS_TRY(pack_linear(p[0], w.w[0], C, F, 0, d.dtype, st));
             PS_TRY(b->pool.alloc_t(&w.b[0], F));
             PS_TRY(pack_bias(p[1], w.b[0], F, d.dtype, st));
-            PS_TRY(b->pool.alloc(&w.w[1], es * C * F));
+            PS_TRY(weights(&w.w[1], C, F));
             PS_TRY(pack_linear(p[2], w.w[1], F, C, 0, d.dtype, st));
             PS_TRY(b->pool.alloc_t(&w.b[1], C));
             PS_TRY(pack_bias(p[3], w.b[1], C, d.dtype, st));
@@ -554,12 +561,12 @@ static int block_create_impl(const pserve_block_desc* desc, const pserve_block_p
         case PSERVE_XATTN:
         case PSERVE_LXATTN: {
             const int D = d.ctx_dim;
-            PS_TRY(b->pool.alloc(&w.w[0], es * C * C));
+            PS_TRY(weights(&w.w[0], C, C));
             PS_TRY(pack_linear(p[0], w.w[0], C, C, 0, d.dtype, st));
-            PS_TRY(b->pool.alloc(&w.w[2], es * 2 * C * D));                       // fused [Wk | Wv] on the text tokens
+            PS_TRY(weights(&w.w[2], 2 * C, D));                       // fused [Wk | Wv] on the text tokens
             PS_TRY(pack_linear(p[1], w.w[2], D, C, 0, d.dtype, st));
             PS_TRY(pack_linear(p[2], w.w[2], D, C, C, d.dtype, st));
-            PS_TRY(b->pool.alloc(&w.w[1], es * C * C));
+            PS_TRY(weights(&w.w[1], C, C));
             PS_TRY(pack_linear(p[3], w.w[1], C, C, 0, d.dtype, st));
             PS_TRY(b->pool.alloc_t(&w.b[1], C));
             PS_TRY(pack_bias(p[4], w.b[1], C, d.dtype, st));
@@ -568,10 +575,10 @@ static int block_create_impl(const pserve_block_desc* desc, const pserve_block_p
         case PSERVE_FFN:
         case PSERVE_LFFN: {
             const int F = d.ffn_mult * C;
-            PS_TRY(b->pool.alloc(&w.w[0], es * 2 * F * C));
+            PS_TRY(weights(&w.w[0], 2 * F, C));
             PS_TRY(b->pool.alloc_t(&w.b[0], 2 * F));
             PS_TRY(pack_geglu(p[0], p[1], w.w[0], w.b[0], C, F, d.dtype, st));
-            PS_TRY(b->pool.alloc(&w.w[1], es * C * F));
+            PS_TRY(weights(&w.w[1], C, F));
             PS_TRY(pack_linear(p[2], w.w[1], F, C, 0, d.dtype, st));
             PS_TRY(b->pool.alloc_t(&w.b[1], C));
             PS_TRY(pack_bias(p[3], w.b[1], C, d.dtype, st));
@@ -579,6 +586,7 @@ static int block_create_impl(const pserve_block_desc* desc, const pserve_block_p
         }
         }
     }
+    for (const Packed& w : packed) PS_TRY(split_packed(w.p, w.rows, w.K, d.dtype, st));
     PS_CHECK_HIP(hipStreamSynchronize(st));
     guard.p = nullptr;
     *out = b;
@@ -622,12 +630,14 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
     const bool sattn = any_stage(d, is_sattn), xattn = any_stage(d, is_xattn);
     const bool ffn = any_stage(d, is_ffn) || has_stage(d, PSERVE_AMLP) || joint;
     const bool gn_sattn = has_stage(d, PSERVE_SATTN);
+    // what feeds a layer may hold fp32 values as three bf16 pieces
+    const size_t ps = d.dtype == PSERVE_F32 ? 6 : es, TCP = (size_t)plan->T * d.C * ps;
     if (conv) {
         PatchGeom g{plan->P, plan->S, plan->ph, plan->pw, plan->pw + 2, (plan->ph + 2) * (plan->pw + 2)};
         c->split_ws_bytes = conv_split_bytes(g, (int32_t)plan->T, d.C, d.C, d.dtype, g_kernel_mode == 1 ? 1 : 0);
         if (c->split_ws_bytes) PS_TRY(c->pool.alloc((void**)&c->split_ws, c->split_ws_bytes));
     }
-    if (conv) PS_TRY(c->pool.alloc(&c->apad, (size_t)plan->P * (plan->ph + 2) * (plan->pw + 2) * d.C * es));
+    if (conv) PS_TRY(c->pool.alloc(&c->apad, (size_t)plan->P * (plan->ph + 2) * (plan->pw + 2) * d.C * ps));
     if (conv || gn_sattn) {
         PS_TRY(c->pool.alloc_t(&c->partial, (size_t)plan->P * std::max<int64_t>(c->nsplit, plan->S / 64) * d.G * 2));
         PS_TRY(c->pool.alloc_t(&c->scale_shift, (size_t)plan->n * d.C * 2));
@@ -656,9 +666,9 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
     }
     if (sattn || xattn) {
         PS_TRY(c->pool.alloc(&c->q, TC));
-        PS_TRY(c->pool.alloc(&c->o, TC));
+        PS_TRY(c->pool.alloc(&c->o, TCP));
     }
-    if (sattn || any_stage(d, has_ln)) PS_TRY(c->pool.alloc(&c->u, TC));     // normalised stage input
+    if (sattn || any_stage(d, has_ln)) PS_TRY(c->pool.alloc(&c->u, TCP));     // normalised stage input
     if (xattn) {
         // text keys / values: rows padded to a multiple of 8 per request and zero-filled once, so that the
         // padding rows (never written) contribute exact zeros; values transposed like the self-attention V
@@ -678,7 +688,7 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
         c->att_qt = attention_max_tiles(plan, 2) * (int64_t)d.heads < 256 ? 1 : 2;
         c->max_tiles = attention_max_tiles(plan, c->att_qt);
     }
-    if (ffn) PS_TRY(c->pool.alloc(&c->hidden, (size_t)plan->T * d.ffn_mult * d.C * es));
+    if (ffn) PS_TRY(c->pool.alloc(&c->hidden, (size_t)plan->T * d.ffn_mult * d.C * ps));
     if (with_slots) PS_TRY(c->pool.alloc(&c->yslot, TC));
     PS_TRY(c->pool.alloc_t(&c->active, (size_t)plan->P));
     PS_TRY(c->pool.alloc_t(&c->count, 1));
@@ -933,18 +943,19 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         }
         else { ProfScope ps("gn_stats", st); PS_TRY(gn_stats(ga, gm, dt, st)); }
         have_partials = false;
+        GemmArgs g = base_gemm(cache->apad, C, C, C, w.w[ci], w.b[ci]);
+        g.conv = 1; g.taps = 9; g.res = res; g.ldr = C;
+        g.a_pieces = push && gemm_takes_pieces(g, dt, mode);
         // reused patches are not convolved: of them only the border tokens are normalised (the neighbours' rings)
         ga.rim_only = reuse_mask;
         if (push) {             // normalise + stitch in one pass (push); otherwise the rims are gathered afterwards (pull)
             ProfScope ps("gn_apply_stitch", st);
-            PS_TRY(gn_apply(ga, gm, dt, /*silu=*/true, /*padded=*/true, /*stitch=*/true, cache->apad, all, st));
+            PS_TRY(gn_apply(ga, gm, dt, /*silu=*/true, /*padded=*/true, /*stitch=*/true, cache->apad, all, st, g.a_pieces));
         } else {
             { ProfScope ps("gn_apply", st); PS_TRY(gn_apply(ga, gm, dt, true, true, false, cache->apad, all, st)); }
             { ProfScope ps("halo_gather", st);
               PS_TRY(halo_gather(cache->apad, plan->d_tab[PSERVE_TAB_HALO_SRC], gm, C, plan->ring, dt, act, st)); }
         }
-        GemmArgs g = base_gemm(cache->apad, C, C, C, w.w[ci], w.b[ci]);
-        g.conv = 1; g.taps = 9; g.res = res; g.ldr = C;
         g.split_ws = cache->split_ws; g.split_ws_bytes = cache->split_ws_bytes;
         g.rowbias = rowbias; g.row_owner = owner;
         g.seg[0].ptr = out; g.seg[0].ld = C;
@@ -1031,7 +1042,7 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
 
     // attention of the queries in cache->q over the keys / values of stage si (self; `joint`: key count from SEQ_LEN,
     // all patches are queries) or over the text keys / values (cross), into cache->o
-    auto run_attention = [&](int si, bool cross, bool joint) -> int {
+    auto run_attention = [&](int si, bool cross, bool joint, bool out_pieces = false) -> int {
         AttnArgs aa{};
         aa.Q = cache->q; aa.O = cache->o; aa.C = C; aa.heads = d.heads; aa.d = C / d.heads; aa.geom = gm;
         aa.K = cross ? cache->kc : cache->k[si];
@@ -1044,7 +1055,7 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         aa.seq_len = joint ? plan->d_tab[PSERVE_TAB_SEQ_LEN] : nullptr;
         aa.cross_len = cross ? d.ctx_len : 0; aa.cross_ld = cross ? cache->cross_ld : 0;
         aa.act_off = cache->act_off; aa.tile_off = cache->tile_off; aa.n = plan->n; aa.max_tiles = cache->max_tiles;
-        aa.qt = cache->att_qt; aa.max_rows = plan->max_tokens_per_image;
+        aa.qt = cache->att_qt; aa.max_rows = plan->max_tokens_per_image; aa.out_pieces = out_pieces;
         ProfScope ps(cross ? "attn_cross" : "attn_self", st);
         return attention(aa, dt, mode, st);
     };
@@ -1057,10 +1068,8 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         g.seg[2].ptr = cache->v[si]; g.seg[2].ld = cache->v_transposed ? cache->v_ld : C; g.seg[2].transposed = cache->v_transposed;
         return g;
     };
-    auto qkv_proj = [&](const void* in, const void* wqkv, int si, ActiveList rows) -> int {
-        ProfScope ps("linear_qkv", st);
-        return gemm(qkv_args(in, wqkv, si, rows), dt, mode, st);
-    };
+    // whether the layer that reads the attention's output takes it in pieces (the plain kernel does not write them)
+    auto attn_pieces = [&](const GemmArgs& g) { return C / d.heads % 4 == 0 && gemm_takes_pieces(g, dt, mode); };
     // the projection of stage si as seen from the main stream: wait for the side stream, or run it here
     auto temb_ready = [&](const StageWeights&, int si, int) -> int {
         if (cache->side_temb) { PS_CHECK_HIP(hipStreamWaitEvent(st, cache->ev_temb[si], 0)); return PSERVE_OK; }
@@ -1097,6 +1106,8 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
             const bool ada = d.stages[si] == PSERVE_ASATTN;
             const bool ln = d.stages[si] == PSERVE_LSATTN || ada;
             if (ada) PS_TRY(temb_ready(w, si, 3 * C));          // [shift | scale | gate] per request
+            GemmArgs gq = qkv_args(cache->u, w.w[0], si, act);
+            gq.a_pieces = gemm_takes_pieces(gq, dt, mode);
             const void* rin = cur;
             if (!ln && cache->with_slots && cur != cache->r[si]) {    // first stage: merge fresh input into the slot
                 ProfScope ps("reuse_copy", st);
@@ -1108,7 +1119,7 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
             if (ln) {                                                 // per token: nothing of the reused patches is needed
                 ProfScope ps("layer_norm", st);
                 PS_TRY(layer_norm(rin, ada ? nullptr : w.gn_g[0], ada ? nullptr : w.gn_b[0], ada ? cache->temb_e[si] : nullptr,
-                                  3 * C, owner, C, d.eps, gm, dt, cache->u, act, st));
+                                  3 * C, owner, C, d.eps, gm, dt, cache->u, act, st, nullptr, nullptr, gq.a_pieces));
             } else {
                 GroupNormArgs ga = gn_args(rin, w.gn_g[0], w.gn_b[0]);
                 if (in_stats && rin == x) {         // the block input itself (not the slot that mixes in cached patches)
@@ -1117,12 +1128,13 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
                     ProfScope ps("gn_finalize", st);
                     PS_TRY(gn_finalize(gi, gm, dt, cache->in_nch, st, /*per_channel=*/true));
                 } else { ProfScope ps("gn_stats", st); PS_TRY(gn_stats(ga, gm, dt, st)); }
-                { ProfScope ps("gn_apply", st); PS_TRY(gn_apply(ga, gm, dt, false, false, false, cache->u, act, st)); }
+                { ProfScope ps("gn_apply", st); PS_TRY(gn_apply(ga, gm, dt, false, false, false, cache->u, act, st, gq.a_pieces)); }
             }
-            PS_TRY(qkv_proj(cache->u, w.w[0], si, act));
-            PS_TRY(run_attention(si, /*cross=*/false, /*joint=*/false));
+            { ProfScope ps("linear_qkv", st); PS_TRY(gemm(gq, dt, mode, st)); }
             GemmArgs go = base_gemm(cache->o, C, C, C, w.w[1], w.b[1]);
             go.res = rin; go.ldr = C;
+            go.a_pieces = attn_pieces(go);
+            PS_TRY(run_attention(si, /*cross=*/false, /*joint=*/false, go.a_pieces));
             if (ada) { go.rowscale = cache->temb_e[si] + 2 * C; go.rowscale_ld = 3 * C; go.row_owner = owner; }
             go.seg[0].ptr = out; go.seg[0].ld = C;
             { ProfScope ps("linear_out", st); PS_TRY(gemm(go, dt, mode, st)); }
@@ -1233,13 +1245,15 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         case PSERVE_AMLP: {
             const int F = d.ffn_mult * C;
             PS_TRY(temb_ready(w, si, 3 * C));
-            { ProfScope ps("layer_norm", st);
-              PS_TRY(layer_norm(cur, nullptr, nullptr, cache->temb_e[si], 3 * C, owner, C, d.eps, gm, dt, cache->u, act, st)); }
-            GemmArgs g1 = base_gemm(cache->u, C, C, F, w.w[0], w.b[0]);
+            GemmArgs g1 = base_gemm(cache->u, C, C, F, w.w[0], w.b[0]), g2 = base_gemm(cache->hidden, F, F, C, w.w[1], w.b[1]);
             g1.act_gelu = 1;
             g1.seg[0].ptr = cache->hidden; g1.seg[0].ld = F;
+            g1.a_pieces = gemm_takes_pieces(g1, dt, mode);
+            g1.out_pieces = g2.a_pieces = g1.a_pieces && gemm_takes_pieces(g2, dt, mode);
+            { ProfScope ps("layer_norm", st);
+              PS_TRY(layer_norm(cur, nullptr, nullptr, cache->temb_e[si], 3 * C, owner, C, d.eps, gm, dt, cache->u, act, st, nullptr, nullptr,
+                                g1.a_pieces)); }
             { ProfScope ps("mlp_in", st); PS_TRY(gemm(g1, dt, mode, st)); }
-            GemmArgs g2 = base_gemm(cache->hidden, F, F, C, w.w[1], w.b[1]);
             g2.res = cur; g2.ldr = C;
             g2.rowscale = cache->temb_e[si] + 2 * C; g2.rowscale_ld = 3 * C; g2.row_owner = owner;
             g2.seg[0].ptr = out; g2.seg[0].ld = C;
@@ -1250,18 +1264,19 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         case PSERVE_LXATTN: {
             if (cache->side_stage == si) PS_CHECK_HIP(hipStreamWaitEvent(st, cache->ev_join, 0));     // join
             else PS_TRY(ctx_kv(w, st));
-            const void* qin = cur;
-            if (d.stages[si] == PSERVE_LXATTN) {
-                ProfScope ps("layer_norm", st);
-                PS_TRY(layer_norm(cur, w.gn_g[0], w.gn_b[0], nullptr, 0, nullptr, C, d.eps, gm, dt, cache->u, act, st));
-                qin = cache->u;
-            }
-            GemmArgs gq = base_gemm(qin, C, C, C, w.w[0], nullptr);
+            const bool ln = d.stages[si] == PSERVE_LXATTN;
+            GemmArgs gq = base_gemm(ln ? cache->u : cur, C, C, C, w.w[0], nullptr);
             gq.seg[0].ptr = cache->q; gq.seg[0].ld = C; gq.seg[0].scale = qscale;
+            if (ln) {
+                gq.a_pieces = gemm_takes_pieces(gq, dt, mode);
+                ProfScope ps("layer_norm", st);
+                PS_TRY(layer_norm(cur, w.gn_g[0], w.gn_b[0], nullptr, 0, nullptr, C, d.eps, gm, dt, cache->u, act, st, nullptr, nullptr, gq.a_pieces));
+            }
             { ProfScope ps("linear_q", st); PS_TRY(gemm(gq, dt, mode, st)); }
-            PS_TRY(run_attention(si, /*cross=*/true, /*joint=*/false));
             GemmArgs go = base_gemm(cache->o, C, C, C, w.w[1], w.b[1]);
             go.res = cur; go.ldr = C;
+            go.a_pieces = attn_pieces(go);
+            PS_TRY(run_attention(si, /*cross=*/true, /*joint=*/false, go.a_pieces));
             go.seg[0].ptr = out; go.seg[0].ld = C;
             { ProfScope ps("linear_out", st); PS_TRY(gemm(go, dt, mode, st)); }
             break;
@@ -1269,17 +1284,17 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         case PSERVE_FFN:
         case PSERVE_LFFN: {
             const int F = d.ffn_mult * C;
-            const void* fin = cur;
-            if (d.stages[si] == PSERVE_LFFN) {
-                ProfScope ps("layer_norm", st);
-                PS_TRY(layer_norm(cur, w.gn_g[0], w.gn_b[0], nullptr, 0, nullptr, C, d.eps, gm, dt, cache->u, act, st));
-                fin = cache->u;
-            }
-            GemmArgs g1 = base_gemm(fin, C, C, 2 * F, w.w[0], w.b[0]);
+            const bool ln = d.stages[si] == PSERVE_LFFN;
+            GemmArgs g1 = base_gemm(ln ? cache->u : cur, C, C, 2 * F, w.w[0], w.b[0]), g2 = base_gemm(cache->hidden, F, F, C, w.w[1], w.b[1]);
             g1.epi = EPI_GEGLU;
             g1.seg[0].ptr = cache->hidden; g1.seg[0].ld = F;
+            if (ln) {
+                g1.a_pieces = gemm_takes_pieces(g1, dt, mode);
+                g1.out_pieces = g2.a_pieces = g1.a_pieces && gemm_takes_pieces(g2, dt, mode);
+                ProfScope ps("layer_norm", st);
+                PS_TRY(layer_norm(cur, w.gn_g[0], w.gn_b[0], nullptr, 0, nullptr, C, d.eps, gm, dt, cache->u, act, st, nullptr, nullptr, g1.a_pieces));
+            }
             { ProfScope ps("ffn_geglu", st); PS_TRY(gemm(g1, dt, mode, st)); }
-            GemmArgs g2 = base_gemm(cache->hidden, F, F, C, w.w[1], w.b[1]);
             g2.res = cur; g2.ldr = C;
             g2.seg[0].ptr = out; g2.seg[0].ld = C;
             { ProfScope ps("ffn_out", st); PS_TRY(gemm(g2, dt, mode, st)); }

@@ -11,6 +11,7 @@
 // Packed weights: B[tap][n][k], k contiguous (conv W[co][ci][ky][kx] -> tap = ky*3+kx;
 // linear W[k][n] -> transposed).  Accumulation is fp32.
 #include "kernels.h"
+#include <type_traits>
 
 namespace pserve {
 
@@ -341,18 +342,25 @@ gemm_f32mma_kernel(GemmArgs a) {
     }
 }
 
+// Time of a launch of gemm_f32mma_kernel in 64 x 64 tiles on the fullest CU (a tile: 32 clocks a k), and its tile: 32 x 32
+// (bm = bn = 32), 64 x 32 or 64 x 64.  The smaller tiles fetch more per MFMA and pay the K reduction, so they must win by
+// their share.
+static double f32mma_tiles(int64_t M, int64_t ncols, int* bm, int* bn) {
+    const double c64 = (double)cdiv(cdiv(M, 64) * cdiv(ncols, 64), 256), cmn = 0.5 * 1.05 * cdiv(cdiv(M, 64) * cdiv(ncols, 32), 256),
+                 c32 = 0.25 * 1.15 * cdiv(cdiv(M, 32) * cdiv(ncols, 32), 256);
+    *bm = c32 < c64 && c32 < cmn ? 32 : 64;
+    *bn = *bm == 64 && c64 <= cmn ? 64 : 32;
+    return std::min(c64, std::min(cmn, c32));
+}
+
 template <typename T>
 static bool gemm_f32mma(const GemmArgs& a, hipStream_t st) {
     // 16-byte (bf16: 8-byte) loads of four k
     if (a.K % 4 != 0 || a.lda % 4 != 0 || ((uintptr_t)a.A | (uintptr_t)a.B) % (4 * sizeof(T)) != 0) return false;
     const bool geglu = a.epi == EPI_GEGLU;
     const int ncols = geglu ? a.N / 2 : a.N;
-    // The tile with the least work on the fullest CU (in 32 x 32 tiles per SIMD, 256 CUs); the smaller tiles fetch more
-    // per MFMA and pay the K reduction, so they must win by their share.
-    const int64_t b64 = cdiv(a.M, 64) * cdiv(ncols, 64), b32 = cdiv(a.M, 32) * cdiv(ncols, 32);
-    const int64_t bmn = cdiv(a.M, 64) * cdiv(ncols, 32);
-    const double c64 = (double)cdiv(b64, 256), cmn = 0.5 * 1.05 * cdiv(bmn, 256), c32 = 0.25 * 1.15 * cdiv(b32, 256);
-    const int bm = c32 < c64 && c32 < cmn ? 32 : 64, bn = bm == 64 && c64 <= cmn ? 64 : 32;
+    int bm, bn;
+    f32mma_tiles(a.M, ncols, &bm, &bn);
     const dim3 grid((unsigned)cdiv(a.M, bm), (unsigned)cdiv(ncols, bn));
 #define PS_F32MMA(BM_, BN_)                                                            \
     do {                                                                               \
@@ -364,6 +372,347 @@ static bool gemm_f32mma(const GemmArgs& a, hipStream_t st) {
     else PS_F32MMA(64, 64);
 #undef PS_F32MMA
     return true;
+}
+
+// ---- fp32 on the bf16 matrix cores ----------------------------------------------------------------
+// The bf16 MFMA does 16 times the work of the fp32 one, so an fp32 value is cut into three bf16 pieces of eight bits each
+// (truncation: x = x0 + x1 + x2 exactly) and a product is x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0), every term exact in
+// the fp32 accumulators; what is left out is below 2^-24 of a product, and a sum has an eighth as many roundings.  The
+// large terms and the others have accumulators of their own.  Both operands come in pieces, rows of [K / 32][3][32]: the weights
+// are cut when they are packed (split_packed), the activations by the kernel that produces them (cutting them here, once a tile
+// and step, took as long as the MFMAs).  A step's 32 k of a row are 192 contiguous bytes: as three runs of 64 the loads into LDS,
+// which bound the kernel, took twice as long.
+//   Tile 64 x 32 TN, four wavefronts: two along M, two sharing a step's 32 k (summed through LDS at the end).  A wavefront reads
+// 3 (1 + TN) fragments for 6 TN MFMAs, so LDS and matrix pipe are about level at TN = 5.  Both operands are staged by direct
+// loads into a ring of three stages (two blocks a CU at TN = 2); behind the barrier of a step its stage is refilled and the NEXT step's fragments are read
+// between the MFMAs of this one.  LDS rows are 192 bytes, chunk c of a piece at c ^ ((row >> 2) & 3): conflict free.
+//   An infinite operand would meet a zero piece (NaN), so a result that is not finite is summed again in plain fp32.
+//   Two convolutions of 7,168 tokens x 320 channels: 162 -> 78 us each (170 TFLOP/s of fp32); bound by the bf16 matrix pipe at the clock it
+// gets (1.0 PFLOP/s) and, for few tiles, by a tile's start and end (7 us).  Error of a block of two convolutions and an attention
+// against 64 bits 2.6e-7 -> 2.0e-7.
+typedef __attribute__((ext_vector_type(8))) __bf16 gs_bf16x8;
+typedef __attribute__((ext_vector_type(4))) uint32_t gs_u32x4;
+typedef __attribute__((address_space(3))) void gs_lds_void;
+
+// f(integral_constant 0), f(1), .. f(N - 1)
+template <int I, int N, class F> __device__ __forceinline__ void gs_for_from(F&& f) {
+    if constexpr (I < N) { f(std::integral_constant<int, I>{}); gs_for_from<I + 1, N>(f); }
+}
+template <int N, class F> __device__ __forceinline__ void gs_for(F&& f) { gs_for_from<0, N>(f); }
+
+template <int TN> struct SplitCfg {
+    static constexpr int BM = 64, BN = 32 * TN, NS = 3;
+    static constexpr int STAGE_V = 3 * (BM + BN) * 4;                  // 16-byte slots: rows of A, then of B, [3][4] each
+    static constexpr int LD = (STAGE_V / 64 + 3) / 4;                  // direct loads of a wavefront and step: three of A, then B
+    static constexpr size_t LDS = (size_t)NS * STAGE_V * 16;
+    static_assert(LDS >= (size_t)4 * TN * 4096 && LDS + BM * 16 <= 160 * 1024, "tile");
+};
+
+template <int TN, bool GEGLU>
+__global__ void __launch_bounds__(256, (SplitCfg<TN>::LDS <= 79 * 1024 ? 2 : 1))
+gemm_split_kernel(GemmArgs a, const uint16_t* __restrict__ Bs) {
+    using Cfg = SplitCfg<TN>;
+    constexpr int BM = Cfg::BM, BN = Cfg::BN, NS = Cfg::NS, STAGE_V = Cfg::STAGE_V, LD = Cfg::LD, NINS = STAGE_V / 64;
+    static_assert(!GEGLU || TN % 2 == 0, "GEGLU: as many values as gates");
+    extern __shared__ __attribute__((aligned(16))) uint8_t gs_smem[];
+    gs_u32x4* ring = reinterpret_cast<gs_u32x4*>(gs_smem);
+    __shared__ int64_t s_aoff[BM];
+    __shared__ int64_t s_tok[BM];                                      // -1: the row does not exist
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int fr = lane & 31, fh = lane >> 5;
+    const int m0 = blockIdx.x * BM, n0 = blockIdx.y * (GEGLU ? BN / 2 : BN);       // n0: output column
+    if (a.tokens_are_rows && a.act.active && m0 >= *a.act.count * a.geom.S) return;
+    const int ncols = GEGLU ? a.N / 2 : a.N;
+    // packed column of output column f (GEGLU: its value or gate)
+    auto packed = [&](int f, int gate) { return GEGLU ? (f / GEGLU_GROUP) * 2 * GEGLU_GROUP + gate * GEGLU_GROUP + f % GEGLU_GROUP : f; };
+    const int K = a.K, tw = a.tap_w ? a.tap_w : 3;
+    const int steps = a.taps * (K / 32);
+    // staging: a load fills 64 slots.  Load l of a wavefront: slots of A for l < 3, else of B; row slot / 12, chunk slot % 12
+    int a_lane[3], b_lane[LD - 3];
+#pragma unroll
+    for (int l = 0; l < LD; ++l) {
+        const int slot = min(wave + 4 * l, NINS - 1) * 64 + lane - (l < 3 ? 0 : 12 * BM), row = slot / 12, c = slot - row * 12;
+        const int chunk = c ^ ((row >> 2) & 3);             // the two low bits: the place inside the piece
+        if (l < 3) {
+            const RowInfo r = row_info(a, m0 + row);
+            if (c == 0) { s_aoff[row] = r.a_off; s_tok[row] = r.valid ? r.out_row : -1; }
+            a_lane[l < 3 ? l : 0] = (int)((r.a_off * 3 + chunk * 8) * 2);
+        } else {
+            const int h = GEGLU && row >= BN / 2, col = packed(min(n0 + row - h * (BN / 2), ncols - 1), h);
+            b_lane[l >= 3 ? l - 3 : 0] = (int)(((int64_t)col * 3 * K + chunk * 8) * 2);
+        }
+    }
+    int tap = 0, k0 = 0, left = steps, istage = 0;      // of the step loaded next; past the last one it is loaded again (never read)
+#if defined(__HIP_DEVICE_COMPILE__)
+    const __amdgpu_buffer_rsrc_t ga = __builtin_amdgcn_make_buffer_rsrc((void*)a.A, 0, 0x7fffffff, 0x00020000);
+    const __amdgpu_buffer_rsrc_t gb = __builtin_amdgcn_make_buffer_rsrc((void*)Bs, 0, 0x7fffffff, 0x00020000);
+#define PS_LOAD(l_)                                                                                                     \
+    {                                                                                                                   \
+        gs_u32x4* d_ = ring + istage * STAGE_V + min(wave + 4 * (l_), NINS - 1) * 64;                                   \
+        if ((l_) < 3) __builtin_amdgcn_raw_ptr_buffer_load_lds(ga, (gs_lds_void*)d_, 16, a_lane[(l_) < 3 ? (l_) : 0], a_s, 0, 0);       \
+        else if ((l_) < LD) __builtin_amdgcn_raw_ptr_buffer_load_lds(gb, (gs_lds_void*)d_, 16, b_lane[(l_) >= 3 && (l_) < LD ? (l_) - 3 : 0], b_s, 0, 0); \
+    }
+#else       // the host pass only needs the kernel's stub
+#define PS_LOAD(l_) (void)0
+#endif
+    // scalar byte offsets of the step loaded next; then the one after it
+#define PS_OFFSETS()                                                                                                    \
+    const int a_s = (int)(((a.conv ? ((int64_t)(tap / tw) * a.geom.ppw + (tap % tw)) * a.lda : 0) + k0) * 6);            \
+    const int b_s = (int)(((int64_t)tap * a.N * K + k0) * 6);
+#define PS_ADVANCE()                                                                                                    \
+    {                                                                                                                   \
+        if (--left > 0) { if (++tap == a.taps) { tap = 0; k0 += 32; } }                                                 \
+        istage = istage + 1 == NS ? 0 : istage + 1;                                                                     \
+    }
+#pragma unroll
+    for (int d = 0; d < NS; ++d) {
+        PS_OFFSETS();
+#pragma unroll
+        for (int l = 0; l < LD; ++l) PS_LOAD(l);
+        PS_ADVANCE();
+    }
+    gm_f32x16 acc[TN][2];
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[j][0][e] = acc[j][1][e] = 0.f;
+    const int wk = wave & 1, wm = wave >> 1;
+    const int arow = wm * 32 + fr, kc = 2 * wk + fh;
+    const gs_u32x4* pA = ring + arow * 12 + (kc ^ ((arow >> 2) & 3));
+    const gs_u32x4* pB = ring + (BM + fr) * 12 + (kc ^ ((fr >> 2) & 3));           // 32 rows further: the same swizzle
+    gs_bf16x8 fa[2][3], fb[2][TN][3];
+    // fragment read r of a step: pieces of A and of the columns, in the order in which the products need them
+#define PS_READ(set_, st_, r_)                                                                                          \
+    {                                                                                                                   \
+        constexpr int g_ = (r_) / (TN + 1), i_ = (r_) % (TN + 1);                                                       \
+        if constexpr (g_ < 3) {                                                                                         \
+            if constexpr (i_ == 0) fa[set_][g_] = __builtin_bit_cast(gs_bf16x8, pA[(st_) * STAGE_V + g_ * 4]);          \
+            else fb[set_][i_ > 0 ? i_ - 1 : 0][g_] = __builtin_bit_cast(gs_bf16x8, pB[(st_) * STAGE_V + (i_ > 0 ? i_ - 1 : 0) * 384 + g_ * 4]); \
+        }                                                                                                               \
+    }
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 1) * LD) : "memory");
+    gs_for<3 * (TN + 1)>([&](auto r) { PS_READ(0, 0, decltype(r)::value); });
+    int st = 0;
+    auto step = [&](auto set_c) {
+        constexpr int set = decltype(set_c)::value;
+        const int nst = st + 1 == NS ? 0 : st + 1;
+        // this step's fragments are all read (its stage is free), the next step has landed
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 2) * LD) : "memory");
+        PS_OFFSETS();
+        gs_for<6 * TN>([&](auto q_c) {
+            constexpr int q = decltype(q_c)::value, p = q / TN, j = q % TN;
+            constexpr int pa[6] = {0, 0, 1, 1, 0, 2}, pb[6] = {0, 1, 0, 1, 2, 0};
+            acc[j][p > 0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][pa[p]], fb[set][j][pb[p]], acc[j][p > 0], 0, 0, 0);
+            PS_READ(set ^ 1, nst, q);
+            if constexpr (q % 2 == 1) PS_LOAD(q / 2);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        static_assert(LD <= 3 * TN, "a load behind every other MFMA");
+        PS_ADVANCE();
+        st = nst;
+    };
+#pragma unroll 1
+    for (int s = 0; s + 2 <= steps; s += 2) {
+        step(std::integral_constant<int, 0>{});
+        step(std::integral_constant<int, 1>{});
+    }
+    if (steps & 1) step(std::integral_constant<int, 0>{});      // (inside the loop the compiler moved all accumulators twice a round)
+#undef PS_READ
+#undef PS_LOAD
+#undef PS_OFFSETS
+#undef PS_ADVANCE
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    // element e of a lane: row 8 (e / 4) + 4 fh + e % 4, column fr of a 32 x 32 tile.  The two K groups of a wavefront tile share
+    // its rows out: group wk finishes the elements 8 wk .. 8 wk + 7, a column tile at a time (a loop: unrolled over the column tiles
+    // this was 25 KB of code that runs once a tile, 20 us of instruction fetches).
+    float* part = reinterpret_cast<float*>(gs_smem) + wm * 2 * TN * 1024 + lane;
+    auto at = [&](int g, int j, int e) -> float& { return part[((g * TN + j) * 16 + e) * 64]; };
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) at(wk, j, e) = acc[j][0][e] + acc[j][1][e];
+    __syncthreads();
+    const int row0 = wm * 32 + 16 * wk + 4 * fh;        // row of element e: row0 + 8 (e / 4) + e % 4
+    // sums of column tile j; one that is not finite is formed again in plain fp32 (the places (wk, j, 8 wk ..) are this
+    // wavefront's alone)
+    auto sums = [&](int j, float (&v)[8]) {
+        bool finite = true;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            v[e] = at(0, j, 8 * wk + e) + at(1, j, 8 * wk + e);
+            finite = finite && fabsf(v[e]) < INFINITY;
+        }
+        if (__any(!finite)) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) at(wk, j, 8 * wk + e) = v[e];
+            const int h = GEGLU && j >= TN / 2, col = packed(min(n0 + 32 * (j - h * (TN / 2)) + fr, ncols - 1), h);
+#pragma unroll 1
+            for (int e = 0; e < 8; ++e) {
+                const int m = row0 + 8 * (e >> 2) + (e & 3);
+                float& r = at(wk, j, 8 * wk + e);
+                if (fabsf(r) < INFINITY || s_tok[m] < 0) continue;
+                float s = 0.f;
+#pragma unroll 1
+                for (int tp = 0; tp < a.taps; ++tp) {
+                    const uint16_t* x = (const uint16_t*)a.A + (s_aoff[m] + (a.conv ? ((int64_t)(tp / tw) * a.geom.ppw + (tp % tw)) * a.lda : 0)) * 3;
+                    const float* w = (const float*)a.B + ((int64_t)tp * a.N + col) * K;
+#pragma unroll 1
+                    for (int k = 0; k < K; ++k) {
+                        const uint16_t* xp = x + piece_index(k);
+                        const float x0 = bf16_bits_to_float(xp[0]);
+                        const float xv = fabsf(x0) < INFINITY ? x0 + (bf16_bits_to_float(xp[32]) + bf16_bits_to_float(xp[64])) : x0;
+                        s = fmaf(xv, w[k], s);
+                    }
+                }
+                r = s;
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = at(wk, j, 8 * wk + e);
+        }
+    };
+    int64_t tok[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) tok[e] = s_tok[row0 + 8 * (e >> 2) + (e & 3)];
+    // residual of the next column tile
+    float rn[8];
+    auto res_load = [&](int j) {
+        const float* rp = (const float*)a.res + min(n0 + 32 * j + fr, ncols - 1);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) rn[e] = rp[max(tok[e], (int64_t)0) * a.ldr];
+    };
+    if (!GEGLU && a.res) res_load(0);
+#pragma unroll 1
+    for (int j = 0; j < (GEGLU ? TN / 2 : TN); ++j) {
+        float v[8], gate[GEGLU ? 8 : 1], r[8];
+        if (!GEGLU && a.res) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) r[e] = rn[e];
+            if (j + 1 < TN) res_load(j + 1);
+        }
+        sums(j, v);
+        if constexpr (GEGLU) sums(j + TN / 2, gate);
+        const int col = n0 + 32 * j + fr;
+        if (col >= ncols) break;
+        const int pc = packed(col, 0);
+        const float b0 = a.bias ? a.bias[pc] : 0.f, b1 = GEGLU && a.bias ? a.bias[pc + GEGLU_GROUP] : 0.f;
+        const int sg = GEGLU ? 0 : col / a.seg_cols;
+        const GemmSeg seg = sg == 0 ? a.seg[0] : (sg == 1 ? a.seg[1] : a.seg[2]);
+        const int sc = col - sg * a.seg_cols;
+        if constexpr (GEGLU) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = (v[e] + b0) * gelu_f(gate[e] + b1);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] += b0;
+            if (a.rowbias || a.rowscale) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int own = a.row_owner[max(tok[e], (int64_t)0) / a.geom.S];
+                    if (a.rowbias) v[e] += a.rowbias[(int64_t)own * a.N + col];
+                    if (a.act_gelu) v[e] = gelu_tanh_f(v[e]);
+                    if (a.rowscale) v[e] *= a.rowscale[(int64_t)own * a.rowscale_ld + col];
+                }
+            } else if (a.act_gelu) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = gelu_tanh_f(v[e]);
+            }
+            if (a.res) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] += r[e];
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] *= seg.scale;
+        }
+        if (a.out_pieces) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                if (tok[e] < 0) continue;
+                uint16_t* op = (uint16_t*)seg.ptr + tok[e] * 3 * seg.ld + piece_index(sc);
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) {
+                    const uint32_t u = __float_as_uint(v[e]);
+                    op[32 * pl] = (uint16_t)(u >> 16);
+                    v[e] -= __uint_as_float(u & 0xFFFF0000u);
+                }
+            }
+        } else {
+            const int64_t rs = seg.transposed ? 1 : seg.ld;
+            float* op = (float*)seg.ptr + (int64_t)sc * (seg.transposed ? seg.ld : 1);
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (tok[e] >= 0) op[tok[e] * rs] = v[e];
+        }
+    }
+}
+
+// Packed fp32 weights [rows][K] are followed, on the next 256-byte boundary, by their pieces (K a multiple of 32).
+static size_t split_offset(int64_t rows, int K) { return (rows * K * sizeof(float) + 255) / 256 * 256; }
+size_t packed_weight_bytes(int64_t rows, int32_t K, int dtype) {
+    return dtype == PSERVE_BF16 ? (size_t)rows * K * 2 : split_offset(rows, K) + (size_t)rows * 3 * K * 2;
+}
+__global__ void split_packed_kernel(const float* __restrict__ w, uint16_t* __restrict__ dst, int64_t rows, int32_t K) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= rows * K) return;
+    const int64_t r = i / K;
+    float v = w[i];
+#pragma unroll
+    for (int pl = 0; pl < 3; ++pl) {
+        const uint32_t u = __float_as_uint(v);
+        dst[r * 3 * K + piece_index((int)(i - r * K)) + 32 * pl] = (uint16_t)(u >> 16);
+        v -= __uint_as_float(u & 0xFFFF0000u);
+    }
+}
+int split_packed(void* packed, int64_t rows, int32_t K, int dtype, hipStream_t st) {
+    if (dtype == PSERVE_BF16 || K % 32 != 0) return PSERVE_OK;
+    split_packed_kernel<<<(unsigned)cdiv(rows * K, 256), 256, 0, st>>>((const float*)packed, (uint16_t*)((char*)packed + split_offset(rows, K)), rows, K);
+    return check_launch("split_packed_kernel");
+}
+
+template <int TN, bool GEGLU>
+static int launch_split(const GemmArgs& a, const uint16_t* Bs, hipStream_t st) {
+    using Cfg = SplitCfg<TN>;
+    PS_SET_LDS_ONCE((gemm_split_kernel<TN, GEGLU>), Cfg::LDS);
+    const dim3 grid((unsigned)cdiv(a.M, Cfg::BM), (unsigned)cdiv(a.N, Cfg::BN));         // (GEGLU: a.N packed columns)
+    gemm_split_kernel<TN, GEGLU><<<grid, 256, Cfg::LDS, st>>>(a, Bs);
+    return check_launch("gemm_split_kernel");
+}
+
+// Column tiles of 32 the split kernel takes a problem with (whose A would come in pieces), 0: not at all.  The modelled times
+// in us are within 15 % of what was measured at 576 .. 7,168 rows, 64 .. 320 columns, K = 64 .. 2,880: two tiles wide two blocks
+// run on a CU (0.33 us a step alone, 0.65 together), five tiles wide one (0.62 us a step on an idle chip, 0.80 on a full one).
+// Convolutions, fp32 kernel / two / five tiles wide: 7,168 x 320 162 / 100 / 78, 1,024 x 320 52 / 35 / 62, 2,304 x 256 50 / 30 / 53,
+// 4,096 x 96 19.5 / 16.1 / 25, 576 x 128 14.3 / 17.7 / 30.  Three and four tiles wide were between or behind in all of them.
+static int split_select(const GemmArgs& a) {
+    if (a.K % 32 != 0 || a.lda != a.K || a.classes) return 0;
+    if (gemm_a_rows(a) * a.lda * 6 >= (int64_t)1 << 31 || (int64_t)a.taps * a.N * a.K * 6 >= (int64_t)1 << 31) return 0;
+    if (((uintptr_t)a.A | (uintptr_t)a.B) & 15) return 0;
+    const bool geglu = a.epi == EPI_GEGLU;
+    const int64_t steps = (int64_t)a.taps * (a.K / 32), mt = cdiv(a.M, 64), t2 = mt * cdiv(a.N, 64), t5 = mt * cdiv(a.N, 160);
+    const int64_t r2 = t2 % 512, r5 = t5 % 256;
+    const double c2 = t2 / 512 * (steps * 0.65 + 4.0) + (r2 == 0 ? 0.0 : r2 <= 256 ? steps * 0.33 + 6.0 : steps * 0.65 + 6.0);
+    const double c5 = geglu || a.N % 160 != 0 ? 1e30 : t5 / 256 * (steps * 0.80 + 7.0) + (r5 == 0 ? 0.0 : steps * (0.62 + 0.18 * r5 / 256) + 7.0);
+    int bm, bn;
+    const double tiles = f32mma_tiles(a.M, geglu ? a.N / 2 : a.N, &bm, &bn) * (geglu ? 2 : 1);
+    const double plain = 4.5 + tiles * a.taps * a.K * (tiles < 0.6 ? 0.0304 : 0.0224);
+    return std::min(c2, c5) > 0.95 * plain ? 0 : c5 < c2 ? 5 : 2;
+}
+bool gemm_takes_pieces(const GemmArgs& a, int dtype, int mode) { return dtype == PSERVE_F32 && mode == 0 && split_select(a) != 0; }
+
+static int gemm_split(const GemmArgs& a, hipStream_t st) {
+    const uint16_t* Bs = (const uint16_t*)((const char*)a.B + split_offset((int64_t)a.taps * a.N, a.K));
+    const int tn = split_select(a);
+    PS_REQUIRE(tn, "gemm: activations in pieces for a layer that does not take them");
+    if (a.epi == EPI_GEGLU) return launch_split<2, true>(a, Bs, st);
+    return tn == 5 ? launch_split<5, false>(a, Bs, st) : launch_split<2, false>(a, Bs, st);
+}
+
+// For tests (host only, no part of the ABI): what split_select says of an fp32 layer of M rows (taps = 9: a 3x3 convolution).
+extern "C" int pserve_test_split_tiles(int32_t M, int32_t N, int32_t K, int32_t taps, int32_t geglu) {
+    GemmArgs a{};
+    a.M = M; a.N = N; a.K = a.lda = K; a.taps = taps; a.epi = geglu ? EPI_GEGLU : EPI_ROUTE;
+    return split_select(a);
 }
 
 // ---- packing kernels -----------------------------------------------------------------------------------
@@ -479,6 +828,7 @@ int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled);     // gem
 
 int gemm(const GemmArgs& a, int dtype, int mode, hipStream_t st) {
     PS_REQUIRE(a.M > 0 && a.N > 0 && a.K > 0, "gemm: empty problem");
+    if (a.a_pieces) return gemm_split(a, st);
     if (mode == 0 && dtype == PSERVE_BF16) {
         bool handled = false;
         PS_TRY(gemm_mfma_bf16(a, st, &handled));

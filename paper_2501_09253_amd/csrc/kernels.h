@@ -23,6 +23,10 @@ template <typename T> __device__ __forceinline__ void st_f(T* p, float v);
 template <> __device__ __forceinline__ void st_f<float>(float* p, float v) { *p = v; }
 template <> __device__ __forceinline__ void st_f<uint16_t>(uint16_t* p, float v) { *p = float_to_bf16_bits(v); }
 
+// fp32 rows as bf16 pieces: rows of [C / 32][3][32], three pieces of every value that sum to it exactly.  Index of the first
+// piece of value c; the others follow 32 and 64 further.
+__host__ __device__ __forceinline__ int piece_index(int c) { return (c >> 5) * 96 + (c & 31); }
+
 // Patch geometry shared by the kernels that walk tokens.
 struct PatchGeom {
     int32_t P, S, ph, pw;      // patches, tokens per patch, patch height / width
@@ -62,15 +66,16 @@ int split_with_stats(const pserve_plan_t* plan, const void* const* images, int32
 // y = x*scale+shift (then SiLU if silu).  padded: write into the interior of the padded patch buffer
 // [P][ph+2][pw+2][C]; else plain [T][C].  Only patches of `act` are written.  stitch (padded, all patches):
 // border tokens also fill the neighbours' ring slots / zero the own ring at image edges (no halo_gather needed).
+// pieces (fp32): every value as three bf16 pieces (piece_index).
 int gn_apply(const GroupNormArgs& a, const PatchGeom& g, int dtype, bool silu, bool padded, bool stitch, void* out,
-             ActiveList act, hipStream_t st);
+             ActiveList act, hipStream_t st, bool pieces = false);
 // Per-token LayerNorm over the C channels (biased variance) of the patches of `act`; out [T][C] at the same token
 // positions.  Affine part: gamma / beta [C] of the block dtype, or (gamma == nullptr) the adaptive form
 // xhat * (1 + scale) + shift with shift = mod[slot * mod_ld + c], scale = mod[slot * mod_ld + C + c], slot = owner[patch].
 // mod_txt (with patch_rc [P][2]): the table of the text patches (patch_rc[2p] < 0), mod being that of the image patches.
 int layer_norm(const void* x, const void* gamma, const void* beta, const float* mod, int64_t mod_ld, const int32_t* owner,
                int32_t C, float eps, const PatchGeom& g, int dtype, void* out, ActiveList act, hipStream_t st,
-               const float* mod_txt = nullptr, const int32_t* patch_rc = nullptr);
+               const float* mod_txt = nullptr, const int32_t* patch_rc = nullptr, bool pieces = false);
 // Fill the one-pixel ring of every active padded patch from the interiors of its neighbours (zeros outside the image).
 int halo_gather(void* apad, const int32_t* halo_src, const PatchGeom& g, int32_t C, int32_t ring, int dtype,
                 ActiveList act, hipStream_t st);
@@ -139,6 +144,8 @@ struct GemmArgs : GemmCore {
     const float* rowscale2;
     ActiveList act2;
     int32_t M2;
+    // fp32: A is in bf16 pieces (gemm_takes_pieces) / the output is written in pieces
+    int32_t a_pieces, out_pieces;
 };
 // Rows of A a problem can address: where rows are tokens, any token of the batch, however few patches its list has (the two
 // lists of a joint batch lie interleaved in one token matrix).
@@ -152,13 +159,18 @@ inline bool gemm_fits32(const GemmArgs& a) {
 }
 // true if gemm(a, ...) with its second problem will take a kernel that runs both in one launch
 bool gemm_takes_two(const GemmArgs& a, int dtype, int mode);
+// true if gemm(a, ...) is faster with its activations in bf16 pieces (a.a_pieces, which the caller then sets)
+bool gemm_takes_pieces(const GemmArgs& a, int dtype, int mode);
 // scratch a 3x3 convolution of M rows, N output and K input channels over this patch geometry can use (0: none)
 size_t conv_split_bytes(const PatchGeom& g, int32_t M, int32_t N, int32_t K, int dtype, int mode);
 // true if gemm(a, ...) will take a kernel that fills a.stats (the caller otherwise runs gn_stats on the output)
 bool gemm_emits_stats(const GemmArgs& a, int dtype, int mode);
 int gemm(const GemmArgs& a, int dtype, int mode, hipStream_t st);
 
-// weight packing into [taps][N][K] (K contiguous); all on device
+// Weight packing into [taps][N][K] (K contiguous); all on device.  A block's fp32 weights (rows = taps x N) are followed by
+// their bf16 pieces: packed_weight_bytes is the size of both, split_packed fills in the pieces once all rows are packed.
+size_t packed_weight_bytes(int64_t rows, int32_t K, int dtype);
+int split_packed(void* packed, int64_t rows, int32_t K, int dtype, hipStream_t st);
 int pack_conv(const void* w, void* dst, int32_t Cout, int32_t Cin, int dtype, hipStream_t st);
 // linear W[K][Ncols] -> rows [row0, row0+Ncols) of dst[Ntotal][K]
 int pack_linear(const void* w, void* dst, int32_t K, int32_t Ncols, int32_t row0, int dtype, hipStream_t st);
@@ -196,6 +208,7 @@ struct AttnArgs {
     int32_t qt;                // 1 or 2: the tables were built for query tiles of 128 * qt rows
     int32_t max_rows;          // host upper bound of the query rows of one request (its tokens)
     int32_t group;             // consecutive work items dealt to an XCD at a time (filled in by the launch)
+    int32_t out_pieces;        // fp32: O is written as bf16 pieces
 };
 // Item k of the work list of a call, longest first: request slots from the last (the plan sorts requests by size,
 // largest last) to the first, head-major inside a slot, so that consecutive items are consecutive query tiles of one head.

@@ -57,6 +57,25 @@ __device__ __forceinline__ void store_vec<uint16_t>(uint16_t* p, const float (&v
     *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// Output rows of the apply passes: the type's own values, or (fp32, PIECES) three bf16 pieces of each value, which sum to it
+// exactly (piece_index).  row: first element of the row, c: the vector's first channel.
+template <typename T, bool PIECES>
+__device__ __forceinline__ void store_out(T* out, int64_t row, int c, const float (&v)[Vec<T>::N]) {
+    if constexpr (!PIECES) {
+        store_vec<T>(out + row + c, v);
+    } else {
+        float r[4] = {v[0], v[1], v[2], v[3]};
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) {
+            uint32_t u[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { u[e] = __float_as_uint(r[e]); r[e] -= __uint_as_float(u[e] & 0xFFFF0000u); }
+            *reinterpret_cast<uint2*>((uint16_t*)out + row + piece_index(c) + 32 * pl) =
+                make_uint2(__builtin_amdgcn_perm(u[1], u[0], 0x07060302), __builtin_amdgcn_perm(u[3], u[2], 0x07060302));
+        }
+    }
+}
+
 // 16 raw bytes of a row now, floats later: lets a kernel issue its row loads before loads it would otherwise wait for
 template <typename T>
 __device__ __forceinline__ void unpack_vec(const uint4& q, float (&v)[Vec<T>::N]);
@@ -292,10 +311,11 @@ __device__ __forceinline__ float silu_f(float v) { return v * __builtin_amdgcn_r
 // token's normalised value is also written into the ring slot of every same-image neighbour patch that needs
 // it; where that neighbour is absent (image edge) the token zero-fills the matching ring slot of its OWN patch.
 // Every ring slot of every patch is written by exactly one thread, so there is no race and no extra pass.
-template <typename T>
+template <typename T, bool PIECES>
 __device__ __forceinline__ void stitch_store(T* __restrict__ out, const int32_t (&nb)[8], const PatchGeom& gm,
                                              int p, int y, int x, int C, int coff, const float (&v)[Vec<T>::N]) {
     if (y != 0 && y != gm.ph - 1 && x != 0 && x != gm.pw - 1) return;
+    const int CW = PIECES ? 3 * C : C;
     float z[Vec<T>::N];
 #pragma unroll
     for (int e = 0; e < Vec<T>::N; ++e) z[e] = 0.f;
@@ -309,9 +329,9 @@ __device__ __forceinline__ void stitch_store(T* __restrict__ out, const int32_t 
             if (on) {
                 const int q = nb[k];
                 if (q >= 0)
-                    store_vec<T>(out + ((int64_t)q * gm.pS + (y - dy * gm.ph + 1) * gm.ppw + (x - dx * gm.pw + 1)) * C + coff, v);
+                    store_out<T, PIECES>(out, ((int64_t)q * gm.pS + (y - dy * gm.ph + 1) * gm.ppw + (x - dx * gm.pw + 1)) * CW, coff, v);
                 else
-                    store_vec<T>(out + ((int64_t)p * gm.pS + (y + dy + 1) * gm.ppw + (x + dx + 1)) * C + coff, z);
+                    store_out<T, PIECES>(out, ((int64_t)p * gm.pS + (y + dy + 1) * gm.ppw + (x + dx + 1)) * CW, coff, z);
             }
             ++k;
         }
@@ -319,12 +339,13 @@ __device__ __forceinline__ void stitch_store(T* __restrict__ out, const int32_t 
 
 // rim_only (padded output): patches with rim_only[p] != 0 are not convolved themselves (their result is reused); only
 // their border tokens are normalised, because the neighbours' rings need them.
-template <typename T, bool SILU, bool PADDED, bool STITCH>
+template <typename T, bool SILU, bool PADDED, bool STITCH, bool PIECES>
 __global__ void gn_apply_kernel(const T* __restrict__ x, const float* __restrict__ scale_shift,
                                 const int32_t* __restrict__ owner, const int32_t* __restrict__ neighbour, PatchGeom gm,
                                 int32_t C, int32_t nsplit, int32_t TL, ActiveList act, const uint8_t* __restrict__ rim_only,
                                 T* __restrict__ out) {
     constexpr int VN = Vec<T>::N;
+    const int CW = PIECES ? 3 * C : C;          // elements of an output row
     int p = blockIdx.x;
     if (act.active) {
         if (p >= *act.count) return;
@@ -357,8 +378,8 @@ __global__ void gn_apply_kernel(const T* __restrict__ x, const float* __restrict
                 v[e] = fmaf(v[e], sc[e], sh[e]);
                 if (SILU) v[e] = silu_f(v[e]);
             }
-            store_vec<T>(out + ((int64_t)p * gm.pS + (y + 1) * gm.ppw + xx + 1) * C + cvb * VN, v);
-            if (STITCH) stitch_store<T>(out, nbr, gm, p, y, xx, C, cvb * VN, v);
+            store_out<T, PIECES>(out, ((int64_t)p * gm.pS + (y + 1) * gm.ppw + xx + 1) * CW, cvb * VN, v);
+            if (STITCH) stitch_store<T, PIECES>(out, nbr, gm, p, y, xx, C, cvb * VN, v);
         }
         return;
     }
@@ -372,14 +393,14 @@ __global__ void gn_apply_kernel(const T* __restrict__ x, const float* __restrict
     const int pw = gm.pw;
     const int dyy = TL / pw, dxx = TL - dyy * pw;                       // one row step in pixel rows / columns
     const int step_in = TL * C;
-    const int step_out = PADDED ? (dyy * gm.ppw + dxx) * C : TL * C;
-    const int wrap_out = PADDED ? (gm.ppw - pw) * C : 0;                // extra when the column wraps into the next pixel row
+    const int step_out = PADDED ? (dyy * gm.ppw + dxx) * CW : TL * CW;
+    const int wrap_out = PADDED ? (gm.ppw - pw) * CW : 0;                // extra when the column wraps into the next pixel row
     int tb = t0 + tl;
     int py = tb / pw, px = tb - py * pw;
     const T* xin = x + ((int64_t)p * gm.S) * C + cv * VN;
-    T* po = out + ((int64_t)p * (PADDED ? gm.pS : gm.S)) * C + cv * VN;
+    const int64_t po = ((int64_t)p * (PADDED ? gm.pS : gm.S)) * CW;
     int in_off = tb * C;
-    int out_off = (PADDED ? (py + 1) * gm.ppw + px + 1 : tb) * C;
+    int out_off = (PADDED ? (py + 1) * gm.ppw + px + 1 : tb) * CW;
     const int last_in = (t1 - 1) * C;
     // The row loads of the first batch go first: they depend on the patch only, while scale / shift hang on the
     // owner table (two dependent loads).  Up to GN_U independent 16-byte loads in flight per thread; rows past the
@@ -419,8 +440,8 @@ __global__ void gn_apply_kernel(const T* __restrict__ x, const float* __restrict
                     v[u][e] = fmaf(v[u][e], sc[e], sh[e]);
                     if (SILU) v[u][e] = silu_f(v[u][e]);
                 }
-                store_vec<T>(po + out_off, v[u]);
-                if (PADDED && STITCH) stitch_store<T>(out, nb, gm, p, py, px, C, cv * VN, v[u]);
+                store_out<T, PIECES>(out, po + out_off, cv * VN, v[u]);
+                if (PADDED && STITCH) stitch_store<T, PIECES>(out, nb, gm, p, py, px, C, cv * VN, v[u]);
             }
             // next row of this thread
             px += dxx;
@@ -452,7 +473,7 @@ __device__ __forceinline__ float lane_sum(float v, int lpt) {
     return v;
 }
 
-template <typename T, int VPL, bool MOD>
+template <typename T, int VPL, bool MOD, bool PIECES>
 __global__ void __launch_bounds__(256)
 layer_norm_kernel(const T* __restrict__ x, const T* __restrict__ gamma, const T* __restrict__ beta,
                   const float* __restrict__ mod, int64_t mod_ld, const int32_t* __restrict__ owner,
@@ -526,7 +547,7 @@ layer_norm_kernel(const T* __restrict__ x, const T* __restrict__ gamma, const T*
             }
         }
         const float rstd = 1.f / sqrtf(lane_sum(s2, LPT) * inv_c + eps);
-        T* po = out + ((int64_t)p * S + t) * C;
+        const int64_t po = ((int64_t)p * S + t) * (PIECES ? 3 * C : C);
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
             as_loaded(cur[k]);
@@ -544,7 +565,7 @@ layer_norm_kernel(const T* __restrict__ x, const T* __restrict__ gamma, const T*
                 unpack_vec<T>(cur[k], v);
 #pragma unroll
                 for (int e = 0; e < VN; ++e) v[e] = fmaf((v[e] - mean) * rstd, g[e], b[e]);
-                store_vec<T>(po + (sub + k * LPT) * VN, v);
+                store_out<T, PIECES>(out, po, (sub + k * LPT) * VN, v);
             }
         }
     }
@@ -637,16 +658,24 @@ constexpr int APPLY_ROWS = 4;        // rows per thread of the apply pass (measu
 
 template <typename T>
 static void launch_apply(const GroupNormArgs& a, const PatchGeom& g, bool silu, bool padded, bool stitch, void* out,
-                         ActiveList act, int CV, int TL, hipStream_t st) {
+                         ActiveList act, int CV, int TL, bool pieces, hipStream_t st) {
     // Own chunking (independent of the statistics pass): about APPLY_ROWS rows per thread.  Many short blocks are
     // dispatched over time, so some load while others compute or store; with few long blocks every wavefront of
     // the chip is in the same phase at once.
     const int nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(cdiv(g.S, (int64_t)APPLY_ROWS * TL), 65535));
     dim3 grid(g.P, nsplit);
     const int nt = TL * CV;
-#define PS_APPLY(SI, PA, ST)                                                                                      \
-    gn_apply_kernel<T, SI, PA, ST><<<grid, nt, 0, st>>>((const T*)a.x, a.scale_shift, a.owner, a.neighbour, g, a.C, \
-                                                        nsplit, TL, act, a.rim_only, (T*)out)
+#define PS_APPLY_(SI, PA, ST, PI)                                                                                     \
+    gn_apply_kernel<T, SI, PA, ST, PI><<<grid, nt, 0, st>>>((const T*)a.x, a.scale_shift, a.owner, a.neighbour, g, a.C, \
+                                                            nsplit, TL, act, a.rim_only, (T*)out)
+#define PS_APPLY(SI, PA, ST) PS_APPLY_(SI, PA, ST, false)
+    if constexpr (sizeof(T) == 4) {
+        if (pieces) {                       // what feeds a layer: the stitched form of a convolution, the plain one of an attention
+            if (padded) PS_APPLY_(true, true, true, true);
+            else PS_APPLY_(false, false, false, true);
+            return;
+        }
+    }
     if (silu && padded && stitch) PS_APPLY(true, true, true);
     else if (padded && stitch) PS_APPLY(false, true, true);
     else if (silu && padded) PS_APPLY(true, true, false);
@@ -654,37 +683,43 @@ static void launch_apply(const GroupNormArgs& a, const PatchGeom& g, bool silu, 
     else if (padded) PS_APPLY(false, true, false);
     else PS_APPLY(false, false, false);
 #undef PS_APPLY
+#undef PS_APPLY_
 }
 
 int gn_apply(const GroupNormArgs& a, const PatchGeom& g, int dtype, bool silu, bool padded, bool stitch, void* out,
-             ActiveList act, hipStream_t st) {
+             ActiveList act, hipStream_t st, bool pieces) {
     int CV, TL;
     PS_TRY(norm_layout(a.C, dtype, &CV, &TL));
+    PS_REQUIRE(!pieces || (dtype == PSERVE_F32 && silu == padded && stitch == padded), "gn_apply: no such form in pieces");
     PS_REQUIRE(!stitch || (padded && a.neighbour && !act.active), "gn_apply: stitching needs the padded layout and all patches");
-    if (dtype == PSERVE_BF16) launch_apply<uint16_t>(a, g, silu, padded, stitch, out, act, CV, TL, st);
-    else launch_apply<float>(a, g, silu, padded, stitch, out, act, CV, TL, st);
+    if (dtype == PSERVE_BF16) launch_apply<uint16_t>(a, g, silu, padded, stitch, out, act, CV, TL, false, st);
+    else launch_apply<float>(a, g, silu, padded, stitch, out, act, CV, TL, pieces, st);
     return check_launch("gn_apply_kernel");
 }
 
 template <typename T>
 static void launch_layer_norm(const void* x, const void* gamma, const void* beta, const float* mod, int64_t mod_ld,
                               const int32_t* owner, const float* mod_txt, const int32_t* patch_rc, int32_t C, float eps,
-                              const PatchGeom& g, void* out, ActiveList act, int LPT, int VPL, hipStream_t st) {
+                              const PatchGeom& g, void* out, ActiveList act, int LPT, int VPL, bool pieces, hipStream_t st) {
     const int tpb = 256 / LPT;
     // one token per lane group while that gives at most ~16 blocks per CU, else more tokens per group
     int64_t per = 1;
     while (per < 8 && g.P * cdiv(g.S, tpb * per) > 4096) per *= 2;
     dim3 grid(g.P, (unsigned)std::max<int64_t>(1, std::min<int64_t>(cdiv(g.S, tpb * per), 65535)));
-#define PS_LNK(V, M) layer_norm_kernel<T, V, M><<<grid, 256, 0, st>>>((const T*)x, (const T*)gamma, (const T*)beta, mod, mod_ld, owner, mod_txt, patch_rc, C, g.S, LPT, eps, act, (T*)out)
+    constexpr bool F32 = sizeof(T) == 4;
+#define PS_LNP(V, M, PI) layer_norm_kernel<T, V, M, PI><<<grid, 256, 0, st>>>((const T*)x, (const T*)gamma, (const T*)beta, mod, mod_ld, owner, mod_txt, patch_rc, C, g.S, LPT, eps, act, (T*)out)
+#define PS_LNK(V, M) do { if (F32 && pieces) PS_LNP(V, M, F32); else PS_LNP(V, M, false); } while (0)
 #define PS_LN(V) case V: if (mod) PS_LNK(V, true); else PS_LNK(V, false); break
     switch (VPL) { PS_LN(1); PS_LN(2); PS_LN(3); PS_LN(4); PS_LN(5); PS_LN(6); PS_LN(7); PS_LN(8); }
 #undef PS_LN
 #undef PS_LNK
+#undef PS_LNP
 }
 
 int layer_norm(const void* x, const void* gamma, const void* beta, const float* mod, int64_t mod_ld, const int32_t* owner,
                int32_t C, float eps, const PatchGeom& g, int dtype, void* out, ActiveList act, hipStream_t st,
-               const float* mod_txt, const int32_t* patch_rc) {
+               const float* mod_txt, const int32_t* patch_rc, bool pieces) {
+    PS_REQUIRE(!pieces || dtype == PSERVE_F32, "LayerNorm: pieces are those of fp32 values");
     PS_REQUIRE((gamma && beta) || (mod && owner), "LayerNorm: neither gamma / beta nor a modulation table");
     if (gamma) mod = nullptr;
     const int vn = dtype == PSERVE_BF16 ? 8 : 4;
@@ -697,8 +732,8 @@ int layer_norm(const void* x, const void* gamma, const void* beta, const float* 
         const int v = (int)cdiv(CV, l);
         if (v <= 8 && v * l - CV < waste) { LPT = l; VPL = v; waste = v * l - CV; }
     }
-    if (dtype == PSERVE_BF16) launch_layer_norm<uint16_t>(x, gamma, beta, mod, mod_ld, owner, mod_txt, patch_rc, C, eps, g, out, act, LPT, VPL, st);
-    else launch_layer_norm<float>(x, gamma, beta, mod, mod_ld, owner, mod_txt, patch_rc, C, eps, g, out, act, LPT, VPL, st);
+    if (dtype == PSERVE_BF16) launch_layer_norm<uint16_t>(x, gamma, beta, mod, mod_ld, owner, mod_txt, patch_rc, C, eps, g, out, act, LPT, VPL, false, st);
+    else launch_layer_norm<float>(x, gamma, beta, mod, mod_ld, owner, mod_txt, patch_rc, C, eps, g, out, act, LPT, VPL, pieces, st);
     return check_launch("layer_norm_kernel");
 }
 

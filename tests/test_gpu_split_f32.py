@@ -1,0 +1,80 @@
+"""GPU: fp32 layers on the bf16 matrix cores (operands in three bf16 pieces), at ragged rows and columns, odd numbers of steps, with
+masks, per-request biases and gates, against the oracle; each case checks that its layers take that kernel.
+
+Bar: sums of up to 2,880 terms with a rounding of 2^-24 every 16 of them are good to sqrt(180) * 6e-8 = 8e-7 of their deviation; the
+largest of a million values is five deviations out and a block chains up to four layers: 2e-5 of the largest value."""
+import numpy as np
+import pytest
+
+import paper_2501_09253_amd as ps
+import workloads as wl
+from oracle import block as ob
+
+torch = pytest.importorskip("torch")
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(), reason="no GPU")]
+
+from harness import GpuRun, rel_err                      # noqa: E402
+
+
+def _layer(cfg, name):
+    C, T = cfg.C, sum(h * w for h, w in cfg.resolutions)
+    F = cfg.ffn_mult * C
+    M, N, K, taps, geglu = {"conv": (T, C, C, 9, 0), "qkv": (T, 3 * C, C, 1, 0), "out": (T, C, C, 1, 0), "geglu": (T, 2 * F, C, 1, 1),
+                            "ffn_out": (T, C, F, 1, 0), "mlp_in": (T, F, C, 1, 0)}[name]
+    return ps.lib().pserve_test_split_tiles(M, N, K, taps, geglu)
+
+
+CASES = {
+    # rows and columns that end inside a tile (96 = 64 + 32, 224 = 3 x 64 + 32), an odd number of steps (9 x 3, 9 x 7)
+    "conv_96": dict(res=[(54, 50), (10, 30)], patch=(2, 10), C=96, stages=("RES2T",), temb_dim=24, tiles=dict(conv=2)),
+    "conv_224_reuse": dict(res=[(24, 40), (40, 32)], patch=(8, 8), C=224, stages=("RES2", "SATTN"), reuse_p=0.4, tiles=dict(conv=2)),
+    "conv_320": dict(res=[(64, 64), (48, 62)], patch=(16, 2), C=320, stages=("RES1",), tiles=dict(conv=5)),
+    "qkv_wide": dict(res=[(48, 48), (8, 12)], patch=(4, 4), C=320, stages=("LSATTN",), tiles=dict(qkv=5)),
+    "geglu": dict(res=[(40, 40), (29, 31)], patch=(1, 1), C=160, stages=("LFFN",), tiles=dict(geglu=2)),
+    "geglu_pieces_out": dict(res=[(40, 40), (36, 22)], patch=(4, 2), C=160, stages=("LFFN",), tiles=dict(geglu=2, ffn_out=2)),
+    "gate_gelu": dict(res=[(40, 40), (24, 35)], patch=(8, 5), C=256, stages=("ASATTN", "AMLP"), temb_dim=20, tiles=dict(qkv=2, out=2, mlp_in=2)),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_against_oracle(name):
+    c = dict(CASES[name])
+    tiles, res, patch, C, stages = c.pop("tiles"), c.pop("res"), c.pop("patch"), c.pop("C"), c.pop("stages")
+    cfg = wl.custom_config(res, patch, C=C, G=8, heads=C // 32, stages=stages, dtype="f32", seed=61, **c)
+    assert {k: _layer(cfg, k) for k in tiles} == tiles
+    w = wl.make_workload(cfg)
+    run = GpuRun(w)
+    if w.cache is not None:
+        run.load_cache()
+    got = run.forward_images(reuse=w.reuse)
+    ref, _ = ob.forward_batch(w.images, cfg.stages, w.params, G=cfg.G, heads=cfg.heads, eps=cfg.eps, ctx=w.ctx, reuse=w.reuse,
+                              cache=w.cache, temb=w.temb)
+    err = rel_err(got, ref)
+    assert np.isfinite(err) and err < 2e-5, err
+
+
+@pytest.mark.parametrize("where", ["w1", "w2", "conv_w"])
+def test_values_that_are_not_finite(where):
+    """Infinite weights (and, behind w1, infinite and undefined activations) give what plain fp32 sums give: the plain kernel of
+    the library, element by element."""
+    stages, C = (("RES1",), 192) if where == "conv_w" else (("LFFN",), 160)
+    cfg = wl.custom_config([(40, 40), (40, 24)], (8, 8), C=C, G=8, heads=1, stages=stages, dtype="f32", seed=67)
+    assert _layer(cfg, "conv") == 2 if where == "conv_w" else _layer(cfg, "geglu") == 2 and _layer(cfg, "ffn_out") == 2
+    w = wl.make_workload(cfg)
+    p = w.params[0][where]
+    if where == "conv_w":
+        p[5, 7, 1, 1], p[6, 3, 0, 2] = np.inf, np.nan
+    else:
+        p[3, 5], p[9, 70] = np.inf, -np.inf
+    got = GpuRun(w).forward_images()
+    ps.set_kernel_mode(1)
+    try:
+        ref = GpuRun(w).forward_images()
+    finally:
+        ps.set_kernel_mode(0)
+    for a, b in zip(got, ref):
+        assert np.isinf(b).any()
+        assert np.array_equal(np.isnan(a), np.isnan(b))
+        assert np.array_equal(np.where(np.isinf(a), np.sign(a), 0), np.where(np.isinf(b), np.sign(b), 0))
+        ok = np.isfinite(b)
+        assert not ok.any() or np.abs(a[ok] - b[ok]).max() < 2e-5 * np.abs(b[ok]).max()      # (behind w1 nothing is finite)
