@@ -324,16 +324,7 @@ attn_f32mma_kernel(AttnArgs a, int group) {
         if constexpr (sizeof(T) == 2)
             *reinterpret_cast<uint2*>(op + c) = make_uint2(pack_bf16x2(v.x * inv, v.y * inv), pack_bf16x2(v.z * inv, v.w * inv));
         else if (a.out_pieces) {
-            uint16_t* o16 = (uint16_t*)a.O + token(r0 + qr) * 3 * C + piece_index(h * d + c);
-            v *= inv;
-#pragma unroll
-            for (int pl = 0; pl < 3; ++pl) {
-                uint32_t u[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) { u[e] = __float_as_uint(v[e]); v[e] -= __uint_as_float(u[e] & 0xFFFF0000u); }
-                *reinterpret_cast<uint2*>(o16 + 32 * pl) =
-                    make_uint2(__builtin_amdgcn_perm(u[1], u[0], 0x07060302), __builtin_amdgcn_perm(u[3], u[2], 0x07060302));
-            }
+            store_pieces4((uint16_t*)a.O + token(r0 + qr) * 3 * C + piece_index(h * d + c), v.x * inv, v.y * inv, v.z * inv, v.w * inv);
         } else
             *reinterpret_cast<at_f32x4*>(op + c) = v * inv;
     }
@@ -360,6 +351,335 @@ static int attn_f32mma(const AttnArgs& a, hipStream_t st) {
 #undef PS_AF
 }
 
+// ---- fp32 self-attention on the bf16 matrix cores ---------------------------------------------------------
+// As the fp32 layers: every operand in three bf16 pieces that sum to it, six products of which all terms are exact in the fp32
+// accumulators.  attn_cut_kernel lays the keys and values of a request out in tiles of 32 keys and one head, K rows of
+// [3][D] and V^T rows of [3][32], in the very order (swizzle included) in which a tile lies in LDS: a tile is one linear copy.
+// attn_split_kernel: a block is 128 queries of one (request, head), four wavefronts of 32; K and V^T fragments and P stay as in
+// the bf16 kernel (a lane owns a query column, its eight scores of a 16-key step are consecutive keys), Q is cut once, P in
+// registers.  Two blocks a CU.  A step forms the scores of the NEXT tile while the softmax of this one runs (24 MFMAs beside
+// most of its ~270 vector instructions), then the output products; keys and values have rings of three stages of their own,
+// filled two steps ahead.  The softmax reference moves only when a score passes it by 8 (a factor of 256 costs fp32 nothing).
+// Requests of 4,096 and 3,072 tokens, 5 heads of 64 (280 blocks of 128 and 96 tiles): 360 (fp32 kernel) -> 231 us = 145 TFLOP/s of
+// fp32; bound by the issue of MFMAs (1,536 clocks a tile) and vector instructions and by 280 blocks on 256 CUs.
+constexpr int ASP_NS = 3;
+template <int D> struct AttnSplitCfg {
+    static constexpr int KV = 3 * 32 * D / 8, TILE_V = 2 * KV;       // 16-byte slots of the keys, of a tile
+    static constexpr int LPT = TILE_V / 256;                         // direct loads of a wavefront and tile
+    static constexpr size_t LDS = (size_t)ASP_NS * TILE_V * 16;
+};
+typedef __attribute__((ext_vector_type(8))) __bf16 at_bf16x8;
+typedef __attribute__((ext_vector_type(4))) uint32_t at_u32x4;
+typedef __attribute__((address_space(3))) void at_lds_void;
+template <int D> __device__ __forceinline__ int at_swz(int row) { return D == 64 ? (row >> 1) & 7 : (row >> 2) & 3; }
+// first tile of request slot s: room for the tiles of all slots before it
+__device__ __forceinline__ int64_t at_tile0(const int32_t* cu_seqlens, int s) { return cu_seqlens[s] / 32 + s; }
+// three pieces of eight values
+__device__ __forceinline__ void at_cut(const float (&x)[8], at_u32x4 (&o)[3]) {
+    uint32_t u[8][3];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) cut3(x[i], u[i]);
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[p][q] = pack_hi16(u[2 * q][p], u[2 * q + 1][p]);
+}
+
+// Block = (tile of the grid's upper bound, head); tiles that no request has are left alone.
+template <int D>
+__global__ void __launch_bounds__(4 * D)
+attn_cut_kernel(const float* __restrict__ K, const float* __restrict__ V, const int32_t* __restrict__ cu_seqlens,
+                const int32_t* __restrict__ seq_len, int32_t n, int32_t C, at_u32x4* __restrict__ out) {
+    using Cfg = AttnSplitCfg<D>;
+    const int64_t tile = blockIdx.x;
+    const int h = blockIdx.y, tid = threadIdx.x;
+    int lo = 0, hi = n;                                 // largest s with tile0(s) <= tile
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (at_tile0(cu_seqlens, mid) <= tile) lo = mid; else hi = mid;
+    }
+    const int64_t k0 = cu_seqlens[lo];
+    const int nk = seq_len ? seq_len[lo] : cu_seqlens[lo + 1] - (int)k0, key0 = (int)(tile - at_tile0(cu_seqlens, lo)) * 32;
+    if (key0 >= nk) return;
+    at_u32x4* dst = out + (tile * gridDim.y + h) * Cfg::TILE_V;
+    const float* Kh = K + k0 * C + h * D;
+    const float* Vh = V + k0 * C + h * D;
+    float x[8];
+    at_u32x4 o[3];
+    {                                                   // eight channels of a key
+        const int r = tid / (D / 8), c = tid % (D / 8), key = key0 + r;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const at_f32x4 w = *reinterpret_cast<const at_f32x4*>(Kh + (int64_t)min(key, nk - 1) * C + 8 * c + 4 * q);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[4 * q + i] = key < nk ? w[i] : 0.f;
+        }
+        at_cut(x, o);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) dst[r * (3 * D / 8) + p * (D / 8) + (c ^ at_swz<D>(r))] = o[p];
+    }
+    {                                                   // eight keys of a channel
+        const int ch = tid % D, c = tid / D;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int key = key0 + 8 * c + i;
+            const float w = Vh[(int64_t)min(key, nk - 1) * C + ch];
+            x[i] = key < nk ? w : 0.f;
+        }
+        at_cut(x, o);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) dst[Cfg::KV + ch * 12 + p * 4 + (c ^ at_swz<32>(ch))] = o[p];
+    }
+}
+
+template <int D>
+__global__ void __launch_bounds__(256, 2)
+attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv) {
+    using Cfg = AttnSplitCfg<D>;
+    constexpr int KS = D / 16, DT = D / 32, LPT = Cfg::LPT, TILE_V = Cfg::TILE_V, KV = Cfg::KV;
+    extern __shared__ __attribute__((aligned(16))) float at_smem[];
+    at_u32x4* ring = reinterpret_cast<at_u32x4*>(at_smem);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int fr = lane & 31, fh = lane >> 5;
+    const int seq = blockIdx.x >> 3, grp = seq / a.group;
+    const int it = (grp * 8 + (blockIdx.x & 7)) * a.group + (seq - grp * a.group);
+    int s, h, tile;
+    if (!attn_item_at(a, it / a.qt, s, h, tile)) return;
+    const int S = a.geom.S, C = a.C;
+    const int rows_s = (a.act_off[s + 1] - a.act_off[s]) * S;
+    const int r0 = (tile * a.qt + it % a.qt) * 128;
+    if (r0 >= rows_s) return;
+    const int64_t k0 = a.cu_seqlens[s];
+    const int nk = a.seq_len ? a.seq_len[s] : a.cu_seqlens[s + 1] - (int)k0;
+    const int steps = (nk + 31) / 32;
+    const at_u32x4* src = tiles_kv + (at_tile0(a.cu_seqlens, s) * a.heads + h) * TILE_V;
+    const int64_t src_step = (int64_t)a.heads * TILE_V;
+    // Keys of tile tk and values of tile tv into stages of their own (past the end: the last tile again, never read).  Buffer
+    // loads: behind flat ones the compiler waits for all LDS reads in flight instead of counting them.
+    auto issue = [&](int tk, int tv, bool values) {
+#if defined(__HIP_DEVICE_COMPILE__)
+        const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc((void*)(src + min(tk, steps - 1) * src_step), 0, TILE_V * 16, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void*)(src + min(tv, steps - 1) * src_step), 0, TILE_V * 16, 0x00020000);
+        at_u32x4* dk = ring + tk % ASP_NS * KV;
+        at_u32x4* dv = ring + (ASP_NS - 1 + tv % ASP_NS) * KV;         // (index i counts on behind the keys of a tile)
+#pragma unroll
+        for (int i = 0; i < LPT; ++i) {
+            const int idx = wave + 4 * i;
+            if (idx < KV / 64) __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (at_lds_void*)(dk + idx * 64), 16, tid * 16, i * 4096, 0, 0);
+            else if (values) __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (at_lds_void*)(dv + idx * 64), 16, tid * 16, i * 4096, 0, 0);
+        }
+#endif
+    };
+    issue(0, 0, false);
+    issue(1, 0, true);
+    issue(2, 1, true);
+    auto token = [&](int r) -> int64_t {                // compact row of the request -> token
+        const int pi = a.act_off[s] + r / S;
+        const int p = a.act.active ? a.act.active[pi] : pi;
+        return (int64_t)p * S + (r - (r / S) * S);
+    };
+    const int my_row = r0 + wave * 32 + fr;
+    const int64_t tok = token(min(my_row, rows_s - 1));
+    at_bf16x8 q[3][KS];
+    {
+        const float* qp = (const float*)a.Q + tok * C + h * D + 8 * fh;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const at_f32x4 w0 = *reinterpret_cast<const at_f32x4*>(qp + 16 * ks), w1 = *reinterpret_cast<const at_f32x4*>(qp + 16 * ks + 4);
+            const float x[8] = {w0[0], w0[1], w0[2], w0[3], w1[0], w1[1], w1[2], w1[3]};
+            at_u32x4 o[3];
+            at_cut(x, o);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) q[p][ks] = __builtin_bit_cast(at_bf16x8, o[p]);
+        }
+    }
+    const int krow = (fr & ~12) | ((fr & 4) << 1) | ((fr & 8) >> 1);         // key of MFMA row fr (bits 2 and 3 swapped)
+    const at_u32x4* pK = ring + krow * (3 * D / 8);
+    const at_u32x4* pV = ring + ASP_NS * KV + fr * 12;
+    const int ksw = at_swz<D>(krow), vsw = at_swz<32>(fr);
+    at_f32x16 sc[2];                                    // scores of a tile: products of the large pieces, the others
+    // Fragments of 16 channels (keys) / of 16 keys x 32 channels (values).  Product n takes pieces pa[n] and pb[n] (n = 1 the large
+    // ones): piece 0 is read two products into the set before into registers of its own, piece 1 behind the last product of the
+    // set before that reads it (n = 3), piece 2 at the head of its set, five products ahead.
+    constexpr int pa[6] = {0, 0, 1, 1, 0, 2}, pb[6] = {1, 0, 0, 1, 2, 0};
+    at_bf16x8 kf[4], vf[4];                             // pieces 0 (two sets), 1, 2
+    auto at_piece = [](int set, int pl) constexpr { return pl == 0 ? set & 1 : 1 + pl; };
+    auto read_k = [&](int st, int ks, int pl) {
+        kf[at_piece(ks, pl)] = __builtin_bit_cast(at_bf16x8, pK[st * KV + pl * (D / 8) + ((2 * ks + fh) ^ ksw)]);
+    };
+    auto read_v = [&](int st, int f, int pl) {          // f: 16-key step f / DT, channels 32 (f % DT) ..
+        vf[at_piece(f, pl)] = __builtin_bit_cast(at_bf16x8, pV[st * KV + (f % DT) * 384 + pl * 4 + ((2 * (f / DT) + fh) ^ vsw)]);
+    };
+    const at_f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    auto score = [&](int ks, int n) {
+        at_f32x16& c = sc[n != 1];
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[at_piece(ks, pa[n])], q[pb[n]][ks], ks == 0 && n < 2 ? zero16 : c, 0, 0, 0);
+    };
+    // Output: products of the large pieces, the others (beside a large sum the matrix unit cuts small products off), and the
+    // total they are added to every ATT_FLUSH tiles (the rounding errors of a long chain).
+    constexpr int ATT_FLUSH = 8;
+    at_f32x16 o[DT], ol[DT], ot[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[dt][e] = ol[dt][e] = ot[dt][e] = 0.f;
+    float m = -INFINITY, l = 0.f, p[16], mx;
+    // the scores of tile t are summed (p, their maximum in mx): those behind the last key are masked, the lane halves meet
+    auto finish = [&](int t) {
+        if ((t + 1) * 32 > nk) {
+            mx = -INFINITY;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                if (t * 32 + 16 * (e >> 3) + 8 * fh + (e & 7) >= nk) p[e] = -INFINITY;
+                mx = fmaxf(mx, p[e]);
+            }
+        }
+        const uint32_t u = __float_as_uint(mx);
+        const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        mx = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    };
+    auto add_scores = [&](int e) {
+        p[e] = sc[0][e] + sc[1][e];
+        mx = e == 0 ? p[0] : fmaxf(mx, p[e]);
+    };
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * LPT) : "memory");     // the keys of tile 0 have landed
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) read_k(0, ks, pl);
+#pragma unroll
+        for (int n = 0; n < 6; ++n) score(ks, n);
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) add_scores(e);
+    finish(0);
+    int st = 0;
+#pragma unroll 1
+    for (int t = 0; t < steps; ++t) {
+        const int nst = st + 1 == ASP_NS ? 0 : st + 1;
+        // The keys of tile t + 1 and the values of tile t have landed (the next ones are on their way); everybody has left
+        // iteration t - 1, which read the keys of tile t and the values of tile t - 1.
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(LPT) : "memory");
+        read_k(nst, 0, 0);
+        read_k(nst, 0, 1);
+        issue(t + 3, t + 2, true);
+        const bool flush = t % ATT_FLUSH == 0;
+        if (flush || __any(mx > m + 8.f)) {             // (a row sum that is not a number stays one)
+            const float mn = t == 0 ? mx : mx > m + 8.f ? mx : m, corr = t == 0 ? 0.f : __builtin_amdgcn_exp2f(m - mn);
+            m = mn;
+            l *= corr;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    ot[dt][e] = (ot[dt][e] + (o[dt][e] + ol[dt][e])) * corr;
+                    o[dt][e] = ol[dt][e] = 0.f;
+                }
+        }
+        // The next tile's scores, and behind each MFMA up to five of this tile's vector instructions (about four are free, and none
+        // where there is no MFMA: as two phases a tile took 3,360 clocks of which 1,536 are MFMAs) and a fragment read for six MFMAs
+        // later: the probabilities in pairs, in four (D = 32: two) steps each; those that the first output products do not need
+        // behind these; then the sums of the next scores.  (Past the end: scores never used.)
+        constexpr int PS = D == 64 ? 6 : 8, SL = 6 * KS, PST = D == 64 ? 4 : 1;      // pairs beside the scores; slots a pair
+        at_u32x4 pp[2][3];
+        float sum = 0.f, x0 = 0.f, x1 = 0.f;
+        auto pair = [&](int g, int step) {              // step 0 .. 3 of pair g
+            if (step == 0) {
+                x0 = __builtin_amdgcn_exp2f(p[2 * g] - m);
+                x1 = __builtin_amdgcn_exp2f(p[2 * g + 1] - m);
+                return;
+            }
+            if (step == 1) sum += x0 + x1;
+            const uint32_t u0 = __float_as_uint(x0), u1 = __float_as_uint(x1);
+            pp[g >> 2][step - 1][g & 3] = __builtin_amdgcn_perm(u1, u0, 0x07060302);
+            if (step < 3) {
+                x0 = fmaxf(x0 - __uint_as_float(u0 & 0xFFFF0000u), PIECE_TINY);       // (cut3 of a value that is not negative)
+                x1 = fmaxf(x1 - __uint_as_float(u1 & 0xFFFF0000u), PIECE_TINY);
+            }
+        };
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < SL; ++i) {
+            const int ks = i / 6, n = i % 6;
+            score(ks, n);
+            if (n == 0) read_k(nst, ks, 2);
+            if (n == 2) { if (ks + 1 < KS) read_k(nst, ks + 1, 0); else read_v(st, 0, 0); }
+            if (n == 4) { if (ks + 1 < KS) read_k(nst, ks + 1, 1); else read_v(st, 0, 1); }
+            if (D == 64) pair(i / PST, i % PST);
+            else {                                      // 32 steps over 12 slots
+#pragma unroll
+                for (int z = i * 32 / SL; z < (i + 1) * 32 / SL; ++z) pair(z / 4, z % 4);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int i = 0; i < 12 * DT; ++i) {
+            const int f = i / 6, n = i % 6;
+            at_f32x16& acc = n == 1 ? o[f % DT] : ol[f % DT];
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[at_piece(f, pa[n])], __builtin_bit_cast(at_bf16x8, pp[f / DT][pb[n]]), acc, 0, 0, 0);
+            if (n == 0) read_v(st, f, 2);
+            if (n == 2 && f + 1 < 2 * DT) read_v(st, f + 1, 0);
+            if (n == 4 && f + 1 < 2 * DT) read_v(st, f + 1, 1);
+            if (D == 64) {
+                if (i < 8) pair(PS + i / 4, i % 4);
+                else add_scores(i - 8);
+            } else if (i >= 4) {
+                add_scores(2 * (i - 4));
+                add_scores(2 * (i - 4) + 1);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        l += sum;
+        finish(t + 1);
+        st = nst;
+    }
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) ot[dt][e] += o[dt][e] + ol[dt][e];
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // no load may still target LDS when the block retires
+    l += __shfl_xor(l, 32, 64);
+    const float inv = 1.f / l;
+    if (my_row < rows_s) {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int c = h * D + 32 * dt + 8 * g + 4 * fh;
+                const at_f32x4 v = {ot[dt][4 * g] * inv, ot[dt][4 * g + 1] * inv, ot[dt][4 * g + 2] * inv, ot[dt][4 * g + 3] * inv};
+                if (a.out_pieces) store_pieces4((uint16_t*)a.O + tok * 3 * C + piece_index(c), v.x, v.y, v.z, v.w);
+                else *reinterpret_cast<at_f32x4*>((float*)a.O + tok * C + c) = v;
+            }
+    }
+}
+
+template <int D>
+static int attn_split(const AttnArgs& a, hipStream_t st) {
+    using Cfg = AttnSplitCfg<D>;
+    const int64_t tiles = (int64_t)a.geom.P * a.geom.S / 32 + a.n;
+    attn_cut_kernel<D><<<dim3((unsigned)tiles, (unsigned)a.heads), 4 * D, 0, st>>>((const float*)a.K, (const float*)a.V, a.cu_seqlens,
+        a.seq_len, a.n, a.C, (at_u32x4*)a.cut);
+    PS_TRY(check_launch("attn_cut_kernel"));
+    PS_SET_LDS_ONCE((attn_split_kernel<D>), Cfg::LDS);
+    AttnArgs b = a;
+    const int64_t items = (int64_t)a.max_tiles * a.qt * a.heads;
+    b.group = (int)std::min<int64_t>(8, cdiv(items, 8));
+    attn_split_kernel<D><<<(unsigned)(8 * b.group * cdiv(items, 8 * b.group)), 256, Cfg::LDS, st>>>(b, (const at_u32x4*)a.cut);
+    return check_launch("attn_split_kernel");
+}
+
+// From 128 blocks of 128 queries on, where a request has 1,024 keys: below, the fp32 kernel's blocks of 32 queries with the keys
+// shared out to four wavefronts spread better.  us of an LSATTN layer, fp32 kernel / this: 4,096 + 3,072 tokens, 5 heads of 64
+// (280 blocks) 460 / 309; 2 x 2,304, 5 of 32 (180) 117 / 102; 4,608, 10 of 32 (360) 391 / 282; 2,304, 5 of 64 (90) 138 / 133;
+// 4 x 576, 5 of 64 (100) 68 / 70; 4,096, 2 of 64 (64) 124 / 181; 16 x 256, 5 of 64 (160) 72 / 73.  Error of a layer of 4,096 tokens
+// against 64 bits 5.2e-8 / 4.2e-8, of 1,024 4.3e-8 / 4.1e-8 (of 256 4.5e-8 / 4.6e-8).
+size_t attention_cut_bytes(const pserve_plan_t* plan, int32_t C, int32_t heads, int dtype, int mode) {
+    if (dtype != PSERVE_F32 || mode != 0 || C % heads != 0 || (C / heads != 32 && C / heads != 64)) return 0;
+    if ((int64_t)attention_max_tiles(plan, 1) * heads < 128 || plan->max_tokens_per_image < 1024) return 0;
+    return (size_t)(plan->T / 32 + plan->n) * C * 32 * 12;
+}
+
 int attention_mfma_bf16(const AttnArgs& a, hipStream_t st, bool* handled);     // attn_mfma.hip
 
 int attention(const AttnArgs& a, int dtype, int mode, hipStream_t st) {
@@ -369,6 +689,8 @@ int attention(const AttnArgs& a, int dtype, int mode, hipStream_t st) {
         PS_TRY(attention_mfma_bf16(a, st, &handled));
         if (handled) return PSERVE_OK;
     }
+    if (mode == 0 && dtype == PSERVE_F32 && a.cut && !a.cross_len && a.tile_off && a.act_off)
+        return a.d == 64 ? attn_split<64>(a, st) : attn_split<32>(a, st);
     // four channels a load (the queries, keys and values are the library's own buffers: rows start 16-byte aligned when C
     // and d are multiples of four)
     if (mode == 0 && a.d % 4 == 0 && a.C % 4 == 0 && (a.v_transposed ? a.d == 64 && dtype == PSERVE_BF16 : a.ldv % 4 == 0) &&

@@ -46,7 +46,6 @@ typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 constexpr int ATT_NS = 3;        // K / V^T ring depth in 64-key tiles
-constexpr float ATT_TINY = 1.17549435e-38f;
 constexpr float ATT_SUM_MAX = 4096.f;   // a lane's 16-key partial row sum above this moves the softmax reference
 
 // MFMA tile row r of a score tile holds key kperm(r) (bits 2 and 3 swapped): with this order the eight scores a lane
@@ -221,8 +220,8 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
                     _Pragma("unroll") for (int q_ = 0; q_ < NP; ++q_) {                                          \
                         const uint32_t u0_ = __float_as_uint(pf_[0]), u1_ = __float_as_uint(pf_[1]);             \
                         pk_[q_][i] = __builtin_amdgcn_perm(u1_, u0_, 0x07060302);                                \
-                        pf_[0] = fmaxf(pf_[0] - __uint_as_float(u0_ & 0xFFFF0000u), ATT_TINY);                   \
-                        pf_[1] = fmaxf(pf_[1] - __uint_as_float(u1_ & 0xFFFF0000u), ATT_TINY);                   \
+                        pf_[0] = fmaxf(pf_[0] - __uint_as_float(u0_ & 0xFFFF0000u), PIECE_TINY);                   \
+                        pf_[1] = fmaxf(pf_[1] - __uint_as_float(u1_ & 0xFFFF0000u), PIECE_TINY);                   \
                     }                                                                                            \
                 } else {                                                                                         \
                     const bf16x2 pb_ = __builtin_convertvector(pf_, bf16x2);                                     \

@@ -312,6 +312,7 @@ struct pserve_cache_s {
     void* k[PSERVE_MAX_STAGES] = {};          // SATTN: keys (slot K)
     void* v[PSERVE_MAX_STAGES] = {};          // SATTN: values (slot V; [C][v_ld] when v_transposed)
     void* q = nullptr;                        // [T][C] scaled queries
+    void* cut = nullptr;                      // fp32 self-attention: keys and values in bf16 pieces (of the stage that runs)
     void* o = nullptr;                        // [T][C] attention output
     void* u = nullptr;                        // [T][C] normalised tokens
     void* kc = nullptr;                       // [n*cross_ld][C] text keys
@@ -687,6 +688,9 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
         // twice the blocks.  Below that the smaller tile, which gives twice as many blocks to spread.
         c->att_qt = attention_max_tiles(plan, 2) * (int64_t)d.heads < 256 ? 1 : 2;
         c->max_tiles = attention_max_tiles(plan, c->att_qt);
+        if (sattn)
+            if (const size_t bytes = attention_cut_bytes(plan, d.C, d.heads, d.dtype, g_kernel_mode == 1 ? 1 : 0))
+                PS_TRY(c->pool.alloc(&c->cut, bytes));
     }
     if (ffn) PS_TRY(c->pool.alloc(&c->hidden, (size_t)plan->T * d.ffn_mult * d.C * ps));
     if (with_slots) PS_TRY(c->pool.alloc(&c->yslot, TC));
@@ -1056,6 +1060,7 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         aa.cross_len = cross ? d.ctx_len : 0; aa.cross_ld = cross ? cache->cross_ld : 0;
         aa.act_off = cache->act_off; aa.tile_off = cache->tile_off; aa.n = plan->n; aa.max_tiles = cache->max_tiles;
         aa.qt = cache->att_qt; aa.max_rows = plan->max_tokens_per_image; aa.out_pieces = out_pieces;
+        aa.cut = cache->cut;
         ProfScope ps(cross ? "attn_cross" : "attn_self", st);
         return attention(aa, dt, mode, st);
     };

@@ -376,7 +376,7 @@ static bool gemm_f32mma(const GemmArgs& a, hipStream_t st) {
 
 // ---- fp32 on the bf16 matrix cores ----------------------------------------------------------------
 // The bf16 MFMA does 16 times the work of the fp32 one, so an fp32 value is cut into three bf16 pieces of eight bits each
-// (truncation: x = x0 + x1 + x2 exactly) and a product is x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0), every term exact in
+// (cut3: x = x0 + x1 + x2) and a product is x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0), every term exact in
 // the fp32 accumulators; what is left out is below 2^-24 of a product, and a sum has an eighth as many roundings.  The
 // large terms and the others have accumulators of their own.  Both operands come in pieces, rows of [K / 32][3][32]: the weights
 // are cut when they are packed (split_packed), the activations by the kernel that produces them (cutting them here, once a tile
@@ -386,7 +386,6 @@ static bool gemm_f32mma(const GemmArgs& a, hipStream_t st) {
 // 3 (1 + TN) fragments for 6 TN MFMAs, so LDS and matrix pipe are about level at TN = 5.  Both operands are staged by direct
 // loads into a ring of three stages (two blocks a CU at TN = 2); behind the barrier of a step its stage is refilled and the NEXT step's fragments are read
 // between the MFMAs of this one.  LDS rows are 192 bytes, chunk c of a piece at c ^ ((row >> 2) & 3): conflict free.
-//   An infinite operand would meet a zero piece (NaN), so a result that is not finite is summed again in plain fp32.
 //   Two convolutions of 7,168 tokens x 320 channels: 162 -> 78 us each (170 TFLOP/s of fp32); bound by the bf16 matrix pipe at the clock it
 // gets (1.0 PFLOP/s) and, for few tiles, by a tile's start and end (7 us).  Error of a block of two convolutions and an attention
 // against 64 bits 2.6e-7 -> 2.0e-7.
@@ -416,7 +415,6 @@ gemm_split_kernel(GemmArgs a, const uint16_t* __restrict__ Bs) {
     static_assert(!GEGLU || TN % 2 == 0, "GEGLU: as many values as gates");
     extern __shared__ __attribute__((aligned(16))) uint8_t gs_smem[];
     gs_u32x4* ring = reinterpret_cast<gs_u32x4*>(gs_smem);
-    __shared__ int64_t s_aoff[BM];
     __shared__ int64_t s_tok[BM];                                      // -1: the row does not exist
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -436,7 +434,7 @@ gemm_split_kernel(GemmArgs a, const uint16_t* __restrict__ Bs) {
         const int chunk = c ^ ((row >> 2) & 3);             // the two low bits: the place inside the piece
         if (l < 3) {
             const RowInfo r = row_info(a, m0 + row);
-            if (c == 0) { s_aoff[row] = r.a_off; s_tok[row] = r.valid ? r.out_row : -1; }
+            if (c == 0) s_tok[row] = r.valid ? r.out_row : -1;
             a_lane[l < 3 ? l : 0] = (int)((r.a_off * 3 + chunk * 8) * 2);
         } else {
             const int h = GEGLU && row >= BN / 2, col = packed(min(n0 + row - h * (BN / 2), ncols - 1), h);
@@ -535,42 +533,9 @@ gemm_split_kernel(GemmArgs a, const uint16_t* __restrict__ Bs) {
         for (int e = 0; e < 16; ++e) at(wk, j, e) = acc[j][0][e] + acc[j][1][e];
     __syncthreads();
     const int row0 = wm * 32 + 16 * wk + 4 * fh;        // row of element e: row0 + 8 (e / 4) + e % 4
-    // sums of column tile j; one that is not finite is formed again in plain fp32 (the places (wk, j, 8 wk ..) are this
-    // wavefront's alone)
-    auto sums = [&](int j, float (&v)[8]) {
-        bool finite = true;
+    auto sums = [&](int j, float (&v)[8]) {             // of column tile j
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            v[e] = at(0, j, 8 * wk + e) + at(1, j, 8 * wk + e);
-            finite = finite && fabsf(v[e]) < INFINITY;
-        }
-        if (__any(!finite)) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) at(wk, j, 8 * wk + e) = v[e];
-            const int h = GEGLU && j >= TN / 2, col = packed(min(n0 + 32 * (j - h * (TN / 2)) + fr, ncols - 1), h);
-#pragma unroll 1
-            for (int e = 0; e < 8; ++e) {
-                const int m = row0 + 8 * (e >> 2) + (e & 3);
-                float& r = at(wk, j, 8 * wk + e);
-                if (fabsf(r) < INFINITY || s_tok[m] < 0) continue;
-                float s = 0.f;
-#pragma unroll 1
-                for (int tp = 0; tp < a.taps; ++tp) {
-                    const uint16_t* x = (const uint16_t*)a.A + (s_aoff[m] + (a.conv ? ((int64_t)(tp / tw) * a.geom.ppw + (tp % tw)) * a.lda : 0)) * 3;
-                    const float* w = (const float*)a.B + ((int64_t)tp * a.N + col) * K;
-#pragma unroll 1
-                    for (int k = 0; k < K; ++k) {
-                        const uint16_t* xp = x + piece_index(k);
-                        const float x0 = bf16_bits_to_float(xp[0]);
-                        const float xv = fabsf(x0) < INFINITY ? x0 + (bf16_bits_to_float(xp[32]) + bf16_bits_to_float(xp[64])) : x0;
-                        s = fmaf(xv, w[k], s);
-                    }
-                }
-                r = s;
-            }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = at(wk, j, 8 * wk + e);
-        }
+        for (int e = 0; e < 8; ++e) v[e] = at(0, j, 8 * wk + e) + at(1, j, 8 * wk + e);
     };
     int64_t tok[8];
 #pragma unroll
@@ -630,12 +595,10 @@ gemm_split_kernel(GemmArgs a, const uint16_t* __restrict__ Bs) {
             for (int e = 0; e < 8; ++e) {
                 if (tok[e] < 0) continue;
                 uint16_t* op = (uint16_t*)seg.ptr + tok[e] * 3 * seg.ld + piece_index(sc);
+                uint32_t u[3];
+                cut3(v[e], u);
 #pragma unroll
-                for (int pl = 0; pl < 3; ++pl) {
-                    const uint32_t u = __float_as_uint(v[e]);
-                    op[32 * pl] = (uint16_t)(u >> 16);
-                    v[e] -= __uint_as_float(u & 0xFFFF0000u);
-                }
+                for (int pl = 0; pl < 3; ++pl) op[32 * pl] = (uint16_t)(u[pl] >> 16);
             }
         } else {
             const int64_t rs = seg.transposed ? 1 : seg.ld;
@@ -656,13 +619,10 @@ __global__ void split_packed_kernel(const float* __restrict__ w, uint16_t* __res
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= rows * K) return;
     const int64_t r = i / K;
-    float v = w[i];
+    uint32_t u[3];
+    cut3(w[i], u);
 #pragma unroll
-    for (int pl = 0; pl < 3; ++pl) {
-        const uint32_t u = __float_as_uint(v);
-        dst[r * 3 * K + piece_index((int)(i - r * K)) + 32 * pl] = (uint16_t)(u >> 16);
-        v -= __uint_as_float(u & 0xFFFF0000u);
-    }
+    for (int pl = 0; pl < 3; ++pl) dst[r * 3 * K + piece_index((int)(i - r * K)) + 32 * pl] = (uint16_t)(u[pl] >> 16);
 }
 int split_packed(void* packed, int64_t rows, int32_t K, int dtype, hipStream_t st) {
     if (dtype == PSERVE_BF16 || K % 32 != 0) return PSERVE_OK;

@@ -26,6 +26,31 @@ template <> __device__ __forceinline__ void st_f<uint16_t>(uint16_t* p, float v)
 // fp32 rows as bf16 pieces: rows of [C / 32][3][32], three pieces of every value that sum to it exactly.  Index of the first
 // piece of value c; the others follow 32 and 64 further.
 __host__ __device__ __forceinline__ int piece_index(int c) { return (c >> 5) * 96 + (c & 31); }
+// The pieces of x, in the upper halves of u: eight bits of its digits each, cut off, so they have its sign.  A piece that would be
+// zero (or, of an infinite x, not a number) is the smallest normal number instead unless x is zero: zero times an infinite
+// factor would be NaN where the product is infinite.
+constexpr float PIECE_TINY = 1.17549435e-38f;
+__device__ __forceinline__ void cut3(float x, uint32_t (&u)[3]) {
+    const float tiny = fminf(fabsf(x), PIECE_TINY);
+    float r = x;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        u[p] = __float_as_uint(r);
+        r = copysignf(fmaxf(fabsf(r - __uint_as_float(u[p] & 0xFFFF0000u)), tiny), x);
+    }
+}
+__device__ __forceinline__ uint32_t pack_hi16(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302); }
+// pieces of four neighbouring values (a multiple of four in front of them), the first at dst
+__device__ __forceinline__ void store_pieces4(uint16_t* dst, float a, float b, float c, float d) {
+    uint32_t u[4][3];
+    cut3(a, u[0]);
+    cut3(b, u[1]);
+    cut3(c, u[2]);
+    cut3(d, u[3]);
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+        *reinterpret_cast<uint2*>(dst + 32 * p) = make_uint2(pack_hi16(u[0][p], u[1][p]), pack_hi16(u[2][p], u[3][p]));
+}
 
 // Patch geometry shared by the kernels that walk tokens.
 struct PatchGeom {
@@ -209,6 +234,7 @@ struct AttnArgs {
     int32_t max_rows;          // host upper bound of the query rows of one request (its tokens)
     int32_t group;             // consecutive work items dealt to an XCD at a time (filled in by the launch)
     int32_t out_pieces;        // fp32: O is written as bf16 pieces
+    void* cut;                 // fp32 self-attention: scratch of attention_cut_bytes, nullptr: the fp32 kernel
 };
 // Item k of the work list of a call, longest first: request slots from the last (the plan sorts requests by size,
 // largest last) to the first, head-major inside a slot, so that consecutive items are consecutive query tiles of one head.
@@ -233,6 +259,8 @@ __device__ __forceinline__ bool attn_item_at(const AttnArgs& a, int64_t k, int& 
 int attention_tiles(const int32_t* request_offset, const uint8_t* mask, int32_t n, int32_t S, int32_t qt, int32_t* act_off,
                     int32_t* tile_off, hipStream_t st);
 int attention_max_tiles(const pserve_plan_t* plan, int32_t qt);
+// scratch (keys and values in bf16 pieces) of an fp32 self-attention over this plan, 0: it takes the fp32 kernel
+size_t attention_cut_bytes(const pserve_plan_t* plan, int32_t C, int32_t heads, int dtype, int mode);
 int attention(const AttnArgs& a, int dtype, int mode, hipStream_t st);
 
 // ---- reuse (block.hip) -------------------------------------------------------------------------------

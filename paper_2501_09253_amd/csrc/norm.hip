@@ -64,15 +64,7 @@ __device__ __forceinline__ void store_out(T* out, int64_t row, int c, const floa
     if constexpr (!PIECES) {
         store_vec<T>(out + row + c, v);
     } else {
-        float r[4] = {v[0], v[1], v[2], v[3]};
-#pragma unroll
-        for (int pl = 0; pl < 3; ++pl) {
-            uint32_t u[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { u[e] = __float_as_uint(r[e]); r[e] -= __uint_as_float(u[e] & 0xFFFF0000u); }
-            *reinterpret_cast<uint2*>((uint16_t*)out + row + piece_index(c) + 32 * pl) =
-                make_uint2(__builtin_amdgcn_perm(u[1], u[0], 0x07060302), __builtin_amdgcn_perm(u[3], u[2], 0x07060302));
-        }
+        store_pieces4((uint16_t*)out + row + piece_index(c), v[0], v[1], v[2], v[3]);
     }
 }
 

@@ -1,5 +1,5 @@
-"""GPU: fp32 layers on the bf16 matrix cores (operands in three bf16 pieces), at ragged rows and columns, odd numbers of steps, with
-masks, per-request biases and gates, against the oracle; each case checks that its layers take that kernel.
+"""GPU: fp32 layers and self-attention on the bf16 matrix cores (operands in three bf16 pieces), at ragged rows, columns and keys,
+odd numbers of steps, with masks, per-request biases and gates, against the oracle; each case checks that its layers take that kernel.
 
 Bar: sums of up to 2,880 terms with a rounding of 2^-24 every 16 of them are good to sqrt(180) * 6e-8 = 8e-7 of their deviation; the
 largest of a million values is five deviations out and a block chains up to four layers: 2e-5 of the largest value."""
@@ -78,3 +78,54 @@ def test_values_that_are_not_finite(where):
         assert np.array_equal(np.where(np.isinf(a), np.sign(a), 0), np.where(np.isinf(b), np.sign(b), 0))
         ok = np.isfinite(b)
         assert not ok.any() or np.abs(a[ok] - b[ok]).max() < 2e-5 * np.abs(b[ok]).max()      # (behind w1 nothing is finite)
+
+
+# requests of one to sixty key tiles, the last one ragged; 130 and more blocks of 128 queries
+ATTN = {"d32": dict(res=[(40, 40), (8, 15), (8, 5)], patch=(8, 5), C=320, heads=10),
+        "d64": dict(res=[(36, 36), (3, 6), (9, 33)], patch=(3, 3), C=640, heads=10),
+        "d32_reuse": dict(res=[(40, 44), (8, 4)], patch=(8, 4), C=320, heads=10, reuse_p=0.5)}
+
+
+def _attn(name, seed):
+    c = dict(ATTN[name])
+    cfg = wl.custom_config(c.pop("res"), c.pop("patch"), G=8, stages=("LSATTN",), dtype="f32", seed=seed, **c)
+    assert sum(-(-h * w // 128) for h, w in cfg.resolutions) * cfg.heads >= 128 and max(h * w for h, w in cfg.resolutions) >= 1024
+    return cfg, wl.make_workload(cfg)
+
+
+def _attn_run(cfg, w):
+    run = GpuRun(w)
+    if w.cache is not None:
+        run.load_cache()
+    got = run.forward_images(reuse=w.reuse)
+    with np.errstate(invalid="ignore"):
+        ref, _ = ob.forward_batch(w.images, cfg.stages, w.params, G=cfg.G, heads=cfg.heads, eps=cfg.eps, reuse=w.reuse, cache=w.cache)
+    return got, ref
+
+
+@pytest.mark.parametrize("name", list(ATTN))
+def test_attention_against_oracle(name):
+    got, ref = _attn_run(*_attn(name, 71))
+    for a, b in zip(got, ref):
+        assert rel_err([a], [b]) < 2e-5
+
+
+def test_attention_reference_moves():
+    """Logits over a range of a few hundred: the softmax reference moves again and again.  A logit of 300 is known to 300 * 2^-23 *
+    sqrt(32 + 64) = 3.5e-4, and so is its exponential."""
+    cfg, w = _attn("d64", 73)
+    w.params[0]["wq"] *= 40.0
+    got, ref = _attn_run(cfg, w)
+    assert rel_err(got, ref) < 1e-3
+
+
+def test_attention_infinite_last_value():
+    cfg, w = _attn("d32_reuse", 79)
+    for r, v in zip(w.reuse, w.cache["0.V"]):
+        r[-1, -1] = True
+        v[5, -1, -1] = np.inf
+    got, ref = _attn_run(cfg, w)
+    assert np.isinf(ref[0]).any()                       # (of the second request every patch is cached)
+    for a, b in zip(got, ref):
+        assert np.array_equal(np.isnan(a), np.isnan(b))
+        assert np.array_equal(np.where(np.isinf(a), np.sign(a), 0), np.where(np.isinf(b), np.sign(b), 0))
