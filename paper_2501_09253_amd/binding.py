@@ -221,7 +221,7 @@ class Plan:
         self.n, self.R, self.P, self.ph, self.pw, self.ring, self.T = (info.n, info.R, info.P, info.ph, info.pw,
                                                                       info.ring, info.T)
         self.text_len, self.text_patches = info.text_len, info.text_patches
-        self.resolutions = [tuple(int(v) for v in r) for r in res]
+        self.resolutions = [tuple(r) for r in res.tolist()]
 
     def text_scatter(self, text, x):
         """pserve_text_scatter: text [n, text_len, C] (caller order) into the text patches of x[T, C] (in place)."""

@@ -24,51 +24,95 @@ void set_error(const char* fmt, ...) {
 
 // ---- kernels ----------------------------------------------------------------------------
 
-// One thread per (patch, ring entry): global token id of the pixel one step outside the patch.  The patch's owner comes by
-// binary search in RequestOffset (a serving batch has few requests); the thread of ring entry 0 also writes the patch's
-// owner, grid position and 8 neighbours.  Text patches: local index >= gh * gw; grid position (-1, k), no neighbours.
-__global__ void plan_patches_kernel(const int32_t* __restrict__ sorted_hw, const int32_t* __restrict__ request_offset,
-                                    int32_t n, int32_t P, int32_t ph, int32_t pw, int32_t ring, int32_t* __restrict__ owner,
-                                    int32_t* __restrict__ rc, int32_t* __restrict__ neighbour, int32_t* __restrict__ halo_src) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)P * ring) return;
-    const int p = (int)(i / ring), k = (int)(i - (int64_t)p * ring);
-    int lo = 0, hi = n;                       // largest s with request_offset[s] <= p
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (request_offset[mid] <= p) lo = mid; else hi = mid;
+// Where the tables of one plan lie: offsets in int32 into an arena that the device and the host hold alike, each a multiple of
+// 64 (PSERVE_TAB_* index; the sorted sizes stand at 0, the per-request tables behind them, then the four per-patch ones).
+struct PlanLayout {
+    int64_t request_offset, owner, rc, neighbour, halo_src, total;
+};
+
+// Requests whose sizes and offsets a block keeps in LDS, and the largest arena written to host memory as well
+constexpr int PLAN_REQ = 256;
+constexpr size_t PLAN_STAGE_BYTES = 1 << 20;
+
+// One thread per entry of the arena, so that every store is one of 64 in a row: over the host link a scattered four-byte
+// store costs as much as a whole line.  The patch's owner comes by binary search in RequestOffset (a serving batch has few
+// requests).  HALO_SRC: global token id of the pixel one step outside the patch.  Text patches: local index >= gh * gw;
+// grid position (-1, k), no neighbours.
+// STAGED: the per-request tables are read from host memory (one trip per block, into LDS) and copied to the device arena,
+// and the per-patch entries go to both arenas.  Else the device arena already holds the per-request part.
+// Bound by latency: 24 requests with 40,000 entries take 14 us, an empty launch and the wait for it 12.
+template <bool STAGED>
+__global__ void __launch_bounds__(256)
+plan_patches_kernel(int32_t* __restrict__ dev, int32_t* __restrict__ host, PlanLayout at, int32_t n, int32_t P, int32_t ph,
+                    int32_t pw, int32_t ring) {
+    __shared__ int32_t l_hw[STAGED ? 2 * PLAN_REQ : 1], l_ro[STAGED ? PLAN_REQ + 1 : 1];
+    if (STAGED) {
+        for (int k = threadIdx.x; k < 2 * n; k += 256) l_hw[k] = host[k];
+        for (int k = threadIdx.x; k <= n; k += 256) l_ro[k] = host[at.request_offset + k];
+        __syncthreads();
     }
-    const int s = lo, first = request_offset[s];
-    const int H = sorted_hw[2 * s], W = sorted_hw[2 * s + 1], gh = H / ph, gw = W / pw;
-    const int local = p - first;
-    const bool image = local < gh * gw;
-    const int r = image ? local / gw : -1, c = image ? local - r * gw : local - gh * gw;
-    if (k == 0) {
-        owner[p] = s;
-        rc[2 * p] = r;
-        rc[2 * p + 1] = c;
-        int j = 0;
-        for (int dy = -1; dy <= 1; ++dy)
-            for (int dx = -1; dx <= 1; ++dx) {
-                if (dy == 0 && dx == 0) continue;
-                const int rr = r + dy, cc = c + dx;
-                neighbour[8 * p + j] = image && rr >= 0 && rr < gh && cc >= 0 && cc < gw ? first + rr * gw + cc : -1;
-                ++j;
+    const int32_t* sorted_hw = STAGED ? l_hw : dev;
+    const int32_t* request_offset = STAGED ? l_ro : dev + at.request_offset;
+    for (int64_t e = (STAGED ? 0 : at.owner) + (int64_t)blockIdx.x * 256 + threadIdx.x; e < at.total; e += (int64_t)gridDim.x * 256) {
+        if (STAGED && e < at.owner) {
+            dev[e] = host[e];
+            continue;
+        }
+        int p, k, kind;                           // entry k of patch p
+        if (e < at.rc) { kind = 0; p = (int)(e - at.owner); k = 0; }
+        else if (e < at.neighbour) { kind = 1; k = (int)(e - at.rc); p = k >> 1; k &= 1; }
+        else if (e < at.halo_src) { kind = 2; k = (int)(e - at.neighbour); p = k >> 3; k &= 7; }
+        else { kind = 3; k = (int)(e - at.halo_src); p = k / ring; k -= p * ring; }
+        if (p >= P) continue;                     // between two tables
+        int lo = 0, hi = n;                       // largest s with request_offset[s] <= p
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (request_offset[mid] <= p) lo = mid; else hi = mid;
+        }
+        const int s = lo, first = request_offset[s];
+        const int H = sorted_hw[2 * s], W = sorted_hw[2 * s + 1], gh = H / ph, gw = W / pw;
+        const int local = p - first;
+        const bool image = local < gh * gw;
+        const int r = image ? local / gw : -1, c = image ? local - r * gw : local - gh * gw;
+        int32_t v = -1;
+        if (kind == 0) v = s;
+        else if (kind == 1) v = k ? c : r;
+        else if (kind == 2) {
+            const int j = k < 4 ? k : k + 1;      // the eight neighbours row by row, the patch itself left out
+            const int rr = r + j / 3 - 1, cc = c + j % 3 - 1;
+            if (image && rr >= 0 && rr < gh && cc >= 0 && cc < gw) v = first + rr * gw + cc;
+        } else {
+            int y, x;                             // ring pixel relative to the patch origin
+            if (k < pw + 2) { y = -1; x = k - 1; }
+            else if (k < 2 * (pw + 2)) { y = ph; x = k - (pw + 2) - 1; }
+            else if (k < 2 * (pw + 2) + ph) { y = k - 2 * (pw + 2); x = -1; }
+            else { y = k - 2 * (pw + 2) - ph; x = pw; }
+            const int Y = r * ph + y, X = c * pw + x;                      // absolute pixel in the image
+            if (image && Y >= 0 && Y < H && X >= 0 && X < W) {
+                const int q = first + (Y / ph) * gw + (X / pw);
+                v = q * ph * pw + (Y % ph) * pw + (X % pw);
             }
+        }
+        dev[e] = v;
+        if (STAGED) host[e] = v;
     }
-    int y, x;                                 // ring pixel relative to the patch origin
-    if (k < pw + 2) { y = -1; x = k - 1; }
-    else if (k < 2 * (pw + 2)) { y = ph; x = k - (pw + 2) - 1; }
-    else if (k < 2 * (pw + 2) + ph) { y = k - 2 * (pw + 2); x = -1; }
-    else { y = k - 2 * (pw + 2) - ph; x = pw; }
-    const int Y = r * ph + y, X = c * pw + x;                          // absolute pixel in the image
-    int32_t tok = -1;
-    if (image && Y >= 0 && Y < H && X >= 0 && X < W) {
-        const int q = first + (Y / ph) * gw + (X / pw);
-        tok = q * ph * pw + (Y % ph) * pw + (X % pw);
-    }
-    halo_src[i] = tok;
 }
+
+// Pinned host memory of the calling thread that a plan's tables pass through: in use only inside one pserve_plan call,
+// which waits for its kernel before it returns, and given back when the thread ends.  A plan of its own pinned memory
+// instead would cost an allocation that takes longer than the whole call.
+struct PlanStage {
+    int32_t* p = nullptr;
+    ~PlanStage() { if (p) (void)hipHostFree(p); }
+    int32_t* get() {
+        if (!p && hipHostMalloc((void**)&p, PLAN_STAGE_BYTES, hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            p = nullptr;
+        }
+        return p;
+    }
+};
+static thread_local PlanStage g_plan_stage;
 
 // ---- split / reassemble -------------------------------------------------------------------
 constexpr int IMG_CHUNK = 32;
@@ -408,9 +452,11 @@ static int plan_text_impl(const int32_t* res, int32_t n, int32_t ph, int32_t pw,
     cnt[PSERVE_TAB_HALO_SRC] = P * ring;
     cnt[PSERVE_TAB_CU_SEQLENS] = n + 1;
     cnt[PSERVE_TAB_SEQ_LEN] = n;
-    // One allocation, one copy each way (a dozen of each took most of the 230 us of a batch of 24 requests; now 70 us, with the seven tables read back): the
-    // per-request tables, a few numbers per request, are filled in on the host and go up in one piece; the per-patch tables
-    // are built by one kernel and come back in one piece.  Every table starts on a 256-byte boundary.
+    // One allocation and one launch.  The per-request tables, a few numbers per request, are filled in on the host; one
+    // kernel builds the per-patch tables.  Up to PLAN_STAGE_BYTES and PLAN_REQ requests (nearly every batch that is served)
+    // the kernel itself moves both ways through pinned host memory: for 24 requests launch and wait take 14 us, with a copy
+    // from and one to ordinary host memory around them 32 us.  Larger plans, where the tables' size decides, and any that
+    // find no pinned memory are copied.  Every table starts on a 256-byte boundary.
     static const int order[PSERVE_TAB_COUNT] = {PSERVE_TAB_PERM, PSERVE_TAB_REQUEST_OFFSET, PSERVE_TAB_RES_OFFSET, PSERVE_TAB_RES_HW,
                                                 PSERVE_TAB_CU_SEQLENS, PSERVE_TAB_SEQ_LEN, PSERVE_TAB_PATCH_OWNER,
                                                 PSERVE_TAB_PATCH_RC, PSERVE_TAB_NEIGHBOUR, PSERVE_TAB_HALO_SRC};
@@ -451,15 +497,25 @@ static int plan_text_impl(const int32_t* res, int32_t n, int32_t ph, int32_t pw,
     h[PSERVE_TAB_CU_SEQLENS][n] = off * ph * pw;
     h[PSERVE_TAB_RES_OFFSET][run] = n;
 
+    const PlanLayout lay = {at[PSERVE_TAB_REQUEST_OFFSET], at[PSERVE_TAB_PATCH_OWNER], at[PSERVE_TAB_PATCH_RC],
+                            at[PSERVE_TAB_NEIGHBOUR], at[PSERVE_TAB_HALO_SRC], total};
     hipStream_t st = (hipStream_t)stream;
-    PS_CHECK_HIP(hipMemcpyAsync(dev, pl->h_arena.get(), sizeof(int32_t) * per_request, hipMemcpyHostToDevice, st));
-    plan_patches_kernel<<<(unsigned)cdiv(P * ring, 256), 256, 0, st>>>(pl->d_sorted_hw, pl->d_tab[PSERVE_TAB_REQUEST_OFFSET], n,
-        (int32_t)P, ph, pw, ring, pl->d_tab[PSERVE_TAB_PATCH_OWNER], pl->d_tab[PSERVE_TAB_PATCH_RC], pl->d_tab[PSERVE_TAB_NEIGHBOUR],
-        pl->d_tab[PSERVE_TAB_HALO_SRC]);
-    PS_TRY(check_launch("plan_patches_kernel"));
-    PS_CHECK_HIP(hipMemcpyAsync(pl->h_arena.get() + per_request, dev + per_request, sizeof(int32_t) * (total - per_request),
-                                hipMemcpyDeviceToHost, st));
-    PS_CHECK_HIP(hipStreamSynchronize(st));
+    int32_t* stage = n <= PLAN_REQ && total * sizeof(int32_t) <= PLAN_STAGE_BYTES ? g_plan_stage.get() : nullptr;
+    if (stage) {
+        memcpy(stage, hw, sizeof(int32_t) * per_request);
+        plan_patches_kernel<true><<<(unsigned)cdiv(total, 256), 256, 0, st>>>(dev, stage, lay, n, (int32_t)P, ph, pw, ring);
+        PS_TRY(check_launch("plan_patches_kernel"));
+        PS_CHECK_HIP(hipStreamSynchronize(st));
+        memcpy(hw + per_request, stage + per_request, sizeof(int32_t) * (total - per_request));
+    } else {
+        PS_CHECK_HIP(hipMemcpyAsync(dev, hw, sizeof(int32_t) * per_request, hipMemcpyHostToDevice, st));
+        const unsigned blocks = (unsigned)std::min<int64_t>(cdiv(total - per_request, 256), 1 << 22);
+        plan_patches_kernel<false><<<blocks, 256, 0, st>>>(dev, nullptr, lay, n, (int32_t)P, ph, pw, ring);
+        PS_TRY(check_launch("plan_patches_kernel"));
+        PS_CHECK_HIP(hipMemcpyAsync(hw + per_request, dev + per_request, sizeof(int32_t) * (total - per_request),
+                                    hipMemcpyDeviceToHost, st));
+        PS_CHECK_HIP(hipStreamSynchronize(st));
+    }
     guard.p = nullptr;
     *out = pl;
     return PSERVE_OK;
