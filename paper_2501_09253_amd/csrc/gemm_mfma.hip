@@ -277,6 +277,16 @@ template <int BM, int BN, int NS, bool OVERLAP> struct GemmCfg {
     static_assert(OVERLAP || NS * STAGE >= EPI, "epilogue staging does not fit the ring");
 };
 
+// Text rows stand L to a request and their outputs row_group_pad apart.  A transposed segment stores four tokens at once
+// where they lie aligned; with L = 77 and 80 only every fourth request's do, and the others' leave two bytes at a time.  The
+// tiles then walk the padded rows instead (those past L hold nothing): 39 -> 33 us for 22 x 77 x 2560, K = 2048.  Not where the
+// padding would be more than an eighth of the rows, nor where L is a multiple of four.
+__host__ __device__ inline bool gemm_pads_rows(const GemmArgs& a) {
+    return !a.tokens_are_rows && a.row_group > 0 && a.row_group % 4 != 0 && a.row_group_pad % 4 == 0 && a.M % a.row_group == 0 &&
+           a.row_group_pad - a.row_group <= a.row_group / 8 && (a.seg[0].transposed || a.seg[1].transposed || a.seg[2].transposed);
+}
+__host__ __device__ inline int32_t gemm_rows(const GemmArgs& a) { return gemm_pads_rows(a) ? a.M / a.row_group * a.row_group_pad : a.M; }
+
 // Block tile BM x BN, WGM x WGN wavefront grid (four wavefronts), ring of NS stages.
 // Step = 64 columns of K: 4 sub-steps of TM*TN MFMAs.  Every memory instruction rides behind an MFMA: during sub-steps
 // 0..2 the fragment reads of the next sub-step, during sub-step 3 the first fragments of the NEXT step and the refill
@@ -319,7 +329,8 @@ gemm_mfma_kernel(GemmArgs a) {
     // shared out by columns.  (An eighth of the M tiles per XCD instead: with 8 M tiles every XCD read all weights, 115 MB
     // for 13 MB of them at K = 5120.)
     const int act_count = (a.tokens_are_rows && a.act.active) ? *a.act.count : 0;              // computed patches
-    const int m_limit = (a.tokens_are_rows && a.act.active) ? act_count * a.geom.S : a.M;      // rows that exist
+    const int m_limit = (a.tokens_are_rows && a.act.active) ? act_count * a.geom.S : gemm_rows(a);      // rows that exist
+    const bool pads_rows = gemm_pads_rows(a);
     const int n_tiles = a.N / BN * (a.classes ? a.classes : 1), m_tiles = (m_limit + BM - 1) / BM;
     const int total = n_tiles * m_tiles, slot_step = gridDim.x >> 3;
     const int slots = (int)((int64_t)total * ((blockIdx.x & 7) + 1) / 8);      // end of this XCD's tiles
@@ -373,7 +384,12 @@ gemm_mfma_kernel(GemmArgs a) {
                 valid = act_p[i] >= 0;                                                                            \
                 tok = valid ? (int64_t)act_p[i] * a.geom.S + ((int)tok - pi * a.geom.S) : 0;                      \
             } else {                                                                                              \
-                valid = tok < a.M;                                                                                \
+                valid = tok < m_limit;                                                                            \
+                if (pads_rows && valid) {                                                                         \
+                    const int g_ = (int)tok / a.row_group_pad, j_ = (int)tok - g_ * a.row_group_pad;              \
+                    valid = j_ < a.row_group;                                                                     \
+                    tok = g_ * a.row_group + j_;                                                                  \
+                }                                                                                                 \
                 if (!valid) tok = 0;                                                                              \
             }                                                                                                     \
             int64_t off, orow = tok;                                                                              \
@@ -1098,7 +1114,7 @@ static int launch_feat(const GemmArgs& a, hipStream_t st) {
     PS_SET_LDS_ONCE((gemm_mfma_kernel<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, FEAT>), lds);
     // all tiles, or as many blocks as run at once (256 CUs x the blocks of this LDS size per CU): each block then
     // walks over several tiles
-    const int64_t all = 8 * cdiv(cdiv(a.M, BM) * (a.N / BN) * std::max(1, a.classes), 8);
+    const int64_t all = 8 * cdiv(cdiv(gemm_rows(a), BM) * (a.N / BN) * std::max(1, a.classes), 8);
     const int64_t resident = 256 * (int64_t)std::max<size_t>(1, std::min<size_t>(2, (160 * 1024) / lds));
     const unsigned grid = (unsigned)std::min(all, resident);
     gemm_mfma_kernel<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, FEAT><<<grid, 256, lds, st>>>(a);
@@ -1106,7 +1122,7 @@ static int launch_feat(const GemmArgs& a, hipStream_t st) {
 }
 
 // The end of a tile without the paths that this problem does not take, against all of them: 22.7 -> 21.7 us (13,312 x 640 x
-// 640), 112 -> 107 us (78,848 x 640 x 640) on 128 x 160 tiles, 17 % off 256 x 128 tiles at K = 640.
+// 640), 112 -> 107 us (78,848 x 640 x 640) on 128 x 160 tiles, 8 to 12 % off 256 x 128 tiles at K = 640.
 template <int BM, int BN, bool GEGLU, int WGM, int WGN, int NS, bool OVERLAP>
 static int launch(const GemmArgs& a, hipStream_t st) {
     bool seg = false;
