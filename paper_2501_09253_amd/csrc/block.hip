@@ -938,6 +938,10 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
     auto norm_conv = [&](const void* in, const StageWeights& w, int ci, const void* res, void* out, bool stats_next,
                          const float* rowbias = nullptr, hipEvent_t rowbias_ready = nullptr) -> int {
         GroupNormArgs ga = gn_args(in, w.gn_g[ci], w.gn_b[ci]);
+        GemmArgs g = base_gemm(cache->apad, C, C, C, w.w[ci], w.b[ci]);
+        g.conv = 1; g.taps = 9; g.res = res; g.ldr = C;
+        g.a_pieces = push && gemm_takes_pieces(g, dt, mode);
+        bool whole = false;
         if (have_partials) { ProfScope ps("gn_finalize", st); PS_TRY(gn_finalize(ga, gm, dt, plan->S / 64, st)); }
         else if (in_stats && in == x) {             // the block input: its moments came with the split
             GroupNormArgs gi = ga;
@@ -945,14 +949,16 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
             ProfScope ps("gn_finalize", st);
             PS_TRY(gn_finalize(gi, gm, dt, cache->in_nch, st, /*per_channel=*/true));
         }
-        else { ProfScope ps("gn_stats", st); PS_TRY(gn_stats(ga, gm, dt, st)); }
+        else {
+            ProfScope ps("gn_stats", st);
+            if (push && !reuse_mask && !g.a_pieces) PS_TRY(gn_whole(ga, gm, dt, /*conv=*/true, cache->apad, st, &whole));
+            if (!whole) PS_TRY(gn_stats(ga, gm, dt, st));
+        }
         have_partials = false;
-        GemmArgs g = base_gemm(cache->apad, C, C, C, w.w[ci], w.b[ci]);
-        g.conv = 1; g.taps = 9; g.res = res; g.ldr = C;
-        g.a_pieces = push && gemm_takes_pieces(g, dt, mode);
         // reused patches are not convolved: of them only the border tokens are normalised (the neighbours' rings)
         ga.rim_only = reuse_mask;
-        if (push) {             // normalise + stitch in one pass (push); otherwise the rims are gathered afterwards (pull)
+        if (whole) {}
+        else if (push) {        // normalise + stitch in one pass (push); otherwise the rims are gathered afterwards (pull)
             ProfScope ps("gn_apply_stitch", st);
             PS_TRY(gn_apply(ga, gm, dt, /*silu=*/true, /*padded=*/true, /*stitch=*/true, cache->apad, all, st, g.a_pieces));
         } else {
@@ -1127,13 +1133,18 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
                                   3 * C, owner, C, d.eps, gm, dt, cache->u, act, st, nullptr, nullptr, gq.a_pieces));
             } else {
                 GroupNormArgs ga = gn_args(rin, w.gn_g[0], w.gn_b[0]);
+                bool whole = false;
                 if (in_stats && rin == x) {         // the block input itself (not the slot that mixes in cached patches)
                     GroupNormArgs gi = ga;
                     gi.partial = cache->in_partial;
                     ProfScope ps("gn_finalize", st);
                     PS_TRY(gn_finalize(gi, gm, dt, cache->in_nch, st, /*per_channel=*/true));
-                } else { ProfScope ps("gn_stats", st); PS_TRY(gn_stats(ga, gm, dt, st)); }
-                { ProfScope ps("gn_apply", st); PS_TRY(gn_apply(ga, gm, dt, false, false, false, cache->u, act, st, gq.a_pieces)); }
+                } else {
+                    ProfScope ps("gn_stats", st);
+                    if (push && !act.active && !gq.a_pieces) PS_TRY(gn_whole(ga, gm, dt, /*conv=*/false, cache->u, st, &whole));
+                    if (!whole) PS_TRY(gn_stats(ga, gm, dt, st));
+                }
+                if (!whole) { ProfScope ps("gn_apply", st); PS_TRY(gn_apply(ga, gm, dt, false, false, false, cache->u, act, st, gq.a_pieces)); }
             }
             { ProfScope ps("linear_qkv", st); PS_TRY(gemm(gq, dt, mode, st)); }
             GemmArgs go = base_gemm(cache->o, C, C, C, w.w[1], w.b[1]);

@@ -14,6 +14,7 @@
 //   gn_finalize_kernel  per (request, group): the partial moments merged in fp64 (shuffles +
 //                       LDS) -> mean, rstd -> per (request, channel) scale and shift
 //   gn_direct_kernel    both of these in one launch, for small requests
+//   gn_whole_kernel     all three in one launch, for small batches
 //   gn_apply_kernel     y = x*scale + shift (+SiLU), written plain or into the interior of
 //                       the padded patch buffer the convolution reads
 // Reductions are deterministic (no float atomics).
@@ -59,9 +60,18 @@ __device__ __forceinline__ void store_vec<uint16_t>(uint16_t* p, const float (&v
 
 // Output rows of the apply passes: the type's own values, or (fp32, PIECES) three bf16 pieces of each value, which sum to it
 // exactly (piece_index).  row: first element of the row, c: the vector's first channel.
-template <typename T, bool PIECES>
-__device__ __forceinline__ void store_out(T* out, int64_t row, int c, const float (&v)[Vec<T>::N]) {
-    if constexpr (!PIECES) {
+template <typename T, int V> struct __attribute__((aligned(V * sizeof(T)))) GnChunk { T e[V]; };
+template <typename T, bool PIECES, int N>
+__device__ __forceinline__ void store_out(T* out, int64_t row, int c, const float (&v)[N]) {
+    if constexpr (N != Vec<T>::N) {                 // part of a vector
+        GnChunk<T, N> o;
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+            if constexpr (sizeof(T) == 4) o.e[e] = v[e];
+            else o.e[e] = float_to_bf16_bits(v[e]);
+        }
+        *reinterpret_cast<GnChunk<T, N>*>(out + row + c) = o;
+    } else if constexpr (!PIECES) {
         store_vec<T>(out + row + c, v);
     } else {
         store_pieces4((uint16_t*)out + row + piece_index(c), v[0], v[1], v[2], v[3]);
@@ -213,14 +223,10 @@ gn_finalize_kernel(const float* __restrict__ partial, const int32_t* __restrict_
 // LeVeque: all terms positive), so one far-off value costs no digits of the others; threads are merged in fp64.  (Sums of
 // x - K with one K for the block took the same time and lost 3 digits of the variance when K was 1,000 deviations out.)
 constexpr int GN_DIRECT_THREADS = 512;
+// Mean and 1 / deviation of a block's elements: `items` chunks of V channels, `per` of them a token, rows of C from `base`
 template <typename T, int V>
-__global__ void __launch_bounds__(GN_DIRECT_THREADS)
-gn_direct_kernel(const T* __restrict__ x, const int32_t* __restrict__ request_offset, const T* __restrict__ gamma,
-                 const T* __restrict__ beta, int32_t C, int32_t G, int32_t S, float eps, float* __restrict__ scale_shift) {
-    struct __attribute__((aligned(V * sizeof(T)))) Chunk { T e[V]; };
-    const int s = blockIdx.x, g = blockIdx.y, cg = C / G, per = cg / V;
-    const int p0 = request_offset[s], tokens = (request_offset[s + 1] - p0) * S, items = tokens * per;
-    const T* base = x + (int64_t)p0 * S * C + g * cg;
+__device__ __forceinline__ void gn_moments(const T* __restrict__ base, int items, int per, int C, float eps, double& mu, double& rstd) {
+    using Chunk = GnChunk<T, V>;
     float n = 0.f, mean = 0.f, m2 = 0.f;                        // moments of x - k0 over the n elements read so far
     float k0 = 0.f;                                             // fp32: the thread's first element (8 bits of bf16 need none)
     constexpr int U = 4;                                        // loads in flight
@@ -271,10 +277,21 @@ gn_direct_kernel(const T* __restrict__ x, const int32_t* __restrict__ request_of
     b = 0.0;
 #pragma unroll
     for (int w = 0; w < GN_DIRECT_THREADS / 64; ++w) { a += red[w][0]; b += red[w][1]; }    // fixed order: deterministic
-    const double total = (double)tokens * cg, mu = a / total;
+    const double total = (double)items * V;
+    mu = a / total;
     double var = b / total - mu * mu;
     var = var > 0.0 ? var : 0.0;
-    const double rstd = 1.0 / sqrt(var + (double)eps);
+    rstd = 1.0 / sqrt(var + (double)eps);
+}
+
+template <typename T, int V>
+__global__ void __launch_bounds__(GN_DIRECT_THREADS)
+gn_direct_kernel(const T* __restrict__ x, const int32_t* __restrict__ request_offset, const T* __restrict__ gamma,
+                 const T* __restrict__ beta, int32_t C, int32_t G, int32_t S, float eps, float* __restrict__ scale_shift) {
+    const int s = blockIdx.x, g = blockIdx.y, cg = C / G, per = cg / V;
+    const int p0 = request_offset[s], items = (request_offset[s + 1] - p0) * S * per;
+    double mu, rstd;
+    gn_moments<T, V>(x + (int64_t)p0 * S * C + g * cg, items, per, C, eps, mu, rstd);
     for (int c = g * cg + threadIdx.x; c < (g + 1) * cg; c += GN_DIRECT_THREADS) {
         const double sc = rstd * (double)ld_f<T>(gamma + c);
         float* dst = scale_shift + ((int64_t)s * C + c) * 2;
@@ -303,14 +320,14 @@ __device__ __forceinline__ float silu_f(float v) { return v * __builtin_amdgcn_r
 // token's normalised value is also written into the ring slot of every same-image neighbour patch that needs
 // it; where that neighbour is absent (image edge) the token zero-fills the matching ring slot of its OWN patch.
 // Every ring slot of every patch is written by exactly one thread, so there is no race and no extra pass.
-template <typename T, bool PIECES>
+template <typename T, bool PIECES, int N>
 __device__ __forceinline__ void stitch_store(T* __restrict__ out, const int32_t (&nb)[8], const PatchGeom& gm,
-                                             int p, int y, int x, int C, int coff, const float (&v)[Vec<T>::N]) {
+                                             int p, int y, int x, int C, int coff, const float (&v)[N]) {
     if (y != 0 && y != gm.ph - 1 && x != 0 && x != gm.pw - 1) return;
     const int CW = PIECES ? 3 * C : C;
-    float z[Vec<T>::N];
+    float z[N];
 #pragma unroll
-    for (int e = 0; e < Vec<T>::N; ++e) z[e] = 0.f;
+    for (int e = 0; e < N; ++e) z[e] = 0.f;
     int k = 0;
 #pragma unroll
     for (int dy = -1; dy <= 1; ++dy)
@@ -327,6 +344,63 @@ __device__ __forceinline__ void stitch_store(T* __restrict__ out, const int32_t 
             }
             ++k;
         }
+}
+
+// Statistics and application in one launch, for small batches, where a launch costs what its kernel does.  A block is one
+// (request, group) and one of gridDim.z shares of its elements: every share reads them all for the moments (the same value
+// in each: fixed order), then its own once more, out of the caches.  Bound by latency.  CONV: SiLU, padded, stitched.
+constexpr int GN_WHOLE_CG = 256;        // channels of a group at most
+template <typename T, int V, bool CONV>
+__global__ void __launch_bounds__(GN_DIRECT_THREADS)
+gn_whole_kernel(const T* __restrict__ x, const int32_t* __restrict__ request_offset, const int32_t* __restrict__ neighbour,
+                const T* __restrict__ gamma, const T* __restrict__ beta, PatchGeom gm, int32_t C, int32_t G, float eps, T* __restrict__ out) {
+    using Chunk = GnChunk<T, V>;
+    const int s = blockIdx.x, g = blockIdx.y, cg = C / G, per = cg / V;
+    const int p0 = request_offset[s], items = (request_offset[s + 1] - p0) * gm.S * per;
+    const T* base = x + (int64_t)p0 * gm.S * C + g * cg;
+    __shared__ float l_sc[GN_WHOLE_CG], l_sh[GN_WHOLE_CG];
+    double mu, rstd;
+    gn_moments<T, V>(base, items, per, C, eps, mu, rstd);
+    for (int c = threadIdx.x; c < cg; c += GN_DIRECT_THREADS) {
+        const double sc = rstd * (double)ld_f<T>(gamma + g * cg + c);
+        l_sc[c] = (float)sc;
+        l_sh[c] = (float)((double)ld_f<T>(beta + g * cg + c) - mu * sc);
+    }
+    __syncthreads();
+    const int share = (items + (int)gridDim.z - 1) / (int)gridDim.z, end = min(items, ((int)blockIdx.z + 1) * share);
+    constexpr int U = 4;                        // loads in flight
+    for (int i = blockIdx.z * share + threadIdx.x; i < end; i += U * GN_DIRECT_THREADS) {
+        Chunk raw[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = min(i + u * GN_DIRECT_THREADS, end - 1), t = j / per;
+            raw[u] = *reinterpret_cast<const Chunk*>(base + (int64_t)t * C + (j - t * per) * V);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = i + u * GN_DIRECT_THREADS, t = j / per, ch = (j - t * per) * V;
+            if (j >= end) break;
+            float v[V];
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                v[e] = fmaf(ld_f<T>(&raw[u].e[e]), l_sc[ch + e], l_sh[ch + e]);
+                if (CONV) v[e] = silu_f(v[e]);
+            }
+            const int pl = t / gm.S, q = t - pl * gm.S, p = p0 + pl;
+            if constexpr (CONV) {
+                const int py = q / gm.pw, px = q - py * gm.pw;
+                store_out<T, false>(out, ((int64_t)p * gm.pS + (py + 1) * gm.ppw + px + 1) * C, g * cg + ch, v);
+                if (py == 0 || py == gm.ph - 1 || px == 0 || px == gm.pw - 1) {
+                    int32_t nb[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) nb[k] = neighbour[8 * p + k];
+                    stitch_store<T, false>(out, nb, gm, p, py, px, C, g * cg + ch, v);
+                }
+            } else {
+                store_out<T, false>(out, ((int64_t)p * gm.S + q) * C, g * cg + ch, v);
+            }
+        }
+    }
 }
 
 // rim_only (padded output): patches with rim_only[p] != 0 are not convolved themselves (their result is reused); only
@@ -606,12 +680,7 @@ static int norm_layout(int32_t C, int dtype, int* CV, int* TL) {
     return PSERVE_OK;
 }
 
-int gn_stats(const GroupNormArgs& a, const PatchGeom& g, int dtype, hipStream_t st) {
-    int CV, TL;
-    PS_TRY(norm_layout(a.C, dtype, &CV, &TL));
-    PS_REQUIRE(a.C % a.G == 0, "GroupNorm: C %% G != 0");
-    const size_t lds = sizeof(float) * 2 * TL * a.C;
-    PS_REQUIRE(lds <= 64 * 1024, "GroupNorm: C=%d too wide for the reduction buffer", a.C);
+static bool gn_takes_direct(const GroupNormArgs& a, const PatchGeom& g, int dtype) {
     // One launch for small requests: a block reads its request's tokens in pieces of C / G channels, so its time grows with
     // its elements and, past an L2's 4 MB, with the lines shared between groups.  us, two launches -> one:
     // G = 32 at 1,024 tokens, 1 .. 24 requests of 64 .. 1280 channels: 6.2 .. 27 -> 3.4 .. 20, always faster; at 2,048, 6
@@ -620,9 +689,51 @@ int gn_stats(const GroupNormArgs& a, const PatchGeom& g, int dtype, hipStream_t 
     // 2,048 the block's elements decide in fp32 (163,840: 14.5 -> 14.3; 655,360: 37.3 -> 48.7; bf16 35.8 -> 33.8), and more than
     // 32 groups share too many lines (G = 64, 3 requests: fp32 C = 320 7.4 -> 11.3, bf16 C = 640 9.1 -> 11.4).
     const int64_t bytes = (int64_t)g.P * g.S * a.C * dtype_size(dtype), block = (int64_t)a.max_tokens * (a.C / a.G);
-    if (a.max_tokens <= 1024 ||
-        (a.max_tokens <= 2048 && bytes <= (8 << 20) && a.G <= 32 && (dtype == PSERVE_BF16 || block <= 200000)))
-        return dtype == PSERVE_BF16 ? gn_direct<uint16_t>(a, g, st) : gn_direct<float>(a, g, st);
+    return a.max_tokens <= 1024 ||
+           (a.max_tokens <= 2048 && bytes <= (8 << 20) && a.G <= 32 && (dtype == PSERVE_BF16 || block <= 200000));
+}
+
+template <typename T>
+static int gn_whole(const GroupNormArgs& a, const PatchGeom& g, bool conv, void* out, hipStream_t st) {
+    const int cg = a.C / a.G;
+    const int z = (int)std::max<int64_t>(1, std::min<int64_t>(256 / ((int64_t)a.n * a.G), 4));
+#define PS_GNW(V)                                                                                                        \
+    {                                                                                                                    \
+        if (conv) gn_whole_kernel<T, V, true><<<dim3(a.n, a.G, z), GN_DIRECT_THREADS, 0, st>>>((const T*)a.x, a.request_offset, a.neighbour, \
+            (const T*)a.gamma, (const T*)a.beta, g, a.C, a.G, a.eps, (T*)out);                                           \
+        else gn_whole_kernel<T, V, false><<<dim3(a.n, a.G, z), GN_DIRECT_THREADS, 0, st>>>((const T*)a.x, a.request_offset, a.neighbour, \
+            (const T*)a.gamma, (const T*)a.beta, g, a.C, a.G, a.eps, (T*)out);                                           \
+    }
+    if (sizeof(T) == 2 && cg % 8 == 0) PS_GNW(16 / sizeof(T))
+    else if (cg % 4 == 0) PS_GNW(4)
+    else if (cg % 2 == 0) PS_GNW(2)
+    else PS_GNW(1)
+#undef PS_GNW
+    return check_launch("gn_whole_kernel");
+}
+
+int gn_whole(const GroupNormArgs& a, const PatchGeom& g, int dtype, bool conv, void* out, hipStream_t st, bool* done) {
+    int CV, TL;
+    PS_TRY(norm_layout(a.C, dtype, &CV, &TL));
+    PS_REQUIRE(a.C % a.G == 0, "GroupNorm: C %% G != 0");
+    // us, two launches -> one, bf16: 64 tokens 7 .. 10.5 -> 5.0 .. 5.6 into the padded buffer, 6.2 .. 9 -> 3.6 .. 5 plain (C = 64 .. 1280,
+    // G = 32); 1,024 tokens 8.7 .. 12.8 -> 5.8 .. 9.9, 7.1 .. 11.4 -> 4.2 .. 8.1; 2,048 tokens 8.9 .. 14.9 -> 6.0 .. 12.4.  Past
+    // that the pieces of C / G channels in which a block writes cost more than the launch, at rows of ten channels first:
+    // 4,096 tokens C = 320 11.2 -> 13.2, C = 1280 17.9 -> 18.4, 12,288 15.5 -> 26.8; plain 10.1 -> 8.4, 13.6 -> 12.2, 13.0 -> 15.0.
+    // A block of many elements reads them alone: G = 1, C = 128: 256 tokens (32,768) 10.6 -> 9.8, 512 11.2 -> 12.1, 1,024 13.6 -> 17.9.
+    *done = gn_takes_direct(a, g, dtype) && a.C / a.G <= GN_WHOLE_CG && (int64_t)a.max_tokens * (a.C / a.G) <= 40960 &&
+            (int64_t)g.P * g.S <= (conv ? 2048 : 4096);
+    if (!*done) return PSERVE_OK;
+    return dtype == PSERVE_BF16 ? gn_whole<uint16_t>(a, g, conv, out, st) : gn_whole<float>(a, g, conv, out, st);
+}
+
+int gn_stats(const GroupNormArgs& a, const PatchGeom& g, int dtype, hipStream_t st) {
+    int CV, TL;
+    PS_TRY(norm_layout(a.C, dtype, &CV, &TL));
+    PS_REQUIRE(a.C % a.G == 0, "GroupNorm: C %% G != 0");
+    const size_t lds = sizeof(float) * 2 * TL * a.C;
+    PS_REQUIRE(lds <= 64 * 1024, "GroupNorm: C=%d too wide for the reduction buffer", a.C);
+    if (gn_takes_direct(a, g, dtype)) return dtype == PSERVE_BF16 ? gn_direct<uint16_t>(a, g, st) : gn_direct<float>(a, g, st);
     dim3 grid(g.P, a.nsplit);
     if (dtype == PSERVE_BF16)
         gn_partial_kernel<uint16_t><<<grid, TL * CV, lds, st>>>((const uint16_t*)a.x, a.C, a.G, g.S, a.nsplit, TL, a.partial);
