@@ -67,18 +67,28 @@ extern __shared__ __attribute__((aligned(16))) uint8_t att_smem[];
 
 // Work item of a block: (request slot, head, query tile of that request).  A block's run time goes with the number of
 // keys of its request, so the items run longest first (attn_item_at).  Groups of up to eight consecutive items are dealt to
-// the XCDs in turn (block b runs on XCD b mod 8 and an XCD starts its blocks in order): neighbouring blocks of an XCD
-// stream the K / V^T tiles of the same head through its L2, every XCD gets the same share of the long items, and the short
-// ones fill the last round.  Groups of 64 left XCDs idle below 512 items (40 items of 1,024 keys: all on one XCD, the layer 41.3 -> 34.2 us)
-// and gave some a whole group more than others above; with 4, 8, 16, 32 the layers of 520 and 1,160 items take 140.5 / 137.8 /
-// 139.0 / 141.7 and 245.8 / 243.5 / 245.9 / 245.5 us (64: 142.4, 250.4), and the 16 MB of keys and values of a head of 65,536 tokens
-// cost nothing more (9.57 against 9.55 ms).
+// the XCDs to and fro (block b runs on XCD b mod 8 and an XCD starts its blocks in order): neighbouring blocks of an XCD
+// stream the K / V^T tiles of the same head through its L2, every XCD gets the same share of the long items, and what is left
+// over, the shortest items, goes to the XCDs in turn and not to the one that also got the longest.
+// us of an LSATTN layer, groups of 64 dealt one way / of 8 one way / of 8, 16, 32 and 64 to and fro, in a process without and
+// with event waits between its streams before (they change which blocks meet on a CU; groups of 64 one way differ by 5 % with it):
+//   520 items (4 x 9 and 4 x 4 tiles, 10 heads)  161.0 154.2 / 155.7 154.6 / 154.1 153.7, 154.2 153.3, 149.0 149.2, 150.1 151.6
+//   320 items of one request                     199.7 199.6 / 173.6 175.3 / 173.1 174.7, 177.8 177.6, 189.5 177.3, 174.2 174.2
+//   640 items of four requests                   340.1 317.9 / 265.6 265.9 / 265.2 265.7, 264.6 264.8, 277.9 277.9, 326.4 308.1
+//   580 items (16, 36, 64 tiles, 5 heads)        654.7 577.3 / 554.5 549.2 / 543.9 546.8, 558.4 560.7, 543.1 523.2, 561.3 558.9
+//   1,160 items of 24 requests, 20 heads         279.7 273.7 / 271.9 266.9 / 270.5 265.6, 270.3 266.0, 270.9 268.0, 277.8 273.4
+// 450, 1,120, 1,176 and 5,120 items likewise: eight to and fro is the fastest or within 2 % of it, but for 32 at 520 items (3 %).
+// 40 items of 1,024 keys, groups of 64 / 8: all on one XCD, 41.3 / 34.2 us.
 constexpr int ATT_GROUP = 8;
+__host__ __device__ inline int attn_dealt(int block, int group) {
+    const int seq = block >> 3, grp = seq / group;
+    const int xcd = grp & 1 ? 7 - (block & 7) : block & 7;                  // place in the round: every other one backwards
+    return (grp * 8 + xcd) * group + (seq - grp * group);
+}
 // BQ: query rows of a block; a tile of the call's tables (128 * a.qt rows) is 128 * a.qt / BQ of them.  r0: its first row.
 template <int BQ>
 __device__ __forceinline__ bool attn_item(const AttnArgs& a, int& s, int& head, int& r0) {
-    const int seq = blockIdx.x >> 3, grp = seq / a.group;
-    const int it = (grp * 8 + (blockIdx.x & 7)) * a.group + (seq - grp * a.group);
+    const int it = attn_dealt(blockIdx.x, a.group);
     const int nsub = BQ == 256 ? 1 : 128 * a.qt / BQ;
     int tile;
     if (!attn_item_at(a, it / nsub, s, head, tile)) return false;
@@ -1064,5 +1074,8 @@ int attention_mfma_bf16(const AttnArgs& a, hipStream_t st, bool* handled) {
     PS_ATT(4, 1, 3);
 #undef PS_ATT
 }
+
+// For tests (host only, no part of the ABI): the work item of a block of a self-attention launch.
+extern "C" int pserve_test_attn_item(int32_t block, int32_t group) { return attn_dealt(block, group); }
 
 }  // namespace pserve
