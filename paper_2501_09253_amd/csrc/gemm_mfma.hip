@@ -36,7 +36,8 @@ enum : int {
     EPF_GATE = 4,       // per-request gate (rowscale)
     EPF_MIXED = 8,      // rows of several requests in one wavefront tile: per-element look-ups of rowbias / rowscale
     EPF_SCALE = 16,     // output segments with a scale other than 1 (the pre-multiplied Q)
-    EPF_ALL = 31
+    EPF_ALL = 31,
+    EPF_PADS = 32       // tiles walk the padded rows of the requests (gemm_pads_rows)
 };
 template <int BM, int BN, bool GEGLU, int WGM = 2, int WGN = 2, bool MAY_STAT = true, int FEAT = EPF_ALL>
 __device__ __forceinline__ void gemm_epilogue(const GemmCore& a, f32x16 (&acc)[BM / WGM / 32][BN / WGN / 32], uint8_t* smem,
@@ -279,10 +280,12 @@ template <int BM, int BN, int NS, bool OVERLAP> struct GemmCfg {
 
 // Text rows stand L to a request and their outputs row_group_pad apart.  A transposed segment stores four tokens at once
 // where they lie aligned; with L = 77 and 80 only every fourth request's do, and the others' leave two bytes at a time.  The
-// tiles then walk the padded rows instead (those past L hold nothing): 39 -> 33 us for 22 x 77 x 2560, K = 2048.  Not where the
-// padding would be more than an eighth of the rows, nor where L is a multiple of four.
+// tiles then walk the padded rows instead (those past L hold nothing): 39 -> 33 us for 22 x 77 x 2560, K = 2048; 16 requests
+// 30.7 -> 26.1, 10 29.1 -> 24.5, 4 19.8 -> 19.2, 2 18.4 -> 18.3.  Not where the padding would be more than an eighth of the rows,
+// nor where L is a multiple of four or there is one request.  A form of its own (EPF_PADS): as a run-time choice in all forms it
+// cost the small layers 2 to 10 % (1,024 x 1,280, K = 1,280 and 128 x 64 tiles 12.5 -> 13.0 .. 13.7 us).
 __host__ __device__ inline bool gemm_pads_rows(const GemmArgs& a) {
-    return !a.tokens_are_rows && a.row_group > 0 && a.row_group % 4 != 0 && a.row_group_pad % 4 == 0 && a.M % a.row_group == 0 &&
+    return !a.tokens_are_rows && a.epi == EPI_ROUTE && !a.rowbias && !a.rowscale && !a.act_gelu && a.row_group > 0 && a.M > a.row_group && a.row_group % 4 != 0 && a.row_group_pad % 4 == 0 && a.M % a.row_group == 0 &&
            a.row_group_pad - a.row_group <= a.row_group / 8 && (a.seg[0].transposed || a.seg[1].transposed || a.seg[2].transposed);
 }
 __host__ __device__ inline int32_t gemm_rows(const GemmArgs& a) { return gemm_pads_rows(a) ? a.M / a.row_group * a.row_group_pad : a.M; }
@@ -329,8 +332,8 @@ gemm_mfma_kernel(GemmArgs a) {
     // shared out by columns.  (An eighth of the M tiles per XCD instead: with 8 M tiles every XCD read all weights, 115 MB
     // for 13 MB of them at K = 5120.)
     const int act_count = (a.tokens_are_rows && a.act.active) ? *a.act.count : 0;              // computed patches
-    const int m_limit = (a.tokens_are_rows && a.act.active) ? act_count * a.geom.S : gemm_rows(a);      // rows that exist
-    const bool pads_rows = gemm_pads_rows(a);
+    constexpr bool PADS = (FEAT & EPF_PADS) != 0;
+    const int m_limit = (a.tokens_are_rows && a.act.active) ? act_count * a.geom.S : PADS ? gemm_rows(a) : a.M;      // rows that exist
     const int n_tiles = a.N / BN * (a.classes ? a.classes : 1), m_tiles = (m_limit + BM - 1) / BM;
     const int total = n_tiles * m_tiles, slot_step = gridDim.x >> 3;
     const int slots = (int)((int64_t)total * ((blockIdx.x & 7) + 1) / 8);      // end of this XCD's tiles
@@ -385,7 +388,7 @@ gemm_mfma_kernel(GemmArgs a) {
                 tok = valid ? (int64_t)act_p[i] * a.geom.S + ((int)tok - pi * a.geom.S) : 0;                      \
             } else {                                                                                              \
                 valid = tok < m_limit;                                                                            \
-                if (pads_rows && valid) {                                                                         \
+                if (PADS && valid) {                                                                              \
                     const int g_ = (int)tok / a.row_group_pad, j_ = (int)tok - g_ * a.row_group_pad;              \
                     valid = j_ < a.row_group;                                                                     \
                     tok = g_ * a.row_group + j_;                                                                  \
@@ -1114,7 +1117,7 @@ static int launch_feat(const GemmArgs& a, hipStream_t st) {
     PS_SET_LDS_ONCE((gemm_mfma_kernel<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, FEAT>), lds);
     // all tiles, or as many blocks as run at once (256 CUs x the blocks of this LDS size per CU): each block then
     // walks over several tiles
-    const int64_t all = 8 * cdiv(cdiv(gemm_rows(a), BM) * (a.N / BN) * std::max(1, a.classes), 8);
+    const int64_t all = 8 * cdiv(cdiv(FEAT & EPF_PADS ? gemm_rows(a) : a.M, BM) * (a.N / BN) * std::max(1, a.classes), 8);
     const int64_t resident = 256 * (int64_t)std::max<size_t>(1, std::min<size_t>(2, (160 * 1024) / lds));
     const unsigned grid = (unsigned)std::min(all, resident);
     gemm_mfma_kernel<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, FEAT><<<grid, 256, lds, st>>>(a);
@@ -1122,14 +1125,26 @@ static int launch_feat(const GemmArgs& a, hipStream_t st) {
 }
 
 // The end of a tile without the paths that this problem does not take, against all of them: 22.7 -> 21.7 us (13,312 x 640 x
-// 640), 112 -> 107 us (78,848 x 640 x 640) on 128 x 160 tiles, 8 to 12 % off 256 x 128 tiles at K = 640.
+// 640), 112 -> 107 us (78,848 x 640 x 640) on 128 x 160 tiles, 345 -> 312 (78,848 x 1,920 x 640, 256 x 128), 39.4 -> 34.8
+// (13,312 x 640 x 640, 256 x 128).  Not for 128 x 64 tiles, which get slower by it (1,024 x 1,280, plain / all paths: with
+// residual K = 1,280 14.0 / 12.3 and 14.9 / 12.3, K = 5,120 31.1 / 30.5; scaled queries 12.7 / 11.6; q, k and v 20.5 / 19.6).  GEGLU has the one segment, neither transposed nor scaled.
 template <int BM, int BN, bool GEGLU, int WGM, int WGN, int NS, bool OVERLAP>
 static int launch(const GemmArgs& a, hipStream_t st) {
     bool seg = false;
     for (const GemmSeg& s : a.seg) seg |= s.transposed || s.scale != 1.f;
-    if (!GEGLU && (a.rowbias || a.rowscale || a.act_gelu)) return launch_feat<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, GEGLU ? 0 : EPF_ALL>(a, st);
-    if (seg) return launch_feat<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, EPF_TRANS | EPF_SCALE>(a, st);
-    return launch_feat<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, 0>(a, st);
+    if constexpr (GEGLU) {
+        PS_REQUIRE(!seg, "gemm: GEGLU has no transposed or scaled output");
+        return launch_feat<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, 0>(a, st);
+    } else {
+        if (gemm_pads_rows(a)) return launch_feat<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, EPF_TRANS | EPF_SCALE | EPF_PADS>(a, st);
+        if constexpr (BN != 64) {
+            if (!a.rowbias && !a.rowscale && !a.act_gelu) {
+                if (seg) return launch_feat<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, EPF_TRANS | EPF_SCALE>(a, st);
+                return launch_feat<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, 0>(a, st);
+            }
+        }
+        return launch_feat<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, EPF_ALL>(a, st);
+    }
 }
 
 // shapes the MFMA kernels take at all

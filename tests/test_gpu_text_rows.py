@@ -14,10 +14,12 @@ pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(),
 from harness import GpuRun, rel_err, tolerance                      # noqa: E402
 
 
-@pytest.mark.parametrize("C", [64, 320])
-@pytest.mark.parametrize("n,L", [(1, 77), (5, 77), (24, 77), (7, 78), (4, 79), (3, 80), (6, 63), (9, 15), (9, 13), (11, 9), (40, 7), (2, 1)])
+# 64-column tiles; from 208 tiles of 128 x 160 on these (87 x 77 rows, 640 columns), from 64 rows of tiles on 128 x 256 (512 columns)
+@pytest.mark.parametrize("C,n,L", [(C, n, L) for C in (64, 320) for n, L in
+                                   [(1, 77), (2, 77), (5, 77), (24, 77), (7, 78), (4, 79), (3, 80), (6, 63), (9, 15), (9, 13), (11, 9), (40, 7), (2, 1)]] +
+                         [(320, 87, 77), (320, 90, 78), (320, 420, 17), (256, 107, 77)])
 def test_text_lengths(C, n, L):
-    cfg = wl.custom_config([(4, 4)] * (n // 2) + [(4, 8)] * (n - n // 2), (4, 4), C=C, G=8, heads=C // 64 * 2 if C == 320 else 1,
+    cfg = wl.custom_config([(4, 4)] * (n // 2) + [(4, 8)] * (n - n // 2), (4, 4), C=C, G=8, heads=10 if C == 320 else C // 64,
                            stages=("LXATTN",), dtype="bf16", ctx_len=L, ctx_dim=128, seed=61)
     w = wl.make_workload(cfg)
     got = GpuRun(w).forward_images()
