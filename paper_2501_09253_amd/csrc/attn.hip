@@ -352,7 +352,7 @@ static int attn_f32mma(const AttnArgs& a, hipStream_t st) {
 }
 
 // ---- fp32 self-attention on the bf16 matrix cores ---------------------------------------------------------
-// As the fp32 layers: every operand in three bf16 pieces that sum to it, six products of which all terms are exact in the fp32
+// As the fp32 layers: every operand in three bf16 pieces (cut3x2), six products of which all terms are exact in the fp32
 // accumulators.  attn_cut_kernel lays the keys and values of a request out in tiles of 32 keys and one head, K rows of
 // [3][D] and V^T rows of [3][32], in the very order (swizzle included) in which a tile lies in LDS: a tile is one linear copy.
 // attn_split_kernel: a block is 128 queries of one (request, head), four wavefronts of 32; K and V^T fragments and P stay as in
@@ -376,13 +376,13 @@ template <int D> __device__ __forceinline__ int at_swz(int row) { return D == 64
 __device__ __forceinline__ int64_t at_tile0(const int32_t* cu_seqlens, int s) { return cu_seqlens[s] / 32 + s; }
 // three pieces of eight values
 __device__ __forceinline__ void at_cut(const float (&x)[8], at_u32x4 (&o)[3]) {
-    uint32_t u[8][3];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) cut3(x[i], u[i]);
+    for (int q = 0; q < 4; ++q) {
+        uint32_t u[3];
+        cut3x2(x[2 * q], x[2 * q + 1], u);
 #pragma unroll
-    for (int p = 0; p < 3; ++p)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) o[p][q] = pack_hi16(u[2 * q][p], u[2 * q + 1][p]);
+        for (int p = 0; p < 3; ++p) o[p][q] = u[p];
+    }
 }
 
 // Block = (tile of the grid's upper bound, head); tiles that no request has are left alone.
@@ -566,7 +566,7 @@ attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv) {
         issue(t + 3, t + 2, true);
         const bool flush = t % ATT_FLUSH == 0;
         if (flush || __any(mx > m + 8.f)) {             // (a row sum that is not a number stays one)
-            const float mn = t == 0 ? mx : mx > m + 8.f ? mx : m, corr = t == 0 ? 0.f : __builtin_amdgcn_exp2f(m - mn);
+            const float mn = t == 0 ? mx : mx > m + 8.f ? mx : m, corr = t == 0 ? 0.f : exp2_square(0.5f * (m - mn));
             m = mn;
             l *= corr;
 #pragma unroll
@@ -577,6 +577,7 @@ attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv) {
                     o[dt][e] = ol[dt][e] = 0.f;
                 }
         }
+        const float hm = -0.5f * m;
         // The next tile's scores, and behind each MFMA up to five of this tile's vector instructions (about four are free, and none
         // where there is no MFMA: as two phases a tile took 3,360 clocks of which 1,536 are MFMAs) and a fragment read for six MFMAs
         // later: the probabilities in pairs, in four (D = 32: two) steps each; those that the first output products do not need
@@ -586,16 +587,16 @@ attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv) {
         float sum = 0.f, x0 = 0.f, x1 = 0.f;
         auto pair = [&](int g, int step) {              // step 0 .. 3 of pair g
             if (step == 0) {
-                x0 = __builtin_amdgcn_exp2f(p[2 * g] - m);
-                x1 = __builtin_amdgcn_exp2f(p[2 * g + 1] - m);
+                x0 = exp2_square(fmaf(p[2 * g], 0.5f, hm));
+                x1 = exp2_square(fmaf(p[2 * g + 1], 0.5f, hm));
                 return;
             }
             if (step == 1) sum += x0 + x1;
-            const uint32_t u0 = __float_as_uint(x0), u1 = __float_as_uint(x1);
-            pp[g >> 2][step - 1][g & 3] = __builtin_amdgcn_perm(u1, u0, 0x07060302);
+            const uint32_t u = near_bf16x2(x0, x1);                 // (cut3x2 of values of at most 2^8; a NaN stays one in x0)
+            pp[g >> 2][step - 1][g & 3] = u;
             if (step < 3) {
-                x0 = fmaxf(x0 - __uint_as_float(u0 & 0xFFFF0000u), PIECE_TINY);       // (cut3 of a value that is not negative)
-                x1 = fmaxf(x1 - __uint_as_float(u1 & 0xFFFF0000u), PIECE_TINY);
+                x0 -= lo_bf16(u);
+                x1 -= hi_bf16(u);
             }
         };
         __builtin_amdgcn_sched_barrier(0);
@@ -672,8 +673,8 @@ static int attn_split(const AttnArgs& a, hipStream_t st) {
 // From 128 blocks of 128 queries on, where a request has 1,024 keys: below, the fp32 kernel's blocks of 32 queries with the keys
 // shared out to four wavefronts spread better.  us of an LSATTN layer, fp32 kernel / this: 4,096 + 3,072 tokens, 5 heads of 64
 // (280 blocks) 460 / 309; 2 x 2,304, 5 of 32 (180) 117 / 102; 4,608, 10 of 32 (360) 391 / 282; 2,304, 5 of 64 (90) 138 / 133;
-// 4 x 576, 5 of 64 (100) 68 / 70; 4,096, 2 of 64 (64) 124 / 181; 16 x 256, 5 of 64 (160) 72 / 73.  Error of a layer of 4,096 tokens
-// against 64 bits 5.2e-8 / 4.2e-8, of 1,024 4.3e-8 / 4.1e-8 (of 256 4.5e-8 / 4.6e-8).
+// 4 x 576, 5 of 64 (100) 68 / 70; 4,096, 2 of 64 (64) 124 / 181; 16 x 256, 5 of 64 (160) 72 / 73.  Error of a layer
+// against 64 bits: 4,096 tokens 4.8e-8 / 3.4e-8, 4 x 1,024 4.7e-8 / 3.4e-8, 4,608 (10 heads) 4.9e-8 / 3.4e-8, 2 x 2,304 4.2e-8 / 3.5e-8.
 size_t attention_cut_bytes(const pserve_plan_t* plan, int32_t C, int32_t heads, int dtype, int mode) {
     if (dtype != PSERVE_F32 || mode != 0 || C % heads != 0 || (C / heads != 32 && C / heads != 64)) return 0;
     if ((int64_t)attention_max_tiles(plan, 1) * heads < 128 || plan->max_tokens_per_image < 1024) return 0;

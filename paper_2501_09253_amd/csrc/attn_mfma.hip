@@ -46,6 +46,7 @@ typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 constexpr int ATT_NS = 3;        // K / V^T ring depth in 64-key tiles
+constexpr float ATT_LEAST = 9.18354962e-41f;   // 2^-133, the smallest bf16 number
 constexpr float ATT_SUM_MAX = 4096.f;   // a lane's 16-key partial row sum above this moves the softmax reference
 
 // MFMA tile row r of a score tile holds key kperm(r) (bits 2 and 3 swapped): with this order the eight scores a lane
@@ -96,6 +97,10 @@ __device__ __forceinline__ bool attn_item(const AttnArgs& a, int& s, int& head, 
     return true;
 }
 
+// 2^(x - ref); RAG: down to the smallest subnormal, as the probabilities of the fp32 kernels
+template <bool RAG> __device__ __forceinline__ float att_exp2(float x, float ref = 0.f) {
+    return RAG ? exp2_square(fmaf(x, 0.5f, -0.5f * ref)) : __builtin_amdgcn_exp2f(x - ref);
+}
 template <int ATT_QT, int QW, int KG, int NS, bool RAG>
 __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
     constexpr int ATT_BQ = QW * 32 * ATT_QT, LPO = 8 / QW;      // query rows of the block; loads per wavefront, tile and operand
@@ -215,23 +220,24 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
     if (NS == 3) PS_ISSUE_TILE(kg + KG, 1);
 
     // probabilities of query sub-tile QT from its shifted scores minus SH_: exp2, bf16 pack, row sum of the packed values
-    // (RAG: row sum of the fp32 values, which go into the product as three pieces of eight bits, exactly; a piece that would
-    // be zero is the smallest normal number, since zero times an infinite value would be NaN)
+    // (RAG: row sum of the fp32 values, which go into the product as three pieces of eight bits, cut off: the values are read
+    // whole and may be infinite, so a piece of the other sign or of zero would give NaN.  A second or third piece that would be zero
+    // is the smallest number of bf16 instead: together they hold the probability to within 2^-132)
 #define PS_PROBS(QT, SH_)                                                                                        \
     {                                                                                                            \
         sum_ = 0.f;                                                                                              \
         _Pragma("unroll") for (int k2 = 0; k2 < 2; ++k2) {                                                       \
             u32x4 pk_[NP];                                                                                       \
             _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                                      \
-                f32x2 pf_ = {__builtin_amdgcn_exp2f(acc_s[QT][8 * k2 + 2 * i] - (SH_)),                          \
-                             __builtin_amdgcn_exp2f(acc_s[QT][8 * k2 + 2 * i + 1] - (SH_))};                     \
+                const float e0_ = acc_s[QT][8 * k2 + 2 * i], e1_ = acc_s[QT][8 * k2 + 2 * i + 1];                \
+                f32x2 pf_ = {att_exp2<RAG>(e0_, SH_), att_exp2<RAG>(e1_, SH_)};                                  \
                 if constexpr (RAG) {                                                                             \
                     sum_ += pf_[0] + pf_[1];                                                                     \
                     _Pragma("unroll") for (int q_ = 0; q_ < NP; ++q_) {                                          \
                         const uint32_t u0_ = __float_as_uint(pf_[0]), u1_ = __float_as_uint(pf_[1]);             \
                         pk_[q_][i] = __builtin_amdgcn_perm(u1_, u0_, 0x07060302);                                \
-                        pf_[0] = fmaxf(pf_[0] - __uint_as_float(u0_ & 0xFFFF0000u), PIECE_TINY);                   \
-                        pf_[1] = fmaxf(pf_[1] - __uint_as_float(u1_ & 0xFFFF0000u), PIECE_TINY);                   \
+                        pf_[0] = fmaxf(pf_[0] - __uint_as_float(u0_ & 0xFFFF0000u), ATT_LEAST);                  \
+                        pf_[1] = fmaxf(pf_[1] - __uint_as_float(u1_ & 0xFFFF0000u), ATT_LEAST);                  \
                     }                                                                                            \
                 } else {                                                                                         \
                     const bf16x2 pb_ = __builtin_convertvector(pf_, bf16x2);                                     \
@@ -295,7 +301,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
                 _Pragma("unroll") for (int e = 0; e < 16; ++e) m_ = fmaxf(m_, acc_s[qt][e]);                     \
                 m_ = half_swap_max(m_);                                                                          \
                 const float d_ = ((FIRST) || m_ > 4.f) ? m_ : 0.f;                                               \
-                const float corr_ = (FIRST) ? 1.f : __builtin_amdgcn_exp2f(-d_);                                 \
+                const float corr_ = (FIRST) ? 1.f : att_exp2<RAG>(-d_);                                          \
                 m_ref[qt] += d_;                                                                                 \
                 l_run[qt] *= corr_;                                                                              \
                 _Pragma("unroll") for (int dt = 0; dt < 2; ++dt)                                                 \
@@ -353,14 +359,14 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
         const int groups = min(KG, steps);
         float m = m_ref[0];
         for (int g = 1; g < groups; ++g) m = fmaxf(m, at(g, 32));
-        const float f0 = __builtin_amdgcn_exp2f(m_ref[0] - m);
+        const float f0 = att_exp2<RAG>(m_ref[0] - m);
         l_run[0] *= f0;
 #pragma unroll
         for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc_o[0][dt][e] *= f0;
         for (int g = 1; g < groups; ++g) {
-            const float f = __builtin_amdgcn_exp2f(at(g, 32) - m);
+            const float f = att_exp2<RAG>(at(g, 32) - m);
             l_run[0] = fmaf(at(g, 33), f, l_run[0]);
 #pragma unroll
             for (int dt = 0; dt < 2; ++dt)
@@ -1035,8 +1041,8 @@ int attention_mfma_bf16(const AttnArgs& a, hipStream_t st, bool* handled) {
         return check_launch("attn_cross_kernel");
     }
     // Requests may start inside a 16-byte piece of the V^T rows: the compiled-apart form of attn_body.  us of an LSATTN layer
-    // against the fp32 kernel: 20,736 tokens x 192 in 6 x 6 patches 3,809 -> 727, 3,780 in four requests 96.5 -> 41.4, 900 x 1280
-    // 121 -> 58; errors against 64 bits equal to four digits.
+    // against the fp32 kernel: 20,736 tokens x 192 in 6 x 6 patches 3,807 -> 733 (712 where probabilities end at 2^-126), 3,780 in four
+    // requests x 320 119.9 -> 47.2, 900 x 1280 127 -> 59; errors against 64 bits equal to four digits.
     const bool rag = !a.cross_len && a.geom.S % 8 != 0;
     auto go = [&](auto kernel, int bq, int threads, int lds, const char* name) -> int {
         AttnArgs b = a;

@@ -375,10 +375,10 @@ static bool gemm_f32mma(const GemmArgs& a, hipStream_t st) {
 }
 
 // ---- fp32 on the bf16 matrix cores ----------------------------------------------------------------
-// The bf16 MFMA does 16 times the work of the fp32 one, so an fp32 value is cut into three bf16 pieces of eight bits each
-// (cut3: x = x0 + x1 + x2) and a product is x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0), every term exact in
-// the fp32 accumulators; what is left out is below 2^-24 of a product, and a sum has an eighth as many roundings.  The
-// large terms and the others have accumulators of their own.  Both operands come in pieces, rows of [K / 32][3][32]: the weights
+// The bf16 MFMA does 16 times the work of the fp32 one, so an fp32 value is cut into three bf16 pieces
+// (cut3x2: x = x0 + x1 + x2) and a product is x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0), every term exact in
+// the fp32 accumulators; what is left out is at most 2^-23.9 of a product, of either sign, and a sum has an eighth as many
+// roundings.  The large terms and the others have accumulators of their own.  Both operands come in pieces, rows of [K / 32][3][32]: the weights
 // are cut when they are packed (split_packed), the activations by the kernel that produces them (cutting them here, once a tile
 // and step, took as long as the MFMAs).  A step's 32 k of a row are 192 contiguous bytes: as three runs of 64 the loads into LDS,
 // which bound the kernel, took twice as long.
@@ -388,7 +388,7 @@ static bool gemm_f32mma(const GemmArgs& a, hipStream_t st) {
 // between the MFMAs of this one.  LDS rows are 192 bytes, chunk c of a piece at c ^ ((row >> 2) & 3): conflict free.
 //   Two convolutions of 7,168 tokens x 320 channels: 162 -> 78 us each (170 TFLOP/s of fp32); bound by the bf16 matrix pipe at the clock it
 // gets (1.0 PFLOP/s) and, for few tiles, by a tile's start and end (7 us).  Error of a block of two convolutions and an attention
-// against 64 bits 2.6e-7 -> 2.0e-7.
+// against 64 bits 2.6e-7 -> 1.9e-7.
 typedef __attribute__((ext_vector_type(8))) __bf16 gs_bf16x8;
 typedef __attribute__((ext_vector_type(4))) uint32_t gs_u32x4;
 typedef __attribute__((address_space(3))) void gs_lds_void;
@@ -592,13 +592,16 @@ gemm_split_kernel(GemmArgs a, const uint16_t* __restrict__ Bs) {
         }
         if (a.out_pieces) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                if (tok[e] < 0) continue;
-                uint16_t* op = (uint16_t*)seg.ptr + tok[e] * 3 * seg.ld + piece_index(sc);
+            for (int e = 0; e < 8; e += 2) {
                 uint32_t u[3];
-                cut3(v[e], u);
+                cut3x2(v[e], v[e + 1], u);
 #pragma unroll
-                for (int pl = 0; pl < 3; ++pl) op[32 * pl] = (uint16_t)(u[pl] >> 16);
+                for (int q = 0; q < 2; ++q) {
+                    if (tok[e + q] < 0) continue;
+                    uint16_t* op = (uint16_t*)seg.ptr + tok[e + q] * 3 * seg.ld + piece_index(sc);
+#pragma unroll
+                    for (int pl = 0; pl < 3; ++pl) op[32 * pl] = (uint16_t)(u[pl] >> 16 * q);
+                }
             }
         } else {
             const int64_t rs = seg.transposed ? 1 : seg.ld;
@@ -620,9 +623,9 @@ __global__ void split_packed_kernel(const float* __restrict__ w, uint16_t* __res
     if (i >= rows * K) return;
     const int64_t r = i / K;
     uint32_t u[3];
-    cut3(w[i], u);
+    cut3x2(w[i], 0.f, u);
 #pragma unroll
-    for (int pl = 0; pl < 3; ++pl) dst[r * 3 * K + piece_index((int)(i - r * K)) + 32 * pl] = (uint16_t)(u[pl] >> 16);
+    for (int pl = 0; pl < 3; ++pl) dst[r * 3 * K + piece_index((int)(i - r * K)) + 32 * pl] = (uint16_t)u[pl];
 }
 int split_packed(void* packed, int64_t rows, int32_t K, int dtype, hipStream_t st) {
     if (dtype == PSERVE_BF16 || K % 32 != 0) return PSERVE_OK;

@@ -23,33 +23,51 @@ template <typename T> __device__ __forceinline__ void st_f(T* p, float v);
 template <> __device__ __forceinline__ void st_f<float>(float* p, float v) { *p = v; }
 template <> __device__ __forceinline__ void st_f<uint16_t>(uint16_t* p, float v) { *p = float_to_bf16_bits(v); }
 
-// fp32 rows as bf16 pieces: rows of [C / 32][3][32], three pieces of every value that sum to it exactly.  Index of the first
-// piece of value c; the others follow 32 and 64 further.
+// fp32 rows as bf16 pieces: rows of [C / 32][3][32], three pieces of every value.  Index of the first piece of value c; the
+// others follow 32 and 64 further.
 __host__ __device__ __forceinline__ int piece_index(int c) { return (c >> 5) * 96 + (c & 31); }
-// The pieces of x, in the upper halves of u: eight bits of its digits each, cut off, so they have its sign.  A piece that would be
-// zero (or, of an infinite x, not a number) is the smallest normal number instead unless x is zero: zero times an infinite
-// factor would be NaN where the product is infinite.
-constexpr float PIECE_TINY = 1.17549435e-38f;
-__device__ __forceinline__ void cut3(float x, uint32_t (&u)[3]) {
-    const float tiny = fminf(fabsf(x), PIECE_TINY);
-    float r = x;
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-        u[p] = __float_as_uint(r);
-        r = copysignf(fmaxf(fabsf(r - __uint_as_float(u[p] & 0xFFFF0000u)), tiny), x);
-    }
+// bf16 numbers nearest to two values (ties to even), the first in the lower half; a half as a float
+typedef __attribute__((ext_vector_type(2))) float ps_f32x2;
+typedef __attribute__((ext_vector_type(2))) __bf16 ps_bf16x2;
+__device__ __forceinline__ uint32_t near_bf16x2(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(ps_f32x2{a, b}, ps_bf16x2));
 }
-__device__ __forceinline__ uint32_t pack_hi16(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302); }
+__device__ __forceinline__ float lo_bf16(uint32_t u) { return __uint_as_float(u << 16); }
+__device__ __forceinline__ float hi_bf16(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
+// The pieces x0, x1, x2 of two values, u[piece]: each the nearest bf16 number to what the ones before it leave, so |x1| <= 2^-8
+// |x|, |x2| <= 2^-17 |x|, their signs are as likely one as the other, and they sum to x exactly; below 2^-110, where the last
+// piece leaves the range of bf16, to within 2^-134.  The product of two values takes six of the nine products of pieces; x1 y2, x2 y1
+// and x2 y2 are at most 2^-23.9 of it and zero in the mean (four million pairs: 2^-24.2, 1e-12).  Pieces cut off instead of
+// rounded lose up to 2^-21.0, always towards zero (2^-21.2, 4e-8).
+// A value that is not finite is (2^-126, 0, x) with x's sign: of the six products only those with the other factor's x0 then hold it,
+// which is zero or has the factor's sign, so infinities and NaN come out as those of the plain product.
+constexpr float PIECE_TINY = 1.17549435e-38f, PIECE_MAX = 3.38953139e38f;       // smallest normal, largest bf16 number
+__device__ __forceinline__ void cut3x2(float a, float b, uint32_t (&u)[3]) {
+    if (fabsf(a) + fabsf(b) <= PIECE_MAX) {
+        u[0] = near_bf16x2(a, b);
+        const float ra = a - lo_bf16(u[0]), rb = b - hi_bf16(u[0]);
+        u[1] = near_bf16x2(ra, rb);
+        u[2] = near_bf16x2(ra - lo_bf16(u[1]), rb - hi_bf16(u[1]));
+        return;
+    }
+    // not finite, or large (the largest values would round to infinity)
+    const bool fa = fabsf(a) < INFINITY, fb = fabsf(b) < INFINITY;
+    u[0] = near_bf16x2(fa ? fminf(fmaxf(a, -PIECE_MAX), PIECE_MAX) : copysignf(PIECE_TINY, a),
+                       fb ? fminf(fmaxf(b, -PIECE_MAX), PIECE_MAX) : copysignf(PIECE_TINY, b));
+    const float ra = fa ? a - lo_bf16(u[0]) : 0.f, rb = fb ? b - hi_bf16(u[0]) : 0.f;
+    u[1] = near_bf16x2(ra, rb);
+    u[2] = near_bf16x2(fa ? ra - lo_bf16(u[1]) : a, fb ? rb - hi_bf16(u[1]) : b);
+}
+// 2^(2 h).  The instruction returns zero below 2^-126; the square of its result goes down to the smallest subnormal, as exp2f,
+// at a multiplication instead of exp2f's five instructions.
+__device__ __forceinline__ float exp2_square(float h) { const float e = __builtin_amdgcn_exp2f(h); return e * e; }
 // pieces of four neighbouring values (a multiple of four in front of them), the first at dst
 __device__ __forceinline__ void store_pieces4(uint16_t* dst, float a, float b, float c, float d) {
-    uint32_t u[4][3];
-    cut3(a, u[0]);
-    cut3(b, u[1]);
-    cut3(c, u[2]);
-    cut3(d, u[3]);
+    uint32_t u[2][3];
+    cut3x2(a, b, u[0]);
+    cut3x2(c, d, u[1]);
 #pragma unroll
-    for (int p = 0; p < 3; ++p)
-        *reinterpret_cast<uint2*>(dst + 32 * p) = make_uint2(pack_hi16(u[0][p], u[1][p]), pack_hi16(u[2][p], u[3][p]));
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2*>(dst + 32 * p) = make_uint2(u[0][p], u[1][p]);
 }
 
 // Patch geometry shared by the kernels that walk tokens.

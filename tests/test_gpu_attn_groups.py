@@ -88,3 +88,21 @@ def test_value_slot_round_trip(patch):
     other.migrate_from(run.cache, src)
     S = ph * pw
     assert torch.equal(other.read(0, ps.SLOT_V), torch.cat([t[p * S:(p + 1) * S] for p in src.tolist()]))
+
+
+@pytest.mark.parametrize("res,patch,C", [SHAPES[4], SHAPES[7]])
+def test_ragged_probabilities_keep_their_digits(res, patch, C):
+    """Values of one and random logits: the result is one whatever the probabilities are, if all their digits meet the values (a row
+    sum of fp32 probabilities over their first eight digits alone is 0.3 % off).  Mean over all results; they are rounded to bf16
+    together with a small random input, 2^-8 at most and of either sign."""
+    cfg = wl.custom_config(res, patch, C=C, G=8, heads=C // 64, stages=("LSATTN",), dtype="bf16", seed=89)
+    w = wl.make_workload(cfg)
+    p = w.params[0]
+    p["ln_g"][0], p["ln_b"][0] = 0, 1                   # channel 0 of the normalised input is one
+    p["wv"][:], p["bo"][:] = 0, 0
+    p["wv"][0] = 1
+    p["wo"] = np.eye(C, dtype=np.float32)
+    w.images = [wl.bf16_round((im * 2.0 ** -6).astype(np.float32)) for im in w.images]
+    got = GpuRun(w).forward_images()
+    err = np.concatenate([(np.asarray(a, np.float64) - im - 1.0).ravel() for a, im in zip(got, w.images)])
+    assert abs(err.mean()) < 5e-4, err.mean()
