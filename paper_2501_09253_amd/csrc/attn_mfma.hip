@@ -200,6 +200,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc_o[qt][dt][e] = 0.f;
     float m_ref[ATT_QT] = {}, l_run[ATT_QT] = {};   // reference maximum (log2 domain) and partial row sums
+    bool none = true, any_none = true;  // KG > 1: the group has met no score above -infinity of this query (of one): no reference yet
     f32x16 cinit[ATT_QT];                                       // -m_ref of the lane's query in every element
     f32x16 acc_s[ATT_QT];                                       // shifted scores of one 32-key half tile, per query sub-tile
     constexpr int NP = RAG ? 3 : 1;                             // bf16 pieces of a probability
@@ -296,12 +297,14 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
         _Pragma("unroll") for (int qt = 0; qt < ATT_QT; ++qt) {                                                       \
             float sum_;                                                                                          \
             PS_PROBS(qt, 0.f);                                                                                   \
-            if ((FIRST) || __any(!(sum_ <= ATT_SUM_MAX))) {                                                      \
+            if ((KG == 1 ? (FIRST) : any_none) || __any(!(sum_ <= ATT_SUM_MAX))) {                               \
                 float m_ = -INFINITY;                                                                            \
                 _Pragma("unroll") for (int e = 0; e < 16; ++e) m_ = fmaxf(m_, acc_s[qt][e]);                     \
                 m_ = half_swap_max(m_);                                                                          \
-                const float d_ = ((FIRST) || m_ > 4.f) ? m_ : 0.f;                                               \
-                const float corr_ = (FIRST) ? 1.f : att_exp2<RAG>(-d_);                                          \
+                const bool first_ = KG == 1 ? (FIRST) : none;                                                    \
+                if (KG > 1) { none = none && m_ == -INFINITY; any_none = __any(none); }                          \
+                const float d_ = KG > 1 && none ? 0.f : first_ || m_ > 4.f ? m_ : 0.f;                           \
+                const float corr_ = first_ ? 1.f : att_exp2<RAG>(-d_);                                           \
                 m_ref[qt] += d_;                                                                                 \
                 l_run[qt] *= corr_;                                                                              \
                 _Pragma("unroll") for (int dt = 0; dt < 2; ++dt)                                                 \
@@ -351,15 +354,16 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int tid) {
             for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) at(kg, 16 * dt + e) = acc_o[0][dt][e];
-            at(kg, 32) = m_ref[0];
+            at(kg, 32) = none ? -INFINITY : m_ref[0];
             at(kg, 33) = l_run[0];
         }
         __syncthreads();
         if (kg > 0) return;
         const int groups = min(KG, steps);
-        float m = m_ref[0];
+        const float m0 = none ? -INFINITY : m_ref[0];
+        float m = m0;
         for (int g = 1; g < groups; ++g) m = fmaxf(m, at(g, 32));
-        const float f0 = att_exp2<RAG>(m_ref[0] - m);
+        const float f0 = att_exp2<RAG>(m0 - m);
         l_run[0] *= f0;
 #pragma unroll
         for (int dt = 0; dt < 2; ++dt)

@@ -106,3 +106,36 @@ def test_ragged_probabilities_keep_their_digits(res, patch, C):
     got = GpuRun(w).forward_images()
     err = np.concatenate([(np.asarray(a, np.float64) - im - 1.0).ravel() for a, im in zip(got, w.images)])
     assert abs(err.mean()) < 5e-4, err.mean()
+
+
+# tiles of 64 keys in two groups of 64 queries, four of 64, two of 128 (requests that start at a multiple of eight and elsewhere)
+@pytest.mark.parametrize("res,patch,C,tile", [([(8, 24), (8, 40)], (8, 8), 64, 1), ([(8, 136), (8, 16)], (8, 8), 64, 3),
+                                              ([(32, 32)] * 4, (8, 8), 320, 1), ([(9, 27), (9, 9), (9, 36)], (9, 9), 64, 1)])
+@pytest.mark.parametrize("all_tiles", [False, True])
+def test_groups_without_a_finite_score(res, patch, C, tile, all_tiles):
+    """Every key that one group of wavefronts meets first (all_tiles: every key but those of one patch) has the score -infinity: it
+    has no weight, whatever group it is in."""
+    cfg = wl.custom_config(res, patch, C=C, G=8, heads=C // 64, stages=("LSATTN",), dtype="bf16", reuse_p=0.5, seed=97)
+    w = wl.make_workload(cfg)
+    p = w.params[0]
+    p["ln_g"][0], p["ln_b"][0] = 0, 1
+    p["wq"][:] = 0
+    p["wq"][0, ::64] = 1                                # queries (1, 0, 0, ..)
+    p["wk"][:, ::64] = 0                                # computed keys 0 there: scores 0
+    ph, pw = patch
+    for r, k in zip(w.reuse, w.cache["0.K"]):
+        r[:] = False
+        n = r.size
+        for q in range(n - 1) if all_tiles else [min(tile, n - 1)] if n > 1 else []:
+            i, j = divmod(q, r.shape[1])
+            r[i, j] = True
+            k[::64, i * ph:(i + 1) * ph, j * pw:(j + 1) * pw] = -np.inf
+    run = GpuRun(w)
+    run.load_cache()
+    got = run.forward_images(reuse=w.reuse)
+    with np.errstate(invalid="ignore"):
+        ref, _ = ob.forward_batch(w.images, cfg.stages, w.params, G=cfg.G, heads=cfg.heads, eps=cfg.eps, reuse=w.reuse, cache=w.cache)
+    for a, b in zip(got, ref):
+        assert np.isfinite(b).all()
+        err = rel_err([a], [b])
+        assert np.isfinite(err) and err < tolerance("bf16"), err
