@@ -190,7 +190,10 @@ int  pserve_split_stats(const pserve_plan_t* plan, const void* const* images, in
 
 /* ---- block: description + weights.  Packs the weights into the layouts the kernels
  * read (device copies owned by the block); the caller's parameter buffers are not
- * referenced after the call returns (it synchronises `stream`).
+ * referenced after the call returns (it synchronises `stream`).  fp32 weights of convolutions,
+ * self-attention, attention outputs and layers behind a LayerNorm (not those of joint blocks) take
+ * 10 bytes a value where their input width is a multiple of 32 (three bf16 pieces beside the value,
+ * for the matrix cores), all others 4, bf16 ones 2.
  * Errors: EINVAL for unknown stage kinds, C % G, C % heads, XATTN without ctx sizes,
  * a NULL parameter; ENOMEM; EHIP. */
 int  pserve_block_create(const pserve_block_desc* desc, const pserve_block_params* params,
@@ -201,7 +204,8 @@ void pserve_block_free(pserve_block_t* block);
  * cache ("Patch-aware Caching Strategy": operands of context operators and the block
  * output of the previous step, per patch) plus all scratch the forward pass needs (for bf16
  * residual convolutions of few patches also up to 42 MB of partial sums: the forward pass then
- * shares a tile's input channels between blocks).
+ * shares a tile's input channels between blocks; for fp32 stages large enough for the bf16 matrix
+ * cores, 6 bytes a value of each layer's input, and keys and values once more at 6 bytes each).
  * with_slots = 0 allocates scratch only (then reuse_mask must be NULL). */
 int  pserve_cache_create(const pserve_plan_t* plan, const pserve_block_t* block, int with_slots,
                          pserve_cache_t** out);

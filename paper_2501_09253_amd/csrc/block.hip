@@ -312,6 +312,8 @@ struct pserve_cache_s {
     void* k[PSERVE_MAX_STAGES] = {};          // SATTN: keys (slot K)
     void* v[PSERVE_MAX_STAGES] = {};          // SATTN: values (slot V; [C][v_ld] when v_transposed)
     void* q = nullptr;                        // [T][C] scaled queries
+    // the buffers that feed layers have room for fp32 values as three bf16 pieces: some layer reads them so at this plan's size
+    bool apad_pieces = false, u_pieces = false, o_pieces = false, hidden_pieces = false;
     void* cut = nullptr;                      // fp32 self-attention: keys and values in bf16 pieces (of the stage that runs)
     void* o = nullptr;                        // [T][C] attention output
     void* u = nullptr;                        // [T][C] normalised tokens
@@ -466,10 +468,12 @@ static int block_create_impl(const pserve_block_desc* desc, const pserve_block_p
     const size_t es = dtype_size(d.dtype);
     const int C = d.C;
     struct Packed { void* p; int64_t rows; int32_t K; };
-    std::vector<Packed> packed;                      // all packed weights: fp32 ones get their bf16 pieces at the end
-    auto weights = [&](void** dst, int64_t rows, int32_t K) -> int {
-        PS_TRY(b->pool.alloc(dst, packed_weight_bytes(rows, K, d.dtype)));
-        packed.push_back({*dst, rows, K});
+    std::vector<Packed> packed;                      // fp32 weights that get their bf16 pieces at the end
+    // pieces: the layer may read its activations, and so its weights, in pieces (the forward pass sets a_pieces for it)
+    auto weights = [&](void** dst, int64_t rows, int32_t K, bool pieces) -> int {
+        const size_t plain = es * rows * K, both = pieces ? packed_weight_bytes(rows, K, d.dtype) : plain;
+        PS_TRY(b->pool.alloc(dst, both));
+        if (both != plain) packed.push_back({*dst, rows, K});
         return PSERVE_OK;
     };
     for (int s = 0; s < d.n_stages; ++s) {
@@ -499,7 +503,7 @@ static int block_create_impl(const pserve_block_desc* desc, const pserve_block_p
             for (int c = 0; c < convs; ++c) {
                 PS_TRY(dup_param(b->pool, p[4 * c + 0], es * C, &w.gn_g[c], st));
                 PS_TRY(dup_param(b->pool, p[4 * c + 1], es * C, &w.gn_b[c], st));
-                PS_TRY(weights(&w.w[c], 9 * C, C));
+                PS_TRY(weights(&w.w[c], 9 * C, C, true));
                 PS_TRY(pack_conv(p[4 * c + 2], w.w[c], C, C, d.dtype, st));
                 PS_TRY(b->pool.alloc_t(&w.b[c], C));
                 PS_TRY(pack_bias(p[4 * c + 3], w.b[c], C, d.dtype, st));
@@ -514,9 +518,9 @@ static int block_create_impl(const pserve_block_desc* desc, const pserve_block_p
                 PS_TRY(dup_param(b->pool, p[0], es * C, &w.gn_g[0], st));
                 PS_TRY(dup_param(b->pool, p[1], es * C, &w.gn_b[0], st));
             }
-            PS_TRY(weights(&w.w[0], 3 * C, C));                       // fused [Wq | Wk | Wv]
+            PS_TRY(weights(&w.w[0], 3 * C, C, true));                 // fused [Wq | Wk | Wv]
             for (int k = 0; k < 3; ++k) PS_TRY(pack_linear(p[o + k], w.w[0], C, C, k * C, d.dtype, st));
-            PS_TRY(weights(&w.w[1], C, C));
+            PS_TRY(weights(&w.w[1], C, C, true));
             PS_TRY(pack_linear(p[o + 3], w.w[1], C, C, 0, d.dtype, st));
             PS_TRY(b->pool.alloc_t(&w.b[1], C));
             PS_TRY(pack_bias(p[o + 4], w.b[1], C, d.dtype, st));
@@ -530,17 +534,17 @@ static int block_create_impl(const pserve_block_desc* desc, const pserve_block_p
                 PS_TRY(dup_param(b->pool, q[0], es * d.temb_dim * 6 * C, &v.wt, st));
                 PS_TRY(b->pool.alloc_t(&v.bt, 6 * C));
                 PS_TRY(pack_bias(q[1], v.bt, 6 * C, d.dtype, st));
-                PS_TRY(weights(&v.w[0], 3 * C, C));
+                PS_TRY(weights(&v.w[0], 3 * C, C, false));
                 for (int k = 0; k < 3; ++k) PS_TRY(pack_linear(q[2 + k], v.w[0], C, C, k * C, d.dtype, st));
-                PS_TRY(weights(&v.w[1], C, C));
+                PS_TRY(weights(&v.w[1], C, C, false));
                 PS_TRY(pack_linear(q[5], v.w[1], C, C, 0, d.dtype, st));
                 PS_TRY(b->pool.alloc_t(&v.b[1], C));
                 PS_TRY(pack_bias(q[6], v.b[1], C, d.dtype, st));
-                PS_TRY(weights(&v.w[3], F, C));
+                PS_TRY(weights(&v.w[3], F, C, false));
                 PS_TRY(pack_linear(q[7], v.w[3], C, F, 0, d.dtype, st));
                 PS_TRY(b->pool.alloc_t(&v.b[3], F));
                 PS_TRY(pack_bias(q[8], v.b[3], F, d.dtype, st));
-                PS_TRY(weights(&v.w[4], C, F));
+                PS_TRY(weights(&v.w[4], C, F, false));
                 PS_TRY(pack_linear(q[9], v.w[4], F, C, 0, d.dtype, st));
                 PS_TRY(b->pool.alloc_t(&v.b[4], C));
                 PS_TRY(pack_bias(q[10], v.b[4], C, d.dtype, st));
@@ -549,11 +553,11 @@ static int block_create_impl(const pserve_block_desc* desc, const pserve_block_p
         }
         case PSERVE_AMLP: {
             const int F = d.ffn_mult * C;
-            PS_TRY(weights(&w.w[0], F, C));
+            PS_TRY(weights(&w.w[0], F, C, true));
             PS_TRY(pack_linear(p[0], w.w[0], C, F, 0, d.dtype, st));
             PS_TRY(b->pool.alloc_t(&w.b[0], F));
             PS_TRY(pack_bias(p[1], w.b[0], F, d.dtype, st));
-            PS_TRY(weights(&w.w[1], C, F));
+            PS_TRY(weights(&w.w[1], C, F, C % 32 == 0));      // (pieces come from the layer before)
             PS_TRY(pack_linear(p[2], w.w[1], F, C, 0, d.dtype, st));
             PS_TRY(b->pool.alloc_t(&w.b[1], C));
             PS_TRY(pack_bias(p[3], w.b[1], C, d.dtype, st));
@@ -562,12 +566,12 @@ static int block_create_impl(const pserve_block_desc* desc, const pserve_block_p
         case PSERVE_XATTN:
         case PSERVE_LXATTN: {
             const int D = d.ctx_dim;
-            PS_TRY(weights(&w.w[0], C, C));
+            PS_TRY(weights(&w.w[0], C, C, has_ln(d.stages[s])));
             PS_TRY(pack_linear(p[0], w.w[0], C, C, 0, d.dtype, st));
-            PS_TRY(weights(&w.w[2], 2 * C, D));                       // fused [Wk | Wv] on the text tokens
+            PS_TRY(weights(&w.w[2], 2 * C, D, false));                // fused [Wk | Wv] on the text tokens
             PS_TRY(pack_linear(p[1], w.w[2], D, C, 0, d.dtype, st));
             PS_TRY(pack_linear(p[2], w.w[2], D, C, C, d.dtype, st));
-            PS_TRY(weights(&w.w[1], C, C));
+            PS_TRY(weights(&w.w[1], C, C, true));
             PS_TRY(pack_linear(p[3], w.w[1], C, C, 0, d.dtype, st));
             PS_TRY(b->pool.alloc_t(&w.b[1], C));
             PS_TRY(pack_bias(p[4], w.b[1], C, d.dtype, st));
@@ -576,10 +580,10 @@ static int block_create_impl(const pserve_block_desc* desc, const pserve_block_p
         case PSERVE_FFN:
         case PSERVE_LFFN: {
             const int F = d.ffn_mult * C;
-            PS_TRY(weights(&w.w[0], 2 * F, C));
+            PS_TRY(weights(&w.w[0], 2 * F, C, has_ln(d.stages[s])));
             PS_TRY(b->pool.alloc_t(&w.b[0], 2 * F));
             PS_TRY(pack_geglu(p[0], p[1], w.w[0], w.b[0], C, F, d.dtype, st));
-            PS_TRY(weights(&w.w[1], C, F));
+            PS_TRY(weights(&w.w[1], C, F, has_ln(d.stages[s]) && C % 32 == 0));
             PS_TRY(pack_linear(p[2], w.w[1], F, C, 0, d.dtype, st));
             PS_TRY(b->pool.alloc_t(&w.b[1], C));
             PS_TRY(pack_bias(p[3], w.b[1], C, d.dtype, st));
@@ -631,14 +635,33 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
     const bool sattn = any_stage(d, is_sattn), xattn = any_stage(d, is_xattn);
     const bool ffn = any_stage(d, is_ffn) || has_stage(d, PSERVE_AMLP) || joint;
     const bool gn_sattn = has_stage(d, PSERVE_SATTN);
-    // what feeds a layer may hold fp32 values as three bf16 pieces
-    const size_t ps = d.dtype == PSERVE_F32 ? 6 : es, TCP = (size_t)plan->T * d.C * ps;
+    const PatchGeom g{plan->P, plan->S, plan->ph, plan->pw, plan->pw + 2, (plan->ph + 2) * (plan->pw + 2)};
+    if (d.dtype == PSERVE_F32) {            // which layers read their activations in pieces: those of the forward pass, by their sizes
+        auto takes = [&](int K, int N, int epi = EPI_ROUTE, int taps = 1) {
+            GemmArgs a{};
+            a.geom = g; a.tokens_are_rows = 1; a.M = (int32_t)plan->T; a.lda = a.K = K; a.N = N; a.epi = epi; a.taps = taps; a.conv = taps > 1;
+            return gemm_takes_pieces(a, d.dtype, g_kernel_mode == 1 ? 1 : 0);
+        };
+        const int C = d.C, F = d.ffn_mult * C;
+        for (int s = 0; s < d.n_stages; ++s) {
+            const int k = d.stages[s];
+            if (k == PSERVE_RES1 || is_res2(k)) c->apad_pieces |= takes(C, C, EPI_ROUTE, 9);
+            if (is_sattn(k) && k != PSERVE_MMDIT) c->u_pieces |= takes(C, 3 * C);
+            if (k == PSERVE_LXATTN) c->u_pieces |= takes(C, C);
+            if ((is_sattn(k) && k != PSERVE_MMDIT) || is_xattn(k)) c->o_pieces |= takes(C, C);
+            if (k == PSERVE_AMLP || k == PSERVE_LFFN) {
+                const bool in = k == PSERVE_AMLP ? takes(C, F) : takes(C, 2 * F, EPI_GEGLU);
+                c->u_pieces |= in;
+                c->hidden_pieces |= in && takes(F, C);
+            }
+        }
+    }
+    auto elem = [&](bool pieces) -> size_t { return pieces ? 6 : es; };
     if (conv) {
-        PatchGeom g{plan->P, plan->S, plan->ph, plan->pw, plan->pw + 2, (plan->ph + 2) * (plan->pw + 2)};
         c->split_ws_bytes = conv_split_bytes(g, (int32_t)plan->T, d.C, d.C, d.dtype, g_kernel_mode == 1 ? 1 : 0);
         if (c->split_ws_bytes) PS_TRY(c->pool.alloc((void**)&c->split_ws, c->split_ws_bytes));
     }
-    if (conv) PS_TRY(c->pool.alloc(&c->apad, (size_t)plan->P * (plan->ph + 2) * (plan->pw + 2) * d.C * ps));
+    if (conv) PS_TRY(c->pool.alloc(&c->apad, (size_t)plan->P * (plan->ph + 2) * (plan->pw + 2) * d.C * elem(c->apad_pieces)));
     if (conv || gn_sattn) {
         PS_TRY(c->pool.alloc_t(&c->partial, (size_t)plan->P * std::max<int64_t>(c->nsplit, plan->S / 64) * d.G * 2));
         PS_TRY(c->pool.alloc_t(&c->scale_shift, (size_t)plan->n * d.C * 2));
@@ -667,9 +690,9 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
     }
     if (sattn || xattn) {
         PS_TRY(c->pool.alloc(&c->q, TC));
-        PS_TRY(c->pool.alloc(&c->o, TCP));
+        PS_TRY(c->pool.alloc(&c->o, (size_t)plan->T * d.C * elem(c->o_pieces)));
     }
-    if (sattn || any_stage(d, has_ln)) PS_TRY(c->pool.alloc(&c->u, TCP));     // normalised stage input
+    if (sattn || any_stage(d, has_ln)) PS_TRY(c->pool.alloc(&c->u, (size_t)plan->T * d.C * elem(c->u_pieces)));     // normalised stage input
     if (xattn) {
         // text keys / values: rows padded to a multiple of 8 per request and zero-filled once, so that the
         // padding rows (never written) contribute exact zeros; values transposed like the self-attention V
@@ -692,7 +715,7 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
             if (const size_t bytes = attention_cut_bytes(plan, d.C, d.heads, d.dtype, g_kernel_mode == 1 ? 1 : 0))
                 PS_TRY(c->pool.alloc(&c->cut, bytes));
     }
-    if (ffn) PS_TRY(c->pool.alloc(&c->hidden, (size_t)plan->T * d.ffn_mult * d.C * ps));
+    if (ffn) PS_TRY(c->pool.alloc(&c->hidden, (size_t)plan->T * d.ffn_mult * d.C * elem(c->hidden_pieces)));
     if (with_slots) PS_TRY(c->pool.alloc(&c->yslot, TC));
     PS_TRY(c->pool.alloc_t(&c->active, (size_t)plan->P));
     PS_TRY(c->pool.alloc_t(&c->count, 1));
@@ -940,7 +963,7 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         GroupNormArgs ga = gn_args(in, w.gn_g[ci], w.gn_b[ci]);
         GemmArgs g = base_gemm(cache->apad, C, C, C, w.w[ci], w.b[ci]);
         g.conv = 1; g.taps = 9; g.res = res; g.ldr = C;
-        g.a_pieces = push && gemm_takes_pieces(g, dt, mode);
+        g.a_pieces = push && cache->apad_pieces && gemm_takes_pieces(g, dt, mode);
         bool whole = false;
         if (have_partials) { ProfScope ps("gn_finalize", st); PS_TRY(gn_finalize(ga, gm, dt, plan->S / 64, st)); }
         else if (in_stats && in == x) {             // the block input: its moments came with the split
@@ -1080,7 +1103,7 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         return g;
     };
     // whether the layer that reads the attention's output takes it in pieces (the plain kernel does not write them)
-    auto attn_pieces = [&](const GemmArgs& g) { return C / d.heads % 4 == 0 && gemm_takes_pieces(g, dt, mode); };
+    auto attn_pieces = [&](const GemmArgs& g) { return cache->o_pieces && C / d.heads % 4 == 0 && gemm_takes_pieces(g, dt, mode); };
     // the projection of stage si as seen from the main stream: wait for the side stream, or run it here
     auto temb_ready = [&](const StageWeights&, int si, int) -> int {
         if (cache->side_temb) { PS_CHECK_HIP(hipStreamWaitEvent(st, cache->ev_temb[si], 0)); return PSERVE_OK; }
@@ -1118,7 +1141,7 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
             const bool ln = d.stages[si] == PSERVE_LSATTN || ada;
             if (ada) PS_TRY(temb_ready(w, si, 3 * C));          // [shift | scale | gate] per request
             GemmArgs gq = qkv_args(cache->u, w.w[0], si, act);
-            gq.a_pieces = gemm_takes_pieces(gq, dt, mode);
+            gq.a_pieces = cache->u_pieces && gemm_takes_pieces(gq, dt, mode);
             const void* rin = cur;
             if (!ln && cache->with_slots && cur != cache->r[si]) {    // first stage: merge fresh input into the slot
                 ProfScope ps("reuse_copy", st);
@@ -1264,8 +1287,8 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
             GemmArgs g1 = base_gemm(cache->u, C, C, F, w.w[0], w.b[0]), g2 = base_gemm(cache->hidden, F, F, C, w.w[1], w.b[1]);
             g1.act_gelu = 1;
             g1.seg[0].ptr = cache->hidden; g1.seg[0].ld = F;
-            g1.a_pieces = gemm_takes_pieces(g1, dt, mode);
-            g1.out_pieces = g2.a_pieces = g1.a_pieces && gemm_takes_pieces(g2, dt, mode);
+            g1.a_pieces = cache->u_pieces && gemm_takes_pieces(g1, dt, mode);
+            g1.out_pieces = g2.a_pieces = g1.a_pieces && cache->hidden_pieces && gemm_takes_pieces(g2, dt, mode);
             { ProfScope ps("layer_norm", st);
               PS_TRY(layer_norm(cur, nullptr, nullptr, cache->temb_e[si], 3 * C, owner, C, d.eps, gm, dt, cache->u, act, st, nullptr, nullptr,
                                 g1.a_pieces)); }
@@ -1284,7 +1307,7 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
             GemmArgs gq = base_gemm(ln ? cache->u : cur, C, C, C, w.w[0], nullptr);
             gq.seg[0].ptr = cache->q; gq.seg[0].ld = C; gq.seg[0].scale = qscale;
             if (ln) {
-                gq.a_pieces = gemm_takes_pieces(gq, dt, mode);
+                gq.a_pieces = cache->u_pieces && gemm_takes_pieces(gq, dt, mode);
                 ProfScope ps("layer_norm", st);
                 PS_TRY(layer_norm(cur, w.gn_g[0], w.gn_b[0], nullptr, 0, nullptr, C, d.eps, gm, dt, cache->u, act, st, nullptr, nullptr, gq.a_pieces));
             }
@@ -1305,8 +1328,8 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
             g1.epi = EPI_GEGLU;
             g1.seg[0].ptr = cache->hidden; g1.seg[0].ld = F;
             if (ln) {
-                g1.a_pieces = gemm_takes_pieces(g1, dt, mode);
-                g1.out_pieces = g2.a_pieces = g1.a_pieces && gemm_takes_pieces(g2, dt, mode);
+                g1.a_pieces = cache->u_pieces && gemm_takes_pieces(g1, dt, mode);
+                g1.out_pieces = g2.a_pieces = g1.a_pieces && cache->hidden_pieces && gemm_takes_pieces(g2, dt, mode);
                 ProfScope ps("layer_norm", st);
                 PS_TRY(layer_norm(cur, w.gn_g[0], w.gn_b[0], nullptr, 0, nullptr, C, d.eps, gm, dt, cache->u, act, st, nullptr, nullptr, g1.a_pieces));
             }

@@ -616,7 +616,9 @@ gemm_split_kernel(GemmArgs a, const uint16_t* __restrict__ Bs) {
 // Packed fp32 weights [rows][K] are followed, on the next 256-byte boundary, by their pieces (K a multiple of 32).
 static size_t split_offset(int64_t rows, int K) { return (rows * K * sizeof(float) + 255) / 256 * 256; }
 size_t packed_weight_bytes(int64_t rows, int32_t K, int dtype) {
-    return dtype == PSERVE_BF16 ? (size_t)rows * K * 2 : split_offset(rows, K) + (size_t)rows * 3 * K * 2;
+    if (dtype == PSERVE_BF16) return (size_t)rows * K * 2;
+    const bool pieces = K % 32 == 0 && rows * K * 6 < (int64_t)1 << 31;          // (as split_select: else nothing reads them)
+    return pieces ? split_offset(rows, K) + (size_t)rows * 3 * K * 2 : (size_t)rows * K * 4;
 }
 __global__ void split_packed_kernel(const float* __restrict__ w, uint16_t* __restrict__ dst, int64_t rows, int32_t K) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -628,7 +630,7 @@ __global__ void split_packed_kernel(const float* __restrict__ w, uint16_t* __res
     for (int pl = 0; pl < 3; ++pl) dst[r * 3 * K + piece_index((int)(i - r * K)) + 32 * pl] = (uint16_t)u[pl];
 }
 int split_packed(void* packed, int64_t rows, int32_t K, int dtype, hipStream_t st) {
-    if (dtype == PSERVE_BF16 || K % 32 != 0) return PSERVE_OK;
+    if (packed_weight_bytes(rows, K, dtype) == dtype_size(dtype) * rows * K) return PSERVE_OK;
     split_packed_kernel<<<(unsigned)cdiv(rows * K, 256), 256, 0, st>>>((const float*)packed, (uint16_t*)((char*)packed + split_offset(rows, K)), rows, K);
     return check_launch("split_packed_kernel");
 }

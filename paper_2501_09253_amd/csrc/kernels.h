@@ -213,8 +213,9 @@ size_t conv_split_bytes(const PatchGeom& g, int32_t M, int32_t N, int32_t K, int
 bool gemm_emits_stats(const GemmArgs& a, int dtype, int mode);
 int gemm(const GemmArgs& a, int dtype, int mode, hipStream_t st);
 
-// Weight packing into [taps][N][K] (K contiguous); all on device.  A block's fp32 weights (rows = taps x N) are followed by
-// their bf16 pieces: packed_weight_bytes is the size of both, split_packed fills in the pieces once all rows are packed.
+// Weight packing into [taps][N][K] (K contiguous); all on device.  fp32 weights (rows = taps x N) of a layer that may take its
+// activations in pieces are followed by their own: packed_weight_bytes is the size of both (of the weights alone where no kernel
+// reads pieces of them), split_packed fills in the pieces once all rows are packed.
 size_t packed_weight_bytes(int64_t rows, int32_t K, int dtype);
 int split_packed(void* packed, int64_t rows, int32_t K, int dtype, hipStream_t st);
 int pack_conv(const void* w, void* dst, int32_t Cout, int32_t Cin, int dtype, hipStream_t st);

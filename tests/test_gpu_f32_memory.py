@@ -1,0 +1,80 @@
+"""GPU: fp32 blocks and their activation stores hold bf16 pieces (6 bytes a value beside or instead of 4) only where a kernel reads them."""
+import numpy as np
+import pytest
+
+import paper_2501_09253_amd as ps
+import workloads as wl
+
+torch = pytest.importorskip("torch")
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(), reason="no GPU")]
+
+from harness import GpuRun, rel_err                      # noqa: E402
+
+
+def _used():
+    torch.cuda.synchronize()
+    return -torch.cuda.mem_get_info()[0]
+
+
+def _sizes(stage, C, res, patch, **k):
+    """Bytes of the weights, device memory of a block and of its activation store."""
+    cfg = wl.custom_config(res, patch, C=C, G=8, heads=next(h for h in range(1, C) if C % h == 0 and C // h <= 128), stages=(stage,), dtype="f32", seed=3, **k)
+    shapes = wl.stage_param_shapes(stage, cfg)
+    params = {n: torch.zeros(s, device="cuda") for n, (s, _) in shapes.items()}
+    plan = ps.Plan(cfg.resolutions, *cfg.patch, text_len=cfg.ctx_len if stage == "MMDIT" else 0)
+    ps.lib()                                            # (the library's own one-time allocations come before)
+    _warm()
+    a = _used()
+    block = ps.Block(cfg.stages, [params], C_=C, G=8, heads=cfg.heads, dtype=ps.F32, eps=cfg.eps, ctx_len=cfg.ctx_len,
+                     ctx_dim=cfg.ctx_dim, ffn_mult=cfg.ffn_mult, temb_dim=cfg.temb_dim)
+    b = _used()
+    cache = ps.Cache(plan, block, False)
+    c = _used()
+    weights = sum(t.numel() for t in params.values()) * 4
+    del cache, block
+    return weights, b - a, c - b, plan.T
+
+
+def _warm():
+    cfg = wl.custom_config([(8, 8)], (8, 8), C=64, G=8, heads=1, stages=("FFN",), dtype="f32", seed=1)
+    GpuRun(wl.make_workload(cfg)).forward()
+
+
+# slack: every allocation is rounded up to 2 MiB, a block has up to 20 and an activation store up to 12
+SLACK = 40 << 20
+
+
+@pytest.mark.parametrize("stage,C,k", [("MMDIT", 1280, dict(ctx_len=16, ctx_dim=1280, temb_dim=8)), ("FFN", 1920, {}), ("LFFN", 1936, {}),
+                                       ("LSATTN", 2888, {})])
+def test_weights_that_nothing_reads_in_pieces(stage, C, k):
+    weights, block, _, _ = _sizes(stage, C, [(4, 4)], (2, 2), **k)
+    assert weights > 100 << 20 and block < weights + SLACK
+
+
+def test_weights_in_pieces():
+    weights, block, _, _ = _sizes("LFFN", 1920, [(4, 4)], (2, 2))
+    assert 2.4 * weights < block < 2.5 * weights + SLACK
+
+
+# tokens times channels of the buffers of each stage: two stage outputs and what the stage itself needs
+@pytest.mark.parametrize("stage,C,n", [("FFN", 64, 2 + 4), ("LFFN", 80, 2 + 1 + 4), ("RES1", 24, 2 + 100 / 64)])
+def test_activations_that_nothing_reads_in_pieces(stage, C, n):
+    _, _, cache, T = _sizes(stage, C, [(512, 512)] * 4, (8, 8))
+    assert cache < n * T * C * 4 + SLACK
+
+
+@pytest.mark.parametrize("create,run", [(1, 0), (0, 1), (2, 0)])
+def test_kernel_mode_set_between(create, run):
+    """A store made in one kernel mode serves calls in the other."""
+    cfg = wl.custom_config([(40, 44), (8, 4)], (8, 4), C=320, G=8, heads=10, stages=("RES2", "LSATTN", "LFFN"), dtype="f32", seed=5)
+    w = wl.make_workload(cfg)
+    want = GpuRun(w).forward_images()
+    try:
+        ps.set_kernel_mode(create)
+        r = GpuRun(w)
+        ps.set_kernel_mode(run)
+        got = r.forward_images()
+    finally:
+        ps.set_kernel_mode(0)
+    err = rel_err(got, want)
+    assert np.isfinite(err) and err < 2e-6, err          # twice the bar of one kernel against the oracle
