@@ -8,6 +8,7 @@
 #include "common.h"
 
 #include <algorithm>
+#include <mutex>
 #include <numeric>
 #include <string.h>
 
@@ -98,21 +99,61 @@ plan_patches_kernel(int32_t* __restrict__ dev, int32_t* __restrict__ host, PlanL
     }
 }
 
-// Pinned host memory of the calling thread that a plan's tables pass through: in use only inside one pserve_plan call,
-// which waits for its kernel before it returns, and given back when the thread ends.  A plan of its own pinned memory
-// instead would cost an allocation that takes longer than the whole call.
+// Pinned host buffers that plans' tables pass through (allocating one takes longer than a whole pserve_plan call).  A buffer is in
+// use only inside one call, which waits for its kernel before it returns, and serves any thread: as many as plan at once, four at most
+// (a fifth call copies); when the last plan is freed all but one are given back.  Coherent memory: the kernel's reads and
+// writes go to the host and not to a cache, so a buffer that the next call fills anew is never stale; what the kernel
+// wrote is there when the wait for it returns.
+constexpr int PLAN_STAGES = 4;
+static struct {
+    std::mutex m;
+    int32_t* idle[PLAN_STAGES];
+    int n_idle, total, plans;
+} g_stages;
 struct PlanStage {
     int32_t* p = nullptr;
-    ~PlanStage() { if (p) (void)hipHostFree(p); }
-    int32_t* get() {
-        if (!p && hipHostMalloc((void**)&p, PLAN_STAGE_BYTES, hipHostMallocPortable) != hipSuccess) {
-            (void)hipGetLastError();
-            p = nullptr;
+    bool done = false;                          // the call's kernel has ended: another call may have the buffer
+    void get() {
+        {
+            std::lock_guard<std::mutex> lock(g_stages.m);
+            if (g_stages.n_idle) { p = g_stages.idle[--g_stages.n_idle]; return; }
+            if (g_stages.total == PLAN_STAGES) return;
+            ++g_stages.total;
         }
-        return p;
+        if (hipHostMalloc((void**)&p, PLAN_STAGE_BYTES, hipHostMallocPortable | hipHostMallocCoherent) == hipSuccess) return;
+        (void)hipGetLastError();
+        p = nullptr;
+        std::lock_guard<std::mutex> lock(g_stages.m);
+        --g_stages.total;
+    }
+    ~PlanStage() {
+        if (!p) return;
+        if (done) {
+            std::lock_guard<std::mutex> lock(g_stages.m);
+            g_stages.idle[g_stages.n_idle++] = p;
+            return;
+        }
+        (void)hipHostFree(p);
+        std::lock_guard<std::mutex> lock(g_stages.m);
+        --g_stages.total;
     }
 };
-static thread_local PlanStage g_plan_stage;
+static void plans_changed(int by) {
+    int32_t* back[PLAN_STAGES];
+    int n = 0;
+    {
+        std::lock_guard<std::mutex> lock(g_stages.m);
+        g_stages.plans += by;
+        if (g_stages.plans == 0)
+            while (g_stages.n_idle > 1) { back[n++] = g_stages.idle[--g_stages.n_idle]; --g_stages.total; }
+    }
+    while (n) (void)hipHostFree(back[--n]);
+}
+// For tests (host only, no part of the ABI): pinned buffers that exist.
+extern "C" int pserve_test_plan_stages() {
+    std::lock_guard<std::mutex> lock(g_stages.m);
+    return g_stages.total;
+}
 
 // ---- split / reassemble -------------------------------------------------------------------
 constexpr int IMG_CHUNK = 32;
@@ -500,12 +541,14 @@ static int plan_text_impl(const int32_t* res, int32_t n, int32_t ph, int32_t pw,
     const PlanLayout lay = {at[PSERVE_TAB_REQUEST_OFFSET], at[PSERVE_TAB_PATCH_OWNER], at[PSERVE_TAB_PATCH_RC],
                             at[PSERVE_TAB_NEIGHBOUR], at[PSERVE_TAB_HALO_SRC], total};
     hipStream_t st = (hipStream_t)stream;
-    int32_t* stage = n <= PLAN_REQ && total * sizeof(int32_t) <= PLAN_STAGE_BYTES ? g_plan_stage.get() : nullptr;
-    if (stage) {
+    PlanStage ps;
+    if (n <= PLAN_REQ && total * sizeof(int32_t) <= PLAN_STAGE_BYTES) ps.get();
+    if (int32_t* stage = ps.p) {
         memcpy(stage, hw, sizeof(int32_t) * per_request);
         plan_patches_kernel<true><<<(unsigned)cdiv(total, 256), 256, 0, st>>>(dev, stage, lay, n, (int32_t)P, ph, pw, ring);
         PS_TRY(check_launch("plan_patches_kernel"));
         PS_CHECK_HIP(hipStreamSynchronize(st));
+        ps.done = true;
         memcpy(hw + per_request, stage + per_request, sizeof(int32_t) * (total - per_request));
     } else {
         PS_CHECK_HIP(hipMemcpyAsync(dev, hw, sizeof(int32_t) * per_request, hipMemcpyHostToDevice, st));
@@ -518,6 +561,7 @@ static int plan_text_impl(const int32_t* res, int32_t n, int32_t ph, int32_t pw,
     }
     guard.p = nullptr;
     *out = pl;
+    plans_changed(1);
     return PSERVE_OK;
 }
 
@@ -526,7 +570,11 @@ int pserve_plan_text(const int32_t* res, int32_t n, int32_t ph, int32_t pw, int3
     return guarded("pserve_plan_text", [&] { return plan_text_impl(res, n, ph, pw, text_len, stream, out); });
 }
 
-void pserve_plan_free(pserve_plan_t* plan) { delete plan; }
+void pserve_plan_free(pserve_plan_t* plan) {
+    if (!plan) return;
+    delete plan;
+    plans_changed(-1);
+}
 
 int pserve_plan_info(const pserve_plan_t* plan, pserve_plan_info_t* out) {
     PS_REQUIRE(plan && out, "pserve_plan_info: NULL argument");

@@ -1,5 +1,6 @@
 """GPU: plan tables on both sides of the limits up to which they pass through pinned host memory (256 requests, 1 MiB of tables),
-host mirror and device copy against the oracle, whole numbers equal; also several threads on streams of their own."""
+host mirror and device copy against the oracle, whole numbers equal; also several threads on streams of their own, and the bound on
+the pinned buffers."""
 import threading
 
 import numpy as np
@@ -66,3 +67,34 @@ def test_threads():
     for t in threads:
         t.join()
     assert not failed, failed
+
+
+def test_pinned_buffers_are_bounded_and_given_back():
+    """Twelve threads that plan at once and live on hold four buffers between them at most, and one once no plan is left."""
+    import gc
+    gc.collect()
+    start, end, plans, failed = threading.Barrier(13), threading.Barrier(13), [], []
+
+    def work(k):
+        try:
+            start.wait(60)
+            for i in range(4):
+                plans.append(ps.Plan([(8, 8), (8 + 8 * k, 16)], 8, 8))
+        except BaseException as e:
+            failed.append(e)
+        end.wait(60)                                     # all threads still live here
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(12)]
+    for t in threads:
+        t.start()
+    start.wait(60)
+    end.wait(60)
+    for t in threads:
+        t.join()
+    assert not failed and len(plans) == 48 and 1 <= ps.lib().pserve_test_plan_stages() <= 4
+    for plan in plans:
+        want = op.plan_tables(plan.resolutions, 8, 8)
+        np.testing.assert_array_equal(plan.table("neighbour").reshape(-1), np.asarray(want["neighbour"]).reshape(-1))
+    del plans[:], plan
+    gc.collect()
+    assert ps.lib().pserve_test_plan_stages() <= 1
