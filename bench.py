@@ -65,6 +65,8 @@ def kernel_work(cfg, n_active_tokens, patch=None):
       attn_cross   4*L*C flops per token
       gn_stats     b*C bytes per token (one read); gn_finalize = the merge of partial moments alone (where the split pass or
                    the previous convolution left them behind): no tensor traffic
+      gn_whole     2*b*C bytes per token (statistics and application of a small batch in one launch: read + write);
+                   gn_whole_stitch: and b*C*ring per patch (rim writes)
       gn_apply     2*b*C bytes per computed token (read + write); gn_apply_stitch: computed tokens plus the border tokens of
                    reused patches, and b*C*ring per patch (rim writes)
       halo_gather  2*b*C*ring bytes per patch (read + write of the ring)
@@ -98,6 +100,8 @@ def kernel_work(cfg, n_active_tokens, patch=None):
         "attn_self": (attn, b * 4.0 * C * Ta),
         "attn_cross": (4.0 * cfg.ctx_len * C * Ta, b * 2.0 * C * Ta),
         "gn_stats": (0.0, 1.0 * b * C * T),
+        "gn_whole": (0.0, 2.0 * b * C * T),
+        "gn_whole_stitch": (0.0, 2.0 * b * C * T + 1.0 * b * C * ring * P),
         "gn_apply": (0.0, 2.0 * b * C * Ta),
         "gn_apply_stitch": (0.0, 2.0 * b * C * (Ta + (P - Pa) * border) + 1.0 * b * C * ring * P),
         "halo_gather": (0.0, 2.0 * b * C * ring * Pa),

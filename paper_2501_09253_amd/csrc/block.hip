@@ -972,11 +972,12 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
             ProfScope ps("gn_finalize", st);
             PS_TRY(gn_finalize(gi, gm, dt, cache->in_nch, st, /*per_channel=*/true));
         }
-        else {
-            ProfScope ps("gn_stats", st);
-            if (push && !reuse_mask && !g.a_pieces) PS_TRY(gn_whole(ga, gm, dt, /*conv=*/true, cache->apad, st, &whole));
-            if (!whole) PS_TRY(gn_stats(ga, gm, dt, st));
+        else if (push && !reuse_mask && !g.a_pieces && gn_takes_whole(ga, gm, dt, /*conv=*/true)) {
+            ProfScope ps("gn_whole_stitch", st);
+            PS_TRY(gn_whole(ga, gm, dt, /*conv=*/true, cache->apad, st));
+            whole = true;
         }
+        else { ProfScope ps("gn_stats", st); PS_TRY(gn_stats(ga, gm, dt, st)); }
         have_partials = false;
         // reused patches are not convolved: of them only the border tokens are normalised (the neighbours' rings)
         ga.rim_only = reuse_mask;
@@ -1162,11 +1163,11 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
                     gi.partial = cache->in_partial;
                     ProfScope ps("gn_finalize", st);
                     PS_TRY(gn_finalize(gi, gm, dt, cache->in_nch, st, /*per_channel=*/true));
-                } else {
-                    ProfScope ps("gn_stats", st);
-                    if (push && !act.active && !gq.a_pieces) PS_TRY(gn_whole(ga, gm, dt, /*conv=*/false, cache->u, st, &whole));
-                    if (!whole) PS_TRY(gn_stats(ga, gm, dt, st));
-                }
+                } else if (push && !act.active && !gq.a_pieces && gn_takes_whole(ga, gm, dt, /*conv=*/false)) {
+                    ProfScope ps("gn_whole", st);
+                    PS_TRY(gn_whole(ga, gm, dt, /*conv=*/false, cache->u, st));
+                    whole = true;
+                } else { ProfScope ps("gn_stats", st); PS_TRY(gn_stats(ga, gm, dt, st)); }
                 if (!whole) { ProfScope ps("gn_apply", st); PS_TRY(gn_apply(ga, gm, dt, false, false, false, cache->u, act, st, gq.a_pieces)); }
             }
             { ProfScope ps("linear_qkv", st); PS_TRY(gemm(gq, dt, mode, st)); }

@@ -100,9 +100,10 @@ struct GroupNormArgs {
     const uint8_t* rim_only = nullptr;   // [P] or nullptr; apply pass into the padded layout: only the border tokens of these patches
 };
 int gn_stats(const GroupNormArgs& a, const PatchGeom& g, int dtype, hipStream_t st);
-// statistics and application of a small batch in one launch: conv: SiLU into the padded buffer with the rims, else plain rows.
-// *done = false where it does not apply (nothing is written then); all patches, no pieces
-int gn_whole(const GroupNormArgs& a, const PatchGeom& g, int dtype, bool conv, void* out, hipStream_t st, bool* done);
+// statistics and application of a small batch (gn_takes_whole) in one launch: conv: SiLU into the padded buffer with the rims,
+// else plain rows; all patches, no pieces
+bool gn_takes_whole(const GroupNormArgs& a, const PatchGeom& g, int dtype, bool conv);
+int gn_whole(const GroupNormArgs& a, const PatchGeom& g, int dtype, bool conv, void* out, hipStream_t st);
 // second half of gn_stats alone: a.partial already holds [P][slots][G][2] partial sums (filled by a convolution)
 int gn_finalize(const GroupNormArgs& a, const PatchGeom& g, int dtype, int32_t slots, hipStream_t st, bool per_channel = false);
 // bf16 split that also leaves per-channel moments stats[P][nch][C][2] behind (plan.hip); *done = false where its

@@ -712,18 +712,19 @@ static int gn_whole(const GroupNormArgs& a, const PatchGeom& g, bool conv, void*
     return check_launch("gn_whole_kernel");
 }
 
-int gn_whole(const GroupNormArgs& a, const PatchGeom& g, int dtype, bool conv, void* out, hipStream_t st, bool* done) {
-    int CV, TL;
-    PS_TRY(norm_layout(a.C, dtype, &CV, &TL));
-    PS_REQUIRE(a.C % a.G == 0, "GroupNorm: C %% G != 0");
+bool gn_takes_whole(const GroupNormArgs& a, const PatchGeom& g, int dtype, bool conv) {
     // us, two launches -> one, bf16: 64 tokens 7 .. 10.5 -> 5.0 .. 5.6 into the padded buffer, 6.2 .. 9 -> 3.6 .. 5 plain (C = 64 .. 1280,
     // G = 32); 1,024 tokens 8.7 .. 12.8 -> 5.8 .. 9.9, 7.1 .. 11.4 -> 4.2 .. 8.1; 2,048 tokens 8.9 .. 14.9 -> 6.0 .. 12.4.  Past
     // that the pieces of C / G channels in which a block writes cost more than the launch, at rows of ten channels first:
     // 4,096 tokens C = 320 11.2 -> 13.2, C = 1280 17.9 -> 18.4, 12,288 15.5 -> 26.8; plain 10.1 -> 8.4, 13.6 -> 12.2, 13.0 -> 15.0.
     // A block of many elements reads them alone: G = 1, C = 128: 256 tokens (32,768) 10.6 -> 9.8, 512 11.2 -> 12.1, 1,024 13.6 -> 17.9.
-    *done = gn_takes_direct(a, g, dtype) && a.C / a.G <= GN_WHOLE_CG && (int64_t)a.max_tokens * (a.C / a.G) <= 40960 &&
-            (int64_t)g.P * g.S <= (conv ? 2048 : 4096);
-    if (!*done) return PSERVE_OK;
+    return gn_takes_direct(a, g, dtype) && a.C / a.G <= GN_WHOLE_CG && (int64_t)a.max_tokens * (a.C / a.G) <= 40960 &&
+           (int64_t)g.P * g.S <= (conv ? 2048 : 4096);
+}
+int gn_whole(const GroupNormArgs& a, const PatchGeom& g, int dtype, bool conv, void* out, hipStream_t st) {
+    int CV, TL;
+    PS_TRY(norm_layout(a.C, dtype, &CV, &TL));
+    PS_REQUIRE(a.C % a.G == 0, "GroupNorm: C %% G != 0");
     return dtype == PSERVE_BF16 ? gn_whole<uint16_t>(a, g, conv, out, st) : gn_whole<float>(a, g, conv, out, st);
 }
 

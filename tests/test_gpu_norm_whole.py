@@ -41,3 +41,18 @@ def test_same_as_two_launches(res, patch, C, G, dtype):
     b = run.forward_images(reuse=[np.zeros((h // patch[0], v // patch[1]), dtype=bool) for h, v in res])
     for x, y in zip(a, b):
         np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("big", [False, True])
+def test_profile_labels(big):
+    """The one-launch form has labels of its own: they stand for a read and a write, gn_stats for one read."""
+    cfg = wl.custom_config([(64, 64)] if big else [(16, 16)], (8, 8), C=64, G=8, heads=1, stages=("RES1", "SATTN"), dtype="f32", seed=77)
+    run = GpuRun(wl.make_workload(cfg))
+    run.forward()
+    ps.profile_enable(True)
+    try:
+        run.forward()
+        labels = {k for k in ps.profile_read() if k.startswith("gn_")}
+    finally:
+        ps.profile_enable(False)
+    assert labels == ({"gn_stats", "gn_apply_stitch", "gn_apply"} if big else {"gn_whole_stitch", "gn_whole"})
