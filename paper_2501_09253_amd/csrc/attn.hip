@@ -344,11 +344,27 @@ static int attn_f32mma_launch(const AttnArgs& a, hipStream_t st) {
 
 template <typename T>
 static int attn_f32mma(const AttnArgs& a, hipStream_t st) {
-    if constexpr (sizeof(T) == 2)                       // the transposed layout: bf16, 64 channels a head, rows past 32-bit offsets
+    if constexpr (sizeof(T) == 2)                       // the transposed layout: bf16, 64 channels a head, rows of 2^25 values and more
         if (a.v_transposed) return attn_f32mma_launch<T, 64, true, true>(a, st);
 #define PS_AF(DD) (a.d == DD ? attn_f32mma_launch<T, DD, false, true>(a, st) : attn_f32mma_launch<T, DD, false, false>(a, st))
     return a.d <= 32 ? PS_AF(32) : a.d <= 64 ? PS_AF(64) : PS_AF(128);
 #undef PS_AF
+}
+
+// For tests (no part of the ABI): self-attention of all tokens of a plan with the transposed bf16 layout on the fp32 matrix
+// cores, which a forward call takes from 2^25 tokens on.  Q pre-scaled, V [C][ldv]; tables: device, 2 (n + 1) int32.
+extern "C" int pserve_test_attn_transposed(const pserve_plan_t* plan, const void* Q, const void* K, const void* V, int64_t ldv, void* O,
+                                           int32_t C, int32_t* tables, void* stream) {
+    PS_REQUIRE(plan && Q && K && V && O && tables && C % 64 == 0 && ldv >= plan->T && plan->text_len == 0, "pserve_test_attn_transposed");
+    AttnArgs a{};
+    a.Q = Q; a.K = K; a.V = V; a.O = O; a.C = C; a.heads = C / 64; a.d = 64; a.v_transposed = true; a.ldv = ldv; a.n = plan->n;
+    a.geom = PatchGeom{plan->P, plan->S, plan->ph, plan->pw, plan->pw + 2, (plan->ph + 2) * (plan->pw + 2)};
+    a.act = ActiveList{nullptr, nullptr};
+    a.owner = plan->d_tab[PSERVE_TAB_PATCH_OWNER]; a.perm = plan->d_tab[PSERVE_TAB_PERM]; a.cu_seqlens = plan->d_tab[PSERVE_TAB_CU_SEQLENS];
+    a.act_off = tables; a.tile_off = tables + plan->n + 1; a.qt = 1; a.max_tiles = attention_max_tiles(plan, 1);
+    a.max_rows = plan->max_tokens_per_image;
+    PS_TRY(attention_tiles(plan->d_tab[PSERVE_TAB_REQUEST_OFFSET], nullptr, plan->n, plan->S, 1, tables, tables + plan->n + 1, (hipStream_t)stream));
+    return attn_f32mma<uint16_t>(a, (hipStream_t)stream);
 }
 
 // ---- fp32 self-attention on the bf16 matrix cores ---------------------------------------------------------

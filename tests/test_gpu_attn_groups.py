@@ -44,7 +44,9 @@ def test_with_reuse(res, patch, C):
     _check(wl.custom_config(res, patch, C=C, G=8, heads=C // 64, stages=("LSATTN",), dtype="bf16", reuse_p=0.5, seed=43))
 
 
-@pytest.mark.parametrize("res,patch,L", [([(6, 6), (18, 24)], (6, 6), 77), ([(10, 10), (30, 20)], (10, 10), 5)])
+# (slots that start at multiples of eight; of 3 x 3 and 5 x 5 patches at others, with and without room behind the last key)
+@pytest.mark.parametrize("res,patch,L", [([(6, 6), (18, 24)], (6, 6), 77), ([(10, 10), (30, 20)], (10, 10), 5), ([(3, 3), (9, 12), (3, 6), (33, 36)], (3, 3), 5),
+                                         ([(3, 3), (6, 9), (12, 12)], (3, 3), 27), ([(5, 5), (15, 20), (35, 40)], (5, 5), 33)])
 def test_ragged_joint_requests(res, patch, L):
     cfg = wl.custom_config(res, patch, C=128, G=8, heads=2, stages=("MMDIT",), dtype="bf16", ctx_len=L, ctx_dim=128, temb_dim=32, seed=47)
     w = wl.make_workload(cfg)
@@ -139,3 +141,26 @@ def test_groups_without_a_finite_score(res, patch, C, tile, all_tiles):
         assert np.isfinite(b).all()
         err = rel_err([a], [b])
         assert np.isfinite(err) and err < tolerance("bf16"), err
+
+
+# a request of patches of nine tokens starts at 9, 27, 108, ..: its first and last 16-byte pieces of the values hold others' too
+@pytest.mark.parametrize("C,res", [(64, [(3, 3), (3, 6), (9, 9), (9, 12), (33, 36)]), (640, [(3, 3), (3, 6), (9, 9), (33, 36), (36, 36)])])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_ragged_neighbours_that_are_not_finite(C, res, value):
+    cfg = wl.custom_config(res, (3, 3), C=C, G=8, heads=C // 64, stages=("LSATTN",), dtype="bf16", reuse_p=0.5, seed=101)
+    w = wl.make_workload(cfg)
+    for i, (r, k, v) in enumerate(zip(w.reuse, w.cache["0.K"], w.cache["0.V"])):
+        r[:] = False
+        if i % 2 == 1:                                  # sizes rise, so the slots are in this order: every other one
+            r[0, 0] = r[-1, -1] = True
+            v[:, 0, 0] = v[:, -1, -1] = value
+            k[3, 0, 0] = k[3, -1, -1] = value
+    run = GpuRun(w)
+    assert any(int(s) % 8 for s in run.plan.table("cu_seqlens"))
+    run.load_cache()
+    got = run.forward_images(reuse=w.reuse)
+    for i, (a, im) in enumerate(zip(got, w.images)):
+        if i % 2 == 0:
+            ref, _ = ob.forward_batch([im], cfg.stages, w.params, G=cfg.G, heads=cfg.heads, eps=cfg.eps)
+            err = rel_err([a], ref)
+            assert np.isfinite(err) and err < tolerance("bf16"), err

@@ -5,6 +5,7 @@ parity tests (1e-4 and 2e-2 of the largest value)."""
 import numpy as np
 import pytest
 
+import paper_2501_09253_amd as ps
 import workloads as wl
 from oracle import block as ob
 
@@ -46,7 +47,7 @@ def test_attention_tiles(res, patch, L, d, dtype):
                             ctx_dim=24, seed=9))
 
 
-# cached patches: compacted query rows, all keys (patches of 36 tokens: bf16 takes this kernel with transposed values)
+# cached patches: compacted query rows, all keys (patches of 36 tokens; bf16 heads of 64 channels take the bf16 kernel)
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_attention_with_reuse(dtype):
     _check(wl.custom_config([(24, 18), (6, 12)], (6, 6), C=128, G=8, heads=2, stages=("RES2", "SATTN"), dtype=dtype,
@@ -54,7 +55,7 @@ def test_attention_with_reuse(dtype):
 
 
 # an infinite cached value in the last key of a request (72 and 108 keys: the last tile is ragged) gives infinities where its
-# probability times weight does, and no NaN.  36-token patches of 64-wide bf16 heads: the transposed layout.
+# probability times weight does, and no NaN.  64-wide bf16 heads: the bf16 kernel and its transposed values.
 @pytest.mark.parametrize("dtype,heads", [("f32", 2), ("bf16", 2), ("bf16", 1)])
 def test_attention_infinite_last_value(dtype, heads):
     cfg = wl.custom_config([(6, 12), (18, 6)], (6, 6), C=64, G=8, heads=heads, stages=("LSATTN",), dtype=dtype, reuse_p=0.5, seed=37)
@@ -134,3 +135,35 @@ def test_layer_norm_widths(C, stage, dtype):
 def test_modulation_of_many_slots(n, dtype):
     _check(wl.custom_config([(2, 2), (2, 4), (4, 2), (2, 2), (6, 2)][:n], (2, 2), C=696, G=1, heads=1, stages=("AMLP",), dtype=dtype,
                             seed=29, ffn_mult=8, temb_dim=83))
+
+
+# The transposed bf16 layout, which forward calls of 2^25 tokens and more take: requests that start anywhere in a vector of four, one
+# to many key tiles; an infinite value in a neighbour.  Values and probabilities in fp32, the result rounded to bf16: 2^-8 of the
+# largest, and the sums' roundings beside it.
+@pytest.mark.parametrize("res,patch,C", [([(1, 1)], (1, 1), 64), ([(3, 3), (3, 6), (9, 9), (15, 18)], (3, 3), 128), ([(8, 8), (24, 24)], (8, 8), 64)])
+def test_attention_transposed_values(res, patch, C):
+    import ctypes
+    plan = ps.Plan(res, *patch)
+    T, gen, h = plan.T, torch.Generator().manual_seed(3), C // 64
+    q, k, v = (torch.randn((T, C), generator=gen).to(torch.bfloat16) for _ in range(3))
+    cu = plan.table("cu_seqlens").tolist()
+    if len(cu) > 2:
+        v[cu[1] - 1, 5] = v[cu[2] if len(cu) > 3 else cu[1] - 1, 7] = float("inf")      # last value of slot 0, first of slot 2
+    ldv = (T + 7) // 8 * 8
+    vt = torch.full((C, ldv), float("nan"), dtype=torch.bfloat16)
+    vt[:, :T] = v.t()
+    dq, dk, dv, o, tab = q.cuda(), k.cuda(), vt.cuda(), torch.zeros((T, C), dtype=torch.bfloat16, device="cuda"), \
+        torch.zeros(2 * (plan.n + 1), dtype=torch.int32, device="cuda")
+    rc = ps.lib().pserve_test_attn_transposed(plan._h, ctypes.c_void_p(dq.data_ptr()), ctypes.c_void_p(dk.data_ptr()),
+                                              ctypes.c_void_p(dv.data_ptr()), ctypes.c_int64(ldv), ctypes.c_void_p(o.data_ptr()), C,
+                                              ctypes.c_void_p(tab.data_ptr()), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    got = o.cpu().double()
+    for a, b in zip(cu[:-1], cu[1:]):
+        for i in range(h):
+            c = slice(64 * i, 64 * i + 64)
+            p = torch.softmax(q[a:b, c].double() @ k[a:b, c].double().t() * np.log(2.0), dim=1)
+            ref = p @ v[a:b, c].double()
+            ok = torch.isfinite(ref)
+            assert torch.equal(torch.isinf(got[a:b, c]), torch.isinf(ref)) and not torch.isnan(got[a:b, c]).any()
+            assert (got[a:b, c][ok] - ref[ok]).abs().max() < 2.0 ** -8 * ref[ok].abs().max()

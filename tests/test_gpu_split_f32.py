@@ -218,3 +218,17 @@ def test_attention_infinite_value_of_a_small_probability(dtype, C, res, patch):
             continue                                    # (of a request of one cached patch nothing is computed)
         ph = patch[0]
         assert np.isposinf(a[3, ph:]).all()              # (the other outputs hold zero times it)
+
+
+def test_joint_attention_in_pieces():
+    """fp32 joint blocks large enough for the attention in pieces; the slots have room behind their last key (77 text tokens in
+    patches of 40)."""
+    cfg = wl.custom_config([(40, 45), (8, 10)], (8, 5), C=320, G=8, heads=10, stages=("MMDIT",), dtype="f32", ctx_len=77, ctx_dim=320,
+                           temb_dim=32, seed=91)
+    assert (-(-(40 * 45 + 80) // 128) + 2) * cfg.heads >= 128
+    w = wl.make_workload(cfg)
+    got = GpuRun(w).forward_images()
+    ref = [ob.mmdit(im, w.ctx[i], w.temb[i], w.params[0], cfg.heads, cfg.eps)[0] for i, im in enumerate(w.images)]
+    for a, b in zip(got, ref):
+        err = rel_err([a], [b])
+        assert np.isfinite(err) and err < 1e-6, err
