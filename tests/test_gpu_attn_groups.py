@@ -39,6 +39,17 @@ def test_groups_and_ragged_requests(res, patch, C):
     _check(wl.custom_config(res, patch, C=C, G=8, heads=C // 64, stages=("LSATTN",), dtype="bf16", seed=41))
 
 
+@pytest.mark.parametrize("res,patch,C", SHAPES)
+def test_same_twice(res, patch, C):
+    """Groups meet in a fixed order: bit for bit the same, also from another store."""
+    w = wl.make_workload(wl.custom_config(res, patch, C=C, G=8, heads=C // 64, stages=("LSATTN",), dtype="bf16", seed=42))
+    run = GpuRun(w)
+    first = run.forward_images()
+    for other in (run, run, GpuRun(w)):
+        for a, b in zip(first, other.forward_images()):
+            np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("res,patch,C", [SHAPES[0], SHAPES[4], SHAPES[5]])
 def test_with_reuse(res, patch, C):
     _check(wl.custom_config(res, patch, C=C, G=8, heads=C // 64, stages=("LSATTN",), dtype="bf16", reuse_p=0.5, seed=43))
