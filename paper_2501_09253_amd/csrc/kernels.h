@@ -40,7 +40,8 @@ __device__ __forceinline__ float hi_bf16(uint32_t u) { return __uint_as_float(u 
 // and x2 y2 are at most 2^-23.9 of it and zero in the mean (four million pairs: 2^-24.2, 1e-12).  Pieces cut off instead of
 // rounded lose up to 2^-21.0, always towards zero (2^-21.2, 4e-8).
 // A value that is not finite is (2^-126, 0, x) with x's sign: of the six products only those with the other factor's x0 then hold it,
-// which is zero or has the factor's sign, so infinities and NaN come out as those of the plain product.
+// which is zero or has the factor's sign, so infinities and NaN come out as those of the plain product.  (A finite product within
+// 1 % of the largest number may come out infinite: x0 y0 may be that much larger.)
 constexpr float PIECE_TINY = 1.17549435e-38f, PIECE_MAX = 3.38953139e38f;       // smallest normal, largest bf16 number
 __device__ __forceinline__ void cut3x2(float a, float b, uint32_t (&u)[3]) {
     if (fabsf(a) + fabsf(b) <= PIECE_MAX) {

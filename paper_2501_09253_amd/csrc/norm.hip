@@ -58,8 +58,8 @@ __device__ __forceinline__ void store_vec<uint16_t>(uint16_t* p, const float (&v
     *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// Output rows of the apply passes: the type's own values, or (fp32, PIECES) three bf16 pieces of each value, which sum to it
-// exactly (piece_index).  row: first element of the row, c: the vector's first channel.
+// Output rows of the apply passes: the type's own values, or (fp32, PIECES) three bf16 pieces of each value (cut3x2,
+// piece_index).  row: first element of the row, c: the vector's first channel.
 template <typename T, int V> struct __attribute__((aligned(V * sizeof(T)))) GnChunk { T e[V]; };
 template <typename T, bool PIECES, int N>
 __device__ __forceinline__ void store_out(T* out, int64_t row, int c, const float (&v)[N]) {
