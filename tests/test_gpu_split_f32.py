@@ -140,6 +140,23 @@ def test_small_values(exponent, bar):
     assert np.isfinite(err) and err < bar, err
 
 
+@pytest.mark.parametrize("value", [3.4028234e38, -3.395e38, 3.3895e38])
+def test_largest_values(value):
+    """A weight that would round to infinity as a bf16 number, times activations of 2^-10 and less: 2^-24 of each result and a few
+    roundings."""
+    cfg, w = _controlled("LFFN")
+    p = w.params[0]
+    p["ln_b"][:] = np.random.default_rng(5).standard_normal(cfg.C)
+    p["w1"][:, 6] *= 2.0 ** -10
+    p["w2"][:, 7] = 0
+    p["w2"][6, 7] = value
+    got = GpuRun(w).forward_images()
+    ref, _ = ob.forward_batch(w.images, cfg.stages, w.params, G=cfg.G, heads=cfg.heads, eps=cfg.eps)
+    for a, b in zip(got, ref):
+        assert np.isfinite(a).all() and (b[7] != 0).all()
+        assert np.abs(np.asarray(a[7], np.float64) / b[7] - 1).max() < 1e-5          # (one activation: GELU and its gate's own digits)
+
+
 # requests of one to sixty key tiles, the last one ragged; 130 and more blocks of 128 queries
 ATTN = {"d32": dict(res=[(40, 40), (8, 15), (8, 5)], patch=(8, 5), C=320, heads=10),
         "d64": dict(res=[(36, 36), (3, 6), (9, 33)], patch=(3, 3), C=640, heads=10),
