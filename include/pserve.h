@@ -193,7 +193,8 @@ int  pserve_split_stats(const pserve_plan_t* plan, const void* const* images, in
  * referenced after the call returns (it synchronises `stream`).  fp32 weights of convolutions,
  * self-attention, attention outputs and layers behind a LayerNorm (not those of joint blocks) take
  * 10 bytes a value where their input width is a multiple of 32 (three bf16 pieces beside the value,
- * for the matrix cores), all others 4, bf16 ones 2.
+ * for the matrix cores), all others 4, bf16 ones 2; where the device memory does not hold the pieces
+ * the block, or an activation store of it, is made without them.
  * Errors: EINVAL for unknown stage kinds, C % G, C % heads, XATTN without ctx sizes,
  * a NULL parameter; ENOMEM; EHIP. */
 int  pserve_block_create(const pserve_block_desc* desc, const pserve_block_params* params,

@@ -287,6 +287,7 @@ struct pserve_block_s {
     pserve_block_desc desc;
     StageWeights sw[PSERVE_MAX_STAGES];
     StageWeights sw_txt[PSERVE_MAX_STAGES];   // MMDIT: the text stream's weights (sw holds the image stream's)
+    bool pieces = false;                      // fp32: weights that may be read in bf16 pieces have them
     DevicePool pool;
 };
 
@@ -431,7 +432,7 @@ int pserve_profile_read(pserve_prof_entry* out, int32_t max, int32_t* count) {
     return guarded("pserve_profile_read", [&] { return profile_read_impl(out, max, count); });
 }
 
-static int block_create_impl(const pserve_block_desc* desc, const pserve_block_params* params, void* stream, pserve_block_t** out) {
+static int block_create_impl(const pserve_block_desc* desc, const pserve_block_params* params, void* stream, bool pieces, pserve_block_t** out) {
     PS_REQUIRE(out, "pserve_block_create: out is NULL");
     *out = nullptr;
     PS_REQUIRE(desc && params, "pserve_block_create: NULL argument");
@@ -464,6 +465,7 @@ static int block_create_impl(const pserve_block_desc* desc, const pserve_block_p
     if (!b) { set_error("pserve_block_create: out of host memory"); return PSERVE_ENOMEM; }
     struct Guard { pserve_block_t* p; ~Guard() { delete p; } } guard{b};
     b->desc = d;
+    b->pieces = pieces;
     hipStream_t st = (hipStream_t)stream;
     const size_t es = dtype_size(d.dtype);
     const int C = d.C;
@@ -471,7 +473,7 @@ static int block_create_impl(const pserve_block_desc* desc, const pserve_block_p
     std::vector<Packed> packed;                      // fp32 weights that get their bf16 pieces at the end
     // pieces: the layer may read its activations, and so its weights, in pieces (the forward pass sets a_pieces for it)
     auto weights = [&](void** dst, int64_t rows, int32_t K, bool pieces) -> int {
-        const size_t plain = es * rows * K, both = pieces ? packed_weight_bytes(rows, K, d.dtype) : plain;
+        const size_t plain = es * rows * K, both = pieces && b->pieces ? packed_weight_bytes(rows, K, d.dtype) : plain;
         PS_TRY(b->pool.alloc(dst, both));
         if (both != plain) packed.push_back({*dst, rows, K});
         return PSERVE_OK;
@@ -599,12 +601,21 @@ static int block_create_impl(const pserve_block_desc* desc, const pserve_block_p
 }
 
 int pserve_block_create(const pserve_block_desc* desc, const pserve_block_params* params, void* stream, pserve_block_t** out) {
-    return guarded("pserve_block_create", [&] { return block_create_impl(desc, params, stream, out); });
+    return guarded("pserve_block_create", [&] {
+        const int s = block_create_impl(desc, params, stream, /*pieces=*/true, out);
+        if (s != PSERVE_ENOMEM || desc->dtype != PSERVE_F32) return s;
+        return block_create_impl(desc, params, stream, /*pieces=*/false, out);      // no room for them: the fp32 kernels
+    });
+}
+
+// For tests (no part of the ABI): what pserve_block_create makes where there is no room for the pieces.
+int pserve_test_block_plain(const pserve_block_desc* desc, const pserve_block_params* params, void* stream, pserve_block_t** out) {
+    return guarded("pserve_test_block_plain", [&] { return block_create_impl(desc, params, stream, /*pieces=*/false, out); });
 }
 
 void pserve_block_free(pserve_block_t* block) { delete block; }
 
-static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* block, int with_slots, pserve_cache_t** out) {
+static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* block, int with_slots, bool pieces, pserve_cache_t** out) {
     PS_REQUIRE(out, "pserve_cache_create: out is NULL");
     *out = nullptr;
     PS_REQUIRE(plan && block, "pserve_cache_create: NULL argument");
@@ -636,7 +647,7 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
     const bool ffn = any_stage(d, is_ffn) || has_stage(d, PSERVE_AMLP) || joint;
     const bool gn_sattn = has_stage(d, PSERVE_SATTN);
     const PatchGeom g{plan->P, plan->S, plan->ph, plan->pw, plan->pw + 2, (plan->ph + 2) * (plan->pw + 2)};
-    if (d.dtype == PSERVE_F32) {            // which layers read their activations in pieces: those of the forward pass, by their sizes
+    if (d.dtype == PSERVE_F32 && pieces && block->pieces) {      // which layers read their activations in pieces: those of the forward pass, by their sizes
         auto takes = [&](int K, int N, int epi = EPI_ROUTE, int taps = 1) {
             GemmArgs a{};
             a.geom = g; a.tokens_are_rows = 1; a.M = (int32_t)plan->T; a.lda = a.K = K; a.N = N; a.epi = epi; a.taps = taps; a.conv = taps > 1;
@@ -712,7 +723,7 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
         c->att_qt = attention_max_tiles(plan, 2) * (int64_t)d.heads < 256 ? 1 : 2;
         c->max_tiles = attention_max_tiles(plan, c->att_qt);
         if (sattn)
-            if (const size_t bytes = attention_cut_bytes(plan, d.C, d.heads, d.dtype, g_kernel_mode == 1 ? 1 : 0))
+            if (const size_t bytes = !pieces ? 0 : attention_cut_bytes(plan, d.C, d.heads, d.dtype, g_kernel_mode == 1 ? 1 : 0))
                 PS_TRY(c->pool.alloc(&c->cut, bytes));
     }
     if (ffn) PS_TRY(c->pool.alloc(&c->hidden, (size_t)plan->T * d.ffn_mult * d.C * elem(c->hidden_pieces)));
@@ -766,7 +777,11 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
 }
 
 int pserve_cache_create(const pserve_plan_t* plan, const pserve_block_t* block, int with_slots, pserve_cache_t** out) {
-    return guarded("pserve_cache_create", [&] { return cache_create_impl(plan, block, with_slots, out); });
+    return guarded("pserve_cache_create", [&] {
+        const int s = cache_create_impl(plan, block, with_slots, /*pieces=*/true, out);
+        if (s != PSERVE_ENOMEM || block->desc.dtype != PSERVE_F32) return s;
+        return cache_create_impl(plan, block, with_slots, /*pieces=*/false, out);       // as for blocks
+    });
 }
 
 void pserve_cache_free(pserve_cache_t* cache) { delete cache; }

@@ -91,6 +91,7 @@ struct DevicePool {
         hipError_t e = hipMalloc(out, bytes);
         if (e != hipSuccess) {
             set_error("hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
+            (void)hipGetLastError();            // (else the next launch would report it)
             *out = nullptr;
             return PSERVE_ENOMEM;
         }

@@ -78,3 +78,17 @@ def test_kernel_mode_set_between(create, run):
         ps.set_kernel_mode(0)
     err = rel_err(got, want)
     assert np.isfinite(err) and err < 2e-6, err          # twice the bar of one kernel against the oracle
+
+
+def test_block_without_room_for_pieces(monkeypatch):
+    """What creation falls back to when the device memory does not hold the pieces: the plain weights, the fp32 kernels."""
+    cfg = wl.custom_config([(40, 44), (8, 4)], (8, 4), C=320, G=8, heads=10, stages=("RES2", "LSATTN", "LFFN"), dtype="f32", seed=5)
+    w = wl.make_workload(cfg)
+    want = GpuRun(w).forward_images()
+    plain = ps.lib().pserve_test_block_plain
+    plain.argtypes = ps.lib().pserve_block_create.argtypes
+    monkeypatch.setattr(ps.lib(), "pserve_block_create", plain)
+    run = GpuRun(w)
+    got = run.forward_images()
+    err = rel_err(got, want)
+    assert np.isfinite(err) and 0 < err < 2e-6, err      # (other kernels: not the same bits)
