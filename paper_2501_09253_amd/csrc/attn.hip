@@ -687,14 +687,21 @@ static int attn_split(const AttnArgs& a, hipStream_t st) {
 }
 
 // From 128 blocks of 128 queries on, where a request has 1,024 keys: below, the fp32 kernel's blocks of 32 queries with the keys
-// shared out to four wavefronts spread better.  us of an LSATTN layer, fp32 kernel / this: 4,096 + 3,072 tokens, 5 heads of 64
+// shared out to four wavefronts spread better.  With heads of 32 channels from 129 on: at 128 the fp32 kernel's 512 blocks run all at once
+// (4,096 tokens, 4 of 32 121 / 138, 16,384, 1 of 32 390 / 448, 4 x 1,024, 4 of 32 52 / 60; 4,096, 5 of 32 (160) 164 / 140; 136 blocks 159 / 135;
+// of 64 channels, 128 blocks: 212 / 207, 682 / 629, 89 / 90).  us of an LSATTN layer, fp32 kernel / this: 4,096 + 3,072 tokens, 5 heads of 64
 // (280 blocks) 460 / 309; 2 x 2,304, 5 of 32 (180) 117 / 102; 4,608, 10 of 32 (360) 391 / 282; 2,304, 5 of 64 (90) 138 / 133;
 // 4 x 576, 5 of 64 (100) 68 / 70; 4,096, 2 of 64 (64) 124 / 181; 16 x 256, 5 of 64 (160) 72 / 73.  Error of a layer
 // against 64 bits: 4,096 tokens 4.8e-8 / 3.4e-8, 4 x 1,024 4.7e-8 / 3.4e-8, 4,608 (10 heads) 4.9e-8 / 3.4e-8, 2 x 2,304 4.2e-8 / 3.5e-8.
 size_t attention_cut_bytes(const pserve_plan_t* plan, int32_t C, int32_t heads, int dtype, int mode) {
     if (dtype != PSERVE_F32 || mode != 0 || C % heads != 0 || (C / heads != 32 && C / heads != 64)) return 0;
-    if ((int64_t)attention_max_tiles(plan, 1) * heads < 128 || plan->max_tokens_per_image < 1024) return 0;
+    if ((int64_t)attention_max_tiles(plan, 1) * heads < (C / heads == 32 ? 129 : 128) || plan->max_tokens_per_image < 1024) return 0;
     return (size_t)(plan->T / 32 + plan->n) * C * 32 * 12;
+}
+
+// For tests (host only, no part of the ABI): whether the fp32 self-attention of a plan goes to the bf16 matrix cores
+extern "C" int pserve_test_attn_cut(const pserve_plan_t* plan, int32_t C, int32_t heads) {
+    return attention_cut_bytes(plan, C, heads, PSERVE_F32, 0) != 0;
 }
 
 int attention_mfma_bf16(const AttnArgs& a, hipStream_t st, bool* handled);     // attn_mfma.hip

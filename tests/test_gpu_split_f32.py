@@ -166,7 +166,7 @@ ATTN = {"d32": dict(res=[(40, 40), (8, 15), (8, 5)], patch=(8, 5), C=320, heads=
 def _attn(name, seed):
     c = dict(ATTN[name])
     cfg = wl.custom_config(c.pop("res"), c.pop("patch"), G=8, stages=("LSATTN",), dtype="f32", seed=seed, **c)
-    assert sum(-(-h * w // 128) for h, w in cfg.resolutions) * cfg.heads >= 128 and max(h * w for h, w in cfg.resolutions) >= 1024
+    assert sum(-(-h * w // 128) for h, w in cfg.resolutions) * cfg.heads > 128 and max(h * w for h, w in cfg.resolutions) >= 1024
     return cfg, wl.make_workload(cfg)
 
 
@@ -178,6 +178,14 @@ def _attn_run(cfg, w):
     with np.errstate(invalid="ignore"):
         ref, _ = ob.forward_batch(w.images, cfg.stages, w.params, G=cfg.G, heads=cfg.heads, eps=cfg.eps, reuse=w.reuse, cache=w.cache)
     return got, ref
+
+
+@pytest.mark.parametrize("res,d,heads,takes", [([(64, 64)], 32, 4, 0), ([(64, 64), (8, 8)], 32, 4, 1), ([(64, 64)], 32, 5, 1), ([(128, 128)], 32, 1, 0),
+                                               ([(64, 64)], 64, 4, 1), ([(64, 64)], 64, 3, 0), ([(24, 40)] * 16, 64, 4, 0), ([(32, 32)] * 4, 64, 4, 1)])
+def test_attention_that_takes_pieces(res, d, heads, takes):
+    """128 blocks of 128 queries and a request of 1,024 tokens; with heads of 32 channels one block more (both sides are in the rule's
+    comment)."""
+    assert ps.lib().pserve_test_attn_cut(ps.Plan(res, 8, 8)._h, d * heads, heads) == takes
 
 
 @pytest.mark.parametrize("name", list(ATTN))
