@@ -1073,10 +1073,11 @@ int attention_mfma_bf16(const AttnArgs& a, hipStream_t st, bool* handled) {
     // CUs would have no block.  us of an LSATTN layer, 128 queries x 1 group / 128 x 2 / 64 x 4 / 64 x 2: 40 items of 16 key
     // tiles 34.2 / 32.3 / 29.6 / 30.0; 64 of 64: 65.8 / 53.4 / 41.3 / 45.7; 40 of 4: 35.4 / 36.1 / 35.4 / 34.4; 80 of 4: 30.6 /
     // 31.4 / 30.7 / 29.9; 160 of 16: 51.3 / 49.2 / 55.0 / 50.0; 160 of 64: 74.2 / 61.8 / 73.4 / 65.9; 240 of 3 (text keys): 43.8 /
-    // 44.7 / 48.7 / 45.1; 320 of 16: 60.7 / 65.8 / 78.0 / 66.9.
+    // 44.7 / 48.7 / 45.1; 320 of 16: 60.7 / 65.8 / 78.0 / 66.9.  Not with one key tile, where there is
+    // nothing to share and the groups still meet: one request of 64 tokens, 64 .. 320 channels 19.1 .. 23.5 / 18.7 .. 22.9.
     const int64_t items = (int64_t)a.max_tiles * a.qt * a.heads;
     const int keys = a.cross_len ? a.cross_len : a.max_rows;
-    if (items <= 128) {
+    if (items <= 128 && keys > ATT_BKV) {
         if (keys >= 1024) PS_ATT(2, 4, 2);
         PS_ATT(2, 2, 2);
     }

@@ -13,12 +13,13 @@ pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(),
 
 from harness import GpuRun, rel_err, tolerance                      # noqa: E402
 
-# fewer key tiles than groups, one more, many; (64 queries x 4 groups), (64 x 2), (128 x 2), (128 x 1)
+# fewer key tiles than groups, one more, many; (64 queries x 4 groups), (64 x 2), (128 x 2), (128 x 1); at the end one key
+# tile, which takes one group
 SHAPES = [([(8, 8), (8, 16), (32, 40), (8, 24)], (8, 8), 64), ([(8, 8), (24, 24), (16, 8)], (8, 8), 128),
           ([(8, 8), (32, 32), (32, 32)], (8, 8), 640), ([(40, 40), (40, 48)], (8, 8), 640),
           ([(3, 3), (3, 6), (9, 9), (33, 36)], (3, 3), 64), ([(6, 6), (12, 18), (18, 6)], (6, 6), 128),
           ([(6, 6), (30, 36), (30, 30)], (6, 6), 640), ([(6, 6), (54, 66)], (6, 6), 640),
-          ([(5, 5), (5, 10), (25, 45)], (5, 5), 64)]
+          ([(5, 5), (5, 10), (25, 45)], (5, 5), 64), ([(8, 8), (4, 8), (4, 4)], (4, 4), 128), ([(7, 7), (7, 7)], (7, 7), 64)]
 
 
 def _check(cfg):
