@@ -278,20 +278,6 @@ template <int BM, int BN, int NS, bool OVERLAP> struct GemmCfg {
     static_assert(OVERLAP || NS * STAGE >= EPI, "epilogue staging does not fit the ring");
 };
 
-// Text rows stand L to a request and their outputs row_group_pad apart.  A transposed segment stores four tokens at once
-// where they lie aligned; with L = 77 and 80 only every fourth request's do, and the others' leave two bytes at a time.  The
-// tiles then walk the padded rows instead (those past L hold nothing): 39 -> 33 us for 22 x 77 x 2560, K = 2048; 16 requests
-// 30.7 -> 26.1, 10 29.1 -> 24.5, 4 19.8 -> 19.2; 4 x 77 x 1280, K = 768 13.5 -> 12.1, but 2 11.7 -> 12.1.  Not where the padding
-// would be more than an eighth of the rows, nor where L is a multiple of four or there are fewer than three requests.  A form of
-// its own (EPF_PADS): as a run-time choice in all forms it cost the small layers 2 to 10 % (1,024 x 1,280, K = 1,280 and 128 x 64
-// tiles 12.5 -> 13.0 .. 13.7 us).
-__host__ __device__ inline bool gemm_pads_rows(const GemmArgs& a) {
-    return !a.tokens_are_rows && a.epi == EPI_ROUTE && !a.rowbias && !a.rowscale && !a.act_gelu && a.row_group > 0 &&
-           a.M > 2 * a.row_group && a.row_group % 4 != 0 && a.row_group_pad % 4 == 0 && a.M % a.row_group == 0 &&
-           a.row_group_pad - a.row_group <= a.row_group / 8 && (a.seg[0].transposed || a.seg[1].transposed || a.seg[2].transposed);
-}
-__host__ __device__ inline int32_t gemm_rows(const GemmArgs& a) { return gemm_pads_rows(a) ? a.M / a.row_group * a.row_group_pad : a.M; }
-
 // Block tile BM x BN, WGM x WGN wavefront grid (four wavefronts), ring of NS stages.
 // Step = 64 columns of K: 4 sub-steps of TM*TN MFMAs.  Every memory instruction rides behind an MFMA: during sub-steps
 // 0..2 the fragment reads of the next sub-step, during sub-step 3 the first fragments of the NEXT step and the refill
@@ -1074,11 +1060,10 @@ static int conv_splits(int64_t tiles, int64_t kchunks) {
 }
 
 template <int BM, int BN, int WGM, int WGN, int APIX, int NSB, int KS = 1>
-static int launch_conv(const GemmArgs& a, const ConvTile& ct, hipStream_t st) {
+static int launch_conv(const GemmArgs& a, const ConvTile& ct, int splits, hipStream_t st) {
     constexpr size_t lds = (size_t)(NSB * BN + 2 * APIX) * 128 + BM * sizeof(int32_t) + 64 * sizeof(int32_t);
     static_assert(lds <= 160 * 1024, "conv LDS budget");
     const int64_t mt = cdiv(a.M, BM), nt = a.N / BN;
-    const int splits = conv_splits(mt * nt, a.K / 64);
     const int slab = split_slab(a.stats ? a.N / a.stats_G : 8);
     if (splits == 1 || !a.split_ws || a.split_ws_bytes < sizeof(float) * splits * mt * BM * a.N || slab == 0) {
         PS_SET_LDS_ONCE((conv_mfma_kernel<BM, BN, WGM, WGN, APIX, NSB, KS, false>), lds);
@@ -1181,11 +1166,41 @@ static int conv_select(const GemmArgs& a, ConvTile* ct, int* wave_cols = nullptr
     return sel;
 }
 
+int few_pick(const GemmArgs& a, int most_rounds, double* us);            // gemm_few.hip
+int gemm_few_bf16(const GemmArgs& a, int tile, hipStream_t st);
+
+static constexpr int CONV_BM[7] = {0, 256, 128, 128, 128, 128, 256}, CONV_BN[7] = {1, 160, 320, 256, 128, 64, 160};
+
+// How long the halo-in-LDS kernel `sel` takes, in us (a step is a tap of a 64-channel chunk; a shared tile's sums are written and
+// read back), and in how many shares of the channel chunks it does.  Fitted to 70 measured sizes; what it decides is between
+// this kernel's two forms and the small tiles of gemm_few.hip, and there it errs by less than a tenth.
+static double conv_time(const GemmArgs& a, int sel, int* splits) {
+    static const double step[7] = {0, 0.95, 0.95, 0.93, 0.6, 0.49, 0.95};
+    const int64_t tiles = cdiv(a.M, CONV_BM[sel]) * (a.N / CONV_BN[sel]), chunks = a.K / 64;
+    const int z = conv_splits(tiles, chunks);
+    const double whole = cdiv(tiles, 256) * (5.0 + 9 * chunks * step[sel]);
+    const double shared = 11.0 + 9 * cdiv(chunks, z) * step[sel] + 1.5e-6 * z * (double)a.M * a.N;
+    *splits = z > 1 && shared < whole ? z : 1;
+    return std::min(whole, shared);
+}
+
+// The tile of gemm_few.hip that a 3x3 convolution with `sel` to choose from takes, 0: it takes that kernel.  us, few / before:
+// 1,024 tokens x 320 channels 9.9 / 23.9, 4,096 15.5 / 34.6, 12,288 42 / 75, 16,384 57 / 51; 1,024 x 640 19 / 31, 4,096 48 / 51, 6,144 69 / 59;
+// 8,192 x 256 21 / 45; 8,192 x 128 8.8 / 16; 16,384 x 64 7.5 / 9.5.  Up to 1,024 channels: above, the weights (more than 29 MB) come from
+// HBM in a whole network, and the longer chain waits for them (1,024 x 1,280 41 / 46, with cold weights 52 / 48).
+static int conv_few(const GemmArgs& a, int sel) {
+    int splits;
+    double us;
+    const int few = a.K <= 1024 ? few_pick(a, 4, &us) : 0;
+    return few && us < conv_time(a, sel, &splits) ? few : 0;
+}
+
 bool gemm_emits_stats(const GemmArgs& a, int dtype, int mode) {
     if (mode != 0 || dtype != PSERVE_BF16 || !a.stats || a.stats_G <= 0 || !mfma_eligible(a)) return false;
     ConvTile ct;
     int wc = 0;
-    if (!conv_select(a, &ct, &wc)) return false;
+    const int sel = conv_select(a, &ct, &wc);
+    if (!sel || conv_few(a, sel)) return false;
     // a wavefront's 64 rows must lie in one patch, and its columns must hold whole groups
     return a.geom.S % 64 == 0 && a.stats_slots == a.geom.S / 64 && !a.act.active && a.N % a.stats_G == 0 &&
            wc % (a.N / a.stats_G) == 0;
@@ -1197,18 +1212,37 @@ size_t conv_split_bytes(const PatchGeom& g, int32_t M, int32_t N, int32_t K, int
     a.conv = 1; a.tokens_are_rows = 1; a.taps = 9; a.geom = g; a.M = M; a.N = N; a.K = K; a.lda = K; a.seg_cols = N;
     for (auto& s : a.seg) s.scale = 1.f;
     ConvTile ct;
-    static const int bm[7] = {0, 256, 128, 128, 128, 128, 256}, bn[7] = {1, 160, 320, 256, 128, 64, 160};
     const int sel = conv_select(a, &ct);
-    if (!sel) return 0;
-    const int64_t mt = cdiv(M, bm[sel]);
-    const int z = conv_splits(mt * (N / bn[sel]), K / 64);
-    return z > 1 ? sizeof(float) * z * mt * bm[sel] * (size_t)N : 0;
+    if (!sel || conv_few(a, sel)) return 0;
+    int z;
+    conv_time(a, sel, &z);
+    return z > 1 ? sizeof(float) * z * cdiv(M, CONV_BM[sel]) * CONV_BM[sel] * (size_t)N : 0;
 }
 
-// For tests (host only, no part of the ABI): 1 if the 3x3 convolutions of such a batch (bf16, C to C channels) share tiles.
+// For tests (host only, no part of the ABI): 1 if the 3x3 convolutions of such a batch (bf16, C to C channels) have few enough
+// tiles to share them, where the small tiles of gemm_few.hip do not take them.
 extern "C" int pserve_test_conv_shares(int32_t P, int32_t ph, int32_t pw, int32_t C) {
     const PatchGeom g{P, ph * pw, ph, pw, pw + 2, (ph + 2) * (pw + 2)};
-    return conv_split_bytes(g, P * ph * pw, C, C, PSERVE_BF16, 0) > 0;
+    GemmArgs a{};
+    a.conv = 1; a.tokens_are_rows = 1; a.taps = 9; a.geom = g; a.M = P * ph * pw; a.N = a.K = a.lda = a.seg_cols = C;
+    for (auto& s : a.seg) s.scale = 1.f;
+    ConvTile ct;
+    const int sel = conv_select(a, &ct);
+    return sel && conv_splits(cdiv(a.M, CONV_BM[sel]) * (a.N / CONV_BN[sel]), a.K / 64) > 1;
+}
+// The tile of gemm_few.hip that such a convolution takes instead (1 .. 5: 32 x 32, 32 x 64, 32 x 80, 64 x 64, 64 x 80), 0: none; linear:
+// that of a linear layer of P * ph * pw rows, K = C, N columns in segments of seg_cols (value-gate pairs: seg_cols = 0).
+extern "C" int pserve_test_few_tile(int32_t P, int32_t ph, int32_t pw, int32_t C, int32_t linear, int32_t N, int32_t seg_cols) {
+    GemmArgs a{};
+    a.geom = PatchGeom{P, ph * pw, ph, pw, pw + 2, (ph + 2) * (pw + 2)};
+    a.tokens_are_rows = 1; a.taps = linear ? 1 : 9; a.conv = !linear; a.M = P * ph * pw; a.K = a.lda = C; a.N = linear ? N : C;
+    a.epi = linear && !seg_cols ? EPI_GEGLU : EPI_ROUTE;
+    a.seg_cols = !linear ? C : seg_cols ? seg_cols : N;
+    for (auto& s : a.seg) s.scale = 1.f;
+    ConvTile ct;
+    double us;
+    const int sel = linear ? 0 : conv_select(a, &ct);
+    return sel ? conv_few(a, sel) : few_pick(a, a.epi == EPI_GEGLU ? 2 : 1, &us);
 }
 
 int gemm_wide_bf16(const GemmArgs& a, hipStream_t st, bool* handled);     // gemm_wide.hip
@@ -1216,6 +1250,14 @@ int gemm_wide_bf16(const GemmArgs& a, hipStream_t st, bool* handled);     // gem
 int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
     *handled = false;
     if (!mfma_eligible(a)) return PSERVE_OK;
+    ConvTile ct;
+    const int sel = a.conv && a.epi == EPI_ROUTE ? conv_select(a, &ct) : 0;
+    double us;
+    const int few = sel ? conv_few(a, sel) : few_pick(a, a.epi == EPI_GEGLU ? 2 : 1, &us);
+    if (few) {
+        *handled = true;
+        return gemm_few_bf16(a, few, st);
+    }
     if (!a.conv) {
         PS_TRY(gemm_wide_bf16(a, st, handled));
         if (*handled || a.B2) return PSERVE_OK;
@@ -1230,14 +1272,15 @@ int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
         return launch<256, 128, true, 4, 1, 2, true>(a, st);
     }
     if (a.seg_cols % 32 != 0) return PSERVE_OK;      // a 32-column tile must not straddle output segments
-    ConvTile ct;
-    switch (conv_select(a, &ct)) {
-    case 1: *handled = true; return launch_conv<256, 160, 4, 1, 384, 3, 2>(a, ct, st);
-    case 2: *handled = true; return launch_conv<128, 320, 2, 2, 256, 2>(a, ct, st);
-    case 3: *handled = true; return launch_conv<128, 256, 2, 2, 256, 2>(a, ct, st);
-    case 4: *handled = true; return launch_conv<128, 128, 2, 2, 256, 2>(a, ct, st);
-    case 5: *handled = true; return launch_conv<128, 64, 2, 2, 256, 2>(a, ct, st);
-    case 6: *handled = true; return launch_conv<256, 160, 4, 1, 416, 2, 2>(a, ct, st);
+    int splits = 1;
+    if (sel) conv_time(a, sel, &splits);
+    switch (sel) {
+    case 1: *handled = true; return launch_conv<256, 160, 4, 1, 384, 3, 2>(a, ct, splits, st);
+    case 2: *handled = true; return launch_conv<128, 320, 2, 2, 256, 2>(a, ct, splits, st);
+    case 3: *handled = true; return launch_conv<128, 256, 2, 2, 256, 2>(a, ct, splits, st);
+    case 4: *handled = true; return launch_conv<128, 128, 2, 2, 256, 2>(a, ct, splits, st);
+    case 5: *handled = true; return launch_conv<128, 64, 2, 2, 256, 2>(a, ct, splits, st);
+    case 6: *handled = true; return launch_conv<256, 160, 4, 1, 416, 2, 2>(a, ct, splits, st);
     default: break;
     }
     // Tile choice.  Two blocks of 128 rows per CU where they fit (one block's prologue and epilogue run beside the

@@ -41,4 +41,18 @@ __device__ __forceinline__ float other_half_f(float v) {
 
 typedef __attribute__((address_space(3))) void lds_void;
 
+// Text rows stand L to a request and their outputs row_group_pad apart.  A transposed segment stores four tokens at once
+// where they lie aligned; with L = 77 and 80 only every fourth request's do, and the others' leave two bytes at a time.  The
+// tiles then walk the padded rows instead (those past L hold nothing): 39 -> 33 us for 22 x 77 x 2560, K = 2048; 16 requests
+// 30.7 -> 26.1, 10 29.1 -> 24.5, 4 19.8 -> 19.2; 4 x 77 x 1280, K = 768 13.5 -> 12.1, but 2 11.7 -> 12.1.  Not where the padding
+// would be more than an eighth of the rows, nor where L is a multiple of four or there are fewer than three requests.  A form of
+// its own (EPF_PADS): as a run-time choice in all forms it cost the small layers 2 to 10 % (1,024 x 1,280, K = 1,280 and 128 x 64
+// tiles 12.5 -> 13.0 .. 13.7 us).
+__host__ __device__ inline bool gemm_pads_rows(const GemmArgs& a) {
+    return !a.tokens_are_rows && a.epi == EPI_ROUTE && !a.rowbias && !a.rowscale && !a.act_gelu && a.row_group > 0 &&
+           a.M > 2 * a.row_group && a.row_group % 4 != 0 && a.row_group_pad % 4 == 0 && a.M % a.row_group == 0 &&
+           a.row_group_pad - a.row_group <= a.row_group / 8 && (a.seg[0].transposed || a.seg[1].transposed || a.seg[2].transposed);
+}
+__host__ __device__ inline int32_t gemm_rows(const GemmArgs& a) { return gemm_pads_rows(a) ? a.M / a.row_group * a.row_group_pad : a.M; }
+
 }  // namespace pserve
