@@ -14,6 +14,7 @@
 // Tried: fragments loaded straight into registers, no LDS (twice the time: 64-byte pieces of 16 rows a load); rings of three and
 // four steps, eight wavefronts (no gain in one round, and one block a CU instead of two); two rounds (no gain but for GEGLU).
 #include "mfma_util.h"
+#include <type_traits>
 
 namespace pserve {
 
@@ -27,9 +28,10 @@ template <int BM, int BN, int W> struct FewCfg {
     static_assert(LDS <= 160 * 1024 && BM * RED_LD * 4 <= PART, "LDS");
 };
 
-template <int BM, int BN, int W, bool GEGLU>
+// TWO: a second problem (GemmArgs::B2: another patch list, weights, bias and gate of its own) continues the row tiles of the first.
+template <int BM, int BN, int W, bool GEGLU, bool TWO>
 __global__ void __launch_bounds__(64 * W)
-gemm_few_kernel(GemmCore a, int pads, int m_first) {
+gemm_few_kernel(std::conditional_t<TWO, GemmArgs, GemmCore> a, int pads, int m_first) {
     using Cfg = FewCfg<BM, BN, W>;
     constexpr int TM = BM / 16, TN = BN / 16, AL = BM / 8, BL = BN / 8, LD = AL + BL;
     static_assert(!GEGLU || BN == 64, "a tile of value-gate pairs is 32 values and their 32 gates");
@@ -43,15 +45,34 @@ gemm_few_kernel(GemmCore a, int pads, int m_first) {
     // Tiles: XCD x (block id mod 8) takes the x-th eighth of the tile numbers, rows or columns fastest (m_first), so that its L2
     // fetches an eighth of the larger operand.
     const bool masked = a.tokens_are_rows && a.act.active;
-    const int act_count = masked ? *a.act.count : 0;
-    const int m_limit = masked ? act_count * a.geom.S : pads ? a.M / a.row_group * a.row_group_pad : a.M;
-    const int n_in = a.N / BN, n_tiles = n_in * (a.classes ? a.classes : 1), m_tiles = (m_limit + BM - 1) / BM;
+    // (the counts decide which tile a block has and so what its loads' scalar offsets and descriptors are: scalars)
+    const int act_count = masked ? __builtin_amdgcn_readfirstlane(*a.act.count) : 0;
+    int m_limit = masked ? act_count * a.geom.S : pads ? a.M / a.row_group * a.row_group_pad : a.M;
+    const int mt1 = (m_limit + BM - 1) / BM;
+    int m_tiles = mt1, m_limit2 = 0;
+    if constexpr (TWO) {
+        m_limit2 = __builtin_amdgcn_readfirstlane(*a.act2.count) * a.geom.S;
+        m_tiles += (m_limit2 + BM - 1) / BM;
+    }
+    const int n_in = a.N / BN, n_tiles = n_in * (a.classes ? a.classes : 1);
     const int total = n_tiles * m_tiles, xcd = blockIdx.x & 7;
     const int t = (int)((int64_t)total * xcd / 8) + (int)(blockIdx.x >> 3);
     if (t >= (int)((int64_t)total * (xcd + 1) / 8)) return;
     const int mt = m_first ? t % m_tiles : t / n_tiles, nt = m_first ? t / m_tiles : t - (t / n_tiles) * n_tiles;
     const int cls = a.classes ? nt / n_in : 0;
-    const int m0 = mt * BM, ntile = nt - cls * n_in;
+    const int ntile = nt - cls * n_in;
+    int m0 = mt * BM;
+    // what differs between the problems (locals: writing to the arguments would move all of them to memory)
+    const void* B = a.B;
+    const float *bias_v = a.bias, *rowscale = a.rowscale;
+    const int32_t* active = a.act.active;
+    if constexpr (TWO) {
+        if (mt >= mt1) {
+            m0 -= mt1 * BM;
+            m_limit = m_limit2;
+            B = a.B2; bias_v = a.bias2; rowscale = a.rowscale2; active = a.act2.active;
+        }
+    }
     // packed column of column c of the tile (value-gate pairs: 32 values, then their gates, 64 further in groups of 128)
     auto bcol = [&](int c) { return GEGLU ? (ntile >> 1) * (2 * GEGLU_GROUP) + (ntile & 1) * 32 + (c >> 5) * GEGLU_GROUP + (c & 31) : ntile * BN + c; };
 
@@ -61,7 +82,7 @@ gemm_few_kernel(GemmCore a, int pads, int m_first) {
     const int fr = lane & 15, kq = lane >> 4;                       // fragment row / column, quarter of a 32-wide K piece
 #if defined(__HIP_DEVICE_COMPILE__)
     const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.A, 0, 0x7fffffff, 0x00020000);
-    const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.B, 0, 0x7fffffff, 0x00020000);
+    const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)B, 0, 0x7fffffff, 0x00020000);
 #define PS_LOAD(rsrc_, dst_, lane_off_, off_) \
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_, (lds_void*)(dst_), 16, lane_off_, off_, 0, 0)
 #else       // the host pass only needs the kernel's stub
@@ -101,7 +122,7 @@ gemm_few_kernel(GemmCore a, int pads, int m_first) {
         bool valid = tok < m_limit;
         if (masked) {
             const int pi = tok / a.geom.S;
-            tok = valid ? a.act.active[pi] * a.geom.S + (tok - pi * a.geom.S) : 0;
+            tok = valid ? active[pi] * a.geom.S + (tok - pi * a.geom.S) : 0;
         } else {
             if (pads && valid) {
                 const int g = tok / a.row_group_pad, j = tok - g * a.row_group_pad;
@@ -127,7 +148,7 @@ gemm_few_kernel(GemmCore a, int pads, int m_first) {
         if (!a.tokens_are_rows && a.row_group > 0) orow = tok / a.row_group * a.row_group_pad + tok % a.row_group;
         s_tok[tid] = valid ? orow : -1;
         s_off[tid] = (int)(off * 2);
-        if (a.rowbias || a.rowscale) s_own[tid] = a.row_owner[tok / a.geom.S];
+        if (a.rowbias || rowscale) s_own[tid] = a.row_owner[tok / a.geom.S];
     }
     // the table is written; the loads stay in flight (__syncthreads() would wait for them)
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -148,15 +169,15 @@ gemm_few_kernel(GemmCore a, int pads, int m_first) {
         for (int q = 0; q < (GEGLU ? 16 : 8); ++q) bias[u][q] = 0.f;
         if (it >= ITEMS) continue;
         if (tr) {
-            if (a.bias) bias[u][0] = a.bias[pcol0 + it / (BM / 8)];
+            if (bias_v) bias[u][0] = bias_v[pcol0 + it / (BM / 8)];
             continue;
         }
         const int row = it / CV, ch = it % CV * 8, tok = s_tok[row];
-        if (a.bias) {
+        if (bias_v) {
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
-                bias[u][q] = a.bias[pcol0 + ch + q];
-                if (GEGLU) bias[u][8 + q] = a.bias[pcol0 + GEGLU_GROUP + ch + q];
+                bias[u][q] = bias_v[pcol0 + ch + q];
+                if (GEGLU) bias[u][8 + q] = bias_v[pcol0 + GEGLU_GROUP + ch + q];
             }
         }
         if (!GEGLU && a.res && tok >= 0) res[u] = *reinterpret_cast<const u32x4*>((const uint16_t*)a.res + (int64_t)tok * a.ldr + pcol0 + ch);
@@ -252,7 +273,7 @@ gemm_few_kernel(GemmCore a, int pads, int m_first) {
             for (int q = 0; q < 8; ++q) {
                 if (a.rowbias) v[q] += a.rowbias[(int64_t)s_own[r0 + q] * a.N + pcol0 + c];
                 if (a.act_gelu) v[q] = gelu_tanh(v[q]);
-                if (a.rowscale) v[q] *= a.rowscale[(int64_t)s_own[r0 + q] * a.rowscale_ld + pcol0 + c];
+                if (rowscale) v[q] *= rowscale[(int64_t)s_own[r0 + q] * a.rowscale_ld + pcol0 + c];
                 v[q] *= seg.scale;
             }
             if (t0 >= 0 && t7 == t0 + 7 && t3 == t0 + 3 && t4 == t0 + 4 && (t0 & 7) == 0 && (seg.ld & 7) == 0) {
@@ -302,8 +323,8 @@ gemm_few_kernel(GemmCore a, int pads, int m_first) {
 #pragma unroll
                 for (int q = 0; q < 8; ++q) v[q] = gelu_tanh(v[q]);
             }
-            if (a.rowscale) {
-                const float* rs = a.rowscale + (int64_t)s_own[row] * a.rowscale_ld + pcol0 + ch;
+            if (rowscale) {
+                const float* rs = rowscale + (int64_t)s_own[row] * a.rowscale_ld + pcol0 + ch;
 #pragma unroll
                 for (int q = 0; q < 8; ++q) v[q] *= rs[q];
             }
@@ -322,16 +343,25 @@ gemm_few_kernel(GemmCore a, int pads, int m_first) {
     }
 }
 
-template <int BM, int BN, bool GEGLU>
-static int launch_few(const GemmArgs& a, hipStream_t st) {
+static int64_t few_tiles(const GemmArgs& a, int bm, int bn) {
+    return (cdiv(gemm_rows(a), bm) + (a.B2 ? cdiv(a.M2, bm) : 0)) * (a.N / bn) * std::max(1, a.classes);
+}
+template <int BM, int BN, bool GEGLU, bool TWO>
+static int launch_few_as(const GemmArgs& a, hipStream_t st) {
     constexpr int W = 4;
     constexpr size_t lds = FewCfg<BM, BN, W>::LDS;
-    PS_SET_LDS_ONCE((gemm_few_kernel<BM, BN, W, GEGLU>), lds);
+    PS_SET_LDS_ONCE((gemm_few_kernel<BM, BN, W, GEGLU, TWO>), lds);
     const bool pads = gemm_pads_rows(a);
-    const int64_t tiles = cdiv(gemm_rows(a), BM) * (a.N / BN) * std::max(1, a.classes);
     const int m_first = (int64_t)a.M <= (int64_t)a.N * a.taps * std::max(1, a.classes);
-    gemm_few_kernel<BM, BN, W, GEGLU><<<(unsigned)(8 * cdiv(tiles, 8)), 64 * W, lds, st>>>(a, pads, m_first);
+    gemm_few_kernel<BM, BN, W, GEGLU, TWO><<<(unsigned)(8 * cdiv(few_tiles(a, BM, BN), 8)), 64 * W, lds, st>>>(a, pads, m_first);
     return check_launch("gemm_few_kernel");
+}
+template <int BM, int BN, bool GEGLU>
+static int launch_few(const GemmArgs& a, hipStream_t st) {
+    if constexpr (!GEGLU) {
+        if (a.B2) return launch_few_as<BM, BN, GEGLU, true>(a, st);
+    }
+    return launch_few_as<BM, BN, GEGLU, false>(a, st);
 }
 
 // Which tile a problem would take here (0: none) and how long it would run, in us: a round of 256 tiles (32 x 32: 512, two
@@ -345,11 +375,12 @@ int few_pick(const GemmArgs& a, int most_rounds, double* us) {
     const bool geglu = a.epi == EPI_GEGLU;
     int best = 0;
     *us = 1e30;
-    if (a.B2 || (geglu && a.N % 128 != 0)) return 0;
+    if (geglu && a.N % 128 != 0) return 0;
+    if (a.B2 && !gemm_two_eligible(a)) return 0;
     for (int v = 1; v <= 5; ++v) {
         const int bm = FEW[v].bm, bn = FEW[v].bn;
         if (geglu ? bn != 64 : a.N % bn != 0 || a.seg_cols % bn != 0) continue;
-        const int64_t tiles = cdiv(gemm_rows(a), bm) * (a.N / bn) * std::max(1, a.classes);
+        const int64_t tiles = few_tiles(a, bm, bn);
         const int64_t steps = (int64_t)a.taps * (a.K / 64), rounds = cdiv(tiles, 256);
         if (v == 1 ? tiles > 512 : rounds > most_rounds) continue;
         const double t = v == 1 && tiles > 256 ? 4.3 + 0.17 * steps : rounds * (FEW[v].fixed + FEW[v].step * steps);

@@ -37,11 +37,12 @@ enum : int {
     EPF_MIXED = 8,      // rows of several requests in one wavefront tile: per-element look-ups of rowbias / rowscale
     EPF_SCALE = 16,     // output segments with a scale other than 1 (the pre-multiplied Q)
     EPF_ALL = 31,
-    EPF_PADS = 32       // tiles walk the padded rows of the requests (gemm_pads_rows)
+    EPF_PADS = 32,      // tiles walk the padded rows of the requests (gemm_pads_rows)
+    EPF_TWO = 64        // a second problem (GemmArgs::B2) continues the row tiles; one tile a block
 };
 template <int BM, int BN, bool GEGLU, int WGM = 2, int WGN = 2, bool MAY_STAT = true, int FEAT = EPF_ALL>
 __device__ __forceinline__ void gemm_epilogue(const GemmCore& a, f32x16 (&acc)[BM / WGM / 32][BN / WGN / 32], uint8_t* smem,
-                                              const int32_t* s_tok, int n0, const float* bias_pre = nullptr) {
+                                              const int32_t* s_tok, int n0, const float* bias_pre, const float* rowscale) {
     constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;     // WGM x WGN wavefront grid
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave / WGN, wn = wave % WGN;
@@ -76,7 +77,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmCore& a, f32x16 (&acc)[B
     // request (rows are ordered by request, so first == last decides), else looked up per element
     bool rb_uniform = false;
     int rb_slot = 0;
-    if (!GEGLU && (a.rowbias || ((FEAT & EPF_GATE) && a.rowscale))) {
+    if (!GEGLU && (a.rowbias || ((FEAT & EPF_GATE) && rowscale))) {
         const int t_first = w_tok[0], t_last = w_tok[WM - 1];
         if (t_first >= 0 && t_last >= 0) {
             rb_slot = a.row_owner[t_first / a.geom.S];
@@ -136,9 +137,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmCore& a, f32x16 (&acc)[B
 #pragma unroll
                     for (int e = 0; e < 16; ++e) vals[i][e] = gelu_tanh(vals[i][e]);
             }
-            if ((FEAT & EPF_GATE) && a.rowscale) {              // gate of the request, before the residual is added
+            if ((FEAT & EPF_GATE) && rowscale) {              // gate of the request, before the residual is added
                 if (rb_uniform || !(FEAT & EPF_MIXED)) {
-                    const float gate = a.rowscale[(int64_t)rb_slot * a.rowscale_ld + pcol + fr];
+                    const float gate = rowscale[(int64_t)rb_slot * a.rowscale_ld + pcol + fr];
 #pragma unroll
                     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -149,7 +150,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmCore& a, f32x16 (&acc)[B
 #pragma unroll
                         for (int e = 0; e < 16; ++e) {
                             const int tok = w_tok[i * 32 + 8 * (e >> 2) + 4 * fh + (e & 3)];
-                            if (tok >= 0) vals[i][e] *= a.rowscale[(int64_t)a.row_owner[tok / a.geom.S] * a.rowscale_ld + pcol + fr];
+                            if (tok >= 0) vals[i][e] *= rowscale[(int64_t)a.row_owner[tok / a.geom.S] * a.rowscale_ld + pcol + fr];
                         }
                 }
             }
@@ -319,10 +320,12 @@ gemm_mfma_kernel(GemmArgs a) {
     // neighbouring tiles, so gm is chosen for the fewest bytes of A and B panels, and few rows with many columns end up
     // shared out by columns.  (An eighth of the M tiles per XCD instead: with 8 M tiles every XCD read all weights, 115 MB
     // for 13 MB of them at K = 5120.)
-    const int act_count = (a.tokens_are_rows && a.act.active) ? *a.act.count : 0;              // computed patches
-    constexpr bool PADS = (FEAT & EPF_PADS) != 0;
-    const int m_limit = (a.tokens_are_rows && a.act.active) ? act_count * a.geom.S : PADS ? gemm_rows(a) : a.M;      // rows that exist
-    const int n_tiles = a.N / BN * (a.classes ? a.classes : 1), m_tiles = (m_limit + BM - 1) / BM;
+    int act_count = (a.tokens_are_rows && a.act.active) ? *a.act.count : 0;                    // computed patches
+    if (FEAT & EPF_TWO) act_count = __builtin_amdgcn_readfirstlane(act_count);      // (decides which problem's pointers a block takes)
+    constexpr bool PADS = (FEAT & EPF_PADS) != 0, TWO = (FEAT & EPF_TWO) != 0;
+    int m_limit = (a.tokens_are_rows && a.act.active) ? act_count * a.geom.S : PADS ? gemm_rows(a) : a.M;      // rows that exist
+    const int n_tiles = a.N / BN * (a.classes ? a.classes : 1), mt1 = (m_limit + BM - 1) / BM;
+    const int cnt2 = TWO ? __builtin_amdgcn_readfirstlane(*a.act2.count) : 0, m_tiles = TWO ? mt1 + (cnt2 * a.geom.S + BM - 1) / BM : mt1;
     const int total = n_tiles * m_tiles, slot_step = gridDim.x >> 3;
     const int slots = (int)((int64_t)total * ((blockIdx.x & 7) + 1) / 8);      // end of this XCD's tiles
     const int gm = min(max((int)(sqrtf((float)min((total + 7) / 8, 64) * BN / BM) + 0.5f), 1), max(m_tiles, 1));
@@ -337,6 +340,18 @@ gemm_mfma_kernel(GemmArgs a) {
     int slot = (int)((int64_t)total * (blockIdx.x & 7) / 8) + (blockIdx.x >> 3);
     if (slot >= slots) return;
     decode(slot, m0, n0);
+    // what differs between the problems (locals: writing to the arguments would move all of them to memory)
+    const void* B = a.B;
+    const float *bias_v = a.bias, *rowscale = a.rowscale;
+    const int32_t* active = a.act.active;
+    if constexpr (TWO) {
+        if (m0 >= mt1 * BM) {
+            m0 -= mt1 * BM;
+            act_count = cnt2;
+            m_limit = cnt2 * a.geom.S;
+            B = a.B2; bias_v = a.bias2; rowscale = a.rowscale2; active = a.act2.active;
+        }
+    }
 
     // Staging by direct global -> LDS loads.  One wavefront instruction fills 64 consecutive 16-byte slots
     // (8 rows x 8 chunk positions); the lane at (row, position pos) fetches global chunk pos ^ f(row),
@@ -363,7 +378,7 @@ gemm_mfma_kernel(GemmArgs a) {
         if (a.tokens_are_rows && a.act.active) {                                                                  \
             _Pragma("unroll") for (int i = 0; i < A_LD; ++i) {                                                    \
                 const int pi = ((tm0) + lr + i * 32) / a.geom.S;                                                  \
-                act_p[i] = pi < act_count ? a.act.active[pi] : -1;                                                \
+                act_p[i] = pi < act_count ? active[pi] : -1;                                                \
             }                                                                                                     \
         }                                                                                                         \
         _Pragma("unroll") for (int i = 0; i < A_LD; ++i) {                                                        \
@@ -407,7 +422,7 @@ gemm_mfma_kernel(GemmArgs a) {
     // fragment into a wait for all LDS reads in flight; 2-4 % on every linear layer)
 #if defined(__HIP_DEVICE_COMPILE__)
     const __amdgpu_buffer_rsrc_t ga_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.A, 0, 0x7fffffff, 0x00020000);
-    const __amdgpu_buffer_rsrc_t gb_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.B, 0, 0x7fffffff, 0x00020000);
+    const __amdgpu_buffer_rsrc_t gb_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)B, 0, 0x7fffffff, 0x00020000);
 #define PS_LOAD(dst_, a_off_, b_off_, l_)                                                                         \
     {                                                                                                             \
         if ((l_) < A_LD)                                                                                          \
@@ -534,7 +549,7 @@ gemm_mfma_kernel(GemmArgs a) {
         // before it, so a bias load behind them would stall the epilogue until the whole next tile start has landed
         float bias_t[TN];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) bias_t[j] = a.bias ? a.bias[n0_cur + wn * WN + j * 32 + fr] : 0.f;
+        for (int j = 0; j < TN; ++j) bias_t[j] = bias_v ? bias_v[n0_cur + wn * WN + j * 32 + fr] : 0.f;
         asm volatile("" ::: "memory");              // keeps the compiler from sinking these loads below the next ones
         if (OVERLAP && nslot < slots) {             // next tile's first steps in flight during this tile's epilogue
             PS_SETUP(nm0, nn0, s_tok2 + (buf ^ 1) * BM);
@@ -543,7 +558,7 @@ gemm_mfma_kernel(GemmArgs a) {
             PS_SETUP(nm0, nn0, s_tok2 + (buf ^ 1) * BM);
             PS_PROLOGUE_STAGES(0, 1);
         }
-        gemm_epilogue<BM, BN, GEGLU, WGM, WGN, false, FEAT>(a, acc, HALF ? smem + STAGE_V * 16 : ep_smem, tok_cur, n0_cur, bias_t);
+        gemm_epilogue<BM, BN, GEGLU, WGM, WGN, false, FEAT>(a, acc, HALF ? smem + STAGE_V * 16 : ep_smem, tok_cur, n0_cur, bias_t, rowscale);
         if (nslot >= slots) break;
         if (!OVERLAP) {
             __syncthreads();                        // every wavefront is done with its staging region in the ring
@@ -929,7 +944,7 @@ conv_mfma_kernel(GemmCore a, std::conditional_t<SPLIT, SharedConvTile, ConvTile>
         return;
     }
     // the launch conditions of these kernels rule the other paths out (conv_select)
-    gemm_epilogue<BM, BN, false, WGM, WGN, true, 0>(a, acc, smem, s_tok, n0, bias_t);
+    gemm_epilogue<BM, BN, false, WGM, WGN, true, 0>(a, acc, smem, s_tok, n0, bias_t, nullptr);
 }
 
 // Second half of a convolution whose tiles were shared: sums the partial tiles in a fixed order, adds the bias (and the
@@ -1104,8 +1119,9 @@ static int launch_feat(const GemmArgs& a, hipStream_t st) {
     PS_SET_LDS_ONCE((gemm_mfma_kernel<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, FEAT>), lds);
     // all tiles, or as many blocks as run at once (256 CUs x the blocks of this LDS size per CU): each block then
     // walks over several tiles
-    const int64_t all = 8 * cdiv(cdiv(FEAT & EPF_PADS ? gemm_rows(a) : a.M, BM) * (a.N / BN) * std::max(1, a.classes), 8);
-    const int64_t resident = 256 * (int64_t)std::max<size_t>(1, std::min<size_t>(2, (160 * 1024) / lds));
+    const int64_t m_tiles = cdiv(FEAT & EPF_PADS ? gemm_rows(a) : a.M, BM) + (FEAT & EPF_TWO ? cdiv(a.M2, BM) : 0);
+    const int64_t all = 8 * cdiv(m_tiles * (a.N / BN) * std::max(1, a.classes), 8);
+    const int64_t resident = FEAT & EPF_TWO ? all : 256 * (int64_t)std::max<size_t>(1, std::min<size_t>(2, (160 * 1024) / lds));
     const unsigned grid = (unsigned)std::min(all, resident);
     gemm_mfma_kernel<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, FEAT><<<grid, 256, lds, st>>>(a);
     return check_launch("gemm_mfma_kernel");
@@ -1133,11 +1149,6 @@ static int launch(const GemmArgs& a, hipStream_t st) {
         }
         return launch_feat<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, EPF_ALL>(a, st);
     }
-}
-
-// shapes the MFMA kernels take at all
-static bool mfma_eligible(const GemmArgs& a) {
-    return a.K % 64 == 0 && a.lda % 8 == 0 && !((uintptr_t)a.A & 15) && !((uintptr_t)a.B & 15) && gemm_fits32(a);
 }
 
 // Which halo-in-LDS convolution kernel a problem takes (0: none) and the columns one wavefront of it covers.
@@ -1196,7 +1207,7 @@ static int conv_few(const GemmArgs& a, int sel) {
 }
 
 bool gemm_emits_stats(const GemmArgs& a, int dtype, int mode) {
-    if (mode != 0 || dtype != PSERVE_BF16 || !a.stats || a.stats_G <= 0 || !mfma_eligible(a)) return false;
+    if (mode != 0 || dtype != PSERVE_BF16 || !a.stats || a.stats_G <= 0 || !gemm_mfma_eligible(a)) return false;
     ConvTile ct;
     int wc = 0;
     const int sel = conv_select(a, &ct, &wc);
@@ -1247,13 +1258,36 @@ extern "C" int pserve_test_few_tile(int32_t P, int32_t ph, int32_t pw, int32_t C
 
 int gemm_wide_bf16(const GemmArgs& a, hipStream_t st, bool* handled);     // gemm_wide.hip
 
+// Two problems in one launch (two_select in gemm_wide.hip): columns of the tile modelled faster, and its time in us, fitted to 70
+// sizes (within a fifth: the time of a gate depends on how many requests a wavefront's rows belong to).  Both run two blocks a CU.
+int gemm_two_cols(const GemmArgs& a, double* us) {
+    const int64_t mt = cdiv(a.M, 128) + cdiv(a.M2, 128), steps = a.K / 64;
+    double t64 = 1e30, t128 = 1e30;
+    if (a.N % 64 == 0 && a.seg_cols % 32 == 0) {
+        const int64_t t = mt * (a.N / 64);
+        const double k = (double)cdiv(t, 256);      // rounds of 256 blocks: each slows the steps of those beside it
+        t64 = t <= 256 ? 5.6 + 0.31 * steps : t <= 512 ? 8.0 + steps * (0.52 + 0.1 * (t - 256) / 256) : 4.0 * k + steps * (0.04 + 0.28 * k);
+    }
+    if (a.N % 128 == 0 && a.seg_cols % 32 == 0) {
+        const int64_t t = mt * (a.N / 128), full = t / 512, rest = t % 512;
+        const double first = full ? 5.0 + 0.55 * steps : 7.2 + 0.61 * steps;
+        t128 = full * (9.0 + 1.05 * steps) + (rest == 0 ? 0.0 : rest <= 256 ? first : 9.0 + steps * (0.75 + 0.3 * (rest - 256) / 256));
+    }
+    *us = std::min(t64, t128);
+    return *us >= 1e30 ? 0 : t64 <= t128 ? 64 : 128;
+}
+int gemm_two_bf16(const GemmArgs& a, int cols, hipStream_t st) {
+    if (cols == 64) return launch_feat<128, 64, false, 2, 2, 3, false, EPF_ALL | EPF_TWO>(a, st);
+    return launch_feat<128, 128, false, 2, 2, 2, false, EPF_ALL | EPF_TWO>(a, st);
+}
+
 int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
     *handled = false;
-    if (!mfma_eligible(a)) return PSERVE_OK;
+    if (!gemm_mfma_eligible(a)) return PSERVE_OK;
     ConvTile ct;
     const int sel = a.conv && a.epi == EPI_ROUTE ? conv_select(a, &ct) : 0;
     double us;
-    const int few = sel ? conv_few(a, sel) : few_pick(a, a.epi == EPI_GEGLU ? 2 : 1, &us);
+    const int few = a.B2 ? 0 : sel ? conv_few(a, sel) : few_pick(a, a.epi == EPI_GEGLU ? 2 : 1, &us);
     if (few) {
         *handled = true;
         return gemm_few_bf16(a, few, st);

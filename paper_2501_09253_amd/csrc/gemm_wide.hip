@@ -496,11 +496,40 @@ static int wide_select(const GemmArgs& a) {
     return c128 <= std::min(c256, c320) ? 0 : c256 <= c320 ? 256 : 320;
 }
 
-bool gemm_takes_two(const GemmArgs& a, int dtype, int mode) { return dtype == PSERVE_BF16 && mode == 0 && a.B2 && wide_select(a) != 0; }
+// Two problems (a.B2) whose rows are too few for wide_select, or whose tiles come out badly: whichever is modelled fastest of these
+// tiles all the same, 128 x 64 or 128 x 128 (gemm_two_bf16), and the small ones of gemm_few.hip in up to four rounds.  As two launches
+// on two streams, the text stream's kernel waits for CUs that the image stream's holds, and every fork and join costs ~10 us.
+// us of a step, two streams / one launch a layer: 576 + 864 rows x 768 166 / 128, 3,072 + 1,280 283 / 211, 6,400 + 600 408 / 327; 3,072 +
+// 1,024 x 1,536 552 / 440, 2,304 + 288 377 / 355; 26 sizes 1.15x in the mean, none slower.
+// Returns the rows of the tile here, 128: gemm_two_bf16 with *tile columns, -1: gemm_few.hip's tile *tile, 0: none takes the problem.
+int few_pick(const GemmArgs& a, int most_rounds, double* us);
+int gemm_few_bf16(const GemmArgs& a, int tile, hipStream_t st);
+int gemm_two_cols(const GemmArgs& a, double* us);
+int gemm_two_bf16(const GemmArgs& a, int cols, hipStream_t st);
+static int two_select(const GemmArgs& a, int* tile) {
+    auto t = [&](int bm) { return (cdiv(a.M, bm) + cdiv(a.M2, bm)) * cdiv(a.N, 256); };
+    if (!gemm_two_eligible(a)) return 0;
+    double us[4];
+    const int few = few_pick(a, 4, &us[0]), cols = gemm_two_cols(a, &us[1]);
+    us[2] = wide_eligible(a, 128) ? 1.1 * wide_cost(t(256), a.K / 64, 0.97, 1.62, 8.0) : 1e30;
+    us[3] = wide_eligible(a, 64) ? 1.1 * wide_cost(t(320), a.K / 64, 1.20, 2.05, 9.0) : 1e30;
+    static const int rows[4] = {-1, 128, 256, 320};
+    const int64_t best = std::min_element(us, us + 4) - us;
+    *tile = best ? cols : few;
+    return us[best] < 1e30 ? rows[best] : 0;
+}
+
+bool gemm_takes_two(const GemmArgs& a, int dtype, int mode) {
+    int tile;
+    return dtype == PSERVE_BF16 && mode == 0 && a.B2 && gemm_mfma_eligible(a) && (wide_select(a) != 0 || two_select(a, &tile) != 0);
+}
 
 int gemm_wide_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
-    const int rows = wide_select(a);
+    int tile = 0, rows = wide_select(a);
+    if (!rows && a.B2) rows = two_select(a, &tile);
     *handled = rows != 0;
+    if (rows < 0) return gemm_few_bf16(a, tile, st);
+    if (rows == 128) return gemm_two_bf16(a, tile, st);
     if (rows == 256) return launch_wide<4, 2, 2, 4>(a, st);
     if (rows == 320) return launch_wide<2, 4, 5, 2>(a, st);
     return PSERVE_OK;
@@ -509,8 +538,7 @@ int gemm_wide_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
 // For tests (host only, no part of the ABI): the rows of the tile such a layer takes here, 0: another kernel's.  P patches of
 // S tokens; rows: those of the layer's patch list, rows2: of a second problem's, 0: none.  flags: 1 last segment transposed,
 // 2 residual, 4 gate, 8 GELU, 16 value-gate pairs, 32 rows without a patch list.
-extern "C" int pserve_test_linear_tile(int32_t P, int32_t S, int32_t rows, int32_t rows2, int32_t N, int32_t K, int32_t seg_cols,
-                                       int32_t flags) {
+static GemmArgs test_args(int32_t P, int32_t S, int32_t rows, int32_t rows2, int32_t N, int32_t K, int32_t seg_cols, int32_t flags) {
     GemmArgs a{};
     void* some = reinterpret_cast<void*>(64);           // tested for alignment, never read
     static const int32_t list = 0;
@@ -523,7 +551,18 @@ extern "C" int pserve_test_linear_tile(int32_t P, int32_t S, int32_t rows, int32
     a.act_gelu = (flags & 8) != 0;
     a.epi = flags & 16 ? EPI_GEGLU : EPI_ROUTE;
     if (rows2) { a.B2 = some; a.M2 = rows2; a.act.active = a.act.count = a.act2.active = a.act2.count = &list; }
-    return wide_select(a);
+    return a;
+}
+extern "C" int pserve_test_linear_tile(int32_t P, int32_t S, int32_t rows, int32_t rows2, int32_t N, int32_t K, int32_t seg_cols,
+                                       int32_t flags) {
+    return wide_select(test_args(P, S, rows, rows2, N, K, seg_cols, flags));
+}
+// The tile that two problems in one launch take where that one is 0: rows of a tile here, 64 or 128: columns of a 128-row one, -1 .. -5:
+// a small one (gemm_few.hip), 0: none.
+extern "C" int pserve_test_two_tile(int32_t P, int32_t S, int32_t rows, int32_t rows2, int32_t N, int32_t K, int32_t seg_cols, int32_t flags) {
+    int tile;
+    const int r = two_select(test_args(P, S, rows, rows2, N, K, seg_cols, flags), &tile);
+    return r == 128 ? tile : r < 0 ? -tile : r;
 }
 
 }  // namespace pserve

@@ -53,6 +53,15 @@ __host__ __device__ inline bool gemm_pads_rows(const GemmArgs& a) {
            a.M > 2 * a.row_group && a.row_group % 4 != 0 && a.row_group_pad % 4 == 0 && a.M % a.row_group == 0 &&
            a.row_group_pad - a.row_group <= a.row_group / 8 && (a.seg[0].transposed || a.seg[1].transposed || a.seg[2].transposed);
 }
+// problems the bf16 MFMA kernels take at all
+inline bool gemm_mfma_eligible(const GemmArgs& a) {
+    return a.K % 64 == 0 && a.lda % 8 == 0 && !((uintptr_t)a.A & 15) && !((uintptr_t)a.B & 15) && gemm_fits32(a);
+}
+// second problems the kernels with one tile a block take
+inline bool gemm_two_eligible(const GemmArgs& a) {
+    return a.epi == EPI_ROUTE && !a.conv && a.tokens_are_rows && a.act.active && a.act2.active && !((uintptr_t)a.B2 & 15) &&
+           !a.bias == !a.bias2 && !a.rowscale == !a.rowscale2 && !a.rowbias;
+}
 __host__ __device__ inline int32_t gemm_rows(const GemmArgs& a) { return gemm_pads_rows(a) ? a.M / a.row_group * a.row_group_pad : a.M; }
 
 }  // namespace pserve

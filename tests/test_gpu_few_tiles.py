@@ -10,12 +10,13 @@ import pytest
 
 import paper_2501_09253_amd as ps
 import workloads as wl
+from oracle import block as ob
 from oracle import resample as ores
 
 torch = pytest.importorskip("torch")
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(), reason="no GPU")]
 
-from harness import rel_err, tolerance      # noqa: E402
+from harness import GpuRun, rel_err, tolerance      # noqa: E402
 from test_gpu_wide import _check            # noqa: E402
 
 T32, T32x64, T32x80, T64, T64x80 = 1, 2, 3, 4, 5
@@ -87,3 +88,63 @@ def test_few_tiles_between_levels(res, patch, C):
         want = [ref(im.double().numpy(), w.double().numpy(), b.double().numpy()) for im in images]
         err = rel_err(got, want)
         assert np.isfinite(err) and err < tolerance("bf16"), (op, err)
+
+
+# Both streams of a joint block in one launch a layer below the sizes of the wide tiles: rows of image and text that end inside
+# tiles, and every tile that takes them.
+@pytest.mark.parametrize("res,patch,C,L,tiles", [([(8, 8), (8, 16)], (8, 8), 64, 7, (-1, -1, -1, -1)), ([(24, 12), (12, 24)], (12, 12), 256, 200, (-4, -2, 64, -2)),
+                                                 ([(16, 32), (16, 32)], (16, 16), 768, 77, (128, 64, 128, 64)), ([(24, 24)], (8, 8), 384, 60, (-4, -1, -4, -1))])
+def test_both_streams_of_a_small_joint_block_in_one_launch(res, patch, C, L, tiles):
+    cfg = wl.custom_config(res, patch, C=C, G=32, heads=C // 64, stages=("MMDIT",), dtype="bf16", ctx_len=L, ctx_dim=C, temb_dim=96, seed=69)
+    S, F = patch[0] * patch[1], cfg.ffn_mult * C
+    image, text = sum(h * w for h, w in res), len(res) * -(-L // S) * S
+    got = [ps.lib().pserve_test_two_tile((image + text) // S, S, image, text, N, K, seg, flags)
+           for N, K, seg, flags in ((3 * C, C, C, 1), (C, C, C, 6), (F, C, F, 8), (C, F, C, 6))]
+    assert tuple(got) == tiles
+    w = wl.make_workload(cfg)
+    out = []
+    for mode in (0, 1):
+        ps.set_kernel_mode(mode)
+        try:
+            run = GpuRun(w)
+            y = run.forward()
+            out.append([a.float().cpu().numpy() for a in run.plan.reassemble(y) + [run.plan.text_gather(y)]])
+        finally:
+            ps.set_kernel_mode(0)
+    err = rel_err(*out)
+    assert np.isfinite(err) and err < 1e-2, err
+    ref = [ob.mmdit(z, w.ctx[i], w.temb[i], w.params[0], cfg.heads, cfg.eps) for i, z in enumerate(w.images)]
+    err = rel_err(out[0], [im for im, _ in ref] + [np.stack([t for _, t in ref])])
+    assert np.isfinite(err) and err < tolerance("bf16"), err
+
+
+def test_two_streams_of_a_joint_block_replayed_from_a_graph():
+    """32 bits: the text stream's kernels on the library's side stream, forked from and joined to the captured one."""
+    cfg = wl.custom_config([(16, 16), (16, 32)], (16, 16), C=64, G=32, heads=2, stages=("MMDIT", "MMDIT"), dtype="f32", ctx_len=40, ctx_dim=64,
+                           seed=71, temb_dim=32)
+    run = GpuRun(wl.make_workload(cfg))
+    y = torch.empty_like(run.x)
+
+    def step():
+        run.cache.forward(run.x, None, None, y=y, temb=run.temb)
+
+    step()
+    torch.cuda.synchronize()
+    ref = y.clone()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        step()
+        side.synchronize()
+        with torch.cuda.graph(g, stream=side):
+            step()
+    torch.cuda.current_stream().wait_stream(side)
+    for k in range(4):
+        y.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, ref), f"replay {k}"
+        step()
+        torch.cuda.synchronize()
+        assert torch.equal(y, ref), f"eager after replay {k}"
