@@ -383,7 +383,8 @@ int few_pick(const GemmArgs& a, int most_rounds, double* us) {
         const int64_t tiles = few_tiles(a, bm, bn);
         const int64_t steps = (int64_t)a.taps * (a.K / 64), rounds = cdiv(tiles, 256);
         if (v == 1 ? tiles > 512 : rounds > most_rounds) continue;
-        const double t = v == 1 && tiles > 256 ? 4.3 + 0.17 * steps : rounds * (FEW[v].fixed + FEW[v].step * steps);
+        double t = v == 1 && tiles > 256 ? 4.3 + 0.17 * steps : rounds * (FEW[v].fixed + FEW[v].step * steps);
+        if (geglu) t = rounds * (3.4 + 0.2 * steps);
         if (t < *us) { *us = t; best = v; }
     }
     return best;

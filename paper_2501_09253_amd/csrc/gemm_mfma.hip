@@ -1299,11 +1299,11 @@ int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
     if (a.epi == EPI_GEGLU) {
         if (a.N % 128 != 0) return PSERVE_OK;
         *handled = true;
-        // The epilogue (GELU of every gate) is as long as the main loop at K = 640: with at least a round of 128-row
-        // tiles, two blocks per CU, one block's epilogue runs beside the other's main loop (163 -> 142 us at
-        // 13,312 x 5,120 x 640); the wavefront tile is then 32 x 128 = [64 values | 64 gates]
-        if (cdiv(a.M, 128) * (a.N / 128) >= 512) return launch<128, 128, true, 4, 1, 2, false>(a, st);
-        return launch<256, 128, true, 4, 1, 2, true>(a, st);
+        // The epilogue (GELU of every gate) is as long as the main loop at K = 640: two blocks of 128 rows a CU, so that one
+        // block's epilogue runs beside the other's main loop, and with fewer tiles on one block a CU.  The wavefront tile is 32 x
+        // 128 = [64 values | 64 gates].  us, 256 x 128 tiles (one block a CU, before) / these: 512 x 7,680, K = 960 20.4 / 15.7; 512 x 10,240,
+        // K = 1,280 25.8 / 22.3; 1,024 x 5,120, K = 640 18.8 / 16.0; 13,312 x 5,120, K = 640 163 / 142.
+        return launch<128, 128, true, 4, 1, 2, false>(a, st);
     }
     if (a.seg_cols % 32 != 0) return PSERVE_OK;      // a 32-column tile must not straddle output segments
     int splits = 1;
@@ -1317,44 +1317,28 @@ int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
     case 6: *handled = true; return launch_conv<256, 160, 4, 1, 416, 2, 2>(a, ct, splits, st);
     default: break;
     }
-    // Tile choice.  Two blocks of 128 rows per CU where they fit (one block's prologue and epilogue run beside the
-    // other's main loop), 256-row tiles with one block per CU (two stages, the next tile's first loads issued before
-    // the epilogue) where the rounds of tiles come out better, and for few rows altogether (the text-token
-    // projections) the narrowest tile.
-    const int64_t m256 = cdiv(a.M, 256), m128 = cdiv(a.M, 128);
+    // Tile choice: two blocks of 128 rows a CU (one block's prologue and epilogue run beside the other's main loop).
+    const int64_t m128 = cdiv(a.M, 128), classes = std::max(1, a.classes);
+    const int64_t t160 = a.N % 160 == 0 ? m128 * (a.N / 160) * classes : 0, t128 = a.N % 128 == 0 ? m128 * (a.N / 128) * classes : 0;
     *handled = true;
-    const bool has_t = a.seg[0].transposed || a.seg[1].transposed || a.seg[2].transposed;
-    // N a multiple of 160: 128 x 160 tiles, two blocks per CU (wavefront tile 32 x 160).  Against the 256 x 160 tile
+    // N a multiple of 160: 128 x 160 tiles (wavefront tile 32 x 160).  Against a 256 x 160 tile
     // the rounds were the same: 34 -> 28 us (13,312 x 640 x 640), 68 -> 63 us (K = 2560), 80 -> 72 us
-    // (13.4 k x 1280 x 1280), 165 -> 137 us (79 k x 640 x 640).  The fused q/k/v projections (N = 1920, 3840, with the
-    // transposed V^T segment and its long epilogue of 8-byte stores) gain 6-11 % over 128 x 128 tiles as well.
+    // (13.4 k x 1280 x 1280), 165 -> 137 us (79 k x 640 x 640).
     // From 208 tiles on: the 128 x 64 tiles, 2.5 times as many, run 512 at a time, so up to 204 of these they take one round
     // and then two.  us, 128 x 160 / 128 x 64: 200 tiles K = 320 16.8 / 13.1, 640 20.1 / 15.8, 1280 26.6 / 22.8, 2560 40.3 / 33.8,
     // 5120 69.3 / 59.5; 204 tiles K = 640 18.9 / 16.8; 208 tiles 17.0 / 17.4, 20.2 / 21.0, 27.0 / 30.0, 42.7 / 46.3, 69.3 / 82.6.
-    if (a.N % 160 == 0 && m128 * (a.N / 160) * std::max(1, a.classes) >= 208) return launch<128, 160, false, 4, 1, 2, false>(a, st);
-    const int64_t tiles128 = a.N % 128 == 0 ? m128 * (a.N / 128) : 0;
-    // a transposed segment otherwise: 128 x 128, two blocks per CU (70 -> 62 us and 212 -> 184 us against 256-row tiles)
-    if (has_t && tiles128 >= 512) return launch<128, 128, false, 2, 2, 2, false>(a, st);
-    // Tile-count quantisation decides between the 256-row tiles (one block per CU: a started round of 256 tiles costs a
-    // whole round) and 128 x 128 with two blocks per CU (512 per round; a last round that is at most half full leaves
-    // one block per CU, which runs faster alone: about 0.65 of a round).  A full round of either does the same work
-    // in about the same time (measured at K = 1536 and 6144), so the cost is rounds x outputs per CU and round.
-    if (a.N % 128 == 0 && m256 * (a.N / 128) >= 160) {
-        const int64_t tiles_a = m256 * (a.N / 128);
-        if (tiles128 >= 512) {
-            const double cost_a = (double)cdiv(tiles_a, 256) * 256 * 128;
-            const int64_t full = tiles128 / 512, rest = tiles128 % 512;
-            const double cost_b = ((double)full + (rest == 0 ? 0.0 : (rest <= 256 ? 0.65 : 1.0))) * 2 * 128 * 128;
-            if (cost_b < cost_a) return launch<128, 128, false, 2, 2, 2, false>(a, st);
-        }
-        return launch<256, 128, false, 4, 1, 2, true>(a, st);
-    }
-    const bool small = a.N % 64 == 0 && m128 * cdiv(a.N, 320) < 128;
-    if (!small) {                                               // (multiples of 320 are taken above)
-        if (a.N % 256 == 0) return launch<128, 256, false, 2, 2, 2, true>(a, st);
-        if (a.N % 128 == 0) return launch<128, 128, false, 2, 2, 3, true>(a, st);
-    }
-    if (a.N % 64 == 0) return launch<128, 64, false, 2, 2, 3, false>(a, st);
+    // But where 128 x 128 tiles still run in one round and these have CUs with two: 9,000 x 640, K = 640 20.3 / 128 x 128 18.4; 6,000 x
+    // 1,280, K = 1,280 32.5 / 30.2; 1,536 x 3,840 29.2 / 26.6 (4,096 x 1,280, K = 5,120, 256 tiles: 67.8 / 74.2).
+    const bool one_round = t128 > 256 && t128 <= 512;
+    if (t160 >= 208 && !(one_round && t160 > 256)) return launch<128, 160, false, 4, 1, 2, false>(a, st);
+    // 128 x 128 tiles from where they do not fit one block a CU.  us, these / 256 x 128 (one block a CU) / 128 x 64: 306 tiles K = 384
+    // 14.6 / 19.4 / 16.5, 480 K = 768 22.6 / 26.2 / 28.3, 576 K = 1,536 48.9 / 56.9 / 50.5, 816 K = 512 31.2 / 36.4 / 37.3, 1,278 K = 768
+    // 49.6 / 60.5 / 60.3.  With fewer, 128 x 64 (204 tiles K = 128 8.5 / 11.9 / 8.9, 120 K = 1,536 22.3 / - / 15.4), unless the chain of
+    // steps is long and these have CUs with two blocks: then 128 x 128 with three stages, one block a CU (144 tiles K = 3,072 28.6 / 31.7).
+    if (t128 > 256) return launch<128, 128, false, 2, 2, 2, false>(a, st);
+    const int64_t t64 = a.N % 64 == 0 ? m128 * (a.N / 64) * classes : 0;
+    if (t128 && t64 > 256 && (int64_t)a.taps * (a.K / 64) >= 32) return launch<128, 128, false, 2, 2, 3, true>(a, st);
+    if (t64) return launch<128, 64, false, 2, 2, 3, false>(a, st);
     *handled = false;
     return PSERVE_OK;
 }

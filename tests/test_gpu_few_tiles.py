@@ -90,6 +90,26 @@ def test_few_tiles_between_levels(res, patch, C):
         assert np.isfinite(err) and err < tolerance("bf16"), (op, err)
 
 
+# 128 x 128 tiles, two blocks a CU, where they are more than 256 and run in one round (and one block a CU where the chain of steps is
+# long); value-gate pairs on 128 x 128 tiles with fewer than that.
+TILES_128 = {
+    "qkv": dict(res=[(24, 24)] * 3 + [(8, 16)], patch=(8, 8), C=768, stages=("LSATTN",)),
+    "qkv_masked": dict(res=[(32, 32), (28, 28)], patch=(4, 4), C=768, stages=("SATTN",), reuse_p=0.3),
+    "residual": dict(res=[(96, 96), (64, 64)], patch=(32, 32), C=384, stages=("XATTN",), ctx_len=20, ctx_dim=64),
+    "gate": dict(res=[(24, 24)] * 4, patch=(12, 12), C=768, stages=("AMLP",), temb_dim=64),
+    "geglu": dict(res=[(28, 28), (12, 12)], patch=(4, 4), C=640, stages=("LFFN",)),
+    "long_chain": dict(res=[(64, 66)], patch=(8, 6), C=512, stages=("LFFN",)),
+}
+
+
+@pytest.mark.parametrize("name", list(TILES_128))
+def test_128_row_tiles(name):
+    c = dict(TILES_128[name])
+    C = c.pop("C")
+    cfg = wl.custom_config(c.pop("res"), c.pop("patch"), C=C, G=32, heads=C // 64, stages=c.pop("stages"), dtype="bf16", seed=63, **c)
+    _check(wl.make_workload(cfg))
+
+
 # Both streams of a joint block in one launch a layer below the sizes of the wide tiles: rows of image and text that end inside
 # tiles, and every tile that takes them.
 @pytest.mark.parametrize("res,patch,C,L,tiles", [([(8, 8), (8, 16)], (8, 8), 64, 7, (-1, -1, -1, -1)), ([(24, 12), (12, 24)], (12, 12), 256, 200, (-4, -2, 64, -2)),
