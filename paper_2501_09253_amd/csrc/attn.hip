@@ -10,6 +10,7 @@
 //
 // Softmax runs in base 2 on logits pre-multiplied by log2(e)/sqrt(d) (done by the Q projection).
 #include "kernels.h"
+#include <type_traits>
 
 namespace pserve {
 
@@ -376,13 +377,16 @@ extern "C" int pserve_test_attn_transposed(const pserve_plan_t* plan, const void
 // registers.  Two blocks a CU.  A step forms the scores of the NEXT tile while the softmax of this one runs (24 MFMAs beside
 // most of its ~270 vector instructions), then the output products; keys and values have rings of three stages of their own,
 // filled two steps ahead.  The softmax reference moves only when a score passes it by 8 (a factor of 256 costs fp32 nothing).
-// Requests of 4,096 and 3,072 tokens, 5 heads of 64 (280 blocks of 128 and 96 tiles): 360 (fp32 kernel) -> 231 us = 145 TFLOP/s of
-// fp32; bound by the issue of MFMAs (1,536 clocks a tile) and vector instructions and by 280 blocks on 256 CUs.
+// Requests of 4,096 and 3,072 tokens, 5 heads of 64 (280 items of 128 and 96 tiles): 360 (fp32 kernel) -> 234 us, a block an item ->
+// 189 + 13 us, 512 equal shares (145 -> 166 TFLOP/s of fp32).  Bound by the issue of MFMAs (1,536 of 2,770 clocks a tile) and vector
+// instructions, with every CU busy by the clock (2.15 GHz with 160 CUs busy, 1.8 with all).
 constexpr int ASP_NS = 3;
+constexpr int AT_SHARES = 512;       // shares of a call (a multiple of 8)
 template <int D> struct AttnSplitCfg {
     static constexpr int KV = 3 * 32 * D / 8, TILE_V = 2 * KV;       // 16-byte slots of the keys, of a tile
     static constexpr int LPT = TILE_V / 256;                         // direct loads of a wavefront and tile
     static constexpr size_t LDS = (size_t)ASP_NS * TILE_V * 16;
+    static constexpr int PART = (D / 2 + 2) * 256;                   // floats of a partial result: 256 lanes' outputs, references, sums
 };
 typedef __attribute__((ext_vector_type(8))) __bf16 at_bf16x8;
 typedef __attribute__((ext_vector_type(4))) uint32_t at_u32x4;
@@ -391,11 +395,13 @@ template <int D> __device__ __forceinline__ int at_swz(int row) { return D == 64
 // first tile of request slot s: room for the tiles of all slots before it
 __device__ __forceinline__ int64_t at_tile0(const int32_t* cu_seqlens, int s) { return cu_seqlens[s] / 32 + s; }
 // three pieces of eight values
+template <bool PLAIN = false>
 __device__ __forceinline__ void at_cut(const float (&x)[8], at_u32x4 (&o)[3]) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         uint32_t u[3];
-        cut3x2(x[2 * q], x[2 * q + 1], u);
+        if constexpr (PLAIN) cut3x2_plain(x[2 * q], x[2 * q + 1], u);
+        else cut3x2(x[2 * q], x[2 * q + 1], u);
 #pragma unroll
         for (int p = 0; p < 3; ++p) o[p][q] = u[p];
     }
@@ -448,9 +454,51 @@ attn_cut_kernel(const float* __restrict__ K, const float* __restrict__ V, const 
     }
 }
 
+// O of a lane's query (column fr of the output tiles), scaled
 template <int D>
+__device__ __forceinline__ void at_store(const AttnArgs& a, const at_f32x16 (&ot)[D / 32], float inv, bool mine, int64_t tok, int h, int fh) {
+    constexpr int DT = D / 32;
+    const int C = a.C;
+    if (mine) {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int c = h * D + 32 * dt + 8 * g + 4 * fh;
+                const at_f32x4 v = {ot[dt][4 * g] * inv, ot[dt][4 * g + 1] * inv, ot[dt][4 * g + 2] * inv, ot[dt][4 * g + 3] * inv};
+                if (a.out_pieces) store_pieces4((uint16_t*)a.O + tok * 3 * C + piece_index(c), v.x, v.y, v.z, v.w);
+                else *reinterpret_cast<at_f32x4*>((float*)a.O + tok * C + c) = v;
+            }
+    }
+}
+
+// The work of a call is a row of units (32 keys of an item): slot by slot, head by head, 128 queries by 128 queries, cut into
+// equal shares, one a block.  Items that a cut goes through leave partial results, which attn_join_kernel puts together.
+struct AttnUnit { int s, h, tile, nq, nk, steps, k; int64_t first; };    // slot, head, query tile of nq, keys, unit k of steps; the item's first unit
+__device__ __forceinline__ AttnUnit at_unit(const AttnArgs& a, int64_t u) {
+    AttnUnit r;
+    int lo = 0, hi = a.n;                               // largest s with unit_off[s] <= u
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (a.unit_off[mid] <= u) lo = mid; else hi = mid;
+    }
+    r.s = __builtin_amdgcn_readfirstlane(lo);
+    r.nk = a.seq_len ? a.seq_len[r.s] : a.cu_seqlens[r.s + 1] - a.cu_seqlens[r.s];
+    r.steps = (r.nk + 31) / 32;
+    r.nq = ((a.act_off[r.s + 1] - a.act_off[r.s]) * a.geom.S + 127) / 128;
+    const int64_t in = u - a.unit_off[r.s], item = in / r.steps;
+    r.k = (int)(in - item * r.steps);
+    r.h = (int)(item / r.nq);
+    r.tile = (int)(item - (int64_t)r.h * r.nq);
+    r.first = u - r.k;
+    return r;
+}
+__device__ __forceinline__ int64_t at_share(int64_t units, int b, int blocks) { return units * b / blocks; }
+
+// SHARED: a block takes a share of the units; else an item, longest first.
+template <int D, bool SHARED>
 __global__ void __launch_bounds__(256, 2)
-attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv) {
+attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv, float* __restrict__ parts) {
     using Cfg = AttnSplitCfg<D>;
     constexpr int KS = D / 16, DT = D / 32, LPT = Cfg::LPT, TILE_V = Cfg::TILE_V, KV = Cfg::KV;
     extern __shared__ __attribute__((aligned(16))) float at_smem[];
@@ -458,18 +506,34 @@ attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int fr = lane & 31, fh = lane >> 5;
-    const int seq = blockIdx.x >> 3, grp = seq / a.group;
-    const int it = (grp * 8 + (blockIdx.x & 7)) * a.group + (seq - grp * a.group);
-    int s, h, tile;
-    if (!attn_item_at(a, it / a.qt, s, h, tile)) return;
     const int S = a.geom.S, C = a.C;
-    const int rows_s = (a.act_off[s + 1] - a.act_off[s]) * S;
-    const int r0 = (tile * a.qt + it % a.qt) * 128;
-    if (r0 >= rows_s) return;
-    const int64_t k0 = a.cu_seqlens[s];
-    const int nk = a.seq_len ? a.seq_len[s] : a.cu_seqlens[s + 1] - (int)k0;
-    const int steps = (nk + 31) / 32;
-    const at_u32x4* src = tiles_kv + (at_tile0(a.cu_seqlens, s) * a.heads + h) * TILE_V;
+    // an XCD's blocks take neighbouring shares: they stream the keys of the same few heads through its L2
+    const int nb = gridDim.x, b = (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3);
+    int64_t u = 0, u1 = 1;
+    if constexpr (SHARED) {
+        const int64_t units = a.unit_off[a.n];
+        u = at_share(units, b, nb);
+        u1 = at_share(units, b + 1, nb);
+    }
+#pragma unroll 1
+    while (u < u1) {
+    AttnUnit w{};
+    if constexpr (SHARED) {
+        w = at_unit(a, u);
+    } else {
+        const int seq = blockIdx.x >> 3, grp = seq / a.group, it = (grp * 8 + (blockIdx.x & 7)) * a.group + (seq - grp * a.group);
+        if (!attn_item_at(a, it / a.qt, w.s, w.h, w.tile)) return;
+        w.tile = w.tile * a.qt + it % a.qt;
+        w.nk = a.seq_len ? a.seq_len[w.s] : a.cu_seqlens[w.s + 1] - a.cu_seqlens[w.s];
+        w.steps = (w.nk + 31) / 32;
+    }
+    const int s = w.s, h = w.h, r0 = w.tile * 128, rows_s = (a.act_off[s + 1] - a.act_off[s]) * S;
+    if (!SHARED && r0 >= rows_s) return;
+    const int steps = SHARED ? (int)min((int64_t)(w.steps - w.k), u1 - u) : w.steps;    // tiles of this share, and the keys from its first on
+    const int nk = w.nk - w.k * 32;
+    const bool whole = !SHARED || steps == w.steps;
+    u += steps;
+    const at_u32x4* src = tiles_kv + ((at_tile0(a.cu_seqlens, s) + w.k) * a.heads + h) * TILE_V;
     const int64_t src_step = (int64_t)a.heads * TILE_V;
     // Keys of tile tk and values of tile tv into stages of their own (past the end: the last tile again, never read).  Buffer
     // loads: behind flat ones the compiler waits for all LDS reads in flight instead of counting them.
@@ -500,15 +564,28 @@ attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv) {
     at_bf16x8 q[3][KS];
     {
         const float* qp = (const float*)a.Q + tok * C + h * D + 8 * fh;
+        float x[KS][8];
+        bool plain = true;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             const at_f32x4 w0 = *reinterpret_cast<const at_f32x4*>(qp + 16 * ks), w1 = *reinterpret_cast<const at_f32x4*>(qp + 16 * ks + 4);
-            const float x[8] = {w0[0], w0[1], w0[2], w0[3], w1[0], w1[1], w1[2], w1[3]};
-            at_u32x4 o[3];
-            at_cut(x, o);
 #pragma unroll
-            for (int p = 0; p < 3; ++p) q[p][ks] = __builtin_bit_cast(at_bf16x8, o[p]);
+            for (int i = 0; i < 4; ++i) { x[ks][i] = w0[i]; x[ks][4 + i] = w1[i]; }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) plain = plain && cut_is_plain(x[ks][2 * i], x[ks][2 * i + 1]);
         }
+        // one branch for all values (one a pair costs 6,000 clocks a share; the loop over 32 keys 2,770)
+        auto cut_all = [&](auto plain_c) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                at_u32x4 o[3];
+                at_cut<decltype(plain_c)::value>(x[ks], o);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) q[p][ks] = __builtin_bit_cast(at_bf16x8, o[p]);
+            }
+        };
+        if (__all(plain)) cut_all(std::true_type{});
+        else cut_all(std::false_type{});
     }
     const int krow = (fr & ~12) | ((fr & 4) << 1) | ((fr & 8) >> 1);         // key of MFMA row fr (bits 2 and 3 swapped)
     const at_u32x4* pK = ring + krow * (3 * D / 8);
@@ -593,7 +670,7 @@ attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv) {
                     o[dt][e] = ol[dt][e] = 0.f;
                 }
         }
-        const float hm = -0.5f * m;
+        const float hm = m == -INFINITY ? 0.f : -0.5f * m;      // (no score above -infinity yet: probabilities of zero)
         // The next tile's scores, and behind each MFMA up to five of this tile's vector instructions (about four are free, and none
         // where there is no MFMA: as two phases a tile took 3,360 clocks of which 1,536 are MFMAs) and a fragment read for six MFMAs
         // later: the probabilities in pairs, in four (D = 32: two) steps each; those that the first output products do not need
@@ -655,20 +732,59 @@ attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv) {
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
         for (int e = 0; e < 16; ++e) ot[dt][e] += o[dt][e] + ol[dt][e];
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // no load may still target LDS when the block retires
+    // no load may still target LDS, and nobody may still read it, when the next share of an item starts
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
     l += __shfl_xor(l, 32, 64);
-    const float inv = 1.f / l;
-    if (my_row < rows_s) {
+    if (!whole) {                                       // place 2 b: of the item that the block's share starts in, 2 b + 1: of its last
+        float* dst = parts + (int64_t)(2 * b + (w.k == 0)) * Cfg::PART + tid;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int c = h * D + 32 * dt + 8 * g + 4 * fh;
-                const at_f32x4 v = {ot[dt][4 * g] * inv, ot[dt][4 * g + 1] * inv, ot[dt][4 * g + 2] * inv, ot[dt][4 * g + 3] * inv};
-                if (a.out_pieces) store_pieces4((uint16_t*)a.O + tok * 3 * C + piece_index(c), v.x, v.y, v.z, v.w);
-                else *reinterpret_cast<at_f32x4*>((float*)a.O + tok * C + c) = v;
-            }
+            for (int e = 0; e < 16; ++e) dst[(16 * dt + e) * 256] = ot[dt][e];
+        dst[16 * DT * 256] = m;
+        dst[(16 * DT + 1) * 256] = l;
+        continue;
     }
+    at_store<D>(a, ot, 1.f / l, my_row < rows_s, tok, h, fh);
+    }
+}
+
+// Puts the items together that a cut between two shares goes through: block j those whose first cut is that behind share j.  The
+// parts come in a fixed order, each scaled to the common reference.
+template <int D>
+__global__ void __launch_bounds__(256)
+attn_join_kernel(AttnArgs a, const float* __restrict__ parts, int nb) {
+    using Cfg = AttnSplitCfg<D>;
+    constexpr int DT = D / 32;
+    const int j = blockIdx.x, tid = threadIdx.x, lane = tid & 63, fr = lane & 31, fh = lane >> 5;
+    const int64_t units = a.unit_off[a.n], cut = at_share(units, j + 1, nb);
+    if (cut >= units) return;
+    const AttnUnit w = at_unit(a, cut);
+    if (w.k == 0 || at_share(units, j, nb) > w.first) return;      // between two items; or not the item's first cut
+    int last = j + 1;                                   // the share that the item ends in
+    while (at_share(units, last + 1, nb) < w.first + w.steps) ++last;
+    const int rows_s = (a.act_off[w.s + 1] - a.act_off[w.s]) * a.geom.S;
+    const int my_row = w.tile * 128 + (tid >> 6) * 32 + fr, row = min(my_row, rows_s - 1), S = a.geom.S;
+    const int pi = a.act_off[w.s] + row / S;
+    const int64_t tok = (int64_t)(a.act.active ? a.act.active[pi] : pi) * S + row % S;
+    auto part = [&](int b) { return parts + (int64_t)(2 * b + (b == j)) * Cfg::PART + tid; };
+    float m = -INFINITY, l = 0.f;
+    for (int b = j; b <= last; ++b) m = fmaxf(m, part(b)[16 * DT * 256]);
+    at_f32x16 o[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[dt][e] = 0.f;
+    for (int b = j; b <= last; ++b) {
+        const float* src = part(b);
+        const float mb = src[16 * DT * 256], f = mb == -INFINITY ? 0.f : exp2_square(0.5f * (mb - m));
+        l = fmaf(src[(16 * DT + 1) * 256], f, l);
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) o[dt][e] = fmaf(src[(16 * dt + e) * 256], f, o[dt][e]);
+    }
+    at_store<D>(a, o, 1.f / l, my_row < rows_s, tok, w.h, fh);
 }
 
 template <int D>
@@ -678,11 +794,19 @@ static int attn_split(const AttnArgs& a, hipStream_t st) {
     attn_cut_kernel<D><<<dim3((unsigned)tiles, (unsigned)a.heads), 4 * D, 0, st>>>((const float*)a.K, (const float*)a.V, a.cu_seqlens,
         a.seq_len, a.n, a.C, (at_u32x4*)a.cut);
     PS_TRY(check_launch("attn_cut_kernel"));
-    PS_SET_LDS_ONCE((attn_split_kernel<D>), Cfg::LDS);
+    if (a.shares) {
+        float* parts = (float*)((at_u32x4*)a.cut + tiles * a.heads * Cfg::TILE_V);
+        PS_SET_LDS_ONCE((attn_split_kernel<D, true>), Cfg::LDS);
+        attn_split_kernel<D, true><<<(unsigned)a.shares, 256, Cfg::LDS, st>>>(a, (const at_u32x4*)a.cut, parts);
+        PS_TRY(check_launch("attn_split_kernel"));
+        attn_join_kernel<D><<<(unsigned)a.shares - 1, 256, 0, st>>>(a, parts, a.shares);
+        return check_launch("attn_join_kernel");
+    }
     AttnArgs b = a;
     const int64_t items = (int64_t)a.max_tiles * a.qt * a.heads;
     b.group = (int)std::min<int64_t>(8, cdiv(items, 8));
-    attn_split_kernel<D><<<(unsigned)(8 * b.group * cdiv(items, 8 * b.group)), 256, Cfg::LDS, st>>>(b, (const at_u32x4*)a.cut);
+    PS_SET_LDS_ONCE((attn_split_kernel<D, false>), Cfg::LDS);
+    attn_split_kernel<D, false><<<(unsigned)(8 * b.group * cdiv(items, 8 * b.group)), 256, Cfg::LDS, st>>>(b, (const at_u32x4*)a.cut, nullptr);
     return check_launch("attn_split_kernel");
 }
 
@@ -696,13 +820,46 @@ static int attn_split(const AttnArgs& a, hipStream_t st) {
 size_t attention_cut_bytes(const pserve_plan_t* plan, int32_t C, int32_t heads, int dtype, int mode) {
     if (dtype != PSERVE_F32 || mode != 0 || C % heads != 0 || (C / heads != 32 && C / heads != 64)) return 0;
     if ((int64_t)attention_max_tiles(plan, 1) * heads < (C / heads == 32 ? 129 : 128) || plan->max_tokens_per_image < 1024) return 0;
-    return (size_t)(plan->T / 32 + plan->n) * C * 32 * 12;
+    const size_t part = (C / heads == 32 ? AttnSplitCfg<32>::PART : AttnSplitCfg<64>::PART) * sizeof(float);
+    return (size_t)(plan->T / 32 + plan->n) * C * 32 * 12 + 2 * attention_shares(plan, C, heads) * part;
+}
+
+// Blocks that share out the units of such a call equally, 0: a block an item.  In tiles of one CU (1.25 us with 64 channels a head,
+// 0.76 with 32; two blocks a CU give 7 % more than one, an item's start and end is an eighth of 70 tiles): items 256 at a time, the
+// longest first; shares their mean, cutting and joining.  us of an LSATTN layer, items / shares: 64 channels: 4,096 tokens, 4 heads 193 / 143,
+// 5 heads 207 / 179, 2 x 4,096 366 / 326, 4,096 + 3,072 312 / 273, 4 x 4,096 632 / 611, 8 x 4,096 1,121 / 1,159, 16,384 1,916 / 1,768; 32 channels: 4,096,
+// 5 heads 139 / 104, 9,216 433 / 363, 2 x 2,304 97 / 89, 5 x 1,024 67 / 72, 3 x 4,096 251 / 258, 6 x 4,096 472 / 480.
+int attention_shares(const pserve_plan_t* plan, int32_t C, int32_t heads) {
+    struct Len { int64_t steps, items; };
+    std::vector<Len> len;
+    int64_t items = 0, units = 0;
+    const int32_t *ro = plan->h_tab[PSERVE_TAB_REQUEST_OFFSET], *sl = plan->h_tab[PSERVE_TAB_SEQ_LEN];
+    for (int s = 0; s < plan->n; ++s) {
+        const int64_t rows = (int64_t)(ro[s + 1] - ro[s]) * plan->S;
+        len.push_back({cdiv(sl[s], 32), cdiv(rows, 128) * heads});
+        items += len.back().items;
+        units += len.back().items * len.back().steps;
+    }
+    std::sort(len.begin(), len.end(), [](const Len& x, const Len& y) { return x.steps > y.steps; });
+    auto nth = [&](int64_t k) -> double {               // steps of item k, longest first
+        for (const Len& l : len) {
+            if (k < l.items) return (double)l.steps;
+            k -= l.items;
+        }
+        return 0.0;
+    };
+    const int64_t full = items / 512, rest = items % 512;
+    const double mean = items ? (double)units / items : 0.0, first = full ? mean : nth(0), second = full ? mean : nth(256);
+    const double by_item = full * 2 * mean + (rest == 0 ? 0.0 : rest <= 256 ? 1.12 * first : first + second);
+    return 1.03 * units / 256 + (C / heads == 32 ? 26 : 28) < by_item ? AT_SHARES : 0;
 }
 
 // For tests (host only, no part of the ABI): whether the fp32 self-attention of a plan goes to the bf16 matrix cores
 extern "C" int pserve_test_attn_cut(const pserve_plan_t* plan, int32_t C, int32_t heads) {
     return attention_cut_bytes(plan, C, heads, PSERVE_F32, 0) != 0;
 }
+// ... and in how many shares (0: a block an item)
+extern "C" int pserve_test_attn_shares(const pserve_plan_t* plan, int32_t C, int32_t heads) { return attention_shares(plan, C, heads); }
 
 int attention_mfma_bf16(const AttnArgs& a, hipStream_t st, bool* handled);     // attn_mfma.hip
 

@@ -330,6 +330,8 @@ struct pserve_cache_s {
     int32_t* count = nullptr;
     int32_t* act_off = nullptr;               // [n+1] attention: computed patches before slot s
     int32_t* tile_off = nullptr;              // [n+1] attention: query tiles before slot s
+    int32_t att_shares = 0;                   // fp32 attention in pieces: attention_shares
+    int64_t* unit_off = nullptr;              // [n+1] ... units before slot s (with shares)
     int32_t max_tiles = 0;
     int32_t att_qt = 2;                       // query tile of the MFMA attention: 128 * att_qt rows
     bool tiles_unmasked = false;              // act_off / tile_off hold the tiling of a call without mask
@@ -725,6 +727,8 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
         if (sattn)
             if (const size_t bytes = !pieces ? 0 : attention_cut_bytes(plan, d.C, d.heads, d.dtype, g_kernel_mode == 1 ? 1 : 0))
                 PS_TRY(c->pool.alloc(&c->cut, bytes));
+        if (c->cut && (c->att_shares = attention_shares(plan, d.C, d.heads)) != 0)
+            PS_TRY(c->pool.alloc_t(&c->unit_off, (size_t)plan->n + 1));
     }
     if (ffn) PS_TRY(c->pool.alloc(&c->hidden, (size_t)plan->T * d.ffn_mult * d.C * elem(c->hidden_pieces)));
     if (with_slots) PS_TRY(c->pool.alloc(&c->yslot, TC));
@@ -948,7 +952,9 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
     if (cache->act_off && (reuse_mask || !cache->tiles_unmasked)) {
         // without a mask the query tiling depends on the plan only: built once and kept
         ProfScope ps("attn_tiles", st);
-        PS_TRY(attention_tiles(request_offset, reuse_mask, plan->n, plan->S, cache->att_qt, cache->act_off, cache->tile_off, st));
+        PS_TRY(attention_tiles(request_offset, reuse_mask, plan->n, plan->S, cache->att_qt, cache->act_off, cache->tile_off, st, cache->unit_off,
+                               plan->d_tab[PSERVE_TAB_CU_SEQLENS], d.stages[0] == PSERVE_MMDIT ? plan->d_tab[PSERVE_TAB_SEQ_LEN] : nullptr,
+                               d.heads));
         cache->tiles_unmasked = reuse_mask == nullptr;
     }
     const ActiveList all{nullptr, nullptr};
@@ -1105,7 +1111,7 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         aa.cross_len = cross ? d.ctx_len : 0; aa.cross_ld = cross ? cache->cross_ld : 0;
         aa.act_off = cache->act_off; aa.tile_off = cache->tile_off; aa.n = plan->n; aa.max_tiles = cache->max_tiles;
         aa.qt = cache->att_qt; aa.max_rows = plan->max_tokens_per_image; aa.out_pieces = out_pieces;
-        aa.cut = cache->cut;
+        aa.cut = cache->cut; aa.unit_off = cache->unit_off; aa.shares = cache->att_shares;
         ProfScope ps(cross ? "attn_cross" : "attn_self", st);
         return attention(aa, dt, mode, st);
     };

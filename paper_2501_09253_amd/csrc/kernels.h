@@ -43,12 +43,16 @@ __device__ __forceinline__ float hi_bf16(uint32_t u) { return __uint_as_float(u 
 // which is zero or has the factor's sign, so infinities and NaN come out as those of the plain product.  (A finite product within
 // 1 % of the largest number may come out infinite: x0 y0 may be that much larger.)
 constexpr float PIECE_TINY = 1.17549435e-38f, PIECE_MAX = 3.38953139e38f;       // smallest normal, largest bf16 number
+__device__ __forceinline__ bool cut_is_plain(float a, float b) { return fabsf(a) + fabsf(b) <= PIECE_MAX; }
+__device__ __forceinline__ void cut3x2_plain(float a, float b, uint32_t (&u)[3]) {     // where cut_is_plain
+    u[0] = near_bf16x2(a, b);
+    const float ra = a - lo_bf16(u[0]), rb = b - hi_bf16(u[0]);
+    u[1] = near_bf16x2(ra, rb);
+    u[2] = near_bf16x2(ra - lo_bf16(u[1]), rb - hi_bf16(u[1]));
+}
 __device__ __forceinline__ void cut3x2(float a, float b, uint32_t (&u)[3]) {
-    if (fabsf(a) + fabsf(b) <= PIECE_MAX) {
-        u[0] = near_bf16x2(a, b);
-        const float ra = a - lo_bf16(u[0]), rb = b - hi_bf16(u[0]);
-        u[1] = near_bf16x2(ra, rb);
-        u[2] = near_bf16x2(ra - lo_bf16(u[1]), rb - hi_bf16(u[1]));
+    if (cut_is_plain(a, b)) {
+        cut3x2_plain(a, b, u);
         return;
     }
     // not finite, or large (the largest values would round to infinity)
@@ -252,11 +256,13 @@ struct AttnArgs {
     // query tiling of the MFMA kernel (attention_tiles fills the two prefix tables)
     const int32_t* act_off;    // [n+1] computed patches before slot s (== RequestOffset without a mask)
     const int32_t* tile_off;   // [n+1] query tiles before slot s
+    const int64_t* unit_off;   // [n+1] fp32 attention in pieces: units (32 keys of 128 queries of a head) before slot s
     int32_t n;                 // request slots
     int32_t max_tiles;         // host upper bound of tile_off[n]
     int32_t qt;                // 1 or 2: the tables were built for query tiles of 128 * qt rows
     int32_t max_rows;          // host upper bound of the query rows of one request (its tokens)
     int32_t group;             // consecutive work items dealt to an XCD at a time (filled in by the launch)
+    int32_t shares;            // fp32 attention in pieces: attention_shares, with unit_off
     int32_t out_pieces;        // fp32: O is written as bf16 pieces
     void* cut;                 // fp32 self-attention: scratch of attention_cut_bytes, nullptr: the fp32 kernel
 };
@@ -280,11 +286,15 @@ __device__ __forceinline__ bool attn_item_at(const AttnArgs& a, int64_t k, int& 
     tile_in_s = r - head * tiles_s;
     return true;
 }
+// unit_off (optional, with the tables it takes): see AttnArgs
 int attention_tiles(const int32_t* request_offset, const uint8_t* mask, int32_t n, int32_t S, int32_t qt, int32_t* act_off,
-                    int32_t* tile_off, hipStream_t st);
+                    int32_t* tile_off, hipStream_t st, int64_t* unit_off = nullptr, const int32_t* cu_seqlens = nullptr,
+                    const int32_t* seq_len = nullptr, int32_t heads = 0);
 int attention_max_tiles(const pserve_plan_t* plan, int32_t qt);
 // scratch (keys and values in bf16 pieces) of an fp32 self-attention over this plan, 0: it takes the fp32 kernel
 size_t attention_cut_bytes(const pserve_plan_t* plan, int32_t C, int32_t heads, int dtype, int mode);
+// blocks that such an attention's work is shared out to (0: one an item)
+int attention_shares(const pserve_plan_t* plan, int32_t C, int32_t heads);
 int attention(const AttnArgs& a, int dtype, int mode, hipStream_t st);
 
 // ---- reuse (block.hip) -------------------------------------------------------------------------------

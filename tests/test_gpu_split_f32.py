@@ -257,3 +257,47 @@ def test_joint_attention_in_pieces():
     for a, b in zip(got, ref):
         err = rel_err([a], [b])
         assert np.isfinite(err) and err < 1e-6, err
+
+
+# the work in shares, cut through items, and a block an item: both sides of the rule, ragged last tiles of keys and of queries, masks
+SHARES = {
+    "d64_shared": dict(res=[(72, 41), (18, 23)], patch=(3, 1), C=320, heads=5, n=512),
+    "d32_shared": dict(res=[(44, 48), (4, 3)], patch=(4, 3), C=320, heads=10, n=512),
+    "d32_items": dict(res=[(32, 32)] * 5, patch=(8, 8), C=160, heads=5, n=0),
+    "d64_shared_mask": dict(res=[(64, 64), (8, 24)], patch=(8, 8), C=256, heads=4, reuse_p=0.4, n=512),
+}
+
+
+@pytest.mark.parametrize("name", list(SHARES))
+def test_attention_in_shares(name):
+    c = dict(SHARES[name])
+    n = c.pop("n")
+    cfg = wl.custom_config(c.pop("res"), c.pop("patch"), G=8, stages=("LSATTN",), dtype="f32", seed=101, **c)
+    plan = ps.Plan(cfg.resolutions, *cfg.patch)
+    assert ps.lib().pserve_test_attn_cut(plan._h, cfg.C, cfg.heads) == 1
+    assert ps.lib().pserve_test_attn_shares(plan._h, cfg.C, cfg.heads) == n
+    got, ref = _attn_run(cfg, wl.make_workload(cfg))
+    for a, b in zip(got, ref):
+        err = rel_err([a], [b])
+        assert np.isfinite(err) and err < 1e-6, err
+
+
+def test_share_that_starts_with_scores_of_minus_infinity():
+    """64 keys of which every score is -infinity, at the head of a share (32 tiles each): they count for nothing."""
+    cfg = wl.custom_config([(64, 64)], (8, 8), C=256, G=8, heads=4, stages=("LSATTN",), dtype="f32", reuse_p=0.5, seed=103)
+    assert ps.lib().pserve_test_attn_shares(ps.Plan(cfg.resolutions, 8, 8)._h, 256, 4) == 512
+    w = wl.make_workload(cfg)
+    p, d = w.params[0], 64
+    p["ln_g"][:] = 0.02 * p["ln_g"]
+    p["ln_b"][:] = 1
+    p["wq"][0, :] = 0
+    p["wq"][:, ::d] = 0
+    p["wq"][0, ::d] = 800.0                              # queries (about 800, ..)
+    w.reuse[0][:] = False
+    w.reuse[0][2, 0] = True                              # patch 16: tokens 1,024 .. 1,087
+    w.cache["0.K"][0][:, 16:24, 0:8] = 0
+    w.cache["0.K"][0][::d, 16:24, 0:8] = -3e38
+    p["wk"][:, ::d] *= 1e-3
+    got, ref = _attn_run(cfg, w)
+    assert np.isfinite(got[0]).all()
+    assert rel_err(got, ref) < 1e-5                      # logits of a few units more than elsewhere in this file
