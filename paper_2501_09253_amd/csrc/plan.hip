@@ -253,6 +253,76 @@ split_vec_kernel(ImagePtrs imgs, int slot0, int patch0, const int32_t* __restric
     }
 }
 
+// Any patch shape (C a multiple of 64): a channel's plane of an image is one run of H * W values, whatever the patches are, so a block
+// takes 128 bytes of it (64 bf16 pixels, 32 fp32) in 64 channels, VEC pixels an access, and the 128 or 256 bytes of 64 channels of each of
+// these pixels' tokens.  Transposed in LDS; 16-byte piece c of a pixel's row lies at c ^ (pixel / 16 bytes), so that neither side's accesses
+// meet in a bank.  us, rows of patches with two-byte accesses (split_kernel) / here:
+// 19,008 tokens x 512 in 12 x 12 patches 28.6 / 8.9 and back 22.2 / 7.3 (39 MB: 4.4 and 5.3 TB/s), 7,600 x 512 in 20 x 20 11.4 / 6.0 and 10.2 / 5.5,
+// fp32 7,168 x 320 in 16 x 16 12.5 / 7.1 and 8.6 / 5.6, 832 x 64 4.5 / 3.0 and 3.9 / 2.9.
+struct PlaneTiles {
+    int32_t end[IMG_CHUNK];   // tiles of the launch's requests up to and with this one
+};
+template <typename T, int VEC, bool TO_PATCH>
+__global__ void __launch_bounds__(256)
+split_plane_kernel(ImagePtrs imgs, PlaneTiles at, int slot0, const int32_t* __restrict__ sorted_hw,
+                   const int32_t* __restrict__ request_offset, int32_t ph, int32_t pw, int32_t C, T* __restrict__ x) {
+    constexpr int PX = 128 / sizeof(T), E = 16 / sizeof(T), LOADS = 64 * PX / VEC / 256, STORES = PX * 64 / E / 256;
+    struct alignas(VEC * sizeof(T)) Vec { T v[VEC]; };
+    struct alignas(16) Row { T v[E]; };
+    __shared__ __attribute__((aligned(16))) T tile[PX * 64];
+    __shared__ int32_t s_tok[PX];
+    const int tid = threadIdx.x, c0 = blockIdx.y * 64;
+    int k = 0;
+    while ((int)blockIdx.x >= at.end[k]) ++k;
+    const int q0 = ((int)blockIdx.x - (k ? at.end[k - 1] : 0)) * PX, s = slot0 + k;
+    const int H = sorted_hw[2 * s], W = sorted_hw[2 * s + 1], N = H * W;
+    T* img = (T*)imgs.p[k];
+    auto place = [&](int px, int ch) { return px * 64 + (((ch / E) ^ ((px / E) & 7)) * E) + ch % E; };
+    auto plane = [&](int i) { return img + (int64_t)(c0 + i / (PX / VEC)) * N + q0 + i % (PX / VEC) * VEC; };
+    Vec in[LOADS];
+    if (TO_PATCH) {
+#pragma unroll
+        for (int l = 0; l < LOADS; ++l) {
+            const int i = tid + 256 * l;
+            if (q0 + i % (PX / VEC) * VEC < N) in[l] = *reinterpret_cast<const Vec*>(plane(i));
+        }
+    }
+    if (tid < PX) {
+        const int q = min(q0 + tid, N - 1), Y = q / W, X = q - Y * W, r = Y / ph, c = X / pw;
+        s_tok[tid] = (request_offset[s] + r * (W / pw) + c) * (ph * pw) + (Y - r * ph) * pw + X - c * pw;
+    }
+    if (TO_PATCH) {
+#pragma unroll
+        for (int l = 0; l < LOADS; ++l) {
+            const int i = tid + 256 * l;
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) tile[place(i % (PX / VEC) * VEC + v, i / (PX / VEC))] = in[l].v[v];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int l = 0; l < STORES; ++l) {
+            const int i = tid + 256 * l, px = i / (64 / E), ch = i % (64 / E) * E;
+            if (q0 + px < N) *reinterpret_cast<Row*>(x + (int64_t)s_tok[px] * C + c0 + ch) = *reinterpret_cast<const Row*>(tile + place(px, ch));
+        }
+    } else {
+        __syncthreads();
+#pragma unroll
+        for (int l = 0; l < STORES; ++l) {
+            const int i = tid + 256 * l, px = i / (64 / E), ch = i % (64 / E) * E;
+            *reinterpret_cast<Row*>(tile + place(px, ch)) = *reinterpret_cast<const Row*>(x + (int64_t)s_tok[px] * C + c0 + ch);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int l = 0; l < LOADS; ++l) {
+            const int i = tid + 256 * l;
+            Vec out;
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) out.v[v] = tile[place(i % (PX / VEC) * VEC + v, i / (PX / VEC))];
+            if (q0 + i % (PX / VEC) * VEC < N) *reinterpret_cast<Vec*>(plane(i)) = out;
+        }
+    }
+}
+
 // Split (bf16 fast path) that also leaves the moments of every channel behind, for a GroupNorm that reads x next:
 // block = (patch, one of `nch` token chunks, 64 channels); it walks the chunk's 32-token tiles like split_vec_kernel
 // and keeps, per thread, the sums of (x - K) and (x - K)^2 of its eight channels (K = the channel's value in the
@@ -375,6 +445,25 @@ static int run_split(const pserve_plan_t* plan, void* const* images, int32_t C, 
             split_vec_kernel<TO_PATCH><<<vgrid, 256, 0, st>>>(ip, s0, patch0, plan->d_sorted_hw,
                 plan->d_tab[PSERVE_TAB_PATCH_OWNER], plan->d_tab[PSERVE_TAB_PATCH_RC], plan->ph, plan->pw, C, (uint16_t*)x);
             PS_TRY(check_launch("split_vec_kernel"));
+            continue;
+        }
+        // pixels an access of split_plane_kernel takes: all planes start at a multiple of as many
+        const int es = (int)dtype_size(dtype);
+        int px = C % 64 == 0 && ((uintptr_t)x & 15) == 0 ? 16 / es : 0;
+        PlaneTiles at{};
+        for (int s = s0, end = 0; s < s1; ++s) {
+            const int64_t N = (int64_t)plan->h_sorted_hw[2 * s] * plan->h_sorted_hw[2 * s + 1];
+            while (px > 1 && (N % px != 0 || ((uintptr_t)ip.p[s - s0] & (px * es - 1)))) px /= 2;
+            at.end[s - s0] = end += (int)cdiv(N, 128 / es);
+        }
+        if (px > 1) {
+            const dim3 pgrid((unsigned)at.end[s1 - s0 - 1], (unsigned)(C / 64));
+#define PS_PLANE(T_, V_) split_plane_kernel<T_, V_, TO_PATCH><<<pgrid, 256, 0, st>>>(ip, at, s0, plan->d_sorted_hw, \
+                             plan->d_tab[PSERVE_TAB_REQUEST_OFFSET], plan->ph, plan->pw, C, (T_*)x)
+            if (dtype == PSERVE_BF16) { if (px == 8) PS_PLANE(uint16_t, 8); else if (px == 4) PS_PLANE(uint16_t, 4); else PS_PLANE(uint16_t, 2); }
+            else { if (px == 4) PS_PLANE(float, 4); else PS_PLANE(float, 2); }
+#undef PS_PLANE
+            PS_TRY(check_launch("split_plane_kernel"));
             continue;
         }
         dim3 grid(npatch * plan->ph, (unsigned)cdiv(C, 64));
