@@ -7,6 +7,8 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from array import array
+from itertools import chain
 from typing import Dict, List, Optional, Sequence
 
 import numpy as np
@@ -147,6 +149,8 @@ def _check(status: int):
 
 def _stream() -> int:
     import torch
+    if torch.cuda.is_initialized():         # the handle alone: no Stream object per call (0.4 us against 1.3)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return torch.cuda.current_stream().cuda_stream
 
 
@@ -212,21 +216,32 @@ class Plan:
     """pserve_plan: Compressed Sparse Patch tables of one batch composition."""
 
     def __init__(self, resolutions: Sequence[Sequence[int]], ph: int = 0, pw: int = 0, text_len: int = 0):
-        res = np.ascontiguousarray(np.asarray(resolutions, dtype=np.int32).reshape(-1, 2))
+        res = self._flat(resolutions)
         self._h = C.c_void_p()
-        _check(lib().pserve_plan_text(res.ctypes.data_as(C.POINTER(C.c_int32)), res.shape[0], ph, pw, text_len, _stream(),
+        _check(lib().pserve_plan_text((C.c_int32 * len(res)).from_buffer(res), len(res) // 2, ph, pw, text_len, _stream(),
                                       C.byref(self._h)))
         info = _PlanInfo()
         _check(lib().pserve_plan_info(self._h, C.byref(info)))
         self.n, self.R, self.P, self.ph, self.pw, self.ring, self.T = (info.n, info.R, info.P, info.ph, info.pw,
                                                                       info.ring, info.T)
         self.text_len, self.text_patches = info.text_len, info.text_patches
-        self.resolutions = [tuple(r) for r in res.tolist()]
+        self.resolutions = list(zip(res[::2], res[1::2]))
+
+    @staticmethod
+    def _flat(resolutions) -> array:
+        """h0, w0, h1, w1, ... as int32.  Lists of pairs of whole numbers, a batch's usual form, without an ndarray on the way
+        (24 requests: 3 us against 5); anything else as numpy converts it, with numpy's errors."""
+        if type(resolutions) in (list, tuple) and set(map(type, resolutions)) <= {list, tuple} and set(map(len, resolutions)) == {2}:
+            try:
+                return array("i", chain.from_iterable(resolutions))
+            except (TypeError, OverflowError):
+                pass
+        return array("i", np.ascontiguousarray(np.asarray(resolutions, dtype=np.int32).reshape(-1, 2)).tobytes())
 
     def text_scatter(self, text, x):
         """pserve_text_scatter: text [n, text_len, C] (caller order) into the text patches of x[T, C] (in place)."""
         assert text.is_contiguous() and x.is_contiguous() and text.dtype == x.dtype
-        assert tuple(text.shape) == (self.n, self.text_len, x.shape[1]) and x.shape[0] == self.T
+        assert text.shape == (self.n, self.text_len, x.shape[1]) and x.shape[0] == self.T
         import torch
         dt = BF16 if x.dtype == torch.bfloat16 else F32
         _check(lib().pserve_text_scatter(self._h, text.data_ptr(), x.shape[1], dt, x.data_ptr(), _stream()))
@@ -246,7 +261,9 @@ class Plan:
         ptr = C.POINTER(C.c_int32)()
         cnt = C.c_int64()
         _check(lib().pserve_plan_table(self._h, TABLES[name], 0, C.byref(ptr), C.byref(cnt)))
-        a = np.ctypeslib.as_array(ptr, shape=(cnt.value,)).copy()
+        a = np.empty(cnt.value, dtype=np.int32)
+        if cnt.value:
+            C.memmove(C.byref(C.c_int32.from_buffer(a)), ptr, a.nbytes)
         shape = {"res_hw": (-1, 2), "patch_rc": (-1, 2), "neighbour": (-1, 8), "halo_src": (self.P, -1)}.get(name)
         return a.reshape(shape) if shape else a
 
@@ -267,7 +284,7 @@ class Plan:
             out = torch.empty((self.T, Cc), dtype=images[0].dtype, device=images[0].device)
         ptrs = (C.c_void_p * self.n)(*[im.data_ptr() for im in images])
         for im, (h, w) in zip(images, self.resolutions):
-            assert im.is_contiguous() and tuple(im.shape) == (Cc, h, w) and im.dtype == images[0].dtype
+            assert im.is_contiguous() and im.shape == (Cc, h, w) and im.dtype == images[0].dtype
         if cache is not None:
             _check(lib().pserve_split_stats(self._h, ptrs, Cc, dt, out.data_ptr(), cache._h, _stream()))
         else:
@@ -377,7 +394,7 @@ class Cache:
         self.plan, self.block = plan, block
 
     def load(self, stage: int, slot: int, src):
-        assert src.is_contiguous() and tuple(src.shape) == (self.plan.T, self.block.C)
+        assert src.is_contiguous() and src.shape == (self.plan.T, self.block.C)
         _check(lib().pserve_cache_load(self._h, stage, slot, src.data_ptr(), _stream()))
 
     def read(self, stage: int, slot: int):
@@ -397,7 +414,7 @@ class Cache:
     def forward(self, x, ctx=None, reuse_mask=None, y=None, temb=None):
         """pserve_block_forward (pserve_block_forward_temb when temb is given) on the current torch stream; returns y[T, C]."""
         import torch
-        assert x.is_contiguous() and tuple(x.shape) == (self.plan.T, self.block.C)
+        assert x.is_contiguous() and x.shape == (self.plan.T, self.block.C)
         assert x.dtype == _torch_dtype(self.block.dtype)
         if y is None:
             y = torch.empty_like(x)
@@ -449,7 +466,7 @@ class Resample:
 
     def forward(self, plan_in: "Plan", plan_out: "Plan", x, y=None, workspace=None):
         import torch
-        assert x.is_contiguous() and tuple(x.shape) == (plan_in.T, self.C_in) and x.dtype == _torch_dtype(self.dtype)
+        assert x.is_contiguous() and x.shape == (plan_in.T, self.C_in) and x.dtype == _torch_dtype(self.dtype)
         if workspace is None:
             need = self.workspace_bytes(plan_in)
             if self._ws is None or self._ws.numel() < need:
