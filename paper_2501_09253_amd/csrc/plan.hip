@@ -207,58 +207,13 @@ split_kernel(ImagePtrs imgs, int slot0, int patch0, const int32_t* __restrict__ 
     }
 }
 
-// bf16 fast path: tile = 64 channels x 32 consecutive tokens of one patch, one 16-byte access per thread on each
-// side (8 pixels of one channel row in NCHW; 8 channels of one token in the patch-major layout), transposed in LDS.
-// Needs pw % 8 == 0, (ph*pw) % 32 == 0, C % 64 == 0, W % 8 == 0 and 16-byte aligned images.
-template <bool TO_PATCH>
-__global__ void __launch_bounds__(256)
-split_vec_kernel(ImagePtrs imgs, int slot0, int patch0, const int32_t* __restrict__ sorted_hw,
-                 const int32_t* __restrict__ owner, const int32_t* __restrict__ rc, int32_t ph, int32_t pw, int32_t C,
-                 uint16_t* __restrict__ x) {
-    __shared__ __attribute__((aligned(16))) uint16_t tile[32][72];      // [token][channel], rows padded to 144 bytes
-    const int S = ph * pw, tiles = S / 32;
-    const int p = patch0 + blockIdx.x / tiles;
-    const int t0 = (blockIdx.x % tiles) * 32;
-    const int c0 = blockIdx.y * 64;
-    if (rc[2 * p] < 0) return;                  // a text patch: not part of any image
-    const int s = owner[p];
-    const int H = sorted_hw[2 * s], W = sorted_hw[2 * s + 1];
-    uint16_t* img = (uint16_t*)imgs.p[s - slot0];
-    const int tid = threadIdx.x;
-    // image side: channel ich, 8 pixels starting at token t0 + 8*iq
-    const int ich = tid >> 2, iq = tid & 3;
-    const int it = t0 + 8 * iq, iy = it / pw, ix = it - iy * pw;
-    uint16_t* ip = img + ((int64_t)(c0 + ich) * H + rc[2 * p] * ph + iy) * W + rc[2 * p + 1] * pw + ix;
-    // patch side: token t0 + ptk, channels 8*pq .. +8
-    const int ptk = tid >> 3, pq = tid & 7;
-    uint16_t* xp = x + ((int64_t)p * S + t0 + ptk) * C + c0 + 8 * pq;
-    typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-    if (TO_PATCH) {
-        const u32x4 v = *reinterpret_cast<const u32x4*>(ip);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            tile[8 * iq + 2 * k][ich] = (uint16_t)(v[k] & 0xFFFFu);
-            tile[8 * iq + 2 * k + 1][ich] = (uint16_t)(v[k] >> 16);
-        }
-        __syncthreads();
-        *reinterpret_cast<u32x4*>(xp) = *reinterpret_cast<const u32x4*>(&tile[ptk][8 * pq]);
-    } else {
-        *reinterpret_cast<u32x4*>(&tile[ptk][8 * pq]) = *reinterpret_cast<const u32x4*>(xp);
-        __syncthreads();
-        u32x4 v;
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            v[k] = (uint32_t)tile[8 * iq + 2 * k][ich] | ((uint32_t)tile[8 * iq + 2 * k + 1][ich] << 16);
-        *reinterpret_cast<u32x4*>(ip) = v;
-    }
-}
-
 // Any patch shape (C a multiple of 64): a channel's plane of an image is one run of H * W values, whatever the patches are, so a block
 // takes 128 bytes of it (64 bf16 pixels, 32 fp32) in 64 channels, VEC pixels an access, and the 128 or 256 bytes of 64 channels of each of
 // these pixels' tokens.  Transposed in LDS; 16-byte piece c of a pixel's row lies at c ^ (pixel / 16 bytes), so that neither side's accesses
 // meet in a bank.  us, rows of patches with two-byte accesses (split_kernel) / here:
 // 19,008 tokens x 512 in 12 x 12 patches 28.6 / 8.9 and back 22.2 / 7.3 (39 MB: 4.4 and 5.3 TB/s), 7,600 x 512 in 20 x 20 11.4 / 6.0 and 10.2 / 5.5,
-// fp32 7,168 x 320 in 16 x 16 12.5 / 7.1 and 8.6 / 5.6, 832 x 64 4.5 / 3.0 and 3.9 / 2.9.
+// fp32 7,168 x 320 in 16 x 16 12.5 / 7.1 and 8.6 / 5.6, 832 x 64 4.5 / 3.0 and 3.9 / 2.9.  Against 16-byte accesses along the rows of bf16
+// patches (back): 13,312 x 1280 in 8 x 8 26.0 / 12.2, 19,008 x 640 in 24 x 24 16.0 / 9.2, 20,480 x 512 in 16 x 32 8.8 / 8.1.
 struct PlaneTiles {
     int32_t end[IMG_CHUNK];   // tiles of the launch's requests up to and with this one
 };
@@ -323,9 +278,18 @@ split_plane_kernel(ImagePtrs imgs, PlaneTiles at, int slot0, const int32_t* __re
     }
 }
 
+// Blocks go to the eight XCDs in turn: numbers b of one XCD get consecutive places, so neighbouring patches, whose rows share cache
+// lines of the image, are read through one L2 (patches narrower than 64 bytes: 13,312 tokens x 1280 in 8 x 8 patches 26.0 -> 18.1 us with
+// the next tile's load ahead, 19,008 x 640 in 24 x 24 17.3 -> 12.9; wider ones gain nothing, 32 wide 10.5 -> 11.5 at 20,480 x 512).
+__device__ __forceinline__ int xcd_run(int b, int n) {
+    const int q = n / 8, r = n % 8, xcd = b % 8;
+    return xcd * q + min(xcd, r) + b / 8;
+}
+
 // Split (bf16 fast path) that also leaves the moments of every channel behind, for a GroupNorm that reads x next:
-// block = (patch, one of `nch` token chunks, 64 channels); it walks the chunk's 32-token tiles like split_vec_kernel
-// and keeps, per thread, the sums of (x - K) and (x - K)^2 of its eight channels (K = the channel's value in the
+// block = (patch, one of `nch` token chunks, 64 channels); it walks the chunk's tiles of 32 tokens, one 16-byte access
+// a thread on each side (8 pixels of a channel's row, 8 channels of a token), transposed in LDS, the next tile's pixels
+// already on their way, and keeps, per thread, the sums of (x - K) and (x - K)^2 of its eight channels (K = the channel's value in the
 // chunk's first token: nothing is lost when the mean is far from zero).  Per (patch, chunk, channel) it stores the
 // mean and the sum of squared deviations M2 of the chunk's tokens: stats[((p * nch + chunk) * C + c) * 2 + {0, 1}],
 // which the GroupNorm finalize merges (fixed order, no atomics).
@@ -337,7 +301,8 @@ split_stats_kernel(ImagePtrs imgs, int slot0, int patch0, const int32_t* __restr
     __shared__ float red[2][32][65];
     __shared__ float kk[64];
     const int S = ph * pw, tiles = S / 32, tpc = tiles / nch;
-    const int p = patch0 + blockIdx.x / nch, tc = blockIdx.x % nch;
+    const int bx = pw % 32 ? xcd_run(blockIdx.x, gridDim.x) : blockIdx.x;
+    const int p = patch0 + bx / nch, tc = bx % nch;
     const int c0 = blockIdx.y * 64;
     if (rc[2 * p] < 0) return;                  // a text patch: not part of any image
     const int s = owner[p];
@@ -351,10 +316,15 @@ split_stats_kernel(ImagePtrs imgs, int slot0, int patch0, const int32_t* __restr
     float s1[8], s2[8], k0[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) { s1[e] = 0.f; s2[e] = 0.f; k0[e] = 0.f; }
+    auto load = [&](int ti) {
+        const int it = (tc * tpc + ti) * 32 + 8 * iq, iy = it / pw, ix = it - iy * pw;
+        return *reinterpret_cast<const u32x4*>(ibase + (int64_t)iy * W + ix);
+    };
+    u32x4 next = load(0);
     for (int ti = 0; ti < tpc; ++ti) {
         const int t0 = (tc * tpc + ti) * 32;
-        const int it = t0 + 8 * iq, iy = it / pw, ix = it - iy * pw;
-        const u32x4 v = *reinterpret_cast<const u32x4*>(ibase + (int64_t)iy * W + ix);
+        const u32x4 v = next;
+        if (ti + 1 < tpc) next = load(ti + 1);
         if (ti) __syncthreads();                // the previous tile has been read
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -437,16 +407,6 @@ static int run_split(const pserve_plan_t* plan, void* const* images, int32_t C, 
         memset(&ip, 0, sizeof(ip));
         for (int s = s0; s < s1; ++s) ip.p[s - s0] = images[perm[s]];
         const int patch0 = ro[s0], npatch = ro[s1] - ro[s0];
-        bool vec = dtype == PSERVE_BF16 && plan->pw % 8 == 0 && plan->S % 32 == 0 && C % 64 == 0 && ((uintptr_t)x & 15) == 0;
-        for (int s = s0; s < s1 && vec; ++s)
-            vec = plan->h_sorted_hw[2 * s + 1] % 8 == 0 && ((uintptr_t)ip.p[s - s0] & 15) == 0;
-        if (vec) {
-            dim3 vgrid(npatch * (plan->S / 32), (unsigned)(C / 64));
-            split_vec_kernel<TO_PATCH><<<vgrid, 256, 0, st>>>(ip, s0, patch0, plan->d_sorted_hw,
-                plan->d_tab[PSERVE_TAB_PATCH_OWNER], plan->d_tab[PSERVE_TAB_PATCH_RC], plan->ph, plan->pw, C, (uint16_t*)x);
-            PS_TRY(check_launch("split_vec_kernel"));
-            continue;
-        }
         // pixels an access of split_plane_kernel takes: all planes start at a multiple of as many
         const int es = (int)dtype_size(dtype);
         int px = C % 64 == 0 && ((uintptr_t)x & 15) == 0 ? 16 / es : 0;

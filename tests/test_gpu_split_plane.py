@@ -15,6 +15,7 @@ CASES = [([(12, 36), (24, 12)], (12, 12), 64, 0, 0),            # whole tiles an
          ([(3, 3), (9, 5)], (3, 1), 64, 0, 0),                  # one
          ([(10, 20), (20, 20)], (10, 20), 192, 2, 0),           # images two values off the grid
          ([(4, 4)] * 33 + [(8, 12)] * 4, (4, 4), 64, 0, 0),     # two launches
+         ([(8, 16), (24, 8)], (8, 8), 128, 0, 0),               # many patches a tile
          ([(12, 12), (12, 24)], (12, 12), 64, 0, 20)]           # a joint plan
 
 
