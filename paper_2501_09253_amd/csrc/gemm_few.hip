@@ -29,9 +29,12 @@ template <int BM, int BN, int W> struct FewCfg {
 };
 
 // TWO: a second problem (GemmArgs::B2: another patch list, weights, bias and gate of its own) continues the row tiles of the first.
-template <int BM, int BN, int W, bool GEGLU, bool TWO>
+// HALO: a convolution that reads the unpadded batch (GemmArgs::halo_src), its A rows' offsets in a table of taps x BM.
+enum : int { FEW_TWO = 1, FEW_HALO = 2 };
+template <int BM, int BN, int W, bool GEGLU, int FORM>
 __global__ void __launch_bounds__(64 * W)
-gemm_few_kernel(std::conditional_t<TWO, GemmArgs, GemmCore> a, int pads, int m_first) {
+gemm_few_kernel(std::conditional_t<FORM != 0, GemmArgs, GemmCore> a, int pads, int m_first) {
+    constexpr bool TWO = FORM == FEW_TWO, HALO = FORM == FEW_HALO;
     using Cfg = FewCfg<BM, BN, W>;
     constexpr int TM = BM / 16, TN = BN / 16, AL = BM / 8, BL = BN / 8, LD = AL + BL;
     static_assert(!GEGLU || BN == 64, "a tile of value-gate pairs is 32 values and their 32 gates");
@@ -39,6 +42,7 @@ gemm_few_kernel(std::conditional_t<TWO, GemmArgs, GemmCore> a, int pads, int m_f
     int32_t* s_tok = reinterpret_cast<int32_t*>(smem + W * Cfg::PART);          // [BM] output row, -1: none
     int32_t* s_off = s_tok + BM;                                                // [BM] byte offset of the A row
     int32_t* s_own = s_off + BM;                                                // [BM] request slot (rowbias / rowscale)
+    int32_t* s_src = s_own + BM;                                                // HALO: [taps][BM]
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -81,7 +85,9 @@ gemm_few_kernel(std::conditional_t<TWO, GemmArgs, GemmCore> a, int pads, int m_f
     const int tap_w = a.tap_w ? a.tap_w : 3;
     const int fr = lane & 15, kq = lane >> 4;                       // fragment row / column, quarter of a 32-wide K piece
 #if defined(__HIP_DEVICE_COMPILE__)
-    const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.A, 0, 0x7fffffff, 0x00020000);
+    int a_bytes = 0x7fffffff;
+    if constexpr (HALO) a_bytes = halo_bytes(a);
+    const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.A, 0, a_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)B, 0, 0x7fffffff, 0x00020000);
 #define PS_LOAD(rsrc_, dst_, lane_off_, off_) \
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_, (lds_void*)(dst_), 16, lane_off_, off_, 0, 0)
@@ -95,7 +101,7 @@ gemm_few_kernel(std::conditional_t<TWO, GemmArgs, GemmCore> a, int pads, int m_f
     auto b_base = [&](int tap, int kc) { return (int)(((int64_t)(cls * a.taps + tap) * a.N * a.K + kc * 64) * 2); };
     auto a_base = [&](int tap, int kc) {
         const int ty = tap == 0 ? 0 : tap / tap_w, tx = tap - ty * tap_w;
-        return (int)(((a.conv ? (int64_t)(ty * a.geom.ppw + tx) * a.lda : 0) + kc * 64) * 2);
+        return (int)(((a.conv && !HALO ? (int64_t)(ty * a.geom.ppw + tx) * a.lda : 0) + kc * 64) * 2);
     };
 
     // staging: lane -> (row lane / 8 of a load's eight, 16-byte position lane % 8); chunk c of row r at c ^ ((r >> 1) & 7)
@@ -111,6 +117,18 @@ gemm_few_kernel(std::conditional_t<TWO, GemmArgs, GemmCore> a, int pads, int m_f
             PS_LOAD(b_rsrc, ring + st * Cfg::STAGE + BM * 128 + i * 1024, i & 1 ? b_lane1 : b_lane0, base + bcol(8 * i) * a.K * 2);
     };
     int tap1 = tap0, kc1 = kc0;
+    constexpr int NSRC = HALO ? (9 * BM + 64 * W - 1) / (64 * W) : 1;
+    int src[NSRC];
+    if constexpr (HALO) {           // (asked for first: a wait for a load waits for all before it)
+        const int tok = min(m0 + tid % BM, m_limit - 1);
+        const int p = tok / a.geom.S, q = tok - p * a.geom.S, y = q / a.geom.pw, x = q - y * a.geom.pw, am = a.a_mul ? a.a_mul : 1;
+#pragma unroll
+        for (int u = 0; u < NSRC; ++u) {
+            const int k = tid / BM + u * (64 * W / BM);
+            if (k < a.taps) src[u] = halo_token(a, p, am * y + (cls >> 1) + k / tap_w, am * x + (cls & 1) + k % tap_w);
+        }
+        asm volatile("" ::: "memory");
+    }
     // the weights need no table: they travel while it is built
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
@@ -149,6 +167,13 @@ gemm_few_kernel(std::conditional_t<TWO, GemmArgs, GemmCore> a, int pads, int m_f
         s_tok[tid] = valid ? orow : -1;
         s_off[tid] = (int)(off * 2);
         if (a.rowbias || rowscale) s_own[tid] = a.row_owner[tok / a.geom.S];
+    }
+    if constexpr (HALO) {
+#pragma unroll
+        for (int u = 0; u < NSRC; ++u) {
+            const int k = tid / BM + u * (64 * W / BM);
+            if (k < a.taps) s_src[k * BM + tid % BM] = halo_offset(a, src[u]);
+        }
     }
     // the table is written; the loads stay in flight (__syncthreads() would wait for them)
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -194,6 +219,10 @@ gemm_few_kernel(std::conditional_t<TWO, GemmArgs, GemmCore> a, int pads, int m_f
     for (int i = 0; i < AL; ++i) a_lane[i] = s_off[8 * i + lrow] + (i & 1 ? gc1 : gc0);
     auto load_a = [&](int tap, int kc, int st) {
         const int base = a_base(tap, kc);
+        if constexpr (HALO) {
+#pragma unroll
+            for (int i = 0; i < AL; ++i) a_lane[i] = s_src[tap * BM + 8 * i + lrow] + (i & 1 ? gc1 : gc0);
+        }
 #pragma unroll
         for (int i = 0; i < AL; ++i) PS_LOAD(a_rsrc, ring + st * Cfg::STAGE + i * 1024, a_lane[i], base);
     };
@@ -346,22 +375,23 @@ gemm_few_kernel(std::conditional_t<TWO, GemmArgs, GemmCore> a, int pads, int m_f
 static int64_t few_tiles(const GemmArgs& a, int bm, int bn) {
     return (cdiv(gemm_rows(a), bm) + (a.B2 ? cdiv(a.M2, bm) : 0)) * (a.N / bn) * std::max(1, a.classes);
 }
-template <int BM, int BN, bool GEGLU, bool TWO>
+template <int BM, int BN, bool GEGLU, int FORM>
 static int launch_few_as(const GemmArgs& a, hipStream_t st) {
     constexpr int W = 4;
-    constexpr size_t lds = FewCfg<BM, BN, W>::LDS;
-    PS_SET_LDS_ONCE((gemm_few_kernel<BM, BN, W, GEGLU, TWO>), lds);
+    constexpr size_t lds = FewCfg<BM, BN, W>::LDS + (FORM == FEW_HALO ? 9 * BM * sizeof(int32_t) : 0);
+    PS_SET_LDS_ONCE((gemm_few_kernel<BM, BN, W, GEGLU, FORM>), lds);
     const bool pads = gemm_pads_rows(a);
     const int m_first = (int64_t)a.M <= (int64_t)a.N * a.taps * std::max(1, a.classes);
-    gemm_few_kernel<BM, BN, W, GEGLU, TWO><<<(unsigned)(8 * cdiv(few_tiles(a, BM, BN), 8)), 64 * W, lds, st>>>(a, pads, m_first);
+    gemm_few_kernel<BM, BN, W, GEGLU, FORM><<<(unsigned)(8 * cdiv(few_tiles(a, BM, BN), 8)), 64 * W, lds, st>>>(a, pads, m_first);
     return check_launch("gemm_few_kernel");
 }
 template <int BM, int BN, bool GEGLU>
 static int launch_few(const GemmArgs& a, hipStream_t st) {
     if constexpr (!GEGLU) {
-        if (a.B2) return launch_few_as<BM, BN, GEGLU, true>(a, st);
+        if (a.B2) return launch_few_as<BM, BN, GEGLU, FEW_TWO>(a, st);
+        if (a.halo_src) return launch_few_as<BM, BN, GEGLU, FEW_HALO>(a, st);
     }
-    return launch_few_as<BM, BN, GEGLU, false>(a, st);
+    return launch_few_as<BM, BN, GEGLU, 0>(a, st);
 }
 
 // Which tile a problem would take here (0: none) and how long it would run, in us: a round of 256 tiles (32 x 32: 512, two

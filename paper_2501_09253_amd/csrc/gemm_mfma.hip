@@ -38,7 +38,8 @@ enum : int {
     EPF_SCALE = 16,     // output segments with a scale other than 1 (the pre-multiplied Q)
     EPF_ALL = 31,
     EPF_PADS = 32,      // tiles walk the padded rows of the requests (gemm_pads_rows)
-    EPF_TWO = 64        // a second problem (GemmArgs::B2) continues the row tiles; one tile a block
+    EPF_TWO = 64,       // a second problem (GemmArgs::B2) continues the row tiles; one tile a block
+    EPF_HALO = 128      // a convolution that reads the unpadded batch (GemmArgs::halo_src)
 };
 template <int BM, int BN, bool GEGLU, int WGM = 2, int WGN = 2, bool MAY_STAT = true, int FEAT = EPF_ALL>
 __device__ __forceinline__ void gemm_epilogue(const GemmCore& a, f32x16 (&acc)[BM / WGM / 32][BN / WGN / 32], uint8_t* smem,
@@ -310,7 +311,9 @@ gemm_mfma_kernel(GemmArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     u32x4* ring = reinterpret_cast<u32x4*>(smem);                     // [NS][STAGE_V]
     int32_t* s_tok2 = reinterpret_cast<int32_t*>(ring + NS * STAGE_V); // [2][BM] output row of each tile row, -1 = none
-    uint8_t* ep_smem = OVERLAP ? reinterpret_cast<uint8_t*>(s_tok2 + 2 * BM) : smem;
+    constexpr bool HALO = (FEAT & EPF_HALO) != 0;
+    int32_t* s_src = s_tok2 + 2 * BM;                                  // HALO: [taps][BM] byte offset of the pixel a tap reads
+    uint8_t* ep_smem = OVERLAP ? reinterpret_cast<uint8_t*>(s_src + (HALO ? 9 * BM : 0)) : smem;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // scalar: LDS destinations of the loads are SGPR math
@@ -416,12 +419,25 @@ gemm_mfma_kernel(GemmArgs a) {
             }                                                                                                     \
         }                                                                                                         \
         b_lane = (int)((((int64_t)cls_ * a.taps * a.N + nl_ + lr) * a.K + gc * 8) * 2);                                               \
+        if constexpr (HALO) {                                                                                     \
+            const int row = tid % BM, tok = min((tm0) + row, m_limit - 1);                                        \
+            const int p = tok / a.geom.S, q = tok - p * a.geom.S, y = q / a.geom.pw, x = q - y * a.geom.pw;       \
+            const int am = a.a_mul ? a.a_mul : 1;                                                                 \
+            for (int t = tid / BM; t < a.taps; t += 256 / BM)                                                     \
+                s_src[t * BM + row] = halo_offset(a, halo_token(a, p, am * y + ady_ + t / tap_w, am * x + adx_ + t % tap_w)); \
+            /* the table is written; loads stay in flight */                                                      \
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");                                       \
+        }                                                                                                         \
+    }
+#define PS_HALO_ROWS(tap_)                                                                                        \
+    {                                                                                                             \
+        _Pragma("unroll") for (int i = 0; i < A_LD; ++i) a_lane[i] = s_src[(tap_) * BM + lr + i * 32] + gc * 16;  \
     }
     // one direct global->LDS load (64 lanes x 16 bytes): l < A_LD an A row group, else a B row group
     // (buffer loads rather than global loads into LDS: behind a flat-class load the compiler turns every wait for one
     // fragment into a wait for all LDS reads in flight; 2-4 % on every linear layer)
 #if defined(__HIP_DEVICE_COMPILE__)
-    const __amdgpu_buffer_rsrc_t ga_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.A, 0, 0x7fffffff, 0x00020000);
+    const __amdgpu_buffer_rsrc_t ga_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.A, 0, HALO ? halo_bytes(a) : 0x7fffffff, 0x00020000);
     const __amdgpu_buffer_rsrc_t gb_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)B, 0, 0x7fffffff, 0x00020000);
 #define PS_LOAD(dst_, a_off_, b_off_, l_)                                                                         \
     {                                                                                                             \
@@ -438,7 +454,7 @@ gemm_mfma_kernel(GemmArgs a) {
     // global offsets of K step (tap, kc)
 #define PS_OFFSETS(tap_, kc_)                                                                                     \
     const int ty_ = (tap_) / tap_w, tx_ = (tap_) - ty_ * tap_w;                                                   \
-    const int64_t a_off = (a.conv ? ((int64_t)ty_ * a.geom.ppw + tx_) * a.lda : 0) + (kc_) * BK;                  \
+    const int64_t a_off = (a.conv && !HALO ? ((int64_t)ty_ * a.geom.ppw + tx_) * a.lda : 0) + (kc_) * BK;                  \
     const int64_t b_off = (tap_) * b_tap_stride + (kc_) * BK;
     // the first NS steps of a tile: all stages in flight
 #define PS_PROLOGUE_STAGES(st0_, st1_)                                                                            \
@@ -446,6 +462,7 @@ gemm_mfma_kernel(GemmArgs a) {
         if ((st0_) == 0) { tap = 0; kc = 0; issued = 0; }                                                         \
         _Pragma("unroll") for (int st = (st0_); st < (st1_); ++st) {                                              \
             PS_OFFSETS(tap, kc);                                                                                  \
+            if constexpr (HALO) PS_HALO_ROWS(tap);                                                                \
             u32x4* dst = ring + st * STAGE_V + wave * 64;                                                         \
             _Pragma("unroll") for (int l = 0; l < LD; ++l) PS_LOAD(dst, a_off, b_off, l);                         \
             if (++issued < KT) { if (++kc == kchunks) { kc = 0; ++tap; } } else { issued = KT - 1; }              \
@@ -504,6 +521,9 @@ gemm_mfma_kernel(GemmArgs a) {
             const int nst = rd + 1 == NS ? 0 : rd + 1;
             const u32x4* nxt = ring + nst * STAGE_V;
             PS_OFFSETS(tap, kc);                    // step kt + NS goes into this step's stage
+            if constexpr (HALO) {
+                if (kc == 0) PS_HALO_ROWS(tap);
+            }
             if (++issued < KT) { if (++kc == kchunks) { kc = 0; ++tap; } } else { issued = KT - 1; }
             u32x4* dst = ring + rd * STAGE_V + wave * 64;
             // With two stages the barrier waits for ALL loads in flight (vmcnt(0)), so the last steps of a tile need not
@@ -576,6 +596,7 @@ gemm_mfma_kernel(GemmArgs a) {
 #undef PS_PROLOGUE_STAGES
 #undef PS_OFFSETS
 #undef PS_LOAD
+#undef PS_HALO_ROWS
 #undef PS_SETUP
 }
 
@@ -1115,7 +1136,8 @@ static bool conv_tile(const GemmArgs& a, int BM, int apix_max, ConvTile* ct) {
 
 template <int BM, int BN, bool GEGLU, int WGM, int WGN, int NS, bool OVERLAP, int FEAT>
 static int launch_feat(const GemmArgs& a, hipStream_t st) {
-    constexpr size_t lds = GemmCfg<BM, BN, NS, OVERLAP>::LDS;
+    constexpr size_t lds = GemmCfg<BM, BN, NS, OVERLAP>::LDS + (FEAT & EPF_HALO ? 9 * BM * sizeof(int32_t) : 0);
+    static_assert(lds <= 160 * 1024, "LDS");
     PS_SET_LDS_ONCE((gemm_mfma_kernel<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, FEAT>), lds);
     // all tiles, or as many blocks as run at once (256 CUs x the blocks of this LDS size per CU): each block then
     // walks over several tiles
@@ -1141,6 +1163,7 @@ static int launch(const GemmArgs& a, hipStream_t st) {
         return launch_feat<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, 0>(a, st);
     } else {
         if (gemm_pads_rows(a)) return launch_feat<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, EPF_TRANS | EPF_SCALE | EPF_PADS>(a, st);
+        if (a.halo_src) return launch_feat<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, EPF_HALO>(a, st);
         if constexpr (BN != 64) {
             if (!a.rowbias && !a.rowscale && !a.act_gelu) {
                 if (seg) return launch_feat<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, EPF_TRANS | EPF_SCALE>(a, st);
@@ -1279,6 +1302,15 @@ int gemm_two_cols(const GemmArgs& a, double* us) {
 int gemm_two_bf16(const GemmArgs& a, int cols, hipStream_t st) {
     if (cols == 64) return launch_feat<128, 64, false, 2, 2, 3, false, EPF_ALL | EPF_TWO>(a, st);
     return launch_feat<128, 128, false, 2, 2, 2, false, EPF_ALL | EPF_TWO>(a, st);
+}
+
+// What gemm_mfma_bf16 sends to gemm_few_kernel or gemm_mfma_kernel, whose HALO forms look up where each row's pixels lie once a tile.
+bool gemm_takes_halo(const GemmArgs& a, int dtype, int mode) {
+    ConvTile ct;
+    double us;
+    return dtype == PSERVE_BF16 && mode == 0 && gemm_mfma_eligible(a) && a.conv && a.epi == EPI_ROUTE && a.tokens_are_rows && !a.act.active &&
+           !a.B2 && a.taps <= 9 && !a.rowbias && !a.rowscale && !a.act_gelu && !a.seg[0].transposed && a.seg[0].scale == 1.f &&
+           a.seg_cols == a.N && !conv_select(a, &ct) && (few_pick(a, 1, &us) || a.N % 64 == 0 || (a.N % 160 == 0 && cdiv(a.M, 128) * (a.N / 160) * std::max(1, a.classes) >= 208));
 }
 
 int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {

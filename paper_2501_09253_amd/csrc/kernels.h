@@ -196,6 +196,9 @@ struct GemmArgs : GemmCore {
     const float* rowscale2;
     ActiveList act2;
     int32_t M2;
+    // conv: A is the unpadded batch [tokens of the input][lda], and the pixels around a patch are looked up here ([P][ring] source tokens, -1: zeros).
+    // Only where gemm_takes_halo() says so, without a patch list.
+    const int32_t* halo_src;
     // fp32: A is in bf16 pieces (gemm_takes_pieces) / the output is written in pieces
     int32_t a_pieces, out_pieces;
 };
@@ -211,6 +214,8 @@ inline bool gemm_fits32(const GemmArgs& a) {
 }
 // true if gemm(a, ...) with its second problem will take a kernel that runs both in one launch
 bool gemm_takes_two(const GemmArgs& a, int dtype, int mode);
+// true if gemm(a, ...) will take a kernel that reads the unpadded batch through a.halo_src
+bool gemm_takes_halo(const GemmArgs& a, int dtype, int mode);
 // true if gemm(a, ...) is faster with its activations in bf16 pieces (a.a_pieces, which the caller then sets)
 bool gemm_takes_pieces(const GemmArgs& a, int dtype, int mode);
 // scratch a 3x3 convolution of M rows, N output and K input channels over this patch geometry can use (0: none)

@@ -62,6 +62,19 @@ inline bool gemm_two_eligible(const GemmArgs& a) {
     return a.epi == EPI_ROUTE && !a.conv && a.tokens_are_rows && a.act.active && a.act2.active && !((uintptr_t)a.B2 & 15) &&
            !a.bias == !a.bias2 && !a.rowscale == !a.rowscale2 && !a.rowbias;
 }
+// Token of the unpadded batch that holds pixel (Y, X) of patch p's padded layout (GemmArgs::halo_src), -1: outside the image
+__device__ __forceinline__ int halo_token(const GemmArgs& a, int p, int Y, int X) {
+    const int ppw = a.geom.ppw, pw = ppw - 2, ph = a.geom.pS / ppw - 2;
+    if (Y >= 1 && Y <= ph && X >= 1 && X <= pw) return p * (ph * pw) + (Y - 1) * pw + X - 1;
+    return a.halo_src[p * (2 * ppw + 2 * ph) + (Y < 1 ? X : Y > ph ? ppw + X : 2 * ppw + (X < 1 ? 0 : ph) + Y - 1)];
+}
+// its byte offset; past the tensor's end, where buffer loads give zeros, for pixels outside the image
+__device__ __forceinline__ int halo_offset(const GemmArgs& a, int tok) { return tok < 0 ? 0x7fffff00 : (int)((int64_t)tok * a.lda * 2); }
+// bytes of the unpadded batch
+__device__ __forceinline__ int halo_bytes(const GemmArgs& a) {
+    const int ppw = a.geom.ppw;
+    return (int)((int64_t)a.geom.P * (a.geom.pS / ppw - 2) * (ppw - 2) * a.lda * 2);
+}
 __host__ __device__ inline int32_t gemm_rows(const GemmArgs& a) { return gemm_pads_rows(a) ? a.M / a.row_group * a.row_group_pad : a.M; }
 
 }  // namespace pserve

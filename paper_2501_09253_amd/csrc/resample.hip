@@ -2,8 +2,12 @@
 // 2x followed by a 3x3 convolution (UP2).  Both keep the patch grid (a ph x pw patch becomes ph/2 x pw/2 resp.
 // 2ph x 2pw), so the output plan is the plan of the halved / doubled resolutions with the halved / doubled patch and
 // has the same patch order, owners and neighbours.
-//   1. the input is copied into the padded patch layout and its rims are pushed to the neighbours (the apply pass
-//      of the GroupNorm without a scale table: the "Patch Edge Stitcher" of the paper as a plain copy);
+//   1. where the kernel of 2 does not read the rims of the neighbours by itself (fp32, widths it does not take, an output over its
+//      input), the input is copied into the padded patch layout and its rims are pushed to the neighbours (the apply pass
+//      of the GroupNorm without a scale table: the "Patch Edge Stitcher" of the paper as a plain copy).  Nothing else of
+//      the input is changed, so the copy was a launch and two passes over memory for the pixels at the patches' edges: down and
+//      up, us, with it / without: 29,696 tokens x 320 in 32 x 32 patches 77.6 / 62.9, 3,400 x 1280 in 10 x 10 165 / 125, 2,000 x 256
+//      38.6 / 16.5 (a call of few tokens is bound by its launches);
 //   2. DOWN2: one implicit GEMM whose rows are OUTPUT tokens (p, y, x) reading the padded pixels (2y + ty, 2x + tx);
 //      UP2:   four implicit GEMMs in one launch, one per output parity (a, b), with rows = INPUT tokens (p, y, x): the nine taps
 //             of output pixel (2y + a, 2x + b) fall on 2 x 2 input pixels, so the weights are merged into four taps per
@@ -94,29 +98,37 @@ int pserve_resample_forward(const pserve_resample_t* op, const pserve_plan_t* pl
     gin.P = plan_in->P; gin.S = plan_in->S; gin.ph = plan_in->ph; gin.pw = plan_in->pw;
     gin.ppw = plan_in->pw + 2; gin.pS = (plan_in->ph + 2) * (plan_in->pw + 2);
     const ActiveList all{nullptr, nullptr};
-    {   // padded copy with the rims of the neighbours (and zeros at the image border)
-        GroupNormArgs ga{};
-        ga.x = x; ga.C = op->C_in; ga.G = 1; ga.n = plan_in->n; ga.nsplit = 1;
-        ga.scale_shift = nullptr;
-        ga.owner = plan_in->d_tab[PSERVE_TAB_PATCH_OWNER];
-        ga.neighbour = plan_in->d_tab[PSERVE_TAB_NEIGHBOUR];
-        ga.request_offset = plan_in->d_tab[PSERVE_TAB_REQUEST_OFFSET];
-        PS_TRY(gn_apply(ga, gin, dt, /*silu=*/false, /*padded=*/true, /*stitch=*/true, workspace, all, st));
-    }
     GemmArgs g{};
-    g.A = workspace; g.lda = op->C_in; g.conv = 1; g.act = all; g.tokens_are_rows = 1;
+    g.lda = op->C_in; g.conv = 1; g.act = all; g.tokens_are_rows = 1;
     g.N = op->C_out; g.K = op->C_in; g.bias = op->b; g.epi = EPI_ROUTE; g.seg_cols = op->C_out;
     for (auto& s : g.seg) { s.ptr = nullptr; s.ld = 0; s.transposed = 0; s.scale = 1.f; }
     g.seg[0].ptr = y; g.seg[0].ld = op->C_out;
     g.geom = gin;
+    g.B = op->w;
     if (op->kind == PSERVE_DOWN2) {
         g.geom.S = plan_out->S; g.geom.pw = plan_out->pw; g.geom.ph = plan_out->ph;     // rows: output tokens
-        g.M = (int32_t)plan_out->T; g.taps = 9; g.tap_w = 3; g.a_mul = 2; g.B = op->w;
+        g.M = (int32_t)plan_out->T; g.taps = 9; g.tap_w = 3; g.a_mul = 2;
+    } else {
+        g.M = (int32_t)plan_in->T; g.taps = 4; g.tap_w = 2; g.a_mul = 1;                 // rows: input tokens
+        g.o_mul = 2; g.o_S = plan_out->S; g.o_pw = plan_out->pw;
+        g.classes = 4;                                  // the four output parities
+    }
+    g.A = x;
+    const uintptr_t x0 = (uintptr_t)x, y0 = (uintptr_t)y;
+    const size_t xb = (size_t)plan_in->T * op->C_in * dtype_size(dt), yb = (size_t)plan_out->T * op->C_out * dtype_size(dt);
+    if (gemm_takes_halo(g, dt, 0) && (x0 + xb <= y0 || y0 + yb <= x0)) {     // (an output over its input needs the copy)
+        g.halo_src = plan_in->d_tab[PSERVE_TAB_HALO_SRC];
         return gemm(g, dt, 0, st);
     }
-    g.M = (int32_t)plan_in->T; g.taps = 4; g.tap_w = 2; g.a_mul = 1;                     // rows: input tokens
-    g.o_mul = 2; g.o_S = plan_out->S; g.o_pw = plan_out->pw;
-    g.classes = 4; g.B = op->w;                         // the four output parities
+    // padded copy with the rims of the neighbours (and zeros at the image border)
+    GroupNormArgs ga{};
+    ga.x = x; ga.C = op->C_in; ga.G = 1; ga.n = plan_in->n; ga.nsplit = 1;
+    ga.scale_shift = nullptr;
+    ga.owner = plan_in->d_tab[PSERVE_TAB_PATCH_OWNER];
+    ga.neighbour = plan_in->d_tab[PSERVE_TAB_NEIGHBOUR];
+    ga.request_offset = plan_in->d_tab[PSERVE_TAB_REQUEST_OFFSET];
+    PS_TRY(gn_apply(ga, gin, dt, /*silu=*/false, /*padded=*/true, /*stitch=*/true, workspace, all, st));
+    g.A = workspace;
     return gemm(g, dt, 0, st);
 }
 
