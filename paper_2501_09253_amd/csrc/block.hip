@@ -676,7 +676,7 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
     }
     if (conv) PS_TRY(c->pool.alloc(&c->apad, (size_t)plan->P * (plan->ph + 2) * (plan->pw + 2) * d.C * elem(c->apad_pieces)));
     if (conv || gn_sattn) {
-        PS_TRY(c->pool.alloc_t(&c->partial, (size_t)plan->P * std::max<int64_t>(c->nsplit, plan->S / 64) * d.G * 2));
+        PS_TRY(c->pool.alloc_t(&c->partial, (size_t)plan->P * std::max<int64_t>(c->nsplit, plan->S / 32) * d.G * 2));
         PS_TRY(c->pool.alloc_t(&c->scale_shift, (size_t)plan->n * d.C * 2));
         // token chunks per patch of the split pass that also takes the input's moments: enough blocks to fill the
         // chip (x C / 64 channel slabs), a divisor of the patch's 32-token tiles
@@ -978,7 +978,7 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
     };
     // GroupNorm(+SiLU) of `in` into the padded buffer, halo ring, 3x3 convolution (+bias, +residual) into `out`
     // stats_next: the output feeds another norm, so the convolution may leave that norm's partial sums behind
-    bool have_partials = false;                     // cache->partial was filled by the previous convolution
+    int partials = 0;                               // a patch's sums in cache->partial that the previous convolution left there
     auto norm_conv = [&](const void* in, const StageWeights& w, int ci, const void* res, void* out, bool stats_next,
                          const float* rowbias = nullptr, hipEvent_t rowbias_ready = nullptr) -> int {
         GroupNormArgs ga = gn_args(in, w.gn_g[ci], w.gn_b[ci]);
@@ -986,7 +986,7 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         g.conv = 1; g.taps = 9; g.res = res; g.ldr = C;
         g.a_pieces = push && cache->apad_pieces && gemm_takes_pieces(g, dt, mode);
         bool whole = false;
-        if (have_partials) { ProfScope ps("gn_finalize", st); PS_TRY(gn_finalize(ga, gm, dt, plan->S / 64, st)); }
+        if (partials) { ProfScope ps("gn_finalize", st); PS_TRY(gn_finalize(ga, gm, dt, partials, st)); }
         else if (in_stats && in == x) {             // the block input: its moments came with the split
             GroupNormArgs gi = ga;
             gi.partial = cache->in_partial;
@@ -999,7 +999,7 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
             whole = true;
         }
         else { ProfScope ps("gn_stats", st); PS_TRY(gn_stats(ga, gm, dt, st)); }
-        have_partials = false;
+        partials = 0;
         // reused patches are not convolved: of them only the border tokens are normalised (the neighbours' rings)
         ga.rim_only = reuse_mask;
         if (whole) {}
@@ -1016,9 +1016,9 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         g.seg[0].ptr = out; g.seg[0].ld = C;
         if (stats_next && !reuse_mask) {
             // (with a mask the reused patches keep cached activations this convolution never sees: gn_stats reads them)
-            g.stats = cache->partial; g.stats_G = d.G; g.stats_slots = plan->S / 64;
-            if (gemm_emits_stats(g, dt, mode)) have_partials = true;
-            else { g.stats = nullptr; g.stats_G = 0; g.stats_slots = 0; }
+            g.stats_G = d.G;
+            if (const int rows = gemm_stats_rows(g, dt, mode)) { g.stats = cache->partial; g.stats_slots = partials = plan->S / rows; }
+            else g.stats_G = 0;
         }
         if (rowbias_ready) PS_CHECK_HIP(hipStreamWaitEvent(st, rowbias_ready, 0));   // produced on the side stream
         ProfScope ps("conv3x3", st);

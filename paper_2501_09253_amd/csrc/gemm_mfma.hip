@@ -1,11 +1,11 @@
 // bf16 MFMA GEMM / implicit-GEMM 3x3 convolution for gfx950.
 //
 // Two kernels share one epilogue:
-//   gemm_mfma_kernel  block tile 256 x 128 / 128 x 160 / 128 x 128 (four wavefronts stacked along M) or 128 x 256 / 128 /
-//                     64 (2 x 2), K in steps of 64, A and B tiles staged by direct global -> LDS loads into a ring of
-//                     two or three stages (one barrier per step); the linear layers gemm_wide.hip (asked first) does not
-//                     take, and convolutions conv_mfma_kernel does not take (taps re-load A): level changes, odd patches.
-//                     The 128-row tiles with two stages run two blocks per CU.
+//   gemm_mfma_kernel  block tile 128 x 160 / 128 x 128 (GEGLU) with four wavefronts stacked along M or 128 x 128 / 128 x 64 (2 x 2), K in
+//                     steps of 64, A and B tiles staged by direct global -> LDS loads into a ring of two or three stages (one
+//                     barrier per step); the linear layers that neither gemm_few.hip nor gemm_wide.hip (asked first) takes, and
+//                     convolutions (taps re-load A): level changes, patches the other kernel does not take, and all others where
+//                     its rounds fit better (conv_choose).  The tiles with two stages run two blocks per CU.
 //   conv_mfma_kernel  3x3 convolution with the haloed activation tile kept in LDS across the nine taps;
 //                     preferred tile 256 x 160 with four wavefronts stacked along M, each doubled by a second
 //                     wavefront that takes the other half of every K step (two wavefronts per SIMD).
@@ -39,7 +39,8 @@ enum : int {
     EPF_ALL = 31,
     EPF_PADS = 32,      // tiles walk the padded rows of the requests (gemm_pads_rows)
     EPF_TWO = 64,       // a second problem (GemmArgs::B2) continues the row tiles; one tile a block
-    EPF_HALO = 128      // a convolution that reads the unpadded batch (GemmArgs::halo_src)
+    EPF_HALO = 128,     // a convolution that reads the unpadded batch (GemmArgs::halo_src)
+    EPF_STAT = 256      // moments of the output (GemmCore::stats)
 };
 template <int BM, int BN, bool GEGLU, int WGM = 2, int WGN = 2, bool MAY_STAT = true, int FEAT = EPF_ALL>
 __device__ __forceinline__ void gemm_epilogue(const GemmCore& a, f32x16 (&acc)[BM / WGM / 32][BN / WGN / 32], uint8_t* smem,
@@ -578,7 +579,7 @@ gemm_mfma_kernel(GemmArgs a) {
             PS_SETUP(nm0, nn0, s_tok2 + (buf ^ 1) * BM);
             PS_PROLOGUE_STAGES(0, 1);
         }
-        gemm_epilogue<BM, BN, GEGLU, WGM, WGN, false, FEAT>(a, acc, HALF ? smem + STAGE_V * 16 : ep_smem, tok_cur, n0_cur, bias_t, rowscale);
+        gemm_epilogue<BM, BN, GEGLU, WGM, WGN, (FEAT & EPF_STAT) != 0, FEAT>(a, acc, HALF ? smem + STAGE_V * 16 : ep_smem, tok_cur, n0_cur, bias_t, rowscale);
         if (nslot >= slots) break;
         if (!OVERLAP) {
             __syncthreads();                        // every wavefront is done with its staging region in the ring
@@ -1136,7 +1137,10 @@ static bool conv_tile(const GemmArgs& a, int BM, int apix_max, ConvTile* ct) {
 
 template <int BM, int BN, bool GEGLU, int WGM, int WGN, int NS, bool OVERLAP, int FEAT>
 static int launch_feat(const GemmArgs& a, hipStream_t st) {
-    constexpr size_t lds = GemmCfg<BM, BN, NS, OVERLAP>::LDS + (FEAT & EPF_HALO ? 9 * BM * sizeof(int32_t) : 0);
+    constexpr size_t sums = FEAT & EPF_STAT ? 4 * (2 * (BN / WGN) + 2) * sizeof(float) : 0;         // behind the epilogue's staging
+    constexpr size_t lds = GemmCfg<BM, BN, NS, OVERLAP>::LDS + (FEAT & EPF_HALO ? 9 * BM * sizeof(int32_t) : 0) + (OVERLAP ? sums : 0);
+    static_assert(OVERLAP || NS * GemmCfg<BM, BN, NS, OVERLAP>::STAGE - GemmCfg<BM, BN, NS, OVERLAP>::STAGE * ((NS - 1) * (BM + BN) * 128 >= 4 * (BM / WGM) * 144) >=
+                  4 * (BM / WGM) * 144 + sums, "epilogue staging and sums do not fit the stages they lie in");
     static_assert(lds <= 160 * 1024, "LDS");
     PS_SET_LDS_ONCE((gemm_mfma_kernel<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, FEAT>), lds);
     // all tiles, or as many blocks as run at once (256 CUs x the blocks of this LDS size per CU): each block then
@@ -1164,8 +1168,10 @@ static int launch(const GemmArgs& a, hipStream_t st) {
     } else {
         if (gemm_pads_rows(a)) return launch_feat<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, EPF_TRANS | EPF_SCALE | EPF_PADS>(a, st);
         if (a.halo_src) return launch_feat<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, EPF_HALO>(a, st);
+        if (a.stats) return launch_feat<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, EPF_STAT>(a, st);       // (gemm_stats_rows)
         if constexpr (BN != 64) {
-            if (!a.rowbias && !a.rowscale && !a.act_gelu) {
+            // (a request's bias needs no look-up per row where a wavefront's rows lie in one patch)
+            if ((!a.rowbias || (a.tokens_are_rows && a.geom.S % (BM / WGM) == 0)) && !a.rowscale && !a.act_gelu) {
                 if (seg) return launch_feat<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, EPF_TRANS | EPF_SCALE>(a, st);
                 return launch_feat<BM, BN, GEGLU, WGM, WGN, NS, OVERLAP, 0>(a, st);
             }
@@ -1174,29 +1180,28 @@ static int launch(const GemmArgs& a, hipStream_t st) {
     }
 }
 
-// Which halo-in-LDS convolution kernel a problem takes (0: none) and the columns one wavefront of it covers.
+// Which halo-in-LDS convolution kernel a problem takes (0: none).
 // Preferred: 256 x 160 tiles, four wavefronts stacked along M (each 64 x 160), three weight stages: half the weight
 // bytes per MFMA of the 128 x 320 tile at the same accumulator shape.  That tile runs with the K split (eight
 // wavefronts): 66 instead of 70 us at C = 320 / 29,696 tokens, 541 instead of 576 us at C = 640 / about 79,000 tokens.
-static int conv_select(const GemmArgs& a, ConvTile* ct, int* wave_cols = nullptr) {
-    int wc = 0, sel = 0;
+static int conv_select(const GemmArgs& a, ConvTile* ct) {
+    int sel = 0;
     const bool plain3x3 = a.taps == 9 && (a.tap_w == 0 || a.tap_w == 3) && a.a_mul <= 1 && !a.a_dy && !a.a_dx && !a.o_mul;
     // no gate, no GELU, no transposed segment; a per-request bias only where a wavefront's 64 rows lie in one patch (the
     // kernels compile the epilogue without those paths)
     const bool lean = a.seg[0].scale == 1.f && !a.rowscale && !a.act_gelu && (!a.rowbias || (a.geom.S % 64 == 0 && a.geom.pw <= 64 && 64 % a.geom.pw == 0));
     if (plain3x3 && gemm_fits32(a) && lean && a.epi == EPI_ROUTE && a.seg_cols % 32 == 0 && a.seg_cols == a.N && !a.seg[0].transposed) {
-        if (a.N % 160 == 0 && conv_tile(a, 256, 384, ct)) { sel = 1; wc = 160; }
+        if (a.N % 160 == 0 && conv_tile(a, 256, 384, ct)) sel = 1;
         // small patches (8 x 8: four segments of 10 x 10 pixels per 256 rows) need more halo slots than that tile's LDS
         // has beside three weight stages; with two weight stages 416 slots fit
-        else if (a.N % 160 == 0 && conv_tile(a, 256, 416, ct)) { sel = 6; wc = 160; }
+        else if (a.N % 160 == 0 && conv_tile(a, 256, 416, ct)) sel = 6;
         else if (conv_tile(a, 128, 256, ct)) {
-            if (a.N % 320 == 0) { sel = 2; wc = 160; }
-            else if (a.N % 256 == 0) { sel = 3; wc = 128; }
-            else if (a.N % 128 == 0) { sel = 4; wc = 64; }
-            else if (a.N % 64 == 0) { sel = 5; wc = 32; }
+            if (a.N % 320 == 0) sel = 2;
+            else if (a.N % 256 == 0) sel = 3;
+            else if (a.N % 128 == 0) sel = 4;
+            else if (a.N % 64 == 0) sel = 5;
         }
     }
-    if (wave_cols) *wave_cols = wc;
     return sel;
 }
 
@@ -1205,78 +1210,154 @@ int gemm_few_bf16(const GemmArgs& a, int tile, hipStream_t st);
 
 static constexpr int CONV_BM[7] = {0, 256, 128, 128, 128, 128, 256}, CONV_BN[7] = {1, 160, 320, 256, 128, 64, 160};
 
-// How long the halo-in-LDS kernel `sel` takes, in us (a step is a tap of a 64-channel chunk; a shared tile's sums are written and
-// read back), and in how many shares of the channel chunks it does.  Fitted to 70 measured sizes; what it decides is between
-// this kernel's two forms and the small tiles of gemm_few.hip, and there it errs by less than a tenth.
+// How long the halo-in-LDS kernel `sel` takes, in us (a step is a tap of a 64-channel chunk, slower the more of the chip is at it; a
+// shared tile's sums are written and read back), and in how many shares of the channel chunks it does.  Fitted to 150 measured sizes
+// (within a tenth).
 static double conv_time(const GemmArgs& a, int sel, int* splits) {
     static const double step[7] = {0, 0.95, 0.95, 0.93, 0.6, 0.49, 0.95};
-    const int64_t tiles = cdiv(a.M, CONV_BM[sel]) * (a.N / CONV_BN[sel]), chunks = a.K / 64;
+    const int64_t tiles = cdiv(a.M, CONV_BM[sel]) * (a.N / CONV_BN[sel]), chunks = a.K / 64, rounds = cdiv(tiles, 256);
     const int z = conv_splits(tiles, chunks);
-    const double whole = cdiv(tiles, 256) * (5.0 + 9 * chunks * step[sel]);
+    const double whole = CONV_BM[sel] == 256 ? rounds * 12.0 + 9 * chunks * (0.6 * rounds + 0.42 * tiles / 256) : rounds * (5.0 + 9 * chunks * step[sel]);
     const double shared = 11.0 + 9 * cdiv(chunks, z) * step[sel] + 1.5e-6 * z * (double)a.M * a.N;
     *splits = z > 1 && shared < whole ? z : 1;
-    return std::min(whole, shared);
+    return *splits > 1 ? shared : whole;
 }
 
-// The tile of gemm_few.hip that a 3x3 convolution with `sel` to choose from takes, 0: it takes that kernel.  us, few / before:
-// 1,024 tokens x 320 channels 9.9 / 23.9, 4,096 15.5 / 34.6, 12,288 42 / 75, 16,384 57 / 51; 1,024 x 640 19 / 31, 4,096 48 / 51, 6,144 69 / 59;
-// 8,192 x 256 21 / 45; 8,192 x 128 8.8 / 16; 16,384 x 64 7.5 / 9.5.  Up to 1,024 channels: above, the weights (more than 29 MB) come from
-// HBM in a whole network, and the longer chain waits for them (1,024 x 1,280 41 / 46, with cold weights 52 / 48).
-static int conv_few(const GemmArgs& a, int sel) {
-    int splits;
-    double us;
-    const int few = a.K <= 1024 ? few_pick(a, 4, &us) : 0;
-    return few && us < conv_time(a, sel, &splits) ? few : 0;
+// gemm_mfma_kernel's tile for a problem: its columns (128 with `three`: three stages and one block a CU), 0: none.
+static int tile_pick(const GemmArgs& a, bool* three) {
+    // Two blocks of 128 rows a CU (one block's prologue and epilogue run beside the other's main loop).
+    const int64_t m128 = cdiv(a.M, 128), classes = std::max(1, a.classes);
+    const int64_t t160 = a.N % 160 == 0 ? m128 * (a.N / 160) * classes : 0, t128 = a.N % 128 == 0 ? m128 * (a.N / 128) * classes : 0;
+    *three = false;
+    if (a.seg_cols % 32 != 0) return 0;             // a 32-column tile must not straddle output segments
+    // N a multiple of 160: 128 x 160 tiles (wavefront tile 32 x 160).  Against a 256 x 160 tile
+    // the rounds were the same: 34 -> 28 us (13,312 x 640 x 640), 68 -> 63 us (K = 2560), 80 -> 72 us
+    // (13.4 k x 1280 x 1280), 165 -> 137 us (79 k x 640 x 640).
+    // From 208 tiles on: the 128 x 64 tiles, 2.5 times as many, run 512 at a time, so up to 204 of these they take one round
+    // and then two.  us, 128 x 160 / 128 x 64: 200 tiles K = 320 16.8 / 13.1, 640 20.1 / 15.8, 1280 26.6 / 22.8, 2560 40.3 / 33.8,
+    // 5120 69.3 / 59.5; 204 tiles K = 640 18.9 / 16.8; 208 tiles 17.0 / 17.4, 20.2 / 21.0, 27.0 / 30.0, 42.7 / 46.3, 69.3 / 82.6.
+    // But where 128 x 128 tiles still run in one round and these have CUs with two: 9,000 x 640, K = 640 20.3 / 128 x 128 18.4; 6,000 x
+    // 1,280, K = 1,280 32.5 / 30.2; 1,536 x 3,840 29.2 / 26.6 (4,096 x 1,280, K = 5,120, 256 tiles: 67.8 / 74.2).
+    const bool one_round = t128 > 256 && t128 <= 512;
+    if (t160 >= 208 && !(one_round && t160 > 256)) return 160;
+    // 128 x 128 tiles from where they do not fit one block a CU.  us, these / 256 x 128 (one block a CU) / 128 x 64: 306 tiles K = 384
+    // 14.6 / 19.4 / 16.5, 480 K = 768 22.6 / 26.2 / 28.3, 576 K = 1,536 48.9 / 56.9 / 50.5, 816 K = 512 31.2 / 36.4 / 37.3, 1,278 K = 768
+    // 49.6 / 60.5 / 60.3.  With fewer, 128 x 64 (204 tiles K = 128 8.5 / 11.9 / 8.9, 120 K = 1,536 22.3 / - / 15.4), unless the chain of
+    // steps is long and these have CUs with two blocks: then 128 x 128 with three stages, one block a CU (144 tiles K = 3,072 28.6 / 31.7).
+    if (t128 > 256) return 128;
+    const int64_t t64 = a.N % 64 == 0 ? m128 * (a.N / 64) * classes : 0;
+    if (t128 && t64 > 256 && (int64_t)a.taps * (a.K / 64) >= 32) {
+        *three = true;
+        return 128;
+    }
+    return t64 ? 64 : 0;
+}
+// How long that takes for a convolution, in us; fitted to 83 measured sizes (within a tenth).
+static double tile_time(const GemmArgs& a) {
+    bool three;
+    const int bn = tile_pick(a, &three);
+    if (!bn) return 1e30;
+    const int64_t t = cdiv(a.M, 128) * (a.N / bn) * std::max(1, a.classes), full = (t - 1) / 512, rest = t - 512 * full;
+    const double s = (double)a.taps * (a.K / 64), one = std::min<int64_t>(t, 256) / 256.0, over = std::max<int64_t>(rest - 256, 0) / 256.0;
+    if (three) return 8.0 + s * (0.47 + 0.09 * one);
+    if (bn == 64) {
+        const double k = (double)cdiv(t, 256);
+        return t <= 256 ? 7.0 + 0.385 * s : t <= 512 ? 9.0 + s * (0.46 + 0.12 * over) : 4.0 * k + s * (0.04 + 0.28 * k);
+    }
+    if (bn == 160) {
+        if (!full) return t <= 256 ? 9.5 + 0.714 * s : 8.0 + s * (0.96 + 0.37 * over);
+        return full * (6.0 + 1.33 * s) + (rest <= 256 ? 4.0 + s * (0.33 + 0.28 * rest / 256) : 6.0 + s * (0.93 + 0.37 * over));
+    }
+    if (!full) return 8.0 + s * (0.84 + 0.26 * over);
+    return full * (6.0 + 1.09 * s) + (rest <= 256 ? 4.0 + s * (0.28 + 0.19 * rest / 256) : 6.0 + s * (0.8 + 0.25 * over));
 }
 
-bool gemm_emits_stats(const GemmArgs& a, int dtype, int mode) {
-    if (mode != 0 || dtype != PSERVE_BF16 || !a.stats || a.stats_G <= 0 || !gemm_mfma_eligible(a)) return false;
+// The kernel a convolution takes: the small tiles of gemm_few.hip (few: which), the halo in LDS (sel, its tile, its shares) or, with
+// neither, gemm_mfma_kernel.  The first are ahead while a few rounds of them do; the second with many channels, where the nine
+// reads of a pixel are long; the last has two blocks a CU and a round of 512 tiles, so it wastes less of one.  By the three models,
+// the last only where it is clearly ahead.  us of one 3x3 convolution, 16 x 16 patches, few or halo / gemm_mfma_kernel:
+//   1,024 tokens x 320 channels 9.9 / 23.9;  4,096 x 640 52.6 / 54.2;  9,216 x 256 31.6 / 26.9, 16,384 38.9 / 29.6, 36,864 79.5 / 61.7;
+//   36,864 x 64 17.3 / 13.4, x 128 33.9 / 25.1, x 192 65.3 / 43.7, x 384 153 / 123, x 512 215 / 202, x 768 422 / 408;
+//   12,288 x 320 44.4 / 35.0, 16,384 48.5 / 41.6, 24,576 53.1 / 59.3, 36,864 100 / 90; 16,384 x 640 107 / 129, 36,864 283 / 287;
+//   6,144 x 960 122 / 144; 2,048 x 1280 71 / 101, 12,288 345 / 356.  Patches the halo does not take, two layers with their norms:
+//   2,304 x 960 154 / 185.
+// Small tiles up to 1,024 channels where the halo is the other choice: above, the weights (more than 29 MB) come from HBM in a whole
+// network, and the longer chain waits for them (1,024 x 1,280 41 / 46, with cold weights 52 / 48).
+struct ConvChoice {
+    int sel, few, splits;
     ConvTile ct;
-    int wc = 0;
-    const int sel = conv_select(a, &ct, &wc);
-    if (!sel || conv_few(a, sel)) return false;
-    // a wavefront's 64 rows must lie in one patch, and its columns must hold whole groups
-    return a.geom.S % 64 == 0 && a.stats_slots == a.geom.S / 64 && !a.act.active && a.N % a.stats_G == 0 &&
-           wc % (a.N / a.stats_G) == 0;
+};
+static ConvChoice conv_choose(const GemmArgs& a) {
+    ConvChoice c{0, 0, 1, {}};
+    double few = 1e30;
+    c.sel = conv_select(a, &c.ct);
+    if (!c.sel) {           // one round of small tiles; more only for plain convolutions
+        c.few = few_pick(a, 1, &few);
+        if (!c.few && a.K <= 1024 && a.taps == 9 && a.a_mul <= 1) {
+            c.few = few_pick(a, 4, &few);
+            if (few > 0.95 * tile_time(a)) c.few = 0;
+        }
+        return c;
+    }
+    const double halo = conv_time(a, c.sel, &c.splits);
+    if (a.K <= 1024) c.few = few_pick(a, 4, &few);
+    if (few >= halo) c.few = 0;
+    if (tile_time(a) < (c.few ? 0.9 * few : c.sel == 4 || c.sel == 5 ? halo : 0.95 * halo)) c.few = c.sel = 0;
+    if (c.few) c.sel = 0;
+    return c;
 }
 
+int gemm_stats_rows(const GemmArgs& a, int dtype, int mode) {
+    if (mode != 0 || dtype != PSERVE_BF16 || !a.conv || a.epi != EPI_ROUTE || a.taps != 9 || a.stats_G <= 0 || !gemm_mfma_eligible(a)) return 0;
+    const ConvChoice c = conv_choose(a);
+    if (c.few || a.act.active || a.N % a.stats_G != 0) return 0;
+    // a wavefront's rows must lie in one patch, and its columns must hold whole groups
+    static constexpr int cols[7] = {0, 160, 160, 128, 64, 32, 160};
+    bool three;
+    const int bn = c.sel ? 0 : tile_pick(a, &three);
+    if (!c.sel && !bn) return 0;
+    const int rows = c.sel || bn != 160 ? 64 : 32, wc = c.sel ? cols[c.sel] : bn == 160 ? 160 : bn / 2;
+    return a.geom.S % rows == 0 && wc % (a.N / a.stats_G) == 0 ? rows : 0;
+}
+
+static GemmArgs conv_args(const PatchGeom& g, int32_t M, int32_t N, int32_t K) {
+    GemmArgs a{};
+    a.conv = 1; a.tokens_are_rows = 1; a.taps = 9; a.geom = g; a.M = M; a.N = a.seg_cols = N; a.K = a.lda = K;
+    for (auto& s : a.seg) s.scale = 1.f;
+    return a;
+}
 size_t conv_split_bytes(const PatchGeom& g, int32_t M, int32_t N, int32_t K, int dtype, int mode) {
     if (dtype != PSERVE_BF16 || mode != 0 || K % 64 != 0) return 0;
-    GemmArgs a{};
-    a.conv = 1; a.tokens_are_rows = 1; a.taps = 9; a.geom = g; a.M = M; a.N = N; a.K = K; a.lda = K; a.seg_cols = N;
-    for (auto& s : a.seg) s.scale = 1.f;
-    ConvTile ct;
-    const int sel = conv_select(a, &ct);
-    if (!sel || conv_few(a, sel)) return 0;
-    int z;
-    conv_time(a, sel, &z);
-    return z > 1 ? sizeof(float) * z * cdiv(M, CONV_BM[sel]) * CONV_BM[sel] * (size_t)N : 0;
+    const GemmArgs a = conv_args(g, M, N, K);
+    const ConvChoice c = conv_choose(a);
+    return c.sel && c.splits > 1 ? sizeof(float) * c.splits * cdiv(M, CONV_BM[c.sel]) * CONV_BM[c.sel] * (size_t)N : 0;
 }
 
 // For tests (host only, no part of the ABI): 1 if the 3x3 convolutions of such a batch (bf16, C to C channels) have few enough
-// tiles to share them, where the small tiles of gemm_few.hip do not take them.
+// tiles to share them, where no other kernel takes them.
 extern "C" int pserve_test_conv_shares(int32_t P, int32_t ph, int32_t pw, int32_t C) {
-    const PatchGeom g{P, ph * pw, ph, pw, pw + 2, (ph + 2) * (pw + 2)};
-    GemmArgs a{};
-    a.conv = 1; a.tokens_are_rows = 1; a.taps = 9; a.geom = g; a.M = P * ph * pw; a.N = a.K = a.lda = a.seg_cols = C;
-    for (auto& s : a.seg) s.scale = 1.f;
     ConvTile ct;
-    const int sel = conv_select(a, &ct);
-    return sel && conv_splits(cdiv(a.M, CONV_BM[sel]) * (a.N / CONV_BN[sel]), a.K / 64) > 1;
+    const int sel = conv_select(conv_args(PatchGeom{P, ph * pw, ph, pw, pw + 2, (ph + 2) * (pw + 2)}, P * ph * pw, C, C), &ct);
+    return sel && conv_splits(cdiv((int64_t)P * ph * pw, CONV_BM[sel]) * (C / CONV_BN[sel]), C / 64) > 1;
+}
+// How such a convolution runs: 0 the small tiles, 1 the halo in LDS, 2 the linear layers' tiles; + 10 x the rows of its output's moments
+// (32 groups).
+extern "C" int pserve_test_conv_kernel(int32_t P, int32_t ph, int32_t pw, int32_t C) {
+    GemmArgs a = conv_args(PatchGeom{P, ph * pw, ph, pw, pw + 2, (ph + 2) * (pw + 2)}, P * ph * pw, C, C);
+    a.stats_G = 32;
+    const ConvChoice c = conv_choose(a);
+    return (c.few ? 0 : c.sel ? 1 : 2) + 10 * gemm_stats_rows(a, PSERVE_BF16, 0);
 }
 // The tile of gemm_few.hip that such a convolution takes instead (1 .. 5: 32 x 32, 32 x 64, 32 x 80, 64 x 64, 64 x 80), 0: none; linear:
 // that of a linear layer of P * ph * pw rows, K = C, N columns in segments of seg_cols (value-gate pairs: seg_cols = 0).
 extern "C" int pserve_test_few_tile(int32_t P, int32_t ph, int32_t pw, int32_t C, int32_t linear, int32_t N, int32_t seg_cols) {
-    GemmArgs a{};
-    a.geom = PatchGeom{P, ph * pw, ph, pw, pw + 2, (ph + 2) * (pw + 2)};
-    a.tokens_are_rows = 1; a.taps = linear ? 1 : 9; a.conv = !linear; a.M = P * ph * pw; a.K = a.lda = C; a.N = linear ? N : C;
-    a.epi = linear && !seg_cols ? EPI_GEGLU : EPI_ROUTE;
-    a.seg_cols = !linear ? C : seg_cols ? seg_cols : N;
-    for (auto& s : a.seg) s.scale = 1.f;
-    ConvTile ct;
+    GemmArgs a = conv_args(PatchGeom{P, ph * pw, ph, pw, pw + 2, (ph + 2) * (pw + 2)}, P * ph * pw, C, C);
+    if (!linear) return conv_choose(a).few;
+    a.taps = 1; a.conv = 0; a.N = N;
+    a.epi = !seg_cols ? EPI_GEGLU : EPI_ROUTE;
+    a.seg_cols = seg_cols ? seg_cols : N;
     double us;
-    const int sel = linear ? 0 : conv_select(a, &ct);
-    return sel ? conv_few(a, sel) : few_pick(a, a.epi == EPI_GEGLU ? 2 : 1, &us);
+    return few_pick(a, a.epi == EPI_GEGLU ? 2 : 1, &us);
 }
 
 int gemm_wide_bf16(const GemmArgs& a, hipStream_t st, bool* handled);     // gemm_wide.hip
@@ -1306,20 +1387,20 @@ int gemm_two_bf16(const GemmArgs& a, int cols, hipStream_t st) {
 
 // What gemm_mfma_bf16 sends to gemm_few_kernel or gemm_mfma_kernel, whose HALO forms look up where each row's pixels lie once a tile.
 bool gemm_takes_halo(const GemmArgs& a, int dtype, int mode) {
-    ConvTile ct;
-    double us;
-    return dtype == PSERVE_BF16 && mode == 0 && gemm_mfma_eligible(a) && a.conv && a.epi == EPI_ROUTE && a.tokens_are_rows && !a.act.active &&
-           !a.B2 && a.taps <= 9 && !a.rowbias && !a.rowscale && !a.act_gelu && !a.seg[0].transposed && a.seg[0].scale == 1.f &&
-           a.seg_cols == a.N && !conv_select(a, &ct) && (few_pick(a, 1, &us) || a.N % 64 == 0 || (a.N % 160 == 0 && cdiv(a.M, 128) * (a.N / 160) * std::max(1, a.classes) >= 208));
+    if (dtype != PSERVE_BF16 || mode != 0 || !gemm_mfma_eligible(a) || !a.conv || a.epi != EPI_ROUTE || !a.tokens_are_rows || a.act.active || a.B2 ||
+        a.taps > 9 || a.rowbias || a.rowscale || a.act_gelu || a.seg[0].transposed || a.seg[0].scale != 1.f || a.seg_cols != a.N) return false;
+    const ConvChoice c = conv_choose(a);
+    bool three;
+    return !c.sel && (c.few || tile_pick(a, &three));
 }
 
 int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
     *handled = false;
     if (!gemm_mfma_eligible(a)) return PSERVE_OK;
-    ConvTile ct;
-    const int sel = a.conv && a.epi == EPI_ROUTE ? conv_select(a, &ct) : 0;
     double us;
-    const int few = a.B2 ? 0 : sel ? conv_few(a, sel) : few_pick(a, a.epi == EPI_GEGLU ? 2 : 1, &us);
+    const bool conv = a.conv && a.epi == EPI_ROUTE;
+    const ConvChoice c = conv ? conv_choose(a) : ConvChoice{0, 0, 1, {}};
+    const int few = a.B2 ? 0 : conv ? c.few : few_pick(a, a.epi == EPI_GEGLU ? 2 : 1, &us);
     if (few) {
         *handled = true;
         return gemm_few_bf16(a, few, st);
@@ -1337,40 +1418,23 @@ int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
         // K = 1,280 25.8 / 22.3; 1,024 x 5,120, K = 640 18.8 / 16.0; 13,312 x 5,120, K = 640 163 / 142.
         return launch<128, 128, true, 4, 1, 2, false>(a, st);
     }
-    if (a.seg_cols % 32 != 0) return PSERVE_OK;      // a 32-column tile must not straddle output segments
-    int splits = 1;
-    if (sel) conv_time(a, sel, &splits);
-    switch (sel) {
-    case 1: *handled = true; return launch_conv<256, 160, 4, 1, 384, 3, 2>(a, ct, splits, st);
-    case 2: *handled = true; return launch_conv<128, 320, 2, 2, 256, 2>(a, ct, splits, st);
-    case 3: *handled = true; return launch_conv<128, 256, 2, 2, 256, 2>(a, ct, splits, st);
-    case 4: *handled = true; return launch_conv<128, 128, 2, 2, 256, 2>(a, ct, splits, st);
-    case 5: *handled = true; return launch_conv<128, 64, 2, 2, 256, 2>(a, ct, splits, st);
-    case 6: *handled = true; return launch_conv<256, 160, 4, 1, 416, 2, 2>(a, ct, splits, st);
+    *handled = true;
+    switch (c.sel) {
+    case 1: return launch_conv<256, 160, 4, 1, 384, 3, 2>(a, c.ct, c.splits, st);
+    case 2: return launch_conv<128, 320, 2, 2, 256, 2>(a, c.ct, c.splits, st);
+    case 3: return launch_conv<128, 256, 2, 2, 256, 2>(a, c.ct, c.splits, st);
+    case 4: return launch_conv<128, 128, 2, 2, 256, 2>(a, c.ct, c.splits, st);
+    case 5: return launch_conv<128, 64, 2, 2, 256, 2>(a, c.ct, c.splits, st);
+    case 6: return launch_conv<256, 160, 4, 1, 416, 2, 2>(a, c.ct, c.splits, st);
     default: break;
     }
-    // Tile choice: two blocks of 128 rows a CU (one block's prologue and epilogue run beside the other's main loop).
-    const int64_t m128 = cdiv(a.M, 128), classes = std::max(1, a.classes);
-    const int64_t t160 = a.N % 160 == 0 ? m128 * (a.N / 160) * classes : 0, t128 = a.N % 128 == 0 ? m128 * (a.N / 128) * classes : 0;
-    *handled = true;
-    // N a multiple of 160: 128 x 160 tiles (wavefront tile 32 x 160).  Against a 256 x 160 tile
-    // the rounds were the same: 34 -> 28 us (13,312 x 640 x 640), 68 -> 63 us (K = 2560), 80 -> 72 us
-    // (13.4 k x 1280 x 1280), 165 -> 137 us (79 k x 640 x 640).
-    // From 208 tiles on: the 128 x 64 tiles, 2.5 times as many, run 512 at a time, so up to 204 of these they take one round
-    // and then two.  us, 128 x 160 / 128 x 64: 200 tiles K = 320 16.8 / 13.1, 640 20.1 / 15.8, 1280 26.6 / 22.8, 2560 40.3 / 33.8,
-    // 5120 69.3 / 59.5; 204 tiles K = 640 18.9 / 16.8; 208 tiles 17.0 / 17.4, 20.2 / 21.0, 27.0 / 30.0, 42.7 / 46.3, 69.3 / 82.6.
-    // But where 128 x 128 tiles still run in one round and these have CUs with two: 9,000 x 640, K = 640 20.3 / 128 x 128 18.4; 6,000 x
-    // 1,280, K = 1,280 32.5 / 30.2; 1,536 x 3,840 29.2 / 26.6 (4,096 x 1,280, K = 5,120, 256 tiles: 67.8 / 74.2).
-    const bool one_round = t128 > 256 && t128 <= 512;
-    if (t160 >= 208 && !(one_round && t160 > 256)) return launch<128, 160, false, 4, 1, 2, false>(a, st);
-    // 128 x 128 tiles from where they do not fit one block a CU.  us, these / 256 x 128 (one block a CU) / 128 x 64: 306 tiles K = 384
-    // 14.6 / 19.4 / 16.5, 480 K = 768 22.6 / 26.2 / 28.3, 576 K = 1,536 48.9 / 56.9 / 50.5, 816 K = 512 31.2 / 36.4 / 37.3, 1,278 K = 768
-    // 49.6 / 60.5 / 60.3.  With fewer, 128 x 64 (204 tiles K = 128 8.5 / 11.9 / 8.9, 120 K = 1,536 22.3 / - / 15.4), unless the chain of
-    // steps is long and these have CUs with two blocks: then 128 x 128 with three stages, one block a CU (144 tiles K = 3,072 28.6 / 31.7).
-    if (t128 > 256) return launch<128, 128, false, 2, 2, 2, false>(a, st);
-    const int64_t t64 = a.N % 64 == 0 ? m128 * (a.N / 64) * classes : 0;
-    if (t128 && t64 > 256 && (int64_t)a.taps * (a.K / 64) >= 32) return launch<128, 128, false, 2, 2, 3, true>(a, st);
-    if (t64) return launch<128, 64, false, 2, 2, 3, false>(a, st);
+    bool three;
+    switch (tile_pick(a, &three)) {
+    case 160: return launch<128, 160, false, 4, 1, 2, false>(a, st);
+    case 128: return three ? launch<128, 128, false, 2, 2, 3, true>(a, st) : launch<128, 128, false, 2, 2, 2, false>(a, st);
+    case 64: return launch<128, 64, false, 2, 2, 3, false>(a, st);
+    default: break;
+    }
     *handled = false;
     return PSERVE_OK;
 }

@@ -179,8 +179,8 @@ struct GemmCore {
     int32_t seg_cols;
     GemmSeg seg[3];
     // Optional GroupNorm partial sums of the OUTPUT (bias included, before the residual), in the layout gn_finalize
-    // reads: stats[P][stats_slots][stats_G][2] = (sum, sum of squares) of 64 consecutive tokens of a patch
-    // (stats_slots = S / 64) and one group.  Only the kernels gemm_emits_stats() accepts fill it (plain stores).
+    // reads: stats[P][stats_slots][stats_G][2] = (mean, sum of squared deviations) of S / stats_slots consecutive tokens of a patch
+    // and one group.  Only the kernels gemm_stats_rows() accepts fill it (plain stores).
     float* stats;
     int32_t stats_G, stats_slots;
 };
@@ -220,8 +220,9 @@ bool gemm_takes_halo(const GemmArgs& a, int dtype, int mode);
 bool gemm_takes_pieces(const GemmArgs& a, int dtype, int mode);
 // scratch a 3x3 convolution of M rows, N output and K input channels over this patch geometry can use (0: none)
 size_t conv_split_bytes(const PatchGeom& g, int32_t M, int32_t N, int32_t K, int dtype, int mode);
-// true if gemm(a, ...) will take a kernel that fills a.stats (the caller otherwise runs gn_stats on the output)
-bool gemm_emits_stats(const GemmArgs& a, int dtype, int mode);
+// tokens a partial sum of a.stats covers where gemm(a, ...), with a.stats_G groups, takes a kernel that fills it, else 0 (the caller then
+// runs gn_stats on the output)
+int gemm_stats_rows(const GemmArgs& a, int dtype, int mode);
 int gemm(const GemmArgs& a, int dtype, int mode, hipStream_t st);
 
 // Weight packing into [taps][N][K] (K contiguous); all on device.  fp32 weights (rows = taps x N) of a layer that may take its
