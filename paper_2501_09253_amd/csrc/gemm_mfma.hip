@@ -1265,7 +1265,7 @@ static double tile_time(const GemmArgs& a) {
         return t <= 256 ? 7.0 + 0.385 * s : t <= 512 ? 9.0 + s * (0.46 + 0.12 * over) : 4.0 * k + s * (0.04 + 0.28 * k);
     }
     if (bn == 160) {
-        if (!full) return t <= 256 ? 9.5 + 0.714 * s : 8.0 + s * (0.96 + 0.37 * over);
+        if (!full) return t <= 256 ? 9.5 + 0.67 * s : 8.0 + s * (0.96 + 0.37 * over);
         return full * (6.0 + 1.33 * s) + (rest <= 256 ? 4.0 + s * (0.33 + 0.28 * rest / 256) : 6.0 + s * (0.93 + 0.37 * over));
     }
     if (!full) return 8.0 + s * (0.84 + 0.26 * over);
@@ -1430,7 +1430,13 @@ int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
     }
     bool three;
     switch (tile_pick(a, &three)) {
-    case 160: return launch<128, 160, false, 4, 1, 2, false>(a, st);
+    case 160:
+        // One block a CU: the LDS that a second one would take holds two more stages.  us, two / four: text keys and values of 22 x 77
+        // tokens x 2,560, K = 2,048 38.7 / 32.6 (and 183.4 / 189.9 for the cross-attention around them); residual blocks of one
+        // convolution, 4,400 tokens x 960 112 / 98, 4,000 x 1280 146 / 135, 8,000 x 640 85.5 / 83.5.  (Three: the same to 1 us; the
+        // 128 x 64 tiles with six instead of three 29.6 / 30.7, 47.5 / 48.1.)
+        if (cdiv(a.M, 128) * (a.N / 160) * std::max(1, a.classes) <= 256) return launch<128, 160, false, 4, 1, 4, false>(a, st);
+        return launch<128, 160, false, 4, 1, 2, false>(a, st);
     case 128: return three ? launch<128, 128, false, 2, 2, 3, true>(a, st) : launch<128, 128, false, 2, 2, 2, false>(a, st);
     case 64: return launch<128, 64, false, 2, 2, 3, false>(a, st);
     default: break;

@@ -37,3 +37,13 @@ def test_conv_choice(name):
     assert ps.lib().pserve_test_conv_kernel(P, ph, pw, C) == kernel + 10 * rows
     c.pop("patch")
     _check(wl.make_workload(wl.custom_config(res, (ph, pw), C=C, G=32, heads=C // 64, stages=c.pop("stages"), dtype="bf16", seed=67, **c)))
+
+
+@pytest.mark.parametrize("c", [dict(res=[(4, 4)] * 22, patch=(4, 4), C=1280, stages=("XATTN",), ctx_len=77, ctx_dim=256),
+                               dict(res=[(80, 80), (20, 10)], patch=(10, 10), C=640, stages=("LFFN",))], ids=["text", "rows"])
+def test_four_stages(c):
+    """208 to 256 tiles of 128 x 160, one block a CU: four stages, as many K steps and more, padded text rows, a ragged last tile."""
+    c = dict(c)
+    C = c.pop("C")
+    _check(wl.make_workload(wl.custom_config(c.pop("res"), c.pop("patch"), C=C, G=32, heads=C // 64, stages=c.pop("stages"), dtype="bf16",
+                                             seed=71, **c)))
