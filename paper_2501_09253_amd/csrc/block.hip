@@ -761,8 +761,8 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
         // their stage.  Those of later stages beside the stage before: 2,064 -> 2,060 us for two stages of 11,520 + 616 tokens
         // x 1536, 4,080 -> 4,065 for four, but 705 -> 717 for three of 4,352 + 462 x 768, which fork and join already.
         c->side_temb = !joint && macs >= (int64_t)8 << 20;
-        // A joint block whose layers do not take both streams in one launch (small batches, fp32) runs the text stream's
-        // kernels (few tiles each: latency bound) on the side stream, beside the image stream's.
+        // A joint block whose layers do not take both streams in one launch (fp32, offsets past 32 bits) runs the text
+        // stream's kernels (few tiles each: latency bound) on the side stream, beside the image stream's.
         if (side_kv || c->side_temb || joint) {
             PS_CHECK_HIP(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
             if (joint)
@@ -1264,7 +1264,8 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
                 PS_TRY(run(MLP_OUT));
                 break;
             }
-            // Small batches: the text stream's kernels go to the side stream.  They touch the rows of the text patches only
+            // Layers that do not take both streams in one launch (fp32, offsets past 32 bits): the text stream's kernels go to the
+            // side stream.  They touch the rows of the text patches only
             // (every buffer is shared row-wise), so the two streams meet at the attention and at the end of the stage.
             hipStream_t sx[2] = {st, cache->side ? cache->side : st};
             auto fork_txt = [&](int e) -> int {           // the side stream continues from this point of the main one
