@@ -791,6 +791,7 @@ int pack_geglu(const void* w1, const void* b1, void* dst, float* bias_dst, int32
 // ---- dispatch -------------------------------------------------------------------------------------------
 int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled);     // gemm_mfma.hip
 
+bool gemm_few_f32(const GemmArgs& a, hipStream_t st);       // gemm_few.hip
 int gemm(const GemmArgs& a, int dtype, int mode, hipStream_t st) {
     PS_REQUIRE(a.M > 0 && a.N > 0 && a.K > 0, "gemm: empty problem");
     if (a.a_pieces) return gemm_split(a, st);
@@ -811,6 +812,7 @@ int gemm(const GemmArgs& a, int dtype, int mode, hipStream_t st) {
         }
         return PSERVE_OK;
     }
+    if (mode == 0 && dtype == PSERVE_F32 && gemm_few_f32(a, st)) return check_launch("gemm_few_kernel");
     if (mode == 0 && (dtype == PSERVE_BF16 ? gemm_f32mma<uint16_t>(a, st) : gemm_f32mma<float>(a, st)))
         return check_launch("gemm_f32mma_kernel");
     const bool geglu = a.epi == EPI_GEGLU;

@@ -30,11 +30,15 @@ template <int BM, int BN, int W> struct FewCfg {
 
 // TWO: a second problem (GemmArgs::B2: another patch list, weights, bias and gate of its own) continues the row tiles of the first.
 // HALO: a convolution that reads the unpadded batch (GemmArgs::halo_src), its A rows' offsets in a table of taps x BM.
+// F32: fp32 operands and outputs.  A K step is then 32 wide (the same 128 bytes a row), and a lane's 16-byte chunks, four k of a row,
+// feed four MFMAs of 16 x 16 x 4; no GELU and no transposed segments.
 enum : int { FEW_TWO = 1, FEW_HALO = 2 };
-template <int BM, int BN, int W, bool GEGLU, int FORM>
+template <int BM, int BN, int W, bool GEGLU, int FORM, bool F32 = false>
 __global__ void __launch_bounds__(64 * W)
 gemm_few_kernel(std::conditional_t<FORM != 0, GemmArgs, GemmCore> a, int pads, int m_first) {
     constexpr bool TWO = FORM == FEW_TWO, HALO = FORM == FEW_HALO;
+    constexpr int ES = F32 ? 4 : 2, KW = 128 / ES;                              // bytes of a value, K of a step
+    static_assert(!F32 || (!GEGLU && FORM == 0 && BM == 16 && BN == 16), "fp32 form");
     using Cfg = FewCfg<BM, BN, W>;
     constexpr int TM = BM / 16, TN = BN / 16, AL = BM / 8, BL = BN / 8, LD = AL + BL;
     static_assert(!GEGLU || BN == 64, "a tile of value-gate pairs is 32 values and their 32 gates");
@@ -80,7 +84,7 @@ gemm_few_kernel(std::conditional_t<FORM != 0, GemmArgs, GemmCore> a, int pads, i
     // packed column of column c of the tile (value-gate pairs: 32 values, then their gates, 64 further in groups of 128)
     auto bcol = [&](int c) { return GEGLU ? (ntile >> 1) * (2 * GEGLU_GROUP) + (ntile & 1) * 32 + (c >> 5) * GEGLU_GROUP + (c & 31) : ntile * BN + c; };
 
-    const int kchunks = a.K / 64, KT = a.taps * kchunks;
+    const int kchunks = a.K / KW, KT = a.taps * kchunks;
     const int mine = wave < KT ? (KT - wave + W - 1) / W : 0;       // K steps of this wavefront
     const int tap_w = a.tap_w ? a.tap_w : 3;
     const int fr = lane & 15, kq = lane >> 4;                       // fragment row / column, quarter of a 32-wide K piece
@@ -98,10 +102,10 @@ gemm_few_kernel(std::conditional_t<FORM != 0, GemmArgs, GemmCore> a, int pads, i
     auto advance = [&](int& tap, int& kc) { for (kc += W; kc >= kchunks; kc -= kchunks) ++tap; };
     int tap0 = 0, kc0 = wave;
     for (; kc0 >= kchunks; kc0 -= kchunks) ++tap0;
-    auto b_base = [&](int tap, int kc) { return (int)(((int64_t)(cls * a.taps + tap) * a.N * a.K + kc * 64) * 2); };
+    auto b_base = [&](int tap, int kc) { return (int)(((int64_t)(cls * a.taps + tap) * a.N * a.K + kc * KW) * ES); };
     auto a_base = [&](int tap, int kc) {
         const int ty = tap == 0 ? 0 : tap / tap_w, tx = tap - ty * tap_w;
-        return (int)(((a.conv && !HALO ? (int64_t)(ty * a.geom.ppw + tx) * a.lda : 0) + kc * 64) * 2);
+        return (int)(((a.conv && !HALO ? (int64_t)(ty * a.geom.ppw + tx) * a.lda : 0) + kc * KW) * ES);
     };
 
     // staging: lane -> (row lane / 8 of a load's eight, 16-byte position lane % 8); chunk c of row r at c ^ ((r >> 1) & 7)
@@ -109,12 +113,12 @@ gemm_few_kernel(std::conditional_t<FORM != 0, GemmArgs, GemmCore> a, int pads, i
     const int gc0 = (lc ^ sw) * 16, gc1 = (lc ^ (sw + 4)) * 16;     // byte offset of the chunk, even / odd load
     typedef __attribute__((address_space(3))) uint8_t lds_u8;
     lds_u8* ring = (lds_u8*)(smem + wave * Cfg::PART);
-    const int b_lane0 = lrow * a.K * 2 + gc0, b_lane1 = lrow * a.K * 2 + gc1;
+    const int b_lane0 = lrow * a.K * ES + gc0, b_lane1 = lrow * a.K * ES + gc1;
     auto load_b = [&](int tap, int kc, int st) {
         const int base = b_base(tap, kc);
 #pragma unroll
         for (int i = 0; i < BL; ++i)
-            PS_LOAD(b_rsrc, ring + st * Cfg::STAGE + BM * 128 + i * 1024, i & 1 ? b_lane1 : b_lane0, base + bcol(8 * i) * a.K * 2);
+            PS_LOAD(b_rsrc, ring + st * Cfg::STAGE + BM * 128 + i * 1024, i & 1 ? b_lane1 : b_lane0, base + bcol(8 * i) * a.K * ES);
     };
     int tap1 = tap0, kc1 = kc0;
     constexpr int NSRC = HALO ? (9 * BM + 64 * W - 1) / (64 * W) : 1;
@@ -165,7 +169,7 @@ gemm_few_kernel(std::conditional_t<FORM != 0, GemmArgs, GemmCore> a, int pads, i
         }
         if (!a.tokens_are_rows && a.row_group > 0) orow = tok / a.row_group * a.row_group_pad + tok % a.row_group;
         s_tok[tid] = valid ? orow : -1;
-        s_off[tid] = (int)(off * 2);
+        s_off[tid] = (int)(off * ES);
         if (a.rowbias || rowscale) s_own[tid] = a.row_owner[tok / a.geom.S];
     }
     if constexpr (HALO) {
@@ -181,15 +185,16 @@ gemm_few_kernel(std::conditional_t<FORM != 0, GemmArgs, GemmCore> a, int pads, i
     const int pcol0 = bcol(0), sg = GEGLU ? 0 : pcol0 / a.seg_cols;
     const GemmSeg seg = sg == 0 ? a.seg[0] : (sg == 1 ? a.seg[1] : a.seg[2]);
     const int ocol0 = GEGLU ? ntile * 32 : pcol0 - sg * a.seg_cols;
-    const bool tr = !GEGLU && seg.transposed;
+    const bool tr = !GEGLU && !F32 && seg.transposed;
     // what the end of the tile needs of memory, asked for in front of the activations
     constexpr int CV = (GEGLU ? 32 : BN) / 8, ITEMS = BM * CV, NIT = (ITEMS + 64 * W - 1) / (64 * W);
-    u32x4 res[NIT];
+    u32x4 res[NIT][F32 ? 2 : 1];
     float bias[NIT][GEGLU ? 16 : 8];
 #pragma unroll
     for (int u = 0; u < NIT; ++u) {
         const int it = tid + u * (64 * W);
-        res[u] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int q = 0; q < (F32 ? 2 : 1); ++q) res[u][q] = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
         for (int q = 0; q < (GEGLU ? 16 : 8); ++q) bias[u][q] = 0.f;
         if (it >= ITEMS) continue;
@@ -205,7 +210,11 @@ gemm_few_kernel(std::conditional_t<FORM != 0, GemmArgs, GemmCore> a, int pads, i
                 if (GEGLU) bias[u][8 + q] = bias_v[pcol0 + GEGLU_GROUP + ch + q];
             }
         }
-        if (!GEGLU && a.res && tok >= 0) res[u] = *reinterpret_cast<const u32x4*>((const uint16_t*)a.res + (int64_t)tok * a.ldr + pcol0 + ch);
+        if (!GEGLU && a.res && tok >= 0) {
+#pragma unroll
+            for (int q = 0; q < (F32 ? 2 : 1); ++q)
+                res[u][q] = *reinterpret_cast<const u32x4*>((const uint8_t*)a.res + ((int64_t)tok * a.ldr + pcol0 + ch) * ES + 16 * q);
+        }
     }
     asm volatile("" ::: "memory");                                  // (no load sinks below the next ones)
 
@@ -234,6 +243,9 @@ gemm_few_kernel(std::conditional_t<FORM != 0, GemmArgs, GemmCore> a, int pads, i
             advance(tap, kc);
         }
     }
+    f32x4 sum[F32 ? 8 : 1];                 // fp32: eight sums of an eighth of the products each, so that rounding does not grow with K
+#pragma unroll
+    for (int e = 0; e < (F32 ? 8 : 1); ++e) sum[e] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int fsw = (fr >> 1) & 7;
     for (int s = 0; s < mine; ++s) {
         // the own loads of step s have landed (in flight behind them: those of step s + 1, at first only its A rows)
@@ -242,14 +254,15 @@ gemm_few_kernel(std::conditional_t<FORM != 0, GemmArgs, GemmCore> a, int pads, i
         else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LD) : "memory");
         typedef const __attribute__((address_space(3))) u32x4* frag_ptr;
         const lds_u8* st = ring + (s & 1) * Cfg::STAGE;
-        bf16x8 fa[2][TM], fb[2][TN];
+        typedef std::conditional_t<F32, f32x4, bf16x8> Frag;
+        Frag fa[2][TM], fb[2][TN];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int pos = ((4 * h + kq) ^ fsw) * 16;
 #pragma unroll
-            for (int i = 0; i < TM; ++i) fa[h][i] = __builtin_bit_cast(bf16x8, *(frag_ptr)(st + (i * 16 + fr) * 128 + pos));
+            for (int i = 0; i < TM; ++i) fa[h][i] = __builtin_bit_cast(Frag, *(frag_ptr)(st + (i * 16 + fr) * 128 + pos));
 #pragma unroll
-            for (int j = 0; j < TN; ++j) fb[h][j] = __builtin_bit_cast(bf16x8, *(frag_ptr)(st + (BM + j * 16 + fr) * 128 + pos));
+            for (int j = 0; j < TN; ++j) fb[h][j] = __builtin_bit_cast(Frag, *(frag_ptr)(st + (BM + j * 16 + fr) * 128 + pos));
         }
         if (s + 2 < mine) {                                        // all fragments are read: the stage is free
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -262,10 +275,17 @@ gemm_few_kernel(std::conditional_t<FORM != 0, GemmArgs, GemmCore> a, int pads, i
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[h][i], fb[h][j], acc[i][j], 0, 0, 0);
+                for (int j = 0; j < TN; ++j) {
+                    if constexpr (F32) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) sum[4 * h + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[h][i][e], fb[h][j][e], sum[4 * h + e], 0, 0, 0);
+                    } else {
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[h][i], fb[h][j], acc[i][j], 0, 0, 0);
+                    }
+                }
     }
 #undef PS_LOAD
+    if constexpr (F32) acc[0][0] = ((sum[0] + sum[1]) + (sum[2] + sum[3])) + ((sum[4] + sum[5]) + (sum[6] + sum[7]));
 
     // ---- partial sums, each in its wavefront's own ring (nobody else reads that before the barrier)
     float* red = reinterpret_cast<float*>(smem);
@@ -360,12 +380,23 @@ gemm_few_kernel(std::conditional_t<FORM != 0, GemmArgs, GemmCore> a, int pads, i
             if (a.res) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    v[2 * q] += __uint_as_float(res[u][q] << 16);
-                    v[2 * q + 1] += __uint_as_float(res[u][q] & 0xFFFF0000u);
+                    if constexpr (F32) {
+                        v[q] += __uint_as_float(res[u][0][q]);
+                        v[4 + q] += __uint_as_float(res[u][1][q]);
+                    } else {
+                        v[2 * q] += __uint_as_float(res[u][0][q] << 16);
+                        v[2 * q + 1] += __uint_as_float(res[u][0][q] & 0xFFFF0000u);
+                    }
                 }
             }
 #pragma unroll
             for (int q = 0; q < 8; ++q) v[q] *= seg.scale;
+        }
+        if constexpr (F32) {
+            f32x4* dst = reinterpret_cast<f32x4*>((float*)seg.ptr + (int64_t)tok * seg.ld + ocol0 + ch);
+            dst[0] = f32x4{v[0], v[1], v[2], v[3]};
+            dst[1] = f32x4{v[4], v[5], v[6], v[7]};
+            continue;
         }
         *reinterpret_cast<u32x4*>(out + (int64_t)tok * seg.ld + ocol0 + ch) =
             u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
@@ -429,6 +460,25 @@ int gemm_few_bf16(const GemmArgs& a, int tile, hipStream_t st) {
     case 4: return launch_few<64, 64, false>(a, st);
     default: return launch_few<64, 80, false>(a, st);
     }
+}
+
+// fp32 (false: not for this kernel): up to 1,024 tiles of 16 x 16, four blocks a CU.  gemm_f32mma_kernel's smallest tile, 32 x 32, is four
+// wavefronts that each walk all of K at 32 clocks per four k; here they share it, on four times the blocks.  us, 32 x 32 / here:
+// convolutions 832 x 64 10.0 / 5.7, 576 x 96 14.5 / 6.1, 576 x 192 19.5 / 10.4, 1,152 x 160 19.1 / 11.4, 576 x 320 30.6 / 17.8, 1,728 x 128
+// (864 tiles) 15.3 / 12.6; linear layers 144 x 256, K = 1,024 12.4 / 5.8, 576 x 320, K = 320 7.8 / 5.6, 576 x 96, K = 96 4.8 / 4.1, but 576 x 384,
+// K = 128 (864 tiles) 5.6 / 5.9 and K = 64 alike (a launch's 4 us).  Pieces, where gemm_takes_pieces says so, come first.
+bool gemm_few_f32(const GemmArgs& a, hipStream_t st) {
+    const int64_t tiles = cdiv(a.M, 16) * (a.N / 16) * std::max(1, a.classes), k = (int64_t)a.taps * a.K;
+    if (tiles > 1024 || k < (tiles > 768 ? 256 : 96) || a.N % 16 != 0 || a.seg_cols % 16 != 0 || a.K % 32 != 0 || a.lda % 4 != 0 || a.epi != EPI_ROUTE || a.B2 ||
+        a.halo_src || a.a_pieces || a.out_pieces || a.act_gelu || a.stats || gemm_pads_rows(a) ||
+        (((uintptr_t)a.A | (uintptr_t)a.B | (uintptr_t)a.res) & 15) || (a.res && a.ldr % 4 != 0) ||
+        gemm_a_rows(a) * a.lda >= (int64_t)1 << 29 || k * a.N * std::max(1, a.classes) >= (int64_t)1 << 29) return false;
+    for (int s = 0; s < cdiv(a.N, a.seg_cols); ++s)
+        if (a.seg[s].transposed || ((uintptr_t)a.seg[s].ptr & 15) || a.seg[s].ld % 4 != 0) return false;
+    constexpr int W = 4;
+    const int m_first = (int64_t)a.M <= (int64_t)a.N * a.taps * std::max(1, a.classes);
+    gemm_few_kernel<16, 16, W, false, 0, true><<<(unsigned)(8 * cdiv(tiles, 8)), 64 * W, FewCfg<16, 16, W>::LDS, st>>>(a, 0, m_first);
+    return true;
 }
 
 }  // namespace pserve
