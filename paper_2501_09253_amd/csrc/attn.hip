@@ -475,14 +475,17 @@ __device__ __forceinline__ void at_store(const AttnArgs& a, const at_f32x16 (&ot
 // The work of a call is a row of units (32 keys of an item): slot by slot, head by head, 128 queries by 128 queries, cut into
 // equal shares, one a block.  Items that a cut goes through leave partial results, which attn_join_kernel puts together.
 struct AttnUnit { int s, h, tile, nq, nk, steps, k; int64_t first; };    // slot, head, query tile of nq, keys, unit k of steps; the item's first unit
-__device__ __forceinline__ AttnUnit at_unit(const AttnArgs& a, int64_t u) {
+__host__ __device__ __forceinline__ AttnUnit at_unit(const AttnArgs& a, int64_t u) {
     AttnUnit r;
     int lo = 0, hi = a.n;                               // largest s with unit_off[s] <= u
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
         if (a.unit_off[mid] <= u) lo = mid; else hi = mid;
     }
-    r.s = __builtin_amdgcn_readfirstlane(lo);
+#if defined(__HIP_DEVICE_COMPILE__)
+    lo = __builtin_amdgcn_readfirstlane(lo);
+#endif
+    r.s = lo;
     r.nk = a.seq_len ? a.seq_len[r.s] : a.cu_seqlens[r.s + 1] - a.cu_seqlens[r.s];
     r.steps = (r.nk + 31) / 32;
     r.nq = ((a.act_off[r.s + 1] - a.act_off[r.s]) * a.geom.S + 127) / 128;
@@ -493,7 +496,28 @@ __device__ __forceinline__ AttnUnit at_unit(const AttnArgs& a, int64_t u) {
     r.first = u - r.k;
     return r;
 }
-__device__ __forceinline__ int64_t at_share(int64_t units, int b, int blocks) { return units * b / blocks; }
+// Shares of a call for which the plan allows `blocks`: a mask may leave fewer units, and the join reads a part of every share that an
+// item lies in, so none is empty.
+__host__ __device__ __forceinline__ int at_shares(int64_t units, int blocks) { return units < blocks ? (int)units : blocks; }
+__host__ __device__ __forceinline__ int64_t at_share(int64_t units, int b, int shares) { return units * b / shares; }
+// share of a block, -1: none.  An XCD's blocks take neighbouring shares: they stream the keys of the same few heads through its L2.
+__host__ __device__ __forceinline__ int at_share_of(int block, int shares) {
+    const int xcd = block & 7, b = xcd * shares / 8 + (block >> 3);
+    return b < (xcd + 1) * shares / 8 ? b : -1;
+}
+// place of the part that share b leaves of an item: 2 b of the item that it starts in, 2 b + 1 of its last, whose head it has
+__host__ __device__ __forceinline__ int64_t at_place(int b, bool head) { return 2 * (int64_t)b + head; }
+// block j of the join: whether an item's first cut is that behind share j, the item, and the share that it ends in
+__host__ __device__ __forceinline__ bool at_join_of(const AttnArgs& a, int j, int blocks, AttnUnit* w, int* last) {
+    const int64_t units = a.unit_off[a.n];
+    const int shares = at_shares(units, blocks);
+    if (j + 1 >= shares) return false;
+    *w = at_unit(a, at_share(units, j + 1, shares));
+    if (w->k == 0 || at_share(units, j, shares) > w->first) return false;      // between two items; or not the item's first cut
+    *last = j + 1;
+    while (at_share(units, *last + 1, shares) < w->first + w->steps) ++*last;
+    return true;
+}
 
 // SHARED: a block takes a share of the units; else an item, longest first.
 template <int D, bool SHARED>
@@ -507,13 +531,15 @@ attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv, float* __re
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int fr = lane & 31, fh = lane >> 5;
     const int S = a.geom.S, C = a.C;
-    // an XCD's blocks take neighbouring shares: they stream the keys of the same few heads through its L2
-    const int nb = gridDim.x, b = (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3);
+    int b = 0;
     int64_t u = 0, u1 = 1;
     if constexpr (SHARED) {
         const int64_t units = a.unit_off[a.n];
-        u = at_share(units, b, nb);
-        u1 = at_share(units, b + 1, nb);
+        const int shares = at_shares(units, gridDim.x);
+        b = at_share_of(blockIdx.x, shares);
+        if (b < 0) return;
+        u = at_share(units, b, shares);
+        u1 = at_share(units, b + 1, shares);
     }
 #pragma unroll 1
     while (u < u1) {
@@ -735,8 +761,8 @@ attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv, float* __re
     // no load may still target LDS, and nobody may still read it, when the next share of an item starts
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
     l += __shfl_xor(l, 32, 64);
-    if (!whole) {                                       // place 2 b: of the item that the block's share starts in, 2 b + 1: of its last
-        float* dst = parts + (int64_t)(2 * b + (w.k == 0)) * Cfg::PART + tid;
+    if (!whole) {
+        float* dst = parts + at_place(b, w.k == 0) * Cfg::PART + tid;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -757,17 +783,14 @@ attn_join_kernel(AttnArgs a, const float* __restrict__ parts, int nb) {
     using Cfg = AttnSplitCfg<D>;
     constexpr int DT = D / 32;
     const int j = blockIdx.x, tid = threadIdx.x, lane = tid & 63, fr = lane & 31, fh = lane >> 5;
-    const int64_t units = a.unit_off[a.n], cut = at_share(units, j + 1, nb);
-    if (cut >= units) return;
-    const AttnUnit w = at_unit(a, cut);
-    if (w.k == 0 || at_share(units, j, nb) > w.first) return;      // between two items; or not the item's first cut
-    int last = j + 1;                                   // the share that the item ends in
-    while (at_share(units, last + 1, nb) < w.first + w.steps) ++last;
+    AttnUnit w;
+    int last;
+    if (!at_join_of(a, j, nb, &w, &last)) return;
     const int rows_s = (a.act_off[w.s + 1] - a.act_off[w.s]) * a.geom.S;
     const int my_row = w.tile * 128 + (tid >> 6) * 32 + fr, row = min(my_row, rows_s - 1), S = a.geom.S;
     const int pi = a.act_off[w.s] + row / S;
     const int64_t tok = (int64_t)(a.act.active ? a.act.active[pi] : pi) * S + row % S;
-    auto part = [&](int b) { return parts + (int64_t)(2 * b + (b == j)) * Cfg::PART + tid; };
+    auto part = [&](int b) { return parts + at_place(b, b == j) * Cfg::PART + tid; };
     float m = -INFINITY, l = 0.f;
     for (int b = j; b <= last; ++b) m = fmaxf(m, part(b)[16 * DT * 256]);
     at_f32x16 o[DT];
@@ -860,6 +883,54 @@ extern "C" int pserve_test_attn_cut(const pserve_plan_t* plan, int32_t C, int32_
 }
 // ... and in how many shares (0: a block an item)
 extern "C" int pserve_test_attn_shares(const pserve_plan_t* plan, int32_t C, int32_t heads) { return attention_shares(plan, C, heads); }
+// Both kernels' walk over the units of a call, on the host: n requests of rows[s] computed rows (a patch each) and keys[s] keys.  0 if every
+// unit is taken once and the join reads the parts that are written, each once; else the number of the check that fails.
+extern "C" int pserve_test_attn_walk(const int32_t* rows, const int32_t* keys, int32_t n, int32_t heads) {
+    PS_REQUIRE(rows && keys && n > 0 && heads > 0, "pserve_test_attn_walk");
+    return guarded("pserve_test_attn_walk", [&]() -> int {
+        std::vector<int32_t> act(n + 1, 0), cu(n + 1, 0);
+        std::vector<int64_t> off(n + 1, 0);
+        for (int s = 0; s < n; ++s) {
+            act[s + 1] = act[s] + rows[s];
+            cu[s + 1] = cu[s] + keys[s];
+            off[s + 1] = off[s] + cdiv(rows[s], 128) * heads * cdiv(keys[s], 32);
+        }
+        AttnArgs a{};
+        a.n = n; a.heads = heads; a.geom.S = 1; a.act_off = act.data(); a.cu_seqlens = cu.data(); a.unit_off = off.data();
+        const int64_t units = off[n];
+        const int shares = at_shares(units, AT_SHARES);
+        std::vector<int> taken(units, 0), part(2 * AT_SHARES, -1);      // part: the first unit of the item it is of
+        for (int block = 0; block < AT_SHARES; ++block) {
+            const int b = at_share_of(block, shares);
+            if (b < 0) continue;
+            int64_t u = at_share(units, b, shares);
+            const int64_t u1 = at_share(units, b + 1, shares);
+            while (u < u1) {
+                const AttnUnit w = at_unit(a, u);
+                const int steps = (int)std::min<int64_t>(w.steps - w.k, u1 - u);
+                for (int i = 0; i < steps; ++i) ++taken[u + i];
+                if (steps != w.steps) {
+                    if (part[at_place(b, w.k == 0)] >= 0) return 1;
+                    part[at_place(b, w.k == 0)] = (int)w.first;
+                }
+                u += steps;
+            }
+        }
+        for (int t : taken) if (t != 1) return 2;
+        for (int j = 0; j < AT_SHARES - 1; ++j) {
+            AttnUnit w;
+            int last;
+            if (!at_join_of(a, j, AT_SHARES, &w, &last)) continue;
+            for (int b = j; b <= last; ++b) {
+                int& p = part[at_place(b, b == j)];
+                if (p != w.first) return 3;
+                p = -1;
+            }
+        }
+        for (int p : part) if (p >= 0) return 4;
+        return 0;
+    });
+}
 
 int attention_mfma_bf16(const AttnArgs& a, hipStream_t st, bool* handled);     // attn_mfma.hip
 

@@ -282,6 +282,37 @@ def test_attention_in_shares(name):
         assert np.isfinite(err) and err < 1e-6, err
 
 
+# masks that leave 480, 24, 256, 512 units and none: fewer than the shares that the plan allows, as many
+FEW_UNITS = {"480": dict(res=[(64, 64), (48, 64)], heads=5, computed=[(1, 2, 3)]), "24": dict(res=[(64, 64), (8, 24)], heads=4, computed=[(1, 0, 1)]),
+             "256": dict(res=[(32, 64)] * 2, heads=4, computed=[(0, 3, 7)]), "512": dict(res=[(32, 64)] * 2, heads=4, computed=[(0, 0, 0), (1, 1, 1)]),
+             "none": dict(res=[(32, 64)] * 2, heads=4, computed=[])}
+
+
+@pytest.mark.parametrize("name", list(FEW_UNITS))
+def test_shares_of_few_units(name):
+    """Behind an unmasked call on the same store, whose partial results are left in its scratch."""
+    res, heads, computed = FEW_UNITS[name]["res"], FEW_UNITS[name]["heads"], FEW_UNITS[name]["computed"]
+    cfg = wl.custom_config(res, (8, 8), C=64 * heads, G=8, heads=heads, stages=("LSATTN",), dtype="f32", reuse_p=0.5, seed=107)
+    plan = ps.Plan(res, 8, 8)
+    assert ps.lib().pserve_test_attn_cut(plan._h, cfg.C, heads) == 1 and ps.lib().pserve_test_attn_shares(plan._h, cfg.C, heads) == 512
+    w = wl.make_workload(cfg)
+    for r in w.reuse:
+        r[:] = True
+    for i, y, x in computed:
+        w.reuse[i][y, x] = False
+    run = GpuRun(w)
+    run.forward()
+    run.load_cache()
+    got = run.forward_images(reuse=w.reuse)
+    ref, _ = ob.forward_batch(w.images, cfg.stages, w.params, G=cfg.G, heads=cfg.heads, eps=cfg.eps, reuse=w.reuse, cache=w.cache)
+    for i, (a, b) in enumerate(zip(got, ref)):
+        assert rel_err([a], [b]) < 1e-6
+        for j, y, x in computed:                         # (most of an image is copied from the cache)
+            if i == j:
+                s = np.s_[:, 8 * y:8 * y + 8, 8 * x:8 * x + 8]
+                assert rel_err([a[s]], [b[s]]) < 1e-6
+
+
 def test_share_that_starts_with_scores_of_minus_infinity():
     """64 keys of which every score is -infinity, at the head of a share (32 tiles each): they count for nothing."""
     cfg = wl.custom_config([(64, 64)], (8, 8), C=256, G=8, heads=4, stages=("LSATTN",), dtype="f32", reuse_p=0.5, seed=103)
