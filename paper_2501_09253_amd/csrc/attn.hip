@@ -685,7 +685,8 @@ attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv, float* __re
         issue(t + 3, t + 2, true);
         const bool flush = t % ATT_FLUSH == 0;
         if (flush || __any(mx > m + 8.f)) {             // (a row sum that is not a number stays one)
-            const float mn = t == 0 ? mx : mx > m + 8.f ? mx : m, corr = t == 0 ? 0.f : exp2_square(0.5f * (m - mn));
+            // (before the first score above -infinity there is nothing to rescale, and -infinity less itself is not a number)
+            const float mn = t == 0 ? mx : mx > m + 8.f ? mx : m, corr = m == -INFINITY ? 0.f : exp2_square(0.5f * (m - mn));
             m = mn;
             l *= corr;
 #pragma unroll

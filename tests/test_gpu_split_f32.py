@@ -313,21 +313,31 @@ def test_shares_of_few_units(name):
                 assert rel_err([a[s]], [b[s]]) < 1e-6
 
 
-def test_share_that_starts_with_scores_of_minus_infinity():
-    """64 keys of which every score is -infinity, at the head of a share (32 tiles each): they count for nothing."""
+# patches (of two key tiles each) from patch 16 on, tokens 1,024 ..; mixed: every second query of a wavefront
+@pytest.mark.parametrize("patches,mixed", [(1, False), (5, False), (1, True), (5, True)])
+def test_share_that_starts_with_scores_of_minus_infinity(patches, mixed):
+    """64 or 320 keys of which every score is -infinity, at the head of a share (32 tiles each): they count for nothing, whenever the
+    reference is looked at: every eight tiles, and where it moves for another query, whose scores are finite and rise from the
+    first tile to the second."""
     cfg = wl.custom_config([(64, 64)], (8, 8), C=256, G=8, heads=4, stages=("LSATTN",), dtype="f32", reuse_p=0.5, seed=103)
     assert ps.lib().pserve_test_attn_shares(ps.Plan(cfg.resolutions, 8, 8)._h, 256, 4) == 512
     w = wl.make_workload(cfg)
     p, d = w.params[0], 64
     p["ln_g"][:] = 0.02 * p["ln_g"]
     p["ln_b"][:] = 1
+    if mixed:                                            # first channel behind the LayerNorm: 1 or 1/800
+        im = w.images[0]
+        level = np.where(np.arange(64) % 2 == 0, 1.0, 1 / 800)
+        im[0] = im[1:].mean(0) + level * im[1:].std(0)
+        p["ln_g"][0], p["ln_b"][0] = 1, 0
     p["wq"][0, :] = 0
     p["wq"][:, ::d] = 0
-    p["wq"][0, ::d] = 800.0                              # queries (about 800, ..)
+    p["wq"][0, ::d] = 800.0                              # queries (about 800, ..), with `mixed` every second (about 1, ..)
     w.reuse[0][:] = False
-    w.reuse[0][2, 0] = True                              # patch 16: tokens 1,024 .. 1,087
-    w.cache["0.K"][0][:, 16:24, 0:8] = 0
-    w.cache["0.K"][0][::d, 16:24, 0:8] = -3e38
+    w.reuse[0][2, :patches] = True
+    w.cache["0.K"][0][:, 16:24, :8 * patches] = 0
+    w.cache["0.K"][0][::d, 16:24, :8 * patches] = -3e38
+    w.cache["0.K"][0][::d, 20:24, :8] = -2e38            # the second key tile
     p["wk"][:, ::d] *= 1e-3
     got, ref = _attn_run(cfg, w)
     assert np.isfinite(got[0]).all()
