@@ -333,6 +333,7 @@ struct pserve_cache_s {
     int32_t att_shares = 0;                   // fp32 attention in pieces: attention_shares
     int64_t* unit_off = nullptr;              // [n+1] ... units before slot s (with shares)
     int32_t max_tiles = 0;
+    int32_t owner_rows = 64;                  // GemmArgs::owner_rows of calls without a mask
     int32_t att_qt = 2;                       // query tile of the MFMA attention: 128 * att_qt rows
     bool tiles_unmasked = false;              // act_off / tile_off hold the tiling of a call without mask
     // The text key / value projection of the one cross-attention stage depends on ctx only: it runs on a stream of
@@ -641,6 +642,8 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
     const int head_dim = d.heads > 0 ? d.C / d.heads : 0;
     c->v_transposed = d.dtype == PSERVE_BF16 && head_dim == 64 && g_kernel_mode != 1;
     c->v_ld = (plan->T + 7) / 8 * 8;
+    for (int i = 1; i < plan->n; ++i)
+        while (plan->h_tab[PSERVE_TAB_CU_SEQLENS][i] % c->owner_rows != 0) c->owner_rows /= 2;
     c->nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(cdiv(768, plan->P), std::max(1, plan->S / 32)));
     PS_TRY(c->pool.alloc(&c->ping[0], TC));
     PS_TRY(c->pool.alloc(&c->ping[1], TC));
@@ -972,7 +975,7 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         GemmArgs g{};
         g.A = A; g.lda = lda; g.conv = 0; g.geom = gm; g.act = act; g.tokens_are_rows = 1; g.M = (int32_t)T;
         g.N = N; g.K = K; g.taps = 1; g.B = B; g.bias = bias; g.res = nullptr; g.ldr = 0;
-        g.epi = EPI_ROUTE; g.seg_cols = N;
+        g.epi = EPI_ROUTE; g.seg_cols = N; g.owner_rows = cache->owner_rows;
         for (auto& s : g.seg) { s.ptr = nullptr; s.ld = 0; s.transposed = 0; s.scale = 1.f; }
         return g;
     };

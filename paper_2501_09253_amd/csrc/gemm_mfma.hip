@@ -1223,12 +1223,31 @@ static double conv_time(const GemmArgs& a, int sel, int* splits) {
     return *splits > 1 ? shared : whole;
 }
 
-// gemm_mfma_kernel's tile for a problem: its columns (128 with `three`: three stages and one block a CU), 0: none.
-static int tile_pick(const GemmArgs& a, bool* three) {
+// 128 x 128 tiles with three stages, one block a CU, in place of t64 tiles of 128 x 64 that have CUs with two: where the chain of steps is long.
+// us, 128 x 64 / these, narrow tiles 264 / 342 / 408 / 504:
+//   linear layers  K = 2,048 22.1 / 21.6, 23.2 / 22.3, 23.5 / 22.9, 25.8 / 24.7;  K = 2,560 28.1 / 25.5, 30.0 / 25.9, 29.7 / 26.6, 32.0 / 28.8;
+//     K = 4,608 42.9 / 38.7, 45.3 / 39.2, 45.2 / 40.6, 49.2 / 44.2;  K = 6,144 58.5 / 49.4, 61.3 / 49.7, 61.7 / 51.0, 66.3 / 55.3.
+//     With a gate, or a transposed segment, K = 2,048 is a tie (300 tiles 23.1 / 23.6, 22.1 / 22.3); 2,176 26.2 / 24.4, 25.9 / 24.0.
+//   rows of several requests in a wavefront (64 x 64 values a look-up each, not 64 x 32): 342 tiles, patches of 20 x 20, K = 2,048 29.0 / 35.3,
+//     4,608 50.5 / 52.1 (in a block 51.6 / 57.1), 6,144 66.2 / 62.7.
+//   3x3 convolutions  256 channels 25.7 / 26.5, 26.6 / 27.0, 27.1 / 27.3 (400), 29.4 / 28.7;  384 34.2 / 34.9, 35.2 / 35.5, 36.4 / 35.9, 40.2 / 38.0;
+//     512 42.4 / 43.2, 43.9 / 43.8, 45.8 / 44.2, 50.5 / 47.1;  640 53.6 / 51.5, 56.9 / 52.2, 56.1 / 52.7, 62.3 / 57.2.
+//   With a mask t64 is only a bound: a linear layer, 360 narrow tiles, a third of the patches computed, K = 2,560 20.7 / 27.4; a 3x3
+//     convolution of 768 channels, 492, seven tenths 55.5 / 62.2 (all 77.0 / 72.5).
+static bool three_stages(const GemmArgs& a, int64_t t64) {
+    const int64_t steps = (int64_t)a.taps * (a.K / 64);
+    if (a.act.active || ((a.rowscale || a.rowbias) && a.owner_rows < 64)) return false;
+    if (a.conv) return steps >= 80 || (steps >= 32 && t64 >= 400);
+    return steps > 32 || (steps == 32 && !a.rowscale && !a.rowbias && !a.seg[0].transposed && !a.seg[1].transposed && !a.seg[2].transposed);
+}
+
+// gemm_mfma_kernel's tile for a problem: its columns (0: none) and the stages of its ring.  Two stages run two blocks a CU, as do three of the
+// 128 x 64 tile.
+static int tile_pick(const GemmArgs& a, int* stages) {
     // Two blocks of 128 rows a CU (one block's prologue and epilogue run beside the other's main loop).
     const int64_t m128 = cdiv(a.M, 128), classes = std::max(1, a.classes);
     const int64_t t160 = a.N % 160 == 0 ? m128 * (a.N / 160) * classes : 0, t128 = a.N % 128 == 0 ? m128 * (a.N / 128) * classes : 0;
-    *three = false;
+    *stages = 2;
     if (a.seg_cols % 32 != 0) return 0;             // a 32-column tile must not straddle output segments
     // N a multiple of 160: 128 x 160 tiles (wavefront tile 32 x 160).  Against a 256 x 160 tile
     // the rounds were the same: 34 -> 28 us (13,312 x 640 x 640), 68 -> 63 us (K = 2560), 80 -> 72 us
@@ -1239,27 +1258,34 @@ static int tile_pick(const GemmArgs& a, bool* three) {
     // But where 128 x 128 tiles still run in one round and these have CUs with two: 9,000 x 640, K = 640 20.3 / 128 x 128 18.4; 6,000 x
     // 1,280, K = 1,280 32.5 / 30.2; 1,536 x 3,840 29.2 / 26.6 (4,096 x 1,280, K = 5,120, 256 tiles: 67.8 / 74.2).
     const bool one_round = t128 > 256 && t128 <= 512;
-    if (t160 >= 208 && !(one_round && t160 > 256)) return 160;
+    if (t160 >= 208 && !(one_round && t160 > 256)) {
+        // One block a CU: the LDS that a second one would take holds two more stages.  us, two / four: text keys and values of 22 x 77
+        // tokens x 2,560, K = 2,048 38.7 / 32.6 (and 183.4 / 189.9 for the cross-attention around them); residual blocks of one
+        // convolution, 4,400 tokens x 960 112 / 98, 4,000 x 1280 146 / 135, 8,000 x 640 85.5 / 83.5.  (Three: the same to 1 us; the
+        // 128 x 64 tiles with six instead of three 29.6 / 30.7, 47.5 / 48.1.)
+        if (t160 <= 256) *stages = 4;
+        return 160;
+    }
     // 128 x 128 tiles from where they do not fit one block a CU.  us, these / 256 x 128 (one block a CU) / 128 x 64: 306 tiles K = 384
     // 14.6 / 19.4 / 16.5, 480 K = 768 22.6 / 26.2 / 28.3, 576 K = 1,536 48.9 / 56.9 / 50.5, 816 K = 512 31.2 / 36.4 / 37.3, 1,278 K = 768
-    // 49.6 / 60.5 / 60.3.  With fewer, 128 x 64 (204 tiles K = 128 8.5 / 11.9 / 8.9, 120 K = 1,536 22.3 / - / 15.4), unless the chain of
-    // steps is long and these have CUs with two blocks: then 128 x 128 with three stages, one block a CU (144 tiles K = 3,072 28.6 / 31.7).
+    // 49.6 / 60.5 / 60.3.  With fewer, 128 x 64 (204 tiles K = 128 8.5 / 11.9 / 8.9, 120 K = 1,536 22.3 / - / 15.4), unless three_stages.
     if (t128 > 256) return 128;
     const int64_t t64 = a.N % 64 == 0 ? m128 * (a.N / 64) * classes : 0;
-    if (t128 && t64 > 256 && (int64_t)a.taps * (a.K / 64) >= 32) {
-        *three = true;
-        return 128;
-    }
-    return t64 ? 64 : 0;
+    if (!t64) return 0;
+    *stages = 3;
+    return t128 && t64 > 256 && three_stages(a, t64) ? 128 : 64;
 }
-// How long that takes for a convolution, in us; fitted to 83 measured sizes (within a tenth).
-static double tile_time(const GemmArgs& a) {
-    bool three;
-    const int bn = tile_pick(a, &three);
+// How long that takes for a convolution without a mask, in us; fitted to 83 measured sizes (within a tenth).  (Calls with a mask take the same
+// kernel: the scratch of shared tiles is there or not.)
+static double tile_time(const GemmArgs& args) {
+    int stages;
+    GemmArgs a = args;
+    a.act.active = nullptr;
+    const int bn = tile_pick(a, &stages);
     if (!bn) return 1e30;
     const int64_t t = cdiv(a.M, 128) * (a.N / bn) * std::max(1, a.classes), full = (t - 1) / 512, rest = t - 512 * full;
     const double s = (double)a.taps * (a.K / 64), one = std::min<int64_t>(t, 256) / 256.0, over = std::max<int64_t>(rest - 256, 0) / 256.0;
-    if (three) return 8.0 + s * (0.47 + 0.09 * one);
+    if (bn == 128 && stages == 3) return 8.0 + s * (0.47 + 0.09 * one);
     if (bn == 64) {
         const double k = (double)cdiv(t, 256);
         return t <= 256 ? 7.0 + 0.385 * s : t <= 512 ? 9.0 + s * (0.46 + 0.12 * over) : 4.0 * k + s * (0.04 + 0.28 * k);
@@ -1313,8 +1339,8 @@ int gemm_stats_rows(const GemmArgs& a, int dtype, int mode) {
     if (c.few || a.act.active || a.N % a.stats_G != 0) return 0;
     // a wavefront's rows must lie in one patch, and its columns must hold whole groups
     static constexpr int cols[7] = {0, 160, 160, 128, 64, 32, 160};
-    bool three;
-    const int bn = c.sel ? 0 : tile_pick(a, &three);
+    int stages;
+    const int bn = c.sel ? 0 : tile_pick(a, &stages);
     if (!c.sel && !bn) return 0;
     const int rows = c.sel || bn != 160 ? 64 : 32, wc = c.sel ? cols[c.sel] : bn == 160 ? 160 : bn / 2;
     return a.geom.S % rows == 0 && wc % (a.N / a.stats_G) == 0 ? rows : 0;
@@ -1348,6 +1374,13 @@ extern "C" int pserve_test_conv_kernel(int32_t P, int32_t ph, int32_t pw, int32_
     const ConvChoice c = conv_choose(a);
     return (c.few ? 0 : c.sel ? 1 : 2) + 10 * gemm_stats_rows(a, PSERVE_BF16, 0);
 }
+// 10 x columns + stages of the last
+int gemm_tile_code(const GemmArgs& a);
+extern "C" int pserve_test_conv_tile(int32_t P, int32_t ph, int32_t pw, int32_t C) {
+    const GemmArgs a = conv_args(PatchGeom{P, ph * pw, ph, pw, pw + 2, (ph + 2) * (pw + 2)}, P * ph * pw, C, C);
+    const ConvChoice c = conv_choose(a);
+    return c.few || c.sel ? 0 : gemm_tile_code(a);
+}
 // The tile of gemm_few.hip that such a convolution takes instead (1 .. 5: 32 x 32, 32 x 64, 32 x 80, 64 x 64, 64 x 80), 0: none; linear:
 // that of a linear layer of P * ph * pw rows, K = C, N columns in segments of seg_cols (value-gate pairs: seg_cols = 0).
 extern "C" int pserve_test_few_tile(int32_t P, int32_t ph, int32_t pw, int32_t C, int32_t linear, int32_t N, int32_t seg_cols) {
@@ -1358,6 +1391,13 @@ extern "C" int pserve_test_few_tile(int32_t P, int32_t ph, int32_t pw, int32_t C
     a.seg_cols = seg_cols ? seg_cols : N;
     double us;
     return few_pick(a, a.epi == EPI_GEGLU ? 2 : 1, &us);
+}
+
+// For tests: tile_pick of a linear layer, 10 x columns + stages
+int gemm_tile_code(const GemmArgs& a) {
+    int stages;
+    const int bn = tile_pick(a, &stages);
+    return bn ? 10 * bn + stages : 0;
 }
 
 int gemm_wide_bf16(const GemmArgs& a, hipStream_t st, bool* handled);     // gemm_wide.hip
@@ -1390,8 +1430,8 @@ bool gemm_takes_halo(const GemmArgs& a, int dtype, int mode) {
     if (dtype != PSERVE_BF16 || mode != 0 || !gemm_mfma_eligible(a) || !a.conv || a.epi != EPI_ROUTE || !a.tokens_are_rows || a.act.active || a.B2 ||
         a.taps > 9 || a.rowbias || a.rowscale || a.act_gelu || a.seg[0].transposed || a.seg[0].scale != 1.f || a.seg_cols != a.N) return false;
     const ConvChoice c = conv_choose(a);
-    bool three;
-    return !c.sel && (c.few || tile_pick(a, &three));
+    int stages;
+    return !c.sel && (c.few || tile_pick(a, &stages));
 }
 
 int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
@@ -1428,16 +1468,10 @@ int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
     case 6: return launch_conv<256, 160, 4, 1, 416, 2, 2>(a, c.ct, c.splits, st);
     default: break;
     }
-    bool three;
-    switch (tile_pick(a, &three)) {
-    case 160:
-        // One block a CU: the LDS that a second one would take holds two more stages.  us, two / four: text keys and values of 22 x 77
-        // tokens x 2,560, K = 2,048 38.7 / 32.6 (and 183.4 / 189.9 for the cross-attention around them); residual blocks of one
-        // convolution, 4,400 tokens x 960 112 / 98, 4,000 x 1280 146 / 135, 8,000 x 640 85.5 / 83.5.  (Three: the same to 1 us; the
-        // 128 x 64 tiles with six instead of three 29.6 / 30.7, 47.5 / 48.1.)
-        if (cdiv(a.M, 128) * (a.N / 160) * std::max(1, a.classes) <= 256) return launch<128, 160, false, 4, 1, 4, false>(a, st);
-        return launch<128, 160, false, 4, 1, 2, false>(a, st);
-    case 128: return three ? launch<128, 128, false, 2, 2, 3, true>(a, st) : launch<128, 128, false, 2, 2, 2, false>(a, st);
+    int stages;
+    switch (tile_pick(a, &stages)) {
+    case 160: return stages == 4 ? launch<128, 160, false, 4, 1, 4, false>(a, st) : launch<128, 160, false, 4, 1, 2, false>(a, st);
+    case 128: return stages == 3 ? launch<128, 128, false, 2, 2, 3, true>(a, st) : launch<128, 128, false, 2, 2, 2, false>(a, st);
     case 64: return launch<128, 64, false, 2, 2, 3, false>(a, st);
     default: break;
     }

@@ -201,6 +201,7 @@ struct GemmArgs : GemmCore {
     const int32_t* halo_src;
     // fp32: A is in bf16 pieces (gemm_takes_pieces) / the output is written in pieces
     int32_t a_pieces, out_pieces;
+    int32_t owner_rows;        // with rowbias / rowscale: the rows of every request start at a multiple of this (1, 2, .. 64; 0: not known)
 };
 // Rows of A a problem can address: where rows are tokens, any token of the batch, however few patches its list has (the two
 // lists of a joint batch lie interleaved in one token matrix).

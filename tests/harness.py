@@ -96,6 +96,22 @@ def joint_layers_in_one_launch(cfg) -> bool:
                for N, K, seg, flags in ((3 * C, C, C, transposed), (C, C, C, res + gate), (F, C, F, gelu), (C, F, C, res + gate)))
 
 
+def linear_kernel(cfg, layer) -> int:
+    """The kernel a bf16 linear layer of a block takes (pserve_test_linear_kernel)."""
+    C, S, F, T = cfg.C, cfg.patch[0] * cfg.patch[1], cfg.ffn_mult * cfg.C, sum(h * w for h, w in cfg.resolutions)
+    transposed, res, gate, gelu, geglu, plain_rows, mask = 1, 2, 4, 8, 16, 32, 64
+    rows, N, K, seg, flags = {"qkv": (T, 3 * C, C, C, transposed), "out": (T, C, C, C, res), "geglu": (T, 2 * F, C, 2 * F, geglu),
+                              "ffn_out": (T, C, F, C, res), "mlp_in": (T, F, C, F, gelu), "mlp_out": (T, C, F, C, res + gate),
+                              "text_kv": (len(cfg.resolutions) * cfg.ctx_len, 2 * C, cfg.ctx_dim, C, transposed + plain_rows)}[layer]
+    if cfg.reuse_p and layer != "text_kv":
+        flags += mask
+    starts = np.cumsum([0] + sorted(h * w for h, w in cfg.resolutions))[1:-1]
+    align = 64
+    while any(s % align for s in starts):
+        align //= 2
+    return ps.lib().pserve_test_linear_kernel(T // S, S, rows, N, K, seg, flags, align)
+
+
 def rel_err(got, ref) -> float:
     """max |got - ref| / max |ref| over a list of arrays."""
     num = max(float(np.abs(np.asarray(g, dtype=np.float64) - r).max()) for g, r in zip(got, ref))

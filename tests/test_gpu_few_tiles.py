@@ -16,7 +16,7 @@ from oracle import resample as ores
 torch = pytest.importorskip("torch")
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(), reason="no GPU")]
 
-from harness import GpuRun, rel_err, tolerance      # noqa: E402
+from harness import GpuRun, linear_kernel, rel_err, tolerance      # noqa: E402
 from test_gpu_wide import _check            # noqa: E402
 
 T32, T32x64, T32x80, T64, T64x80 = 1, 2, 3, 4, 5
@@ -93,20 +93,25 @@ def test_few_tiles_between_levels(res, patch, C):
 # 128 x 128 tiles, two blocks a CU, where they are more than 256 and run in one round (and one block a CU where the chain of steps is
 # long); value-gate pairs on 128 x 128 tiles with fewer than that.
 TILES_128 = {
-    "qkv": dict(res=[(24, 24)] * 3 + [(8, 16)], patch=(8, 8), C=768, stages=("LSATTN",)),
-    "qkv_masked": dict(res=[(32, 32), (28, 28)], patch=(4, 4), C=768, stages=("SATTN",), reuse_p=0.3),
-    "residual": dict(res=[(96, 96), (64, 64)], patch=(32, 32), C=384, stages=("XATTN",), ctx_len=20, ctx_dim=64),
-    "gate": dict(res=[(24, 24)] * 4, patch=(12, 12), C=768, stages=("AMLP",), temb_dim=64),
-    "geglu": dict(res=[(28, 28), (12, 12)], patch=(4, 4), C=640, stages=("LFFN",)),
-    "long_chain": dict(res=[(64, 66)], patch=(8, 6), C=512, stages=("LFFN",)),
+    "qkv": dict(res=[(24, 24)] * 3 + [(8, 16)], patch=(8, 8), C=768, stages=("LSATTN",), kernels=dict(qkv=1282)),
+    "qkv_masked": dict(res=[(32, 32), (28, 28)], patch=(4, 4), C=768, stages=("SATTN",), reuse_p=0.3, kernels=dict(qkv=1282)),
+    "residual": dict(res=[(96, 96), (64, 64)], patch=(32, 32), C=384, stages=("XATTN",), ctx_len=20, ctx_dim=64, kernels=dict(out=1282)),
+    "gate": dict(res=[(24, 24)] * 4, patch=(12, 12), C=768, stages=("AMLP",), temb_dim=64, kernels=dict(mlp_in=1282)),
+    "geglu": dict(res=[(28, 28), (12, 12)], patch=(4, 4), C=640, stages=("LFFN",), kernels=dict(geglu=1282)),
+    "long_chain": dict(res=[(64, 66)], patch=(8, 6), C=512, stages=("LFFN",), kernels=dict(ffn_out=1283)),
+    # with a gate: requests that start at multiples of 64 rows and elsewhere; a mask
+    "long_gate": dict(res=[(24, 24)] * 5, patch=(12, 12), C=768, stages=("AMLP",), temb_dim=64, kernels=dict(mlp_out=1283)),
+    "long_gate_mixed": dict(res=[(20, 20)] * 7, patch=(10, 10), C=768, stages=("AMLP",), temb_dim=64, kernels=dict(mlp_out=643)),
+    "long_masked": dict(res=[(64, 66)], patch=(8, 6), C=512, stages=("LSATTN", "LFFN"), reuse_p=0.6, kernels=dict(ffn_out=643)),
 }
 
 
 @pytest.mark.parametrize("name", list(TILES_128))
 def test_128_row_tiles(name):
     c = dict(TILES_128[name])
-    C = c.pop("C")
+    C, kernels = c.pop("C"), c.pop("kernels")
     cfg = wl.custom_config(c.pop("res"), c.pop("patch"), C=C, G=32, heads=C // 64, stages=c.pop("stages"), dtype="bf16", seed=63, **c)
+    assert {layer: linear_kernel(cfg, layer) for layer in kernels} == kernels       # 10 x columns + stages
     _check(wl.make_workload(cfg))
 
 

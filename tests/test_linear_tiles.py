@@ -1,4 +1,4 @@
-"""CPU: which linear layers take the 256- and 320-row tiles (host side of the dispatch, no kernel is launched)."""
+"""CPU: which linear layers take which tiles (host side of the dispatch, no kernel is launched)."""
 import pytest
 
 import paper_2501_09253_amd as ps
@@ -17,3 +17,19 @@ def test_both_streams_stay_below_the_offset_limit(C, n):
     assert 16 * (n + 1) * S * F < 1 << 30                       # the image rows alone would still fit
     assert tile(n, F) in (256, 320) and tile(n + 1, F) == 0
     assert tile(n + 1, C) in (256, 320)                         # narrower operands do not reach the limit
+
+
+LAST_TRANSPOSED, MASK = 1, 64
+WIDE_3, NARROW = 1283, 643                               # 10 x columns + stages
+
+
+# 128 x 128 tiles with three stages, one block a CU, or 128 x 64 ones, two: 342 narrow tiles, K steps, what the end of a tile looks up for
+# its rows and where their requests start, a mask
+@pytest.mark.parametrize("steps,flags,owner_rows,kernel", [(31, RES, 64, NARROW), (32, RES, 64, WIDE_3), (32, LAST_TRANSPOSED, 64, NARROW),
+                                                           (33, LAST_TRANSPOSED, 64, WIDE_3), (32, RES + GATE, 64, NARROW), (33, RES + GATE, 64, WIDE_3),
+                                                           (72, RES + GATE, 32, NARROW), (72, RES + GATE, 0, NARROW), (72, RES, 1, WIDE_3),
+                                                           (72, RES + MASK, 64, NARROW), (40, LAST_TRANSPOSED + MASK, 64, NARROW)])
+def test_three_stages_or_narrow_tiles(steps, flags, owner_rows, kernel):
+    S, rows, N = 16, 2400, 1152
+    seg = N // 2 if flags & LAST_TRANSPOSED else N
+    assert ps.lib().pserve_test_linear_kernel(rows // S, S, rows, N, 64 * steps, seg, flags, owner_rows) == kernel
