@@ -558,7 +558,7 @@ attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv, float* __re
     const int steps = SHARED ? (int)min((int64_t)(w.steps - w.k), u1 - u) : w.steps;    // tiles of this share, and the keys from its first on
     const int nk = w.nk - w.k * 32;
     const bool whole = !SHARED || steps == w.steps;
-    u += steps;
+    if constexpr (SHARED) u += steps;
     const at_u32x4* src = tiles_kv + ((at_tile0(a.cu_seqlens, s) + w.k) * a.heads + h) * TILE_V;
     const int64_t src_step = (int64_t)a.heads * TILE_V;
     // Keys of tile tk and values of tile tv into stages of their own (past the end: the last tile again, never read).  Buffer
@@ -773,6 +773,7 @@ attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv, float* __re
         continue;
     }
     at_store<D>(a, ot, 1.f / l, my_row < rows_s, tok, h, fh);
+    if constexpr (!SHARED) return;
     }
 }
 
