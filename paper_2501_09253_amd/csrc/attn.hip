@@ -381,6 +381,7 @@ extern "C" int pserve_test_attn_transposed(const pserve_plan_t* plan, const void
 // 189 + 13 us, 512 equal shares (145 -> 166 TFLOP/s of fp32).  Bound by the issue of MFMAs (1,536 of 2,770 clocks a tile) and vector
 // instructions, with every CU busy by the clock (2.15 GHz with 160 CUs busy, 1.8 with all).
 constexpr int ASP_NS = 3;
+constexpr float AT_LOWEST = -3.402823466e38f;       // the softmax reference in front of the first key
 constexpr int AT_SHARES = 512;       // shares of a call (a multiple of 8)
 template <int D> struct AttnSplitCfg {
     static constexpr int KV = 3 * 32 * D / 8, TILE_V = 2 * KV;       // 16-byte slots of the keys, of a tile
@@ -643,7 +644,8 @@ attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv, float* __re
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
         for (int e = 0; e < 16; ++e) o[dt][e] = ol[dt][e] = ot[dt][e] = 0.f;
-    float m = -INFINITY, l = 0.f, p[16], mx;
+    // (the reference is never -infinity, so that scores of -infinity have probabilities of zero until there is another)
+    float m = AT_LOWEST, l = 0.f, p[16], mx;
     // the scores of tile t are summed (p, their maximum in mx): those behind the last key are masked, the lane halves meet
     auto finish = [&](int t) {
         if ((t + 1) * 32 > nk) {
@@ -685,8 +687,7 @@ attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv, float* __re
         issue(t + 3, t + 2, true);
         const bool flush = t % ATT_FLUSH == 0;
         if (flush || __any(mx > m + 8.f)) {             // (a row sum that is not a number stays one)
-            // (before the first score above -infinity there is nothing to rescale, and -infinity less itself is not a number)
-            const float mn = t == 0 ? mx : mx > m + 8.f ? mx : m, corr = m == -INFINITY ? 0.f : exp2_square(0.5f * (m - mn));
+            const float mn = mx > m + 8.f ? mx : m, corr = exp2_square(0.5f * (m - mn));
             m = mn;
             l *= corr;
 #pragma unroll
@@ -697,7 +698,7 @@ attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv, float* __re
                     o[dt][e] = ol[dt][e] = 0.f;
                 }
         }
-        const float hm = m == -INFINITY ? 0.f : -0.5f * m;      // (no score above -infinity yet: probabilities of zero)
+        const float hm = -0.5f * m;
         // The next tile's scores, and behind each MFMA up to five of this tile's vector instructions (about four are free, and none
         // where there is no MFMA: as two phases a tile took 3,360 clocks of which 1,536 are MFMAs) and a fragment read for six MFMAs
         // later: the probabilities in pairs, in four (D = 32: two) steps each; those that the first output products do not need
@@ -793,7 +794,7 @@ attn_join_kernel(AttnArgs a, const float* __restrict__ parts, int nb) {
     const int pi = a.act_off[w.s] + row / S;
     const int64_t tok = (int64_t)(a.act.active ? a.act.active[pi] : pi) * S + row % S;
     auto part = [&](int b) { return parts + at_place(b, b == j) * Cfg::PART + tid; };
-    float m = -INFINITY, l = 0.f;
+    float m = AT_LOWEST, l = 0.f;
     for (int b = j; b <= last; ++b) m = fmaxf(m, part(b)[16 * DT * 256]);
     at_f32x16 o[DT];
 #pragma unroll
@@ -802,7 +803,7 @@ attn_join_kernel(AttnArgs a, const float* __restrict__ parts, int nb) {
         for (int e = 0; e < 16; ++e) o[dt][e] = 0.f;
     for (int b = j; b <= last; ++b) {
         const float* src = part(b);
-        const float mb = src[16 * DT * 256], f = mb == -INFINITY ? 0.f : exp2_square(0.5f * (mb - m));
+        const float mb = src[16 * DT * 256], f = exp2_square(0.5f * (mb - m));
         l = fmaf(src[(16 * DT + 1) * 256], f, l);
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
