@@ -206,7 +206,8 @@ void pserve_block_free(pserve_block_t* block);
  * output of the previous step, per patch) plus all scratch the forward pass needs (for bf16
  * residual convolutions of few patches also up to 42 MB of partial sums: the forward pass then
  * shares a tile's input channels between blocks; for fp32 stages large enough for the bf16 matrix
- * cores, 6 bytes a value of each layer's input, and keys and values once more at 6 bytes each).
+ * cores, 6 bytes a value of each layer's input, keys and values once more at 6 bytes each, and where
+ * the attention's work is shared out between blocks up to 36 MB of partial results).
  * with_slots = 0 allocates scratch only (then reuse_mask must be NULL). */
 int  pserve_cache_create(const pserve_plan_t* plan, const pserve_block_t* block, int with_slots,
                          pserve_cache_t** out);

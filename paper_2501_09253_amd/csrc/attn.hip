@@ -378,11 +378,15 @@ extern "C" int pserve_test_attn_transposed(const pserve_plan_t* plan, const void
 // most of its ~270 vector instructions), then the output products; keys and values have rings of three stages of their own,
 // filled two steps ahead.  The softmax reference moves only when a score passes it by 8 (a factor of 256 costs fp32 nothing).
 // Requests of 4,096 and 3,072 tokens, 5 heads of 64 (280 items of 128 and 96 tiles): 360 (fp32 kernel) -> 234 us, a block an item ->
-// 189 + 13 us, 512 equal shares (145 -> 166 TFLOP/s of fp32).  Bound by the issue of MFMAs (1,536 of 2,770 clocks a tile) and vector
+// 189 + 13 us, 512 shares (145 -> 166 TFLOP/s of fp32).  Bound by the issue of MFMAs (1,536 of 2,770 clocks a tile) and vector
 // instructions, with every CU busy by the clock (2.15 GHz with 160 CUs busy, 1.8 with all).
 constexpr int ASP_NS = 3;
 constexpr float AT_LOWEST = -3.402823466e38f;       // the softmax reference in front of the first key
 constexpr int AT_SHARES = 512;       // shares of a call (a multiple of 8)
+// Units of a share at least.  us of an LSATTN layer, no such bound / 8 / 12 / 16: 4,096 tokens, 4 heads of 64, a fiftieth computed 216 / 107 / 106 / 108, a
+// twentieth 160 / 109 / 109 / 110; all of 1,024 + 12 x 256 88 / 79 / 75 / 82, 1,600 + 20 x 256 117 / 114 / 116 / 121.
+constexpr int AT_SHORTEST = 12;
+static_assert(AT_SHORTEST > AT_START, "a share without keys");
 template <int D> struct AttnSplitCfg {
     static constexpr int KV = 3 * 32 * D / 8, TILE_V = 2 * KV;       // 16-byte slots of the keys, of a tile
     static constexpr int LPT = TILE_V / 256;                         // direct loads of a wavefront and tile
@@ -473,9 +477,11 @@ __device__ __forceinline__ void at_store(const AttnArgs& a, const at_f32x16 (&ot
     }
 }
 
-// The work of a call is a row of units (32 keys of an item): slot by slot, head by head, 128 queries by 128 queries, cut into
-// equal shares, one a block.  Items that a cut goes through leave partial results, which attn_join_kernel puts together.
-struct AttnUnit { int s, h, tile, nq, nk, steps, k; int64_t first; };    // slot, head, query tile of nq, keys, unit k of steps; the item's first unit
+// The work of a call is a row of units: slot by slot, head by head, 128 queries by 128 queries, an item of AT_START units for its start and end
+// and one for each 32 keys.  It is cut into equal shares, one a block; a cut that falls into an item's start lies in front of its first key.
+// Items that a cut goes through leave partial results, which attn_join_kernel puts together.
+// slot, head, query tile of nq, keys, tile of keys k of steps that a share with this unit starts at; the item's first unit
+struct AttnUnit { int s, h, tile, nq, nk, steps, k; int64_t first; };
 __host__ __device__ __forceinline__ AttnUnit at_unit(const AttnArgs& a, int64_t u) {
     AttnUnit r;
     int lo = 0, hi = a.n;                               // largest s with unit_off[s] <= u
@@ -490,16 +496,25 @@ __host__ __device__ __forceinline__ AttnUnit at_unit(const AttnArgs& a, int64_t 
     r.nk = a.seq_len ? a.seq_len[r.s] : a.cu_seqlens[r.s + 1] - a.cu_seqlens[r.s];
     r.steps = (r.nk + 31) / 32;
     r.nq = ((a.act_off[r.s + 1] - a.act_off[r.s]) * a.geom.S + 127) / 128;
-    const int64_t in = u - a.unit_off[r.s], item = in / r.steps;
-    r.k = (int)(in - item * r.steps);
+    const int64_t in = u - a.unit_off[r.s], item = in / (r.steps + AT_START);
+    const int at = (int)(in - item * (r.steps + AT_START));
+    r.k = at < AT_START ? 0 : at - AT_START;
     r.h = (int)(item / r.nq);
     r.tile = (int)(item - (int64_t)r.h * r.nq);
-    r.first = u - r.k;
+    r.first = u - at;
     return r;
 }
-// Shares of a call for which the plan allows `blocks`: a mask may leave fewer units, and the join reads a part of every share that an
-// item lies in, so none is empty.
-__host__ __device__ __forceinline__ int at_shares(int64_t units, int blocks) { return units < blocks ? (int)units : blocks; }
+// tiles of keys of an item that lie in front of unit u
+__host__ __device__ __forceinline__ int at_tiles(const AttnUnit& w, int64_t u) {
+    const int64_t t = u - w.first - AT_START;
+    return t >= w.steps ? w.steps : t < 0 ? 0 : (int)t;
+}
+// Shares of a call for which the plan allows `blocks`: a mask may leave few units.  None is shorter than AT_SHORTEST, so none has no keys: the join
+// reads a part of every share that an item lies in.
+__host__ __device__ __forceinline__ int at_shares(int64_t units, int blocks) {
+    const int64_t most = units / AT_SHORTEST;
+    return units == 0 ? 0 : most < 1 ? 1 : most < blocks ? (int)most : blocks;
+}
 __host__ __device__ __forceinline__ int64_t at_share(int64_t units, int b, int shares) { return units * b / shares; }
 // share of a block, -1: none.  An XCD's blocks take neighbouring shares: they stream the keys of the same few heads through its L2.
 __host__ __device__ __forceinline__ int at_share_of(int block, int shares) {
@@ -514,9 +529,9 @@ __host__ __device__ __forceinline__ bool at_join_of(const AttnArgs& a, int j, in
     const int shares = at_shares(units, blocks);
     if (j + 1 >= shares) return false;
     *w = at_unit(a, at_share(units, j + 1, shares));
-    if (w->k == 0 || at_share(units, j, shares) > w->first) return false;      // between two items; or not the item's first cut
+    if (w->k == 0 || at_tiles(*w, at_share(units, j, shares)) > 0) return false;       // between two items; or not the item's first cut
     *last = j + 1;
-    while (at_share(units, *last + 1, shares) < w->first + w->steps) ++*last;
+    while (at_tiles(*w, at_share(units, *last + 1, shares)) < w->steps) ++*last;
     return true;
 }
 
@@ -545,21 +560,23 @@ attn_split_kernel(AttnArgs a, const at_u32x4* __restrict__ tiles_kv, float* __re
 #pragma unroll 1
     while (u < u1) {
     AttnUnit w{};
+    int steps;                                          // tiles of this share, and below the keys from its first on
     if constexpr (SHARED) {
         w = at_unit(a, u);
+        steps = at_tiles(w, u1) - w.k;
+        u = w.first + AT_START + w.steps;
+        if (steps == 0) return;                         // (the share ends in this item's start)
     } else {
         const int seq = blockIdx.x >> 3, grp = seq / a.group, it = (grp * 8 + (blockIdx.x & 7)) * a.group + (seq - grp * a.group);
         if (!attn_item_at(a, it / a.qt, w.s, w.h, w.tile)) return;
         w.tile = w.tile * a.qt + it % a.qt;
         w.nk = a.seq_len ? a.seq_len[w.s] : a.cu_seqlens[w.s + 1] - a.cu_seqlens[w.s];
-        w.steps = (w.nk + 31) / 32;
+        steps = w.steps = (w.nk + 31) / 32;
     }
     const int s = w.s, h = w.h, r0 = w.tile * 128, rows_s = (a.act_off[s + 1] - a.act_off[s]) * S;
     if (!SHARED && r0 >= rows_s) return;
-    const int steps = SHARED ? (int)min((int64_t)(w.steps - w.k), u1 - u) : w.steps;    // tiles of this share, and the keys from its first on
     const int nk = w.nk - w.k * 32;
     const bool whole = !SHARED || steps == w.steps;
-    if constexpr (SHARED) u += steps;
     const at_u32x4* src = tiles_kv + ((at_tile0(a.cu_seqlens, s) + w.k) * a.heads + h) * TILE_V;
     const int64_t src_step = (int64_t)a.heads * TILE_V;
     // Keys of tile tk and values of tile tv into stages of their own (past the end: the last tile again, never read).  Buffer
@@ -850,34 +867,38 @@ size_t attention_cut_bytes(const pserve_plan_t* plan, int32_t C, int32_t heads, 
     return (size_t)(plan->T / 32 + plan->n) * C * 32 * 12 + 2 * attention_shares(plan, C, heads) * part;
 }
 
-// Blocks that share out the units of such a call equally, 0: a block an item.  In tiles of one CU (1.25 us with 64 channels a head,
-// 0.76 with 32; two blocks a CU give 7 % more than one, an item's start and end is an eighth of 70 tiles): items 256 at a time, the
-// longest first; shares their mean, cutting and joining.  us of an LSATTN layer, items / shares: 64 channels: 4,096 tokens, 4 heads 193 / 143,
-// 5 heads 207 / 179, 2 x 4,096 366 / 326, 4,096 + 3,072 312 / 273, 4 x 4,096 632 / 611, 8 x 4,096 1,121 / 1,159, 16,384 1,916 / 1,768; 32 channels: 4,096,
-// 5 heads 139 / 104, 9,216 433 / 363, 2 x 2,304 97 / 89, 5 x 1,024 67 / 72, 3 x 4,096 251 / 258, 6 x 4,096 472 / 480.
+// Blocks that share out the units of such a call equally, 0: a block an item.  Both in tiles of one CU (1.25 us with 64 channels a head, 0.76 with
+// 32): items go, the longest first, to the CU with the least work, the last one of an odd number alone, which costs a fifth of it more; shares
+// take their mean, and cutting and joining.  185 batches (1,024 to 16,384 tokens, up to 100 small requests beside a large one): the slower
+// form by 2.3 % at most.  us of an LSATTN layer, items / shares: 64 channels, 5 heads: 4,096 tokens 220 / 181, 2 x 4,096 373 / 331, 4,096 + 3,072
+// 316 / 277, 4 x 4,096 653 / 628, 8 x 4,096 1,161 / 1,192, 5 x 2,304 309 / 332, 16,384 1,980 / 1,813, 1,024 + 24 x 64 90 / 84, 4,096 + 60 x 64 274 / 237;
+// 32 channels, 5 heads: 4,096 140 / 107, 9,216 443 / 375, 3 x 4,096 256 / 260, 5 x 1,024 70 / 75.
 int attention_shares(const pserve_plan_t* plan, int32_t C, int32_t heads) {
-    struct Len { int64_t steps, items; };
+    struct Len { int64_t cost, items; };
     std::vector<Len> len;
     int64_t items = 0, units = 0;
     const int32_t *ro = plan->h_tab[PSERVE_TAB_REQUEST_OFFSET], *sl = plan->h_tab[PSERVE_TAB_SEQ_LEN];
     for (int s = 0; s < plan->n; ++s) {
         const int64_t rows = (int64_t)(ro[s + 1] - ro[s]) * plan->S;
-        len.push_back({cdiv(sl[s], 32), cdiv(rows, 128) * heads});
+        len.push_back({AT_START + cdiv(sl[s], 32), cdiv(rows, 128) * heads});
         items += len.back().items;
-        units += len.back().items * len.back().steps;
+        units += len.back().items * len.back().cost;
     }
-    std::sort(len.begin(), len.end(), [](const Len& x, const Len& y) { return x.steps > y.steps; });
-    auto nth = [&](int64_t k) -> double {               // steps of item k, longest first
-        for (const Len& l : len) {
-            if (k < l.items) return (double)l.steps;
-            k -= l.items;
+    const int shares = (int)std::min<int64_t>(AT_SHARES, units / AT_SHORTEST / 8 * 8);
+    if (shares == 0 || items > 32 * 256) return 0;      // (so many items come out even)
+    std::sort(len.begin(), len.end(), [](const Len& x, const Len& y) { return x.cost > y.cost; });
+    struct Cu { int64_t load, last; bool odd; };
+    auto more = [](const Cu& x, const Cu& y) { return x.load > y.load; };
+    std::vector<Cu> cu(256, Cu{0, 0, false});           // a heap, the least load in front
+    for (const Len& l : len)
+        for (int64_t i = 0; i < l.items; ++i) {
+            std::pop_heap(cu.begin(), cu.end(), more);
+            cu.back() = Cu{cu.back().load + l.cost, l.cost, !cu.back().odd};
+            std::push_heap(cu.begin(), cu.end(), more);
         }
-        return 0.0;
-    };
-    const int64_t full = items / 512, rest = items % 512;
-    const double mean = items ? (double)units / items : 0.0, first = full ? mean : nth(0), second = full ? mean : nth(256);
-    const double by_item = full * 2 * mean + (rest == 0 ? 0.0 : rest <= 256 ? 1.12 * first : first + second);
-    return 1.03 * units / 256 + (C / heads == 32 ? 26 : 28) < by_item ? AT_SHARES : 0;
+    double by_item = 0.0;
+    for (const Cu& c : cu) by_item = std::max(by_item, c.load + (c.odd ? 0.2 * c.last : 0.0));
+    return 1.04 * units / 256 + 27 < by_item ? shares : 0;
 }
 
 // For tests (host only, no part of the ABI): whether the fp32 self-attention of a plan goes to the bf16 matrix cores
@@ -896,7 +917,7 @@ extern "C" int pserve_test_attn_walk(const int32_t* rows, const int32_t* keys, i
         for (int s = 0; s < n; ++s) {
             act[s + 1] = act[s] + rows[s];
             cu[s + 1] = cu[s] + keys[s];
-            off[s + 1] = off[s] + cdiv(rows[s], 128) * heads * cdiv(keys[s], 32);
+            off[s + 1] = off[s] + cdiv(rows[s], 128) * heads * (AT_START + cdiv(keys[s], 32));
         }
         AttnArgs a{};
         a.n = n; a.heads = heads; a.geom.S = 1; a.act_off = act.data(); a.cu_seqlens = cu.data(); a.unit_off = off.data();
@@ -910,15 +931,20 @@ extern "C" int pserve_test_attn_walk(const int32_t* rows, const int32_t* keys, i
             const int64_t u1 = at_share(units, b + 1, shares);
             while (u < u1) {
                 const AttnUnit w = at_unit(a, u);
-                const int steps = (int)std::min<int64_t>(w.steps - w.k, u1 - u);
-                for (int i = 0; i < steps; ++i) ++taken[u + i];
-                if (steps != w.steps) {
+                const int steps = at_tiles(w, u1) - w.k;
+                if (steps < 0) return 5;
+                for (int i = 0; i < steps; ++i) ++taken[w.first + AT_START + w.k + i];
+                if (steps != 0 && steps != w.steps) {
                     if (part[at_place(b, w.k == 0)] >= 0) return 1;
                     part[at_place(b, w.k == 0)] = (int)w.first;
                 }
-                u += steps;
+                u = w.first + AT_START + w.steps;
+                if (steps == 0) break;
             }
         }
+        for (int s = 0; s < n; ++s)                     // (nobody takes the units of an item's start)
+            for (int64_t u = off[s]; u < off[s + 1]; u += cdiv(keys[s], 32) + AT_START)
+                for (int i = 0; i < AT_START; ++i) ++taken[u + i];
         for (int t : taken) if (t != 1) return 2;
         for (int j = 0; j < AT_SHARES - 1; ++j) {
             AttnUnit w;

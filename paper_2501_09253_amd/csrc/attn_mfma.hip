@@ -1003,7 +1003,7 @@ __global__ void attn_tiles_kernel(const int32_t* __restrict__ request_offset, co
             til = (cnt * S + ATT_BQ - 1) / ATT_BQ;
             if (unit_off) {
                 const int nk = seq_len ? seq_len[s] : cu_seqlens[s + 1] - cu_seqlens[s];
-                unit = (int64_t)((cnt * S + 127) / 128) * heads * ((nk + 31) / 32);
+                unit = (int64_t)((cnt * S + 127) / 128) * heads * (AT_START + (nk + 31) / 32);
             }
         }
         s_cnt[tid] = cnt;

@@ -244,6 +244,9 @@ int pack_conv_up2(const void* w, void* dst, int32_t Cout, int32_t Cin, int dtype
 constexpr int GEGLU_GROUP = 64;
 
 // ---- attention (attn.hip) -------------------------------------------------------------------------
+constexpr int AT_START = 4;          // fp32 attention in pieces: an item's start and end, in tiles of 32 keys (us, shares of equal numbers of tiles, 0, and of
+                                     // these units, 2 / 4 / 6 / 9: 4,096 + 8 x 64 tokens, 5 heads of 64 281 / 202 / 188 / 190 / 190 us, 2,304 + 60 x 64
+                                     // 177 / 137 / 134 / 139 / 143)
 struct AttnArgs {
     const void* Q;             // [T][C], already multiplied by log2(e)/sqrt(d)
     const void* K;             // self: [T][C]; cross: [n*L][C]
@@ -263,7 +266,7 @@ struct AttnArgs {
     // query tiling of the MFMA kernel (attention_tiles fills the two prefix tables)
     const int32_t* act_off;    // [n+1] computed patches before slot s (== RequestOffset without a mask)
     const int32_t* tile_off;   // [n+1] query tiles before slot s
-    const int64_t* unit_off;   // [n+1] fp32 attention in pieces: units (32 keys of 128 queries of a head) before slot s
+    const int64_t* unit_off;   // [n+1] fp32 attention in pieces: units (at_unit) before slot s
     int32_t n;                 // request slots
     int32_t max_tiles;         // host upper bound of tile_off[n]
     int32_t qt;                // 1 or 2: the tables were built for query tiles of 128 * qt rows

@@ -1,5 +1,5 @@
-"""CPU: how the fp32 self-attention's units (32 keys of 128 queries of a head) are cut into shares, the parts of results that the shares
-leave and the join reads, replayed on the host for the numbers of computed rows that masks leave of a plan."""
+"""CPU: how the fp32 self-attention's units (32 keys of 128 queries of a head, and an item's start) are cut into shares, the parts of results
+that the shares leave and the join reads, replayed on the host for the numbers of computed rows that masks leave of a plan."""
 import ctypes as C
 import random
 
@@ -13,8 +13,8 @@ def _walk(rows, keys, heads):
     return ps.lib().pserve_test_attn_walk((C.c_int32 * n)(*rows), (C.c_int32 * n)(*keys), n, heads)
 
 
-def test_one_to_six_hundred_units():
-    """Uneven items of every total, among them requests of which nothing is computed."""
+def test_one_to_six_hundred_tiles():
+    """Uneven items of every total of tiles, among them requests of which nothing is computed."""
     rng = random.Random(1)
     for total in range(0, 601):
         for _ in range(4):
@@ -41,3 +41,13 @@ def test_one_to_six_hundred_units():
                                              ([4096, 3072], [4096, 3072], 5), ([16384], [16384], 1)])
 def test_masks(rows, keys, heads):
     assert _walk(rows, keys, heads) == 0
+
+
+def test_large_totals():
+    """Many short items beside long ones, around and far above as many units as 512 shares of the shortest length."""
+    rng = random.Random(2)
+    for _ in range(300):
+        n = rng.randint(1, 40)
+        rows = [rng.choice([0, 1, 63, 64, 128, 129, 300, 1000, 4096]) for _ in range(n)]
+        keys = [rng.choice([1, 31, 32, 33, 64, 192, 256, 1000, 4096]) for _ in range(n)]
+        assert _walk(rows, keys, rng.choice([1, 2, 5, 10])) == 0, (rows, keys)

@@ -264,6 +264,9 @@ SHARES = {
     "d64_shared": dict(res=[(72, 41), (18, 23)], patch=(3, 1), C=320, heads=5, n=512),
     "d32_shared": dict(res=[(44, 48), (4, 3)], patch=(4, 3), C=320, heads=10, n=512),
     "d32_items": dict(res=[(32, 32)] * 5, patch=(8, 8), C=160, heads=5, n=0),
+    # many short items: a share holds the starts of several, and fewer shares than 512
+    "d64_small_requests": dict(res=[(32, 32)] + [(8, 8)] * 24, patch=(8, 8), C=256, heads=4, n=144),
+    "d32_small_requests": dict(res=[(48, 48)] + [(4, 6)] * 40, patch=(4, 6), C=320, heads=10, n=512),
     "d64_shared_mask": dict(res=[(64, 64), (8, 24)], patch=(8, 8), C=256, heads=4, reuse_p=0.4, n=512),
 }
 
@@ -282,7 +285,7 @@ def test_attention_in_shares(name):
         assert np.isfinite(err) and err < 1e-6, err
 
 
-# masks that leave 480, 24, 256, 512 units and none: fewer than the shares that the plan allows, as many
+# masks that leave 480, 24, 256, 512 tiles of keys and queries (and four units more an item) and none: fewer shares than the plan allows
 FEW_UNITS = {"480": dict(res=[(64, 64), (48, 64)], heads=5, computed=[(1, 2, 3)]), "24": dict(res=[(64, 64), (8, 24)], heads=4, computed=[(1, 0, 1)]),
              "256": dict(res=[(32, 64)] * 2, heads=4, computed=[(0, 3, 7)]), "512": dict(res=[(32, 64)] * 2, heads=4, computed=[(0, 0, 0), (1, 1, 1)]),
              "none": dict(res=[(32, 64)] * 2, heads=4, computed=[])}
