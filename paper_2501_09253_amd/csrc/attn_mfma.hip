@@ -981,16 +981,21 @@ attn_cross_kernel(AttnArgs a, int chunks) {
     }
 }
 
-// One block: per request slot, number of computed patches and of query tiles (exclusive prefixes).
+// One block: per request slot, number of computed patches and of query tiles (exclusive prefixes); UNITS: and units of the fp32 attention in
+// shares (a form of its own: their 64-bit sums cost every other masked call 1 us, 3.5 -> 4.5 with two requests).
+template <bool UNITS>
 __global__ void attn_tiles_kernel(const int32_t* __restrict__ request_offset, const uint8_t* __restrict__ mask, int32_t n,
                                   int32_t S, int32_t ATT_BQ, int32_t* __restrict__ act_off, int32_t* __restrict__ tile_off,
                                   int64_t* __restrict__ unit_off, const int32_t* __restrict__ cu_seqlens,
                                   const int32_t* __restrict__ seq_len, int32_t heads) {
     __shared__ int32_t s_cnt[1024], s_til[1024];
-    __shared__ int64_t s_unit[1024], c_unit;
+    __shared__ int64_t s_unit[UNITS ? 1024 : 1], c_unit;
     __shared__ int32_t c_cnt, c_til;
     const int tid = threadIdx.x;
-    if (tid == 0) { c_cnt = 0; c_til = 0; c_unit = 0; act_off[0] = 0; tile_off[0] = 0; if (unit_off) unit_off[0] = 0; }
+    if (tid == 0) {
+        c_cnt = 0; c_til = 0; act_off[0] = 0; tile_off[0] = 0;
+        if constexpr (UNITS) { c_unit = 0; unit_off[0] = 0; }
+    }
     __syncthreads();
     for (int base = 0; base < n; base += 1024) {
         const int s = base + tid;
@@ -1001,32 +1006,38 @@ __global__ void attn_tiles_kernel(const int32_t* __restrict__ request_offset, co
             if (mask) { for (int p = p0; p < p1; ++p) cnt += mask[p] == 0; }
             else cnt = p1 - p0;
             til = (cnt * S + ATT_BQ - 1) / ATT_BQ;
-            if (unit_off) {
+            if constexpr (UNITS) {
                 const int nk = seq_len ? seq_len[s] : cu_seqlens[s + 1] - cu_seqlens[s];
                 unit = (int64_t)((cnt * S + 127) / 128) * heads * (AT_START + (nk + 31) / 32);
             }
         }
         s_cnt[tid] = cnt;
         s_til[tid] = til;
-        s_unit[tid] = unit;
+        if constexpr (UNITS) s_unit[tid] = unit;
         __syncthreads();
         for (int off = 1; off < 1024; off <<= 1) {
             int x = 0, y = 0;
             int64_t z = 0;
-            if (tid >= off) { x = s_cnt[tid - off]; y = s_til[tid - off]; z = s_unit[tid - off]; }
+            if (tid >= off) {
+                x = s_cnt[tid - off]; y = s_til[tid - off];
+                if constexpr (UNITS) z = s_unit[tid - off];
+            }
             __syncthreads();
             s_cnt[tid] += x;
             s_til[tid] += y;
-            s_unit[tid] += z;
+            if constexpr (UNITS) s_unit[tid] += z;
             __syncthreads();
         }
         if (s < n) {
             act_off[s + 1] = c_cnt + s_cnt[tid];
             tile_off[s + 1] = c_til + s_til[tid];
-            if (unit_off) unit_off[s + 1] = c_unit + s_unit[tid];
+            if constexpr (UNITS) unit_off[s + 1] = c_unit + s_unit[tid];
         }
         __syncthreads();
-        if (tid == 1023) { c_cnt += s_cnt[tid]; c_til += s_til[tid]; c_unit += s_unit[tid]; }
+        if (tid == 1023) {
+            c_cnt += s_cnt[tid]; c_til += s_til[tid];
+            if constexpr (UNITS) c_unit += s_unit[tid];
+        }
         __syncthreads();
     }
 }
@@ -1034,7 +1045,8 @@ __global__ void attn_tiles_kernel(const int32_t* __restrict__ request_offset, co
 int attention_tiles(const int32_t* request_offset, const uint8_t* mask, int32_t n, int32_t S, int32_t qt, int32_t* act_off,
                     int32_t* tile_off, hipStream_t st, int64_t* unit_off, const int32_t* cu_seqlens, const int32_t* seq_len,
                     int32_t heads) {
-    attn_tiles_kernel<<<1, 1024, 0, st>>>(request_offset, mask, n, S, 128 * qt, act_off, tile_off, unit_off, cu_seqlens, seq_len, heads);
+    if (unit_off) attn_tiles_kernel<true><<<1, 1024, 0, st>>>(request_offset, mask, n, S, 128 * qt, act_off, tile_off, unit_off, cu_seqlens, seq_len, heads);
+    else attn_tiles_kernel<false><<<1, 1024, 0, st>>>(request_offset, mask, n, S, 128 * qt, act_off, tile_off, nullptr, nullptr, nullptr, 0);
     return check_launch("attn_tiles_kernel");
 }
 
