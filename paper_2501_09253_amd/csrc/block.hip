@@ -1249,7 +1249,7 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
             bool one = true;
             for (int k = 0; k < 4; ++k) one = one && gemm_takes_two(both(k), dt, mode);
             if (one) {
-                // Large enough for the wide tiles: every layer once over both streams, everything on the caller's stream
+                // Every layer once over both streams, whatever its tiles, everything on the caller's stream
                 // (as two kernels on two streams the text stream's few tiles took whole CUs from the image stream's
                 // rounds, and every fork and join cost ~10 us: 1.11 -> 1.04 ms for 11,520 + 616 tokens of 1536).
                 auto norm = [&](const void* in, int off) -> int {

@@ -2,7 +2,7 @@
 //
 // Two kernels share one epilogue:
 //   gemm_mfma_kernel  block tile 128 x 160 / 128 x 128 (GEGLU) with four wavefronts stacked along M or 128 x 128 / 128 x 64 (2 x 2), K in
-//                     steps of 64, A and B tiles staged by direct global -> LDS loads into a ring of two or three stages (one
+//                     steps of 64, A and B tiles staged by direct global -> LDS loads into a ring of two, three or four stages (one
 //                     barrier per step); the linear layers that neither gemm_few.hip nor gemm_wide.hip (asked first) takes, and
 //                     convolutions (taps re-load A): level changes, patches the other kernel does not take, and all others where
 //                     its rounds fit better (conv_choose).  The tiles with two stages run two blocks per CU.
@@ -86,8 +86,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmCore& a, f32x16 (&acc)[B
             rb_uniform = rb_slot == a.row_owner[t_last / a.geom.S];
         }
     }
-    // GroupNorm partial sums of the output (optional): column sums over this wavefront's 64 rows, which lie in one patch
-    const bool STATS = MAY_STAT && !GEGLU && a.stats != nullptr;     // only the convolution kernels leave the sums behind
+    // GroupNorm partial sums of the output (optional): column moments over this wavefront's WM rows (32 or 64), which lie in one patch
+    const bool STATS = MAY_STAT && !GEGLU && a.stats != nullptr;     // only convolutions leave them behind
     float* colsum = reinterpret_cast<float*>(smem) + WGM * WGN * (WM * EP_LD) + wave * (2 * WN + 2);    // [WN][2] + row count
     uint32_t row_ok[TM];                                            // bit e: row 8*(e/4) + 4*fh + e%4 of tile i exists
     const bool all_rows = STATS && w_tok[WM - 1] >= 0;              // existing rows are a prefix of the tile
@@ -157,7 +157,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmCore& a, f32x16 (&acc)[B
                 }
             }
             if (STATS) {
-                // column moments over the wavefront's 64 rows, around the value of the column's first row (shifted sums:
+                // column moments over the wavefront's WM rows, around the value of the column's first row (shifted sums:
                 // nothing is lost when the mean is far from zero); stored as (mean, M2) of the column
                 const float own0 = vals[0][0], oth0 = other_half_f(own0);
                 const float kc = fh == 0 ? own0 : oth0;             // both lane halves of a column use the lower half's value
@@ -253,7 +253,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmCore& a, f32x16 (&acc)[B
     }
     if (STATS) {
         __builtin_amdgcn_wave_barrier();
-        const int cg = a.N / a.stats_G;                             // channels per group (divides WN, see gemm_emits_stats)
+        const int cg = a.N / a.stats_G;                             // channels per group (divides WN, see gemm_stats_rows)
         const int tok0 = w_tok[0];
         if (lane < WN / cg && tok0 >= 0) {
             // the group's columns cover the same rows: mean of the column means, M2 by the merge formula
@@ -1020,7 +1020,7 @@ split_reduce_kernel(GemmArgs a, int splits, int m_pad, int W) {
 #pragma unroll
         for (int q = 0; q < 8; ++q) v[r][q] += bias[q] + (rb ? rb[q] : 0.f);
     }
-    if (a.stats) {                                  // all 64 rows exist and lie in one patch (gemm_emits_stats)
+    if (a.stats) {                                  // all 64 rows exist and lie in one patch (gemm_stats_rows)
         const int cg = a.N / a.stats_G, groups = W / cg;
         float mean[8];
 #pragma unroll
