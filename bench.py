@@ -30,7 +30,7 @@ EVENT_EVERY = 4                # the timed region brackets the dominant kernel i
 # each scaled by what the same counter reads for the 256 MiB calibration copy below; they are read from the committed
 # summary of those runs, which is named beside the number in the output.  Kernel label -> kernel name in the summary.
 PROFILE_KERNEL = {"conv3x3": "conv_mfma_kernel", "attn_self": "attn_pipe_kernel", "attn_cross": "attn_cross_kernel",
-                  "ffn_geglu": "gemm_mfma_kernel<128, 128, true", "gn_stats": "gn_partial_kernel"}
+                  "ffn_geglu": "gemm_wide_kernel<4, 2, 2, 4, 4", "gn_stats": "gn_partial_kernel"}
 
 
 def profiled_traffic(cfg_id, label):
