@@ -1036,6 +1036,10 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         const int64_t ctx_rows = (int64_t)plan->n * cache->cross_ld;
         gk.seg[0].ptr = cache->kc; gk.seg[0].ld = C;
         gk.seg[1].ptr = cache->vc; gk.seg[1].ld = cache->v_transposed ? ctx_rows : C; gk.seg[1].transposed = cache->v_transposed;
+        // Beside stages that fill the chip (200 tiles of 128 x 64): blocks with a CU's LDS for themselves keep theirs waiting, and the block waits for
+        // nothing but the last.  us of a block, such kernels / others: RES2T ... LFFN of 17,280 tokens x 1280, 12 x 154 text tokens 2,580 / 2,496; RES2 ... XATTN of
+        // 9 x 576 x 320, 9 x 154 182 / 178; 4,032 x 512, 10 x 77 205 / 197.  Beside less the shorter launch pays: 384 x 256, 77 86 / 94, 384 x 640 98 / 105.
+        gk.beside = s2 != st && cdiv(T, 128) * cdiv(C, 64) > 200;
         ProfScope ps("linear_ctx_kv", s2);
         return gemm(gk, dt, mode, s2);
     };

@@ -1236,7 +1236,7 @@ static double conv_time(const GemmArgs& a, int sel, int* splits) {
 //     convolution of 768 channels, 492, seven tenths 55.5 / 62.2 (all 77.0 / 72.5).
 static bool three_stages(const GemmArgs& a, int64_t t64) {
     const int64_t steps = (int64_t)a.taps * (a.K / 64);
-    if (a.act.active || ((a.rowscale || a.rowbias) && a.owner_rows < 64)) return false;
+    if (a.act.active || a.beside || ((a.rowscale || a.rowbias) && a.owner_rows < 64)) return false;
     if (a.conv) return steps >= 80 || (steps >= 32 && t64 >= 400);
     return steps > 32 || (steps == 32 && !a.rowscale && !a.rowbias && !a.seg[0].transposed && !a.seg[1].transposed && !a.seg[2].transposed);
 }
@@ -1263,7 +1263,7 @@ static int tile_pick(const GemmArgs& a, int* stages) {
         // tokens x 2,560, K = 2,048 38.7 / 32.6 (and 183.4 / 189.9 for the cross-attention around them); residual blocks of one
         // convolution, 4,400 tokens x 960 112 / 98, 4,000 x 1280 146 / 135, 8,000 x 640 85.5 / 83.5.  (Three: the same to 1 us; the
         // 128 x 64 tiles with six instead of three 29.6 / 30.7, 47.5 / 48.1.)
-        if (t160 <= 256) *stages = 4;
+        if (t160 <= 256 && !a.beside) *stages = 4;
         return 160;
     }
     // 128 x 128 tiles from where they do not fit one block a CU.  us, these / 256 x 128 (one block a CU) / 128 x 64: 306 tiles K = 384
@@ -1440,7 +1440,7 @@ int gemm_mfma_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
     double us;
     const bool conv = a.conv && a.epi == EPI_ROUTE;
     const ConvChoice c = conv ? conv_choose(a) : ConvChoice{0, 0, 1, {}};
-    const int few = a.B2 ? 0 : conv ? c.few : few_pick(a, a.epi == EPI_GEGLU ? 2 : 1, &us);
+    const int few = a.B2 || a.beside ? 0 : conv ? c.few : few_pick(a, a.epi == EPI_GEGLU ? 2 : 1, &us);
     if (few) {
         *handled = true;
         return gemm_few_bf16(a, few, st);

@@ -537,7 +537,8 @@ int gemm_wide_bf16(const GemmArgs& a, hipStream_t st, bool* handled) {
 
 // For tests (host only, no part of the ABI): the rows of the tile such a layer takes here, 0: another kernel's.  P patches of
 // S tokens; rows: those of the layer's patch list, rows2: of a second problem's, 0: none.  flags: 1 last segment transposed,
-// 2 residual, 4 gate, 8 GELU, 16 value-gate pairs, 32 rows without a patch list, 64 a mask.
+// 2 residual, 4 gate, 8 GELU, 16 value-gate pairs, 32 rows without a patch list, 64 a mask,
+// 128 beside another stream's kernels.
 static GemmArgs test_args(int32_t P, int32_t S, int32_t rows, int32_t rows2, int32_t N, int32_t K, int32_t seg_cols, int32_t flags) {
     GemmArgs a{};
     void* some = reinterpret_cast<void*>(64);           // tested for alignment, never read
@@ -551,6 +552,7 @@ static GemmArgs test_args(int32_t P, int32_t S, int32_t rows, int32_t rows2, int
     a.act_gelu = (flags & 8) != 0;
     a.epi = flags & 16 ? EPI_GEGLU : EPI_ROUTE;
     if (flags & 64) a.act.active = a.act.count = &list;
+    a.beside = (flags & 128) != 0;
     if (rows2) { a.B2 = some; a.M2 = rows2; a.act.active = a.act.count = a.act2.active = a.act2.count = &list; }
     return a;
 }
@@ -565,7 +567,8 @@ extern "C" int pserve_test_linear_kernel(int32_t P, int32_t S, int32_t rows, int
     GemmArgs a = test_args(P, S, rows, 0, N, K, seg_cols, flags);
     a.owner_rows = owner_rows;
     double us;
-    if (const int few = few_pick(a, a.epi == EPI_GEGLU ? 2 : 1, &us)) return -few;
+    const int few = a.beside ? 0 : few_pick(a, a.epi == EPI_GEGLU ? 2 : 1, &us);
+    if (few) return -few;
     if (const int r = wide_select(a)) return r;
     return a.epi == EPI_GEGLU ? (N % 128 == 0 ? 1282 : 0) : gemm_tile_code(a);
 }

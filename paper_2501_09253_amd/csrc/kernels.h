@@ -202,6 +202,7 @@ struct GemmArgs : GemmCore {
     // fp32: A is in bf16 pieces (gemm_takes_pieces) / the output is written in pieces
     int32_t a_pieces, out_pieces;
     int32_t owner_rows;        // with rowbias / rowscale: the rows of every request start at a multiple of this (1, 2, .. 64; 0: not known)
+    int32_t beside;            // runs beside kernels of another stream that fill the chip: no kernel whose blocks want a CU's LDS for themselves
 };
 // Rows of A a problem can address: where rows are tokens, any token of the batch, however few patches its list has (the two
 // lists of a joint batch lie interleaved in one token matrix).

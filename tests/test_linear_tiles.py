@@ -33,3 +33,12 @@ def test_three_stages_or_narrow_tiles(steps, flags, owner_rows, kernel):
     S, rows, N = 16, 2400, 1152
     seg = N // 2 if flags & LAST_TRANSPOSED else N
     assert ps.lib().pserve_test_linear_kernel(rows // S, S, rows, N, 64 * steps, seg, flags, owner_rows) == kernel
+
+
+# Text keys and values beside kernels of another stream that fill the chip: no blocks with a CU's LDS for themselves (four stages, the larger
+# tiles that share K, three stages of 128 x 128)
+@pytest.mark.parametrize("rows,N,K,alone,beside", [(22 * 77, 2560, 2048, 1604, 1602), (9 * 154, 640, 768, -4, 643), (18 * 160, 1280, 2304, 1283, 643)])
+def test_beside_another_stream(rows, N, K, alone, beside):
+    PLAIN_ROWS, BESIDE = 32, 128
+    kernel = lambda flags: ps.lib().pserve_test_linear_kernel(1, 64, rows, N, K, N // 2, LAST_TRANSPOSED + PLAIN_ROWS + flags, 64)
+    assert (kernel(0), kernel(BESIDE)) == (alone, beside)
