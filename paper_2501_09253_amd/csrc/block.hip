@@ -674,7 +674,7 @@ static int cache_create_impl(const pserve_plan_t* plan, const pserve_block_t* bl
     }
     auto elem = [&](bool pieces) -> size_t { return pieces ? 6 : es; };
     if (conv) {
-        c->split_ws_bytes = conv_split_bytes(g, (int32_t)plan->T, d.C, d.C, d.dtype, g_kernel_mode == 1 ? 1 : 0);
+        c->split_ws_bytes = conv_split_bytes(g, (int32_t)plan->T, d.C, d.C, d.G, d.dtype, g_kernel_mode == 1 ? 1 : 0);
         if (c->split_ws_bytes) PS_TRY(c->pool.alloc((void**)&c->split_ws, c->split_ws_bytes));
     }
     if (conv) PS_TRY(c->pool.alloc(&c->apad, (size_t)plan->P * (plan->ph + 2) * (plan->pw + 2) * d.C * elem(c->apad_pieces)));
@@ -1020,8 +1020,9 @@ int pserve_block_forward_temb(const pserve_plan_t* plan, const void* x, const vo
         if (stats_next && !reuse_mask) {
             // (with a mask the reused patches keep cached activations this convolution never sees: gn_stats reads them)
             g.stats_G = d.G;
+            g.moments_us = gn_takes_direct(ga, gm, dt) ? 0.f : MOMENTS_US;
             if (const int rows = gemm_stats_rows(g, dt, mode)) { g.stats = cache->partial; g.stats_slots = partials = plan->S / rows; }
-            else g.stats_G = 0;
+            else { g.stats_G = 0; g.moments_us = 0.f; }
         }
         if (rowbias_ready) PS_CHECK_HIP(hipStreamWaitEvent(st, rowbias_ready, 0));   // produced on the side stream
         ProfScope ps("conv3x3", st);

@@ -427,8 +427,8 @@ static int launch_few(const GemmArgs& a, hipStream_t st) {
 
 // Which tile a problem would take here (0: none) and how long it would run, in us: a round of 256 tiles (32 x 32: 512, two
 // blocks a CU, each then slower) is a fixed time, of which 4 are launch, tables and end, and a time per K step, fitted to 160
-// measured sizes (within 10 %).  Linear layers and convolutions that conv_mfma_kernel does not take only where it is one round:
-// with two, the 128 x 64 tiles win (1,280 x 1,280, K = 1,280 13.4 against 17.7); value-gate pairs with two (768 x 2,560, K = 960
+// measured sizes (within 10 %).  Linear layers and convolutions that conv_mfma_kernel takes too only where it is one round: with two, the 128-row tiles win (1,280 x
+// 1,280, K = 1,280 13.4 against 17.7; RES2 of 4,096 x 512 93 against 102, 4,608 x 320 64.5 against 66.7); value-gate pairs with two (768 x 2,560, K = 960
 // 12.9 against 19.9, K = 320 8.9 against 12.2; three rounds 18.0 against 20.2 and 12.5 against 12.4).
 static const struct { int bm, bn; double fixed, step; } FEW[] = {{0, 0, 0, 0},        {32, 32, 4.0, 0.083}, {32, 64, 4.4, 0.125},
                                                                  {32, 80, 5.0, 0.145}, {64, 64, 4.9, 0.18},  {64, 80, 5.8, 0.205}};

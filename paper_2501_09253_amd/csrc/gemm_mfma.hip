@@ -1217,8 +1217,11 @@ static double conv_time(const GemmArgs& a, int sel, int* splits) {
     static const double step[7] = {0, 0.95, 0.95, 0.93, 0.6, 0.49, 0.95};
     const int64_t tiles = cdiv(a.M, CONV_BM[sel]) * (a.N / CONV_BN[sel]), chunks = a.K / 64, rounds = cdiv(tiles, 256);
     const int z = conv_splits(tiles, chunks);
+    // (a shared tile's blocks go to the XCDs by column tile and share, all row tiles of one to the same 32 CUs: 3,072 x 640, 48 tiles x 5
+    // 48.7 + 11.7 us, 4,096 x 640, 64 x 4 39.6 + 12)
+    const int64_t xcd_rounds = cdiv(cdiv(a.N / CONV_BN[sel] * z, 8) * cdiv(a.M, CONV_BM[sel]), 32);
     const double whole = CONV_BM[sel] == 256 ? rounds * 12.0 + 9 * chunks * (0.6 * rounds + 0.42 * tiles / 256) : rounds * (5.0 + 9 * chunks * step[sel]);
-    const double shared = 11.0 + 9 * cdiv(chunks, z) * step[sel] + 1.5e-6 * z * (double)a.M * a.N;
+    const double shared = 11.0 + 9 * cdiv(chunks, z) * step[sel] * xcd_rounds + 1.5e-6 * z * (double)a.M * a.N;
     *splits = z > 1 && shared < whole ? z : 1;
     return *splits > 1 ? shared : whole;
 }
@@ -1299,36 +1302,52 @@ static double tile_time(const GemmArgs& args) {
 }
 
 // The kernel a convolution takes: the small tiles of gemm_few.hip (few: which), the halo in LDS (sel, its tile, its shares) or, with
-// neither, gemm_mfma_kernel.  The first are ahead while a few rounds of them do; the second with many channels, where the nine
+// neither, gemm_mfma_kernel.  The first are ahead while one round of them does; the second with many channels, where the nine
 // reads of a pixel are long; the last has two blocks a CU and a round of 512 tiles, so it wastes less of one.  By the three models,
 // the last only where it is clearly ahead.  us of one 3x3 convolution, 16 x 16 patches, few or halo / gemm_mfma_kernel:
-//   1,024 tokens x 320 channels 9.9 / 23.9;  4,096 x 640 52.6 / 54.2;  9,216 x 256 31.6 / 26.9, 16,384 38.9 / 29.6, 36,864 79.5 / 61.7;
+//   1,024 tokens x 320 channels 9.9 / 23.9;  4,096 x 640 51.5 / 54.2;  9,216 x 256 31.6 / 26.9, 16,384 38.9 / 29.6, 36,864 79.5 / 61.7;
 //   36,864 x 64 17.3 / 13.4, x 128 33.9 / 25.1, x 192 65.3 / 43.7, x 384 153 / 123, x 512 215 / 202, x 768 422 / 408;
 //   12,288 x 320 44.4 / 35.0, 16,384 48.5 / 41.6, 24,576 53.1 / 59.3, 36,864 100 / 90; 16,384 x 640 107 / 129, 36,864 283 / 287;
 //   6,144 x 960 122 / 144; 2,048 x 1280 71 / 101, 12,288 345 / 356.  Patches the halo does not take, two layers with their norms:
 //   2,304 x 960 154 / 185.
 // Small tiles up to 1,024 channels where the halo is the other choice: above, the weights (more than 29 MB) come from HBM in a whole
 // network, and the longer chain waits for them (1,024 x 1,280 41 / 46, with cold weights 52 / 48).
+// Moments of the output that one of the two leaves behind are worth moments_us: 9,216 tokens x 64 channels, two layers, few / halo 43.6 / 41.2 us
+// (few for the second alone: 38).
 struct ConvChoice {
     int sel, few, splits;
     ConvTile ct;
 };
+// rows of a partial sum that the halo kernel (sel) or gemm_mfma_kernel (0) leaves behind, 0: none
+static int moment_rows(const GemmArgs& a, int sel) {
+    if (a.stats_G <= 0 || a.act.active || a.N % a.stats_G != 0) return 0;
+    // a wavefront's rows must lie in one patch, and its columns must hold whole groups
+    static constexpr int cols[7] = {0, 160, 160, 128, 64, 32, 160};
+    int stages;
+    const int bn = sel ? 0 : tile_pick(a, &stages);
+    if (!sel && !bn) return 0;
+    const int rows = sel || bn != 160 ? 64 : 32, wc = sel ? cols[sel] : bn == 160 ? 160 : bn / 2;
+    return a.geom.S % rows == 0 && wc % (a.N / a.stats_G) == 0 ? rows : 0;
+}
 static ConvChoice conv_choose(const GemmArgs& a) {
     ConvChoice c{0, 0, 1, {}};
     double few = 1e30;
+    // (gemm_mfma_kernel's end is longer for it: 36.0 -> 39.4 us at 3,456 x 512, 91.8 -> 95.7 at 36,864 x 320)
+    auto spared = [&](int sel) { return a.moments_us > 0 && moment_rows(a, sel) ? (sel ? 1.0 : 0.7) * a.moments_us : 0.0; };
     c.sel = conv_select(a, &c.ct);
-    if (!c.sel) {           // one round of small tiles; more only for plain convolutions
-        c.few = few_pick(a, 1, &few);
+    c.few = few_pick(a, 1, &few);
+    const double tile = tile_time(a) - spared(0);
+    if (!c.sel) {           // more than one round only for plain convolutions
         if (!c.few && a.K <= 1024 && a.taps == 9 && a.a_mul <= 1) {
             c.few = few_pick(a, 4, &few);
-            if (few > 0.95 * tile_time(a)) c.few = 0;
+            if (few > 0.95 * tile) c.few = 0;
         }
+        if (spared(0) > 0 && few > tile) c.few = 0;
         return c;
     }
-    const double halo = conv_time(a, c.sel, &c.splits);
-    if (a.K <= 1024) c.few = few_pick(a, 4, &few);
-    if (few >= halo) c.few = 0;
-    if (tile_time(a) < (c.few ? 0.9 * few : c.sel == 4 || c.sel == 5 ? halo : 0.95 * halo)) c.few = c.sel = 0;
+    const double halo = conv_time(a, c.sel, &c.splits) - spared(c.sel);
+    if (a.K > 1024 || few >= halo) c.few = 0;
+    if (tile < (c.few ? 0.95 * few : c.sel == 4 || c.sel == 5 ? halo : 0.95 * halo)) c.few = c.sel = 0;
     if (c.few) c.sel = 0;
     return c;
 }
@@ -1336,14 +1355,7 @@ static ConvChoice conv_choose(const GemmArgs& a) {
 int gemm_stats_rows(const GemmArgs& a, int dtype, int mode) {
     if (mode != 0 || dtype != PSERVE_BF16 || !a.conv || a.epi != EPI_ROUTE || a.taps != 9 || a.stats_G <= 0 || !gemm_mfma_eligible(a)) return 0;
     const ConvChoice c = conv_choose(a);
-    if (c.few || a.act.active || a.N % a.stats_G != 0) return 0;
-    // a wavefront's rows must lie in one patch, and its columns must hold whole groups
-    static constexpr int cols[7] = {0, 160, 160, 128, 64, 32, 160};
-    int stages;
-    const int bn = c.sel ? 0 : tile_pick(a, &stages);
-    if (!c.sel && !bn) return 0;
-    const int rows = c.sel || bn != 160 ? 64 : 32, wc = c.sel ? cols[c.sel] : bn == 160 ? 160 : bn / 2;
-    return a.geom.S % rows == 0 && wc % (a.N / a.stats_G) == 0 ? rows : 0;
+    return c.few || (!c.sel && a.moments_us <= 0) ? 0 : moment_rows(a, c.sel);       // (gn_direct_kernel costs less than moments from there)
 }
 
 static GemmArgs conv_args(const PatchGeom& g, int32_t M, int32_t N, int32_t K) {
@@ -1352,11 +1364,17 @@ static GemmArgs conv_args(const PatchGeom& g, int32_t M, int32_t N, int32_t K) {
     for (auto& s : a.seg) s.scale = 1.f;
     return a;
 }
-size_t conv_split_bytes(const PatchGeom& g, int32_t M, int32_t N, int32_t K, int dtype, int mode) {
+size_t conv_split_bytes(const PatchGeom& g, int32_t M, int32_t N, int32_t K, int32_t G, int dtype, int mode) {
     if (dtype != PSERVE_BF16 || mode != 0 || K % 64 != 0) return 0;
-    const GemmArgs a = conv_args(g, M, N, K);
-    const ConvChoice c = conv_choose(a);
-    return c.sel && c.splits > 1 ? sizeof(float) * c.splits * cdiv(M, CONV_BM[c.sel]) * CONV_BM[c.sel] * (size_t)N : 0;
+    GemmArgs a = conv_args(g, M, N, K);
+    a.stats_G = G;
+    size_t most = 0;
+    for (const float us : {0.f, MOMENTS_US}) {          // whether somebody reads the output's moments or not
+        a.moments_us = us;
+        const ConvChoice c = conv_choose(a);
+        if (c.sel && c.splits > 1) most = std::max(most, sizeof(float) * c.splits * cdiv(M, CONV_BM[c.sel]) * CONV_BM[c.sel] * (size_t)N);
+    }
+    return most;
 }
 
 // For tests (host only, no part of the ABI): 1 if the 3x3 convolutions of such a batch (bf16, C to C channels) have few enough
@@ -1366,22 +1384,25 @@ extern "C" int pserve_test_conv_shares(int32_t P, int32_t ph, int32_t pw, int32_
     const int sel = conv_select(conv_args(PatchGeom{P, ph * pw, ph, pw, pw + 2, (ph + 2) * (pw + 2)}, P * ph * pw, C, C), &ct);
     return sel && conv_splits(cdiv((int64_t)P * ph * pw, CONV_BM[sel]) * (C / CONV_BN[sel]), C / 64) > 1;
 }
-// How such a convolution runs: 0 the small tiles, 1 the halo in LDS, 2 the linear layers' tiles; + 10 x the rows of its output's moments
-// (32 groups).
+// How such a convolution runs where somebody reads its output's moments (32 groups): 0 the small tiles, 1 the halo in LDS, 2 the linear
+// layers' tiles; + 10 x the rows of the moments.
 extern "C" int pserve_test_conv_kernel(int32_t P, int32_t ph, int32_t pw, int32_t C) {
     GemmArgs a = conv_args(PatchGeom{P, ph * pw, ph, pw, pw + 2, (ph + 2) * (pw + 2)}, P * ph * pw, C, C);
     a.stats_G = 32;
+    a.moments_us = MOMENTS_US;
     const ConvChoice c = conv_choose(a);
     return (c.few ? 0 : c.sel ? 1 : 2) + 10 * gemm_stats_rows(a, PSERVE_BF16, 0);
 }
 // 10 x columns + stages of the last
 int gemm_tile_code(const GemmArgs& a);
 extern "C" int pserve_test_conv_tile(int32_t P, int32_t ph, int32_t pw, int32_t C) {
-    const GemmArgs a = conv_args(PatchGeom{P, ph * pw, ph, pw, pw + 2, (ph + 2) * (pw + 2)}, P * ph * pw, C, C);
+    GemmArgs a = conv_args(PatchGeom{P, ph * pw, ph, pw, pw + 2, (ph + 2) * (pw + 2)}, P * ph * pw, C, C);
+    a.stats_G = 32;
+    a.moments_us = MOMENTS_US;
     const ConvChoice c = conv_choose(a);
     return c.few || c.sel ? 0 : gemm_tile_code(a);
 }
-// The tile of gemm_few.hip that such a convolution takes instead (1 .. 5: 32 x 32, 32 x 64, 32 x 80, 64 x 64, 64 x 80), 0: none; linear:
+// The tile of gemm_few.hip that such a convolution, without moments, takes (1 .. 5: 32 x 32, 32 x 64, 32 x 80, 64 x 64, 64 x 80), 0: none; linear:
 // that of a linear layer of P * ph * pw rows, K = C, N columns in segments of seg_cols (value-gate pairs: seg_cols = 0).
 extern "C" int pserve_test_few_tile(int32_t P, int32_t ph, int32_t pw, int32_t C, int32_t linear, int32_t N, int32_t seg_cols) {
     GemmArgs a = conv_args(PatchGeom{P, ph * pw, ph, pw, pw + 2, (ph + 2) * (pw + 2)}, P * ph * pw, C, C);

@@ -105,6 +105,8 @@ struct GroupNormArgs {
     const uint8_t* rim_only = nullptr;   // [P] or nullptr; apply pass into the padded layout: only the border tokens of these patches
 };
 int gn_stats(const GroupNormArgs& a, const PatchGeom& g, int dtype, hipStream_t st);
+// true if that is one launch, about as long as gn_finalize alone
+bool gn_takes_direct(const GroupNormArgs& a, const PatchGeom& g, int dtype);
 // statistics and application of a small batch (gn_takes_whole) in one launch: conv: SiLU into the padded buffer with the rims,
 // else plain rows; all patches, no pieces
 bool gn_takes_whole(const GroupNormArgs& a, const PatchGeom& g, int dtype, bool conv);
@@ -203,6 +205,7 @@ struct GemmArgs : GemmCore {
     int32_t a_pieces, out_pieces;
     int32_t owner_rows;        // with rowbias / rowscale: the rows of every request start at a multiple of this (1, 2, .. 64; 0: not known)
     int32_t beside;            // runs beside kernels of another stream that fill the chip: no kernel whose blocks want a CU's LDS for themselves
+    float moments_us;          // conv with stats_G: what the output's moments spare its norm (0: nothing)
 };
 // Rows of A a problem can address: where rows are tokens, any token of the batch, however few patches its list has (the two
 // lists of a joint batch lie interleaved in one token matrix).
@@ -221,7 +224,8 @@ bool gemm_takes_halo(const GemmArgs& a, int dtype, int mode);
 // true if gemm(a, ...) is faster with its activations in bf16 pieces (a.a_pieces, which the caller then sets)
 bool gemm_takes_pieces(const GemmArgs& a, int dtype, int mode);
 // scratch a 3x3 convolution of M rows, N output and K input channels over this patch geometry can use (0: none)
-size_t conv_split_bytes(const PatchGeom& g, int32_t M, int32_t N, int32_t K, int dtype, int mode);
+constexpr float MOMENTS_US = 6.f;      // gn_partial_kernel, 4.5 us at 9,216 tokens x 64 to 8 at 4,096 x 640
+size_t conv_split_bytes(const PatchGeom& g, int32_t M, int32_t N, int32_t K, int32_t G, int dtype, int mode);
 // tokens a partial sum of a.stats covers where gemm(a, ...), with a.stats_G groups, takes a kernel that fills it, else 0 (the caller then
 // runs gn_stats on the output)
 int gemm_stats_rows(const GemmArgs& a, int dtype, int mode);

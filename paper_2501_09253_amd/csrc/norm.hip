@@ -680,7 +680,7 @@ static int norm_layout(int32_t C, int dtype, int* CV, int* TL) {
     return PSERVE_OK;
 }
 
-static bool gn_takes_direct(const GroupNormArgs& a, const PatchGeom& g, int dtype) {
+bool gn_takes_direct(const GroupNormArgs& a, const PatchGeom& g, int dtype) {
     // One launch for small requests: a block reads its request's tokens in pieces of C / G channels, so its time grows with
     // its elements and, past an L2's 4 MB, with the lines shared between groups.  us, two launches -> one:
     // G = 32 at 1,024 tokens, 1 .. 24 requests of 64 .. 1280 channels: 6.2 .. 27 -> 3.4 .. 20, always faster; at 2,048, 6

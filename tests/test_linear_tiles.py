@@ -42,3 +42,13 @@ def test_beside_another_stream(rows, N, K, alone, beside):
     PLAIN_ROWS, BESIDE = 32, 128
     kernel = lambda flags: ps.lib().pserve_test_linear_kernel(1, 64, rows, N, K, N // 2, LAST_TRANSPOSED + PLAIN_ROWS + flags, 64)
     assert (kernel(0), kernel(BESIDE)) == (alone, beside)
+
+
+# 3x3 convolutions: the small tiles (1 .. 5) that one without moments takes; 0 small tiles, 1 the halo in LDS, 2 128-row tiles (+ 10 x the
+# rows of a sum) of one whose moments spare the next norm a launch.  Sizes where the small tiles take one round and two; where moments decide;
+# where an XCD would get more shares of tiles than it has CUs; patches that the halo kernel does not take.
+@pytest.mark.parametrize("P,ph,pw,C,few,kernel", [(16, 16, 16, 320, 5, 0), (4, 32, 32, 512, 0, 642), (9, 32, 32, 64, 4, 641), (12, 16, 16, 640, 0, 2),
+                                                  (16, 16, 16, 640, 0, 641), (9, 16, 16, 384, 4, 0), (16, 12, 12, 960, 5, 0)])
+def test_convolutions(P, ph, pw, C, few, kernel):
+    lib = ps.lib()
+    assert (lib.pserve_test_few_tile(P, ph, pw, C, 0, 0, 0), lib.pserve_test_conv_kernel(P, ph, pw, C)) == (few, kernel)
