@@ -1312,6 +1312,8 @@ static double tile_time(const GemmArgs& args) {
 //   2,304 x 960 154 / 185.
 // Small tiles up to 1,024 channels where the halo is the other choice: above, the weights (more than 29 MB) come from HBM in a whole
 // network, and the longer chain waits for them (1,024 x 1,280 41 / 46, with cold weights 52 / 48).
+// With a mask the rows are a bound: more than one round of small tiles then (4,096 x 512, three fifths reused, RES2 + SATTN 145 / 172 us with
+// the 128-row tiles).
 // Moments of the output that one of the two leaves behind are worth moments_us: 9,216 tokens x 64 channels, two layers, few / halo 43.6 / 41.2 us
 // (few for the second alone: 38).
 struct ConvChoice {
@@ -1337,6 +1339,8 @@ static ConvChoice conv_choose(const GemmArgs& a) {
     c.sel = conv_select(a, &c.ct);
     c.few = few_pick(a, 1, &few);
     const double tile = tile_time(a) - spared(0);
+    const bool mask = a.act.active != nullptr;
+    if (mask && c.sel && !c.few && a.K <= 1024) c.few = few_pick(a, 4, &few);
     if (!c.sel) {           // more than one round only for plain convolutions
         if (!c.few && a.K <= 1024 && a.taps == 9 && a.a_mul <= 1) {
             c.few = few_pick(a, 4, &few);
@@ -1347,7 +1351,7 @@ static ConvChoice conv_choose(const GemmArgs& a) {
     }
     const double halo = conv_time(a, c.sel, &c.splits) - spared(c.sel);
     if (a.K > 1024 || few >= halo) c.few = 0;
-    if (tile < (c.few ? 0.95 * few : c.sel == 4 || c.sel == 5 ? halo : 0.95 * halo)) c.few = c.sel = 0;
+    if (tile < (c.few ? (mask ? 0.9 : 0.95) * few : c.sel == 4 || c.sel == 5 ? halo : 0.95 * halo)) c.few = c.sel = 0;
     if (c.few) c.sel = 0;
     return c;
 }

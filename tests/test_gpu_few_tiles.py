@@ -58,6 +58,7 @@ CASES = {
     "conv_t64x80": dict(res=[(64, 60)], patch=(16, 20), C=320, stages=("RES2",), tiles=dict(conv=T64x80)),
     "conv_t32x80": dict(res=[(32, 32)], patch=(32, 32), C=640, stages=("RES2",), tiles=dict(conv=T32x80)),
     "conv_rounds": dict(res=[(96, 64)], patch=(16, 16), C=256, stages=("RES2",), tiles=dict(conv=0)),       # (more than one of them)
+    "conv_rounds_masked": dict(res=[(64, 64)], patch=(16, 16), C=512, stages=("RES2",), reuse_p=0.6, tiles=dict(conv=0)),     # (0 without a mask)
     # what is left to tiles shared between blocks: a mask and a time embedding there
     "shared_masked": dict(res=[(16, 32), (16, 16)], patch=(8, 8), C=1280, stages=("RES2T",), reuse_p=0.4, temb_dim=40, tiles=dict(conv=0)),
 }
