@@ -1235,12 +1235,14 @@ static double conv_time(const GemmArgs& a, int sel, int* splits) {
 //     4,608 50.5 / 52.1 (in a block 51.6 / 57.1), 6,144 66.2 / 62.7.
 //   3x3 convolutions  256 channels 25.7 / 26.5, 26.6 / 27.0, 27.1 / 27.3 (400), 29.4 / 28.7;  384 34.2 / 34.9, 35.2 / 35.5, 36.4 / 35.9, 40.2 / 38.0;
 //     512 42.4 / 43.2, 43.9 / 43.8, 45.8 / 44.2, 50.5 / 47.1;  640 53.6 / 51.5, 56.9 / 52.2, 56.1 / 52.7, 62.3 / 57.2.
+//   2x upsampling (four taps), the level around it, 280 / 320 narrow tiles: 640 channels 47.7 / 46.3, 48.9 / 47.3;  768, 288 / 336 56.3 / 54.2,
+//     55.8 / 54.3.
 //   With a mask t64 is only a bound: a linear layer, 360 narrow tiles, a third of the patches computed, K = 2,560 20.7 / 27.4; a 3x3
 //     convolution of 768 channels, 492, seven tenths 55.5 / 62.2 (all 77.0 / 72.5).
 static bool three_stages(const GemmArgs& a, int64_t t64) {
     const int64_t steps = (int64_t)a.taps * (a.K / 64);
     if (a.act.active || a.beside || ((a.rowscale || a.rowbias) && a.owner_rows < 64)) return false;
-    if (a.conv) return steps >= 80 || (steps >= 32 && t64 >= 400);
+    if (a.conv && a.taps == 9) return steps >= 80 || (steps >= 32 && t64 >= 400);
     return steps > 32 || (steps == 32 && !a.rowscale && !a.rowbias && !a.seg[0].transposed && !a.seg[1].transposed && !a.seg[2].transposed);
 }
 

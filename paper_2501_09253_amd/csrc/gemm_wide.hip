@@ -561,11 +561,15 @@ extern "C" int pserve_test_linear_tile(int32_t P, int32_t S, int32_t rows, int32
     return wide_select(test_args(P, S, rows, rows2, N, K, seg_cols, flags));
 }
 // The kernel of such a layer: -1 .. -5 a small tile (gemm_few.hip), 256 or 320 rows of a tile here, 10 x columns + stages of a 128-row one.
-// owner_rows: GemmArgs.
+// owner_rows: GemmArgs.  flags & 256: a 2x upsampling of K channels.
 int gemm_tile_code(const GemmArgs& a);
 extern "C" int pserve_test_linear_kernel(int32_t P, int32_t S, int32_t rows, int32_t N, int32_t K, int32_t seg_cols, int32_t flags, int32_t owner_rows) {
     GemmArgs a = test_args(P, S, rows, 0, N, K, seg_cols, flags);
     a.owner_rows = owner_rows;
+    if (flags & 256) {
+        a.conv = 1; a.taps = a.classes = 4;
+        return gemm_tile_code(a);
+    }
     double us;
     const int few = a.beside ? 0 : few_pick(a, a.epi == EPI_GEGLU ? 2 : 1, &us);
     if (few) return -few;

@@ -35,6 +35,12 @@ def test_three_stages_or_narrow_tiles(steps, flags, owner_rows, kernel):
     assert ps.lib().pserve_test_linear_kernel(rows // S, S, rows, N, 64 * steps, seg, flags, owner_rows) == kernel
 
 
+# 2x upsampling: four taps a channel
+@pytest.mark.parametrize("rows,C,kernel", [(1024, 640, WIDE_3), (864, 640, WIDE_3), (768, 768, WIDE_3), (768, 448, NARROW), (640, 384, NARROW)])
+def test_upsampling(rows, C, kernel):
+    assert ps.lib().pserve_test_linear_kernel(1, 64, rows, C, C, C, 256, 64) == kernel
+
+
 # Text keys and values beside kernels of another stream that fill the chip: no blocks with a CU's LDS for themselves (four stages, the larger
 # tiles that share K, three stages of 128 x 128)
 @pytest.mark.parametrize("rows,N,K,alone,beside", [(22 * 77, 2560, 2048, 1604, 1602), (9 * 154, 640, 768, -4, 643), (18 * 160, 1280, 2304, 1283, 643)])
