@@ -378,7 +378,7 @@ extern "C" int pserve_test_attn_transposed(const pserve_plan_t* plan, const void
 // most of its ~270 vector instructions), then the output products; keys and values have rings of three stages of their own,
 // filled two steps ahead.  The softmax reference moves only when a score passes it by 8 (a factor of 256 costs fp32 nothing).
 // Requests of 4,096 and 3,072 tokens, 5 heads of 64 (280 items of 128 and 96 tiles): 360 (fp32 kernel) -> 234 us, a block an item ->
-// 189 + 13 us, 512 shares (145 -> 166 TFLOP/s of fp32).  Bound by the issue of MFMAs (1,536 of 2,770 clocks a tile) and vector
+// 173 + 15 us, 512 shares and no spilled register in the loop (143 -> 178 TFLOP/s of fp32).  Bound by the issue of MFMAs (1,536 of 2,770 clocks a tile) and vector
 // instructions, with every CU busy by the clock (2.15 GHz with 160 CUs busy, 1.8 with all).
 constexpr int ASP_NS = 3;
 constexpr float AT_LOWEST = -3.402823466e38f;       // the softmax reference in front of the first key
